@@ -98,7 +98,7 @@ def draw(rng):
                     store_chunks=requests * chunks if own else max(chunks, 48), page=page, ratio=ratio)
     if kind == "stack":
         ctx = _spread(rng, 512, 16384)
-        return dict(kind=kind, **GQA4, half_layout=half, layers=rng.randint(1, 2), hidden=4096, ffn=14336, chunks=max(1, ctx // 1000), ctx=ctx,
+        return dict(kind=kind, **GQA4, half_layout=False, layers=rng.randint(1, 2), hidden=4096, ffn=14336, chunks=max(1, ctx // 1000), ctx=ctx,
                     question=_spread(rng, 16, 512), ratio=min(ratio, 0.15), select=rng.random() < 0.5)
     ctx = _spread(rng, 1024, 16384)
     return dict(kind=kind, **rng.choice([GQA4, GQA7]), half_layout=half, layers=rng.randint(2, 32), chunks=max(1, ctx // 1000), ctx=ctx,
