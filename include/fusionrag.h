@@ -243,9 +243,9 @@ fr_status fr_sparse_prefill_attn_writeback(fr_ctx* ctx, const void* q_rows, cons
  *   chunk_store_row0, chunk_src_pos0   host [n_chunks]
  *   L                  prompt length; every position in [L_ctx, L) must be listed in q_index
  *   q_rows, q_index, R, k_new, v_new (both required), out, lse_out: as in fr_sparse_prefill_attn
- * Errors as fr_sparse_prefill_attn, plus FR_ERR_INVALID_ARG for chunk rows outside the store.  Contexts the tiled
- * kernels do not take (fp32, head_dim 64, group sizes other than 1, 2, 4, 8) gather the query's shifted keys and its
- * values into the context's workspace (2 x max_tokens rows, part of fr_workspace_bytes) and run the generic kernel. */
+ * Errors as fr_sparse_prefill_attn, plus FR_ERR_INVALID_ARG for chunk rows outside the store.  Contexts whose
+ * kernels do not read a store (fp32, head_dim 64, group sizes other than 1, 2, 4, 8) gather the query's shifted keys and its
+ * values into the context's workspace (2 x max_tokens rows, part of fr_workspace_bytes) first. */
 fr_status fr_sparse_prefill_attn_shared(fr_ctx* ctx, const void* q_rows, const int32_t* q_index, int32_t R,
                                         const void* k_store, const void* v_store, int64_t n_store_rows,
                                         const int32_t* chunk_offsets, const int32_t* chunk_store_row0,
@@ -263,7 +263,7 @@ fr_status fr_sparse_prefill_attn_shared(fr_ctx* ctx, const void* q_rows, const i
  *              query); owned by the caller, contents undefined afterwards, must stay untouched until the call's
  *              work on the stream has finished
  * Every query is validated before the first launch.  Errors as fr_sparse_prefill_attn_shared (the message names
- * the query), plus FR_ERR_WORKSPACE when workspace_bytes is too small.  Contexts served by the generic kernel run
+ * the query), plus FR_ERR_WORKSPACE when workspace_bytes is too small.  Contexts whose kernels do not read a store run
  * the queries one after the other from the context's own workspace: fr_shared_batch_workspace_bytes is 0 for them
  * and workspace may be NULL. */
 typedef struct {

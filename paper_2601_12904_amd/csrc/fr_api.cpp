@@ -146,20 +146,21 @@ fr_status fr_create(const fr_layer_desc* desc, int64_t max_tokens, int32_t max_c
         return FR_ERR_DEVICE;
     }
     w.n_cu = prop.multiProcessorCount;
-    w.attn_flags_elems = (size_t)(max_tokens / 32 + 1) * s.Hkv;   // one per (row tile of >= 32 rows, KV head)
+    const bool tiled = attn_mfma_supported(s);
+    w.attn_flags_elems = tiled ? attn_mfma_flags_elems(s, max_tokens) : 0;
     const size_t o_flags = take(w.attn_flags_elems * 4);
-    w.kv_images_bytes = (s.dtype == FR_BF16 && s.d == 128) ? (size_t)((max_tokens + 63) / 64) * s.Hkv * 36864 : 0;
+    w.kv_images_bytes = tiled ? attn_mfma_images_bytes(s, max_tokens) : 0;
     const size_t o_img = take(w.kv_images_bytes);
-    w.attn_partials_bytes = (s.dtype == FR_BF16 && s.d == 128) ? attn_mfma_partials_bytes(s, max_tokens) : 0;
+    w.attn_partials_bytes = tiled ? attn_mfma_partials_bytes(s, max_tokens) : 0;
     const size_t o_part = take(w.attn_partials_bytes);
     const size_t o_dpart = take(decode_partials_bytes(s));
     const size_t o_drot = take(decode_rot_table_bytes(s));
     const size_t o_rr = take((size_t)max_tokens * (s.d / 2) * sizeof(float2));
     w.gemm_partials_bytes = (s.dtype == FR_BF16) ? gemm_partials_bytes() : 0;
     const size_t o_gp = take(w.gemm_partials_bytes);
-    // shapes without a tiled path serve the shared chunk store through a gathered copy of the query's keys and values
+    // shapes whose kernels do not read a chunk store serve it through a gathered copy of the query's keys and values
     const size_t store_copy_bytes =
-        (attn_mfma_supported(s) && score_mfma_supported(s)) ? 0 : (size_t)max_tokens * s.Hkv * s.d * s.esize;
+        (attn_mfma_store_supported(s) && score_mfma_supported(s)) ? 0 : (size_t)max_tokens * s.Hkv * s.d * s.esize;
     const size_t o_sk = take(store_copy_bytes);
     const size_t o_sv = take(store_copy_bytes);
     w.bytes = off;
@@ -410,9 +411,9 @@ fr_status fr_score_select(fr_ctx* ctx, const void* q_question, int32_t nq, const
     return FR_OK;
 }
 
-// Shapes the tiled kernels do not take: the query's keys (moved to their prompt positions, Appendix A) and, when
+// Shapes whose kernels do not read a chunk store: the query's keys (moved to their prompt positions, Appendix A) and, when
 // v_store is given, its values are gathered from the chunk store into the workspace's [L, Hkv, d] copies, on which
-// the generic kernels then run.  Values go through the same kernel with a rotation by zero positions, which is
+// the kernels for ordinary caches then run.  Values go through the same kernel with a rotation by zero positions, which is
 // the identity in every arithmetic (cos 0 = 1, sin 0 = 0).  Rows [L_ctx, L) are cleared.
 static fr_status gather_from_store(fr_ctx* ctx, const void* k_store, const void* v_store, const ChunkTable& ct,
                                    const int32_t* chunk_store_row0, const ChunkDeltas& dl, int64_t L, hipStream_t hs) {
@@ -519,6 +520,26 @@ static fr_status check_rows(fr_ctx* ctx, int32_t R, int64_t L) {
     return FR_OK;
 }
 
+// Attention over a cache of the query's own (or a gathered copy): tiled kernels, or the generic one.
+static hipError_t attn_over_cache(fr_ctx* ctx, const void* q_rows, const int32_t* q_index, int32_t R, const void* k_cache,
+                                  const void* v_cache, int64_t L, const void* k_new, const void* v_new, void* out,
+                                  float* lse_out, bool writeback, hipStream_t hs) {
+    const Shape& s = ctx->shape;
+    if (attn_mfma_supported(s))   // (the tiled path finds the fresh rows of a key tile while it packs the tile)
+        return launch_attn_mfma(s, q_rows, q_index, R, k_cache, v_cache, L, k_new, v_new, out, lse_out, ctx->ws,
+                                ctx->attn_softmax_mode, ctx->attn_split_mode, nullptr, &ctx->attn_timer, writeback, hs);
+    const int32_t* inv = nullptr;   // position -> fresh row map
+    if (k_new) {
+        hipError_t e = launch_inv_index(q_index, R, L, ctx->ws.inv_index, hs);
+        if (e != hipSuccess) return e;
+        inv = ctx->ws.inv_index;
+    }
+    hipError_t e = launch_attn_simt(s, q_rows, q_index, R, k_cache, v_cache, L, k_new, v_new, inv, out, lse_out, hs);
+    if (e == hipSuccess && writeback)   // the generic kernel has no packing pass to fuse it into
+        e = launch_kv_scatter(s, k_new, v_new, q_index, R, const_cast<void*>(k_cache), const_cast<void*>(v_cache), L, hs);
+    return e;
+}
+
 static fr_status prefill_attn_impl(fr_ctx* ctx, const void* q_rows, const int32_t* q_index, int32_t R,
                                    const void* k_cache, const void* v_cache, int64_t L, const void* k_new,
                                    const void* v_new, void* out, float* lse_out, bool writeback, void* stream) {
@@ -540,21 +561,7 @@ static fr_status prefill_attn_impl(fr_ctx* ctx, const void* q_rows, const int32_
     if ((st = need_device(ctx)) != FR_OK) return st;
     hipStream_t hs = (hipStream_t)stream;
     if (writeback && !k_new) return fail(ctx, FR_ERR_INVALID_ARG, "the write-back needs k_new / v_new");
-    hipError_t e;
-    if (attn_mfma_supported(s)) {   // (the tiled path finds the fresh rows of a key tile while it packs the tile)
-        e = launch_attn_mfma(s, q_rows, q_index, R, k_cache, v_cache, L, k_new, v_new, out, lse_out, ctx->ws,
-                             ctx->attn_softmax_mode, ctx->attn_split_mode, nullptr, &ctx->attn_timer, writeback, hs);
-    } else {
-        const int32_t* inv = nullptr;   // position -> fresh row map
-        if (k_new) {
-            e = launch_inv_index(q_index, R, L, ctx->ws.inv_index, hs);
-            if (e != hipSuccess) return hip_fail(ctx, "index map launch", e);
-            inv = ctx->ws.inv_index;
-        }
-        e = launch_attn_simt(s, q_rows, q_index, R, k_cache, v_cache, L, k_new, v_new, inv, out, lse_out, hs);
-        if (e == hipSuccess && writeback)   // the generic kernel has no packing pass to fuse it into
-            e = launch_kv_scatter(s, k_new, v_new, q_index, R, const_cast<void*>(k_cache), const_cast<void*>(v_cache), L, hs);
-    }
+    hipError_t e = attn_over_cache(ctx, q_rows, q_index, R, k_cache, v_cache, L, k_new, v_new, out, lse_out, writeback, hs);
     if (e != hipSuccess) return hip_fail(ctx, "attention launch", e);
     return FR_OK;
 }
@@ -624,12 +631,9 @@ fr_status fr_sparse_prefill_attn_shared(fr_ctx* ctx, const void* q_rows, const i
     if ((st = need_device(ctx)) != FR_OK) return st;
     hipStream_t hs = (hipStream_t)stream;
     hipError_t e = hipSuccess;
-    if (!attn_mfma_supported(s)) {   // no tiled kernel for this shape: gathered keys and values, generic kernel
-        e = launch_inv_index(q_index, R, L, ctx->ws.inv_index, hs);
-        if (e != hipSuccess) return hip_fail(ctx, "index map launch", e);
+    if (!attn_mfma_store_supported(s)) {   // gathered keys and values
         if ((st = gather_from_store(ctx, k_store, v_store, sh.ct, chunk_store_row0, dl, L, hs)) != FR_OK) return st;
-        e = launch_attn_simt(s, q_rows, q_index, R, ctx->ws.store_k, ctx->ws.store_v, L, k_new, v_new, ctx->ws.inv_index, out,
-                             lse_out, hs);
+        e = attn_over_cache(ctx, q_rows, q_index, R, ctx->ws.store_k, ctx->ws.store_v, L, k_new, v_new, out, lse_out, false, hs);
         if (e != hipSuccess) return hip_fail(ctx, "attention launch", e);
         return FR_OK;
     }
@@ -670,7 +674,7 @@ BatchScratch batch_scratch(const Shape& s, int64_t L, int64_t R, size_t base) {
 
 int64_t fr_shared_batch_workspace_bytes(const fr_ctx* ctx, int32_t n_queries, int64_t max_L) {
     if (!ctx || n_queries <= 0 || max_L <= 0) return 0;
-    if (!attn_mfma_supported(ctx->shape)) return 0;   // such shapes are served query by query from the context's own workspace
+    if (!attn_mfma_store_supported(ctx->shape)) return 0;   // such shapes are served query by query from the context's own workspace
     const int64_t group = n_queries < ATTN_MAX_BATCH ? n_queries : ATTN_MAX_BATCH;
     return group * (int64_t)batch_scratch(ctx->shape, max_L, max_L, 0).end;
 }
@@ -709,7 +713,7 @@ fr_status fr_sparse_prefill_attn_shared_batch(fr_ctx* ctx, const fr_shared_query
         deltas.push_back(dl);
     }
     if (work.empty()) return FR_OK;
-    if (!attn_mfma_supported(s)) {   // no tiled kernel for this shape: one query after the other, on the same stream
+    if (!attn_mfma_store_supported(s)) {   // no store-reading kernel for this shape: one query after the other, on the same stream
         for (int i = 0; i < n_queries; ++i) {
             const fr_shared_query& q = queries[i];
             if (q.R == 0) continue;

@@ -58,7 +58,7 @@ struct Workspace {
     float2* decode_rot = nullptr;        // [DECODE_MAX_UNITS][d/2] (cos, sin) of the segments' position shifts
     float* attn_partials = nullptr;      // partial results of an attention launch whose items are computed in parts
     size_t attn_partials_bytes = 0;
-    unsigned char* kv_images = nullptr;  // [Hkv][ceil(max_tokens / 64)] LDS-ready K / V^T tile images, 32 KB each
+    unsigned char* kv_images = nullptr;  // [Hkv][ceil(max_tokens / 64)] LDS-ready K / V^T tile images
     size_t kv_images_bytes = 0;
 };
 
@@ -181,6 +181,7 @@ hipError_t launch_attn_simt(const Shape& s, const void* q_rows, const int32_t* q
                             const void* k_cache, const void* v_cache, int64_t L, const void* k_new,
                             const void* v_new, const int32_t* inv, void* out, float* lse, hipStream_t st);
 bool attn_mfma_supported(const Shape& s);
+bool attn_mfma_store_supported(const Shape& s);   // also over a chunk store (launch_attn_mfma with `shared`, and the batch)
 hipError_t launch_attn_mfma(const Shape& s, const void* q_rows, const int32_t* q_index, int R,
                             const void* k_cache, const void* v_cache, int64_t L, const void* k_new,
                             const void* v_new, void* out, float* lse,

@@ -1,7 +1,7 @@
 // Sparse prefill attention (eq. 9, Sec. 4.3) -- generic kernel for any supported shape and both
 // storage types: one wave per (row, query head); lanes stride over the visible keys with a
-// running softmax each and are merged at the end.  The tiled matrix-core kernel serves the
-// Llama-shaped bf16 case; this one serves everything else (fp32 in particular).
+// running softmax each and are merged at the end.  The tiled matrix-core kernel serves bf16 with up to 64
+// query heads per KV head; this one serves everything else (fp32 in particular).
 #include "fr_internal.hpp"
 
 namespace fr {

@@ -1,0 +1,87 @@
+"""The matrix-core kernels at group sizes and head dimensions that have no instance of their own (any number of query
+heads per KV head up to 64, head_dim 64), against the oracle: `pytest -m gpu`."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import fusionrag_oracle as orc
+from paper_2601_12904_amd import binding as B
+from paper_2601_12904_amd import synth
+from tests import harness as H
+from tests.test_gpu_parity import assembled_cache, run_attention, staged
+
+pytestmark = pytest.mark.gpu
+
+# Outputs are rounded to bf16 once: 8 significant bits (one of them implicit), so half a unit is up to 2^-8 of the element
+# and of the tensor's largest value at most.  The weights are carried to 16 bits (2^-17 of the largest value vector, which
+# is of the size of the largest output here) and the sums are fp32, so nothing else shows at this scale.
+OUT_TOL = 2.0 ** -8 + 2.0 ** -14
+
+
+def workload(Hq, Hkv, d, lens, nq, ratio=0.2):
+    shape = synth.LayerShape(n_q_heads=Hq, n_kv_heads=Hkv, head_dim=d, dtype="bf16", rope_base=500000.0)
+    return synth.config_small_bf16(seed=Hq + d, ratio=ratio, chunk_lens=lens, nq=nq, shape=shape)
+
+
+# (query heads, KV heads, head_dim): rows per wave floor(64 / G) from 64 down to 1; columns left idle: none, 1 (G = 7), 4 (5), 21 (43)
+SHAPES = [(7, 1, 128), (28, 4, 128), (6, 2, 128), (5, 1, 128), (16, 1, 128), (43, 1, 128), (64, 1, 128), (2, 2, 64), (8, 4, 64), (14, 2, 64), (64, 2, 64)]
+
+
+@pytest.mark.parametrize("split", [B.FR_ATTN_SPLIT_OFF, B.FR_ATTN_SPLIT_ON])
+@pytest.mark.parametrize("Hq,Hkv,d", SHAPES)
+def test_attention(Hq, Hkv, d, split):
+    w = workload(Hq, Hkv, d, (130, 0, 333, 61), 37)
+    k_ctx, _, k, qi = staged(w)
+    k_cache, v_cache = assembled_cache(w, k_ctx)
+    ctx = H.make_ctx(w.shape, w.L, w.n_chunks, w.nq)
+    ctx.fr_set_option(B.FR_OPT_ATTN_SPLIT, split)
+    got, lse = run_attention(ctx, w, qi, k_cache, v_cache)
+    want, want_lse = orc.sparse_prefill_attn(w.q_full[qi], qi, k_cache, v_cache, w.k_full[qi], w.v_full[qi])
+    assert H.max_rel_err(got, want) <= OUT_TOL
+    assert np.max(np.abs(lse - want_lse)) <= 1e-4
+    kc, vc = H.dev(k_cache, "bf16"), H.dev(v_cache, "bf16")
+    out = torch.zeros((len(qi), Hq, d), dtype=torch.bfloat16, device="cuda")
+    ctx.fr_sparse_prefill_attn_writeback(H.dev(w.q_full[qi], "bf16"), torch.from_numpy(qi.astype(np.int32)).cuda(), len(qi), kc, vc,
+                                         w.L, H.dev(w.k_full[qi], "bf16"), H.dev(w.v_full[qi], "bf16"), out)
+    torch.cuda.synchronize()
+    assert H.max_rel_err(H.host(out), want) <= OUT_TOL
+    k_eff, v_eff = orc.kv_scatter(qi, w.k_full[qi], w.v_full[qi], k_cache, v_cache)
+    assert np.array_equal(H.host(kc), k_eff) and np.array_equal(H.host(vc), v_eff)
+    ctx.close()
+
+
+@pytest.mark.parametrize("split", [B.FR_ATTN_SPLIT_OFF, B.FR_ATTN_SPLIT_ON])
+@pytest.mark.parametrize("Hq,Hkv,d", [(7, 1, 128), (4, 2, 64)])
+def test_attention_logits_beyond_the_fixed_reference(Hq, Hkv, d, split):
+    """A few keys whose logits lie far above those of the first 32 keys: the sums overflow and the rows are recomputed."""
+    w = workload(Hq, Hkv, d, (200, 120), 20, ratio=0.1)
+    k_ctx, _, k, qi = staged(w)
+    k_cache, v_cache = assembled_cache(w, k_ctx)
+    q = w.q_full.copy()
+    hot = [150, 210]
+    for j in hot:
+        k_cache[j] = 0.0
+        k_cache[j, :, 0] = 40.0
+    q[:, :, 0] = 60.0
+    q, k_cache = synth.round_to_storage(q, "bf16"), synth.round_to_storage(k_cache, "bf16")
+    qi = np.array([i for i in qi if i not in hot])
+    w.q_full = q
+    ctx = H.make_ctx(w.shape, w.L, w.n_chunks, w.nq)
+    ctx.fr_set_option(B.FR_OPT_ATTN_SPLIT, split)
+    got, _ = run_attention(ctx, w, qi, k_cache, v_cache)
+    want, _ = orc.sparse_prefill_attn(q[qi], qi, k_cache, v_cache, w.k_full[qi], w.v_full[qi])
+    assert H.max_rel_err(got, want) <= OUT_TOL
+    ctx.close()
+
+
+@pytest.mark.parametrize("Hq,Hkv,d", [(7, 1, 128), (4, 2, 64)])
+def test_more_rows_than_one_launch_in_parts(Hq, Hkv, d):
+    """Every row of a prompt of several key tiles (100 % recompute equals dense causal attention)."""
+    w = workload(Hq, Hkv, d, (500, 413), 65, ratio=1.0)
+    k_ctx, _, k, qi = staged(w)
+    k_cache, v_cache = assembled_cache(w, k_ctx)
+    ctx = H.make_ctx(w.shape, w.L, w.n_chunks, w.nq)
+    got, _ = run_attention(ctx, w, qi, k_cache, v_cache)
+    want, _ = orc.sparse_prefill_attn(w.q_full[qi], qi, k_cache, v_cache, w.k_full[qi], w.v_full[qi])
+    assert H.max_rel_err(got, want) <= OUT_TOL
+    ctx.close()
