@@ -170,8 +170,7 @@ fr_status fr_score_select(fr_ctx* ctx, const void* q_question, int32_t nq, const
  *   k_store  dev [n_store_rows, Hkv, d], read only
  *   chunk_offsets, chunk_store_row0, chunk_src_pos0  host, as in fr_sparse_prefill_attn_shared
  *   norm     FR_NORM_PER_CHUNK or FR_NORM_GLOBAL
- * Everything else as in fr_score_select.  Contexts the tiled kernels do not take (fp32, head_dim 64, group sizes
- * other than 1, 2, 4, 8) gather the shifted keys into the context's workspace and run the generic kernel. */
+ * Everything else as in fr_score_select. */
 fr_status fr_score_select_shared(fr_ctx* ctx, const void* q_question, int32_t nq, const void* k_store,
                                  int64_t n_store_rows, const int32_t* chunk_offsets, const int32_t* chunk_store_row0,
                                  const int32_t* chunk_src_pos0, int32_t n_chunks, int64_t k, int32_t norm,

@@ -130,10 +130,9 @@ fr_status fr_create(const fr_layer_desc* desc, int64_t max_tokens, int32_t max_c
         return o;
     };
     const size_t o_table = take((size_t)max_chunks * (s.d / 2) * sizeof(float2));
-    // normalisers per (head, chunk or whole context, question token); the tiled kernels pad every row of
-    // G x question tokens to a multiple of 64
-    const size_t o_lse = take((size_t)s.Hkv * (max_chunks + 1) * ((size_t)s.G * (max_question_tokens > 0 ? max_question_tokens : 1) + 63) * 4);
-    const size_t o_col = take((size_t)s.Hkv * max_tokens * 4);
+    const size_t o_lse = take(score_lse_floats(s, max_tokens, max_chunks, max_question_tokens) * 4);
+    w.col_splits = score_column_ranges(s, max_tokens, max_question_tokens);
+    const size_t o_col = take((size_t)w.col_splits * s.Hkv * max_tokens * 4);
     const size_t o_scores = take((size_t)max_tokens * 4);
     const size_t o_inv = take((size_t)max_tokens * 4);
     const size_t o_srow = take((size_t)max_tokens * 4);
@@ -160,7 +159,7 @@ fr_status fr_create(const fr_layer_desc* desc, int64_t max_tokens, int32_t max_c
     const size_t o_gp = take(w.gemm_partials_bytes);
     // shapes whose kernels do not read a chunk store serve it through a gathered copy of the query's keys and values
     const size_t store_copy_bytes =
-        (attn_mfma_store_supported(s) && score_mfma_supported(s)) ? 0 : (size_t)max_tokens * s.Hkv * s.d * s.esize;
+        attn_mfma_store_supported(s) ? 0 : (size_t)max_tokens * s.Hkv * s.d * s.esize;
     const size_t o_sk = take(store_copy_bytes);
     const size_t o_sv = take(store_copy_bytes);
     w.bytes = off;
@@ -398,12 +397,12 @@ fr_status fr_score_select(fr_ctx* ctx, const void* q_question, int32_t nq, const
     const bool need_scores = (scores_out != nullptr) || (k > 0 && k < L_ctx);
     if (L_ctx > 0 && need_scores) {
         hipError_t e;
-        if (score_mfma_supported(s) && nq > 0 && norm != FR_NORM_RAW)
-            e = launch_score_mfma(s, q_question, nq, k_ctx, ct, norm, ctx->ws, scores, hs);
-        else if (norm == FR_NORM_RAW && score_raw_supported(s))
+        if (nq > 0 && norm != FR_NORM_RAW)
+            e = launch_score(s, q_question, nq, k_ctx, ct, norm, ctx->ws, scores, nullptr, nullptr, hs);
+        else if (nq > 0 && score_raw_supported(s))
             e = launch_score_raw(s, q_question, nq, k_ctx, L_ctx, ctx->ws.qsum, scores, hs);
         else
-            e = launch_score_simt(s, q_question, nq, k_ctx, ct, norm, ctx->ws, scores, hs);
+            e = launch_score_simt(s, q_question, nq, k_ctx, L_ctx, scores, hs);
         if (e != hipSuccess) return hip_fail(ctx, "score launch", e);
     }
     hipError_t e = launch_select(scores, L_ctx, k, nq, q_index_out, ctx->ws.select_tmp, select_workspace_bytes(), hs);
@@ -411,8 +410,8 @@ fr_status fr_score_select(fr_ctx* ctx, const void* q_question, int32_t nq, const
     return FR_OK;
 }
 
-// Shapes whose kernels do not read a chunk store: the query's keys (moved to their prompt positions, Appendix A) and, when
-// v_store is given, its values are gathered from the chunk store into the workspace's [L, Hkv, d] copies, on which
+// Shapes whose kernels do not read a chunk store: the query's keys (moved to their prompt positions, Appendix A) and its
+// values are gathered from the chunk store into the workspace's [L, Hkv, d] copies, on which
 // the kernels for ordinary caches then run.  Values go through the same kernel with a rotation by zero positions, which is
 // the identity in every arithmetic (cos 0 = 1, sin 0 = 0).  Rows [L_ctx, L) are cleared.
 static fr_status gather_from_store(fr_ctx* ctx, const void* k_store, const void* v_store, const ChunkTable& ct,
@@ -426,7 +425,7 @@ static fr_status gather_from_store(fr_ctx* ctx, const void* k_store, const void*
         max_len = std::max(max_len, ct.off[c + 1] - ct.off[c]);
     }
     hipError_t e = hipSuccess;
-    if (v_store && L_ctx > 0) {
+    if (L_ctx > 0) {
         const ChunkDeltas zero{};
         e = launch_rope_table(s, zero, ct.n, ctx->ws.rope_table, hs);
         if (e == hipSuccess) e = launch_rope_shift(s, v_store, ctx->ws.store_v, ct, max_len, ctx->ws.rope_table, 1, 0, 0, &rows, hs);
@@ -440,7 +439,7 @@ static fr_status gather_from_store(fr_ctx* ctx, const void* k_store, const void*
     const int64_t row_words = (int64_t)s.Hkv * s.d * s.esize / 4;
     if (L > L_ctx) {
         e = launch_clear_words((uint32_t*)ctx->ws.store_k + L_ctx * row_words, (L - L_ctx) * row_words, hs);
-        if (e == hipSuccess && v_store)
+        if (e == hipSuccess)
             e = launch_clear_words((uint32_t*)ctx->ws.store_v + L_ctx * row_words, (L - L_ctx) * row_words, hs);
         if (e != hipSuccess) return hip_fail(ctx, "clear launch", e);
     }
@@ -490,20 +489,15 @@ fr_status fr_score_select_shared(fr_ctx* ctx, const void* q_question, int32_t nq
     float* scores = scores_out ? scores_out : ctx->ws.scores;
     const bool need_scores = (scores_out != nullptr) || (k > 0 && k < L_ctx);
     if (L_ctx > 0 && need_scores) {
+        hipError_t e;
         if (nq == 0) {   // no question rows: every score is an empty sum (the generic kernel writes the zeros; no key is read)
-            hipError_t e = launch_score_simt(s, q_question, 0, k_store, ct, norm, ctx->ws, scores, hs);
-            if (e != hipSuccess) return hip_fail(ctx, "score launch", e);
-        } else if (!score_mfma_supported(s)) {   // no tiled kernel for this shape: gathered keys, generic kernel
-            if ((st = gather_from_store(ctx, k_store, nullptr, ct, chunk_store_row0, dl, L_ctx, hs)) != FR_OK) return st;
-            hipError_t e = launch_score_simt(s, q_question, nq, ctx->ws.store_k, ct, norm, ctx->ws, scores, hs);
-            if (e != hipSuccess) return hip_fail(ctx, "score launch", e);
+            e = launch_score_simt(s, q_question, 0, k_store, L_ctx, scores, hs);
         } else {
-            hipError_t e = launch_rope_table(s, dl, n_chunks, ctx->ws.rope_table, hs);
+            e = launch_rope_table(s, dl, n_chunks, ctx->ws.rope_table, hs);
             if (e != hipSuccess) return hip_fail(ctx, "rope table launch", e);
-            e = launch_score_mfma_shared(s, q_question, nq, k_store, ct, chunk_store_row0, ctx->ws.rope_table, norm, ctx->ws,
-                                         scores, hs);
-            if (e != hipSuccess) return hip_fail(ctx, "score launch", e);
+            e = launch_score(s, q_question, nq, k_store, ct, norm, ctx->ws, scores, chunk_store_row0, ctx->ws.rope_table, hs);
         }
+        if (e != hipSuccess) return hip_fail(ctx, "score launch", e);
     }
     hipError_t e = launch_select(scores, L_ctx, k, nq, q_index_out, ctx->ws.select_tmp, select_workspace_bytes(), hs);
     if (e != hipSuccess) return hip_fail(ctx, "select launch", e);

@@ -38,8 +38,9 @@ struct Workspace {
     char* base = nullptr;
     size_t bytes = 0;
     float2* rope_table = nullptr;   // [max_chunks][d/2] (cos, sin)
-    float* lse = nullptr;           // [Hq][max_chunks + 1][max_q]  natural-log row normalisers
-    float* col_partial = nullptr;   // [Hkv][max_ctx] per-KV-head column sums
+    float* lse = nullptr;           // base-2 row normalisers of the two-pass scoring (score_lse_floats)
+    float* col_partial = nullptr;   // [col_splits][Hkv][max_ctx] column sums per range of question columns and KV head
+    int col_splits = 0;
     float* scores = nullptr;        // [max_tokens]
     int32_t* inv_index = nullptr;   // [max_tokens] position -> row of k_new / -1
     int32_t* store_row_map = nullptr;   // [max_tokens] prompt position -> row of the shared chunk store / -1
@@ -113,19 +114,22 @@ hipError_t launch_clear_words(uint32_t* words, int64_t n_words, hipStream_t st);
 hipError_t launch_kv_scatter(const Shape& s, const void* k_new, const void* v_new, const int32_t* q_index,
                              int R, void* k_cache, void* v_cache, int64_t L, hipStream_t st);
 
-hipError_t launch_score_simt(const Shape& s, const void* q, int nq, const void* k_ctx, const ChunkTable& ct,
-                             int norm, const Workspace& ws, float* scores, hipStream_t st);
+// Literal products (FR_NORM_RAW) of shapes that launch_score_raw does not take; nq = 0: zeros.
+hipError_t launch_score_simt(const Shape& s, const void* q, int nq, const void* k_ctx, int64_t L_ctx, float* scores,
+                             hipStream_t st);
 bool score_raw_supported(const Shape& s);
 size_t score_raw_workspace_bytes(const Shape& s);
 hipError_t launch_score_raw(const Shape& s, const void* q, int nq, const void* k_ctx, int64_t L_ctx, float* qsum,
                             float* scores, hipStream_t st);
-bool score_mfma_supported(const Shape& s);
-hipError_t launch_score_mfma(const Shape& s, const void* q, int nq, const void* k_ctx, const ChunkTable& ct,
-                             int norm, const Workspace& ws, float* scores, hipStream_t st);
-
-hipError_t launch_score_mfma_shared(const Shape& s, const void* q, int nq, const void* k_store, const ChunkTable& ct,
-                                    const int32_t* store_row0, const float2* table, int norm, const Workspace& ws,
-                                    float* scores, hipStream_t st);
+bool score_two_pass_supported(const Shape& s);
+size_t score_two_pass_lse_floats(const Shape& s, int max_chunks, int max_q);
+hipError_t launch_score_two_pass(const Shape& s, const void* q, int nq, const void* k, const ChunkTable& ct, int norm,
+                                 const Workspace& ws, float* scores, const int32_t* store_row0, const float2* table,
+                                 hipStream_t st);
+size_t score_lse_floats(const Shape& s, int64_t max_tokens, int max_chunks, int max_q);
+int score_column_ranges(const Shape& s, int64_t max_tokens, int max_q);
+hipError_t launch_score(const Shape& s, const void* q, int nq, const void* k, const ChunkTable& ct, int norm,
+                        const Workspace& ws, float* scores, const int32_t* store_row0, const float2* table, hipStream_t st);
 
 // `tmp` (tmp_bytes bytes of device scratch) is used beyond SELECT_ONE_WORKGROUP_MAX scores only; a scratch too small
 // for n gives hipErrorInvalidValue before anything is launched.

@@ -322,7 +322,7 @@ __global__ __launch_bounds__(256) void pack_kv_images_shared_kernel(const __bf16
     for (int i = 0; i < 4; ++i) {
         if (rk[i] < 0) {
             if (sk[i] >= 0)
-                kreg[i] = rotate_key_vector<LAYOUT>(kreg[i], LAYOUT != FR_ROPE_INTERLEAVED ? kpart[i] : kreg[i],
+                kreg[i] = rotate_key_vector<__bf16, D, LAYOUT>(kreg[i], LAYOUT != FR_ROPE_INTERLEAVED ? kpart[i] : kreg[i],
                                                     table + (size_t)ck[i] * (D / 2), st_vec);
             else
                 kreg[i] = zero;

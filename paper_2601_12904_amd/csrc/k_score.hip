@@ -1,0 +1,612 @@
+// Query-Guided Selection, critical scores (Sec. 3.2) on the gfx950 matrix cores: bf16 and fp32, head_dim 64 and 128, any
+// group size.
+//
+// The score of context token j is the column sum, over all question rows and query heads, of the softmax-normalised
+// attention weights.  A weight needs its row's normaliser, i.e. the logits of every key in the softmax's scope, before it
+// can be added up.  Where the scope is a chunk of at most SEG keys (the usual case: chunks of 1024 tokens, softmax per
+// chunk) one workgroup holds the whole chunk: its keys sit in the registers of the eight waves and the query columns
+// stream past them, so every logit and every exponential is formed once.  Otherwise the chunk (or, for one softmax over
+// the whole context, the prompt) is cut into segments of at most SEG keys and walked twice.
+//
+//   MODE_FUSED   logits -> weights exp2(s - ref) -> sum l per query column (exchanged between the waves through LDS) ->
+//                score[key] += weight / l
+//   MODE_LSE     the same up to l; leaves ref + log2 l per (segment, column)
+//   MODE_GIVEN   score[key] += exp2(s - lse) with the normalisers that score_lse_combine_kernel made of those
+//   reduce       scores[j] = sum over column ranges and KV heads of the partial sums, in a fixed order
+//
+// A "query column" n of KV head g is the pair (question token n / G, query head g G + n % G).
+//
+// Layout.  S^T = K Q^T with 16 x 16 tiles: keys on the accumulator's register dimension, query columns on lanes.  A wave
+// owns key blocks w, w + 8, w + 16, ... (16 keys each; the chunk's last, possibly partial block is then the last of its
+// wave, the only one that needs a mask).  Per 16 columns a wave has 4 NB logits per lane; its accumulators of
+// the score (4 NB per lane, one per key and column mod 16) are added up across the 16 lanes once at the end.
+// 128 keys x 256 bytes per wave are 128 registers; with 32 x 32 tiles the weights and the accumulators would be 64
+// registers each and would not fit beside them, with 16 x 16 tiles they are 32.  What bounds the kernel is the vector
+// ALU: fma + exp2 + add + fma per logit, 20 issue cycles of a wave for 64 logits against 16 of the matrix pipe (head_dim
+// 128, bf16).  The weights of a step are kept until the next one: its barrier is also the one that makes the other waves'
+// sums visible, so a step has a single barrier.
+//
+// Exponent reference.  exp2(s - ref) / sum exp2(s - ref) does not depend on ref.  The reference of a column is the maximum
+// over the segment's first 16 keys, whose logits wave 0 has a step ahead; l >= 1 then, and fp32 has 2^127 of headroom.  If a later logit
+// exceeds the reference by more than about 2^100 the sum shows it, and the workgroup repeats its range with the exact
+// maxima.
+//
+// Measured (16 x 1024 keys, 512 question tokens, 32/8 heads, bf16): 92 us + 6 us for the reduction, of which about 14 us
+// load the keys before the first step; the two passes of k_score_mfma.hip took 66 + 62 + 5 us (layer 656 -> 618 us).  28/4
+// heads: 0.10 ms, 71 ms with one thread per key; fp32, 4 x 128 keys, 32 question tokens: 7 us, before 205 us.
+// All sums run in a fixed order: the scores are reproducible bit for bit.
+#include "fr_internal.hpp"
+#include "k_rotate.hpp"
+
+#include <algorithm>
+#include <type_traits>
+
+namespace fr {
+
+namespace {
+
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+
+enum { MODE_FUSED = 0, MODE_LSE = 1, MODE_GIVEN = 2 };
+enum { SRC_PROMPT = 0, SRC_STORE_INTERLEAVED = 1, SRC_STORE_HALF = 2 };
+
+constexpr int WAVES = 8;
+constexpr int TILE = 64;          // query columns per LDS tile
+constexpr int RANGE_UNIT = 32;    // column ranges are multiples of the longest step
+constexpr int MAX_COLS = 2048;    // query columns per workgroup (their references sit in LDS)
+constexpr int CG2_MAX_KEYS = 20;  // most 4-register key vectors per lane with two column groups per step in MODE_FUSED
+
+template <typename T, int D>
+struct Op {
+    static constexpr int ROWB = D * (int)sizeof(T);            // bytes of a head row: 128, 256 or 512
+    static constexpr int NV = ROWB / 16;                       // its 16-byte vectors
+    static constexpr int NJ = NV / 4;                          // vectors per lane: lane (row x, quarter kg) holds vectors 4 j + kg
+    static constexpr int NB_MAX = ROWB == 512 ? 4 : 8;         // key blocks per wave: NB x NJ x 4 registers
+    static constexpr int SEG = 16 * WAVES * NB_MAX;            // most keys of a workgroup
+    // 16-byte vector c of row r sits in slot c ^ swz(r) of the row: any 16 rows' vectors c then start in 16 different
+    // 16-byte bank groups (two 128-byte rows share one stretch of banks)
+    static __device__ __forceinline__ int swz(int r) { return ROWB == 128 ? (r >> 1) & 7 : r & 15; }
+    static __device__ __forceinline__ void multiply(const u32x4& a, const u32x4& b, f32x4& acc) {
+        if constexpr (sizeof(T) == 2) {
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[e]), __uint_as_float(b[e]), acc, 0, 0, 0);
+        }
+    }
+};
+
+struct ScoreArgs {
+    const void* q;
+    const void* k;
+    const float2* table;      // (cos, sin) rows of the chunks, stores only
+    float* lse2;              // [Hkv][lse_rows][NQG] base-2 normalisers of the two-pass modes
+    float* partial;           // [n_split][Hkv][L_ctx]
+    int nq, Hq, Hkv, G, lse_rows, n_split, split_cols, max_parts, src, global_scope;
+    uint32_t magic;           // ceil(2^32 / G): n / G = mulhi(n, magic) for G > 1
+    float scale_log2e;
+    ChunkTable ct;
+    ChunkRows rows;
+    uint8_t order[FR_MAX_CHUNKS];   // chunks, longest first
+};
+
+// A chunk of `len` keys as segments of equal length (the last one may be shorter): keys per segment, and their number.
+template <int SEG>
+__host__ __device__ __forceinline__ int segment_keys(int len) {
+    const int parts = (len + SEG - 1) / SEG;
+    return (len + parts - 1) / parts;
+}
+template <int SEG>
+__host__ __device__ __forceinline__ int segments(int len) {
+    return len <= SEG ? (len > 0 ? 1 : 0) : (len + segment_keys<SEG>(len) - 1) / segment_keys<SEG>(len);
+}
+// Row of lse2 that holds segment 0 of chunk c: chunks before it have at most c + off[c] / SEG segments together.
+template <int SEG>
+__host__ __device__ __forceinline__ int lse_row(int c, int off) { return c + off / SEG; }
+
+__device__ __forceinline__ uint32_t lds_address(const void* p) {
+    return __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) const unsigned char*)p);
+}
+__device__ __forceinline__ void plain_barrier() {   // without the fences of __syncthreads(): the waits are explicit
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+// Sum and maximum over the four lanes that hold the same column (lanes x, x + 16, x + 32, x + 48).
+__device__ __forceinline__ float column_sum(float v) {
+    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float column_max(float v) {
+    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+template <int CTRL>
+__device__ __forceinline__ float add_rotated(float v) {
+    return v + __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), CTRL, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float row_sum(float v) {   // over the 16 lanes of a row: rotations by 8, 4, 2, 1
+    v = add_rotated<0x128>(v);
+    v = add_rotated<0x124>(v);
+    v = add_rotated<0x122>(v);
+    return add_rotated<0x121>(v);
+}
+
+template <typename T, int D>
+struct Smem {
+    alignas(1024) unsigned char q[2][TILE * Op<T, D>::ROWB];
+    float ref[MAX_COLS + 32];      // exponent references, or the given normalisers (and room for those of a step too many)
+    alignas(16) float l[2][32][WAVES];
+};
+
+// Work of one workgroup: keys [s0, s0 + len) of chunk c, query columns [n0, n1).  NB = key blocks per wave.
+template <typename T, int D, int MODE, int NB>
+__device__ __forceinline__ void walk_columns(const ScoreArgs& a, Smem<T, D>& sm, int g, int c, int s0, int len, int row,
+                                             int n0, int n1, int split) {
+    using O = Op<T, D>;
+    // Column groups of 16 per step.  A step costs about 0.3 us besides its logits (barrier, exchange of the sums, LDS
+    // latency: NB = 1, 2, 4, 6, 8 blocks took 0.44, 0.58, 0.77, 0.97, 1.19 us per step of 16 columns), so it takes two groups wherever the
+    // registers hold them: the weights are the only ones that double.
+    constexpr int CG = (MODE == MODE_FUSED && NB * Op<T, D>::NJ > CG2_MAX_KEYS) ? 1 : 2;
+    constexpr int STEP = 16 * CG, SPT = TILE / STEP;                 // columns per step, steps per tile
+    // The logits of a step come as NB x CG units of 16 keys x 16 columns, in pairs (two independent chains of matrix
+    // instructions): unit k is block k / CG, group k % CG.
+    constexpr int NU = NB * CG, NP = (NU + 1) / 2;
+    constexpr int NJ = O::NJ;                                        // vectors per lane
+    constexpr int MFMAS = 2 * NJ * (sizeof(T) == 2 ? 1 : 4) / 8;     // matrix instructions per logit of a pair and lane
+    const int tid = threadIdx.x, lane = tid & 63, x = lane & 15, kg = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int NQG = a.nq * a.G;
+    const T* __restrict__ q = static_cast<const T*>(a.q);
+    const T* __restrict__ k = static_cast<const T*>(a.k);
+    auto column_row = [&](int n) -> const unsigned char* {   // columns past the end: a copy of the last one
+        n = min(n, NQG - 1);
+        const int tok = a.G > 1 ? (int)__umulhi((uint32_t)n, a.magic) : n;
+        return reinterpret_cast<const unsigned char*>(q + ((size_t)tok * a.Hq + g * a.G + (n - tok * a.G)) * D);
+    };
+    // copies of one tile of query columns, global -> LDS directly: 1 KB per wave instruction, lane = (row, slot)
+    auto copy_tile = [&](int t, int buf) {
+        constexpr int COPIES = TILE * O::ROWB / 1024 / WAVES;
+        int ln = lane;   // (opaque: the addresses are formed anew for every tile, no register holds parts of them meanwhile)
+        asm volatile("" : "+v"(ln));
+#pragma unroll
+        for (int i = 0; i < COPIES; ++i) {
+            const int r = (1024 / O::ROWB) * (COPIES * wave + i) + ln / O::NV;
+            const unsigned char* src = column_row(n0 + TILE * t + r) + 16 * ((ln % O::NV) ^ O::swz(r));
+            const uint32_t dst = lds_address(sm.q[buf]) + (uint32_t)(COPIES * wave + i) * 1024u;
+            asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(dst) : "memory");
+        }
+    };
+    const int n_steps = (n1 - n0 + STEP - 1) / STEP, n_tiles = (n_steps + SPT - 1) / SPT;
+    copy_tile(0, 0);
+    if (n_tiles > 1) copy_tile(1, 1);
+
+    // this lane's vectors 4 j + kg of keys 16 (wave + 8 b) + x; keys past the end: a copy of the last one
+    u32x4 kf[NB][NJ];
+    auto key_row = [&](int b) -> const unsigned char* {
+        const int j = min(16 * (wave + WAVES * b) + x, len - 1) + s0;
+        const int64_t r = a.src == SRC_PROMPT ? (int64_t)j : (int64_t)a.rows.row0[c] + (j - a.ct.off[c]);
+        return reinterpret_cast<const unsigned char*>(k + (r * a.Hkv + g) * D);
+    };
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        const unsigned char* kr = key_row(b) + 16 * kg;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) kf[b][j] = *reinterpret_cast<const u32x4*>(kr + 64 * j);
+    }
+    if (a.src != SRC_PROMPT) {   // moved to their prompt positions
+        const float2* trow = a.table + (size_t)c * (D / 2);
+        if (a.src == SRC_STORE_INTERLEAVED) {
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+#pragma unroll
+                for (int j = 0; j < NJ; ++j)
+                    kf[b][j] = rotate_key_vector<T, D, FR_ROPE_INTERLEAVED>(kf[b][j], kf[b][j], trow, 4 * j + kg);
+                __builtin_amdgcn_sched_barrier(0);   // block by block: the registers are taken
+            }
+        } else {   // (p, p + D/2): the partner of vector 4 j + kg is vector 4 (j ^ NJ / 2) + kg of the same lane
+            static_assert(NJ % 2 == 0, "pairs inside a lane");
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+#pragma unroll
+                for (int j = 0; j < NJ / 2; ++j) {
+                    const u32x4 lo = kf[b][j], hi = kf[b][j + NJ / 2];
+                    kf[b][j] = rotate_key_vector<T, D, FR_ROPE_HALF>(lo, hi, trow, 4 * j + kg);
+                    kf[b][j + NJ / 2] = rotate_key_vector<T, D, FR_ROPE_HALF>(hi, lo, trow, 4 * (j + NJ / 2) + kg);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    }
+    const int last_key = 16 * (wave + WAVES * (NB - 1)) + 4 * kg;   // of the wave's last block: the lane's four keys
+    bool valid[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) valid[i] = last_key + i < len;
+    if constexpr (MODE == MODE_GIVEN) {
+        const float* src = a.lse2 + ((size_t)g * a.lse_rows + row) * NQG;
+        for (int i = tid; i < n_steps * STEP; i += 64 * WAVES) sm.ref[i] = n0 + i < NQG ? src[n0 + i] : INFINITY;
+    }
+
+    float sc[NB][4], p[CG][NB][4];
+    // fragments of step st's columns (vector 4 j + kg of row 16 cg + x), and the products of a pair of units
+    u32x4 qv[CG][NJ];
+    const int q_lane = x * O::ROWB + 16 * (kg ^ O::swz(x));   // (swz(16 i + x) = swz(x))
+    auto load_q = [&](int st) {
+        const uint32_t at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)sm.q +
+                            ((st / SPT) & 1) * (uint32_t)sizeof(sm.q[0]) + (st % SPT) * (STEP * O::ROWB) + (uint32_t)q_lane;
+#pragma unroll
+        for (int cg = 0; cg < CG; ++cg)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)   // 16 ((4 j + kg) ^ swz) = 64 j ^ 16 (kg ^ swz): one register for all vectors
+                qv[cg][j] = *(__attribute__((address_space(3))) const u32x4*)(uintptr_t)((at ^ (64u * j)) + cg * (16 * O::ROWB));
+    };
+    f32x4 s[2][2];
+    auto products = [&](int pr) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) s[pr & 1][u] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+                if (2 * pr + u < NU) O::multiply(kf[(2 * pr + u) / CG][j], qv[(2 * pr + u) % CG][j], s[pr & 1][u]);
+    };
+    auto wait_copies = [&] { __builtin_amdgcn_s_waitcnt(0x0f70); };   // vmcnt(0)
+    auto wait_lds = [&] { __builtin_amdgcn_s_waitcnt(0xc07f); };      // lgkmcnt(0)
+    bool bad = false;
+    // 1 / l of this lane's column of group cg of step st (0 past the last column); MODE_LSE: the normaliser goes out
+    auto finish_column = [&](int st, int cg) -> float {
+        const int i = STEP * st + 16 * cg + x;
+        const f32x4 l0 = *reinterpret_cast<const f32x4*>(&sm.l[st & 1][16 * cg + x][0]);
+        const f32x4 l1 = *reinterpret_cast<const f32x4*>(&sm.l[st & 1][16 * cg + x][4]);
+        const float l = ((l0[0] + l0[1]) + (l0[2] + l0[3])) + ((l1[0] + l1[1]) + (l1[2] + l1[3]));
+        bad = bad || !(l < 0x1p100f);
+        if constexpr (MODE == MODE_LSE) {
+            if (wave == 0 && kg == 0 && n0 + i < n1)
+                a.lse2[((size_t)g * a.lse_rows + row) * NQG + n0 + i] = sm.ref[i] + __builtin_amdgcn_logf(l);
+            return 0.f;
+        } else {
+            return n0 + i < n1 ? __builtin_amdgcn_rcpf(l) : 0.f;
+        }
+    };
+    // the references of step st's columns: keys 0 .. 15 are block 0 of wave 0, whose logits are units 0 and (CG = 2) 1
+    auto set_references = [&](int st) {
+#pragma unroll
+        for (int cg = 0; cg < CG; ++cg) {
+            const f32x4& t = s[0][cg];
+            sm.ref[STEP * st + 16 * cg + x] = column_max(fmaxf(fmaxf(t[0], t[1]), fmaxf(t[2], t[3]))) * a.scale_log2e;
+        }
+    };
+    for (int attempt = 0;; ++attempt) {
+        const bool fixed = MODE != MODE_GIVEN && attempt == 0 && wave == 0;   // this wave sets the references as it goes
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                sc[b][i] = 0.f;
+#pragma unroll
+                for (int cg = 0; cg < CG; ++cg) p[cg][b][i] = 0.f;
+            }
+        bad = false;
+        wait_copies();
+        wait_lds();
+        plain_barrier();
+        load_q(0);
+        products(0);
+        if (fixed) set_references(0);
+        // Step st: its first pair's products were issued in the step before.  The barrier makes the other waves' sums and the
+        // references visible; in a tile's last step also the next tile, which the fragments of the next step come from, and
+        // it frees this tile's slot (the fragments of the tile's last step were read before the barrier).
+        for (int st = 0; st < n_steps; ++st) {
+            const bool last_of_tile = st % SPT == SPT - 1;
+            if (last_of_tile) wait_copies();
+            wait_lds();
+            plain_barrier();
+            if (last_of_tile && st / SPT + 2 < n_tiles) copy_tile(st / SPT + 2, (st / SPT) & 1);
+            float f[CG], ref[CG], lsum[CG][2];
+#pragma unroll
+            for (int cg = 0; cg < CG; ++cg) {
+                f[cg] = (MODE != MODE_GIVEN && st > 0) ? finish_column(st - 1, cg) : 0.f;
+                ref[cg] = sm.ref[STEP * st + 16 * cg + x];
+                lsum[cg][0] = lsum[cg][1] = 0.f;
+            }
+            // The fragments of the next step are read as soon as this step's last products are issued, its first products go
+            // beside the last pair's exponentials (an odd number of pairs: behind them, the accumulators alternate).
+#pragma unroll
+            for (int pr = 0; pr < NP; ++pr) {
+                if (pr + 1 < NP) products(pr + 1);
+                else if (NP % 2 == 0) products(0);
+                if (pr == (NP > 1 ? NP - 2 : 0)) load_q(st + 1);   // (past the last step: read, never used)
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const int b = (2 * pr + u) / CG, cg = (2 * pr + u) % CG;
+                    if (b >= NB) continue;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        float minus = -ref[cg];
+                        if (b == NB - 1 && !valid[i]) minus = -INFINITY;   // keys past the end: weight 0
+                        const float w = __builtin_amdgcn_exp2f(__builtin_fmaf(s[pr & 1][u][i], a.scale_log2e, minus));
+                        if constexpr (MODE == MODE_FUSED) sc[b][i] = __builtin_fmaf(p[cg][b][i], f[cg], sc[b][i]);
+                        if constexpr (MODE == MODE_GIVEN) sc[b][i] += w;
+                        if constexpr (MODE != MODE_GIVEN) lsum[cg][b & 1] += w;
+                        if constexpr (MODE == MODE_FUSED) p[cg][b][i] = w;
+                    }
+                }
+                // a weight takes the register of the step before: keep that one's use here (the compiler would sink the sums
+                // behind the branch below and hold two steps' weights)
+                if constexpr (MODE == MODE_FUSED)
+#pragma unroll
+                    for (int b = 2 * pr / CG; b < (2 * pr + 2) / CG && b < NB; ++b)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(sc[b][i]));
+                if (pr + 1 < NP || NP % 2 == 0) {   // matrix and vector instructions in turn
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        __builtin_amdgcn_sched_group_barrier(0x008, MFMAS, 0);   // matrix
+                        __builtin_amdgcn_sched_group_barrier(0x400, 1, 0);       // transcendental
+                        __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);       // other vector instructions
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (NP % 2 == 1) products(0);
+            // (all four lanes of a column store the same sum: no branch in the step)
+            if constexpr (MODE != MODE_GIVEN)
+#pragma unroll
+                for (int cg = 0; cg < CG; ++cg) sm.l[st & 1][16 * cg + x][wave] = column_sum(lsum[cg][0] + lsum[cg][1]);
+            if (fixed) set_references(st + 1);
+        }
+        if constexpr (MODE != MODE_GIVEN) {
+            wait_lds();
+            plain_barrier();
+#pragma unroll
+            for (int cg = 0; cg < CG; ++cg) {
+                const float f = finish_column(n_steps - 1, cg);
+                if constexpr (MODE == MODE_FUSED) {
+#pragma unroll
+                    for (int b = 0; b < NB; ++b)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) sc[b][i] = __builtin_fmaf(p[cg][b][i], f, sc[b][i]);
+                }
+            }
+        }
+        if (MODE == MODE_GIVEN || attempt > 0 || !__any(bad)) break;   // (every wave has seen every column's sum)
+        // A sum left the range of the fixed references: exact maxima of all columns, then once more.
+        for (int st = 0; st < n_steps; ++st) {
+            if (st % SPT == 0) {
+                plain_barrier();
+                copy_tile(st / SPT, (st / SPT) & 1);
+                wait_copies();
+            }
+            wait_lds();
+            plain_barrier();
+            load_q(st);
+            float m[CG];
+#pragma unroll
+            for (int cg = 0; cg < CG; ++cg) {
+                m[cg] = -INFINITY;
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    f32x4 z = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int j = 0; j < NJ; ++j) O::multiply(kf[b][j], qv[cg][j], z);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (b < NB - 1 || valid[i]) m[cg] = fmaxf(m[cg], z[i]);
+                }
+                sm.l[st & 1][16 * cg + x][wave] = column_max(m[cg]);
+            }
+            wait_lds();
+            plain_barrier();
+            if (wave == 0) {
+#pragma unroll
+                for (int cg = 0; cg < CG; ++cg) {
+                    for (int w2 = 0; w2 < WAVES; ++w2) m[cg] = fmaxf(m[cg], sm.l[st & 1][16 * cg + x][w2]);
+                    sm.ref[STEP * st + 16 * cg + x] = m[cg] * a.scale_log2e;
+                }
+            }
+        }
+        wait_lds();
+        plain_barrier();
+        copy_tile(0, 0);
+        if (n_tiles > 1) copy_tile(1, 1);
+    }
+    if constexpr (MODE != MODE_LSE) {
+        float* dst = a.partial + ((size_t)split * a.Hkv + g) * a.ct.off[a.ct.n] + s0;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            float v = 0.f;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float t = row_sum(sc[b][i]);
+                if (x == i) v = t;
+            }
+            const int key = 16 * (wave + WAVES * b) + 4 * kg + x;
+            if (x < 4 && key < len) dst[key] = v;
+        }
+    }
+}
+
+// One workgroup = (KV head, chunk, segment of the chunk, column range).  1-D grid, KV head fastest: with 8 KV heads an
+// XCD's L2 serves the queries of one head and the keys that its column ranges share.
+template <typename T, int D, int MODE>
+__global__ __launch_bounds__(64 * WAVES, 2) void score_kernel(const ScoreArgs a) {
+    using O = Op<T, D>;
+    __shared__ Smem<T, D> sm;
+    int t = blockIdx.x;
+    const int g = t % a.Hkv; t /= a.Hkv;
+    const int split = t % a.n_split; t /= a.n_split;
+    const int part = t % a.max_parts;
+    const int c = a.order[t / a.max_parts];
+    const int c0 = a.ct.off[c], clen = a.ct.off[c + 1] - c0;
+    const int parts = segments<O::SEG>(clen);
+    if (part >= parts) return;
+    // softmax per chunk: chunks of one segment are done in the fused mode, the longer ones in the other two
+    if (!a.global_scope && (parts > 1) != (MODE != MODE_FUSED)) return;
+    const int per = segment_keys<O::SEG>(clen);
+    const int s0 = c0 + part * per, len = min(per, clen - part * per);
+    const int NQG = a.nq * a.G;
+    const int n0 = split * a.split_cols, n1 = min(NQG, n0 + a.split_cols);
+    if (n0 >= n1) return;
+    int row = lse_row<O::SEG>(c, c0) + part;             // MODE_LSE: this segment's normalisers go there
+    if (MODE == MODE_GIVEN) row = a.global_scope ? a.lse_rows - 1 : row - part;   // combined: the chunk's first row, or the last of all
+    switch ((len + 16 * WAVES - 1) / (16 * WAVES)) {
+        case 1: walk_columns<T, D, MODE, 1>(a, sm, g, c, s0, len, row, n0, n1, split); break;
+        case 2: walk_columns<T, D, MODE, 2>(a, sm, g, c, s0, len, row, n0, n1, split); break;
+        case 3: walk_columns<T, D, MODE, 3>(a, sm, g, c, s0, len, row, n0, n1, split); break;
+        case 4: walk_columns<T, D, MODE, 4>(a, sm, g, c, s0, len, row, n0, n1, split); break;
+        default:
+            if constexpr (O::NB_MAX > 4) {
+                switch ((len + 16 * WAVES - 1) / (16 * WAVES)) {
+                    case 5: walk_columns<T, D, MODE, 5>(a, sm, g, c, s0, len, row, n0, n1, split); break;
+                    case 6: walk_columns<T, D, MODE, 6>(a, sm, g, c, s0, len, row, n0, n1, split); break;
+                    case 7: walk_columns<T, D, MODE, 7>(a, sm, g, c, s0, len, row, n0, n1, split); break;
+                    default: walk_columns<T, D, MODE, 8>(a, sm, g, c, s0, len, row, n0, n1, split); break;
+                }
+            }
+    }
+}
+
+// Base-2 log-sum-exp over a chunk's segments into the chunk's first row (chunks of several segments), or over all
+// segments of the prompt into the last row.  grid (columns / 256, KV heads, chunks or 1).
+template <int SEG>
+__global__ __launch_bounds__(256) void score_lse_combine_kernel(ChunkTable ct, int NQG, int lse_rows, int global_scope,
+                                                                float* __restrict__ lse2) {
+    const int n = blockIdx.x * 256 + threadIdx.x;
+    if (n >= NQG) return;
+    float* base = lse2 + (size_t)blockIdx.y * lse_rows * NQG + n;
+    const int first = global_scope ? 0 : (int)blockIdx.z, end = global_scope ? ct.n : first + 1;
+    float m = -INFINITY, l = 0.f;
+    for (int pass = 0; pass < 2; ++pass)
+        for (int c = first; c < end; ++c) {
+            const int parts = segments<SEG>(ct.off[c + 1] - ct.off[c]);
+            if (!global_scope && parts < 2) return;
+            for (int i = 0; i < parts; ++i) {
+                const float v = base[(size_t)(lse_row<SEG>(c, ct.off[c]) + i) * NQG];
+                if (pass == 0) m = fmaxf(m, v); else l += exp2f(v - m);
+            }
+        }
+    base[(size_t)(global_scope ? lse_rows - 1 : lse_row<SEG>(first, ct.off[first])) * NQG] = m + log2f(l);
+}
+
+__global__ __launch_bounds__(256) void score_reduce_kernel(const float* __restrict__ partial, int n_parts, int L_ctx,
+                                                           float* __restrict__ scores) {
+    const int j = blockIdx.x * 256 + threadIdx.x;
+    if (j >= L_ctx) return;
+    float t = 0.f;
+    for (int i = 0; i < n_parts; ++i) t += partial[(size_t)i * L_ctx + j];
+    scores[j] = t;
+}
+
+// Column ranges per (chunk, KV head).  A workgroup holds a compute unit to itself, pays about 6 steps' time before its
+// first step (12 us of 1024 keys x 2 KB, against 2 us per 32 columns), and a chunk's steps cannot be balanced otherwise:
+// the fewest ranges that fill the chip, counted in rounds of workgroups.
+int choose_splits(int items, int n_steps, int n_cu, int max_split) {
+    const int least = (n_steps * RANGE_UNIT + MAX_COLS - 1) / MAX_COLS;
+    int best = least;
+    double best_t = 1e30;
+    for (int s = least; s <= std::max(least, std::min(max_split, n_steps)); ++s) {
+        const double rounds = (double)items * s / n_cu, per = 6.0 + (n_steps + s - 1) / s;
+        const double t = per * (rounds < 4.0 ? (double)(int64_t)(rounds + 0.999) : rounds + 0.5);
+        if (t < best_t - 1e-9) { best_t = t; best = s; }
+    }
+    return best;
+}
+
+template <typename T, int D>
+hipError_t run(const Shape& s, const void* q, int nq, const void* k, const ChunkTable& ct, int norm, const Workspace& ws,
+               float* scores, int src, const int32_t* store_row0, const float2* table, hipStream_t st) {
+    using O = Op<T, D>;
+    const int L_ctx = ct.off[ct.n], NQG = nq * s.G;
+    ScoreArgs a;
+    a.q = q; a.k = k; a.table = table; a.lse2 = ws.lse; a.partial = ws.col_partial;
+    a.nq = nq; a.Hq = s.Hq; a.Hkv = s.Hkv; a.G = s.G;
+    a.src = src;
+    a.global_scope = norm == FR_NORM_GLOBAL;
+    a.magic = (uint32_t)((((uint64_t)1 << 32) + s.G - 1) / s.G);
+    a.scale_log2e = (1.0f / sqrtf((float)s.d)) * 1.4426950408889634f;
+    a.ct = ct;
+    int n = 0, max_len = 0, min_parts = INT32_MAX;   // non-empty chunks, longest first
+    for (int c = 0; c < ct.n; ++c) {
+        a.rows.row0[c] = store_row0 ? store_row0[c] : 0;
+        const int len = ct.off[c + 1] - ct.off[c];
+        if (len == 0) continue;
+        a.order[n++] = (uint8_t)c;
+        max_len = std::max(max_len, len);
+        min_parts = std::min(min_parts, segments<O::SEG>(len));
+    }
+    std::stable_sort(a.order, a.order + n, [&](uint8_t x, uint8_t y) { return ct.off[x + 1] - ct.off[x] > ct.off[y + 1] - ct.off[y]; });
+    a.max_parts = (max_len + O::SEG - 1) / O::SEG;   // (at least segments(len) for every chunk)
+    a.lse_rows = ct.n + L_ctx / O::SEG + 1;
+    const int n_steps = (NQG + RANGE_UNIT - 1) / RANGE_UNIT;
+    a.n_split = choose_splits(n * a.max_parts * s.Hkv, n_steps, ws.n_cu, ws.col_splits);
+    a.split_cols = (n_steps + a.n_split - 1) / a.n_split * RANGE_UNIT;
+    a.n_split = (NQG + a.split_cols - 1) / a.split_cols;
+    if (a.n_split > ws.col_splits) return hipErrorInvalidValue;
+    const dim3 block(64 * WAVES);
+    if (!a.global_scope && min_parts == 1) {   // (the chunks of several segments return at once)
+        const int parts = a.max_parts;
+        a.max_parts = 1;
+        score_kernel<T, D, MODE_FUSED><<<dim3(n * a.n_split * s.Hkv), block, 0, st>>>(a);
+        a.max_parts = parts;
+    }
+    if (a.global_scope || a.max_parts > 1) {
+        const dim3 grid(n * a.max_parts * a.n_split * s.Hkv);
+        score_kernel<T, D, MODE_LSE><<<grid, block, 0, st>>>(a);
+        score_lse_combine_kernel<O::SEG><<<dim3((NQG + 255) / 256, s.Hkv, a.global_scope ? 1 : ct.n), dim3(256), 0, st>>>(
+            ct, NQG, a.lse_rows, a.global_scope, a.lse2);
+        score_kernel<T, D, MODE_GIVEN><<<grid, block, 0, st>>>(a);
+    }
+    score_reduce_kernel<<<dim3((L_ctx + 255) / 256), dim3(256), 0, st>>>(ws.col_partial, a.n_split * s.Hkv, L_ctx, scores);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+// Workspace of the softmax scoring, in floats: normalisers of the two-pass modes, and how many column ranges of partial
+// sums fit (at least one per MAX_COLS columns; up to 16 while they stay below 4 MB).
+size_t score_lse_floats(const Shape& s, int64_t max_tokens, int max_chunks, int max_q) {
+    const int64_t seg = (s.d * s.esize == 512) ? Op<float, 128>::SEG : Op<__bf16, 128>::SEG;
+    const size_t own = (size_t)s.Hkv * (size_t)(max_chunks + max_tokens / seg + 1) * s.G * (size_t)(max_q > 0 ? max_q : 1);
+    return score_two_pass_supported(s) ? std::max(own, score_two_pass_lse_floats(s, max_chunks, max_q)) : own;
+}
+int score_column_ranges(const Shape& s, int64_t max_tokens, int max_q) {
+    const int64_t need = ((int64_t)max_q * s.G + RANGE_UNIT - 1) / RANGE_UNIT * RANGE_UNIT / MAX_COLS + 1;
+    const int64_t fit = ((int64_t)4 << 20) / (s.Hkv * max_tokens * 4);
+    return (int)std::max(need, std::min<int64_t>(16, std::max<int64_t>(fit, 2)));
+}
+
+// One softmax over the prompt, or any chunk of more than SEG keys: shapes that k_score_mfma.hip takes go there, with the
+// whole call.  Its two passes keep 64 columns or keys of a wave in registers without any exchange between waves; MODE_LSE
+// and MODE_GIVEN pay a barrier per step (layer times: 16 x 1024 keys, 512 question tokens, 32/8 heads, global scope 0.329
+// against 0.348 ms; 12 chunks of 500 to 1500 keys, where three launches each leave most of the chip idle, 0.206 against 0.340 ms).
+// Chunks of at most SEG keys are faster here at every size (layer times against the two passes: 64 chunks of 128 keys 0.218
+// / 0.230 ms, 32 of 512 0.286 / 0.325, 16 of 1024 0.618 / 0.656, 8 of 128 with 30 question tokens 0.0654 / 0.0661).
+//
+// Softmax scopes only; FR_NORM_RAW has kernels of its own.  store_row0 != NULL (host): k is a chunk store that is never
+// written; chunk c occupies its rows store_row0[c] .., and its keys are moved to their prompt positions while they are
+// loaded (`table`: device, [chunks][d / 2]).
+hipError_t launch_score(const Shape& s, const void* q, int nq, const void* k, const ChunkTable& ct, int norm,
+                        const Workspace& ws, float* scores, const int32_t* store_row0, const float2* table, hipStream_t st) {
+    if (ct.off[ct.n] == 0 || nq == 0) return hipSuccess;
+    if (score_two_pass_supported(s)) {
+        int max_len = 0;
+        for (int c = 0; c < ct.n; ++c) max_len = std::max(max_len, ct.off[c + 1] - ct.off[c]);
+        if (norm == FR_NORM_GLOBAL || max_len > Op<__bf16, 128>::SEG)
+            return launch_score_two_pass(s, q, nq, k, ct, norm, ws, scores, store_row0, table, st);
+    }
+    const int src = !store_row0 ? SRC_PROMPT : s.rope_layout == FR_ROPE_INTERLEAVED ? SRC_STORE_INTERLEAVED : SRC_STORE_HALF;
+    if (s.dtype == FR_BF16)
+        return s.d == 64 ? run<__bf16, 64>(s, q, nq, k, ct, norm, ws, scores, src, store_row0, table, st)
+                         : run<__bf16, 128>(s, q, nq, k, ct, norm, ws, scores, src, store_row0, table, st);
+    return s.d == 64 ? run<float, 64>(s, q, nq, k, ct, norm, ws, scores, src, store_row0, table, st)
+                     : run<float, 128>(s, q, nq, k, ct, norm, ws, scores, src, store_row0, table, st);
+}
+
+}  // namespace fr

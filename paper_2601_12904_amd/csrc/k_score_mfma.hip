@@ -1,4 +1,6 @@
-// Query-Guided Selection, critical scores (Sec. 3.2) on the gfx950 matrix cores: bf16, head_dim 128.
+// Query-Guided Selection, critical scores (Sec. 3.2) on the gfx950 matrix cores, two passes over the logits: bf16,
+// head_dim 128, group sizes 1, 2, 4, 8, softmax scopes that do not fit one workgroup (a chunk of more than 1024 keys, or
+// the whole context).  Chunks that fit are scored in one pass (k_score.hip), and so are all other shapes.
 //
 // The score of context token j is the column sum, over all question rows and query heads, of the
 // softmax-normalised attention weights.  A column sum needs every row's normaliser first, so the
@@ -47,9 +49,9 @@ template <int SRC>
 __device__ __forceinline__ u32x4 load_key_vector(const __bf16* row, int vec, const float2* trow) {
     const u32x4 own = *reinterpret_cast<const u32x4*>(row + 8 * vec);
     if (SRC == SRC_PROMPT) return own;
-    if (SRC == SRC_STORE_INTERLEAVED) return rotate_key_vector<FR_ROPE_INTERLEAVED>(own, own, trow, vec);
+    if (SRC == SRC_STORE_INTERLEAVED) return rotate_key_vector<__bf16, D, FR_ROPE_INTERLEAVED>(own, own, trow, vec);
     const u32x4 partner = *reinterpret_cast<const u32x4*>(row + 8 * (vec ^ 8));
-    return rotate_key_vector<FR_ROPE_HALF>(own, partner, trow, vec);
+    return rotate_key_vector<__bf16, D, FR_ROPE_HALF>(own, partner, trow, vec);
 }
 
 __device__ __forceinline__ bf16x8 zero8() {
@@ -513,27 +515,23 @@ hipError_t dispatch(const Shape& s, const void* q, int nq, const void* k, const 
 
 }  // namespace
 
-bool score_mfma_supported(const Shape& s) {
+bool score_two_pass_supported(const Shape& s) {
     return s.dtype == FR_BF16 && s.d == 128 && (s.G == 1 || s.G == 2 || s.G == 4 || s.G == 8);
 }
-
-// Softmax scopes only; the caller routes FR_NORM_RAW to the generic kernels.
-hipError_t launch_score_mfma(const Shape& s, const void* q, int nq, const void* k_ctx, const ChunkTable& ct, int norm,
-                             const Workspace& ws, float* scores, hipStream_t st) {
-    const ChunkRows none{};
-    return dispatch<SRC_PROMPT>(s, q, nq, k_ctx, ct, norm, ws, scores, none, nullptr, st);
+size_t score_two_pass_lse_floats(const Shape& s, int max_chunks, int max_q) {
+    return (size_t)s.Hkv * (max_chunks + 1) * ((size_t)s.G * max_q + 63);
 }
 
-// The same over a shared chunk store: store_row0 (host) gives every chunk's first store row, `table` (device,
-// [chunks][d / 2]) the (cos, sin) of every chunk's position shift.
-hipError_t launch_score_mfma_shared(const Shape& s, const void* q, int nq, const void* k_store, const ChunkTable& ct,
-                                    const int32_t* store_row0, const float2* table, int norm, const Workspace& ws,
-                                    float* scores, hipStream_t st) {
+// Arguments as launch_score.
+hipError_t launch_score_two_pass(const Shape& s, const void* q, int nq, const void* k, const ChunkTable& ct, int norm,
+                                 const Workspace& ws, float* scores, const int32_t* store_row0, const float2* table,
+                                 hipStream_t st) {
     ChunkRows rows{};
+    if (!store_row0) return dispatch<SRC_PROMPT>(s, q, nq, k, ct, norm, ws, scores, rows, nullptr, st);
     for (int c = 0; c < ct.n; ++c) rows.row0[c] = store_row0[c];
     if (s.rope_layout == FR_ROPE_INTERLEAVED)
-        return dispatch<SRC_STORE_INTERLEAVED>(s, q, nq, k_store, ct, norm, ws, scores, rows, table, st);
-    return dispatch<SRC_STORE_HALF>(s, q, nq, k_store, ct, norm, ws, scores, rows, table, st);
+        return dispatch<SRC_STORE_INTERLEAVED>(s, q, nq, k, ct, norm, ws, scores, rows, table, st);
+    return dispatch<SRC_STORE_HALF>(s, q, nq, k, ct, norm, ws, scores, rows, table, st);
 }
 
 }  // namespace fr

@@ -85,3 +85,66 @@ def test_more_rows_than_one_launch_in_parts(Hq, Hkv, d):
     want, _ = orc.sparse_prefill_attn(w.q_full[qi], qi, k_cache, v_cache, w.k_full[qi], w.v_full[qi])
     assert H.max_rel_err(got, want) <= OUT_TOL
     ctx.close()
+
+
+# Scores: products of bf16 are exact in fp32; the sums, the exponentials and the normalisers are fp32 (2^-24 relative each,
+# arguments of the exponentials up to about 30 in base 2, i.e. 2^-19 of a weight): 1e-5 of the largest score covers both
+# storage types.
+SCORE_TOL = 1e-5
+
+# (query heads, KV heads, head_dim, dtype, question tokens, chunk lengths): key blocks of a wave from 1 to 8 (16, 128, 129, 1024 keys) and
+# the last block partial; chunks of more than one workgroup's keys (1025; 513 for fp32 at head_dim 128); one column, a
+# whole and a partial step and tile of columns, more than one range of columns (2048)
+SCORES = [(7, 1, 128, "bf16", 1, (16, 1, 0, 128)), (7, 1, 128, "bf16", 37, (129, 640, 513)), (28, 4, 128, "bf16", 16, (1024, 900)),
+          (7, 1, 128, "bf16", 300, (70, 50)), (3, 1, 128, "bf16", 21, (1025, 300, 2100)), (4, 2, 64, "bf16", 33, (1024, 255, 17)),
+          (4, 1, 64, "bf16", 16, (1500, 40)), (4, 4, 64, "f32", 32, (128, 127, 1024)), (5, 1, 64, "f32", 7, (1030, 3)),
+          (8, 2, 128, "f32", 9, (512, 100)), (8, 2, 128, "f32", 5, (513, 64)), (8, 2, 128, "bf16", 65, (768, 1024, 33))]
+
+
+@pytest.mark.parametrize("norm", [B.FR_NORM_PER_CHUNK, B.FR_NORM_GLOBAL])
+@pytest.mark.parametrize("Hq,Hkv,d,dt,nq,lens", SCORES)
+def test_scores(Hq, Hkv, d, dt, nq, lens, norm):
+    shape = synth.LayerShape(n_q_heads=Hq, n_kv_heads=Hkv, head_dim=d, dtype=dt, rope_base=500000.0)
+    w = synth.config_small_bf16(seed=Hq + nq, chunk_lens=lens, nq=nq, shape=shape)
+    k_ctx = synth.round_to_storage(orc.rope_shift(w.k_cached, w.chunk_offsets, w.src_pos0, None, shape.rope_base), dt)
+    want = orc.critical_scores(w.q_question, k_ctx, w.chunk_offsets, "global" if norm == B.FR_NORM_GLOBAL else "per_chunk")
+    ctx = H.make_ctx(shape, w.L, w.n_chunks, w.nq)
+    scores = torch.full((w.L_ctx,), -7.0, dtype=torch.float32, device="cuda")
+    qi = torch.zeros(w.nq, dtype=torch.int32, device="cuda")
+    ctx.fr_score_select(H.dev(w.q_question, dt), w.nq, H.dev(k_ctx, dt), w.chunk_offsets, 0, norm, scores, qi)
+    torch.cuda.synchronize()
+    assert H.max_rel_err(scores.cpu().numpy().astype(np.float64), want) <= SCORE_TOL
+    # from a chunk store, the keys moved on the way.  The fp32 rotation may differ from the position shift's in its last bit,
+    # and an element that lies between two bf16 numbers may then round the other way: 2^-8 of one element, which is
+    # |q_e k_e| 2^-8 / sqrt(d) on a unit-scale logit, at most 5e-3 for elements of four standard deviations each.
+    store = torch.cat([torch.zeros_like(H.dev(w.k_cached, dt))[:5], H.dev(w.k_cached, dt)])
+    shifted = torch.zeros_like(H.dev(w.k_cached, dt))
+    scores2, scores3 = torch.zeros_like(scores), torch.zeros_like(scores)
+    ctx.fr_rope_shift(H.dev(w.k_cached, dt), shifted, w.chunk_offsets, w.src_pos0)
+    ctx.fr_score_select(H.dev(w.q_question, dt), w.nq, shifted, w.chunk_offsets, 0, norm, scores2, qi)
+    ctx.fr_score_select_shared(H.dev(w.q_question, dt), w.nq, store, len(store), w.chunk_offsets, w.chunk_offsets[:-1] + 5, w.src_pos0,
+                               0, norm, scores3, qi)
+    torch.cuda.synchronize()
+    assert H.max_rel_err(scores3.cpu().numpy(), scores2.cpu().numpy()) <= 5e-3
+    ctx.close()
+
+
+@pytest.mark.parametrize("norm", [B.FR_NORM_PER_CHUNK, B.FR_NORM_GLOBAL])
+def test_scores_beyond_the_first_reference(norm):
+    """Logits far above those of a chunk's first 16 keys: the column ranges that overflow are repeated with exact maxima."""
+    shape = synth.LLAMA3_8B_BF16
+    w = synth.config_small_bf16(seed=3, chunk_lens=(300, 150), nq=20, shape=shape)
+    q, k = w.q_question.copy(), w.k_cached.copy()
+    q[:, :, 0] = 60.0
+    k[:, :, 0] = 0.0
+    k[[100, 101, 170, 350], :, 0] = 45.0
+    q, k = synth.round_to_storage(q, "bf16"), synth.round_to_storage(k, "bf16")
+    want = orc.critical_scores(q, k, w.chunk_offsets, "global" if norm == B.FR_NORM_GLOBAL else "per_chunk")
+    ctx = H.make_ctx(shape, w.L, w.n_chunks, w.nq)
+    scores = torch.zeros(w.L_ctx, dtype=torch.float32, device="cuda")
+    qi = torch.zeros(w.nq, dtype=torch.int32, device="cuda")
+    ctx.fr_score_select(H.dev(q, "bf16"), w.nq, H.dev(k, "bf16"), w.chunk_offsets, 0, norm, scores, qi)
+    torch.cuda.synchronize()
+    # exponents of several hundred: 2^-24 of them is 2^-14 of a weight
+    assert H.max_rel_err(scores.cpu().numpy().astype(np.float64), want) <= 2e-4
+    ctx.close()
