@@ -514,7 +514,7 @@ static fr_status check_rows(fr_ctx* ctx, int32_t R, int64_t L) {
     return FR_OK;
 }
 
-// Attention over a cache of the query's own (or a gathered copy): tiled kernels, or the generic one.
+// Attention over a cache of the query's own (or a gathered copy): tiled kernels, or the one with fp32 products.
 static hipError_t attn_over_cache(fr_ctx* ctx, const void* q_rows, const int32_t* q_index, int32_t R, const void* k_cache,
                                   const void* v_cache, int64_t L, const void* k_new, const void* v_new, void* out,
                                   float* lse_out, bool writeback, hipStream_t hs) {
@@ -522,14 +522,8 @@ static hipError_t attn_over_cache(fr_ctx* ctx, const void* q_rows, const int32_t
     if (attn_mfma_supported(s))   // (the tiled path finds the fresh rows of a key tile while it packs the tile)
         return launch_attn_mfma(s, q_rows, q_index, R, k_cache, v_cache, L, k_new, v_new, out, lse_out, ctx->ws,
                                 ctx->attn_softmax_mode, ctx->attn_split_mode, nullptr, &ctx->attn_timer, writeback, hs);
-    const int32_t* inv = nullptr;   // position -> fresh row map
-    if (k_new) {
-        hipError_t e = launch_inv_index(q_index, R, L, ctx->ws.inv_index, hs);
-        if (e != hipSuccess) return e;
-        inv = ctx->ws.inv_index;
-    }
-    hipError_t e = launch_attn_simt(s, q_rows, q_index, R, k_cache, v_cache, L, k_new, v_new, inv, out, lse_out, hs);
-    if (e == hipSuccess && writeback)   // the generic kernel has no packing pass to fuse it into
+    hipError_t e = launch_attn_f32(s, q_rows, q_index, R, k_cache, v_cache, L, k_new, v_new, ctx->ws.inv_index, out, lse_out, hs);
+    if (e == hipSuccess && writeback)   // this kernel has no packing pass to fuse it into
         e = launch_kv_scatter(s, k_new, v_new, q_index, R, const_cast<void*>(k_cache), const_cast<void*>(v_cache), L, hs);
     return e;
 }

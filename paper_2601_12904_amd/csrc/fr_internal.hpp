@@ -42,7 +42,7 @@ struct Workspace {
     float* col_partial = nullptr;   // [col_splits][Hkv][max_ctx] column sums per range of question columns and KV head
     int col_splits = 0;
     float* scores = nullptr;        // [max_tokens]
-    int32_t* inv_index = nullptr;   // [max_tokens] position -> row of k_new / -1
+    int32_t* inv_index = nullptr;   // [max_tokens] position -> row of k_new / -1 (launch_attn_f32)
     int32_t* store_row_map = nullptr;   // [max_tokens] prompt position -> row of the shared chunk store / -1
     int32_t* chunk_id_map = nullptr;    // [max_tokens] prompt position -> chunk
     float* qsum = nullptr;              // [Hkv][d] question queries summed per KV head (raw scores), then partial sums
@@ -180,10 +180,9 @@ struct SharedStoreArgs {
     const float2* table;
 };
 
-hipError_t launch_inv_index(const int32_t* q_index, int R, int64_t L, int32_t* inv, hipStream_t st);
-hipError_t launch_attn_simt(const Shape& s, const void* q_rows, const int32_t* q_index, int R,
-                            const void* k_cache, const void* v_cache, int64_t L, const void* k_new,
-                            const void* v_new, const int32_t* inv, void* out, float* lse, hipStream_t st);
+hipError_t launch_attn_f32(const Shape& s, const void* q_rows, const int32_t* q_index, int R, const void* k_cache,
+                           const void* v_cache, int64_t L, const void* k_new, const void* v_new, int32_t* inv, void* out,
+                           float* lse, hipStream_t st);
 bool attn_mfma_supported(const Shape& s);
 bool attn_mfma_store_supported(const Shape& s);   // also over a chunk store (launch_attn_mfma with `shared`, and the batch)
 hipError_t launch_attn_mfma(const Shape& s, const void* q_rows, const int32_t* q_index, int R,

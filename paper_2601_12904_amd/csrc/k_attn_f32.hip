@@ -1,0 +1,189 @@
+// Sparse prefill attention (eq. 9, Sec. 4.3) with fp32 products on the matrix cores: fp32 contexts, and bf16 contexts with
+// more query heads per KV head than the tiled kernel takes.
+//
+// One workgroup = one KV head x 16 query columns ((row, query head) pairs, the heads of the group fastest), its waves deal
+// the key blocks of 16 among themselves (wave w takes blocks w, w + W, ...), each with a running softmax of its own, and are
+// merged through LDS once at the end.  The shapes served here are small (verification runs of a few hundred tokens), so what
+// bounds the kernel is latency: with one wave per column tile the chip would hold a few dozen waves that walk dozens of
+// blocks each; dealt to 16 waves every wave has two or three.  S^T = K Q^T and O^T = V^T P^T with
+// v_mfma_f32_16x16x4_f32: keys on the register dimension of S^T, columns on lanes, and register i of the weights is
+// exactly the B operand of step i of the second product (its contraction index kg is key 4 kg + i), so the weights never
+// leave their registers.  Fresh rows are found through a position -> row map in LDS, built by the workgroup itself.
+// 4 heads, 109 rows, 544 positions, head_dim 64: 15.9 us; one wave per (row, head) on the vector ALU, behind a kernel that
+// built the map: 31.5 + 2.7 us.
+#include "fr_internal.hpp"
+
+#include <algorithm>
+
+namespace fr {
+
+namespace {
+
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+constexpr float NEG_BIG = -1.0e30f;
+constexpr int MAP_MAX_L = 8192;   // positions whose map fits LDS beside the rest (16-bit row numbers: 16 KB)
+
+template <typename T>
+__device__ __forceinline__ f32x4 load4(const T* p) {
+    struct alignas(4 * sizeof(T)) V { T v[4]; };
+    const V t = *reinterpret_cast<const V*>(p);
+    return f32x4{Elem<T>::to_f32(t.v[0]), Elem<T>::to_f32(t.v[1]), Elem<T>::to_f32(t.v[2]), Elem<T>::to_f32(t.v[3])};
+}
+__device__ __forceinline__ float column_max(float v) { v = fmaxf(v, __shfl_xor(v, 16)); return fmaxf(v, __shfl_xor(v, 32)); }
+__device__ __forceinline__ float column_sum(float v) { v += __shfl_xor(v, 16); return v + __shfl_xor(v, 32); }
+
+template <typename T, int D, int W>
+__global__ __launch_bounds__(64 * W) void attn_f32_kernel(const T* __restrict__ q_rows, const int32_t* __restrict__ q_index, int R,
+                                                          const T* __restrict__ k_cache, const T* __restrict__ v_cache, int L,
+                                                          const T* __restrict__ k_new, const T* __restrict__ v_new,
+                                                          const int32_t* __restrict__ inv, T* __restrict__ out,
+                                                          float* __restrict__ lse, int Hq, int Hkv, int n_tiles, float scale_log2e) {
+    constexpr int NJ = D / 16, PITCH = D + 4;
+    __shared__ float o_lds[W][16][PITCH];
+    __shared__ float m_lds[W][16], l_lds[W][16];
+    __shared__ uint16_t row_of[MAP_MAX_L];   // fresh row + 1 of a position, 0 = none (only where `inv` is not given)
+    const int tid = threadIdx.x, lane = tid & 63, x = lane & 15, kg = lane >> 4, wave = tid >> 6;
+    const int g = blockIdx.x % Hkv, tile = n_tiles - 1 - blockIdx.x / Hkv;   // longest tiles first
+    const int G = Hq / Hkv, cols = R * G;
+    const int n = min(16 * tile + x, cols - 1), r = n / G, head = g * G + n % G;   // columns past the end: a copy of the last
+    const int pos = q_index[r];
+    const int p_max = q_index[min(16 * tile + 15, cols - 1) / G];   // rows ascend
+    const int n_blocks = min(p_max, L - 1) / 16 + 1;
+
+    const bool have_new = k_new != nullptr, own_map = have_new && inv == nullptr;
+    if (own_map) {   // rows up to the tile's last one, the others' positions are not visible
+        for (int j = tid; j < 16 * n_blocks; j += 64 * W) row_of[j] = 0;
+        __syncthreads();
+        const int last = min(16 * tile + 15, cols - 1) / G;
+        for (int i = tid; i <= last; i += 64 * W) {
+            const int p = q_index[i];
+            if (p >= 0 && p < 16 * n_blocks) row_of[p] = (uint16_t)(i + 1);
+        }
+        __syncthreads();
+    }
+    auto fresh_row = [&](int j) -> int { return own_map ? (int)row_of[j] - 1 : have_new ? inv[j] : -1; };
+    auto row_ptr = [&](int j, const T* cache, const T* fresh) -> const T* {
+        j = min(j, L - 1);
+        const int f = fresh_row(j);
+        return f >= 0 ? fresh + ((size_t)f * Hkv + g) * D : cache + ((size_t)j * Hkv + g) * D;
+    };
+
+    f32x4 qv[NJ];   // dims 16 j + 4 kg + e of this lane's column
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) qv[j] = load4(q_rows + ((size_t)r * Hq + head) * D + 16 * j + 4 * kg);
+    f32x4 o[NJ];    // O^T: dims 16 md + 4 kg + i of the column
+#pragma unroll
+    for (int md = 0; md < NJ; ++md) o[md] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float m = NEG_BIG, l = 0.f;
+    f32x4 kv[NJ];
+    auto load_k = [&](int b) {
+        const T* p = row_ptr(16 * b + x, k_cache, k_new) + 4 * kg;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) kv[j] = load4(p + 16 * j);
+    };
+    if (wave < n_blocks) load_k(wave);
+    for (int b = wave; b < n_blocks; b += W) {
+        float vv[4][NJ];   // values of keys 4 kg + i, dims 16 md + x
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const T* p = row_ptr(16 * b + 4 * kg + i, v_cache, v_new) + x;
+#pragma unroll
+            for (int md = 0; md < NJ; ++md) vv[i][md] = Elem<T>::to_f32(p[16 * md]);
+        }
+        f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {   // two chains
+            s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[j][0], qv[j][0], s0, 0, 0, 0);
+            s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[j][1], qv[j][1], s1, 0, 0, 0);
+            s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[j][2], qv[j][2], s0, 0, 0, 0);
+            s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[j][3], qv[j][3], s1, 0, 0, 0);
+        }
+        if (b + W < n_blocks) load_k(b + W);
+        f32x4 s = s0 + s1;
+        float mx = NEG_BIG;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (16 * b + 4 * kg + i > pos) s[i] = -INFINITY;
+            mx = fmaxf(mx, s[i] * scale_log2e);
+        }
+        const float m_new = fmaxf(m, column_max(mx)), alpha = __builtin_amdgcn_exp2f(m - m_new);
+        m = m_new;
+        float p[4], psum = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            p[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i], scale_log2e, -m_new));
+            psum += p[i];
+        }
+        l = l * alpha + psum;
+#pragma unroll
+        for (int md = 0; md < NJ; ++md) o[md] *= alpha;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int md = 0; md < NJ; ++md) o[md] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[i][md], p[i], o[md], 0, 0, 0);
+    }
+    // ---- merge the waves ---------------------------------------------------------------------------------------------
+    l = column_sum(l);
+    if (kg == 0) { m_lds[wave][x] = m; l_lds[wave][x] = l; }
+    __syncthreads();
+    float M = NEG_BIG;
+    for (int w = 0; w < W; ++w) M = fmaxf(M, m_lds[w][x]);
+    const float f = __builtin_amdgcn_exp2f(m - M);   // (a wave without a visible key: m = NEG_BIG, factor 0)
+#pragma unroll
+    for (int md = 0; md < NJ; ++md) *reinterpret_cast<f32x4*>(&o_lds[wave][x][16 * md + 4 * kg]) = o[md] * f;
+    __syncthreads();
+    for (int i = tid; i < 16 * D; i += 64 * W) {
+        const int c = i / D, e = i % D, nc = 16 * tile + c;
+        if (nc >= cols) continue;
+        float mc = NEG_BIG, lc = 0.f, v = 0.f;
+        for (int w = 0; w < W; ++w) mc = fmaxf(mc, m_lds[w][c]);
+        for (int w = 0; w < W; ++w) {
+            lc += l_lds[w][c] * __builtin_amdgcn_exp2f(m_lds[w][c] - mc);
+            v += o_lds[w][c][e];
+        }
+        const size_t oc = (size_t)(nc / G) * Hq + g * G + nc % G;
+        out[oc * D + e] = Elem<T>::from_f32(v / lc);
+        if (e == 0 && lse != nullptr) lse[oc] = (mc + __builtin_amdgcn_logf(lc)) * 0.6931471805599453f;
+    }
+}
+
+// inv[j] = row r of k_new / v_new that holds the recomputed entry of position j, else -1: prompts whose map does not fit LDS.
+__global__ __launch_bounds__(256) void inv_index_kernel(const int32_t* __restrict__ q_index, int R, int64_t L, int32_t* __restrict__ inv) {
+    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (j >= L) return;
+    int lo = 0, hi = R;   // first r with q_index[r] >= j
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (q_index[mid] < j) lo = mid + 1; else hi = mid;
+    }
+    inv[j] = (lo < R && q_index[lo] == j) ? lo : -1;
+}
+
+}  // namespace
+
+// `inv`: device scratch of L ints.
+hipError_t launch_attn_f32(const Shape& s, const void* q_rows, const int32_t* q_index, int R, const void* k_cache,
+                           const void* v_cache, int64_t L, const void* k_new, const void* v_new, int32_t* inv, void* out,
+                           float* lse, hipStream_t st) {
+    if (R == 0) return hipSuccess;
+    if (k_new == nullptr || L <= MAP_MAX_L)
+        inv = nullptr;
+    else
+        inv_index_kernel<<<dim3((unsigned)((L + 255) / 256)), dim3(256), 0, st>>>(q_index, R, L, inv);
+    const int n_tiles = (int)(((int64_t)R * s.G + 15) / 16);
+    const dim3 grid((unsigned)(n_tiles * s.Hkv));
+    const float scale_log2e = (1.0f / sqrtf((float)s.d)) * 1.4426950408889634f;
+#define FR_ATTN_LAUNCH(T, D, W)                                                                                             \
+    attn_f32_kernel<T, D, W><<<grid, dim3(64 * W), 0, st>>>((const T*)q_rows, q_index, R, (const T*)k_cache, (const T*)v_cache, \
+                                                            (int)L, (const T*)k_new, (const T*)v_new, inv, (T*)out, lse, s.Hq, \
+                                                            s.Hkv, n_tiles, scale_log2e)
+    if (s.dtype == FR_BF16) {
+        if (s.d == 64) FR_ATTN_LAUNCH(__bf16, 64, 16); else FR_ATTN_LAUNCH(__bf16, 128, 8);
+    } else {
+        if (s.d == 64) FR_ATTN_LAUNCH(float, 64, 16); else FR_ATTN_LAUNCH(float, 128, 8);
+    }
+#undef FR_ATTN_LAUNCH
+    return hipGetLastError();
+}
+
+}  // namespace fr

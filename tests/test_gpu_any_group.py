@@ -148,3 +148,25 @@ def test_scores_beyond_the_first_reference(norm):
     # exponents of several hundred: 2^-24 of them is 2^-14 of a weight
     assert H.max_rel_err(scores.cpu().numpy().astype(np.float64), want) <= 2e-4
     ctx.close()
+
+
+# fp32 products (fp32 storage; bf16 with more than 64 heads per KV head): sums of a few hundred fp32 terms, 1e-5 of the
+# largest output as everywhere for fp32; prompts below and above the size whose position map fits LDS (8192), column tiles
+# with rows of several and of less than one tile, fewer key blocks than waves.
+@pytest.mark.parametrize("Hq,Hkv,d,dt,lens,nq,ratio", [(4, 4, 64, "f32", (5,), 3, 0.5), (4, 4, 64, "f32", (128, 77), 32, 0.15),
+                                                       (6, 2, 64, "f32", (300, 0, 129), 17, 1.0), (5, 1, 128, "f32", (260, 40), 9, 0.2),
+                                                       (2, 1, 64, "f32", (8100, 200), 21, 0.01), (80, 1, 64, "bf16", (90, 60), 5, 0.2)])
+def test_attention_with_fp32_products(Hq, Hkv, d, dt, lens, nq, ratio):
+    shape = synth.LayerShape(n_q_heads=Hq, n_kv_heads=Hkv, head_dim=d, dtype=dt, rope_base=500000.0)
+    w = synth.config_small_bf16(seed=Hq + nq, ratio=ratio, chunk_lens=lens, nq=nq, shape=shape)
+    k_ctx, _, k, qi = staged(w)
+    k_cache, v_cache = assembled_cache(w, k_ctx)
+    ctx = H.make_ctx(w.shape, w.L, w.n_chunks, w.nq)
+    tol = 1e-5 if dt == "f32" else OUT_TOL
+    for with_new in (True, False):
+        kc, vc = (k_cache, v_cache) if with_new else orc.kv_scatter(qi, w.k_full[qi], w.v_full[qi], k_cache, v_cache)
+        got, lse = run_attention(ctx, w, qi, kc, vc, with_new=with_new)
+        want, want_lse = orc.sparse_prefill_attn(w.q_full[qi], qi, k_cache, v_cache, w.k_full[qi], w.v_full[qi])
+        assert H.max_rel_err(got, want) <= tol
+        assert np.max(np.abs(lse - want_lse)) <= 1e-5
+    ctx.close()
