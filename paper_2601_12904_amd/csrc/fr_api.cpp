@@ -153,7 +153,7 @@ fr_status fr_create(const fr_layer_desc* desc, int64_t max_tokens, int32_t max_c
     w.attn_partials_bytes = tiled ? attn_mfma_partials_bytes(s, max_tokens) : 0;
     const size_t o_part = take(w.attn_partials_bytes);
     const size_t o_dpart = take(decode_partials_bytes(s));
-    const size_t o_drot = take(decode_rot_table_bytes(s));
+    const size_t o_theta = take((size_t)(s.d / 2) * sizeof(double));
     const size_t o_rr = take((size_t)max_tokens * (s.d / 2) * sizeof(float2));
     w.gemm_partials_bytes = (s.dtype == FR_BF16) ? gemm_partials_bytes() : 0;
     const size_t o_gp = take(w.gemm_partials_bytes);
@@ -176,7 +176,10 @@ fr_status fr_create(const fr_layer_desc* desc, int64_t max_tokens, int32_t max_c
     w.store_row_map = (int32_t*)(w.base + o_srow);
     w.chunk_id_map = (int32_t*)(w.base + o_cid);
     w.select_tmp = (uint32_t*)(w.base + o_sel);
-    if (hipMemset(w.select_tmp, 0, select_zeroed_bytes()) != hipSuccess) {   // the selection expects (and leaves) it zero
+    double theta[64];
+    for (int p = 0; p < s.d / 2; ++p) theta[p] = pow(s.rope_base, -2.0 * (double)(p + s.rope_index_base) / (double)s.d);
+    if (hipMemset(w.select_tmp, 0, select_zeroed_bytes()) != hipSuccess ||   // the selection expects (and leaves) it zero
+        hipMemcpy(w.base + o_theta, theta, (size_t)(s.d / 2) * sizeof(double), hipMemcpyHostToDevice) != hipSuccess) {
         (void)hipFree(w.base);
         w.base = nullptr;
         delete ctx;
@@ -187,7 +190,7 @@ fr_status fr_create(const fr_layer_desc* desc, int64_t max_tokens, int32_t max_c
     w.kv_images = (unsigned char*)(w.base + o_img);
     w.attn_partials = (float*)(w.base + o_part);
     w.decode_partials = (float*)(w.base + o_dpart);
-    w.decode_rot = (float2*)(w.base + o_drot);
+    w.rope_theta = (double*)(w.base + o_theta);
     w.rope_rows = (float2*)(w.base + o_rr);
     w.gemm_partials = w.gemm_partials_bytes ? (float*)(w.base + o_gp) : nullptr;
     w.store_k = store_copy_bytes ? (void*)(w.base + o_sk) : nullptr;
@@ -785,7 +788,7 @@ fr_status fr_decode_attn(fr_ctx* ctx, const void* q, int32_t n_queries, const vo
     a.k_pages = k_pages; a.v_pages = v_pages; a.page_stride = page_stride_rows; a.page_len = page_len;
     a.out = out; a.lse_out = lse_out;
     a.force_generic = ctx->decode_generic;
-    hipError_t e = launch_decode_attn(ctx->shape, a, ctx->ws.decode_partials, ctx->ws.decode_rot, (hipStream_t)stream);
+    hipError_t e = launch_decode_attn(ctx->shape, a, ctx->ws.decode_partials, ctx->ws.rope_theta, ctx->ws.n_cu, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(ctx, "decode attention launch", e);
     return FR_OK;
 }

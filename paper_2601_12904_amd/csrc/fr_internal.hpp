@@ -55,8 +55,8 @@ struct Workspace {
     float* gemm_partials = nullptr; // partial sums of the GEMM tiles that are split along K
     size_t gemm_partials_bytes = 0;
     float2* rope_rows = nullptr;    // [max_tokens][d/2] (cos, sin) of the recomputed rows' positions
-    float* decode_partials = nullptr;    // [DECODE_MAX_UNITS][Hq][d + 2] partial softmax results of fr_decode_attn
-    float2* decode_rot = nullptr;        // [DECODE_MAX_UNITS][d/2] (cos, sin) of the segments' position shifts
+    float* decode_partials = nullptr;    // [DECODE_MAX_UNITS][Hq][d + 2] partial softmax results of fr_decode_attn's pieces
+    double* rope_theta = nullptr;        // [d/2] rotary frequencies base^(-2 (p + index_base) / d)
     float* attn_partials = nullptr;      // partial results of an attention launch whose items are computed in parts
     size_t attn_partials_bytes = 0;
     unsigned char* kv_images = nullptr;  // [Hkv][ceil(max_tokens / 64)] LDS-ready K / V^T tile images
@@ -164,11 +164,11 @@ struct DecodeArgs {
     void* out; float* lse_out;
     int force_generic;   // 1: the all-vector-ALU kernel also where the matrix-core one applies (tests)
 };
-constexpr int DECODE_MAX_UNITS = 4096;   // segments + queries of one call (sizes the partial-result buffer)
+constexpr int DECODE_MAX_UNITS = 4096;   // segments + queries of one call, and their pieces (sizes the partial-result buffer)
 bool decode_supported(const Shape& s);
 size_t decode_partials_bytes(const Shape& s);
-size_t decode_rot_table_bytes(const Shape& s);
-hipError_t launch_decode_attn(const Shape& s, const DecodeArgs& a, float* partials, float2* rot_table, hipStream_t st);
+// theta: device, [d/2] rotary frequencies
+hipError_t launch_decode_attn(const Shape& s, const DecodeArgs& a, float* partials, const double* theta, int n_cu, hipStream_t st);
 hipError_t launch_mark_stale(uint32_t* bits, int64_t n_words, const int32_t* rows, int n_rows, int clear, hipStream_t st);
 
 // When given to launch_attn_mfma, k_cache / v_cache are a chunk store shared between queries: prompt position
@@ -240,5 +240,34 @@ struct Elem<__bf16> {
     static __device__ __forceinline__ float to_f32(__bf16 v) { return (float)v; }
     static __device__ __forceinline__ __bf16 from_f32(float v) { return (__bf16)v; }  // nearest-even
 };
+
+// sin and cos of a rotation angle in fp64: reduced to [-pi/4, pi/4] by multiples of pi/2 (two-part constant, fused
+// multiply-adds), then the Taylor polynomials of degree 15 and 16, whose remainders there are below 5e-17.  About 25
+// instructions where the library's routine, with its path for arguments of any size, has over a hundred.  |x| < 2^31.
+__device__ __forceinline__ void sincos_reduced(double x, double* sn, double* cs) {
+    const double k = __builtin_rint(x * 0.63661977236758134308);   // 2 / pi
+    double r = __builtin_fma(-k, 1.57079632679489661923, x);
+    r = __builtin_fma(-k, 6.12323399573676603587e-17, r);          // pi / 2 beyond its leading 53 bits
+    const double z = r * r;
+    double s = -1.0 / 1307674368000.0, c = 1.0 / 20922789888000.0;  // 1/15!, 1/16!
+    s = __builtin_fma(s, z, 1.0 / 6227020800.0);
+    c = __builtin_fma(c, z, -1.0 / 87178291200.0);
+    s = __builtin_fma(s, z, -1.0 / 39916800.0);
+    c = __builtin_fma(c, z, 1.0 / 479001600.0);
+    s = __builtin_fma(s, z, 1.0 / 362880.0);
+    c = __builtin_fma(c, z, -1.0 / 3628800.0);
+    s = __builtin_fma(s, z, -1.0 / 5040.0);
+    c = __builtin_fma(c, z, 1.0 / 40320.0);
+    s = __builtin_fma(s, z, 1.0 / 120.0);
+    c = __builtin_fma(c, z, -1.0 / 720.0);
+    s = __builtin_fma(s, z, -1.0 / 6.0);
+    c = __builtin_fma(c, z, 1.0 / 24.0);
+    s = __builtin_fma(s * z, r, r);
+    c = __builtin_fma(__builtin_fma(c, z, -0.5), z, 1.0);
+    const int q = (int)((long long)k & 3);
+    const double a = (q & 1) ? c : s, b = (q & 1) ? s : c;
+    *sn = (q & 2) ? -a : a;
+    *cs = (q == 1 || q == 2) ? -b : b;
+}
 
 }  // namespace fr

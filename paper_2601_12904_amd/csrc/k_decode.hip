@@ -9,11 +9,13 @@
 // K/V, the question's and the generated tokens' live in the query's exclusive page, which is one more segment
 // (delta 0, no mask).
 //
-// HBM-bound streaming (2 flop per byte): one workgroup per (segment or page, KV head), every lane reads 16
+// HBM-bound streaming (2 flop per byte): one workgroup per (piece of a segment or page, KV head), every lane reads 16
 // bytes of a key row and of the matching value row, the LPK lanes of a row reduce their partial dot products
 // by shuffles, all vector-ALU work is in fp32.  Every lane keeps an online-softmax state for the rows it has
 // seen; lanes, waves and finally the segments of a query are merged in a fixed order (reproducible results).
 #include "fr_internal.hpp"
+
+#include <algorithm>
 
 namespace fr {
 
@@ -60,16 +62,33 @@ __device__ __forceinline__ float row_group_sum(float t) {
     return t;
 }
 
-// Partial result of one (unit, query head): [m (base-2 exponent reference), l, o[D]] in fp32.
+// (cos, sin)(delta theta_pair) of a segment, by the workgroup itself (threads 0 .. D/2 - 1): fp64, rounded once.  A kernel
+// of its own for the table was 4.7 us per call; here the first rows' loads are in flight meanwhile.
+template <int D>
+__device__ __forceinline__ void rotation_table(float2 (&rot)[D / 2], int delta, const double* __restrict__ theta) {
+    if (threadIdx.x < D / 2) {
+        double sn = 0.0, cs = 1.0;
+        if (delta != 0) sincos_reduced((double)delta * theta[threadIdx.x], &sn, &cs);
+        rot[threadIdx.x] = make_float2((float)cs, (float)sn);
+    }
+}
+
+// Units are cut into pieces so that a batch of few queries fills the chip too: every segment into `seg` pieces, every page
+// into `page` of them (equal shares of whole 32-row blocks; the lengths are device data, so the host goes by counts only).
+struct Pieces {
+    int seg, page;
+};
+
+// Partial result of one (piece, query head): [m (base-2 exponent reference), l, o[D]] in fp32.
 template <int D>
 constexpr int part_floats() { return D + 2; }
 
-// What a workgroup streams.  unit u < n_seg: segment u of the shared store; unit n_seg + b: the exclusive page of
-// query b.  The pages are usually the longest units, so the grid starts with them (blockIdx.x < B) and the tail
+// What a workgroup streams: a piece of unit u.  u < n_seg: segment u of the shared store; u = n_seg + b: the exclusive page
+// of query b.  The pages are usually the longest units, so the grid starts with their pieces and the tail
 // consists of segments.  Rows outside the tensors are never read, whatever the descriptors say.
 template <typename T>
 struct Unit {
-    int unit, b, delta;
+    int piece, b, delta;   // piece: index of its partial result (segments' pieces first)
     int64_t row0, len;
     const T *kbase, *vbase;
     const uint32_t* stale;
@@ -77,20 +96,28 @@ struct Unit {
                                             const int32_t* seg_offsets, const int32_t* seg_row0, const int32_t* seg_len,
                                             const int32_t* seg_delta, int n_seg, const uint32_t* stale_bits,
                                             int64_t stale_words, const T* k_pages, const T* v_pages, int64_t page_stride,
-                                            const int32_t* page_len, size_t row_elems) {
-        unit = ((int)blockIdx.x < B) ? n_seg + (int)blockIdx.x : (int)blockIdx.x - B;
+                                            const int32_t* page_len, size_t row_elems, Pieces pc) {
+        const int n_page = B * pc.page, at = (int)blockIdx.x;
+        const int parts = at < n_page ? pc.page : pc.seg;
+        const int part = (at < n_page ? at : at - n_page) % parts;
+        const int unit = at < n_page ? n_seg + at / parts : (at - n_page) / parts;
+        piece = at < n_page ? n_seg * pc.seg + at : at - n_page;
         stale = nullptr;
         int64_t limit;
         if (unit < n_seg) {
-            int lo = 0, hi = B;   // largest b with seg_offsets[b] <= unit
-            while (hi - lo > 1) {
-                const int mid = (lo + hi) >> 1;
-                if (seg_offsets[mid] <= unit) lo = mid; else hi = mid;
-            }
-            b = lo;
             row0 = seg_row0[unit];
             len = seg_len[unit];
             delta = seg_delta[unit];
+            // largest b with seg_offsets[b] <= unit: every wave looks at 64 offsets at once (they ascend), so that a batch of
+            // up to 64 queries costs one load, beside those above, in front of everything else
+            b = 0;
+            for (int from = 1; from < B; from += 64) {
+                const int at = from + (int)(threadIdx.x & 63);
+                const int below = __popcll(__ballot(at < B && seg_offsets[min(at, B - 1)] <= unit));
+                b += below;
+                if (below < 64) break;
+            }
+            b = __builtin_amdgcn_readfirstlane(b);
             kbase = k_shared;
             vbase = v_shared;
             limit = n_shared;
@@ -107,6 +134,9 @@ struct Unit {
         if (row0 < 0) { len += row0; row0 = 0; }
         if (row0 + len > limit) len = limit - row0;
         if (len < 0) len = 0;
+        const int64_t per = (len + 32 * parts - 1) / (32 * parts) * 32, skip = min(len, per * part);
+        row0 += skip;
+        len = min(per, len - skip);
     }
 };
 
@@ -117,8 +147,8 @@ __global__ __launch_bounds__(256) void decode_partial_kernel(
     const int32_t* __restrict__ seg_offsets, const int32_t* __restrict__ seg_row0, const int32_t* __restrict__ seg_len,
     const int32_t* __restrict__ seg_delta, int n_seg, const uint32_t* __restrict__ stale_bits, int64_t stale_words,
     const T* __restrict__ k_pages, const T* __restrict__ v_pages, int64_t page_stride, const int32_t* __restrict__ page_len,
-    int Hq, int Hkv, const float2* __restrict__ rot_table, int rope_layout, float scale_log2e,
-    float* __restrict__ partials) {
+    int Hq, int Hkv, const double* __restrict__ theta, int rope_layout, float scale_log2e,
+    float* __restrict__ partials, Pieces pc) {
     constexpr int N = Row16<T>::N;              // elements per 16-byte vector
     constexpr int LPK = D / N;                  // lanes per key row (8, 16 or 32)
     constexpr int KPW = 64 / LPK;               // key rows per wave and step
@@ -131,8 +161,11 @@ __global__ __launch_bounds__(256) void decode_partial_kernel(
     const size_t row_elems = (size_t)Hkv * D;
     Unit<T> un;
     un.resolve(B, k_shared, v_shared, n_shared, seg_offsets, seg_row0, seg_len, seg_delta, n_seg, stale_bits, stale_words,
-               k_pages, v_pages, page_stride, page_len, row_elems);
-    const int unit = un.unit, b = un.b, delta = un.delta;
+               k_pages, v_pages, page_stride, page_len, row_elems, pc);
+    const int b = un.b;
+    __shared__ float2 rot[D / 2];
+    rotation_table<D>(rot, un.delta, theta);
+    __syncthreads();
     const int64_t row0 = un.row0, len = un.len;
     const T *kbase = un.kbase, *vbase = un.vbase;
     const uint32_t* stale = un.stale;
@@ -147,8 +180,7 @@ __global__ __launch_bounds__(256) void decode_partial_kernel(
             const int idx = e0 + e;
             const int pair = (rope_layout == FR_ROPE_INTERLEAVED) ? (idx >> 1) : (idx % (D / 2));
             const bool first = (rope_layout == FR_ROPE_INTERLEAVED) ? ((idx & 1) == 0) : (idx < D / 2);
-            float2 t = make_float2(1.f, 0.f);
-            if (delta != 0) t = rot_table[(size_t)unit * (D / 2) + pair];   // (cos, sin)(delta theta_pair)
+            const float2 t = rot[pair];   // (cos, sin)(delta theta_pair)
             cs[e] = t.x;
             sn[e] = first ? t.y : -t.y;   // RoPE(q, -delta): a' = a cos + b sin, b' = b cos - a sin
         }
@@ -266,7 +298,7 @@ __global__ __launch_bounds__(256) void decode_partial_kernel(
             lt += merge[w][col][1] * a;
             ot += merge[w][col][2 + e] * a;
         }
-        float* dst = partials + ((size_t)unit * Hq + g * G + col) * PF;
+        float* dst = partials + ((size_t)un.piece * Hq + g * G + col) * PF;
         if (e == 0) { dst[0] = mt; dst[1] = lt; }
         dst[2 + e] = ot;
     }
@@ -275,9 +307,9 @@ __global__ __launch_bounds__(256) void decode_partial_kernel(
 
 // bf16, head_dim 128: the logits come from the matrix cores, the value product stays on the vector ALU.
 // Per wave and block of 32 key rows:
-//   * S^T = K q^T with v_mfma_f32_32x32x16_bf16: the A operand (32 key rows x 16 dims per step) is read straight
-//     from memory, 16 bytes per lane (lane = (row x, 8-dim half h)); the B operand holds the G rotated queries in
-//     columns 0..G-1 (the other columns are zero);
+//   * S^T = K q^T with v_mfma_f32_16x16x32_bf16: the A operand (16 key rows x 32 dims per step) is read straight
+//     from memory, 16 bytes per lane (lane = (row x, 8-dim quarter kg): 64 contiguous bytes of a row per instruction,
+//     where a 32 x 32 tile has 32); the B operand holds the G rotated queries in columns 0..G-1 (the other columns are zero);
 //   * the G lanes that own a query column (and their partners for the other 4-row groups) run the online softmax
 //     and leave the 32 x G weights and the G rescale factors in LDS;
 //   * O += P V with the lanes regrouped as (row r of 4, 16-byte slice c of the value row): coalesced value loads,
@@ -285,7 +317,7 @@ __global__ __launch_bounds__(256) void decode_partial_kernel(
 // Against the all-vector-ALU kernel this removes the dot products, their cross-lane reductions and the 16-fold
 // redundant exponentials: about 14 instead of 31 vector instructions per key row and lane.
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 template <int G>
 __global__ __launch_bounds__(256, 2) void decode_partial_mfma_kernel(
@@ -294,57 +326,29 @@ __global__ __launch_bounds__(256, 2) void decode_partial_mfma_kernel(
     const int32_t* __restrict__ seg_len, const int32_t* __restrict__ seg_delta, int n_seg,
     const uint32_t* __restrict__ stale_bits, int64_t stale_words, const __bf16* __restrict__ k_pages,
     const __bf16* __restrict__ v_pages, int64_t page_stride, const int32_t* __restrict__ page_len, int Hq, int Hkv,
-    const float2* __restrict__ rot_table, int rope_layout, float scale_log2e, float* __restrict__ partials) {
+    const double* __restrict__ theta, int rope_layout, float scale_log2e, float* __restrict__ partials,
+    Pieces pc) {
     constexpr int D = 128, PF = part_floats<D>();
     constexpr int GP = G < 4 ? 4 : G;                       // weights per row in LDS, padded to a 16-byte read
-    __shared__ float merge[4][G][PF];
+    __shared__ __attribute__((aligned(16))) float o_merge[4][4][G][D];   // per wave and row r of the value view
+    __shared__ float m_merge[4][G], l_merge[4][G];
     __shared__ __attribute__((aligned(16))) float p_lds[4][32][GP];
     __shared__ float alpha_lds[4][GP];
     __shared__ __attribute__((aligned(16))) __bf16 q_rot[G][D];
+    __shared__ float2 rot[D / 2];
 
     const int g = blockIdx.y;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int x = lane & 31, h = lane >> 5;                 // matrix view: key row (or query column) x, half h
+    const int x = lane & 15, kg = lane >> 4;                // matrix view: key row (or query column) x, quarter kg
     const int r = lane >> 4, c = lane & 15;                 // value view: row r of a step, 16-byte slice c
     const size_t row_elems = (size_t)Hkv * D;
     Unit<__bf16> un;
     un.resolve(B, k_shared, v_shared, n_shared, seg_offsets, seg_row0, seg_len, seg_delta, n_seg, stale_bits, stale_words,
-               k_pages, v_pages, page_stride, page_len, row_elems);
+               k_pages, v_pages, page_stride, page_len, row_elems, pc);
     const int64_t row0 = un.row0, len = un.len;
     const uint32_t* stale = un.stale;
 
-    // ---- the G queries of this KV head, rotated by -delta, rounded to bf16, through LDS into B-operand fragments ----
-    for (int idx = tid; idx < G * D; idx += 256) {
-        const int col = idx / D, e = idx % D;
-        const int pair = (rope_layout == FR_ROPE_INTERLEAVED) ? (e >> 1) : (e % (D / 2));
-        const bool first = (rope_layout == FR_ROPE_INTERLEAVED) ? ((e & 1) == 0) : (e < D / 2);
-        const int partner = (rope_layout == FR_ROPE_INTERLEAVED) ? (e ^ 1) : ((e + D / 2) % D);
-        float2 t = make_float2(1.f, 0.f);
-        if (un.delta != 0) t = rot_table[(size_t)un.unit * (D / 2) + pair];
-        const __bf16* qp = q + ((size_t)un.b * Hq + g * G + col) * D;
-        // RoPE(q, -delta): a' = a cos + b sin, b' = b cos - a sin
-        q_rot[col][e] = (__bf16)((float)qp[e] * t.x + (float)qp[partner] * (first ? t.y : -t.y));
-    }
-    __syncthreads();
-    bf16x8 qf[8];
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
-        if (x < G) {
-            qf[ks] = *reinterpret_cast<const bf16x8*>(&q_rot[x < G ? x : 0][16 * ks + 8 * h]);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) qf[ks][e] = (__bf16)0.0f;
-        }
-    }
-
-    float m = NEG_BIG, l = 0.f;        // of query column x (lanes x < G; the two halves h keep the same m)
-    float o[G][8];                     // value view: this lane's slice of the G output rows, over its key rows
-#pragma unroll
-    for (int col = 0; col < G; ++col)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) o[col][e] = 0.f;
-
-    const __bf16* kp = un.kbase + (size_t)g * D + 8 * h;    // + row * row_elems + 16 ks
+    const __bf16* kp = un.kbase + (size_t)g * D + 8 * kg;   // + row * row_elems + 32 ks
     const __bf16* vp = un.vbase + (size_t)g * D + 8 * c;    // + row * row_elems
     const int64_t n_blocks = (len + 31) / 32;
     uint4 kw[8], vw[8];
@@ -367,9 +371,12 @@ __global__ __launch_bounds__(256, 2) void decode_partial_mfma_kernel(
     // first row instead, which stays in the cache, so the skipped rows cost no memory traffic (their logits are masked
     // and their weights are zero).  No branch: the address is chosen, not the load.
     auto load_block = [&](int64_t bi, uint32_t okbits) {
-        const int64_t rk = ((okbits >> x) & 1u) ? row0 + 32 * bi + x : row0;
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) kw[ks] = *reinterpret_cast<const uint4*>(kp + (size_t)rk * row_elems + 16 * ks);
+        for (int u = 0; u < 2; ++u) {
+            const int64_t rk = ((okbits >> (16 * u + x)) & 1u) ? row0 + 32 * bi + 16 * u + x : row0;
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) kw[4 * u + ks] = *reinterpret_cast<const uint4*>(kp + (size_t)rk * row_elems + 32 * ks);
+        }
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
             const int64_t rv = ((okbits >> (4 * t + r)) & 1u) ? row0 + 32 * bi + 4 * t + r : row0;
@@ -379,14 +386,46 @@ __global__ __launch_bounds__(256, 2) void decode_partial_mfma_kernel(
     // the masks run one block ahead of the loads, the loads one block ahead of the arithmetic
     uint32_t ok_cur = rows_that_count(wave), ok_next = rows_that_count(wave + 4);
     if (wave < n_blocks) load_block(wave, ok_cur);
+    // ---- the G queries of this KV head, rotated by -delta, rounded to bf16, through LDS into B-operand fragments ----
+    rotation_table<D>(rot, un.delta, theta);
+    __syncthreads();
+    for (int idx = tid; idx < G * D; idx += 256) {
+        const int col = idx / D, e = idx % D;
+        const int pair = (rope_layout == FR_ROPE_INTERLEAVED) ? (e >> 1) : (e % (D / 2));
+        const bool first = (rope_layout == FR_ROPE_INTERLEAVED) ? ((e & 1) == 0) : (e < D / 2);
+        const int partner = (rope_layout == FR_ROPE_INTERLEAVED) ? (e ^ 1) : ((e + D / 2) % D);
+        const float2 t = rot[pair];
+        const __bf16* qp = q + ((size_t)un.b * Hq + g * G + col) * D;
+        // RoPE(q, -delta): a' = a cos + b sin, b' = b cos - a sin
+        q_rot[col][e] = (__bf16)((float)qp[e] * t.x + (float)qp[partner] * (first ? t.y : -t.y));
+    }
+    __syncthreads();
+    bf16x8 qf[4];
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+        if (x < G) {
+            qf[ks] = *reinterpret_cast<const bf16x8*>(&q_rot[x < G ? x : 0][32 * ks + 8 * kg]);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) qf[ks][e] = (__bf16)0.0f;
+        }
+    }
+
+    float m = NEG_BIG, l = 0.f;        // of query column x (lanes x < G; the four quarters keep the same m)
+    float o[G][8];                     // value view: this lane's slice of the G output rows, over its key rows
+#pragma unroll
+    for (int col = 0; col < G; ++col)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[col][e] = 0.f;
+
     for (int64_t bi = wave; bi < n_blocks; bi += 4) {
         // ---- logits of the block's 32 rows -----------------------------------------------------------------
-        f32x16 s;
+        f32x4 s[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-        for (int v = 0; v < 16; ++v) s[v] = 0.f;
+        for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks)
-            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kw[ks]), qf[ks], s, 0, 0, 0);
+            for (int u = 0; u < 2; ++u)
+                s[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kw[4 * u + ks]), qf[ks], s[u], 0, 0, 0);
         uint4 vcur[8];
 #pragma unroll
         for (int t = 0; t < 8; ++t) vcur[t] = vw[t];
@@ -395,27 +434,31 @@ __global__ __launch_bounds__(256, 2) void decode_partial_mfma_kernel(
         ok_cur = ok_next;
         ok_next = rows_that_count(bi + 8);
 
-        // ---- online softmax of column x over the 16 rows this lane holds: 8 (v / 4) + 4 h + v % 4 -----------
+        // ---- online softmax of column x over the 8 rows this lane holds: 16 u + 4 kg + i ---------------------
         float mx = NEG_BIG;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int key = 8 * (v >> 2) + 4 * h + (v & 3);
-            s[v] = ((okbits >> key) & 1u) ? s[v] * scale_log2e : -INFINITY;
-            mx = fmaxf(mx, s[v]);
-        }
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                s[u][i] = ((okbits >> (16 * u + 4 * kg + i)) & 1u) ? s[u][i] * scale_log2e : -INFINITY;
+                mx = fmaxf(mx, s[u][i]);
+            }
+        mx = fmaxf(mx, __shfl_xor(mx, 16));
         mx = fmaxf(mx, __shfl_xor(mx, 32));
         const float m_new = fmaxf(m, mx);
         const float alpha = __builtin_amdgcn_exp2f(m - m_new);
         m = m_new;
         float psum = 0.f;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const float p = __builtin_amdgcn_exp2f(s[v] - m_new);
-            psum += p;
-            if (x < G) p_lds[wave][8 * (v >> 2) + 4 * h + (v & 3)][x] = p;
-        }
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float p = __builtin_amdgcn_exp2f(s[u][i] - m_new);
+                psum += p;
+                if (x < G) p_lds[wave][16 * u + 4 * kg + i][x] = p;
+            }
         l = l * alpha + psum;
-        if (x < G && h == 0) alpha_lds[wave][x] = alpha;
+        if (x < G && kg == 0) alpha_lds[wave][x] = alpha;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // the wave's LDS writes precede its LDS reads below
         __builtin_amdgcn_wave_barrier();
 
@@ -447,78 +490,78 @@ __global__ __launch_bounds__(256, 2) void decode_partial_mfma_kernel(
     }
 
     // ---- merge inside the wave, then the four waves in wave order (as in the generic kernel) -----------------
+    l += __shfl_xor(l, 16);
     l += __shfl_xor(l, 32);
-    if (x < G && h == 0) { merge[wave][x][0] = m; merge[wave][x][1] = l; }
+    if (x < G && kg == 0) { m_merge[wave][x] = m; l_merge[wave][x] = l; }
 #pragma unroll
     for (int col = 0; col < G; ++col)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            float t = o[col][e];
-            t += __shfl_xor(t, 16);
-            t += __shfl_xor(t, 32);
-            if (r == 0) merge[wave][col][2 + 8 * c + e] = t;
-        }
+        for (int e = 0; e < 8; e += 4)
+            *reinterpret_cast<float4*>(&o_merge[wave][r][col][8 * c + e]) = make_float4(o[col][e], o[col][e + 1], o[col][e + 2], o[col][e + 3]);
     __syncthreads();
     for (int idx = tid; idx < G * D; idx += 256) {
         const int col = idx / D, e = idx % D;
         float mt = NEG_BIG;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) mt = fmaxf(mt, merge[w][col][0]);
+        for (int w = 0; w < 4; ++w) mt = fmaxf(mt, m_merge[w][col]);
         float lt = 0.f, ot = 0.f;
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
-            const float a = __builtin_amdgcn_exp2f(merge[w][col][0] - mt);
-            lt += merge[w][col][1] * a;
-            ot += merge[w][col][2 + e] * a;
+            const float a = __builtin_amdgcn_exp2f(m_merge[w][col] - mt);
+            lt += l_merge[w][col] * a;
+            ot += ((o_merge[w][0][col][e] + o_merge[w][1][col][e]) + (o_merge[w][2][col][e] + o_merge[w][3][col][e])) * a;
         }
-        float* dst = partials + ((size_t)un.unit * Hq + g * G + col) * PF;
+        float* dst = partials + ((size_t)un.piece * Hq + g * G + col) * PF;
         if (e == 0) { dst[0] = mt; dst[1] = lt; }
         dst[2 + e] = ot;
     }
 }
 
-// rot_table[u][p] = (cos, sin)(seg_delta[u] * theta_p), theta_p = base^(-2 (p + index_base) / d): fp64, rounded once.
-__global__ void decode_rot_table_kernel(const int32_t* __restrict__ seg_delta, int half_d, int d, double base,
-                                        int index_base, float2* __restrict__ table) {
-    const int u = blockIdx.x;
-    const double delta = (double)seg_delta[u];
-    for (int p = threadIdx.x; p < half_d; p += blockDim.x) {
-        const double theta = pow(base, -2.0 * (double)(p + index_base) / (double)d);
-        double sn, cs;
-        sincos(delta * theta, &sn, &cs);
-        table[(size_t)u * half_d + p] = make_float2((float)cs, (float)sn);
-    }
-}
-
-// One wave per (query, query head): merges the units of the query in a fixed order (its segments, then its page).
+// One workgroup per (query, query head): merges the pieces of the query's segments, then of its page.  Every wave takes
+// pieces w, w + 4, ... (their loads do not depend on one another: the weights come from the maximum over all pieces, found
+// first), the four waves are added in wave order.
 template <typename T, int D>
-__global__ __launch_bounds__(64) void decode_combine_kernel(const float* __restrict__ partials,
-                                                            const int32_t* __restrict__ seg_offsets, int n_seg, int Hq,
-                                                            T* __restrict__ out, float* __restrict__ lse_out) {
+__global__ __launch_bounds__(256) void decode_combine_kernel(const float* __restrict__ partials, const int32_t* __restrict__ seg_offsets,
+                                                             int n_seg, int Hq, Pieces pc, T* __restrict__ out,
+                                                             float* __restrict__ lse_out) {
     constexpr int PF = part_floats<D>();
     constexpr int EPT = D / 64;   // elements per lane
-    const int b = blockIdx.x, h = blockIdx.y, lane = threadIdx.x;
+    __shared__ float o_lds[4][D], l_lds[4], m_lds[4];
+    const int b = blockIdx.x, h = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int s0 = seg_offsets[b], s1 = seg_offsets[b + 1];
     s0 = max(0, min(s0, n_seg));
     s1 = max(s0, min(s1, n_seg));
-    float mt = NEG_BIG, lt = 0.f, ot[EPT];
+    const int from_seg = (s1 - s0) * pc.seg, n = from_seg + pc.page;
+    auto part = [&](int i) -> const float* {   // piece i of the query
+        const int piece = i < from_seg ? s0 * pc.seg + i : n_seg * pc.seg + b * pc.page + (i - from_seg);
+        return partials + ((size_t)piece * Hq + h) * PF;
+    };
+    float mt = NEG_BIG;
+    for (int i = threadIdx.x; i < n; i += 256) mt = fmaxf(mt, part(i)[0]);
+    for (int sft = 32; sft > 0; sft >>= 1) mt = fmaxf(mt, __shfl_xor(mt, sft));
+    if (lane == 0) m_lds[wave] = mt;
+    __syncthreads();
+    mt = fmaxf(fmaxf(m_lds[0], m_lds[1]), fmaxf(m_lds[2], m_lds[3]));
+    float lt = 0.f, ot[EPT];
 #pragma unroll
     for (int e = 0; e < EPT; ++e) ot[e] = 0.f;
-    for (int u = s0; u <= s1; ++u) {   // u == s1 stands for the page
-        const int unit = (u < s1) ? u : n_seg + b;
-        const float* p = partials + ((size_t)unit * Hq + h) * PF;
-        const float mu = p[0], lu = p[1];
-        const float m_new = fmaxf(mt, mu);
-        const float a_old = __builtin_amdgcn_exp2f(mt - m_new), a_new = __builtin_amdgcn_exp2f(mu - m_new);
-        lt = lt * a_old + lu * a_new;
+#pragma unroll 4
+    for (int i = wave; i < n; i += 4) {
+        const float* p = part(i);
+        const float a = __builtin_amdgcn_exp2f(p[0] - mt);
+        lt += p[1] * a;
 #pragma unroll
-        for (int e = 0; e < EPT; ++e) ot[e] = ot[e] * a_old + p[2 + lane * EPT + e] * a_new;
-        mt = m_new;
+        for (int e = 0; e < EPT; ++e) ot[e] += p[2 + lane * EPT + e] * a;
     }
-    const float inv = 1.0f / lt;
 #pragma unroll
-    for (int e = 0; e < EPT; ++e) out[((size_t)b * Hq + h) * D + lane * EPT + e] = Elem<T>::from_f32(ot[e] * inv);
-    if (lse_out != nullptr && lane == 0) lse_out[(size_t)b * Hq + h] = (mt + __builtin_amdgcn_logf(lt)) * 0.6931471805599453f;
+    for (int e = 0; e < EPT; ++e) o_lds[wave][lane * EPT + e] = ot[e];
+    if (lane == 0) l_lds[wave] = lt;
+    __syncthreads();
+    lt = (l_lds[0] + l_lds[1]) + (l_lds[2] + l_lds[3]);
+    const float inv = 1.0f / lt;
+    for (int e = threadIdx.x; e < D; e += 256)
+        out[((size_t)b * Hq + h) * D + e] = Elem<T>::from_f32(((o_lds[0][e] + o_lds[1][e]) + (o_lds[2][e] + o_lds[3][e])) * inv);
+    if (lse_out != nullptr && threadIdx.x == 0) lse_out[(size_t)b * Hq + h] = (mt + __builtin_amdgcn_logf(lt)) * 0.6931471805599453f;
 }
 
 // Sets the bits of the listed store rows in one query's mask (optionally clearing the mask first).
@@ -535,41 +578,54 @@ __global__ void clear_words_kernel(uint32_t* __restrict__ bits, int64_t n_words)
     if (i < n_words) bits[i] = 0u;
 }
 
+// Pieces per unit (see Pieces): about four workgroups per compute unit (two are resident), and pages, which hold the
+// recomputed tokens of all segments, in proportion to the rows they have room for.  Two queries of 16 x 1024 store rows and
+// 2978 page rows (272 whole units): 41.0 us per call with four pieces per segment and twelve per page, 42.1 with half as
+// many, 43.6 with pages cut like segments, 58 with twice as many, 68 us uncut.  From 32 queries on segments stay whole.
+Pieces choose_pieces(const DecodeArgs& a, int Hkv, int n_cu) {
+    Pieces pc{1, 1};
+    const int units = (a.n_seg + a.B) * Hkv;
+    pc.seg = std::max(1, std::min(8, (4 * n_cu + units - 1) / units));
+    pc.page = (int)std::max<int64_t>(1, std::min<int64_t>(16, pc.seg * std::max<int64_t>(1, (a.page_stride + 512) / 1024)));
+    while ((int64_t)a.n_seg * pc.seg + (int64_t)a.B * pc.page > DECODE_MAX_UNITS) {   // what the partial results' buffer holds
+        pc.seg = std::max(1, pc.seg / 2);
+        pc.page = std::max(1, pc.page / 2);
+    }
+    return pc;
+}
+
 template <typename T, int D, int G>
-hipError_t run(const Shape& s, const DecodeArgs& a, float* partials, float2* rot_table, hipStream_t st) {
+hipError_t run(const Shape& s, const DecodeArgs& a, float* partials, const double* theta, int n_cu, hipStream_t st) {
     const float scale_log2e = (1.0f / sqrtf((float)D)) * 1.4426950408889634f;
-    const int units = a.n_seg + a.B;
-    if (a.n_seg > 0)
-        decode_rot_table_kernel<<<dim3(a.n_seg), dim3(64), 0, st>>>(a.seg_delta, D / 2, D, s.rope_base, s.rope_index_base,
-                                                                    rot_table);
+    const Pieces pc = choose_pieces(a, s.Hkv, n_cu);
+    const dim3 grid(a.n_seg * pc.seg + a.B * pc.page, s.Hkv);
+    bool matrix = false;
     if constexpr (sizeof(T) == 2 && D == 128) {
-        if (!a.force_generic) {
-            decode_partial_mfma_kernel<G><<<dim3(units, s.Hkv), dim3(256), 0, st>>>(
+        matrix = !a.force_generic;
+        if (matrix)
+            decode_partial_mfma_kernel<G><<<grid, dim3(256), 0, st>>>(
                 (const __bf16*)a.q, a.B, (const __bf16*)a.k_shared, (const __bf16*)a.v_shared, a.n_shared, a.seg_offsets,
                 a.seg_row0, a.seg_len, a.seg_delta, a.n_seg, a.stale_bits, a.stale_words, (const __bf16*)a.k_pages,
-                (const __bf16*)a.v_pages, a.page_stride, a.page_len, s.Hq, s.Hkv, rot_table, s.rope_layout, scale_log2e,
-                partials);
-            decode_combine_kernel<T, D><<<dim3(a.B, s.Hq), dim3(64), 0, st>>>(partials, a.seg_offsets, a.n_seg, s.Hq,
-                                                                              (T*)a.out, a.lse_out);
-            return hipGetLastError();
-        }
+                (const __bf16*)a.v_pages, a.page_stride, a.page_len, s.Hq, s.Hkv, theta, s.rope_layout, scale_log2e,
+                partials, pc);
     }
-    decode_partial_kernel<T, D, G><<<dim3(units, s.Hkv), dim3(256), 0, st>>>(
-        (const T*)a.q, a.B, (const T*)a.k_shared, (const T*)a.v_shared, a.n_shared, a.seg_offsets, a.seg_row0, a.seg_len,
-        a.seg_delta, a.n_seg, a.stale_bits, a.stale_words, (const T*)a.k_pages, (const T*)a.v_pages, a.page_stride,
-        a.page_len, s.Hq, s.Hkv, rot_table, s.rope_layout, scale_log2e, partials);
-    decode_combine_kernel<T, D><<<dim3(a.B, s.Hq), dim3(64), 0, st>>>(partials, a.seg_offsets, a.n_seg, s.Hq, (T*)a.out,
-                                                                      a.lse_out);
+    if (!matrix)
+        decode_partial_kernel<T, D, G><<<grid, dim3(256), 0, st>>>(
+            (const T*)a.q, a.B, (const T*)a.k_shared, (const T*)a.v_shared, a.n_shared, a.seg_offsets, a.seg_row0, a.seg_len,
+            a.seg_delta, a.n_seg, a.stale_bits, a.stale_words, (const T*)a.k_pages, (const T*)a.v_pages, a.page_stride,
+            a.page_len, s.Hq, s.Hkv, theta, s.rope_layout, scale_log2e, partials, pc);
+    decode_combine_kernel<T, D><<<dim3(a.B, s.Hq), dim3(256), 0, st>>>(partials, a.seg_offsets, a.n_seg, s.Hq, pc, (T*)a.out,
+                                                                       a.lse_out);
     return hipGetLastError();
 }
 
 template <typename T, int D>
-hipError_t run_g(const Shape& s, const DecodeArgs& a, float* partials, float2* rot_table, hipStream_t st) {
+hipError_t run_g(const Shape& s, const DecodeArgs& a, float* partials, const double* theta, int n_cu, hipStream_t st) {
     switch (s.G) {
-        case 1: return run<T, D, 1>(s, a, partials, rot_table, st);
-        case 2: return run<T, D, 2>(s, a, partials, rot_table, st);
-        case 4: return run<T, D, 4>(s, a, partials, rot_table, st);
-        case 8: return run<T, D, 8>(s, a, partials, rot_table, st);
+        case 1: return run<T, D, 1>(s, a, partials, theta, n_cu, st);
+        case 2: return run<T, D, 2>(s, a, partials, theta, n_cu, st);
+        case 4: return run<T, D, 4>(s, a, partials, theta, n_cu, st);
+        case 8: return run<T, D, 8>(s, a, partials, theta, n_cu, st);
         default: return hipErrorInvalidValue;
     }
 }
@@ -582,13 +638,11 @@ size_t decode_partials_bytes(const Shape& s) {
     return (size_t)DECODE_MAX_UNITS * s.Hq * (s.d + 2) * sizeof(float);
 }
 
-size_t decode_rot_table_bytes(const Shape& s) { return (size_t)DECODE_MAX_UNITS * (s.d / 2) * sizeof(float2); }
-
-hipError_t launch_decode_attn(const Shape& s, const DecodeArgs& a, float* partials, float2* rot_table, hipStream_t st) {
+hipError_t launch_decode_attn(const Shape& s, const DecodeArgs& a, float* partials, const double* theta, int n_cu, hipStream_t st) {
     if (a.B == 0) return hipSuccess;
     if (s.dtype == FR_BF16)
-        return s.d == 128 ? run_g<__bf16, 128>(s, a, partials, rot_table, st) : run_g<__bf16, 64>(s, a, partials, rot_table, st);
-    return s.d == 128 ? run_g<float, 128>(s, a, partials, rot_table, st) : run_g<float, 64>(s, a, partials, rot_table, st);
+        return s.d == 128 ? run_g<__bf16, 128>(s, a, partials, theta, n_cu, st) : run_g<__bf16, 64>(s, a, partials, theta, n_cu, st);
+    return s.d == 128 ? run_g<float, 128>(s, a, partials, theta, n_cu, st) : run_g<float, 64>(s, a, partials, theta, n_cu, st);
 }
 
 hipError_t launch_clear_words(uint32_t* words, int64_t n_words, hipStream_t st) {
