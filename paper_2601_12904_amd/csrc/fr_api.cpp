@@ -146,8 +146,6 @@ fr_status fr_create(const fr_layer_desc* desc, int64_t max_tokens, int32_t max_c
     }
     w.n_cu = prop.multiProcessorCount;
     const bool tiled = attn_mfma_supported(s);
-    w.attn_flags_elems = tiled ? attn_mfma_flags_elems(s, max_tokens) : 0;
-    const size_t o_flags = take(w.attn_flags_elems * 4);
     w.kv_images_bytes = tiled ? attn_mfma_images_bytes(s, max_tokens) : 0;
     const size_t o_img = take(w.kv_images_bytes);
     w.attn_partials_bytes = tiled ? attn_mfma_partials_bytes(s, max_tokens) : 0;
@@ -186,7 +184,6 @@ fr_status fr_create(const fr_layer_desc* desc, int64_t max_tokens, int32_t max_c
         return FR_ERR_DEVICE;
     }
     w.qsum = (float*)(w.base + o_qsum);
-    w.attn_flags = (int32_t*)(w.base + o_flags);
     w.kv_images = (unsigned char*)(w.base + o_img);
     w.attn_partials = (float*)(w.base + o_part);
     w.decode_partials = (float*)(w.base + o_dpart);
@@ -640,10 +637,10 @@ fr_status fr_sparse_prefill_attn_shared(fr_ctx* ctx, const void* q_rows, const i
 // Scratch of one query of a batch inside the caller's workspace, every part 256-byte aligned.
 namespace {
 struct BatchScratch {
-    size_t srow, cid, table, images, flags, end;
-    size_t images_bytes, flags_elems;
+    size_t srow, cid, table, images, end;
+    size_t images_bytes;
 };
-BatchScratch batch_scratch(const Shape& s, int64_t L, int64_t R, size_t base) {
+BatchScratch batch_scratch(const Shape& s, int64_t L, size_t base) {
     BatchScratch b{};
     size_t off = base;
     auto take = [&](size_t bytes) {
@@ -656,8 +653,6 @@ BatchScratch batch_scratch(const Shape& s, int64_t L, int64_t R, size_t base) {
     b.table = take((size_t)FR_MAX_CHUNKS * (s.d / 2) * sizeof(float2));
     b.images_bytes = attn_mfma_images_bytes(s, L);
     b.images = take(b.images_bytes);
-    b.flags_elems = attn_mfma_flags_elems(s, R);
-    b.flags = take(b.flags_elems * 4);
     b.end = off;
     return b;
 }
@@ -667,7 +662,7 @@ int64_t fr_shared_batch_workspace_bytes(const fr_ctx* ctx, int32_t n_queries, in
     if (!ctx || n_queries <= 0 || max_L <= 0) return 0;
     if (!attn_mfma_store_supported(ctx->shape)) return 0;   // such shapes are served query by query from the context's own workspace
     const int64_t group = n_queries < ATTN_MAX_BATCH ? n_queries : ATTN_MAX_BATCH;
-    return group * (int64_t)batch_scratch(ctx->shape, max_L, max_L, 0).end;
+    return group * (int64_t)batch_scratch(ctx->shape, max_L, 0).end;
 }
 
 fr_status fr_sparse_prefill_attn_shared_batch(fr_ctx* ctx, const fr_shared_query* queries, int32_t n_queries,
@@ -720,7 +715,7 @@ fr_status fr_sparse_prefill_attn_shared_batch(fr_ctx* ctx, const fr_shared_query
     for (size_t g0 = 0; g0 < work.size(); g0 += ATTN_MAX_BATCH) {
         const size_t g1 = std::min(work.size(), g0 + (size_t)ATTN_MAX_BATCH);
         size_t off = 0;
-        for (size_t i = g0; i < g1; ++i) off = batch_scratch(s, work[i].L, work[i].R, off).end;
+        for (size_t i = g0; i < g1; ++i) off = batch_scratch(s, work[i].L, off).end;
         if ((int64_t)off > workspace_bytes)
             return fail(ctx, FR_ERR_WORKSPACE, "the batch needs %lld bytes of workspace, %lld given "
                         "(fr_shared_batch_workspace_bytes gives a sufficient size)", (long long)off, (long long)workspace_bytes);
@@ -734,7 +729,7 @@ fr_status fr_sparse_prefill_attn_shared_batch(fr_ctx* ctx, const fr_shared_query
         size_t off = 0;
         for (size_t i = g0; i < g1; ++i) {
             SharedBatchQuery& w = work[i];
-            const BatchScratch b = batch_scratch(s, w.L, w.R, off);
+            const BatchScratch b = batch_scratch(s, w.L, off);
             off = b.end;
             float2* table = reinterpret_cast<float2*>(base + b.table);
             hipError_t e = launch_rope_table(s, deltas[i], w.shared.ct.n, table, hs);
@@ -744,11 +739,9 @@ fr_status fr_sparse_prefill_attn_shared_batch(fr_ctx* ctx, const fr_shared_query
             w.chunk_id_map = reinterpret_cast<int32_t*>(base + b.cid);
             w.images = base + b.images;
             w.images_bytes = b.images_bytes;
-            w.flags = reinterpret_cast<int32_t*>(base + b.flags);
-            w.flags_elems = b.flags_elems;
         }
-        hipError_t e = launch_attn_mfma_shared_batch(s, (int)(g1 - g0), &work[g0], k_store, v_store, ctx->attn_softmax_mode,
-                                                     &ctx->attn_timer, hs);
+        hipError_t e = launch_attn_mfma_shared_batch(s, (int)(g1 - g0), &work[g0], k_store, v_store, ctx->ws, ctx->attn_softmax_mode,
+                                                     ctx->attn_split_mode, &ctx->attn_timer, hs);
         if (e != hipSuccess) return hip_fail(ctx, "attention launch", e);
     }
     return FR_OK;

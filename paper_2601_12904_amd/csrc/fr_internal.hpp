@@ -47,8 +47,6 @@ struct Workspace {
     int32_t* chunk_id_map = nullptr;    // [max_tokens] prompt position -> chunk
     float* qsum = nullptr;              // [Hkv][d] question queries summed per KV head (raw scores), then partial sums
     uint32_t* select_tmp = nullptr; // state, histogram, per-wave counts and candidate list of the selection kernels
-    int32_t* attn_flags = nullptr;  // per (row tile, KV head) of an attention launch: 1 = redo with a running maximum
-    size_t attn_flags_elems = 0;
     int n_cu = 0;                   // compute units of the device
     void* store_k = nullptr;        // shapes without a tiled path: a query's keys / values gathered from a shared
     void* store_v = nullptr;        // chunk store ([max_tokens, Hkv, d] each), for the generic kernels
@@ -191,7 +189,7 @@ hipError_t launch_attn_mfma(const Shape& s, const void* q_rows, const int32_t* q
                             const Workspace& ws, int softmax_mode, int split_mode, const struct SharedStoreArgs* shared,
                             struct KernelTimer* timer, bool writeback, hipStream_t st);
 // Several queries over one shared chunk store in one attention launch (Sec. 4.3).  Each query brings its scratch:
-// prompt maps, rotation table, tile images and recompute flags (sizes: attn_mfma_images_bytes, attn_mfma_flags_elems).
+// prompt maps, rotation table and tile images (attn_mfma_images_bytes).
 // R > 0 for every query.
 constexpr int ATTN_MAX_BATCH = 16;
 struct SharedBatchQuery {
@@ -200,19 +198,18 @@ struct SharedBatchQuery {
     SharedStoreArgs shared;          // chunk table, store rows (host), rotation table (device)
     int32_t* store_row_map; int32_t* chunk_id_map;   // device [L] each
     unsigned char* images; size_t images_bytes;
-    int32_t* flags; size_t flags_elems;
 };
 size_t attn_mfma_images_bytes(const Shape& s, int64_t L);
-size_t attn_mfma_flags_elems(const Shape& s, int64_t R);
 hipError_t launch_attn_mfma_shared_batch(const Shape& s, int n, const SharedBatchQuery* qs, const void* k_store,
-                                         const void* v_store, int softmax_mode, struct KernelTimer* timer, hipStream_t st);
-// A one-query attention launch with few (row tile, KV head) items deals every item's key tiles to several workgroups
+                                         const void* v_store, const Workspace& ws, int softmax_mode, int split_mode, struct KernelTimer* timer,
+                                         hipStream_t st);
+// An attention launch with few (row tile, KV head) items deals every item's key tiles to several workgroups
 // (parts), on its own up to ATTN_SPLIT_AUTO_ITEMS items (beyond that the items alone keep the chip busy and the partial
 // results' traffic costs more than the better balance gains): two parts, more (up to ATTN_MAX_PARTS) while that still
 // leaves at most one piece per compute unit.  FR_ATTN_SPLIT_ON asks for two parts at any size the partial-result buffer
 // takes.
 constexpr int ATTN_SPLIT_AUTO_ITEMS = 400;
-constexpr int ATTN_MAX_PARTS = 4;
+constexpr int ATTN_MAX_PARTS = 8;
 size_t attn_mfma_partials_bytes(const Shape& s, int64_t max_tokens);
 
 // `partials` (gemm_partials_bytes() bytes, or NULL: no split) holds the partial sums of the tiles of a launch's last,

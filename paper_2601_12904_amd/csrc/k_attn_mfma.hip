@@ -22,8 +22,8 @@
 // headroom, so the fast kernel fixes each query column's reference m once (the maximum over the
 // column's first 32 visible keys) and never rescales: the tile loop holds no maximum, no
 // comparison and no branch.  If a later logit exceeds the reference by more than that headroom
-// the sums overflow to inf; the workgroup then raises a flag, and the safe kernel (classic online
-// softmax with a running maximum) recomputes exactly the flagged workgroups.
+// the sums overflow to inf; the workgroup then recomputes its item with the classic online softmax
+// (running maximum).
 //
 // K/V tile images.  Every row tile of a KV head walks the same K/V stream (47 row tiles per head at 17k
 // tokens / 15 %), so the work that does not depend on the rows is done once, by a packing pre-pass: for each
@@ -585,7 +585,7 @@ __device__ __forceinline__ void store_output(const Geometry<G>& ge, f32x16 (&o)[
 // column's largest value, four times finer than the bf16 the output is rounded to), the two sums, the two exponent
 // references and the two scale exponents as 32-bit words: 70 words instead of 132.  Register-major (word r of thread t
 // at [r * 256 + t]: every store and load is one coalesced 1 KB line per wave).  Part p of item (ordinal, KV head g)
-// lives at ((ordinal * n_parts + p) * Hkv + g) * WORDS.  Infinities and NaNs survive the packing (the combine
+// lives at (((query * max_row_tiles + ordinal) * n_parts + p) * Hkv + g) * WORDS.  Infinities and NaNs survive the packing (the combine
 // pass must still see an overflow).
 // SPLIT: the accumulators stay fp32 (head_dim + 6 words; the scale exponents are unused).
 template <int D, bool SPLIT>
@@ -647,7 +647,6 @@ struct AttnQuery {
     const unsigned char* images;
     __bf16* out;
     float* lse;
-    int32_t* flags;        // per (row tile, KV head): 1 = redo with a running maximum
     int R, n_row_tiles, n_img_tiles, pad;
 };
 struct AttnBatch {
@@ -760,13 +759,14 @@ __device__ __forceinline__ int sums_overflowed(const f32x16 (&o)[D / 32][2], con
 }
 
 // ---- fast path: key tiles [kb, ke) of one (row tile, KV head) ---------------------------------------------
-// part < 0: the piece is the whole item; the workgroup finishes it: overflow check, then either the output or the
-// item's flag (the kernel that follows recomputes flagged items with a running maximum).  part >= 0: the piece is
+// part < 0: the piece is the whole item; the workgroup finishes it: overflow check, then the output, or the item again with
+// a running maximum (in this kernel: a second one that looked for flagged items cost 4 us per call and found none).
+// part >= 0: the piece is
 // share `part` of `n_parts` of the item's key tiles; it leaves its partial sums, and attn_combine_kernel finishes
 // the item.  Every part uses the same exponent reference (each derives it from keys 0..31), so the parts simply add up.
 template <int G, int D, bool SPLIT>
 __device__ __forceinline__ void process_piece(const AttnQuery& aq, int g, int ordinal, int part, int n_parts,
-                                              float* __restrict__ partials, int Hq, int Hkv, float scale_log2e,
+                                              float* __restrict__ item_partials, int Hq, int Hkv, float scale_log2e,
                                               unsigned char* smem_raw) {
     using I = Img<D>;
     Rings<D>& rg = *reinterpret_cast<Rings<D>*>(smem_raw);
@@ -797,7 +797,7 @@ __device__ __forceinline__ void process_piece(const AttnQuery& aq, int g, int or
     // this piece's key tiles [kb, ke): shares of ceil(n_kt / n_parts) tiles, so part 0 is never empty
     const int per_part = part < 0 ? n_kt : (n_kt + n_parts - 1) / n_parts;
     const int kb = part < 0 ? 0 : part * per_part, ke = min(n_kt, kb + per_part);
-    float* part_dst = part < 0 ? nullptr : partials + (((size_t)ordinal * n_parts + part) * Hkv + g) * Part<D, SPLIT>::WORDS + threadIdx.x;
+    float* part_dst = part < 0 ? nullptr : item_partials + (size_t)part * Hkv * Part<D, SPLIT>::WORDS + threadIdx.x;
     if (kb >= ke) {   // fewer key tiles than parts: this one adds nothing
         for (int r = 0; r < (Part<D, SPLIT>::REGS); ++r) part_dst[r * 256] = 0.f;
         return;       // (the hardware waits for the outstanding copy before it retires the wave)
@@ -891,14 +891,17 @@ __device__ __forceinline__ void process_piece(const AttnQuery& aq, int g, int or
         return;
     }
     float l[2];
-    const int any_bad = sums_overflowed<D>(o, lsum, l);
-    if (threadIdx.x == 0) aq.flags[ordinal * Hkv + g] = any_bad;   // raised: the item is recomputed with a running maximum
-    if (any_bad) return;
-    store_output<G, D>(ge, o, l, mref, R, Hq, smem_raw, aq.out, aq.lse);
+    if (!sums_overflowed<D>(o, lsum, l)) {
+        store_output<G, D>(ge, o, l, mref, R, Hq, smem_raw, aq.out, aq.lse);
+        return;
+    }
+    // the sums overflowed the fixed exponent reference (rare): the item again, with a running maximum
+    __syncthreads();
+    running_max_item<G, D, SPLIT>(aq, g, ordinal, Hq, Hkv, scale_log2e, smem_raw);
 }
 
 // blockIdx.x = ((query * max_row_tiles + ordinal) * n_parts + part) * Hkv + KV head.  n_parts = 1: every item whole.
-// n_parts > 1 (one query, few items: the chip would idle behind the longest ones): the key tiles of every item are
+// n_parts > 1 (few items: the chip would idle behind the longest ones): the key tiles of every item are
 // dealt to n_parts workgroups in equal consecutive shares; items are launched longest first, so the pieces are too.
 // Dynamic LDS: the larger of the K/V rings and the epilogue's staging.
 template <int G, int D, bool SPLIT>
@@ -911,21 +914,26 @@ __global__ __launch_bounds__(256) void attn_fixed_ref_kernel(const AttnBatch bat
     const int ordinal = t % batch.max_row_tiles, query = t / batch.max_row_tiles;
     const AttnQuery& aq = batch.q[query];
     if (ordinal >= aq.n_row_tiles) return;
-    process_piece<G, D, SPLIT>(aq, g, ordinal, n_parts > 1 ? part : -1, n_parts, partials, Hq, Hkv, scale_log2e, smem_raw);
+    process_piece<G, D, SPLIT>(aq, g, ordinal, n_parts > 1 ? part : -1, n_parts,
+                               partials + ((size_t)t * n_parts * Hkv + g) * Part<D, SPLIT>::WORDS, Hq, Hkv, scale_log2e, smem_raw);
 }
 
 // ---- combine: adds the parts of every item, then checks and stores like the fast path's own epilogue; on overflow
-//      the item is recomputed with a running maximum.  grid.x = n_row_tiles * Hkv, LDS = max(epilogue staging, one image).
+//      the item is recomputed with a running maximum.  grid.x = queries * max_row_tiles * Hkv, LDS = max(epilogue staging, one image).
 template <int G, int D, bool SPLIT>
-__global__ __launch_bounds__(256, 2) void attn_combine_kernel(const AttnQuery aq, const float* __restrict__ partials,
+__global__ __launch_bounds__(256, 2) void attn_combine_kernel(const AttnBatch batch, const float* __restrict__ partials,
                                                               int n_parts, int Hq, int Hkv, float scale_log2e) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-    const int g = (int)blockIdx.x % Hkv, ordinal = (int)blockIdx.x / Hkv;
+    BlockWork bw;
+    bw.init(batch.max_row_tiles, Hkv);
+    const AttnQuery& aq = batch.q[bw.query];
+    const int g = bw.g, ordinal = bw.ordinal, item = (int)blockIdx.x / Hkv;
+    if (ordinal >= aq.n_row_tiles) return;
     {
         constexpr int OW = Part<D, SPLIT>::O_WORDS;
         Geometry<G> ge;
         ge.init(aq.q_index, aq.R, Hq, Hkv, aq.n_row_tiles, aq.n_img_tiles, g, ordinal);
-        const uint32_t* p0 = reinterpret_cast<const uint32_t*>(partials + (((size_t)ordinal * n_parts) * Hkv + g) * Part<D, SPLIT>::WORDS) + threadIdx.x;
+        const uint32_t* p0 = reinterpret_cast<const uint32_t*>(partials + ((size_t)item * n_parts * Hkv + g) * Part<D, SPLIT>::WORDS) + threadIdx.x;
         const size_t part_stride = (size_t)Hkv * Part<D, SPLIT>::WORDS;
         f32x16 o[D / 32][2];
         float lsum[2] = {0.f, 0.f}, mref[2];
@@ -978,17 +986,15 @@ __global__ __launch_bounds__(256, 2) void attn_combine_kernel(const AttnQuery aq
     running_max_item<G, D, SPLIT>(aq, g, ordinal, Hq, Hkv, scale_log2e, smem_raw);
 }
 
-// ---- the items of a launch without parts with the running maximum: the flagged ones (use_flags), or all of them
-//      (FR_ATTN_SOFTMAX_RUNNING_MAX) ---------------------------------------------------------------------------
+// ---- all items with the running maximum (FR_ATTN_SOFTMAX_RUNNING_MAX) -------------------------------------
 template <int G, int D, bool SPLIT>
-__global__ __launch_bounds__(256) void attn_running_max_kernel(const AttnBatch batch, int use_flags, int Hq, int Hkv,
+__global__ __launch_bounds__(256) void attn_running_max_kernel(const AttnBatch batch, int Hq, int Hkv,
                                                                float scale_log2e) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     BlockWork bw;
     bw.init(batch.max_row_tiles, Hkv);
     const AttnQuery& aq = batch.q[bw.query];
     if (bw.ordinal >= aq.n_row_tiles) return;
-    if (use_flags && aq.flags[bw.ordinal * Hkv + bw.g] == 0) return;
     running_max_item<G, D, SPLIT>(aq, bw.g, bw.ordinal, Hq, Hkv, scale_log2e, smem_raw);
 }
 
@@ -998,8 +1004,6 @@ struct QueryScratch {
     int32_t* chunk_id_map;    // [L], shared-store queries only
     unsigned char* images;
     size_t images_bytes;
-    int32_t* flags;
-    size_t flags_elems;
 };
 
 template <int D>
@@ -1033,7 +1037,6 @@ hipError_t pack_query(const Shape& s, const void* q_rows, const int32_t* q_index
     const int n_row_tiles = (R + TR - 1) / TR;
     const int n_img_tiles = (int)((L + KT - 1) / KT);
     const dim3 block(256);
-    if ((size_t)n_row_tiles * s.Hkv > sc.flags_elems) return hipErrorInvalidValue;
     if ((size_t)n_img_tiles * s.Hkv * Img<D>::BYTES > sc.images_bytes) return hipErrorInvalidValue;
     if (shared == nullptr) {
         if (writeback)
@@ -1069,7 +1072,6 @@ hipError_t pack_query(const Shape& s, const void* q_rows, const int32_t* q_index
     aq->images = sc.images;
     aq->out = (__bf16*)out;
     aq->lse = lse;
-    aq->flags = sc.flags;
     aq->R = R;
     aq->n_row_tiles = n_row_tiles;
     aq->n_img_tiles = n_img_tiles;
@@ -1099,13 +1101,34 @@ void launch_tile_loop(const AttnBatch& batch, dim3 grid, float* partials, int n_
 // results' traffic and the combine pass cost more than the balance gains); below half a workgroup per compute unit more
 // parts pay until there is about one piece per compute unit (question-only prefill, 64 items: 4 parts, 0.24 -> 0.17 ms);
 // in between two parts stay best (168 items at 5 %, 128 items of the offline stage: three or four parts lose 3-15 %).
+// Short prompts (under 32 key tiles) are cut only below half a workgroup per compute unit, down to two tiles a part: a tile
+// is 1.8 us of a workgroup, the combine pass 5 us (920 tokens, 24 items of up to 15 tiles: 31 us whole, 13 + 5 in eight parts).
 int choose_parts(int split_mode, int items, int n_img_tiles, int n_cu, size_t part_bytes, size_t partials_bytes) {
     int parts = 1;
     if (split_mode == FR_ATTN_SPLIT_ON) parts = 2;
-    if (split_mode == FR_ATTN_SPLIT_AUTO && n_img_tiles >= 32 && items <= ATTN_SPLIT_AUTO_ITEMS)
-        parts = std::max(2, std::min(ATTN_MAX_PARTS, n_cu / std::max(items, 1)));
+    if (split_mode == FR_ATTN_SPLIT_AUTO) {
+        if (2 * items <= n_cu) parts = std::min({ATTN_MAX_PARTS, n_cu / std::max(items, 1), (n_img_tiles + 1) / 2});
+        if (n_img_tiles >= 32 && items <= ATTN_SPLIT_AUTO_ITEMS) parts = std::max(parts, 2);
+    }
     while (parts > 1 && (size_t)items * parts * part_bytes > partials_bytes) --parts;
     return parts;
+}
+
+// Packed queries -> attention launches: tile loop (+ combine pass), or the running-maximum kernel.
+template <int G, int D, bool SPLIT>
+hipError_t launch_packed(const Shape& s, const AttnBatch& batch, int n_parts, const Workspace& ws, int mode, KernelTimer* timer,
+                         hipStream_t st) {
+    const float scale_log2e = (1.0f / sqrtf((float)s.d)) * 1.4426950408889634f;
+    const dim3 grid(batch.max_row_tiles * batch.n * s.Hkv);
+    if (mode == FR_ATTN_SOFTMAX_RUNNING_MAX) {   // every item with the running maximum
+        attn_running_max_kernel<G, D, SPLIT><<<grid, dim3(256), LDS_SAFE<D>, st>>>(batch, s.Hq, s.Hkv, scale_log2e);
+        return hipGetLastError();
+    }
+    const bool timed = timer != nullptr && timer->n_slots > 0;
+    launch_tile_loop<G, D, SPLIT>(batch, dim3(grid.x * n_parts), ws.attn_partials, n_parts, s, scale_log2e, timer, timed, st);
+    if (n_parts > 1)   // adds the parts, stores, and recomputes the items whose sums overflowed
+        attn_combine_kernel<G, D, SPLIT><<<grid, dim3(256), LDS_SAFE<D>, st>>>(batch, ws.attn_partials, n_parts, s.Hq, s.Hkv, scale_log2e);
+    return hipGetLastError();
 }
 
 template <int G, int D, bool SPLIT>
@@ -1115,57 +1138,45 @@ hipError_t launch(const Shape& s, const void* q_rows, const int32_t* q_index, in
                   bool writeback, hipStream_t st) {
     hipError_t e = set_kernel_attributes<G, D, SPLIT>();
     if (e != hipSuccess) return e;
-    const float scale_log2e = (1.0f / sqrtf((float)s.d)) * 1.4426950408889634f;
-    const QueryScratch sc{ws.store_row_map, ws.chunk_id_map, ws.kv_images, ws.kv_images_bytes, ws.attn_flags,
-                          ws.attn_flags_elems};
+    const QueryScratch sc{ws.store_row_map, ws.chunk_id_map, ws.kv_images, ws.kv_images_bytes};
     AttnBatch batch;
     batch.n = 1;
     e = pack_query<D>(s, q_rows, q_index, R, k_cache, v_cache, L, k_new, v_new, out, lse, sc, shared, writeback, &batch.q[0], st);
     if (e != hipSuccess) return e;
     batch.max_row_tiles = batch.q[0].n_row_tiles;
-    const int items = batch.q[0].n_row_tiles * s.Hkv;
-    const dim3 grid(items);
-    if (mode == FR_ATTN_SOFTMAX_RUNNING_MAX) {   // every item with the running maximum
-        attn_running_max_kernel<G, D, SPLIT><<<grid, dim3(256), LDS_SAFE<D>, st>>>(batch, 0, s.Hq, s.Hkv, scale_log2e);
-        return hipGetLastError();
-    }
-    const int n_parts = choose_parts(split_mode, items, batch.q[0].n_img_tiles, ws.n_cu, Part<D, SPLIT>::WORDS * sizeof(float),
-                                     ws.attn_partials_bytes);
-    const bool timed = timer != nullptr && timer->n_slots > 0;
-    launch_tile_loop<G, D, SPLIT>(batch, dim3(items * n_parts), ws.attn_partials, n_parts, s, scale_log2e, timer, timed, st);
-    if (n_parts > 1)   // adds the parts, stores, and recomputes the items whose sums overflowed
-        attn_combine_kernel<G, D, SPLIT><<<grid, dim3(256), LDS_SAFE<D>, st>>>(batch.q[0], ws.attn_partials, n_parts, s.Hq, s.Hkv, scale_log2e);
-    else               // recomputes the items whose workgroups raised their flag
-        attn_running_max_kernel<G, D, SPLIT><<<grid, dim3(256), LDS_SAFE<D>, st>>>(batch, 1, s.Hq, s.Hkv, scale_log2e);
-    return hipGetLastError();
+    const int n_parts = choose_parts(split_mode, batch.q[0].n_row_tiles * s.Hkv, batch.q[0].n_img_tiles, ws.n_cu,
+                                     Part<D, SPLIT>::WORDS * sizeof(float), ws.attn_partials_bytes);
+    return launch_packed<G, D, SPLIT>(s, batch, n_parts, ws, mode, timer, st);
 }
 
 template <int G, int D, bool SPLIT>
-hipError_t launch_shared_batch(const Shape& s, int n, const SharedBatchQuery* qs, const void* k_store,
-                               const void* v_store, int mode, KernelTimer* timer, hipStream_t st) {
+hipError_t launch_shared_batch(const Shape& s, int n, const SharedBatchQuery* qs, const void* k_store, const void* v_store,
+                               const Workspace& ws, int mode, int split_mode, KernelTimer* timer, hipStream_t st) {
     hipError_t e = set_kernel_attributes<G, D, SPLIT>();
     if (e != hipSuccess) return e;
-    const float scale_log2e = (1.0f / sqrtf((float)s.d)) * 1.4426950408889634f;
     AttnBatch batch;
     batch.n = n;
     batch.max_row_tiles = 0;
+    const size_t part_bytes = Part<D, SPLIT>::WORDS * sizeof(float);
+    int n_parts = 1;
     for (int i = 0; i < n; ++i) {
         const SharedBatchQuery& q = qs[i];
-        const QueryScratch sc{q.store_row_map, q.chunk_id_map, q.images, q.images_bytes, q.flags, q.flags_elems};
+        const QueryScratch sc{q.store_row_map, q.chunk_id_map, q.images, q.images_bytes};
         e = pack_query<D>(s, q.q_rows, q.q_index, q.R, k_store, v_store, q.L, q.k_new, q.v_new, q.out, q.lse, sc, &q.shared,
                           false, &batch.q[i], st);
         if (e != hipSuccess) return e;
         batch.max_row_tiles = std::max(batch.max_row_tiles, batch.q[i].n_row_tiles);
+        n_parts = std::max(n_parts, choose_parts(split_mode, batch.q[i].n_row_tiles * s.Hkv, batch.q[i].n_img_tiles, ws.n_cu,
+                                                 part_bytes, ws.attn_partials_bytes));
     }
-    // a batch of queries fills the chip by itself: every item whole, one workgroup each
-    const dim3 grid(batch.max_row_tiles * n * s.Hkv);
-    if (mode == FR_ATTN_SOFTMAX_RUNNING_MAX) {
-        attn_running_max_kernel<G, D, SPLIT><<<grid, dim3(256), LDS_SAFE<D>, st>>>(batch, 0, s.Hq, s.Hkv, scale_log2e);
-    } else {
-        launch_tile_loop<G, D, SPLIT>(batch, grid, nullptr, 1, s, scale_log2e, timer, timer != nullptr && timer->n_slots > 0, st);
-        attn_running_max_kernel<G, D, SPLIT><<<grid, dim3(256), LDS_SAFE<D>, st>>>(batch, 1, s.Hq, s.Hkv, scale_log2e);
-    }
-    return hipGetLastError();
+    // A batch of queries usually fills the chip by itself: every item whole, one workgroup each.  Up to a quarter of a
+    // workgroup per compute unit it is cut like its queries would be alone; in between like one query of as many items.
+    const int items = batch.max_row_tiles * n * s.Hkv;
+    int tiles = 0;
+    for (int i = 0; i < n; ++i) tiles = std::max(tiles, batch.q[i].n_img_tiles);
+    if (4 * items > ws.n_cu) n_parts = choose_parts(split_mode, items, tiles, ws.n_cu, part_bytes, ws.attn_partials_bytes);
+    while (n_parts > 1 && (size_t)items * n_parts * part_bytes > ws.attn_partials_bytes) --n_parts;
+    return launch_packed<G, D, SPLIT>(s, batch, n_parts, ws, mode, timer, st);
 }
 
 }  // namespace
@@ -1181,7 +1192,8 @@ size_t attn_mfma_partials_bytes(const Shape& s, int64_t max_tokens) {
     const int64_t tr = 4 * (64 / s.G);   // token rows per workgroup
     const int64_t items = std::min<int64_t>(((max_tokens + tr - 1) / tr) * s.Hkv, ATTN_SPLIT_AUTO_ITEMS);
     const size_t words = own_instance(s) ? Part<128, false>::WORDS : s.d == 128 ? Part<128, true>::WORDS : Part<64, true>::WORDS;
-    return (size_t)(2 * items) * words * sizeof(float);   // two parts of the most items that are split without being asked
+    // two parts of the most items that are split without being asked, up to eight of few items (a batch's too)
+    return (size_t)std::max<int64_t>(2 * items, std::min<int64_t>(ATTN_MAX_PARTS * items, 512)) * words * sizeof(float);
 }
 
 bool attn_mfma_supported(const Shape& s) { return s.dtype == FR_BF16 && s.G <= 64; }
@@ -1208,17 +1220,17 @@ hipError_t launch_attn_mfma(const Shape& s, const void* q_rows, const int32_t* q
 size_t attn_mfma_images_bytes(const Shape& s, int64_t L) {
     return (size_t)((L + KT - 1) / KT) * s.Hkv * (s.d == 128 ? Img<128>::BYTES : Img<64>::BYTES);
 }
-size_t attn_mfma_flags_elems(const Shape& s, int64_t R) { return (size_t)(R / (4 * (64 / s.G)) + 1) * s.Hkv; }
 
 hipError_t launch_attn_mfma_shared_batch(const Shape& s, int n, const SharedBatchQuery* qs, const void* k_store,
-                                         const void* v_store, int mode, KernelTimer* timer, hipStream_t st) {
+                                         const void* v_store, const Workspace& ws, int mode, int split_mode, KernelTimer* timer,
+                                         hipStream_t st) {
     if (n <= 0) return hipSuccess;
     if (n > ATTN_MAX_BATCH) return hipErrorInvalidValue;
     switch (s.G) {
-        case 1: return launch_shared_batch<1, 128, false>(s, n, qs, k_store, v_store, mode, timer, st);
-        case 2: return launch_shared_batch<2, 128, false>(s, n, qs, k_store, v_store, mode, timer, st);
-        case 4: return launch_shared_batch<4, 128, false>(s, n, qs, k_store, v_store, mode, timer, st);
-        default: return launch_shared_batch<8, 128, false>(s, n, qs, k_store, v_store, mode, timer, st);
+        case 1: return launch_shared_batch<1, 128, false>(s, n, qs, k_store, v_store, ws, mode, split_mode, timer, st);
+        case 2: return launch_shared_batch<2, 128, false>(s, n, qs, k_store, v_store, ws, mode, split_mode, timer, st);
+        case 4: return launch_shared_batch<4, 128, false>(s, n, qs, k_store, v_store, ws, mode, split_mode, timer, st);
+        default: return launch_shared_batch<8, 128, false>(s, n, qs, k_store, v_store, ws, mode, split_mode, timer, st);
     }
 }
 
