@@ -580,31 +580,31 @@ __device__ __forceinline__ void store_output(const Geometry<G>& ge, f32x16 (&o)[
     }
 }
 
-// Partial result of one part of an item, per lane: its 128 output accumulators as half-precision pairs (the 64 of a
-// column block scaled by a power of two that brings the largest of them into [0.5, 1): 11 significant bits of that
-// column's largest value, four times finer than the bf16 the output is rounded to), the two sums, the two exponent
-// references and the two scale exponents as 32-bit words: 70 words instead of 132.  Register-major (word r of thread t
-// at [r * 256 + t]: every store and load is one coalesced 1 KB line per wave).  Part p of item (ordinal, KV head g)
-// lives at (((query * max_row_tiles + ordinal) * n_parts + p) * Hkv + g) * WORDS.  Infinities and NaNs survive the packing (the combine
-// pass must still see an overflow).
-// SPLIT: the accumulators stay fp32 (head_dim + 6 words; the scale exponents are unused).
-template <int D, bool SPLIT>
+// Partial result of one part of an item, per lane: its 2 x D / 2 output accumulators, the two sums, the two exponent
+// references and two scale exponents as 32-bit words.  Register-major (word r of thread t at [r * 256 + t]: every store
+// and load is one coalesced 1 KB line per wave).  Part p of item (ordinal, KV head g) lives at
+// (((query * max_row_tiles + ordinal) * n_parts + p) * Hkv + g) * WORDS.  Infinities and NaNs survive the packing (the
+// combine pass must still see an overflow).
+// F32: the accumulators as they are.  Otherwise as half-precision pairs, the 64 of a column block scaled by a power of two
+// that brings the largest of them into [0.5, 1) (11 significant bits of that column's largest value): 70 words instead of
+// 134.  Which one: half_parts.
+template <int D, bool F32>
 struct Part {
-    static constexpr int O_WORDS = SPLIT ? D : D / 2;   // per lane, both column blocks
+    static constexpr int O_WORDS = F32 ? D : D / 2;   // per lane, both column blocks
     static constexpr int REGS = O_WORDS + 6;
-    static constexpr int WORDS = REGS * 256;            // 32-bit words of a part
+    static constexpr int WORDS = REGS * 256;          // 32-bit words of a part
 };
 typedef _Float16 __attribute__((ext_vector_type(2))) f16x2;
 
-template <int D, bool SPLIT>
+template <int D, bool F32>
 __device__ __forceinline__ void store_partial(float* __restrict__ dst_f, const f32x16 (&o)[D / 32][2], const float (&lsum)[2],
                                               const float (&mref)[2]) {
-    constexpr int OW = Part<D, SPLIT>::O_WORDS;
+    constexpr int OW = Part<D, F32>::O_WORDS;
     uint32_t* dst = reinterpret_cast<uint32_t*>(dst_f);
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb) {
         int e = 0;
-        if constexpr (SPLIT) {
+        if constexpr (F32) {
 #pragma unroll
             for (int md = 0; md < D / 32; ++md)
 #pragma unroll
@@ -765,8 +765,8 @@ __device__ __forceinline__ int sums_overflowed(const f32x16 (&o)[D / 32][2], con
 // share `part` of `n_parts` of the item's key tiles; it leaves its partial sums, and attn_combine_kernel finishes
 // the item.  Every part uses the same exponent reference (each derives it from keys 0..31), so the parts simply add up.
 template <int G, int D, bool SPLIT>
-__device__ __forceinline__ void process_piece(const AttnQuery& aq, int g, int ordinal, int part, int n_parts,
-                                              float* __restrict__ item_partials, int Hq, int Hkv, float scale_log2e,
+__device__ __forceinline__ void process_piece(const AttnQuery& aq, int g, int ordinal, int part, int n_parts, int item,
+                                              float* __restrict__ partials, bool half, int Hq, int Hkv, float scale_log2e,
                                               unsigned char* smem_raw) {
     using I = Img<D>;
     Rings<D>& rg = *reinterpret_cast<Rings<D>*>(smem_raw);
@@ -797,9 +797,10 @@ __device__ __forceinline__ void process_piece(const AttnQuery& aq, int g, int or
     // this piece's key tiles [kb, ke): shares of ceil(n_kt / n_parts) tiles, so part 0 is never empty
     const int per_part = part < 0 ? n_kt : (n_kt + n_parts - 1) / n_parts;
     const int kb = part < 0 ? 0 : part * per_part, ke = min(n_kt, kb + per_part);
-    float* part_dst = part < 0 ? nullptr : item_partials + (size_t)part * Hkv * Part<D, SPLIT>::WORDS + threadIdx.x;
+    const int part_words = half ? Part<D, false>::WORDS : Part<D, true>::WORDS;
+    float* part_dst = part < 0 ? nullptr : partials + (((size_t)item * n_parts + part) * Hkv + g) * part_words + threadIdx.x;
     if (kb >= ke) {   // fewer key tiles than parts: this one adds nothing
-        for (int r = 0; r < (Part<D, SPLIT>::REGS); ++r) part_dst[r * 256] = 0.f;
+        for (int r = 0; r < part_words; r += 256) part_dst[r] = 0.f;
         return;       // (the hardware waits for the outstanding copy before it retires the wave)
     }
     f32x16 o[D / 32][2];
@@ -887,7 +888,7 @@ __device__ __forceinline__ void process_piece(const AttnQuery& aq, int g, int or
     pv_half<D, SPLIT>(rg.vt[k2], 1, pf_b, fo, o);   // the last half: V image ke-1 now sits in slot k2
 
     if (part >= 0) {   // leave the partial result; attn_combine_kernel adds the parts, checks and stores
-        store_partial<D, SPLIT>(part_dst, o, lsum, mref);
+        if (!SPLIT && half) store_partial<D, false>(part_dst, o, lsum, mref); else store_partial<D, true>(part_dst, o, lsum, mref);
         return;
     }
     float l[2];
@@ -906,7 +907,7 @@ __device__ __forceinline__ void process_piece(const AttnQuery& aq, int g, int or
 // Dynamic LDS: the larger of the K/V rings and the epilogue's staging.
 template <int G, int D, bool SPLIT>
 __global__ __launch_bounds__(256) void attn_fixed_ref_kernel(const AttnBatch batch, float* __restrict__ partials, int n_parts,
-                                                             int Hq, int Hkv, float scale_log2e) {
+                                                             int half, int Hq, int Hkv, float scale_log2e) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     int t = (int)blockIdx.x;
     const int g = t % Hkv; t /= Hkv;
@@ -914,13 +915,12 @@ __global__ __launch_bounds__(256) void attn_fixed_ref_kernel(const AttnBatch bat
     const int ordinal = t % batch.max_row_tiles, query = t / batch.max_row_tiles;
     const AttnQuery& aq = batch.q[query];
     if (ordinal >= aq.n_row_tiles) return;
-    process_piece<G, D, SPLIT>(aq, g, ordinal, n_parts > 1 ? part : -1, n_parts,
-                               partials + ((size_t)t * n_parts * Hkv + g) * Part<D, SPLIT>::WORDS, Hq, Hkv, scale_log2e, smem_raw);
+    process_piece<G, D, SPLIT>(aq, g, ordinal, n_parts > 1 ? part : -1, n_parts, t, partials, half != 0, Hq, Hkv, scale_log2e, smem_raw);
 }
 
 // ---- combine: adds the parts of every item, then checks and stores like the fast path's own epilogue; on overflow
 //      the item is recomputed with a running maximum.  grid.x = queries * max_row_tiles * Hkv, LDS = max(epilogue staging, one image).
-template <int G, int D, bool SPLIT>
+template <int G, int D, bool SPLIT, bool F32>
 __global__ __launch_bounds__(256, 2) void attn_combine_kernel(const AttnBatch batch, const float* __restrict__ partials,
                                                               int n_parts, int Hq, int Hkv, float scale_log2e) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
@@ -930,11 +930,11 @@ __global__ __launch_bounds__(256, 2) void attn_combine_kernel(const AttnBatch ba
     const int g = bw.g, ordinal = bw.ordinal, item = (int)blockIdx.x / Hkv;
     if (ordinal >= aq.n_row_tiles) return;
     {
-        constexpr int OW = Part<D, SPLIT>::O_WORDS;
+        constexpr int OW = Part<D, F32>::O_WORDS;
         Geometry<G> ge;
         ge.init(aq.q_index, aq.R, Hq, Hkv, aq.n_row_tiles, aq.n_img_tiles, g, ordinal);
-        const uint32_t* p0 = reinterpret_cast<const uint32_t*>(partials + ((size_t)item * n_parts * Hkv + g) * Part<D, SPLIT>::WORDS) + threadIdx.x;
-        const size_t part_stride = (size_t)Hkv * Part<D, SPLIT>::WORDS;
+        const uint32_t* p0 = reinterpret_cast<const uint32_t*>(partials + ((size_t)item * n_parts * Hkv + g) * Part<D, F32>::WORDS) + threadIdx.x;
+        const size_t part_stride = (size_t)Hkv * Part<D, F32>::WORDS;
         f32x16 o[D / 32][2];
         float lsum[2] = {0.f, 0.f}, mref[2];
 #pragma unroll
@@ -963,7 +963,7 @@ __global__ __launch_bounds__(256, 2) void attn_combine_kernel(const AttnBatch ba
                 for (int md = 0; md < D / 32; ++md)
 #pragma unroll
                     for (int v = 0; v < 16; v += 2) {
-                        if constexpr (SPLIT) {
+                        if constexpr (F32) {
                             o[md][nb][v] += __uint_as_float(w[nb][md * 16 + v]);
                             o[md][nb][v + 1] += __uint_as_float(w[nb][md * 16 + v + 1]);
                         } else {
@@ -1019,9 +1019,14 @@ hipError_t set_kernel_attributes() {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_fixed_ref_kernel<G, D, SPLIT>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_FAST<D>);
         if (e != hipSuccess) return e;
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_combine_kernel<G, D, SPLIT>),
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_combine_kernel<G, D, SPLIT, true>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_SAFE<D>);
         if (e != hipSuccess) return e;
+        if constexpr (!SPLIT) {
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_combine_kernel<G, D, SPLIT, false>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_SAFE<D>);
+            if (e != hipSuccess) return e;
+        }
         return hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_running_max_kernel<G, D, SPLIT>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_SAFE<D>);
     }();
@@ -1082,15 +1087,15 @@ hipError_t pack_query(const Shape& s, const void* q_rows, const int32_t* q_index
 // Launches the key-tile loop; with a live timer its event pair rides on the kernel's own dispatch (start and end of its
 // execution), so the stream carries no extra marker packets and the kernels before and after it are not held up.
 template <int G, int D, bool SPLIT>
-void launch_tile_loop(const AttnBatch& batch, dim3 grid, float* partials, int n_parts, const Shape& s, float scale_log2e,
+void launch_tile_loop(const AttnBatch& batch, dim3 grid, float* partials, int n_parts, bool half, const Shape& s, float scale_log2e,
                       KernelTimer* timer, bool timed, hipStream_t st) {
     if (timed) {
         const int slot = (int)(timer->n_recorded % timer->n_slots);
         hipExtLaunchKernelGGL((attn_fixed_ref_kernel<G, D, SPLIT>), grid, dim3(256), (uint32_t)LDS_FAST<D>, st, timer->start[slot],
-                              timer->stop[slot], 0u, batch, partials, n_parts, s.Hq, s.Hkv, scale_log2e);
+                              timer->stop[slot], 0u, batch, partials, n_parts, (int)half, s.Hq, s.Hkv, scale_log2e);
         ++timer->n_recorded;
     } else {
-        attn_fixed_ref_kernel<G, D, SPLIT><<<grid, dim3(256), LDS_FAST<D>, st>>>(batch, partials, n_parts, s.Hq, s.Hkv, scale_log2e);
+        attn_fixed_ref_kernel<G, D, SPLIT><<<grid, dim3(256), LDS_FAST<D>, st>>>(batch, partials, n_parts, (int)half, s.Hq, s.Hkv, scale_log2e);
     }
 }
 
@@ -1114,10 +1119,18 @@ int choose_parts(int split_mode, int items, int n_img_tiles, int n_cu, size_t pa
     return parts;
 }
 
+// Half-precision partial results: only for a single query of a long prompt (32 key tiles and more) whose weights are plain
+// bf16, where 400 items in two parts would otherwise move 2 x 108 MB of partial sums (combine pass 21.1 us, 15.5 us in half
+// precision).  Short prompts and batches, a few hundred pieces at most, keep all 32 bits.
+template <bool SPLIT>
+bool half_parts(int n_img_tiles) { return !SPLIT && n_img_tiles >= 32; }
+template <int D>
+size_t part_bytes(bool half) { return (half ? Part<D, false>::WORDS : Part<D, true>::WORDS) * sizeof(float); }
+
 // Packed queries -> attention launches: tile loop (+ combine pass), or the running-maximum kernel.
 template <int G, int D, bool SPLIT>
-hipError_t launch_packed(const Shape& s, const AttnBatch& batch, int n_parts, const Workspace& ws, int mode, KernelTimer* timer,
-                         hipStream_t st) {
+hipError_t launch_packed(const Shape& s, const AttnBatch& batch, int n_parts, bool half, const Workspace& ws, int mode,
+                         KernelTimer* timer, hipStream_t st) {
     const float scale_log2e = (1.0f / sqrtf((float)s.d)) * 1.4426950408889634f;
     const dim3 grid(batch.max_row_tiles * batch.n * s.Hkv);
     if (mode == FR_ATTN_SOFTMAX_RUNNING_MAX) {   // every item with the running maximum
@@ -1125,9 +1138,16 @@ hipError_t launch_packed(const Shape& s, const AttnBatch& batch, int n_parts, co
         return hipGetLastError();
     }
     const bool timed = timer != nullptr && timer->n_slots > 0;
-    launch_tile_loop<G, D, SPLIT>(batch, dim3(grid.x * n_parts), ws.attn_partials, n_parts, s, scale_log2e, timer, timed, st);
-    if (n_parts > 1)   // adds the parts, stores, and recomputes the items whose sums overflowed
-        attn_combine_kernel<G, D, SPLIT><<<grid, dim3(256), LDS_SAFE<D>, st>>>(batch, ws.attn_partials, n_parts, s.Hq, s.Hkv, scale_log2e);
+    launch_tile_loop<G, D, SPLIT>(batch, dim3(grid.x * n_parts), ws.attn_partials, n_parts, half, s, scale_log2e, timer, timed, st);
+    if (n_parts > 1) {   // adds the parts, stores, and recomputes the items whose sums overflowed
+        if constexpr (!SPLIT) {
+            if (half) {
+                attn_combine_kernel<G, D, SPLIT, false><<<grid, dim3(256), LDS_SAFE<D>, st>>>(batch, ws.attn_partials, n_parts, s.Hq, s.Hkv, scale_log2e);
+                return hipGetLastError();
+            }
+        }
+        attn_combine_kernel<G, D, SPLIT, true><<<grid, dim3(256), LDS_SAFE<D>, st>>>(batch, ws.attn_partials, n_parts, s.Hq, s.Hkv, scale_log2e);
+    }
     return hipGetLastError();
 }
 
@@ -1144,9 +1164,10 @@ hipError_t launch(const Shape& s, const void* q_rows, const int32_t* q_index, in
     e = pack_query<D>(s, q_rows, q_index, R, k_cache, v_cache, L, k_new, v_new, out, lse, sc, shared, writeback, &batch.q[0], st);
     if (e != hipSuccess) return e;
     batch.max_row_tiles = batch.q[0].n_row_tiles;
+    const bool half = half_parts<SPLIT>(batch.q[0].n_img_tiles);
     const int n_parts = choose_parts(split_mode, batch.q[0].n_row_tiles * s.Hkv, batch.q[0].n_img_tiles, ws.n_cu,
-                                     Part<D, SPLIT>::WORDS * sizeof(float), ws.attn_partials_bytes);
-    return launch_packed<G, D, SPLIT>(s, batch, n_parts, ws, mode, timer, st);
+                                     part_bytes<D>(half), ws.attn_partials_bytes);
+    return launch_packed<G, D, SPLIT>(s, batch, n_parts, half, ws, mode, timer, st);
 }
 
 template <int G, int D, bool SPLIT>
@@ -1157,7 +1178,7 @@ hipError_t launch_shared_batch(const Shape& s, int n, const SharedBatchQuery* qs
     AttnBatch batch;
     batch.n = n;
     batch.max_row_tiles = 0;
-    const size_t part_bytes = Part<D, SPLIT>::WORDS * sizeof(float);
+    const size_t slot = part_bytes<D>(false);   // partial results of a batch stay fp32
     int n_parts = 1;
     for (int i = 0; i < n; ++i) {
         const SharedBatchQuery& q = qs[i];
@@ -1167,16 +1188,16 @@ hipError_t launch_shared_batch(const Shape& s, int n, const SharedBatchQuery* qs
         if (e != hipSuccess) return e;
         batch.max_row_tiles = std::max(batch.max_row_tiles, batch.q[i].n_row_tiles);
         n_parts = std::max(n_parts, choose_parts(split_mode, batch.q[i].n_row_tiles * s.Hkv, batch.q[i].n_img_tiles, ws.n_cu,
-                                                 part_bytes, ws.attn_partials_bytes));
+                                                 slot, ws.attn_partials_bytes));
     }
     // A batch of queries usually fills the chip by itself: every item whole, one workgroup each.  Up to a quarter of a
     // workgroup per compute unit it is cut like its queries would be alone; in between like one query of as many items.
     const int items = batch.max_row_tiles * n * s.Hkv;
     int tiles = 0;
     for (int i = 0; i < n; ++i) tiles = std::max(tiles, batch.q[i].n_img_tiles);
-    if (4 * items > ws.n_cu) n_parts = choose_parts(split_mode, items, tiles, ws.n_cu, part_bytes, ws.attn_partials_bytes);
-    while (n_parts > 1 && (size_t)items * n_parts * part_bytes > ws.attn_partials_bytes) --n_parts;
-    return launch_packed<G, D, SPLIT>(s, batch, n_parts, ws, mode, timer, st);
+    if (4 * items > ws.n_cu) n_parts = choose_parts(split_mode, items, tiles, ws.n_cu, slot, ws.attn_partials_bytes);
+    while (n_parts > 1 && (size_t)items * n_parts * slot > ws.attn_partials_bytes) --n_parts;
+    return launch_packed<G, D, SPLIT>(s, batch, n_parts, false, ws, mode, timer, st);
 }
 
 }  // namespace
@@ -1191,9 +1212,11 @@ static bool own_instance(const Shape& s) { return s.d == 128 && (s.G == 1 || s.G
 size_t attn_mfma_partials_bytes(const Shape& s, int64_t max_tokens) {
     const int64_t tr = 4 * (64 / s.G);   // token rows per workgroup
     const int64_t items = std::min<int64_t>(((max_tokens + tr - 1) / tr) * s.Hkv, ATTN_SPLIT_AUTO_ITEMS);
-    const size_t words = own_instance(s) ? Part<128, false>::WORDS : s.d == 128 ? Part<128, true>::WORDS : Part<64, true>::WORDS;
-    // two parts of the most items that are split without being asked, up to eight of few items (a batch's too)
-    return (size_t)std::max<int64_t>(2 * items, std::min<int64_t>(ATTN_MAX_PARTS * items, 512)) * words * sizeof(float);
+    // two parts of the most items that are split without being asked (32-bit words unless they may be half_parts), and up
+    // to eight parts of few items (about one piece per compute unit), always in 32 bits
+    const size_t full = (s.d == 128 ? Part<128, true>::WORDS : Part<64, true>::WORDS) * sizeof(float);
+    const size_t half = own_instance(s) ? Part<128, false>::WORDS * sizeof(float) : full;
+    return std::max((size_t)(2 * items) * half, (size_t)std::min<int64_t>(ATTN_MAX_PARTS * items, 256) * full);
 }
 
 bool attn_mfma_supported(const Shape& s) { return s.dtype == FR_BF16 && s.G <= 64; }
