@@ -38,6 +38,7 @@
 #include <hip/hip_ext.h>
 
 #include <algorithm>
+#include <type_traits>
 
 namespace fr {
 
@@ -580,6 +581,40 @@ __device__ __forceinline__ void store_output(const Geometry<G>& ge, f32x16 (&o)[
     }
 }
 
+// The same for dims 32 md .. 32 md + 31 only (a workgroup of the combine pass).
+template <int G, int D>
+__device__ __forceinline__ void store_slice(const Geometry<G>& ge, const f32x16 (&acc)[2], int md, const float (&l)[2],
+                                            const float (&mref)[2], int R, int Hq, unsigned char* smem,
+                                            __bf16* __restrict__ out, float* __restrict__ lse_out) {
+    constexpr int PITCH = 40;   // 32 dims + 16 bytes
+    __bf16* ob = reinterpret_cast<__bf16*>(smem) + ge.wave * 64 * PITCH;
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) {
+        const float inv_l = 1.0f / l[nb];
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+            bf16x4 w;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w[e] = (__bf16)(acc[nb][4 * q4 + e] * inv_l);
+            *reinterpret_cast<bf16x4*>(&ob[(32 * nb + ge.x) * PITCH + 8 * q4 + 4 * ge.h]) = w;
+        }
+        if (md == 0 && lse_out != nullptr && ge.h == 0 && ge.col_row[nb] < R && 32 * nb + ge.x < ge.trw * ge.heads)
+            lse_out[(size_t)ge.col_row[nb] * Hq + ge.col_head[nb]] =
+                (mref[nb] + __builtin_amdgcn_logf(l[nb])) * 0.6931471805599453f;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int col = 16 * i + lane / 4, vec = lane % 4;
+        const int r = ge.row0 + ge.wave * ge.trw + (col % ge.trw), head = col / ge.trw;
+        if (r < R && head < ge.heads) {
+            const u32x4 w = *reinterpret_cast<const u32x4*>(&ob[col * PITCH + 8 * vec]);
+            *reinterpret_cast<u32x4*>(out + ((size_t)r * Hq + ge.g * ge.heads + head) * D + 32 * md + 8 * vec) = w;
+        }
+    }
+}
+
 // Partial result of one part of an item, per lane: its 2 x D / 2 output accumulators, the two sums, the two exponent
 // references and two scale exponents as 32-bit words.  Register-major (word r of thread t at [r * 256 + t]: every store
 // and load is one coalesced 1 KB line per wave).  Part p of item (ordinal, KV head g) lives at
@@ -665,10 +700,11 @@ struct BlockWork {
 
 // ---- classic online softmax (running maximum) for one (row tile, KV head): the whole key range, one workgroup.
 //      Runs where the fixed exponent reference overflowed, and everywhere under FR_ATTN_SOFTMAX_RUNNING_MAX.
-//      `smem` holds one image or the epilogue's staging; every thread of the workgroup calls it. ------------------------
+//      `smem` holds one image or the epilogue's staging; every thread of the workgroup calls it.  slice >= 0: only the
+//      dims of that block of 32 are stored (a workgroup of the combine pass).  -------------------------------------------
 template <int G, int D, bool SPLIT>
 __device__ __forceinline__ void running_max_item(const AttnQuery& aq, int g, int ordinal, int Hq, int Hkv,
-                                                 float scale_log2e, unsigned char* smem) {
+                                                 float scale_log2e, unsigned char* smem, int slice = -1) {
     const __bf16* __restrict__ q_rows = aq.q_rows;
     const int R = aq.R, n_img_tiles = aq.n_img_tiles;
     unsigned char* k_img = smem;
@@ -737,7 +773,15 @@ __device__ __forceinline__ void running_max_item(const AttnQuery& aq, int g, int
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb) l[nb] = lsum[nb] + __shfl_xor(lsum[nb], 32);
     __syncthreads();
-    store_output<G, D>(ge, o, l, m2, R, Hq, smem, aq.out, aq.lse);
+    if (slice < 0) {
+        store_output<G, D>(ge, o, l, m2, R, Hq, smem, aq.out, aq.lse);
+        return;
+    }
+    f32x16 acc[2] = {o[0][0], o[0][1]};
+#pragma unroll
+    for (int md = 1; md < D / 32; ++md)
+        if (md == slice) { acc[0] = o[md][0]; acc[1] = o[md][1]; }
+    store_slice<G, D>(ge, acc, slice, l, m2, R, Hq, smem, aq.out, aq.lse);
 }
 
 // Overflow check of a finished item: with a fixed reference a runaway logit shows up as inf / nan in the sums.
@@ -919,71 +963,92 @@ __global__ __launch_bounds__(256) void attn_fixed_ref_kernel(const AttnBatch bat
 }
 
 // ---- combine: adds the parts of every item, then checks and stores like the fast path's own epilogue; on overflow
-//      the item is recomputed with a running maximum.  grid.x = queries * max_row_tiles * Hkv, LDS = max(epilogue staging, one image).
+//      the item is recomputed with a running maximum.  One workgroup per (item, 32 dims of the output): the pass is bound by
+//      the latency of its loads, and a workgroup per item left a short prompt's 24 items in eight parts to 24 compute units
+//      (24 us; now 7.5; the offline stage's 128 items in two parts 13.6 -> 7.6).  A column's sum is added up by every slice; a slice that sees an overflow computes and stores its own dims.
+//      grid.x = ((query * max_row_tiles + ordinal) * D / 32 + slice) * Hkv + KV head, LDS = max(epilogue staging, one image).
 template <int G, int D, bool SPLIT, bool F32>
 __global__ __launch_bounds__(256, 2) void attn_combine_kernel(const AttnBatch batch, const float* __restrict__ partials,
                                                               int n_parts, int Hq, int Hkv, float scale_log2e) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-    BlockWork bw;
-    bw.init(batch.max_row_tiles, Hkv);
-    const AttnQuery& aq = batch.q[bw.query];
-    const int g = bw.g, ordinal = bw.ordinal, item = (int)blockIdx.x / Hkv;
+    int t = (int)blockIdx.x;
+    const int g = t % Hkv; t /= Hkv;
+    const int md = t % (D / 32);
+    const int item = t / (D / 32);
+    const int ordinal = item % batch.max_row_tiles;
+    const AttnQuery& aq = batch.q[item / batch.max_row_tiles];
     if (ordinal >= aq.n_row_tiles) return;
     {
-        constexpr int OW = Part<D, F32>::O_WORDS;
-        Geometry<G> ge;
-        ge.init(aq.q_index, aq.R, Hq, Hkv, aq.n_row_tiles, aq.n_img_tiles, g, ordinal);
-        const uint32_t* p0 = reinterpret_cast<const uint32_t*>(partials + ((size_t)item * n_parts * Hkv + g) * Part<D, F32>::WORDS) + threadIdx.x;
-        const size_t part_stride = (size_t)Hkv * Part<D, F32>::WORDS;
-        f32x16 o[D / 32][2];
+        using P = Part<D, F32>;
+        constexpr int OW = P::O_WORDS, SW = F32 ? 16 : 8;   // words of a part, of a slice of a column block
+        constexpr int AHEAD = 4;                            // parts whose loads are in flight together
+        const uint32_t* p0 = reinterpret_cast<const uint32_t*>(partials + ((size_t)item * n_parts * Hkv + g) * P::WORDS) + threadIdx.x;
+        const size_t part_stride = (size_t)Hkv * P::WORDS;
+        f32x16 acc[2];
         float lsum[2] = {0.f, 0.f}, mref[2];
 #pragma unroll
-        for (int md = 0; md < D / 32; ++md)
+        for (int nb = 0; nb < 2; ++nb) {
 #pragma unroll
-            for (int nb = 0; nb < 2; ++nb)
+            for (int v = 0; v < 16; ++v) acc[nb][v] = 0.f;
+            mref[nb] = __uint_as_float(p0[(OW + 2 + nb) * 256]);   // part 0 is never empty; every part derives the same reference
+        }
+        auto add = [&](int first, auto count) {
+            constexpr int N = decltype(count)::value;
+            uint32_t w[N][2][SW], tail[N][2][2];
 #pragma unroll
-                for (int v = 0; v < 16; ++v) o[md][nb][v] = 0.f;
+            for (int i = 0; i < N; ++i) {
+                const uint32_t* pp = p0 + (first + i) * part_stride;
 #pragma unroll
-        for (int nb = 0; nb < 2; ++nb) mref[nb] = __uint_as_float(p0[(OW + 2 + nb) * 256]);   // part 0 is never empty; every part derives the same reference
-        for (int part = 0; part < n_parts; ++part) {   // a part's loads are in flight together, then unpacked and added
-            const uint32_t* pp = p0 + part * part_stride;
-            uint32_t w[2][OW / 2];
-            uint32_t tail[2][2];
+                for (int nb = 0; nb < 2; ++nb) {
 #pragma unroll
-            for (int nb = 0; nb < 2; ++nb) {
-#pragma unroll
-                for (int j2 = 0; j2 < OW / 2; ++j2) w[nb][j2] = pp[(nb * (OW / 2) + j2) * 256];
-                tail[nb][0] = pp[(OW + nb) * 256];
-                tail[nb][1] = pp[(OW + 4 + nb) * 256];
+                    for (int j = 0; j < SW; ++j) w[i][nb][j] = pp[(nb * (OW / 2) + md * SW + j) * 256];
+                    tail[i][nb][0] = pp[(OW + nb) * 256];
+                    tail[i][nb][1] = F32 ? 0u : pp[(OW + 4 + nb) * 256];
+                }
             }
 #pragma unroll
-            for (int nb = 0; nb < 2; ++nb) {
-                const int e = (int)tail[nb][1];
+            for (int i = 0; i < N; ++i)
 #pragma unroll
-                for (int md = 0; md < D / 32; ++md)
+                for (int nb = 0; nb < 2; ++nb) {
+                    const int e = (int)tail[i][nb][1];
 #pragma unroll
                     for (int v = 0; v < 16; v += 2) {
                         if constexpr (F32) {
-                            o[md][nb][v] += __uint_as_float(w[nb][md * 16 + v]);
-                            o[md][nb][v + 1] += __uint_as_float(w[nb][md * 16 + v + 1]);
+                            acc[nb][v] += __uint_as_float(w[i][nb][v]);
+                            acc[nb][v + 1] += __uint_as_float(w[i][nb][v + 1]);
                         } else {
-                            const f16x2 h = __builtin_bit_cast(f16x2, w[nb][md * 8 + v / 2]);
-                            o[md][nb][v] += __builtin_ldexpf((float)h[0], e);
-                            o[md][nb][v + 1] += __builtin_ldexpf((float)h[1], e);
+                            const f16x2 h = __builtin_bit_cast(f16x2, w[i][nb][v / 2]);
+                            acc[nb][v] += __builtin_ldexpf((float)h[0], e);
+                            acc[nb][v + 1] += __builtin_ldexpf((float)h[1], e);
                         }
                     }
-                lsum[nb] += __uint_as_float(tail[nb][0]);
-            }
-        }
+                    lsum[nb] += __uint_as_float(tail[i][nb][0]);
+                }
+        };
+        int part = 0;
+        for (; part + AHEAD <= n_parts; part += AHEAD) add(part, std::integral_constant<int, AHEAD>{});
+        if (part + 2 <= n_parts) { add(part, std::integral_constant<int, 2>{}); part += 2; }
+        if (part < n_parts) add(part, std::integral_constant<int, 1>{});
+        Geometry<G> ge;
+        ge.init(aq.q_index, aq.R, Hq, Hkv, aq.n_row_tiles, aq.n_img_tiles, g, ordinal);
         float l[2];
-        if (!sums_overflowed<D>(o, lsum, l)) {
-            store_output<G, D>(ge, o, l, mref, aq.R, Hq, smem_raw, aq.out, aq.lse);
+        bool bad = false;
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) {
+            l[nb] = lsum[nb] + __shfl_xor(lsum[nb], 32);
+            float chk = l[nb];
+#pragma unroll
+            for (int v = 0; v < 16; ++v) chk += fabsf(acc[nb][v]);
+            bad = bad || !(chk < INFINITY) || !(l[nb] > 0.f);
+        }
+        if (!__syncthreads_or(bad ? 1 : 0)) {
+            store_slice<G, D>(ge, acc, md, l, mref, aq.R, Hq, smem_raw, aq.out, aq.lse);
             return;
         }
     }
     // the sums overflowed the fixed exponent reference (rare): the item again, with a running maximum
     __syncthreads();
-    running_max_item<G, D, SPLIT>(aq, g, ordinal, Hq, Hkv, scale_log2e, smem_raw);
+    running_max_item<G, D, SPLIT>(aq, g, ordinal, Hq, Hkv, scale_log2e, smem_raw, md);
 }
 
 // ---- all items with the running maximum (FR_ATTN_SOFTMAX_RUNNING_MAX) -------------------------------------
@@ -1107,7 +1172,7 @@ void launch_tile_loop(const AttnBatch& batch, dim3 grid, float* partials, int n_
 // parts pay until there is about one piece per compute unit (question-only prefill, 64 items: 4 parts, 0.24 -> 0.17 ms);
 // in between two parts stay best (168 items at 5 %, 128 items of the offline stage: three or four parts lose 3-15 %).
 // Short prompts (under 32 key tiles) are cut only below half a workgroup per compute unit, down to two tiles a part: a tile
-// is 1.8 us of a workgroup, the combine pass 5 us (920 tokens, 24 items of up to 15 tiles: 31 us whole, 13 + 5 in eight parts).
+// is 1.8 us of a workgroup, the combine pass 7.5 us (920 tokens, 24 items of up to 15 tiles: 31 us whole, 14 + 7.5 in eight parts).
 int choose_parts(int split_mode, int items, int n_img_tiles, int n_cu, size_t part_bytes, size_t partials_bytes) {
     int parts = 1;
     if (split_mode == FR_ATTN_SPLIT_ON) parts = 2;
@@ -1142,11 +1207,11 @@ hipError_t launch_packed(const Shape& s, const AttnBatch& batch, int n_parts, bo
     if (n_parts > 1) {   // adds the parts, stores, and recomputes the items whose sums overflowed
         if constexpr (!SPLIT) {
             if (half) {
-                attn_combine_kernel<G, D, SPLIT, false><<<grid, dim3(256), LDS_SAFE<D>, st>>>(batch, ws.attn_partials, n_parts, s.Hq, s.Hkv, scale_log2e);
+                attn_combine_kernel<G, D, SPLIT, false><<<dim3(grid.x * (D / 32)), dim3(256), LDS_SAFE<D>, st>>>(batch, ws.attn_partials, n_parts, s.Hq, s.Hkv, scale_log2e);
                 return hipGetLastError();
             }
         }
-        attn_combine_kernel<G, D, SPLIT, true><<<grid, dim3(256), LDS_SAFE<D>, st>>>(batch, ws.attn_partials, n_parts, s.Hq, s.Hkv, scale_log2e);
+        attn_combine_kernel<G, D, SPLIT, true><<<dim3(grid.x * (D / 32)), dim3(256), LDS_SAFE<D>, st>>>(batch, ws.attn_partials, n_parts, s.Hq, s.Hkv, scale_log2e);
     }
     return hipGetLastError();
 }
