@@ -2,13 +2,17 @@
 // and the Q index of Sec. 4.3 (ascending critical tokens, then the question tokens).
 //
 // Integer work only.  Scores are mapped to order-preserving 32-bit keys; a most-significant-digit
-// radix select (at most 4 passes of 8 bits, LDS histograms) finds the key of the k-th largest score; an
+// radix select (digits of 12 bits, LDS histogram) finds the key of the k-th largest score: passes go on until the bin that
+// holds it has at most CANDIDATES keys (after the first one as a rule), whose ranks are then counted directly; an
 // ordered compaction then emits, in index order, every token above that key plus the first
 // (lowest-index) tokens equal to it that are still needed.  The result is unique, so it does not
 // depend on scheduling.  One workgroup: the 64 KB of scores of a 17k-token prompt fit its registers, and the
 // whole selection is latency- rather than bandwidth-sized (longer score vectors: k_select_large.hip).  Scores of one prompt are clustered (their sign and
 // most exponent bits agree), which would pile a plain histogram onto one or two bins; the digits are therefore
-// taken from key - min(key), starting at the highest bit in which the largest and the smallest key differ.
+// taken from key - min(key), starting at the highest bit in which the largest and the smallest key differ.  Even so most scores lie near the smallest
+// one: with 256 bins the adds of a wave queued up behind one LDS word, and every pass costs its barriers and scans (four
+// passes of 8 bits: 9.6 / 19.5 / 33.0 us at 880 / 16384 / 32768 scores of a prompt, now 8.1 / 14.7 / 25.2; taking all
+// of 16384, without any search, is 8.1).
 #include "fr_internal.hpp"
 
 namespace fr {
@@ -20,34 +24,39 @@ __device__ __forceinline__ uint32_t score_key(float f) {
 
 constexpr int SEL_THREADS = 1024;
 
+constexpr int BINS = 4 * SEL_THREADS;   // one 16-byte vector of bins per thread
+constexpr int DIGIT = 12;
+constexpr uint32_t CANDIDATES = 256;
+static_assert(BINS == 1 << DIGIT, "digit");
+
 // Among the candidates of this pass (keys that share the digits fixed so far), the digit of the k-th largest
-// key is the largest d whose suffix count S[d] = sum_{b >= d} hist[b] still reaches `remaining`.  One thread
-// per bin: suffix sums by wave shuffles, then the single thread that satisfies the condition publishes it.
+// key is the largest d whose suffix count S[d] = sum_{b >= d} hist[b] still reaches `remaining`.  Four bins
+// per thread: suffix sums by wave shuffles, then the single thread that holds the matching bin publishes it.
 // `remaining` is read before the first barrier: between the two barriers the matching thread overwrites it, and the
-// four bin waves do not run in lockstep, so a read behind the first barrier could see the reduced value and let a
+// waves do not run in lockstep, so a read behind the first barrier could see the reduced value and let a
 // second bin match.  (The caller's barrier after the histogram orders this read behind the previous pass's write.)
 __device__ __forceinline__ void pick_digit(const uint32_t* hist, uint32_t* wave_tot, uint32_t* s_prefix,
-                                           uint32_t* s_remaining, int shift) {
+                                           uint32_t* s_remaining, uint32_t* s_count, int shift) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t remaining = *s_remaining;
-    uint32_t suf = 0u, own = 0u;
-    if (tid < 256) {
-        own = hist[tid];
-        suf = own;
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t t = __shfl_down(suf, o);
-            if (lane + o < 64) suf += t;
-        }
-        if (lane == 0) wave_tot[wave] = suf;   // total of bins 64 wave .. 64 wave + 63
+    const uint4 own = reinterpret_cast<const uint4*>(hist)[tid];
+    uint32_t suf = own.x + own.y + own.z + own.w;
+    const uint32_t mine = suf;
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t t = __shfl_down(suf, o);
+        if (lane + o < 64) suf += t;
     }
+    if (lane == 0) wave_tot[wave] = suf;   // total of the wave's 256 bins
     __syncthreads();
-    if (tid < 256) {
-        for (int w2 = wave + 1; w2 < 4; ++w2) suf += wave_tot[w2];
-        const uint32_t above = suf - own;      // candidates with a larger digit
-        if (suf >= remaining && above < remaining) {
-            *s_remaining = remaining - above;  // still to take among keys with this digit
-            *s_prefix |= (uint32_t)tid << shift;
-        }
+    for (int w2 = wave + 1; w2 < SEL_THREADS / 64; ++w2) suf += wave_tot[w2];
+    uint32_t above = suf - mine;           // candidates with a larger digit than any of this thread's
+    if (suf >= remaining && above < remaining) {
+        const uint32_t bins[4] = {own.x, own.y, own.z, own.w};
+        int d = 3;
+        while (d > 0 && above + bins[d] < remaining) above += bins[d--];
+        *s_remaining = remaining - above;  // still to take among keys with this digit
+        *s_count = bins[d];
+        *s_prefix |= (uint32_t)(4 * tid + d) << shift;
     }
     __syncthreads();
 }
@@ -63,10 +72,11 @@ template <int PER>
 __global__ __launch_bounds__(SEL_THREADS) void select_topk_kernel(const float* __restrict__ scores, int64_t n,
                                                                   int64_t k, int nq, int32_t* __restrict__ out) {
     constexpr int WAVES = SEL_THREADS / 64;
-    __shared__ uint32_t hist[256];
+    __shared__ __attribute__((aligned(16))) uint32_t hist[BINS];
     __shared__ uint32_t wave_a[WAVES], wave_b[WAVES];
-    __shared__ uint32_t wave_tot[4];
-    __shared__ uint32_t s_prefix, s_remaining;
+    __shared__ uint32_t wave_tot[WAVES];
+    __shared__ __attribute__((aligned(16))) uint32_t candidates[CANDIDATES];
+    __shared__ uint32_t s_prefix, s_remaining, s_count, s_listed;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 
     // question tokens: positions n .. n + nq - 1
@@ -99,21 +109,21 @@ __global__ __launch_bounds__(SEL_THREADS) void select_topk_kernel(const float* _
             kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, o));
         }
         if (lane == 0) { wave_a[wave] = kmin; wave_b[wave] = kmax; }
-        if (tid == 0) { s_prefix = 0u; s_remaining = (uint32_t)k; }
+        if (tid == 0) { s_prefix = 0u; s_remaining = (uint32_t)k; s_listed = 0u; }
+        reinterpret_cast<uint4*>(hist)[tid] = make_uint4(0u, 0u, 0u, 0u);
         __syncthreads();
         kmin = wave_a[0];
         kmax = wave_b[0];
         for (int w2 = 1; w2 < WAVES; ++w2) { kmin = min(kmin, wave_a[w2]); kmax = max(kmax, wave_b[w2]); }
-        // relative keys rk = key - kmin lie in [0, kmax - kmin]; digits of 8 bits (the last one narrower) are taken
+        // relative keys rk = key - kmin lie in [0, kmax - kmin]; digits of 12 bits (the last one narrower) are taken
         // from the highest bit in which the two extremes differ downwards
         const uint32_t span = kmax - kmin;
-        int hi_bit = (span == 0u) ? 1 : 32 - __clz((int)span);   // number of significant bits of the relative keys
+        int shift = (span == 0u) ? 1 : 32 - __clz((int)span);   // number of significant bits of the relative keys
         uint32_t mask = 0u;
-        while (hi_bit > 0) {
-            const int width = min(8, hi_bit), shift = hi_bit - width;
+        for (;;) {
+            const int width = min(DIGIT, shift);
+            shift -= width;
             const uint32_t digit_mask = (1u << width) - 1u;
-            if (tid < 256) hist[tid] = 0u;
-            __syncthreads();
             const uint32_t prefix = s_prefix;
 #pragma unroll
             for (int i = 0; i < PER; ++i) {
@@ -121,9 +131,38 @@ __global__ __launch_bounds__(SEL_THREADS) void select_topk_kernel(const float* _
                 if (i < cnt && (rk & mask) == prefix) atomicAdd(&hist[(rk >> shift) & digit_mask], 1u);
             }
             __syncthreads();
-            pick_digit(hist, wave_tot, &s_prefix, &s_remaining, shift);
+            pick_digit(hist, wave_tot, &s_prefix, &s_remaining, &s_count, shift);
             mask |= digit_mask << shift;
-            hi_bit = shift;
+            if (shift == 0 || s_count <= CANDIDATES) break;
+            reinterpret_cast<uint4*>(hist)[tid] = make_uint4(0u, 0u, 0u, 0u);   // (read before pick_digit's barriers)
+            __syncthreads();
+        }
+        if (shift > 0) {   // the remaining digits of at most CANDIDATES keys: count how many are larger than, and equal to, each
+            const uint32_t prefix = s_prefix, count = s_count, remaining = s_remaining;
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                const uint32_t rk = keys[i] - kmin;
+                if (i < cnt && (rk & mask) == prefix) candidates[atomicAdd(&s_listed, 1u)] = rk;
+            }
+            __syncthreads();
+            if (tid < (int)count) {
+                const uint32_t own = candidates[tid];
+                uint32_t larger = 0u, equal = 0u;
+                for (uint32_t j = 0; j < count; j += 4) {
+                    const uint4 c = *reinterpret_cast<const uint4*>(&candidates[j]);   // entries past `count` do not count
+                    const uint32_t v[4] = {c.x, c.y, c.z, c.w};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        larger += (j + e < count && v[e] > own) ? 1u : 0u;
+                        equal += (j + e < count && v[e] == own) ? 1u : 0u;
+                    }
+                }
+                if (larger < remaining && larger + equal >= remaining) {   // (every copy of the k-th largest key writes the same)
+                    s_prefix = own;
+                    s_remaining = remaining - larger;
+                }
+            }
+            __syncthreads();
         }
         thr_key = s_prefix + kmin;
         need_eq = s_remaining;

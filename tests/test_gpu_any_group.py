@@ -187,3 +187,26 @@ def test_parts_of_short_prompts_keep_32_bits(Hq, Hkv, d):
         outs.append(run_attention(ctx, w, qi, k_cache, v_cache)[0])
         ctx.close()
     assert np.linalg.norm(outs[1] - outs[0]) <= 1.2e-4 * np.linalg.norm(outs[0])
+
+
+@pytest.mark.parametrize("in_bin", [1, 2, 255, 256, 257, 300])
+@pytest.mark.parametrize("n", [900, 8193, 32768])
+def test_select_rank_inside_a_histogram_bin(n, in_bin):
+    """The k-th largest score lies in a bin of `in_bin` keys, around the number that is ranked directly: every rank in it,
+    with distinct keys and with ties."""
+    ctx = H.make_ctx(synth.TINY_F32, 70000, 4, 16)
+    rng = np.random.default_rng(n + in_bin)
+    top = n // 10
+    for ties in (1, 3):
+        s = np.empty(n, dtype=np.float32)
+        s[:top] = 64.0 + rng.random(top)                                       # larger than all of the bin
+        s[top:top + in_bin] = 8.0 + (np.arange(in_bin) // ties) * 2.0 ** -20    # one unit in the last place apart: one bin
+        s[top + in_bin:] = 1.0 + rng.random(n - top - in_bin)
+        s = s[rng.permutation(n)]
+        dev = torch.from_numpy(s).cuda()
+        for k in sorted({top, top + 1, top + 2, top + in_bin // 2 + 1, top + in_bin, min(n - 1, top + in_bin + 1)}):
+            out = torch.full((k + 1,), -7, dtype=torch.int32, device="cuda")
+            ctx.fr_select_topk(dev, n, k, 1, out)
+            torch.cuda.synchronize()
+            assert np.array_equal(out.cpu().numpy(), orc.select_q_index(s, k, 1)), (ties, k)
+    ctx.close()
