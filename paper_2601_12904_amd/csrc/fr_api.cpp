@@ -321,10 +321,8 @@ fr_status fr_rope_shift(fr_ctx* ctx, const void* k_src, void* k_dst, const int32
     if (L_ctx == 0 || n_batch == 0) return FR_OK;
     if ((st = need_device(ctx)) != FR_OK) return st;
     hipStream_t hs = (hipStream_t)stream;
-    hipError_t e = launch_rope_table(s, dl, n_chunks, ctx->ws.rope_table, hs);
-    if (e != hipSuccess) return hip_fail(ctx, "rope table launch", e);
-    e = launch_rope_shift(s, k_src, k_dst, ct, max_len, ctx->ws.rope_table, n_batch, src_batch_stride,
-                          dst_batch_stride, nullptr, hs);
+    const hipError_t e = launch_rope_shift(s, k_src, k_dst, ct, dl, max_len, ctx->ws.rope_theta, n_batch, src_batch_stride,
+                                           dst_batch_stride, nullptr, hs);
     if (e != hipSuccess) return hip_fail(ctx, "rope shift launch", e);
     return FR_OK;
 }
@@ -427,13 +425,11 @@ static fr_status gather_from_store(fr_ctx* ctx, const void* k_store, const void*
     hipError_t e = hipSuccess;
     if (L_ctx > 0) {
         const ChunkDeltas zero{};
-        e = launch_rope_table(s, zero, ct.n, ctx->ws.rope_table, hs);
-        if (e == hipSuccess) e = launch_rope_shift(s, v_store, ctx->ws.store_v, ct, max_len, ctx->ws.rope_table, 1, 0, 0, &rows, hs);
+        e = launch_rope_shift(s, v_store, ctx->ws.store_v, ct, zero, max_len, ctx->ws.rope_theta, 1, 0, 0, &rows, hs);
         if (e != hipSuccess) return hip_fail(ctx, "value gather launch", e);
     }
     if (L_ctx > 0) {
-        e = launch_rope_table(s, dl, ct.n, ctx->ws.rope_table, hs);
-        if (e == hipSuccess) e = launch_rope_shift(s, k_store, ctx->ws.store_k, ct, max_len, ctx->ws.rope_table, 1, 0, 0, &rows, hs);
+        e = launch_rope_shift(s, k_store, ctx->ws.store_k, ct, dl, max_len, ctx->ws.rope_theta, 1, 0, 0, &rows, hs);
         if (e != hipSuccess) return hip_fail(ctx, "key gather launch", e);
     }
     const int64_t row_words = (int64_t)s.Hkv * s.d * s.esize / 4;
@@ -493,7 +489,7 @@ fr_status fr_score_select_shared(fr_ctx* ctx, const void* q_question, int32_t nq
         if (nq == 0) {   // no question rows: every score is an empty sum (the generic kernel writes the zeros; no key is read)
             e = launch_score_simt(s, q_question, 0, k_store, L_ctx, scores, hs);
         } else {
-            e = launch_rope_table(s, dl, n_chunks, ctx->ws.rope_table, hs);
+            e = launch_rope_table(s, dl, n_chunks, ctx->ws.rope_theta, ctx->ws.rope_table, hs);
             if (e != hipSuccess) return hip_fail(ctx, "rope table launch", e);
             e = launch_score(s, q_question, nq, k_store, ct, norm, ctx->ws, scores, chunk_store_row0, ctx->ws.rope_table, hs);
         }
@@ -625,7 +621,7 @@ fr_status fr_sparse_prefill_attn_shared(fr_ctx* ctx, const void* q_rows, const i
         if (e != hipSuccess) return hip_fail(ctx, "attention launch", e);
         return FR_OK;
     }
-    e = launch_rope_table(s, dl, n_chunks, ctx->ws.rope_table, hs);
+    e = launch_rope_table(s, dl, n_chunks, ctx->ws.rope_theta, ctx->ws.rope_table, hs);
     if (e != hipSuccess) return hip_fail(ctx, "rope table launch", e);
     sh.table = ctx->ws.rope_table;
     e = launch_attn_mfma(s, q_rows, q_index, R, k_store, v_store, L, k_new, v_new, out, lse_out, ctx->ws,
@@ -732,7 +728,7 @@ fr_status fr_sparse_prefill_attn_shared_batch(fr_ctx* ctx, const fr_shared_query
             const BatchScratch b = batch_scratch(s, w.L, off);
             off = b.end;
             float2* table = reinterpret_cast<float2*>(base + b.table);
-            hipError_t e = launch_rope_table(s, deltas[i], w.shared.ct.n, table, hs);
+            hipError_t e = launch_rope_table(s, deltas[i], w.shared.ct.n, ctx->ws.rope_theta, table, hs);
             if (e != hipSuccess) return hip_fail(ctx, "rope table launch", e);
             w.shared.table = table;
             w.store_row_map = reinterpret_cast<int32_t*>(base + b.srow);

@@ -101,12 +101,13 @@ struct fr_ctx {
 namespace fr {
 
 // Launchers.  Each returns hipSuccess or the launch error; none synchronises.
-hipError_t launch_rope_table(const Shape& s, const ChunkDeltas& deltas, int n_chunks, float2* table,
+// theta: device, [d/2] rotary frequencies
+hipError_t launch_rope_table(const Shape& s, const ChunkDeltas& deltas, int n_chunks, const double* theta, float2* table,
                              hipStream_t st);
 // src_rows != NULL: chunk c's source rows start at src row src_rows->row0[c] (a chunk store) instead of at its
 // prompt offset.
-hipError_t launch_rope_shift(const Shape& s, const void* src, void* dst, const ChunkTable& ct,
-                             int max_chunk_len, const float2* table, int n_batch, int64_t src_stride,
+hipError_t launch_rope_shift(const Shape& s, const void* src, void* dst, const ChunkTable& ct, const ChunkDeltas& deltas,
+                             int max_chunk_len, const double* theta, int n_batch, int64_t src_stride,
                              int64_t dst_stride, const ChunkRows* src_rows, hipStream_t st);
 hipError_t launch_clear_words(uint32_t* words, int64_t n_words, hipStream_t st);
 hipError_t launch_kv_scatter(const Shape& s, const void* k_new, const void* v_new, const int32_t* q_index,

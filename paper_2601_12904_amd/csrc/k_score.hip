@@ -497,7 +497,7 @@ __global__ __launch_bounds__(256) void score_lse_combine_kernel(ChunkTable ct, i
 
 // Sum of a token's n_parts partial sums: 64 tokens per workgroup, wave w adds parts w, w + groups, ... and the waves' sums
 // are added in order.  One thread per token walked up to 128 parts of a short prompt one after the other (10.8 us for 880
-// tokens, 6.0 for 16384); with at most REDUCE_AHEAD parts per wave, all in flight together, it is one round trip (3.5, 4.7).
+// tokens, 6.0 for 16384); with at most REDUCE_AHEAD parts per wave, all in flight together, it is one round trip (2.6, 4.8).
 constexpr int REDUCE_AHEAD = 8, REDUCE_MAX_WAVES = 16;
 __global__ __launch_bounds__(64 * REDUCE_MAX_WAVES) void score_reduce_kernel(const float* __restrict__ partial, int n_parts, int L_ctx,
                                                                              float* __restrict__ scores) {
@@ -507,12 +507,10 @@ __global__ __launch_bounds__(64 * REDUCE_MAX_WAVES) void score_reduce_kernel(con
     for (int i0 = threadIdx.y; i0 < n_parts; i0 += REDUCE_AHEAD * groups) {
         float v[REDUCE_AHEAD];
 #pragma unroll
-        for (int u = 0; u < REDUCE_AHEAD; ++u) {
-            const int i = i0 + u * groups;
-            v[u] = i < n_parts ? partial[(size_t)i * L_ctx + j] : 0.f;
-        }
+        for (int u = 0; u < REDUCE_AHEAD; ++u)   // (clamped rather than skipped: behind a branch each load would be waited for)
+            v[u] = partial[(size_t)min(i0 + u * groups, n_parts - 1) * L_ctx + j];
 #pragma unroll
-        for (int u = 0; u < REDUCE_AHEAD; ++u) t += v[u];
+        for (int u = 0; u < REDUCE_AHEAD; ++u) t += i0 + u * groups < n_parts ? v[u] : 0.f;
     }
     sums[threadIdx.y][threadIdx.x] = t;
     __syncthreads();
