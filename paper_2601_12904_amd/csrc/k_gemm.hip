@@ -6,7 +6,8 @@
 // kernel computes the transposed tile C^T = W A^T with v_mfma_f32_32x32x16_bf16: output features run along the
 // accumulator's register dimension and activation rows along lanes, which puts four consecutive features of one
 // row into one lane -- rotary pairs and (gate, up) pairs are then combined without any lane exchange.
-// One workgroup computes (64 WF) features x 128 rows with WF x 2 waves of 64 x 64 each: WF = 4 (8 waves, two per
+// Large launches run the 256 x 256 kernel further down; in the others
+// one workgroup computes (64 WF) features x 128 rows with WF x 2 waves of 64 x 64 each: WF = 4 (8 waves, two per
 // SIMD, so one wave's LDS reads and barriers hide behind the other's matrix instructions; 48 KB per K tile, ring
 // of 3) where the feature count allows, else WF = 2 (4 waves, 32 KB per K tile, ring of 4).  K is walked in tiles
 // of 64: both operand tiles (rows of 128 bytes) are copied straight into an LDS ring with direct-to-LDS loads
@@ -33,10 +34,43 @@ constexpr int BR = 128;   // activation rows per workgroup (MFMA N side)
 constexpr int BK = 64;    // K elements per tile: 128 bytes per row
 constexpr int EPI_PITCH = 64 + 4;                   // fp32 elements per row of a wave's epilogue staging
 
+enum { EPI_STORE = 0, EPI_RESIDUAL = 1, EPI_QKV_ROPE = 2, EPI_SWIGLU = 3 };
+
+struct GemmArgs {
+    const __bf16* a;        // [M, K]
+    const __bf16* w;        // [N, K]
+    int M, N, K;
+    __bf16* out;            // EPI_STORE / EPI_RESIDUAL: [M, N];  EPI_SWIGLU: [M, N / 2]
+    const __bf16* residual; // EPI_RESIDUAL: [M, N]
+    // EPI_QKV_ROPE: features [0, Hq d) -> q_out[M, Hq, d] rotated, [Hq d, (Hq + Hkv) d) -> k_out rotated, rest -> v_out
+    __bf16 *q_out, *k_out, *v_out;
+    const float2* rope;     // [M][d / 2] (cos, sin) of each row's position
+    int Hq, Hkv, d;
+    // Tail split.  Tiles [0, n_whole) are computed by one workgroup each; every later tile by n_parts workgroups that
+    // walk 1 / n_parts of K each and leave their fp32 accumulators in `partials` (gemm_fixup_kernel adds them and
+    // runs the epilogue).  n_parts = 1: no tile is split.
+    int n_whole, n_parts;
+    float* partials;        // [(tile - n_whole) * n_parts + part][wave][64 registers][64 lanes]
+    size_t partials_bytes;  // (host side: what the buffer holds)
+};
+
 template <int WF>
 struct Tiling {
     static constexpr int NW = 2 * WF;                    // waves per workgroup
     static constexpr int BF = 64 * WF;                   // output features per workgroup (MFMA M side)
+    static constexpr int BRT = BR;                       // and rows
+    static constexpr int WAVE_TILES = NW;                // 64 x 64 pieces of the output tile
+    // What a launch takes (plan_tiling): time per K tile of a full round, the share of it that a nearly empty round still
+    // takes (a full round is held back by the chip's power limit), pipeline fill and epilogue, a split last round.
+    static constexpr float US_PER_K_TILE = 0.9f, ROUND_BASE = 0.5f, US_LAUNCH = 3.0f, US_SPLIT = 14.0f;
+    static __host__ __device__ constexpr int feature0(int v) { return 64 * (v % WF); }
+    static __host__ __device__ constexpr int row_0(int v) { return 64 * (v / WF); }
+    // feature tiles fastest, so that workgroups that share an activation tile are neighbours
+    static __device__ __forceinline__ void origin(const GemmArgs& g, int tile, int& f0, int& r0) {
+        const int n_f = (g.N + BF - 1) / BF;
+        f0 = (tile % n_f) * BF;
+        r0 = (tile / n_f) * BRT;
+    }
     static constexpr int W_TILE_BYTES = BF * BK * 2;     // 16 or 32 KB
     static constexpr int A_TILE_BYTES = BR * BK * 2;     // 16 KB
     static constexpr int STAGE_BYTES = W_TILE_BYTES + A_TILE_BYTES;
@@ -89,25 +123,6 @@ __device__ __forceinline__ void barrier_keep_loads_in_flight() {
     asm volatile("" ::: "memory");
 }
 
-enum { EPI_STORE = 0, EPI_RESIDUAL = 1, EPI_QKV_ROPE = 2, EPI_SWIGLU = 3 };
-
-struct GemmArgs {
-    const __bf16* a;        // [M, K]
-    const __bf16* w;        // [N, K]
-    int M, N, K;
-    __bf16* out;            // EPI_STORE / EPI_RESIDUAL: [M, N];  EPI_SWIGLU: [M, N / 2]
-    const __bf16* residual; // EPI_RESIDUAL: [M, N]
-    // EPI_QKV_ROPE: features [0, Hq d) -> q_out[M, Hq, d] rotated, [Hq d, (Hq + Hkv) d) -> k_out rotated, rest -> v_out
-    __bf16 *q_out, *k_out, *v_out;
-    const float2* rope;     // [M][d / 2] (cos, sin) of each row's position
-    int Hq, Hkv, d;
-    // Tail split.  Tiles [0, n_whole) are computed by one workgroup each; every later tile by n_parts workgroups that
-    // walk 1 / n_parts of K each and leave their fp32 accumulators in `partials` (gemm_fixup_kernel adds them and
-    // runs the epilogue).  n_parts = 1: no tile is split.
-    int n_whole, n_parts;
-    float* partials;        // [(tile - n_whole) * n_parts + part][wave][64 registers][64 lanes]
-    size_t partials_bytes;  // (host side: what the buffer holds)
-};
 constexpr int PARTIAL_FLOATS_PER_WAVE = 64 * 64;
 constexpr int MIN_K_TILES_PER_PART = 16;
 
@@ -191,13 +206,11 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, f32x16 (&acc)[2
 template <int EPI, int WF>
 __global__ __launch_bounds__(128 * WF) void gemm_bf16_kernel(GemmArgs g) {
     using TL = Tiling<WF>;
-    constexpr int NW = TL::NW, BF = TL::BF, STAGE_BYTES = TL::STAGE_BYTES, N_STAGE = TL::N_STAGE;
+    constexpr int NW = TL::NW, STAGE_BYTES = TL::STAGE_BYTES, N_STAGE = TL::N_STAGE;
     constexpr int DMA_PER_TILE = TL::W_ROUNDS + TL::A_ROUNDS;   // outstanding copies per lane and K tile
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, x = lane & 31, h = lane >> 5;
     const int wf = wave % WF, wr = wave / WF;          // wave position: features x rows
-    // tile order: feature tiles fastest, so that workgroups that share an activation tile are neighbours
-    const int n_ftiles = (g.N + BF - 1) / BF;
     int tile = (int)blockIdx.x, part = 0;
     if (tile >= g.n_whole) {
         const int j = tile - g.n_whole;
@@ -205,7 +218,8 @@ __global__ __launch_bounds__(128 * WF) void gemm_bf16_kernel(GemmArgs g) {
         part = j % g.n_parts;
     }
     const bool split_tile = (int)blockIdx.x >= g.n_whole && g.n_parts > 1;
-    const int f0 = (tile % n_ftiles) * BF, r0 = (tile / n_ftiles) * BR;
+    int f0, r0;
+    TL::origin(g, tile, f0, r0);
     const int n_kt_all = g.K / BK;
     const int kt_begin = split_tile ? (int)((int64_t)n_kt_all * part / g.n_parts) : 0;
     const int kt_end = split_tile ? (int)((int64_t)n_kt_all * (part + 1) / g.n_parts) : n_kt_all;
@@ -333,20 +347,254 @@ __global__ __launch_bounds__(128 * WF) void gemm_bf16_kernel(GemmArgs g) {
     gemm_epilogue<EPI>(g, acc, smem, wave, lane, f0 + 64 * wf, r0 + 64 * wr);
 }
 
+// The 256 x 256 kernel: eight waves (two per SIMD) of 128 features x 64 rows, K tiles of 64 in two stages of LDS.
+//
+// What bounds the 256 x 128 kernel is the vector-memory path that feeds the ring (48 KB per K tile and 16 matrix
+// instructions of a wave; 64 KB per 32 here), and the fragment reads, one per matrix instruction (24 per 32 here).
+// The eight waves run as two groups half a phase apart: while one wave of a SIMD multiplies (8 matrix instructions, a
+// quarter of its tile, at raised priority), the other one reads fragments and issues copies; a barrier separates any
+// two half phases.  Per K tile and wave (w = its 4 blocks of 32 features, a = its 2 blocks of 32 rows):
+//
+//   phase   reads for this phase and the next ones    copies of tile k + 2    products
+//     0     a0, first half of w2                       w0, w1                  (w0, w1) x a0
+//     1     a1, second half of w2                      a0                      (w0, w1) x a1
+//     2     w3; first quarter of the next w0, w1       a1                      (w2, w3) x a1
+//     3     the rest of the next w0, w1                w2, w3                  (w2, w3) x a0
+//
+// Six reads (one in 16 cycles) per phase of 256 cycles of the matrix pipe.  A stage consists of four 16 KB pieces (w0 w1
+// of all waves, w2 w3, a0, a1).  A wave waits for its own reads before the barrier that ends its half phase, so a piece is
+// free one phase after it was last read, which is when its copy for tile k + 2 goes out; that copy is waited for (by
+// count, never to zero before the last two tiles) five to seven phases later, at the end of the phase in front of its
+// first read.
+// At 4096 rows of the gate / up projection (N = 28672, K = 4096): 882 -> 707 us, 1360 TFLOP/s on normally distributed
+// operands, 1830 on zeros (1054 before): with real data the chip's power limit is the bound, no longer the schedule.
+// Waiting only for the reads that the coming products need, with the copies one phase later: no difference.
+struct Tiling256 {
+    static constexpr int NW = 8;
+    static constexpr int BF = 256, BRT = 256;
+    static constexpr int PIECE = 128 * BK * 2;             // 16 KB
+    static constexpr int STAGE = 4 * PIECE;                // [w0 w1][w2 w3][a0][a1]
+    static constexpr int WAVE_TILES = 16;                  // 64 x 64 pieces of the output tile, two per wave
+    static constexpr int LDS_BYTES = NW * 64 * EPI_PITCH * 4;
+    static constexpr float US_PER_K_TILE = 1.5f, ROUND_BASE = 0.2f, US_LAUNCH = 7.0f, US_SPLIT = 22.0f;   // see Tiling
+    static_assert(2 * STAGE <= LDS_BYTES, "the epilogue staging is the larger one");
+    static __host__ __device__ constexpr int feature0(int v) { return 128 * (v >> 3) + 64 * (v & 1); }   // v = 2 wave + half
+    static __host__ __device__ constexpr int row_0(int v) { return 64 * ((v >> 1) & 3); }
+    static __device__ __forceinline__ void origin(const GemmArgs& g, int tile, int& f0, int& r0) {
+        // rows fastest inside groups of 8 row tiles: the 32 workgroups of an XCD walk about 8 x 4 tiles, so its L2 takes 12
+        // operand slices instead of up to 35 (gate / up, 2970 rows: 567 -> 551 us; the other projections unchanged)
+        constexpr int GR = 8;
+        const int n_f = (g.N + BF - 1) / BF, n_r = (g.M + BRT - 1) / BRT;
+        const int grp = tile / (GR * n_f), in = tile % (GR * n_f), gr = min(GR, n_r - grp * GR);
+        f0 = in / gr * BF;
+        r0 = (grp * GR + in % gr) * BRT;
+    }
+};
+
+template <int EPI>
+__global__ __launch_bounds__(512) void gemm_bf16_256_kernel(GemmArgs g) {
+    using TL = Tiling256;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & 63, x = lane & 31, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wf = wave >> 2, wr = wave & 3;           // 2 x 4 waves; waves w and w + 4 share a SIMD
+    int tile = (int)blockIdx.x, part = 0;
+    const bool split_tile = tile >= g.n_whole && g.n_parts > 1;
+    if (split_tile) {
+        const int j = tile - g.n_whole;
+        tile = g.n_whole + j / g.n_parts;
+        part = j % g.n_parts;
+    } else {   // workgroups go to the XCDs in turn: XCD x takes the x-th run of whole tiles
+        const int q = g.n_whole >> 3, extra = g.n_whole & 7, xcd = tile & 7;
+        tile = xcd * q + min(xcd, extra) + (tile >> 3);
+    }
+    int f0, r0;
+    TL::origin(g, tile, f0, r0);
+    const int n_kt_all = g.K / BK;
+    const int kt_begin = split_tile ? (int)((int64_t)n_kt_all * part / g.n_parts) : 0;
+    const int kt_end = split_tile ? (int)((int64_t)n_kt_all * (part + 1) / g.n_parts) : n_kt_all;
+    const int n_kt = kt_end - kt_begin;
+
+    // Copies: 16-byte chunk u of a piece lies at byte 16 u; row r of a w piece is feature 128 (r / 64) + r % 64 of the
+    // tile (+ 64 in the second one), row r of an a piece is row 64 (r / 32) + r % 32 (+ 32).  Rows past the end are
+    // clamped and never stored.
+    uint32_t w_off[2], a_off[2][2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int u = (j * TL::NW + wave) * 64 + lane;
+        const int r = u >> 3, c = (u & 7) ^ swz(r);
+        w_off[j] = (uint32_t)(((int64_t)(128 * (r >> 6) + (r & 63)) * g.K + 8 * c) * 2);
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf)
+            a_off[hf][j] = (uint32_t)(((int64_t)(min(r0 + 64 * (r >> 5) + (r & 31) + 32 * hf, g.M - 1) - r0) * g.K + 8 * c) * 2);
+    }
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem);
+    const unsigned char* w_src = reinterpret_cast<const unsigned char*>(g.w + (int64_t)f0 * g.K + (int64_t)kt_begin * BK);
+    const unsigned char* a_src = reinterpret_cast<const unsigned char*>(g.a + (int64_t)r0 * g.K + (int64_t)kt_begin * BK);
+    const int64_t w_half = (int64_t)64 * g.K * 2;
+    enum { W01 = 0, W23 = 1, A0 = 2, A1 = 3 };
+    auto copy = [&](auto piece_c, int kt) {
+        constexpr int piece = decltype(piece_c)::value;
+        const uint32_t dst = lds0 + (uint32_t)(kt & 1) * TL::STAGE + piece * TL::PIECE;
+        const int64_t k_bytes = (int64_t)kt * BK * 2;
+        if constexpr (piece == W01) dma_tile<2, TL::NW>(w_src + k_bytes, w_off, dst, wave);
+        if constexpr (piece == W23) dma_tile<2, TL::NW>(w_src + w_half + k_bytes, w_off, dst, wave);
+        if constexpr (piece == A0) dma_tile<2, TL::NW>(a_src + k_bytes, a_off[0], dst, wave);
+        if constexpr (piece == A1) dma_tile<2, TL::NW>(a_src + k_bytes, a_off[1], dst, wave);
+    };
+    using CW01 = std::integral_constant<int, W01>;
+    using CW23 = std::integral_constant<int, W23>;
+    using CA0 = std::integral_constant<int, A0>;
+    using CA1 = std::integral_constant<int, A1>;
+
+    // Fragment reads: row 64 wf + 32 b + x of a w piece (b = 0, 1), row 32 wr + x of an a piece; k step ks -> chunk
+    // (2 ks + h) ^ swz(row), and swz(32 m + x) = swz(x) ^ 4 (m & 1), so block b reads where block 0 of step ks ^ 2 b does.
+    typedef const bf16x8 __attribute__((address_space(3))) * lds_frag_ptr;
+    uint32_t rd_w[4], rd_a[4];
+    {
+        const uint32_t lds_v = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            rd_w[ks] = lds_v + (64 * wf + x) * 128 + (((2 * ks + h) ^ swz(x)) << 4);
+            rd_a[ks] = lds_v + A0 * TL::PIECE + (32 * wr + x) * 128 + (((2 * ks + h) ^ swz(x) ^ (4 * (wr & 1))) << 4);
+        }
+    }
+    // (the other stage is reached by adding its offset with one vector instruction per address and tile: it lies beyond the
+    // 64 KB of an instruction's offset field)
+    int stage_step = TL::STAGE;
+    auto frag_w = [&](int blk, int ks) {
+        return *reinterpret_cast<lds_frag_ptr>((uintptr_t)(rd_w[ks ^ (2 * (blk & 1))] + (blk >> 1) * TL::PIECE + (blk & 1) * (32 * 128)));
+    };
+    auto frag_a = [&](int hf, int ks) { return *reinterpret_cast<lds_frag_ptr>((uintptr_t)(rd_a[ks] + hf * TL::PIECE)); };
+
+    f32x16 acc[2][2][2];   // [features + 64][features + 32][rows + 32]
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+            for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[q][mb][nb][v] = 0.f;
+
+    bf16x8 w[4][4], a[2][4];   // [block][k step]
+    auto end_of_reads = [&] {  // own reads complete; then both groups change places
+        __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
+        __builtin_amdgcn_sched_barrier(0);
+        barrier_keep_loads_in_flight();
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto multiply = [&](auto q_c, auto hf_c) {
+        constexpr int q = decltype(q_c)::value, hf = decltype(hf_c)::value;
+        __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+            for (int mb = 0; mb < 2; ++mb)
+                acc[q][mb][hf] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[2 * q + mb][ks], a[hf][ks], acc[q][mb][hf], 0, 0, 0);
+        __builtin_amdgcn_s_setprio(0);
+        __builtin_amdgcn_sched_barrier(0);
+        barrier_keep_loads_in_flight();
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+
+    copy(CW01{}, 0); copy(CA0{}, 0); copy(CA1{}, 0); copy(CW23{}, 0);
+    if (n_kt > 1) {
+        copy(CW01{}, 1); copy(CA0{}, 1); copy(CA1{}, 1); copy(CW23{}, 1);
+        __builtin_amdgcn_s_waitcnt(0x0f70 | 8);
+    } else {
+        __builtin_amdgcn_s_waitcnt(0x0f70);
+    }
+    barrier_keep_loads_in_flight();
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) { w[0][ks] = frag_w(0, ks); w[1][ks] = frag_w(1, ks); }
+    end_of_reads();
+    if (wave >= 4) barrier_keep_loads_in_flight();   // the second group starts half a phase later
+
+    for (int kt = 0; kt < n_kt; ++kt) {
+        const bool more = kt + 2 < n_kt;
+        // phase 0
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) a[0][ks] = frag_a(0, ks);
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) w[2][ks] = frag_w(2, ks);
+        if (more) copy(CW01{}, kt + 2);
+        end_of_reads();
+        multiply(I0{}, I0{});
+        // phase 1
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) a[1][ks] = frag_a(1, ks);
+#pragma unroll
+        for (int ks = 2; ks < 4; ++ks) w[2][ks] = frag_w(2, ks);
+        if (more) {
+            copy(CA0{}, kt + 2);
+            __builtin_amdgcn_s_waitcnt(0x0f70 | 10);   // w0, w1 of the next tile are there
+        } else {
+            __builtin_amdgcn_s_waitcnt(0x0f70 | 6);
+        }
+        end_of_reads();
+        multiply(I0{}, I1{});
+        // phase 2
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) w[3][ks] = frag_w(3, ks);
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {   // on to the other stage (behind the last tile: stale data, never used)
+            rd_w[ks] += stage_step;
+            rd_a[ks] += stage_step;
+        }
+        stage_step = -stage_step;
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) w[0][ks] = frag_w(0, ks);
+        if (more) copy(CA1{}, kt + 2);
+        end_of_reads();
+        multiply(I1{}, I1{});
+        // phase 3
+#pragma unroll
+        for (int ks = 2; ks < 4; ++ks) w[0][ks] = frag_w(0, ks);
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) w[1][ks] = frag_w(1, ks);
+        if (more) {
+            copy(CW23{}, kt + 2);
+            __builtin_amdgcn_s_waitcnt(0x0f70 | 8);    // everything of the next tile is there
+        } else {
+            __builtin_amdgcn_s_waitcnt(0x0f70);
+        }
+        end_of_reads();
+        multiply(I1{}, I0{});
+    }
+    if (wave < 4) barrier_keep_loads_in_flight();
+
+    if (split_tile) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            float* dst = g.partials + ((size_t)(((int)blockIdx.x - g.n_whole) * TL::WAVE_TILES + 2 * wave + q)) * PARTIAL_FLOATS_PER_WAVE + lane;
+#pragma unroll
+            for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+                for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) dst[((2 * mb + nb) * 16 + v) * 64] = acc[q][mb][nb][v];
+        }
+        return;
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+        gemm_epilogue<EPI>(g, acc[q], smem, wave, lane, f0 + TL::feature0(2 * wave + q), r0 + TL::row_0(2 * wave + q));
+}
+
 // Adds the n_parts partial sums of every split tile and runs the epilogue on the result.  One wave per workgroup and
 // grid.x = split tiles * NW: the work is a stream of partial sums, and with a 17 KB staging area instead of the
 // ring's LDS many of these small workgroups share a CU and keep enough loads in flight.
-template <int EPI, int WF>
+template <int EPI, class TL>
 __global__ __launch_bounds__(64) void gemm_fixup_kernel(GemmArgs g) {
-    using TL = Tiling<WF>;
-    constexpr int NW = TL::NW, BF = TL::BF;
+    constexpr int NW = TL::WAVE_TILES;
     __shared__ __attribute__((aligned(16))) unsigned char smem[64 * EPI_PITCH * 4];
     const int lane = threadIdx.x;
     const int split = (int)blockIdx.x / NW, wave = (int)blockIdx.x % NW;
-    const int wf = wave % WF, wr = wave / WF;
-    const int n_ftiles = (g.N + BF - 1) / BF;
-    const int tile = g.n_whole + split;
-    const int f0 = (tile % n_ftiles) * BF, r0 = (tile / n_ftiles) * BR;
+    int f0, r0;
+    TL::origin(g, g.n_whole + split, f0, r0);
     f32x16 acc[2][2];
 #pragma unroll
     for (int mb = 0; mb < 2; ++mb)
@@ -363,7 +611,7 @@ __global__ __launch_bounds__(64) void gemm_fixup_kernel(GemmArgs g) {
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[mb][nb][v] += src[((2 * mb + nb) * 16 + v) * 64];
     }
-    gemm_epilogue<EPI>(g, acc, smem, /*staging slot*/ 0, lane, f0 + 64 * wf, r0 + 64 * wr);
+    gemm_epilogue<EPI>(g, acc, smem, /*staging slot*/ 0, lane, f0 + TL::feature0(wave), r0 + TL::row_0(wave));
 }
 
 // y = x * rsqrt(mean(x^2) + eps) * gain, one wave per row, fp32 statistics.
@@ -402,58 +650,77 @@ __global__ void rope_rows_table_kernel(const int32_t* __restrict__ positions, in
     table[(size_t)r * half_d + p] = make_float2((float)cs, (float)sn);
 }
 
-template <int EPI, int WF>
-hipError_t launch_gemm_wf(GemmArgs g, const GemmTuning& tune, hipStream_t st) {
-    using TL = Tiling<WF>;
-    // once per process (a function-local static is initialised exactly once, also under concurrent first calls)
-    struct Setup { hipError_t err; int n_cu; };
-    static const Setup setup = [] {
-        Setup r{hipSuccess, 0};
-        r.err = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_kernel<EPI, WF>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, TL::LDS_BYTES);
-        if (r.err != hipSuccess) return r;
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&r.n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || r.n_cu <= 0)
-            r.err = hipErrorInvalidDevice;
-        return r;
-    }();
-    if (setup.err != hipSuccess) return setup.err;
-    const int n_cu = setup.n_cu;
-    // One workgroup per CU at a time (the LDS ring fills it), so a launch runs in rounds of n_cu tiles and a last round
-    // of `rest` tiles leaves CUs idle.  The tiles of that round are split along K over n_cu / rest workgroups each: the
-    // round then takes 1 / n_parts of a tile's time, and the launch rest / n_cu rounds less.
-    const int n_tiles = ((g.N + TL::BF - 1) / TL::BF) * ((g.M + BR - 1) / BR);
-    const int rest = n_tiles % n_cu;
+// How a launch of one tiling is laid out, and what it takes.
+// One workgroup per CU at a time (the LDS ring fills it), so a launch runs in rounds of n_cu tiles and a last round
+// of `rest` tiles leaves CUs idle.  The tiles of that round are split along K over n_cu / rest workgroups each: the
+// round then takes 1 / n_parts of a tile's time, and the launch rest / n_cu rounds less.
+// A part pays its own pipeline fill, a dump of partial sums (128 or 256 KB) and its share of the second kernel (13 us for
+// 128 tiles of 256 x 128 in two parts).  Measured at 2970 rows with 256 x 128 tiles: K = 14336, 384 tiles, two parts of
+// 112 K tiles: 9 % less time; K = 4096, 576 tiles, four parts of 16: 8 % less; K = 4096, 384 tiles, two parts of 32: 4 %
+// less; K = 4096, 2688 tiles (a tenth of them in the last round): no change.
+struct Plan {
+    int n_tiles, n_whole, n_parts;
+    float us;
+};
+template <class TL>
+Plan plan_tiling(const GemmArgs& g, int n_cu, const GemmTuning& tune) {
+    Plan p;
+    p.n_tiles = ((g.N + TL::BF - 1) / TL::BF) * ((g.M + TL::BRT - 1) / TL::BRT);
+    const int rest = p.n_tiles % n_cu, n_kt = g.K / BK;
     int n_parts = (rest == 0 || tune.tail_split == 0) ? 1 : std::min(n_cu / rest, 8);
-    // A part pays its own pipeline fill, a 128 KB dump of partial sums and its share of the second kernel (13 us for 128
-    // tiles in two parts).  Measured at 2970 rows: K = 14336, 384 tiles, two parts of 112 K tiles: 9 % less time;
-    // K = 4096, 576 tiles, four parts of 16: 8 % less; K = 4096, 384 tiles, two parts of 32: 4 % less; K = 4096,
-    // 2688 tiles (a tenth of them in the last round): no change.
-    n_parts = std::min(n_parts, (g.K / BK) / MIN_K_TILES_PER_PART);
+    n_parts = std::min(n_parts, n_kt / MIN_K_TILES_PER_PART);
     if (n_parts > 1 &&
-        (g.partials == nullptr || (size_t)rest * n_parts * TL::NW * PARTIAL_FLOATS_PER_WAVE * sizeof(float) > g.partials_bytes))
+        (g.partials == nullptr || (size_t)rest * n_parts * TL::WAVE_TILES * PARTIAL_FLOATS_PER_WAVE * sizeof(float) > g.partials_bytes))
         n_parts = 1;
-    g.n_parts = std::max(n_parts, 1);
-    g.n_whole = g.n_parts > 1 ? n_tiles - rest : n_tiles;
-    const int grid = g.n_whole + (n_tiles - g.n_whole) * g.n_parts;
-    gemm_bf16_kernel<EPI, WF><<<dim3(grid), dim3(64 * TL::NW), TL::LDS_BYTES, st>>>(g);
-    if (g.n_parts > 1)
-        gemm_fixup_kernel<EPI, WF><<<dim3((n_tiles - g.n_whole) * TL::NW), dim3(64), 0, st>>>(g);
+    p.n_parts = std::max(n_parts, 1);
+    p.n_whole = p.n_parts > 1 ? p.n_tiles - rest : p.n_tiles;
+    const float last = (float)(rest * p.n_parts) / (float)n_cu;   // share of the CUs that the last round keeps busy
+    const float last_round = rest ? TL::ROUND_BASE + (1.0f - TL::ROUND_BASE) * last : 0.0f;
+    p.us = TL::US_PER_K_TILE * n_kt * ((float)(p.n_tiles / n_cu) + last_round / (float)p.n_parts) + TL::US_LAUNCH +
+           (p.n_parts > 1 ? TL::US_SPLIT : 0.0f);
+    return p;
+}
+
+template <int EPI, class TL>
+hipError_t launch_tiling(GemmArgs g, void (*kernel)(GemmArgs), const Plan& p, hipStream_t st) {
+    // once per process (a function-local static is initialised exactly once, also under concurrent first calls)
+    static const hipError_t setup = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, TL::LDS_BYTES);
+    if (setup != hipSuccess) return setup;
+    g.n_whole = p.n_whole;
+    g.n_parts = p.n_parts;
+    kernel<<<dim3(p.n_whole + (p.n_tiles - p.n_whole) * p.n_parts), dim3(64 * TL::NW), TL::LDS_BYTES, st>>>(g);
+    if (p.n_parts > 1) gemm_fixup_kernel<EPI, TL><<<dim3((p.n_tiles - p.n_whole) * TL::WAVE_TILES), dim3(64), 0, st>>>(g);
     return hipGetLastError();
 }
 
 template <int EPI>
 hipError_t launch_gemm(const GemmArgs& g, const GemmTuning& tune, hipStream_t st) {
+    static const int n_cu = [] {
+        int dev = 0, n = 0;
+        return hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess ? n : 0;
+    }();
+    if (n_cu <= 0) return hipErrorInvalidDevice;
     // (Feeding the weight fragments from memory straight into registers, to halve the LDS traffic, was tried: 16-byte
     // pieces of 32 rows per load instruction cost far more in the memory pipeline than they save: 400-500 TFLOP/s.)
     const bool wide = (tune.tile == 256) || (tune.tile == 0 && g.N % 256 == 0);
-    return wide ? launch_gemm_wf<EPI, 4>(g, tune, st) : launch_gemm_wf<EPI, 2>(g, tune, st);
+    if (!wide) return launch_tiling<EPI, Tiling<2>>(g, &gemm_bf16_kernel<EPI, 2>, plan_tiling<Tiling<2>>(g, n_cu, tune), st);
+    const Plan narrow = plan_tiling<Tiling<4>>(g, n_cu, tune);
+    // 256 rows per workgroup where that is the shorter launch by the estimate above: a tile of twice the area takes 1.6
+    // times as long, but it comes in rounds twice as coarse and its partial sums cost more.  256 x 128 -> 256 x 256, us:
+    //   28672 x 4096 (gate / up): 2048 rows 438 -> 382, 2970 rows 670 -> 551, 16896 rows 3529 -> 2929
+    //   4096 x 14336 (down):      1100 rows 174 -> 125, 2048 rows 208 -> 200, 2970 rows 313 -> 278
+    //   4096 x 4096 (output):     1100 rows  48 stays (53), 2048 rows 61 stays (75), 2970 rows 101 -> 86
+    //   6144 x 4096 (Q / K / V):  1100 rows  55 stays (72), 2048 rows 108 -> 100, 2970 rows 156 -> 145
+    if (tune.tile == 0) {
+        const Plan square = plan_tiling<Tiling256>(g, n_cu, tune);
+        if (square.us < narrow.us) return launch_tiling<EPI, Tiling256>(g, &gemm_bf16_256_kernel<EPI>, square, st);
+    }
+    return launch_tiling<EPI, Tiling<4>>(g, &gemm_bf16_kernel<EPI, 4>, narrow, st);
 }
 
 }  // namespace
 
-size_t gemm_partials_bytes() { return (size_t)256 * 8 * PARTIAL_FLOATS_PER_WAVE * sizeof(float); }   // 256 parts of 8 waves
+size_t gemm_partials_bytes() { return (size_t)256 * 16 * PARTIAL_FLOATS_PER_WAVE * sizeof(float); }   // 256 parts of a 256 x 256 tile
 
 hipError_t launch_linear(const void* a, const void* w, int M, int N, int K, const void* residual, void* out,
                          float* partials, size_t partials_bytes, const GemmTuning& tune, hipStream_t st) {

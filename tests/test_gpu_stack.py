@@ -288,3 +288,56 @@ def test_full_size_stack_layers_teacher_forced(full_stack_run, layer):
     H.assert_close(H.host(r["v_cache"][layer][idx]), v_new, "bf16", f"layer {layer}: fresh V rows written back")
     got = H.host(r["capture"][layer]["h_out"][torch.from_numpy(rows).cuda()])
     H.assert_close(got, ho, "bf16", f"layer {layer}: output rows")
+
+
+@pytest.mark.parametrize("M,N,K", [
+    (16397, 28672, 64), (16397, 14336, 128),                            # one and two K tiles, a nearly empty last row tile
+    (2818, 4096, 768), (2900, 4096, 832), (3072, 4096, 896),            # even and odd numbers of K tiles; 1 and 256 rows too many
+])
+def test_linear_256_rows_per_workgroup(ctx, M, N, K):
+    """Whole tiles of the 256 x 256 kernel add the products of an element in the order of the 256 x 128 kernel: the same bits."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M + N + K)
+    a = torch.randn((M, K), generator=g, device="cuda").to(torch.bfloat16)
+    w = (torch.randn((N, K), generator=g, device="cuda") * 0.05).to(torch.bfloat16)
+    out = torch.zeros((2, M + 1, N), dtype=torch.bfloat16, device="cuda")
+    ctx.fr_set_option(B.FR_OPT_GEMM_TAIL_SPLIT, 0)
+    try:
+        for i, tile in enumerate((0, 256)):
+            ctx.fr_set_option(B.FR_OPT_GEMM_TILE, tile)
+            ctx.fr_linear(a, w, M, N, K, None, out[i])
+    finally:
+        ctx.fr_set_option(B.FR_OPT_GEMM_TILE, 0)
+        ctx.fr_set_option(B.FR_OPT_GEMM_TAIL_SPLIT, 1)
+    torch.cuda.synchronize()
+    assert torch.equal(out[0], out[1])
+    assert not out[0, M].any()                                          # nothing behind the last row
+    rows = [0, 255, 256, M - 1]
+    H.assert_close(H.host(out[0, rows]), H.host(a[rows].double() @ w.double().T), "bf16", "linear")
+
+
+def test_epilogues_256_rows_per_workgroup_split(ctx):
+    """A launch of one round whose 256 x 256 tiles are split along K, with every epilogue."""
+    M, K, Hq, Hkv, d = 1101, 14336, SHAPE.n_q_heads, SHAPE.n_kv_heads, SHAPE.head_dim
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    rand = lambda *s: torch.randn(s, generator=g, device="cuda").to(torch.bfloat16)  # noqa: E731
+    a, res = rand(M, K), rand(M, 4096)
+    w, wg, wq = 0.02 * rand(4096, K), 0.02 * rand(4096, K), 0.02 * rand((Hq + 2 * Hkv) * d, K)
+    want = a.double() @ w.double().T + res.double()
+    ctx.fr_linear(a, w, M, 4096, K, res, res)
+    H.assert_close(H.host(res), H.host(want), "bf16", "linear + residual")
+    sw = torch.zeros((M, 2048), dtype=torch.bfloat16, device="cuda")
+    ctx.fr_linear_swiglu(a, wg, M, 2048, K, sw)
+    y = a.double() @ wg.double().T
+    H.assert_close(H.host(sw), H.host(torch.nn.functional.silu(y[:, 0::2]) * y[:, 1::2]), "bf16", "swiglu")
+    pos = torch.arange(M, dtype=torch.int32, device="cuda") * 3
+    q, k, v = (torch.zeros((M, n, d), dtype=torch.bfloat16, device="cuda") for n in (Hq, Hkv, Hkv))
+    ctx.fr_qkv_rope(a, wq, M, K, pos, q, k, v)
+    y = (a.double() @ wq.double().T).view(M, Hq + 2 * Hkv, d)
+    ang = pos.double()[:, None, None] * SHAPE.rope_base ** (-torch.arange(0, d, 2, device="cuda", dtype=torch.float64) / d)
+    e, o, cs, sn = y[..., 0::2], y[..., 1::2], ang.cos(), ang.sin()
+    rot = torch.stack((e * cs - o * sn, o * cs + e * sn), dim=-1).flatten(-2)
+    H.assert_close(H.host(q), H.host(rot[:, :Hq]), "bf16", "q")
+    H.assert_close(H.host(k), H.host(rot[:, Hq:Hq + Hkv]), "bf16", "k")
+    H.assert_close(H.host(v), H.host(y[:, Hq + Hkv:]), "bf16", "v")
