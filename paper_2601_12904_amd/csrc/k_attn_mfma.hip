@@ -1186,7 +1186,10 @@ int choose_parts(int split_mode, int items, int n_img_tiles, int n_cu, size_t pa
 
 // Half-precision partial results: only for a single query of a long prompt (32 key tiles and more) whose weights are plain
 // bf16, where 400 items in two parts would otherwise move 2 x 108 MB of partial sums (combine pass 21.1 us, 15.5 us in half
-// precision).  Short prompts and batches, a few hundred pieces at most, keep all 32 bits.
+// precision).  Short prompts, batches and more than four parts, a few hundred pieces at most, keep all 32 bits
+// (6730 tokens, 32 items: 2.174e-3 off float64 in eight parts, 2.184e-3 in four of half precision; the layer takes 163 us, 159 in
+// eight of half precision, 183 in four).
+constexpr int HALF_MAX_PARTS = 4;
 template <bool SPLIT>
 bool half_parts(int n_img_tiles) { return !SPLIT && n_img_tiles >= 32; }
 template <int D>
@@ -1229,9 +1232,17 @@ hipError_t launch(const Shape& s, const void* q_rows, const int32_t* q_index, in
     e = pack_query<D>(s, q_rows, q_index, R, k_cache, v_cache, L, k_new, v_new, out, lse, sc, shared, writeback, &batch.q[0], st);
     if (e != hipSuccess) return e;
     batch.max_row_tiles = batch.q[0].n_row_tiles;
-    const bool half = half_parts<SPLIT>(batch.q[0].n_img_tiles);
-    const int n_parts = choose_parts(split_mode, batch.q[0].n_row_tiles * s.Hkv, batch.q[0].n_img_tiles, ws.n_cu,
-                                     part_bytes<D>(half), ws.attn_partials_bytes);
+    bool half = half_parts<SPLIT>(batch.q[0].n_img_tiles);
+    auto parts_of = [&](bool h) {
+        return choose_parts(split_mode, batch.q[0].n_row_tiles * s.Hkv, batch.q[0].n_img_tiles, ws.n_cu, part_bytes<D>(h),
+                            ws.attn_partials_bytes);
+    };
+    int n_parts = parts_of(half);
+    if (half && n_parts > HALF_MAX_PARTS) {   // 32 bits, or as many parts as half precision may have
+        const int full = parts_of(false);
+        half = full <= HALF_MAX_PARTS;
+        n_parts = half ? HALF_MAX_PARTS : full;
+    }
     return launch_packed<G, D, SPLIT>(s, batch, n_parts, half, ws, mode, timer, st);
 }
 
