@@ -174,3 +174,25 @@ def test_decode_attn_full_size_sampled():
                                          [bt["k_pages"][b]], [bt["v_pages"][b]], bt["shape"].rope_base)
         H.assert_close(got[[b]], want, "bf16", f"decode output of query {b}")
         assert np.max(np.abs(got_lse[[b]] - want_lse)) <= 2e-3
+
+
+@pytest.mark.parametrize("generic", [False, True])
+@pytest.mark.parametrize("chunk_lens,prompts,n_gen,page_stride", [
+    ((1,), ((0,),), 1, None),                       # one row in eight pieces of a segment, seven of them empty
+    ((33, 31), ((0, 1),), 1, 4100),                 # pages cut by the room they have, of which a few rows are filled
+    ((2000, 7), ((0,), (1,)), 1600, None),          # pieces of several blocks per wave, ragged tails
+    ((5,), ((0,),) * 300, 1, 3600),                 # more pieces than the partial results' buffer holds: cut into fewer
+])
+def test_decode_attn_pieces(chunk_lens, prompts, n_gen, page_stride, generic):
+    """Segments and pages in pieces (their number follows from counts alone) against the oracle, one KV head."""
+    shape = synth.LayerShape(n_q_heads=4, n_kv_heads=1, head_dim=128, dtype="bf16", rope_base=500000.0)
+    n = len(prompts)
+    bt = make_batch(shape, 11, chunk_lens=chunk_lens, prompts=prompts, nq=(1,) * n, n_gen=(n_gen,) * n, page_stride=page_stride)
+    want, want_lse = orc.decode_attn(bt["q"], bt["k_store"], bt["v_store"], bt["segments"], bt["stale"], bt["k_pages"],
+                                     bt["v_pages"], shape.rope_base)
+    got, lse, _ = run_gpu(bt, generic=generic)
+    H.assert_close(got, want, "bf16", "decode attention in pieces")
+    # The matrix-core kernel rounds the rotated query to bf16: 2^-9 relative per element, evenly spread, so a logit of unit
+    # variance is off by a standard deviation of at most 2^-9 / sqrt 3, and so is the sum's logarithm where one key
+    # dominates.  Five of them for up to 1200 results over a few keys each (in fp64 with such queries: 3.18e-3 at worst).
+    assert np.max(np.abs(lse - want_lse)) <= 5 * 2.0 ** -9 / np.sqrt(3)
