@@ -9,6 +9,9 @@
 // v_mfma_f32_16x16x4_f32: keys on the register dimension of S^T, columns on lanes, and register i of the weights is
 // exactly the B operand of step i of the second product (its contraction index kg is key 4 kg + i), so the weights never
 // leave their registers.  Fresh rows are found through a position -> row map in LDS, built by the workgroup itself.
+// A weight of 0 does not take a NaN or an infinity out of a matrix product, so what a column does not see is kept out by hand:
+// keys behind the tile's last row are neither read (they may be stale or hold nothing) nor multiplied, and a block that only some
+// of the columns see whole is searched for values that are not finite.
 // 4 heads, 109 rows, 544 positions, head_dim 64: 15.9 us; one wave per (row, head) on the vector ALU, behind a kernel that
 // built the map: 31.5 + 2.7 us.
 #include "fr_internal.hpp"
@@ -48,7 +51,8 @@ __global__ __launch_bounds__(64 * W) void attn_f32_kernel(const T* __restrict__ 
     const int n = min(16 * tile + x, cols - 1), r = n / G, head = g * G + n % G;   // columns past the end: a copy of the last
     const int pos = q_index[r];
     const int p_max = q_index[min(16 * tile + 15, cols - 1) / G];   // rows ascend
-    const int n_blocks = min(p_max, L - 1) / 16 + 1;
+    const int p_last = min(p_max, L - 1), n_blocks = p_last / 16 + 1;
+    const int p_first = q_index[16 * tile / G];   // keys up to here are visible to every column of the tile
 
     const bool have_new = k_new != nullptr, own_map = have_new && inv == nullptr;
     if (own_map) {   // rows up to the tile's last one, the others' positions are not visible
@@ -63,7 +67,7 @@ __global__ __launch_bounds__(64 * W) void attn_f32_kernel(const T* __restrict__ 
     }
     auto fresh_row = [&](int j) -> int { return own_map ? (int)row_of[j] - 1 : have_new ? inv[j] : -1; };
     auto row_ptr = [&](int j, const T* cache, const T* fresh) -> const T* {
-        j = min(j, L - 1);
+        j = min(j, p_last);
         const int f = fresh_row(j);
         return f >= 0 ? fresh + ((size_t)f * Hkv + g) * D : cache + ((size_t)j * Hkv + g) * D;
     };
@@ -88,7 +92,10 @@ __global__ __launch_bounds__(64 * W) void attn_f32_kernel(const T* __restrict__ 
         for (int i = 0; i < 4; ++i) {
             const T* p = row_ptr(16 * b + 4 * kg + i, v_cache, v_new) + x;
 #pragma unroll
-            for (int md = 0; md < NJ; ++md) vv[i][md] = Elem<T>::to_f32(p[16 * md]);
+            for (int md = 0; md < NJ; ++md) {
+                const float v = Elem<T>::to_f32(p[16 * md]);
+                vv[i][md] = 16 * b + 4 * kg + i <= p_last ? v : 0.f;
+            }
         }
         f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -117,6 +124,32 @@ __global__ __launch_bounds__(64 * W) void attn_f32_kernel(const T* __restrict__ 
         l = l * alpha + psum;
 #pragma unroll
         for (int md = 0; md < NJ; ++md) o[md] *= alpha;
+        if (16 * b + 15 > p_first) {   // values that are not finite: out of the product, into the columns that see them
+            bool odd = false;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int md = 0; md < NJ; ++md) odd = odd || !(fabsf(vv[i][md]) < INFINITY);
+            if (__any(odd)) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int md = 0; md < NJ; ++md) {
+                        const bool finite = fabsf(vv[i][md]) < INFINITY;
+                        const float apart = finite ? 0.f : vv[i][md];
+                        if (!finite) vv[i][md] = 0.f;
+                        for (int src = 0; src < 4; ++src) {   // key 4 src + i of the block
+                            const bool seen = 16 * b + 4 * src + i <= pos;
+                            const float weight = __shfl(p[i], 16 * src + x);
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) {
+                                const float v = __shfl(apart, 16 * src + 4 * kg + e);   // dim 16 md + 4 kg + e
+                                if (seen && v != 0.f) o[md][e] += weight * v;
+                            }
+                        }
+                    }
+            }
+        }
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
