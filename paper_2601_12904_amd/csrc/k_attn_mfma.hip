@@ -29,9 +29,14 @@
 // tokens / 15 %), so the work that does not depend on the rows is done once, by a packing pre-pass: for each
 // (KV head, 64-key tile) it resolves stale / fresh rows (key j comes from k_new/v_new when inv[j] >= 0, i.e.
 // its token is in the Q index, and from the cache otherwise: the cache is never written and stale rows are
-// never read), transposes V, applies the LDS bank swizzle and writes a 32 KB image that is byte for byte what
-// the attention kernels want in LDS.  The fast kernel's tile loop then stages a tile with direct-to-LDS
+// never read), transposes V, pads the rows against LDS bank conflicts and writes an image (35 KB at head_dim 128) that is byte
+// for byte what the attention kernels want in LDS.  The fast kernel's tile loop then stages a tile with direct-to-LDS
 // copies: no lookups, no pointer selects, no permutes, no address arithmetic, no staging registers.
+//
+// What a row does not see.  A weight of 0 does not take a NaN or an infinity out of a matrix product.  Positions behind the last
+// row of the Q index may hold anything: their values enter the images as zeros.  A value that is not finite and that only some
+// rows of a tile see makes the sums of the others NaN, which the overflow check finds; running_max_item keeps such values
+// apart.
 #include "fr_internal.hpp"
 #include "k_rotate.hpp"
 
@@ -235,6 +240,7 @@ __global__ __launch_bounds__(256) void pack_kv_images_kernel(const __bf16* k_cac
     const int kt = blockIdx.x, g = blockIdx.y;
     const PackShare<D> ps;
     const bool have_new = k_new != nullptr;   // else the cache already holds the fresh rows
+    const int last = q_index[R - 1];          // no row sees a position behind it
     if (have_new) tile_fresh_rows(q_index, R, kt, fresh);
     // key `t` of the tile (one past the end is clamped: it lies beyond every row's position), from k_new / v_new where it
     // is fresh; (with the write-back a clamped key past the end repeats key L - 1: the same bytes again)
@@ -252,7 +258,10 @@ __global__ __launch_bounds__(256) void pack_kv_images_kernel(const __bf16* k_cac
     for (int i = 0; i < PackShare<D>::KI; ++i) kreg[i] = fetch(ps.key + (256 / PackShare<D>::NV) * i, k_cache, k_new);
     if (ps.has_v) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) vreg[i] = fetch(4 * ps.key + i, v_cache, v_new);
+        for (int i = 0; i < 4; ++i) {
+            vreg[i] = fetch(4 * ps.key + i, v_cache, v_new);
+            if (kt * KT + 4 * ps.key + i > last) vreg[i] = u32x4{0u, 0u, 0u, 0u};
+        }
     }
     write_image<D>(ps, kreg, vreg, img, images + ((size_t)g * n_img_tiles + kt) * Img<D>::BYTES);
 }
@@ -447,19 +456,60 @@ __device__ __forceinline__ void mask_half(f32x16 (&s)[2], const int (&col_pos)[2
         }
 }
 
-// O^T += V^T P^T for the 32 keys of half mb.
+// The two bf16 numbers of a word, 0 in the place of one that is not finite.
+__device__ __forceinline__ uint32_t finite_or_zero(uint32_t w) {
+    if ((w & 0x00007F80u) == 0x00007F80u) w &= 0xFFFF0000u;
+    if ((w & 0x7F800000u) == 0x7F800000u) w &= 0x0000FFFFu;
+    return w;
+}
+
+// O^T += V^T P^T for the 32 keys of half mb.  finite_only: without the values that are not finite.
 template <int D, bool SPLIT>
 __device__ __forceinline__ void pv_half(const unsigned char* vt, int mb, const Weights<SPLIT>& pf, const FragOffsets<D>& fo,
-                                        f32x16 (&o)[D / 32][2]) {
+                                        f32x16 (&o)[D / 32][2], bool finite_only = false) {
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk) {
         const int kb = 2 * mb + kk;
 #pragma unroll
         for (int md = 0; md < D / 32; ++md) {
-            const bf16x8 a = *reinterpret_cast<const bf16x8*>(vt + fo.v + 32 * kb + md * (32 * V_ROW));
+            u32x4 bits = *reinterpret_cast<const u32x4*>(vt + fo.v + 32 * kb + md * (32 * V_ROW));
+            if (finite_only)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) bits[e] = finite_or_zero(bits[e]);
+            const bf16x8 a = __builtin_bit_cast(bf16x8, bits);
 #pragma unroll
             for (int nb = 0; nb < 2; ++nb) pf.multiply(a, nb, kk, o[md][nb]);
         }
+    }
+}
+
+// Does the V^T image of a tile hold a value that is not finite?  The same answer in every lane of the wave.
+template <int D>
+__device__ __forceinline__ bool holds_not_finite(const unsigned char* vt) {
+    bool found = false;
+    for (int i = (threadIdx.x & 63) * 16; i < Img<D>::V_BYTES; i += 1024) {
+        const u32x4 w = *reinterpret_cast<const u32x4*>(vt + i);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) found = found || finite_or_zero(w[e]) != w[e];
+    }
+    return __any(found);
+}
+// O^T += those values, for the columns that see them.  Their weights are positive: an infinity stays what it is, a NaN too.
+template <int D>
+__device__ __forceinline__ void add_not_finite(const unsigned char* vt, int key_base, const int (&col_pos)[2], int h,
+                                               f32x16 (&o)[D / 32][2]) {
+    for (int t = 0; t < KT; ++t) {
+        const unsigned char* key = vt + 2 * key_slot(t) + 4 * h * V_ROW;
+#pragma unroll
+        for (int md = 0; md < D / 32; ++md)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const uint32_t w = *reinterpret_cast<const uint16_t*>(key + (32 * md + 8 * (v >> 2) + (v & 3)) * V_ROW);
+                if ((w & 0x7F80u) != 0x7F80u) continue;
+#pragma unroll
+                for (int nb = 0; nb < 2; ++nb)
+                    if (key_base + t <= col_pos[nb]) o[md][nb][v] += __uint_as_float(w << 16);
+            }
     }
 }
 
@@ -738,6 +788,7 @@ __device__ __forceinline__ void running_max_item(const AttnQuery& aq, int g, int
         sg.write(k_img);
         __syncthreads();
         if (kt * KT > ge.wp_max) continue;   // wave-uniform; the barriers stay outside
+        const bool apart = kt >= ge.n_plain && holds_not_finite<D>(v_img);   // some rows may not see them
 #pragma unroll
         for (int mb = 0; mb < 2; ++mb) {
             f32x16 s[2];
@@ -766,8 +817,9 @@ __device__ __forceinline__ void running_max_item(const AttnQuery& aq, int g, int
 #pragma unroll
                     for (int v = 0; v < 16; ++v) o[md][nb][v] *= alpha;
             }
-            pv_half<D, SPLIT>(v_img, mb, pf, fo, o);
+            pv_half<D, SPLIT>(v_img, mb, pf, fo, o, apart);
         }
+        if (apart) add_not_finite<D>(v_img, kt * KT, ge.col_pos, h, o);
     }
     float l[2];
 #pragma unroll

@@ -48,14 +48,19 @@ def attend(ctx, w, qi, q, k_cache, v_cache, k_new=None, v_new=None, writeback=Fa
 # head_dim 64 and 128, bf16 with more than 64 heads per KV head
 FP32_PRODUCTS = [(4, 4, 64, "f32", (128, 77), 32, 0.15), (4, 1, 64, "f32", (130, 60), 9, 0.15), (5, 1, 128, "f32", (260, 40), 9, 0.2),
                  (2, 2, 64, "f32", (8100, 200), 21, 0.01), (80, 1, 64, "bf16", (90, 60), 5, 0.2)]
-CASES = FP32_PRODUCTS
+# the tiled kernels: group sizes with and without an instance of their own, head_dim 64; items whole, in parts, and with a
+# running maximum throughout
+TILED = [(Hq, Hkv, d, "bf16", (130, 0, 333, 61), 37, 0.2) for Hq, Hkv, d in ((4, 4, 128), (4, 2, 128), (8, 2, 128), (16, 2, 128), (7, 1, 128), (14, 2, 64))]
+WHOLE, PARTS, RUNNING = (B.FR_OPT_ATTN_SPLIT, B.FR_ATTN_SPLIT_OFF), (B.FR_OPT_ATTN_SPLIT, B.FR_ATTN_SPLIT_ON), (B.FR_OPT_ATTN_SOFTMAX, B.FR_ATTN_SOFTMAX_RUNNING_MAX)
+CASES = [(c, WHOLE) for c in FP32_PRODUCTS] + [(c, option) for c in TILED for option in (WHOLE, PARTS, RUNNING)]
 
 
 @pytest.mark.parametrize("with_new", [True, False])
-@pytest.mark.parametrize("case_args", CASES)
-def test_rows_that_hold_nothing(case_args, with_new):
+@pytest.mark.parametrize("case_args,option", CASES)
+def test_rows_that_hold_nothing(case_args, option, with_new):
     """Also with the question rows left out of the index: its last row then ends in the middle of a key block."""
     w, qi_all, k_cache, v_cache, ctx = case(*case_args)
+    ctx.fr_set_option(*option)
     dt = w.shape.dtype
     for qi in (qi_all, qi_all[:-w.nq]):
         k_new, v_new = w.k_full[qi], w.v_full[qi]
@@ -78,11 +83,12 @@ def test_rows_that_hold_nothing(case_args, with_new):
     ctx.close()
 
 
-@pytest.mark.parametrize("case_args", CASES)
-def test_values_that_are_not_finite_reach_later_rows_only(case_args):
+@pytest.mark.parametrize("case_args,option", CASES)
+def test_values_that_are_not_finite_reach_later_rows_only(case_args, option):
     """A fresh value row with a NaN and an infinity, and a cached one that no listed row has replaced: rows in front of them
     are as without them, rows behind them have the NaN and the infinity in those elements and are otherwise as without them."""
     w, qi, k_cache, v_cache, ctx = case(*case_args)
+    ctx.fr_set_option(*option)
     dt = w.shape.dtype
     k_new, v_new = w.k_full[qi], w.v_full[qi].copy()
     at = len(qi) // 2                                               # a row in the middle of the index
