@@ -404,17 +404,22 @@ struct FragOffsets {
     }
 };
 
-// The weights of 32 keys x 64 columns as operands of the second product.  SPLIT: every weight as the sum of two bf16
-// numbers, hi = bf16(p) and lo = bf16(p - hi), i.e. 16 significant bits, for the shapes whose weights have always been
-// kept in fp32; the second product then takes two instructions per fragment.
+// The weights of 32 keys x 64 columns as operands of the second product.  SPLIT: every weight as the sum of three bf16
+// numbers, each the rounding of what the ones before leave (8 bits each, the differences are exact): all 24 bits of an fp32 weight, for
+// the shapes whose weights have always been kept in fp32; the second product then takes three instructions per fragment.
+// (Error of the output beyond its own rounding, 17k tokens: two numbers 2.0e-6, three 0.4e-6, the vector ALU's fp32 0.2e-6.  Two
+// take 0.62 ms for the tile loop of 28 / 4 heads and 2970 rows, three 0.80.)
 template <bool SPLIT>
 struct Weights {
-    bf16x8 hi[2][2];
-    bf16x8 lo[SPLIT ? 2 : 1][SPLIT ? 2 : 1];
+    static constexpr int PARTS = SPLIT ? 3 : 1;
+    bf16x8 part[PARTS][2][2];
     __device__ __forceinline__ void set(int nb, int v, float p) {
-        const __bf16 t = (__bf16)p;
-        hi[nb][v >> 3][v & 7] = t;
-        if constexpr (SPLIT) lo[nb][v >> 3][v & 7] = (__bf16)(p - (float)t);
+#pragma unroll
+        for (int i = 0; i < PARTS; ++i) {
+            const __bf16 t = (__bf16)p;
+            part[i][nb][v >> 3][v & 7] = t;
+            p -= (float)t;
+        }
     }
     __device__ __forceinline__ void clear() {
 #pragma unroll
@@ -423,8 +428,8 @@ struct Weights {
             for (int v = 0; v < 16; ++v) set(nb, v, 0.f);
     }
     __device__ __forceinline__ void multiply(const bf16x8& a, int nb, int kk, f32x16& acc) const {
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, hi[nb][kk], acc, 0, 0, 0);
-        if constexpr (SPLIT) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, lo[nb][kk], acc, 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < PARTS; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, part[i][nb][kk], acc, 0, 0, 0);
     }
 };
 
@@ -516,7 +521,7 @@ __device__ __forceinline__ void add_not_finite(const unsigned char* vt, int key_
 // One step of the fast kernel's software pipeline, at the granularity of 32 keys ("a half").  It turns the
 // logits of half j (s_cur) into bf16 weights (pf_cur), while the matrix cores form the logits of half j+1
 // (s_nxt = K Q^T, 16 instructions at head_dim 128) and add half j-1 to the output (O^T += V^T P^T with pf_prev, 16
-// instructions, 32 with split weights).  The three strands are independent, so the vector ALU's exp work runs in the shadow of the
+// instructions, 48 with split weights).  The three strands are independent, so the vector ALU's exp work runs in the shadow of the
 // matrix instructions.  The exponent reference is fixed per column: no maximum, no rescale, no branch.
 template <int D, bool SPLIT, bool MASK, bool DO_QK>
 __device__ __forceinline__ void pipeline_step(const unsigned char* k_next, int mb_next, const unsigned char* vt_prev,
@@ -589,7 +594,7 @@ __device__ __forceinline__ void pipeline_step(const unsigned char* k_next, int m
         if (i + PF < 2 * NK) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // fragment i + PF
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-            if (SPLIT && i >= NK) __builtin_amdgcn_sched_group_barrier(0x008, 2, 0); else __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // matrix
+            if (SPLIT && i >= NK) __builtin_amdgcn_sched_group_barrier(0x008, Weights<SPLIT>::PARTS, 0); else __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // matrix
             __builtin_amdgcn_sched_group_barrier(0x400, EW / 2, 0);   // transcendental
         }
     }
@@ -1332,8 +1337,8 @@ hipError_t launch_shared_batch(const Shape& s, int n, const SharedBatchQuery* qs
 
 // Shapes with an instance of their own; the others (any group size up to 64, head_dim 64 too) run the kernels whose group
 // size is an argument and whose weights are split (Weights).  The group size enters the prologue and the epilogue only.
-// 28 query / 4 KV heads over a 17k-token prompt, 2970 rows: 0.62 ms for the tile loop (387 GFLOP as 580 GFLOP of matrix
-// instructions: 0.93 PFLOP/s) + 0.024 + 0.016 ms; one wave per (row, head) on the vector ALU took 50.5 ms.
+// 28 query / 4 KV heads over a 17k-token prompt, 2970 rows: 0.80 ms for the tile loop (387 GFLOP as 774 GFLOP of matrix
+// instructions: 0.97 PFLOP/s) + 0.022 + 0.018 ms; one wave per (row, head) on the vector ALU took 50.5 ms.
 static bool own_instance(const Shape& s) { return s.d == 128 && (s.G == 1 || s.G == 2 || s.G == 4 || s.G == 8); }
 
 // Partial results of a launch in parts: one slot per piece.

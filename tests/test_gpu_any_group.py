@@ -13,8 +13,7 @@ from tests.test_gpu_parity import assembled_cache, run_attention, staged
 pytestmark = pytest.mark.gpu
 
 # Outputs are rounded to bf16 once: 8 significant bits (one of them implicit), so half a unit is up to 2^-8 of the element
-# and of the tensor's largest value at most.  The weights are carried to 16 bits (2^-17 of the largest value vector, which
-# is of the size of the largest output here) and the sums are fp32, so nothing else shows at this scale.
+# and of the tensor's largest value at most.  The weights and the sums are fp32, so nothing else shows at this scale.
 OUT_TOL = 2.0 ** -8 + 2.0 ** -14
 
 
@@ -48,6 +47,34 @@ def test_attention(Hq, Hkv, d, split):
     k_eff, v_eff = orc.kv_scatter(qi, w.k_full[qi], w.v_full[qi], k_cache, v_cache)
     assert np.array_equal(H.host(kc), k_eff) and np.array_equal(H.host(vc), v_eff)
     ctx.close()
+
+
+@pytest.mark.parametrize("Hq,Hkv,d", [(7, 1, 128), (2, 1, 64)])
+def test_weights_keep_32_bits(Hq, Hkv, d):
+    """Values whose weighted sum nearly cancels for the last row and head 0 (signs against the running sum, the rest into one
+    key): what is left, about 1e-6, is rounded to bf16 at 1e-9 and shows the weights' own errors.  A weight in fp32 is off
+    by some 2^-22 (a logit's sum, its scale and the exponential, 2^-24 each of a few units), one of 16 bits by up to 2^-17;
+    independent errors of unit values add up to that times the root of the weights' squares.  2^-20 lies between."""
+    w = workload(Hq, Hkv, d, (200, 120), 20)
+    L, rng = w.L, np.random.default_rng(d)
+    logits = (w.k_full[:, 0].astype(np.float64) @ w.q_full[L - 1, 0].astype(np.float64)) / np.sqrt(d)
+    weight = np.exp(logits - logits.max())
+    weight /= weight.sum()
+    v = np.zeros((L, Hkv, d), dtype=np.float32)
+    for e in range(d):
+        order, total = rng.permutation(L), 0.0
+        for j in order[:-3]:
+            v[j, 0, e] = -1.0 if total > 0 else 1.0
+            total += weight[j] * v[j, 0, e]
+        for j in order[-3:]:
+            v[j, 0, e] = synth.round_to_storage(np.float32([-total / weight[j]]), "bf16")[0]
+            total += weight[j] * v[j, 0, e]
+    want = weight @ v[:, 0].astype(np.float64)
+    ctx = H.make_ctx(w.shape, L, w.n_chunks, w.nq)
+    got, _ = run_attention(ctx, w, np.arange(L), w.k_full, v, with_new=False)
+    ctx.close()
+    assert np.max(np.abs(want)) < 1e-4
+    assert np.sqrt(np.mean((got[L - 1, 0] - want) ** 2)) <= 2.0 ** -20 * np.sqrt(np.sum((weight[:, None] * v[:, 0]) ** 2) / d)
 
 
 @pytest.mark.parametrize("split", [B.FR_ATTN_SPLIT_OFF, B.FR_ATTN_SPLIT_ON])
