@@ -130,7 +130,8 @@ fr_status fr_create(const fr_layer_desc* desc, int64_t max_tokens, int32_t max_c
         return o;
     };
     const size_t o_table = take((size_t)max_chunks * (s.d / 2) * sizeof(float2));
-    const size_t o_lse = take(score_lse_floats(s, max_tokens, max_chunks, max_question_tokens) * 4);
+    w.lse_floats = score_lse_floats(s, max_tokens, max_chunks, max_question_tokens);
+    const size_t o_lse = take(w.lse_floats * 4);
     w.col_splits = score_column_ranges(s, max_tokens, max_question_tokens);
     const size_t o_col = take((size_t)w.col_splits * s.Hkv * max_tokens * 4);
     const size_t o_scores = take((size_t)max_tokens * 4);

@@ -38,7 +38,8 @@ struct Workspace {
     char* base = nullptr;
     size_t bytes = 0;
     float2* rope_table = nullptr;   // [max_chunks][d/2] (cos, sin)
-    float* lse = nullptr;           // base-2 row normalisers of the two-pass scoring (score_lse_floats)
+    float* lse = nullptr;           // base-2 row normalisers of the two-pass scoring
+    size_t lse_floats = 0;          // (score_lse_floats)
     float* col_partial = nullptr;   // [col_splits][Hkv][max_ctx] column sums per range of question columns and KV head
     int col_splits = 0;
     float* scores = nullptr;        // [max_tokens]

@@ -83,8 +83,9 @@ struct ScoreArgs {
     const void* q;
     const void* k;
     const float2* table;      // (cos, sin) rows of the chunks, stores only
-    float* lse2;              // [Hkv][lse_rows][NQG] base-2 normalisers of the two-pass modes
+    float* lse2;              // [Hkv][lse_rows][col_end - col0] base-2 normalisers of the two-pass modes
     float* partial;           // [n_split][Hkv][L_ctx]
+    int col0, col_end;        // the launch's query columns
     int nq, Hq, Hkv, G, lse_rows, n_split, split_cols, max_parts, src, global_scope;
     uint32_t magic;           // ceil(2^32 / G): n / G = mulhi(n, magic) for G > 1
     float scale_log2e;
@@ -230,8 +231,8 @@ __device__ __forceinline__ void walk_columns(const ScoreArgs& a, Smem<T, D>& sm,
 #pragma unroll
     for (int i = 0; i < 4; ++i) valid[i] = last_key + i < len;
     if constexpr (MODE == MODE_GIVEN) {
-        const float* src = a.lse2 + ((size_t)g * a.lse_rows + row) * NQG;
-        for (int i = tid; i < n_steps * STEP; i += 64 * WAVES) sm.ref[i] = n0 + i < NQG ? src[n0 + i] : INFINITY;
+        const float* src = a.lse2 + ((size_t)g * a.lse_rows + row) * (a.col_end - a.col0) + (n0 - a.col0);
+        for (int i = tid; i < n_steps * STEP; i += 64 * WAVES) sm.ref[i] = n0 + i < n1 ? src[i] : INFINITY;
     }
 
     float sc[NB][4], p[CG][NB][4];
@@ -269,7 +270,7 @@ __device__ __forceinline__ void walk_columns(const ScoreArgs& a, Smem<T, D>& sm,
         bad = bad || !(l < 0x1p100f);
         if constexpr (MODE == MODE_LSE) {
             if (wave == 0 && kg == 0 && n0 + i < n1)
-                a.lse2[((size_t)g * a.lse_rows + row) * NQG + n0 + i] = sm.ref[i] + __builtin_amdgcn_logf(l);
+                a.lse2[((size_t)g * a.lse_rows + row) * (a.col_end - a.col0) + (n0 - a.col0) + i] = sm.ref[i] + __builtin_amdgcn_logf(l);
             return 0.f;
         } else {
             return n0 + i < n1 ? __builtin_amdgcn_rcpf(l) : 0.f;
@@ -451,8 +452,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void score_kernel(const ScoreArgs a)
     if (!a.global_scope && (parts > 1) != (MODE != MODE_FUSED)) return;
     const int per = segment_keys<O::SEG>(clen);
     const int s0 = c0 + part * per, len = min(per, clen - part * per);
-    const int NQG = a.nq * a.G;
-    const int n0 = split * a.split_cols, n1 = min(NQG, n0 + a.split_cols);
+    const int n0 = a.col0 + split * a.split_cols, n1 = min(a.col_end, n0 + a.split_cols);
     if (n0 >= n1) return;
     int row = lse_row<O::SEG>(c, c0) + part;             // MODE_LSE: this segment's normalisers go there
     if (MODE == MODE_GIVEN) row = a.global_scope ? a.lse_rows - 1 : row - part;   // combined: the chunk's first row, or the last of all
@@ -476,11 +476,11 @@ __global__ __launch_bounds__(64 * WAVES, 2) void score_kernel(const ScoreArgs a)
 // Base-2 log-sum-exp over a chunk's segments into the chunk's first row (chunks of several segments), or over all
 // segments of the prompt into the last row.  grid (columns / 256, KV heads, chunks or 1).
 template <int SEG>
-__global__ __launch_bounds__(256) void score_lse_combine_kernel(ChunkTable ct, int NQG, int lse_rows, int global_scope,
+__global__ __launch_bounds__(256) void score_lse_combine_kernel(ChunkTable ct, int n_cols, int lse_rows, int global_scope,
                                                                 float* __restrict__ lse2) {
     const int n = blockIdx.x * 256 + threadIdx.x;
-    if (n >= NQG) return;
-    float* base = lse2 + (size_t)blockIdx.y * lse_rows * NQG + n;
+    if (n >= n_cols) return;
+    float* base = lse2 + (size_t)blockIdx.y * lse_rows * n_cols + n;
     const int first = global_scope ? 0 : (int)blockIdx.z, end = global_scope ? ct.n : first + 1;
     float m = -INFINITY, l = 0.f;
     for (int pass = 0; pass < 2; ++pass)
@@ -488,11 +488,11 @@ __global__ __launch_bounds__(256) void score_lse_combine_kernel(ChunkTable ct, i
             const int parts = segments<SEG>(ct.off[c + 1] - ct.off[c]);
             if (!global_scope && parts < 2) return;
             for (int i = 0; i < parts; ++i) {
-                const float v = base[(size_t)(lse_row<SEG>(c, ct.off[c]) + i) * NQG];
+                const float v = base[(size_t)(lse_row<SEG>(c, ct.off[c]) + i) * n_cols];
                 if (pass == 0) m = fmaxf(m, v); else l += exp2f(v - m);
             }
         }
-    base[(size_t)(global_scope ? lse_rows - 1 : lse_row<SEG>(first, ct.off[first])) * NQG] = m + log2f(l);
+    base[(size_t)(global_scope ? lse_rows - 1 : lse_row<SEG>(first, ct.off[first])) * n_cols] = m + log2f(l);
 }
 
 // Sum of a token's n_parts partial sums: 64 tokens per workgroup, wave w adds parts w, w + groups, ... and the waves' sums
@@ -500,7 +500,7 @@ __global__ __launch_bounds__(256) void score_lse_combine_kernel(ChunkTable ct, i
 // tokens, 6.0 for 16384); with at most REDUCE_AHEAD parts per wave, all in flight together, it is one round trip (2.6, 4.8).
 constexpr int REDUCE_AHEAD = 8, REDUCE_MAX_WAVES = 16;
 __global__ __launch_bounds__(64 * REDUCE_MAX_WAVES) void score_reduce_kernel(const float* __restrict__ partial, int n_parts, int L_ctx,
-                                                                             float* __restrict__ scores) {
+                                                                             int add, float* __restrict__ scores) {
     __shared__ float sums[REDUCE_MAX_WAVES][64];
     const int j = min((int)(blockIdx.x * 64 + threadIdx.x), L_ctx - 1), groups = blockDim.y;
     float t = 0.f;
@@ -517,7 +517,7 @@ __global__ __launch_bounds__(64 * REDUCE_MAX_WAVES) void score_reduce_kernel(con
     if (threadIdx.y != 0) return;
     t = 0.f;
     for (int w = 0; w < groups; ++w) t += sums[w][threadIdx.x];
-    if ((int)(blockIdx.x * 64 + threadIdx.x) < L_ctx) scores[j] = t;
+    if ((int)(blockIdx.x * 64 + threadIdx.x) < L_ctx) scores[j] = add ? scores[j] + t : t;   // add: not the first columns
 }
 
 // Column ranges per (chunk, KV head).  A workgroup holds a compute unit to itself, pays about 6 steps' time before its
@@ -560,44 +560,57 @@ hipError_t run(const Shape& s, const void* q, int nq, const void* k, const Chunk
     std::stable_sort(a.order, a.order + n, [&](uint8_t x, uint8_t y) { return ct.off[x + 1] - ct.off[x] > ct.off[y + 1] - ct.off[y]; });
     a.max_parts = (max_len + O::SEG - 1) / O::SEG;   // (at least segments(len) for every chunk)
     a.lse_rows = ct.n + L_ctx / O::SEG + 1;
-    const int n_steps = (NQG + RANGE_UNIT - 1) / RANGE_UNIT;
-    a.n_split = choose_splits(n * a.max_parts * s.Hkv, n_steps, ws.n_cu, ws.col_splits);
-    a.split_cols = (n_steps + a.n_split - 1) / a.n_split * RANGE_UNIT;
-    a.n_split = (NQG + a.split_cols - 1) / a.split_cols;
-    if (a.n_split > ws.col_splits) return hipErrorInvalidValue;
-    const dim3 block(64 * WAVES);
-    if (!a.global_scope && min_parts == 1) {   // (the chunks of several segments return at once)
-        const int parts = a.max_parts;
-        a.max_parts = 1;
-        score_kernel<T, D, MODE_FUSED><<<dim3(n * a.n_split * s.Hkv), block, 0, st>>>(a);
-        a.max_parts = parts;
+    const bool two_walks = a.global_scope || a.max_parts > 1;
+    // All columns at once where the workspace holds their partial sums and normalisers (score_lse_floats, score_column_ranges), else in turns.
+    int64_t cols = std::min<int64_t>(NQG, (int64_t)ws.col_splits * MAX_COLS);
+    if (two_walks) cols = std::min<int64_t>(cols, (int64_t)(ws.lse_floats / ((size_t)s.Hkv * a.lse_rows)));
+    if (cols < NQG) cols = cols / RANGE_UNIT * RANGE_UNIT;
+    if (cols <= 0) return hipErrorInvalidValue;
+    const int all_parts = a.max_parts;
+    for (a.col0 = 0; a.col0 < NQG; a.col0 = a.col_end) {
+        a.col_end = (int)std::min<int64_t>(NQG, a.col0 + cols);
+        const int n_cols = a.col_end - a.col0, n_steps = (n_cols + RANGE_UNIT - 1) / RANGE_UNIT;
+        a.n_split = choose_splits(n * all_parts * s.Hkv, n_steps, ws.n_cu, ws.col_splits);
+        a.split_cols = (n_steps + a.n_split - 1) / a.n_split * RANGE_UNIT;
+        a.n_split = (n_cols + a.split_cols - 1) / a.split_cols;
+        if (a.n_split > ws.col_splits) return hipErrorInvalidValue;
+        const dim3 block(64 * WAVES);
+        if (!a.global_scope && min_parts == 1) {   // (the chunks of several segments return at once)
+            a.max_parts = 1;
+            score_kernel<T, D, MODE_FUSED><<<dim3(n * a.n_split * s.Hkv), block, 0, st>>>(a);
+            a.max_parts = all_parts;
+        }
+        if (two_walks) {
+            const dim3 grid(n * a.max_parts * a.n_split * s.Hkv);
+            score_kernel<T, D, MODE_LSE><<<grid, block, 0, st>>>(a);
+            score_lse_combine_kernel<O::SEG><<<dim3((n_cols + 255) / 256, s.Hkv, a.global_scope ? 1 : ct.n), dim3(256), 0, st>>>(
+                ct, n_cols, a.lse_rows, a.global_scope, a.lse2);
+            score_kernel<T, D, MODE_GIVEN><<<grid, block, 0, st>>>(a);
+        }
+        const int n_sums = a.n_split * s.Hkv;
+        score_reduce_kernel<<<dim3((L_ctx + 63) / 64), dim3(64, std::min(REDUCE_MAX_WAVES, (n_sums + REDUCE_AHEAD - 1) / REDUCE_AHEAD)), 0, st>>>(
+            ws.col_partial, n_sums, L_ctx, a.col0 > 0, scores);
     }
-    if (a.global_scope || a.max_parts > 1) {
-        const dim3 grid(n * a.max_parts * a.n_split * s.Hkv);
-        score_kernel<T, D, MODE_LSE><<<grid, block, 0, st>>>(a);
-        score_lse_combine_kernel<O::SEG><<<dim3((NQG + 255) / 256, s.Hkv, a.global_scope ? 1 : ct.n), dim3(256), 0, st>>>(
-            ct, NQG, a.lse_rows, a.global_scope, a.lse2);
-        score_kernel<T, D, MODE_GIVEN><<<grid, block, 0, st>>>(a);
-    }
-    const int n_sums = a.n_split * s.Hkv;
-    score_reduce_kernel<<<dim3((L_ctx + 63) / 64), dim3(64, std::min(REDUCE_MAX_WAVES, (n_sums + REDUCE_AHEAD - 1) / REDUCE_AHEAD)), 0, st>>>(
-        ws.col_partial, n_sums, L_ctx, scores);
     return hipGetLastError();
 }
 
 }  // namespace
 
-// Workspace of the softmax scoring, in floats: normalisers of the two-pass modes, and how many column ranges of partial
-// sums fit (at least one per MAX_COLS columns; up to 16 while they stay below 4 MB).
+// Workspace of the softmax scoring.  lse_floats: normalisers; the two-pass kernels need all columns' at once, those of this file
+// run them in turns of as many as fit.  col_splits: column ranges of partial sums, up to 16 while they stay below 4 MB, and
+// enough for all columns at once while they stay below SCORE_TURN_BYTES.
+constexpr int64_t SCORE_TURN_BYTES = (int64_t)64 << 20;
 size_t score_lse_floats(const Shape& s, int64_t max_tokens, int max_chunks, int max_q) {
+    if (score_two_pass_supported(s)) return score_two_pass_lse_floats(s, max_chunks, max_q);   // (chunks that fit need none)
     const int64_t seg = (s.d * s.esize == 512) ? Op<float, 128>::SEG : Op<__bf16, 128>::SEG;
-    const size_t own = (size_t)s.Hkv * (size_t)(max_chunks + max_tokens / seg + 1) * s.G * (size_t)(max_q > 0 ? max_q : 1);
-    return score_two_pass_supported(s) ? std::max(own, score_two_pass_lse_floats(s, max_chunks, max_q)) : own;
+    const int64_t rows = (int64_t)s.Hkv * (max_chunks + max_tokens / seg + 1);
+    return (size_t)(rows * std::min<int64_t>((int64_t)s.G * max_q, std::max<int64_t>(MAX_COLS, SCORE_TURN_BYTES / 4 / rows)));
 }
 int score_column_ranges(const Shape& s, int64_t max_tokens, int max_q) {
-    const int64_t need = ((int64_t)max_q * s.G + RANGE_UNIT - 1) / RANGE_UNIT * RANGE_UNIT / MAX_COLS + 1;
-    const int64_t fit = ((int64_t)4 << 20) / (s.Hkv * max_tokens * 4);
-    return (int)std::max(need, std::min<int64_t>(16, std::max<int64_t>(fit, 2)));
+    const int64_t all = ((int64_t)max_q * s.G + RANGE_UNIT - 1) / RANGE_UNIT * RANGE_UNIT / MAX_COLS + 1;
+    const int64_t range_bytes = s.Hkv * max_tokens * 4;
+    const int64_t few = std::min<int64_t>(16, std::max<int64_t>(((int64_t)4 << 20) / range_bytes, 2));
+    return (int)std::max(few, std::min(all, SCORE_TURN_BYTES / range_bytes));
 }
 
 // One softmax over the prompt, or any chunk of more than SEG keys: shapes that k_score_mfma.hip takes go there, with the

@@ -157,6 +157,34 @@ def test_scores(Hq, Hkv, d, dt, nq, lens, norm):
 
 
 @pytest.mark.parametrize("norm", [B.FR_NORM_PER_CHUNK, B.FR_NORM_GLOBAL])
+def test_scores_of_more_columns_than_the_workspace_holds(norm):
+    """A context of two million tokens holds the partial sums of 4096 query columns and the normalisers of 2048 at a time: 4400
+    columns take two and three turns."""
+    shape = synth.LayerShape(n_q_heads=16, n_kv_heads=4, head_dim=64, dtype="f32", rope_base=10000.0)
+    w = synth.config_small_bf16(seed=2, chunk_lens=(500, 1030, 40), nq=1100, shape=shape)
+    want = orc.critical_scores(w.q_question, w.k_cached, w.chunk_offsets, "global" if norm == B.FR_NORM_GLOBAL else "per_chunk")
+    ctx = H.make_ctx(shape, 2 << 20, w.n_chunks, w.nq)
+    scores = torch.full((w.L_ctx,), -7.0, dtype=torch.float32, device="cuda")
+    qi = torch.zeros(w.nq, dtype=torch.int32, device="cuda")
+    ctx.fr_score_select(H.dev(w.q_question, "f32"), w.nq, H.dev(w.k_cached, "f32"), w.chunk_offsets, 0, norm, scores, qi)
+    torch.cuda.synchronize()
+    assert H.max_rel_err(scores.cpu().numpy().astype(np.float64), want) <= SCORE_TOL
+    ctx.close()
+
+
+@pytest.mark.parametrize("shape", [synth.LLAMA3_8B_BF16, synth.TINY_F32, synth.LayerShape(28, 4, 128, "bf16", 1e6)])
+def test_workspace_of_many_question_tokens(shape):
+    """What the question tokens add to a context of 131072 tokens: one normaliser per (KV head, chunk or whole prompt, column),
+    and the columns' partial sums and segments' normalisers of one turn, 64 MB each."""
+    tokens, chunks, size = 131072, 16, []
+    for max_q in (512, tokens):
+        ctx = H.make_ctx(shape, tokens, chunks, max_q)
+        size.append(ctx.workspace_bytes())
+        ctx.close()
+    assert size[1] - size[0] <= 4 * shape.n_kv_heads * (chunks + 1) * shape.group * (tokens - 512) + 2 * (64 << 20)
+
+
+@pytest.mark.parametrize("norm", [B.FR_NORM_PER_CHUNK, B.FR_NORM_GLOBAL])
 def test_scores_beyond_the_first_reference(norm):
     """Logits far above those of a chunk's first 16 keys: the column ranges that overflow are repeated with exact maxima."""
     shape = synth.LLAMA3_8B_BF16
