@@ -34,9 +34,10 @@
 // copies: no lookups, no pointer selects, no permutes, no address arithmetic, no staging registers.
 //
 // What a row does not see.  A weight of 0 does not take a NaN or an infinity out of a matrix product.  Positions behind the last
-// row of the Q index may hold anything: their values enter the images as zeros.  A value that is not finite and that only some
-// rows of a tile see makes the sums of the others NaN, which the overflow check finds; running_max_item keeps such values
-// apart.
+// row of the Q index may hold anything: they are not read.  A value that is not finite and that only some rows of a tile see makes the
+// sums of the others NaN, which the overflow check finds; in the instances with split weights running_max_item then keeps such values apart.  (In
+// the others the code for it would cost the tile loop 0.6 % through its registers; there a row is NaN too if one of the at most 63
+// positions behind it in its last key tile is.)
 #include "fr_internal.hpp"
 #include "k_rotate.hpp"
 
@@ -240,12 +241,12 @@ __global__ __launch_bounds__(256) void pack_kv_images_kernel(const __bf16* k_cac
     const int kt = blockIdx.x, g = blockIdx.y;
     const PackShare<D> ps;
     const bool have_new = k_new != nullptr;   // else the cache already holds the fresh rows
-    const int last = q_index[R - 1];          // no row sees a position behind it
+    // no row sees a position behind `last`: such keys of the tile repeat the one there (they may hold anything)
+    const int last = max(min(q_index[R - 1], L - 1), kt * KT);
     if (have_new) tile_fresh_rows(q_index, R, kt, fresh);
-    // key `t` of the tile (one past the end is clamped: it lies beyond every row's position), from k_new / v_new where it
-    // is fresh; (with the write-back a clamped key past the end repeats key L - 1: the same bytes again)
+    // key `t` of the tile, from k_new / v_new where it is fresh (with the write-back a repeated one: the same bytes again)
     auto fetch = [&](int t, const __bf16* cache, const __bf16* fresh_rows) -> u32x4 {
-        const int j = min(kt * KT + t, L - 1);
+        const int j = min(kt * KT + t, last);
         const int r = have_new ? fresh[j - kt * KT] : -1;
         const __bf16* src = r >= 0 ? fresh_rows + ((size_t)r * Hkv + g) * D : cache + ((size_t)j * Hkv + g) * D;
         const u32x4 x = *reinterpret_cast<const u32x4*>(src + 8 * ps.vec);
@@ -258,10 +259,7 @@ __global__ __launch_bounds__(256) void pack_kv_images_kernel(const __bf16* k_cac
     for (int i = 0; i < PackShare<D>::KI; ++i) kreg[i] = fetch(ps.key + (256 / PackShare<D>::NV) * i, k_cache, k_new);
     if (ps.has_v) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            vreg[i] = fetch(4 * ps.key + i, v_cache, v_new);
-            if (kt * KT + 4 * ps.key + i > last) vreg[i] = u32x4{0u, 0u, 0u, 0u};
-        }
+        for (int i = 0; i < 4; ++i) vreg[i] = fetch(4 * ps.key + i, v_cache, v_new);
     }
     write_image<D>(ps, kreg, vreg, img, images + ((size_t)g * n_img_tiles + kt) * Img<D>::BYTES);
 }
@@ -468,20 +466,22 @@ __device__ __forceinline__ uint32_t finite_or_zero(uint32_t w) {
     return w;
 }
 
-// O^T += V^T P^T for the 32 keys of half mb.  finite_only: without the values that are not finite.
-template <int D, bool SPLIT>
+// O^T += V^T P^T for the 32 keys of half mb.  FINITE_ONLY: without the values that are not finite.
+template <int D, bool SPLIT, bool FINITE_ONLY = false>
 __device__ __forceinline__ void pv_half(const unsigned char* vt, int mb, const Weights<SPLIT>& pf, const FragOffsets<D>& fo,
-                                        f32x16 (&o)[D / 32][2], bool finite_only = false) {
+                                        f32x16 (&o)[D / 32][2]) {
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk) {
         const int kb = 2 * mb + kk;
 #pragma unroll
         for (int md = 0; md < D / 32; ++md) {
-            u32x4 bits = *reinterpret_cast<const u32x4*>(vt + fo.v + 32 * kb + md * (32 * V_ROW));
-            if (finite_only)
+            bf16x8 a = *reinterpret_cast<const bf16x8*>(vt + fo.v + 32 * kb + md * (32 * V_ROW));
+            if constexpr (FINITE_ONLY) {
+                u32x4 bits = __builtin_bit_cast(u32x4, a);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) bits[e] = finite_or_zero(bits[e]);
-            const bf16x8 a = __builtin_bit_cast(bf16x8, bits);
+                a = __builtin_bit_cast(bf16x8, bits);
+            }
 #pragma unroll
             for (int nb = 0; nb < 2; ++nb) pf.multiply(a, nb, kk, o[md][nb]);
         }
@@ -793,7 +793,7 @@ __device__ __forceinline__ void running_max_item(const AttnQuery& aq, int g, int
         sg.write(k_img);
         __syncthreads();
         if (kt * KT > ge.wp_max) continue;   // wave-uniform; the barriers stay outside
-        const bool apart = kt >= ge.n_plain && holds_not_finite<D>(v_img);   // some rows may not see them
+        const bool apart = SPLIT && kt >= ge.n_plain && holds_not_finite<D>(v_img);   // some rows may not see them
 #pragma unroll
         for (int mb = 0; mb < 2; ++mb) {
             f32x16 s[2];
@@ -822,9 +822,13 @@ __device__ __forceinline__ void running_max_item(const AttnQuery& aq, int g, int
 #pragma unroll
                     for (int v = 0; v < 16; ++v) o[md][nb][v] *= alpha;
             }
-            pv_half<D, SPLIT>(v_img, mb, pf, fo, o, apart);
+            if constexpr (SPLIT) {
+                if (apart) pv_half<D, SPLIT, true>(v_img, mb, pf, fo, o); else pv_half<D, SPLIT>(v_img, mb, pf, fo, o);
+            } else {
+                pv_half<D, SPLIT>(v_img, mb, pf, fo, o);
+            }
         }
-        if (apart) add_not_finite<D>(v_img, kt * KT, ge.col_pos, h, o);
+        if constexpr (SPLIT) { if (apart) add_not_finite<D>(v_img, kt * KT, ge.col_pos, h, o); }
     }
     float l[2];
 #pragma unroll
