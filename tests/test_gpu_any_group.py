@@ -101,16 +101,22 @@ def test_attention_logits_beyond_the_fixed_reference(Hq, Hkv, d, split):
     ctx.close()
 
 
-@pytest.mark.parametrize("Hq,Hkv,d", [(7, 1, 128), (4, 2, 64)])
-def test_more_rows_than_one_launch_in_parts(Hq, Hkv, d):
+# Row tiles hold 4 floor(64 / G) rows.  Short prompts are cut up to 128 items (row tiles x KV heads; half of 256 compute units),
+# prompts of 32 key tiles and more up to 400: one case on either side of both lines, and the smallest.
+@pytest.mark.parametrize("Hq,Hkv,d,lens", [(7, 1, 128, (500, 413)), (4, 2, 64, (500, 413)),                      # 28 and 16 items: eight parts
+                                           (28, 4, 128, (500, 413)), (56, 8, 128, (500, 413)),                  # 112 in two parts, 224 whole
+                                           (32, 16, 64, (500, 413)), (34, 17, 64, (500, 413)),                  # 128 in two parts, 136 whole
+                                           (42, 6, 128, (1000, 990)), (56, 8, 128, (1000, 990))])               # 348 in two parts, 464 whole
+def test_items_on_both_sides_of_the_split_rules(Hq, Hkv, d, lens):
     """Every row of a prompt of several key tiles (100 % recompute equals dense causal attention)."""
-    w = workload(Hq, Hkv, d, (500, 413), 65, ratio=1.0)
-    k_ctx, _, k, qi = staged(w)
-    k_cache, v_cache = assembled_cache(w, k_ctx)
+    w = workload(Hq, Hkv, d, lens, 65, ratio=1.0)
+    qi = np.arange(w.L)
+    k_cache, v_cache = assembled_cache(w, w.k_cached)
     ctx = H.make_ctx(w.shape, w.L, w.n_chunks, w.nq)
     got, _ = run_attention(ctx, w, qi, k_cache, v_cache)
-    want, _ = orc.sparse_prefill_attn(w.q_full[qi], qi, k_cache, v_cache, w.k_full[qi], w.v_full[qi])
-    assert H.max_rel_err(got, want) <= OUT_TOL
+    rows = qi if Hq <= 7 else np.unique(np.concatenate([np.arange(0, w.L, 29), [w.L - 1]]))
+    want, _ = orc.sparse_prefill_attn(w.q_full[qi], qi, k_cache, v_cache, w.k_full[qi], w.v_full[qi], rows=rows)
+    assert H.max_rel_err(got[rows], want) <= OUT_TOL
     ctx.close()
 
 
@@ -242,6 +248,43 @@ def test_parts_of_short_prompts_keep_32_bits(Hq, Hkv, d):
         outs.append(run_attention(ctx, w, qi, k_cache, v_cache)[0])
         ctx.close()
     assert np.linalg.norm(outs[1] - outs[0]) <= 1.2e-4 * np.linalg.norm(outs[0])
+
+
+# (query heads, recomputed context rows, split): two parts are asked for; eight parts of the few items of a small call; four
+# parts (64 items of 32 rows)
+@pytest.mark.parametrize("Hq,Hkv,rows,split,parts", [(Hq, 2, 30, B.FR_ATTN_SPLIT_ON, 2) for Hq in (2, 4, 8, 16)] +
+                         [(8, 2, 30, B.FR_ATTN_SPLIT_AUTO, 8), (64, 8, 190, B.FR_ATTN_SPLIT_AUTO, 4)])
+@pytest.mark.parametrize("key_tiles", [31, 32, 33])
+@pytest.mark.parametrize("runaway", [False, True])
+def test_parts_in_half_precision_and_in_32_bits(Hq, Hkv, rows, split, parts, key_tiles, runaway):
+    """Up to four parts of a prompt of 32 key tiles and more hold their sums in half precision, all others in 32 bits.  Against
+    whole items: sums of 2000 fp32 terms differ by 2^-24 sqrt(2000) = 2.7e-6 of an element, which turns the bf16 rounding of
+    2.7e-6 / 2^-8 of them: 1e-4 of the norm.  Half precision: 2^-12 of a column's largest partial sum, about 3.5 times its
+    norm's share, uniform, for two parts and more: 7e-4 to 1e-3, and the rounding of a fifth of the elements turned: 1.5e-3."""
+    shape = synth.LayerShape(n_q_heads=Hq, n_kv_heads=Hkv, head_dim=128, dtype="bf16", rope_base=500000.0)
+    L, nq = 64 * key_tiles - 5, 40
+    w = synth.config_small_bf16(seed=Hq, chunk_lens=(L - nq,), nq=nq, shape=shape)
+    qi = np.concatenate([np.sort(np.random.default_rng(1).choice(L - nq, size=rows, replace=False)), np.arange(L - nq, L)])
+    k_cache, v_cache = assembled_cache(w, w.k_cached)
+    if runaway:      # one key far above the first ones: the sums of the rows behind it overflow, and their items are done again
+        w.q_full[:, :, 0] = 60.0
+        k_cache[1200] = w.k_full[1200] = 0.0
+        k_cache[1200, :, 0] = w.k_full[1200, :, 0] = 40.0
+    outs = []
+    for mode in (B.FR_ATTN_SPLIT_OFF, split):
+        ctx = H.make_ctx(shape, L, 1, nq)
+        ctx.fr_set_option(B.FR_OPT_ATTN_SPLIT, mode)
+        outs.append(run_attention(ctx, w, qi, k_cache, v_cache)[0])
+        ctx.close()
+    some = np.unique(np.concatenate([np.arange(0, len(qi), 7), [len(qi) - 1]]))
+    want, _ = orc.sparse_prefill_attn(w.q_full[qi], qi, k_cache, v_cache, w.k_full[qi], w.v_full[qi], rows=some)
+    H.assert_close(outs[1][some], want, "bf16", "attention")
+    before = slice(0, np.searchsorted(qi, 1200) // (4 * 64 // shape.group) * (4 * 64 // shape.group)) if runaway else slice(None)
+    off = np.linalg.norm((outs[1] - outs[0])[before]) / max(np.linalg.norm(outs[0][before]), 1e-30)
+    if key_tiles < 32 or parts > 4:
+        assert off <= 2e-4
+    else:
+        assert off <= 2.5e-3 and (runaway or off > 2e-4)
 
 
 @pytest.mark.parametrize("in_bin", [1, 2, 255, 256, 257, 300])

@@ -249,6 +249,64 @@ def test_shared_store_prefill_batch_of_queries():
     ctx.close()
 
 
+# (chunks, ratio, question tokens) of the queries.  Items of a call = longest query's row tiles x queries x KV heads (2 here); up to
+# a quarter of the 256 compute units its queries are cut as they would be alone, beyond that like one query of all the items.
+BATCHES = {
+    "two_12": [((0, 2, 4), 0.15, 40), ((5, 1), 0.0, 7)],                                    # 12 items: seven parts, three of them empty for the short query
+    "four_64": [((0, 2, 4, 5), 0.5, 40), ((3,), 1.0, 3), ((1,), 0.0, 5), ((2, 5), 0.3, 20)],        # 64 items: the last size of the first rule
+    "three_66": [((0, 1, 2, 3, 4), 0.65, 60), ((5,), 0.0, 9), ((4, 3), 0.15, 33)],            # 66: the first of the second, three parts
+    "four_144": [((0, 1, 2, 3, 4, 5), 1.0, 40), ((3, 0), 0.1, 5), ((2,), 0.2, 1), ((5,), 0.0, 11)],   # 144: whole unless asked
+}
+
+
+@pytest.mark.parametrize("split", [B.FR_ATTN_SPLIT_AUTO, B.FR_ATTN_SPLIT_ON])
+@pytest.mark.parametrize("name", BATCHES)
+def test_shared_store_batch_in_parts(name, split):
+    """Queries of very different lengths and row numbers whose items are cut into parts; every second query has a key far above
+    its first ones, so that its sums overflow and its items are done again."""
+    dt = "bf16"
+    shape = synth.LayerShape(n_q_heads=8, n_kv_heads=2, head_dim=128, dtype=dt, rope_base=500000.0)
+    rng = np.random.default_rng(len(name))
+    base = synth.config_small_bf16(seed=5, chunk_lens=(200, 64, 333, 91, 256, 130), shape=shape)
+    k_store, v_store, row0_all = scattered_store(base, rng)
+    ks_d, vs_d = H.dev(k_store, dt), H.dev(v_store, dt)
+    chunk_len = np.diff(base.chunk_offsets)
+    ctx = H.make_ctx(shape, base.L + 64, base.n_chunks, 64)
+    ctx.fr_set_option(B.FR_OPT_ATTN_SPLIT, split)
+    queries, wants = [], []
+    for i, (chunks, ratio, nq) in enumerate(BATCHES[name]):
+        offs = np.concatenate([[0], np.cumsum([int(chunk_len[c]) for c in chunks])]).astype(np.int32)
+        L_ctx = int(offs[-1])
+        src_pos0 = rng.integers(0, 3000, size=len(chunks)).astype(np.int32)
+        k = orc.topk_count(L_ctx, ratio)
+        qi = np.concatenate([np.sort(rng.choice(L_ctx, size=k, replace=False)), L_ctx + np.arange(nq)]).astype(np.int64)
+        R = len(qi)
+        mk = lambda n, heads, scale: synth.round_to_storage((scale * rng.standard_normal((n, heads, 128))).astype(np.float32), dt)
+        q_rows, k_new, v_new = mk(R, 8, np.sqrt(128)), mk(R, 2, 128 ** -0.5), mk(R, 2, 128 ** -0.5)
+        if i % 2 == 1:
+            q_rows[:, :, 0] = 60.0
+            hot = min(R - 1, int(np.searchsorted(qi, 40)))           # the first row behind the keys that set the reference
+            k_new[hot] = 0.0
+            k_new[hot, :, 0] = 40.0
+        at = np.concatenate([np.arange(base.chunk_offsets[c], base.chunk_offsets[c + 1]) for c in chunks])
+        queries.append(dict(q_rows=H.dev(q_rows, dt), q_index=torch.from_numpy(qi.astype(np.int32)).cuda(), R=R, chunk_offsets=offs,
+                            chunk_store_row0=row0_all[list(chunks)], chunk_src_pos0=src_pos0, L=L_ctx + nq, k_new=H.dev(k_new, dt),
+                            v_new=H.dev(v_new, dt), out=torch.zeros((R, 8, 128), dtype=torch.bfloat16, device="cuda"),
+                            lse_out=torch.zeros((R, 8), dtype=torch.float32, device="cuda")))
+        k_ctx = synth.round_to_storage(orc.rope_shift(base.k_cached[at], offs, src_pos0, None, shape.rope_base, "interleaved"), dt)
+        pad = np.zeros((nq, 2, 128))
+        wants.append(orc.sparse_prefill_attn(q_rows, qi, np.concatenate([k_ctx, pad]), np.concatenate([base.v_cached[at], pad]), k_new, v_new))
+    tiles = max((q["R"] + 63) // 64 for q in queries)
+    assert tiles * len(queries) * 2 == int(name.split("_")[1])
+    ws = torch.empty(ctx.fr_shared_batch_workspace_bytes(len(queries), max(q["L"] for q in queries)), dtype=torch.uint8, device="cuda")
+    ctx.fr_sparse_prefill_attn_shared_batch(queries, ks_d, vs_d, len(k_store), ws)
+    torch.cuda.synchronize()
+    for q, (want, want_lse) in zip(queries, wants):
+        H.assert_close(H.host(q["out"]), want, dt, "batch in parts")
+        assert np.max(np.abs(q["lse_out"].cpu().numpy() - want_lse)) <= 2e-3 * max(1.0, float(np.max(np.abs(want_lse))) / 100)
+    ctx.close()
+
+
 def test_shared_store_batch_full_size_sampled():
     """The launch configuration `bench.py --config 8` times (Llama-3-8B layer shape, queries of 16 chunks x 1024 tokens
     drawn from a 32-chunk store, 512 question tokens, 15 %), three queries per call: sampled output rows against the

@@ -293,9 +293,11 @@ def test_full_size_stack_layers_teacher_forced(full_stack_run, layer):
 @pytest.mark.parametrize("M,N,K", [
     (16397, 28672, 64), (16397, 14336, 128),                            # one and two K tiles, a nearly empty last row tile
     (2818, 4096, 768), (2900, 4096, 832), (3072, 4096, 896),            # even and odd numbers of K tiles; 1 and 256 rows too many
+    (8193, 4096, 768), (8400, 4096, 832), (8448, 4096, 896),
 ])
 def test_linear_256_rows_per_workgroup(ctx, M, N, K):
-    """Whole tiles of the 256 x 256 kernel add the products of an element in the order of the 256 x 128 kernel: the same bits."""
+    """Whole tiles of the 256 x 256 kernel add the products of an element in the order of the 256 x 128 kernel: the same bits.
+    (On 256 compute units the launcher's estimate is for the 256 x 256 kernel, by 8 % at the large sizes, 1 % at about 3000 rows.)"""
     g = torch.Generator(device="cuda")
     g.manual_seed(M + N + K)
     a = torch.randn((M, K), generator=g, device="cuda").to(torch.bfloat16)
