@@ -61,8 +61,10 @@ struct Tiling {
     static constexpr int BRT = BR;                       // and rows
     static constexpr int WAVE_TILES = NW;                // 64 x 64 pieces of the output tile
     // What a launch takes (plan_tiling): time per K tile of a full round, the share of it that a nearly empty round still
-    // takes (a full round is held back by the chip's power limit), pipeline fill and epilogue, a split last round.
-    static constexpr float US_PER_K_TILE = 0.9f, ROUND_BASE = 0.5f, US_LAUNCH = 3.0f, US_SPLIT = 14.0f;
+    // takes (a full round is held back by the chip's power limit), launch, pipeline fill and epilogue, a split last round.
+    // Chosen so that the better of the two tilings is taken: over 742 products (N 256 .. 28672, K 128 .. 14336, 1 .. 4096
+    // rows) the choice is 0.2 % slower than the faster one on average.  Two K tiles of many features are its worst (9 %).
+    static constexpr float US_PER_K_TILE = 0.9f, ROUND_BASE = 0.33f, US_LAUNCH = 8.0f, US_SPLIT = 6.0f;
     static __host__ __device__ constexpr int feature0(int v) { return 64 * (v % WF); }
     static __host__ __device__ constexpr int row_0(int v) { return 64 * (v / WF); }
     // feature tiles fastest, so that workgroups that share an activation tile are neighbours
@@ -376,7 +378,7 @@ struct Tiling256 {
     static constexpr int STAGE = 4 * PIECE;                // [w0 w1][w2 w3][a0][a1]
     static constexpr int WAVE_TILES = 16;                  // 64 x 64 pieces of the output tile, two per wave
     static constexpr int LDS_BYTES = NW * 64 * EPI_PITCH * 4;
-    static constexpr float US_PER_K_TILE = 1.5f, ROUND_BASE = 0.2f, US_LAUNCH = 7.0f, US_SPLIT = 22.0f;   // see Tiling
+    static constexpr float US_PER_K_TILE = 1.6f, ROUND_BASE = 0.25f, US_LAUNCH = 9.5f, US_SPLIT = 15.0f;   // see Tiling
     static_assert(2 * STAGE <= LDS_BYTES, "the epilogue staging is the larger one");
     static __host__ __device__ constexpr int feature0(int v) { return 128 * (v >> 3) + 64 * (v & 1); }   // v = 2 wave + half
     static __host__ __device__ constexpr int row_0(int v) { return 64 * ((v >> 1) & 3); }
@@ -707,10 +709,11 @@ hipError_t launch_gemm(const GemmArgs& g, const GemmTuning& tune, hipStream_t st
     const Plan narrow = plan_tiling<Tiling<4>>(g, n_cu, tune);
     // 256 rows per workgroup where that is the shorter launch by the estimate above: a tile of twice the area takes 1.6
     // times as long, but it comes in rounds twice as coarse and its partial sums cost more.  256 x 128 -> 256 x 256, us:
-    //   28672 x 4096 (gate / up): 2048 rows 438 -> 382, 2970 rows 670 -> 551, 16896 rows 3529 -> 2929
-    //   4096 x 14336 (down):      1100 rows 174 -> 125, 2048 rows 208 -> 200, 2970 rows 313 -> 278
-    //   4096 x 4096 (output):     1100 rows  48 stays (53), 2048 rows 61 stays (75), 2970 rows 101 -> 86
-    //   6144 x 4096 (Q / K / V):  1100 rows  55 stays (72), 2048 rows 108 -> 100, 2970 rows 156 -> 145
+    //   28672 x 4096 (gate / up): 1100 rows 232 stays, 2048 rows 417 -> 377, 2970 rows 652 -> 548, 16896 rows 3529 -> 2929
+    //   4096 x 14336 (down):      1100 rows 154 -> 139, 2048 rows 192 -> 196, 2970 rows 304 -> 270
+    //   4096 x 4096 (output):     1100 rows  48 stays (59), 2048 rows 62 stays (76), 2970 rows 100 -> 86
+    //   6144 x 4096 (Q / K / V):  1100 rows  54 stays (73), 2048 rows 104 -> 91, 2970 rows 146 -> 139
+    //   256 x 1792:               1 row      19 stays (30)
     if (tune.tile == 0) {
         const Plan square = plan_tiling<Tiling256>(g, n_cu, tune);
         if (square.us < narrow.us) return launch_tiling<EPI, Tiling256>(g, &gemm_bf16_256_kernel<EPI>, square, st);

@@ -297,7 +297,7 @@ def test_full_size_stack_layers_teacher_forced(full_stack_run, layer):
 ])
 def test_linear_256_rows_per_workgroup(ctx, M, N, K):
     """Whole tiles of the 256 x 256 kernel add the products of an element in the order of the 256 x 128 kernel: the same bits.
-    (On 256 compute units the launcher's estimate is for the 256 x 256 kernel, by 8 % at the large sizes, 1 % at about 3000 rows.)"""
+    (On 256 compute units the launcher's estimate is for the 256 x 256 kernel, by 2 % at about 3000 rows, 3 to 7 % at the large sizes.)"""
     g = torch.Generator(device="cuda")
     g.manual_seed(M + N + K)
     a = torch.randn((M, K), generator=g, device="cuda").to(torch.bfloat16)
@@ -319,7 +319,7 @@ def test_linear_256_rows_per_workgroup(ctx, M, N, K):
 
 
 def test_epilogues_256_rows_per_workgroup_split(ctx):
-    """A launch of one round whose 256 x 256 tiles are split along K, with every epilogue."""
+    """A launch of one round whose 256 x 256 tiles are split along K, with every epilogue (three parts of 80 and of 72 tiles)."""
     M, K, Hq, Hkv, d = 1101, 14336, SHAPE.n_q_heads, SHAPE.n_kv_heads, SHAPE.head_dim
     g = torch.Generator(device="cuda")
     g.manual_seed(5)
@@ -333,6 +333,7 @@ def test_epilogues_256_rows_per_workgroup_split(ctx):
     ctx.fr_linear_swiglu(a, wg, M, 2048, K, sw)
     y = a.double() @ wg.double().T
     H.assert_close(H.host(sw), H.host(torch.nn.functional.silu(y[:, 0::2]) * y[:, 1::2]), "bf16", "swiglu")
+    M, a = 701, a[:701].contiguous()
     pos = torch.arange(M, dtype=torch.int32, device="cuda") * 3
     q, k, v = (torch.zeros((M, n, d), dtype=torch.bfloat16, device="cuda") for n in (Hq, Hkv, Hkv))
     ctx.fr_qkv_rope(a, wq, M, K, pos, q, k, v)
