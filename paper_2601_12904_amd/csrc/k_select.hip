@@ -145,22 +145,25 @@ __global__ __launch_bounds__(SEL_THREADS) void select_topk_kernel(const float* _
                 if (i < cnt && (rk & mask) == prefix) candidates[atomicAdd(&s_listed, 1u)] = rk;
             }
             __syncthreads();
-            if (tid < (int)count) {
-                const uint32_t own = candidates[tid];
-                uint32_t larger = 0u, equal = 0u;
-                for (uint32_t j = 0; j < count; j += 4) {
-                    const uint4 c = *reinterpret_cast<const uint4*>(&candidates[j]);   // entries past `count` do not count
-                    const uint32_t v[4] = {c.x, c.y, c.z, c.w};
+            // four threads per candidate, each counts in every fourth vector of the list (one thread each: 16 us instead of 12 for
+            // 6196 scores of 50 different values, whose bins hold over a hundred)
+            static_assert(4 * CANDIDATES <= SEL_THREADS, "candidates per pass");
+            const uint32_t own = candidates[min(tid >> 2, (int)count - 1)];
+            uint32_t larger = 0u, equal = 0u;
+            for (uint32_t j = 4 * (tid & 3); j < count; j += 16) {
+                const uint4 c = *reinterpret_cast<const uint4*>(&candidates[j]);   // entries past `count` do not count
+                const uint32_t v[4] = {c.x, c.y, c.z, c.w};
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        larger += (j + e < count && v[e] > own) ? 1u : 0u;
-                        equal += (j + e < count && v[e] == own) ? 1u : 0u;
-                    }
+                for (int e = 0; e < 4; ++e) {
+                    larger += (j + e < count && v[e] > own) ? 1u : 0u;
+                    equal += (j + e < count && v[e] == own) ? 1u : 0u;
                 }
-                if (larger < remaining && larger + equal >= remaining) {   // (every copy of the k-th largest key writes the same)
-                    s_prefix = own;
-                    s_remaining = remaining - larger;
-                }
+            }
+            larger += __shfl_xor((int)larger, 1); equal += __shfl_xor((int)equal, 1);
+            larger += __shfl_xor((int)larger, 2); equal += __shfl_xor((int)equal, 2);
+            if (larger < remaining && larger + equal >= remaining) {   // (every copy of the k-th largest key writes the same)
+                s_prefix = own;
+                s_remaining = remaining - larger;
             }
             __syncthreads();
         }
