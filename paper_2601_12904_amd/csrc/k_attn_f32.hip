@@ -51,7 +51,7 @@ __global__ __launch_bounds__(64 * W) void attn_f32_kernel(const T* __restrict__ 
     const int n = min(16 * tile + x, cols - 1), r = n / G, head = g * G + n % G;   // columns past the end: a copy of the last
     const int pos = q_index[r];
     const int p_max = q_index[min(16 * tile + 15, cols - 1) / G];   // rows ascend
-    const int p_last = min(p_max, L - 1), n_blocks = p_last / 16 + 1;
+    const int p_last = max(min(p_max, L - 1), 0), n_blocks = p_last / 16 + 1;   // (in bounds whatever the Q index holds)
     const int p_first = q_index[16 * tile / G];   // keys up to here are visible to every column of the tile
 
     const bool have_new = k_new != nullptr, own_map = have_new && inv == nullptr;
