@@ -98,12 +98,14 @@ int64_t fr_workspace_bytes(const fr_ctx* ctx);
  * FR_OPT_ATTN_SPLIT: AUTO (default) deals the key range of every (row tile, KV head) to two or more workgroups when
  * there are too few of those to fill the chip (few recomputed rows, e.g. question-only prefill or the offline stage of
  * eq. 10); OFF: never; ON: two workgroups each whenever the partial results fit the workspace.  Same results up to the
- * summation order and the partial sums' storage format (half precision after a per-column power-of-two scale: 11
- * significant bits of a column's largest partial value, finer than the bf16 output).
+ * summation order and, for up to four parts of a prompt of 32 key tiles of 64 and more at group sizes 1, 2, 4, 8 and
+ * head_dim 128, the partial sums' storage format (half precision after a per-column power-of-two scale: 11
+ * significant bits of a column's largest partial value, finer than the bf16 output); all other parts keep 32 bits.
  * FR_OPT_DECODE_KERNEL: AUTO (default) lets fr_decode_attn form the logits on the matrix cores where it can (bf16,
  * head_dim 128); GENERIC forces the all-vector-ALU kernel that every other shape uses (so that tests reach both).
- * FR_OPT_GEMM_TILE: output features per workgroup of the projection kernels, 0 (default: 256 where the feature count
- * is a multiple of 256, else 128), 128 or 256; for tests and tuning.
+ * FR_OPT_GEMM_TILE: output features x rows per workgroup of the projection kernels: 0 (default: 256 x 256 or 256 x 128,
+ * whichever an estimate of the launch's time favours, where the feature count is a multiple of 256, else 128 x 128),
+ * 128 (x 128) or 256 (x 128); for tests and tuning.
  * FR_OPT_GEMM_TAIL_SPLIT: 1 (default): when the output tiles of a projection do not fill the last round of
  * workgroups (one per CU), the tiles of that round are split along K over several workgroups each and a second small
  * kernel adds the parts; 0: never.  Same results up to fp32 summation order; for tests and tuning.  (Like every
@@ -210,7 +212,7 @@ fr_status fr_kv_deviation(fr_ctx* ctx, const void* kv_a, const void* kv_b, int64
 /* Sparse prefill attention (eq. 9, Sec. 4.3).  Row r holds the query of the token at position
  * q_index[r]; it attends to every key at a position <= q_index[r].  The key/value at a position
  * listed in q_index is the recomputed one (k_new/v_new row of that token), every other position
- * reads the cache: the stale cache entries of recomputed tokens are never read.
+ * reads the cache: the stale cache entries of recomputed tokens are never read, nor is any position behind q_index[R - 1].
  *   q_rows   dev [R, Hq, d]
  *   q_index  dev [R] int32, strictly ascending, every entry < L
  *   k_cache, v_cache dev [L, Hkv, d] (read only)

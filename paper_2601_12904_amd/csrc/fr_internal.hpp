@@ -49,8 +49,8 @@ struct Workspace {
     float* qsum = nullptr;              // [Hkv][d] question queries summed per KV head (raw scores), then partial sums
     uint32_t* select_tmp = nullptr; // state, histogram, per-wave counts and candidate list of the selection kernels
     int n_cu = 0;                   // compute units of the device
-    void* store_k = nullptr;        // shapes without a tiled path: a query's keys / values gathered from a shared
-    void* store_v = nullptr;        // chunk store ([max_tokens, Hkv, d] each), for the generic kernels
+    void* store_k = nullptr;        // shapes whose kernels do not read a chunk store: a query's keys / values gathered
+    void* store_v = nullptr;        // from it ([max_tokens, Hkv, d] each)
     float* gemm_partials = nullptr; // partial sums of the GEMM tiles that are split along K
     size_t gemm_partials_bytes = 0;
     float2* rope_rows = nullptr;    // [max_tokens][d/2] (cos, sin) of the recomputed rows' positions

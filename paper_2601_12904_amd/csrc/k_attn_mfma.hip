@@ -59,7 +59,7 @@ typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 constexpr int KT = 64;           // keys per tile
 constexpr float NEG_BIG = -1.0e30f;
 
-// Tile image = [K image][V^T image] (18 KB each at head_dim 128, 9 KB at 64), padded so that 16-byte operand reads (one
+// Tile image = [K image][V^T image] (17 and 18 KB at head_dim 128, 9 KB each at 64), padded so that 16-byte operand reads (one
 // lane per row, 16 lanes per LDS pass) fall into 16 distinct bank groups and every fragment address is base + constant:
 //   K image:   64 rows (keys) of 2 D bytes of data + 16 B pad, rounded up to whole KB;
 //   V^T image: D rows (dims) of 144 B (64 key slots = 128 B of data + 16 B pad), slot order see key_slot.

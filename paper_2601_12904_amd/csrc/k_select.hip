@@ -65,6 +65,11 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t ballot) {   // set bits
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(ballot >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)ballot, 0u));
 }
 
+__device__ __forceinline__ uint32_t quad_sum(uint32_t v) {   // over four neighbouring lanes
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);    // quad_perm [1,0,3,2]
+    return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);   // quad_perm [2,3,0,1]
+}
+
 // Wave w owns the contiguous index range [w * 64 * per, (w + 1) * 64 * per); its i-th load covers the 64
 // consecutive tokens base + 64 i + lane, so loads and stores are coalesced and (i, lane) order is index order.
 // Every thread keeps its PER keys in registers (n <= SEL_THREADS * PER).
@@ -159,8 +164,8 @@ __global__ __launch_bounds__(SEL_THREADS) void select_topk_kernel(const float* _
                     equal += (j + e < count && v[e] == own) ? 1u : 0u;
                 }
             }
-            larger += __shfl_xor((int)larger, 1); equal += __shfl_xor((int)equal, 1);
-            larger += __shfl_xor((int)larger, 2); equal += __shfl_xor((int)equal, 2);
+            larger = quad_sum(larger);
+            equal = quad_sum(equal);
             if (larger < remaining && larger + equal >= remaining) {   // (every copy of the k-th largest key writes the same)
                 s_prefix = own;
                 s_remaining = remaining - larger;
