@@ -583,21 +583,23 @@ __global__ void clear_words_kernel(uint32_t* __restrict__ bits, int64_t n_words)
 // 2978 page rows (272 whole units): 41.0 us per call with four pieces per segment and twelve per page, 42.1 with half as
 // many, 43.6 with pages cut like segments, 58 with twice as many, 68 us uncut.  Segments stay whole from 1024
 // units x KV heads on (eight queries of 16 chunks, 8 KV heads).
-// No piece is cut with room for fewer than min_rows: a workgroup costs its rotation, its merge of lanes and waves and its share
-// of the combine pass whatever it reads.  The matrix-core kernel gives each of its four waves a block of 32 rows; the other
-// one merges every lane's slice of all heads of the group, four rows for each of its elements (bf16, head_dim 64, group of 8: two
-// queries of 8 x 512 rows and 600 page rows 39 -> 25 us, 25 pages of 13 rows 29 -> 14; uncut 27 and 14).  A segment has room for the store, or for its
-// share of it where a query's segments do not overlap.
-Pieces choose_pieces(const DecodeArgs& a, int Hkv, int n_cu, int min_rows) {
+// No piece is cut with room for fewer than seg_rows or page_rows: a workgroup costs its rotation, its merge of lanes and waves
+// and its share of the combine pass whatever it reads.  The matrix-core kernel gives a wave a block of 32 rows: 96 rows of a
+// segment, 64 of a page, which is filled (150 batches of 1 to 32 queries: 5.5 % less time on average than without the limits,
+// none more than 3 % slower; 128 of both 6 %, some 6 % slower; 64 of both 4 %).  The other one merges every lane's slice of
+// all heads of the group, four rows for each of its elements (bf16, head_dim 64, group of 8: two queries of 8 x 512 rows and 600
+// page rows 39 -> 25 us, 25 pages of 13 rows 29 -> 14; uncut 27 and 14).  A segment has room for the store, or for its share
+// of it where a query's segments do not overlap.
+Pieces choose_pieces(const DecodeArgs& a, int Hkv, int n_cu, int seg_rows, int page_rows) {
     Pieces pc{1, 1};
     const int units = (a.n_seg + a.B) * Hkv;
     pc.seg = std::max(1, std::min(8, (4 * n_cu + units - 1) / units));
     pc.page = (int)std::max<int64_t>(1, std::min<int64_t>(16, pc.seg * std::max<int64_t>(1, (a.page_stride + 512) / 1024)));
     if (a.n_seg > 0) {
         const int64_t room = a.n_seg > a.B ? a.n_shared / a.n_seg * a.B + a.n_shared % a.n_seg * a.B / a.n_seg : a.n_shared;
-        pc.seg = (int)std::max<int64_t>(1, std::min<int64_t>(pc.seg, room / min_rows));
+        pc.seg = (int)std::max<int64_t>(1, std::min<int64_t>(pc.seg, room / seg_rows));
     }
-    pc.page = (int)std::max<int64_t>(1, std::min<int64_t>(pc.page, a.page_stride / min_rows));
+    pc.page = (int)std::max<int64_t>(1, std::min<int64_t>(pc.page, a.page_stride / page_rows));
     while ((int64_t)a.n_seg * pc.seg + (int64_t)a.B * pc.page > DECODE_MAX_UNITS) {   // what the partial results' buffer holds
         pc.seg = std::max(1, pc.seg / 2);
         pc.page = std::max(1, pc.page / 2);
@@ -609,7 +611,8 @@ template <typename T, int D, int G>
 hipError_t run(const Shape& s, const DecodeArgs& a, float* partials, const double* theta, int n_cu, hipStream_t st) {
     const float scale_log2e = (1.0f / sqrtf((float)D)) * 1.4426950408889634f;
     const bool matrix = sizeof(T) == 2 && D == 128 && !a.force_generic;
-    const Pieces pc = choose_pieces(a, s.Hkv, n_cu, matrix ? 128 : std::max(64, 4 * G * Row16<T>::N));
+    constexpr int generic_rows = std::max(64, 4 * G * Row16<T>::N);
+    const Pieces pc = choose_pieces(a, s.Hkv, n_cu, matrix ? 96 : generic_rows, matrix ? 64 : generic_rows);
     const dim3 grid(a.n_seg * pc.seg + a.B * pc.page, s.Hkv);
     if constexpr (sizeof(T) == 2 && D == 128) {
         if (matrix)

@@ -182,7 +182,7 @@ def test_decode_attn_full_size_sampled():
     ((33, 31, 4200), ((0, 1),), 1, 4100),           # pages cut by the room they have, of which a few rows are filled
     ((2000, 7), ((0,), (1,)), 1600, None),          # pieces of several blocks per wave, ragged tails
     ((5,), ((0,) * 500,) * 8, 1, 15900),            # more pieces than the partial results' buffer holds: cut into fewer
-    ((127,), ((0,),), 100, 128), ((255, 2), ((0,),), 200, 256), ((129,), ((0, 0),), 200, 257),   # room for less than two pieces, for two, for
+    ((127,), ((0,),), 100, 128), ((255, 2), ((0,),), 200, 256), ((129,), ((0, 0),), 200, 257),   # room for one piece, for two, for
     ((300, 212), ((0, 1), (1, 0)), 100, 512),                                                    # its share of the store only
 ])
 def test_decode_attn_pieces(chunk_lens, prompts, n_gen, page_stride, generic):
