@@ -578,8 +578,8 @@ __global__ void clear_words_kernel(uint32_t* __restrict__ bits, int64_t n_words)
     if (i < n_words) bits[i] = 0u;
 }
 
-// Pieces per unit (see Pieces): about four workgroups per compute unit (two are resident), and pages, which hold the
-// recomputed tokens of all segments, in proportion to the rows they have room for.  Two queries of 16 x 1024 store rows and
+// Pieces per unit (see Pieces): about four workgroups per compute unit in the matrix-core kernel (two are resident), and pages,
+// which hold the recomputed tokens of all segments, in proportion to the rows they have room for.  Two queries of 16 x 1024 store rows and
 // 2978 page rows (272 whole units): 41.0 us per call with four pieces per segment and twelve per page, 42.1 with half as
 // many, 43.6 with pages cut like segments, 58 with twice as many, 68 us uncut.  Segments stay whole from 1024
 // units x KV heads on (eight queries of 16 chunks, 8 KV heads).
@@ -587,13 +587,14 @@ __global__ void clear_words_kernel(uint32_t* __restrict__ bits, int64_t n_words)
 // and its share of the combine pass whatever it reads.  The matrix-core kernel gives a wave a block of 32 rows: 96 rows of a
 // segment, 64 of a page, which is filled (150 batches of 1 to 32 queries: 5.5 % less time on average than without the limits,
 // none more than 3 % slower; 128 of both 6 %, some 6 % slower; 64 of both 4 %).  The other one merges every lane's slice of
-// all heads of the group, four rows for each of its elements (bf16, head_dim 64, group of 8: two queries of 8 x 512 rows and 600
-// page rows 39 -> 25 us, 25 pages of 13 rows 29 -> 14; uncut 27 and 14).  A segment has room for the store, or for its share
+// all heads: two workgroups per compute unit, 32 rows for each element of a 16-byte vector (bf16, head_dim 64, group of 8, us,
+// uncut / by counts alone / now: 2 x 8 x 512 rows and 600 page rows 27 / 39 / 25, 25 pages of 13 rows 14 / 29 / 13, 6 x 4 x 700
+// and 300 30 / 40 / 33, 2 x 16 x 1024 and 2978 78 / 46 / 42).  A segment has room for the store, or for its share
 // of it where a query's segments do not overlap.
-Pieces choose_pieces(const DecodeArgs& a, int Hkv, int n_cu, int seg_rows, int page_rows) {
+Pieces choose_pieces(const DecodeArgs& a, int Hkv, int workgroups, int seg_rows, int page_rows) {
     Pieces pc{1, 1};
     const int units = (a.n_seg + a.B) * Hkv;
-    pc.seg = std::max(1, std::min(8, (4 * n_cu + units - 1) / units));
+    pc.seg = std::max(1, std::min(8, (workgroups + units - 1) / units));
     pc.page = (int)std::max<int64_t>(1, std::min<int64_t>(16, pc.seg * std::max<int64_t>(1, (a.page_stride + 512) / 1024)));
     if (a.n_seg > 0) {
         const int64_t room = a.n_seg > a.B ? a.n_shared / a.n_seg * a.B + a.n_shared % a.n_seg * a.B / a.n_seg : a.n_shared;
@@ -611,8 +612,8 @@ template <typename T, int D, int G>
 hipError_t run(const Shape& s, const DecodeArgs& a, float* partials, const double* theta, int n_cu, hipStream_t st) {
     const float scale_log2e = (1.0f / sqrtf((float)D)) * 1.4426950408889634f;
     const bool matrix = sizeof(T) == 2 && D == 128 && !a.force_generic;
-    constexpr int generic_rows = std::max(64, 4 * G * Row16<T>::N);
-    const Pieces pc = choose_pieces(a, s.Hkv, n_cu, matrix ? 96 : generic_rows, matrix ? 64 : generic_rows);
+    constexpr int rows = 32 * Row16<T>::N;
+    const Pieces pc = matrix ? choose_pieces(a, s.Hkv, 4 * n_cu, 96, 64) : choose_pieces(a, s.Hkv, 2 * n_cu, rows, rows);
     const dim3 grid(a.n_seg * pc.seg + a.B * pc.page, s.Hkv);
     if constexpr (sizeof(T) == 2 && D == 128) {
         if (matrix)
