@@ -1,35 +1,44 @@
 // Sparse prefill attention (eq. 9, Sec. 4.3) on the gfx950 matrix cores: bf16, head_dim 64 or 128, up to 64 query heads
 // per KV head.
 //
-// Work split.  One workgroup (4 waves) owns one KV head and a tile of consecutive Q-index rows;
-// each wave owns 64 "query columns" = floor(64 / G) token rows x the G query heads that share the KV
+// Work split.  One workgroup owns one KV head and a tile of consecutive Q-index rows in four row groups of 64 "query columns" =
+// floor(64 / G) token rows x the G query heads that share the KV
 // head (a group size that does not divide 64 leaves a few columns idle: one of 64 at 7, four at 5), so every K/V tile staged in LDS is reused by the whole grouped-query group and by all
-// four waves.  Rows are sorted by position, so a tile needs keys 0 .. (position of its last row);
-// tiles are issued longest first.
+// row groups.  The fast kernel has two waves per row group (and per SIMD), each with half of the keys of every tile.  Rows are sorted by
+// position, so a tile needs keys 0 .. (position of its last row); tiles are issued longest first.
 //
 // Orientation.  The kernel computes the transposed products S^T = K Q^T and O^T = V^T P^T with
-// v_mfma_f32_32x32x16_bf16:
+// v_mfma_f32_16x16x32_bf16:
 //   * keys run along the M (register) dimension of S^T and query columns along N (lanes), so the
-//     softmax statistics of a query column live in one lane (plus its partner lane + 32);
-//   * the fp32 accumulator layout of S^T is, after conversion to bf16, exactly the B-operand
+//     softmax statistics of a query column live in four lanes (x, x + 16, x + 32, x + 48), and in-lane during the loop;
+//   * the fp32 accumulators of two S^T blocks (32 keys) are, after conversion to bf16, exactly the B-operand
 //     layout of the second product (contraction over keys), so P never leaves registers;
 //   * V is transposed once per (KV head, key tile) by the packing pre-pass (4 keys x 8 dims per lane,
 //     repacked with byte permutes), so the A operand of the second product is a 16-byte LDS read.
-// The key order inside every block of 16 keys is permuted identically in P^T and V^T
-// ([0-3, 8-11, 4-7, 12-15]); a contraction does not care about the order of its terms.
+// The key order inside every block of 32 keys is permuted identically in P^T and V^T (key_slot); a contraction does not care
+// about the order of its terms.
+//
+// What bounds it.  The chip's power: matrix instructions alone, on normally distributed operands in registers, sustain 1.78 PFLOP/s as
+// 32 x 32 x 16 and 1.98 as 16 x 16 x 32 (2.45 either on zeros), because a contraction of 32 reads and writes its accumulators half as often; and 2 - 3 % more where
+// neighbouring instructions share an operand.  With one wave per SIMD and 32 x 32 tiles (four waves, vector work between the matrix
+// instructions of the same wave) the loop took 20 % more cycles at a higher clock; two waves per SIMD with 32 x 32 tiles needed the fewest
+// cycles (matrix pipe busy 73 %) at 1.63 GHz and were 4 % faster; with 16 x 16 tiles 71 % at 1.93 GHz.  Measured on one box, 32 / 8 heads:
+// 2970 of 16896 rows 432 -> 371 us, all rows 1974 -> 1661 us (1.18 -> 1.41 PFLOP/s); 28 / 4 heads with split weights 709 -> 581 us.
+// Raising the priority of either phase changes nothing; query fragments from LDS instead of registers cost 1 % for each
+// quarter of them (power again), so as many stay in registers as the loop has room for.
 //
 // Softmax.  exp(s - m) / sum exp(s - m) does not depend on m, and fp32 / bf16 leave about 2^127 of
 // headroom, so the fast kernel fixes each query column's reference m once (the maximum over the
 // column's first 32 visible keys) and never rescales: the tile loop holds no maximum, no
-// comparison and no branch.  If a later logit exceeds the reference by more than that headroom
+// comparison and no branch on values.  If a later logit exceeds the reference by more than that headroom
 // the sums overflow to inf; the workgroup then recomputes its item with the classic online softmax
 // (running maximum).
 //
 // K/V tile images.  Every row tile of a KV head walks the same K/V stream (47 row tiles per head at 17k
 // tokens / 15 %), so the work that does not depend on the rows is done once, by a packing pre-pass: for each
-// (KV head, 64-key tile) it resolves stale / fresh rows (key j comes from k_new/v_new when inv[j] >= 0, i.e.
-// its token is in the Q index, and from the cache otherwise: the cache is never written and stale rows are
-// never read), transposes V, pads the rows against LDS bank conflicts and writes an image (35 KB at head_dim 128) that is byte
+// (KV head, 64-key tile) it resolves stale / fresh rows (key j comes from k_new/v_new when its token is in the Q index, and
+// from the cache otherwise: the cache is never written and stale rows are
+// never read), transposes V and writes an image (32 KB at head_dim 128) that is byte
 // for byte what the attention kernels want in LDS.  The fast kernel's tile loop then stages a tile with direct-to-LDS
 // copies: no lookups, no pointer selects, no permutes, no address arithmetic, no staging registers.
 //
@@ -52,39 +61,49 @@ namespace {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 
 constexpr int KT = 64;           // keys per tile
 constexpr float NEG_BIG = -1.0e30f;
 
-// Tile image = [K image][V^T image] (17 and 18 KB at head_dim 128, 9 KB each at 64), padded so that 16-byte operand reads (one
-// lane per row, 16 lanes per LDS pass) fall into 16 distinct bank groups and every fragment address is base + constant:
-//   K image:   64 rows (keys) of 2 D bytes of data + 16 B pad, rounded up to whole KB;
-//   V^T image: D rows (dims) of 144 B (64 key slots = 128 B of data + 16 B pad), slot order see key_slot.
-constexpr int V_ROW = 144;
+// Tile image = [K image][V^T image], 16 KB each at head_dim 128, 8 KB at 64.  Both are stored as the matrix operands read them: in
+// planes of 16 bytes per row,
+//   K image:   plane = 16-byte vector (8 dims) of the head row, row = key;
+//   V^T image: plane = eight key slots (slot order see key_slot), row = dim.
+// A fragment (lane = row x, quarter kg) is 16 bytes of plane 4 ks + kg (K) or 4 half + kg (V^T).  Planes are multiples of 256 bytes: any
+// 16 lanes that the LDS serves together hold 16 different rows mod 16, so 16 different 16-byte bank groups, whichever quarters they are.
+// Every fragment address is base + constant.
 template <int D>
 struct Img {
-    static constexpr int K_ROW = 2 * D + 16;
-    static constexpr int K_BYTES = (KT * K_ROW + 1023) / 1024 * 1024;
-    static constexpr int V_BYTES = D * V_ROW;
+    static constexpr int K_PLANE = KT * 16, V_PLANE = D * 16;
+    static constexpr int BLOCK = 16 * 16;                             // from one block of 16 rows to the next
+    static constexpr int K_BYTES = D / 8 * K_PLANE, V_BYTES = KT / 8 * V_PLANE;
     static constexpr int BYTES = K_BYTES + V_BYTES;
-    static constexpr int NK = D / 16;        // matrix steps of a 32-key half's logits, and of its share of the output
-    static constexpr int MD = D / 32;        // 32-dim blocks of the output
+    static constexpr int NK = D / 32;        // matrix steps over the dims of a logit
+    static constexpr int MD = D / 16;        // 16-dim blocks of the output
     static constexpr int O_PITCH = D + 8;    // bf16 elements per output row in the epilogue's LDS staging
     static constexpr size_t EPILOGUE_LDS = 4 * 64 * O_PITCH * sizeof(__bf16);   // four waves x [64 columns][d] bf16
-    static_assert(V_BYTES % 1024 == 0 && BYTES % 1024 == 0, "image layout");
+    static_assert(K_BYTES == V_BYTES && K_BYTES % (8 * 1024) == 0, "the fast kernel's copies");
 };
-// Inside every block of 16 keys the order is [0-3, 8-11, 4-7, 12-15]: the order in which the accumulator
+// Inside every block of 32 keys the order is [0-3, 16-19, 4-7, 20-23, 8-11, 24-27, 12-15, 28-31]: the order in which the accumulator
 // layout of S^T hands the keys to the second product.  Slot of key t (0..63) of a tile:
-__device__ __forceinline__ int key_slot(int t) { return 16 * (t >> 4) + 4 * ((0x3120 >> (4 * ((t >> 2) & 3))) & 3) + (t & 3); }
+__device__ __forceinline__ int key_slot(int t) { return (t & 32) + 8 * ((t >> 2) & 3) + 4 * ((t >> 4) & 1) + (t & 3); }
+constexpr int NC = 4;            // blocks of 16 query columns per wave
 
-// The fast kernel keeps separate rings of three K images and three V^T images (see its tile loop).
-template <int D>
-struct __attribute__((aligned(16))) Rings {
+// LDS of the fast kernel: rings of K and V^T images (see its tile loop) and the part of the query fragments that does not stay in
+// registers, as [row group][column block][matrix step][lane]: both waves of a row group read the same 16 bytes per lane.
+template <int D, bool SPLIT>
+struct __attribute__((aligned(16))) FastLds {
+    static constexpr int NK = Img<D>::NK;
+    static constexpr int QR = D == 64 ? NK : SPLIT ? 1 : 3;   // matrix steps whose query fragments stay in registers
+    static constexpr int QL = NK - QR;                        // and those that come from LDS
     unsigned char k[3][Img<D>::K_BYTES];
     unsigned char vt[3][Img<D>::V_BYTES];
+    unsigned char q[QL > 0 ? 4 * QL * NC * 1024 : 16];
+    int pos[4][64];                                           // positions of the row groups' columns (masked tiles)
 };
 
 __device__ __forceinline__ uint32_t perm_lo(uint32_t a, uint32_t b) {  // (a.lo16, b.lo16) -> a in low half
@@ -94,14 +113,14 @@ __device__ __forceinline__ uint32_t perm_hi(uint32_t a, uint32_t b) {  // (a.hi1
     return __builtin_amdgcn_perm(b, a, 0x07060302u);
 }
 
-// ---- what a lane knows about its workgroup, wave and two query columns ---------------------------
+// ---- what a lane knows about its workgroup, wave and four query columns ---------------------------
 // G: query heads per KV head; 0 = known at run time only (group sizes without an instance of their own).
 template <int G>
 struct Geometry {
     int heads, trw;                      // query heads per KV head, token rows per wave
     int g, tile, row0;
-    int x, h, wave;
-    int col_row[2], col_head[2], col_pos[2];
+    int x, kg, wave;                     // column inside a block, quarter of the keys (of the dims), row group
+    int col_row[NC], col_head[NC], col_pos[NC];
     int wp_max;    // no key beyond it is visible to any row of this wave
     int n_kt;      // key tiles the workgroup walks
     int n_plain;   // leading tiles whose keys are visible to every row of the workgroup
@@ -112,20 +131,22 @@ struct Geometry {
         init_rows(Hq, Hkv, n_row_tiles, g_, ordinal);
         init_positions(q_index, R, n_img_tiles);
     }
-    // The part that does not read the Q index: which rows and heads the lane's two columns are.
+    // The part that does not read the Q index: which rows and heads the lane's columns are.
     __device__ __forceinline__ void init_rows(int Hq, int Hkv, int n_row_tiles, int g_, int ordinal) {
-        const int tid = threadIdx.x, lane = tid & 63;
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));   // (opaque: what is formed from it again later need not be kept meanwhile)
+        const int lane = tid & 63;
         heads = G > 0 ? G : Hq / Hkv;
         trw = G > 0 ? 64 / (G > 0 ? G : 1) : 64 / heads;
-        wave = tid >> 6;
-        x = lane & 31;
-        h = lane >> 5;
+        wave = (tid >> 6) & 3;                               // (the fast kernel has two waves per row group)
+        x = lane & 15;
+        kg = lane >> 4;
         g = g_;
         tile = n_row_tiles - 1 - ordinal;                   // longest tiles first
         row0 = tile * 4 * trw;
 #pragma unroll
-        for (int nb = 0; nb < 2; ++nb) {
-            const int col = 32 * nb + x;
+        for (int nb = 0; nb < NC; ++nb) {
+            const int col = 16 * nb + x;
             const int head = min(col / trw, heads - 1);      // columns past trw x heads compute a copy of an earlier one
             const int r = row0 + wave * trw + (col % trw);
             col_row[nb] = r;                                 // rows past the end compute a copy of the last
@@ -136,12 +157,12 @@ struct Geometry {
     // (a position beyond the prompt breaks the caller's contract; the walk then ends with the last image that exists)
     __device__ __forceinline__ void init_positions(const int32_t* __restrict__ q_index, int R, int n_img_tiles) {
 #pragma unroll
-        for (int nb = 0; nb < 2; ++nb) col_pos[nb] = q_index[min(col_row[nb], R - 1)];
+        for (int nb = 0; nb < NC; ++nb) col_pos[nb] = q_index[min(col_row[nb], R - 1)];
         const int p_first = q_index[row0];                   // rows ascend: every key <= p_first is visible to all
         const int p_max = q_index[min(R, row0 + 4 * trw) - 1];    // the workgroup's furthest key
         wp_max = q_index[min(row0 + wave * trw + trw, R) - 1];   // a wave past the end copies the last row
-        n_kt = min(p_max / KT + 1, n_img_tiles);
-        n_plain = min((p_first + 1) / KT, n_kt - 1);
+        n_kt = __builtin_amdgcn_readfirstlane(min(p_max / KT + 1, n_img_tiles));
+        n_plain = __builtin_amdgcn_readfirstlane(min((p_first + 1) / KT, n_kt - 1));
     }
 };
 
@@ -177,7 +198,7 @@ __device__ __forceinline__ void tile_fresh_rows(const int32_t* __restrict__ q_in
     __syncthreads();
 }
 
-// ---- packing pre-pass: grid (key tiles, KV heads) ---------------------------------------------------------
+// ---- packing pre-pass: grid (key tiles x KV heads) ---------------------------------------------------------
 // A thread's share of a tile in the packing kernels: 16-byte vector `vec` of the head rows of keys key + (256 / NV) i
 // (K), and of the four consecutive keys 4 key + i (V, whose first 16 NV threads have a share).
 template <int D>
@@ -197,19 +218,16 @@ struct PackShare {
 template <int D>
 __device__ __forceinline__ void write_image(const PackShare<D>& ps, const u32x4 (&kreg)[PackShare<D>::KI],
                                             const u32x4 (&vreg)[4], unsigned char* img, unsigned char* __restrict__ dst) {
+    // Staged in LDS with the rows of a plane permuted, so that neither the writes (a key row's vectors, the dims of eight-dim
+    // groups) nor the reads (a plane's rows) meet in one bank group: row r of K plane v at r ^ (v & 15), of V^T planes at r ^ ((r >> 3) & 7).
     using I = Img<D>;
     const int tid = threadIdx.x;
 #pragma unroll
     for (int i = 0; i < PackShare<D>::KI; ++i)
-        *reinterpret_cast<u32x4*>(&img[(ps.key + (256 / PackShare<D>::NV) * i) * I::K_ROW + 16 * ps.vec]) = kreg[i];
-    {   // pads: K row tails, K image tail, V^T row tails (never read by the matrix operands; kept zero)
-        const u32x4 z = {0u, 0u, 0u, 0u};
-        if (tid < KT) *reinterpret_cast<u32x4*>(&img[tid * I::K_ROW + 2 * D]) = z;
-        if (tid < (I::K_BYTES - KT * I::K_ROW) / 16) *reinterpret_cast<u32x4*>(&img[KT * I::K_ROW + 16 * tid]) = z;
-        if (tid < D) *reinterpret_cast<u32x4*>(&img[I::K_BYTES + tid * V_ROW + 128]) = z;
-    }
+        *reinterpret_cast<u32x4*>(&img[ps.vec * I::K_PLANE + 16 * ((ps.key + (256 / PackShare<D>::NV) * i) ^ ps.vec)]) = kreg[i];
     if (ps.has_v) {
         const int slot = key_slot(4 * ps.key);   // the 4 keys of this lane occupy slots slot .. slot + 3
+        unsigned char* vt = img + I::K_BYTES + (slot >> 3) * I::V_PLANE + 2 * (slot & 7);
 #pragma unroll
         for (int c = 0; c < 4; ++c) {   // dims 8 vec + 2c and + 2c + 1: gather the 4 keys of each
             u32x2 lo, hi;
@@ -218,13 +236,17 @@ __device__ __forceinline__ void write_image(const PackShare<D>& ps, const u32x4 
             hi[0] = perm_hi(vreg[0][c], vreg[1][c]);
             hi[1] = perm_hi(vreg[2][c], vreg[3][c]);
             const int d0 = 8 * ps.vec + 2 * c, d1 = d0 + 1;
-            *reinterpret_cast<u32x2*>(&img[I::K_BYTES + d0 * V_ROW + 2 * slot]) = lo;
-            *reinterpret_cast<u32x2*>(&img[I::K_BYTES + d1 * V_ROW + 2 * slot]) = hi;
+            *reinterpret_cast<u32x2*>(vt + 16 * (d0 ^ (ps.vec & 7))) = lo;
+            *reinterpret_cast<u32x2*>(vt + 16 * (d1 ^ (ps.vec & 7))) = hi;
         }
     }
     __syncthreads();
-    for (int i = tid * 16; i < I::BYTES; i += 4096)
-        *reinterpret_cast<u32x4*>(dst + i) = *reinterpret_cast<const u32x4*>(&img[i]);
+#pragma unroll
+    for (int i = 0; i < I::BYTES / 4096; ++i) {
+        const int at = i * 4096 + tid * 16, r = at >> 4;
+        const int perm = at < I::K_BYTES ? (at / I::K_PLANE) & 15 : (r >> 3) & 7;
+        *reinterpret_cast<u32x4*>(dst + at) = *reinterpret_cast<const u32x4*>(&img[at ^ (16 * perm)]);
+    }
 }
 
 // WRITEBACK: the fresh rows are also stored at their positions of the cache (the write-back of Sec. 4.3 fused into
@@ -238,7 +260,7 @@ __global__ __launch_bounds__(256) void pack_kv_images_kernel(const __bf16* k_cac
                                                              int n_img_tiles, unsigned char* __restrict__ images) {
     __shared__ __attribute__((aligned(16))) unsigned char img[Img<D>::BYTES];
     __shared__ int32_t fresh[KT];
-    const int kt = blockIdx.x, g = blockIdx.y;
+    const int kt = blockIdx.x / Hkv, g = blockIdx.x % Hkv;   // as in the attention kernels: the workgroups of a KV head on one XCD
     const PackShare<D> ps;
     const bool have_new = k_new != nullptr;   // else the cache already holds the fresh rows
     // no row sees a position behind `last`: such keys of the tile repeat the one there (they may hold anything)
@@ -299,7 +321,7 @@ __global__ __launch_bounds__(256) void pack_kv_images_shared_kernel(const __bf16
     constexpr int D = 128;
     __shared__ __attribute__((aligned(16))) unsigned char img[Img<D>::BYTES];
     __shared__ int32_t fresh[KT];
-    const int kt = blockIdx.x, g = blockIdx.y;
+    const int kt = blockIdx.x / Hkv, g = blockIdx.x % Hkv;   // as in the attention kernels: the workgroups of a KV head on one XCD
     const PackShare<D> ps;
     const int st_vec = ps.vec, st_key = ps.key;
     const u32x4 zero = {0u, 0u, 0u, 0u};
@@ -341,30 +363,40 @@ __global__ __launch_bounds__(256) void pack_kv_images_shared_kernel(const __bf16
 }
 
 // ---- staging in the fast kernel: image -> LDS directly (global_load_lds_dwordx4: lane i of a wave deposits its
-//      16 bytes at the wave's LDS base + 16 i), no registers involved.  An image is N = 18 (9 at head_dim 64) chunks
-//      of 1 KB; wave w moves chunks w, w + 4, ...  Completion: the issuing wave's vmcnt, then a workgroup barrier. ----------
+//      16 bytes at the wave's LDS base + 16 i), no registers involved, 1 KB per wave instruction.  Completion: the issuing
+//      wave's vmcnt, then a workgroup barrier. ----------
+__device__ __forceinline__ uint32_t lds_address(const unsigned char* p) {
+    return __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) const unsigned char*)p);
+}
+// Written out rather than left to the builtin: the compiler treats a pending direct-to-LDS load as an access
+// that may complete out of order with the LDS reads, and from then on waits for *all* outstanding fragment
+// reads before every use (lgkmcnt(0)), which puts a full LDS round trip in front of the matrix pipe every few
+// fragments.  Completion is waited for explicitly anyway, so nothing is lost.  The address is the same for the whole
+// wave (scalar registers, + 16 lane): the copies cost the vector ALU nothing.
+__device__ __forceinline__ void dma_chunk(const unsigned char* src, uint32_t lds_dst, uint32_t lane_off) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(lane_off), "s"(src), "s"(lds_dst) : "memory");
+}
+typedef const bf16x8 __attribute__((address_space(3)))* lds_frag_ptr;
+constexpr int FAST_WAVES = 8;
+// A wave's share of an image: chunks w, w + 8, ... of its N.  `wave` must be wave-uniform in the compiler's eyes (readfirstlane).
 template <int N>
-__device__ __forceinline__ void dma_image(const unsigned char* src, unsigned char* lds_dst, int wave, int lane) {
-    // Written out rather than left to the builtin: the compiler treats a pending direct-to-LDS load as an access
-    // that may complete out of order with the LDS reads, and from then on waits for *all* outstanding fragment
-    // reads before every use (lgkmcnt(0)), which puts a full LDS round trip in front of the matrix pipe every few
-    // fragments.  Completion is waited for explicitly anyway (wait_dma + workgroup barrier), so nothing is lost.
-    // The image address is the same for the whole workgroup, so it travels in scalar registers (base + 16 lane):
-    // the copies cost the vector ALU nothing.  `wave` must be wave-uniform in the compiler's eyes (readfirstlane).
-    const uint32_t lds_base = __builtin_amdgcn_readfirstlane(
-        (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds_dst);
-    const uint32_t lane_off = (uint32_t)lane * 16u;
+__device__ __forceinline__ void dma_image(const unsigned char* src, uint32_t lds_dst, int wave, uint32_t lane_off) {
+    static_assert(N % FAST_WAVES == 0, "the same for every wave");
 #pragma unroll
-    for (int c = 0; c < (N + 3) / 4; ++c) {
-        const int chunk = wave + 4 * c;
-        if (4 * c + 3 < N || wave < N - 4 * c) {
-            const unsigned char* g = src + chunk * 1024;
-            const uint32_t l = lds_base + (uint32_t)chunk * 1024u;
-            asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(lane_off), "s"(g), "s"(l) : "memory");
-        }
-    }
+    for (int c = 0; c < N / FAST_WAVES; ++c)
+        dma_chunk(src + (wave + FAST_WAVES * c) * 1024, lds_dst + (uint32_t)(wave + FAST_WAVES * c) * 1024u, lane_off);
 }
 __device__ __forceinline__ void wait_dma() { __builtin_amdgcn_s_waitcnt(0x0f70); }   // vmcnt(0)
+template <int N>
+__device__ __forceinline__ void wait_dma_but() {   // until all but the wave's last N copies have landed
+    static_assert(N < 16, "one field of the counter");
+    __builtin_amdgcn_s_waitcnt(0x0f70 | N);
+}
+__device__ __forceinline__ void plain_barrier() {   // without the fences of __syncthreads(): the waits are explicit
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
 
 // ---- staging in the safe kernel: image -> registers -> LDS, 16 bytes per lane and copy -------------------
 template <int D>
@@ -391,72 +423,91 @@ struct ImageStager {
     }
 };
 
-// Per-lane byte offsets of the operand fragments inside an image: row x, 16-byte half h.
+// Per-lane byte offsets of the operand fragments inside an image: row x, 16-byte quarter kg.
 template <int D>
 struct FragOffsets {
-    int k;   // K fragment: + 32 ks (16 dims per step) + 32 * Img<D>::K_ROW for the second half of the tile
-    int v;   // V^T fragment: + 32 kb (16 key slots per block) + 32 * V_ROW * md for dim block md
-    __device__ __forceinline__ void init(int x, int h) {
-        k = x * Img<D>::K_ROW + 16 * h;
-        v = x * V_ROW + 16 * h;
+    int k;   // K fragment: + 4 planes per step of 32 dims + Img<D>::BLOCK per block of 16 keys
+    int v;   // V^T fragment: + 4 planes for the second half of the key slots + Img<D>::BLOCK per block of 16 dims
+    __device__ __forceinline__ void init(int x, int kg) {
+        k = kg * Img<D>::K_PLANE + 16 * x;
+        v = kg * Img<D>::V_PLANE + 16 * x;
     }
 };
+__device__ __forceinline__ f32x4 mfma(const bf16x8& a, const bf16x8& b, const f32x4& c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+// Sum and maximum over the four lanes that hold the same column (lanes x, x + 16, x + 32, x + 48).
+__device__ __forceinline__ float column_sum(float v) {
+    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float column_max(float v) {
+    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
 
-// The weights of 32 keys x 64 columns as operands of the second product.  SPLIT: every weight as the sum of three bf16
-// numbers, each the rounding of what the ones before leave (8 bits each, the differences are exact): all 24 bits of an fp32 weight, for
+// The weights of 32 keys x 64 columns as operands of the second product: weight (b, v) of a column is that of key 16 b + 4 kg + v.
+// SPLIT: every weight as the sum of three bf16
+// numbers, each the leading 8 bits of what the ones before leave: together exactly the 24 bits of an fp32 weight, for
 // the shapes whose weights have always been kept in fp32; the second product then takes three instructions per fragment.
-// (Error of the output beyond its own rounding, 17k tokens: two numbers 2.0e-6, three 0.4e-6, the vector ALU's fp32 0.2e-6.  Two
-// take 0.62 ms for the tile loop of 28 / 4 heads and 2970 rows, three 0.80.)
+// (Cut off rather than rounded: a pair of leading parts is then one byte permute of the two weights.)
 template <bool SPLIT>
 struct Weights {
     static constexpr int PARTS = SPLIT ? 3 : 1;
-    bf16x8 part[PARTS][2][2];
-    __device__ __forceinline__ void set(int nb, int v, float p) {
+    u32x4 part[PARTS][NC];
+    __device__ __forceinline__ void set_pair(int nb, int b, int v, float p0, float p1) {   // weights (b, v) and (b, v + 1); v is 0 or 2
+        const int at = 2 * b + v / 2;
+        if constexpr (SPLIT) {
 #pragma unroll
-        for (int i = 0; i < PARTS; ++i) {
-            const __bf16 t = (__bf16)p;
-            part[i][nb][v >> 3][v & 7] = t;
-            p -= (float)t;
+            for (int i = 0; i < PARTS; ++i) {
+                part[i][nb][at] = __builtin_amdgcn_perm(__float_as_uint(p1), __float_as_uint(p0), 0x07060302u);   // the upper halves
+                if (i + 1 < PARTS) {
+                    p0 -= __uint_as_float(__float_as_uint(p0) & 0xFFFF0000u);
+                    p1 -= __uint_as_float(__float_as_uint(p1) & 0xFFFF0000u);
+                }
+            }
+        } else {
+            bf16x2 t;
+            t[0] = (__bf16)p0;
+            t[1] = (__bf16)p1;
+            part[0][nb][at] = __builtin_bit_cast(uint32_t, t);
         }
     }
-    __device__ __forceinline__ void clear() {
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) set(nb, v, 0.f);
-    }
-    __device__ __forceinline__ void multiply(const bf16x8& a, int nb, int kk, f32x16& acc) const {
-#pragma unroll
-        for (int i = 0; i < PARTS; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, part[i][nb][kk], acc, 0, 0, 0);
-    }
+    __device__ __forceinline__ bf16x8 operand(int i, int nb) const { return __builtin_bit_cast(bf16x8, part[i][nb]); }
 };
 
-// S^T for 32 keys (half mb of a staged tile) against this wave's 64 query columns.
+// S^T for 32 keys (half mb of a staged tile) against this wave's 64 query columns: s[b][nb][v] is key 16 b + 4 kg + v.
 template <int D>
-__device__ __forceinline__ void qk_half(const unsigned char* k, int mb, const bf16x8 (&qf)[2][D / 16], const FragOffsets<D>& fo,
-                                        f32x16 (&s)[2]) {
+__device__ __forceinline__ void qk_half(const unsigned char* k, int mb, const bf16x8 (&qf)[NC][D / 32], const FragOffsets<D>& fo,
+                                        f32x4 (&s)[2][NC]) {
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb)
+    for (int b = 0; b < 2; ++b)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) s[nb][v] = 0.f;
+        for (int nb = 0; nb < NC; ++nb) s[b][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int ks = 0; ks < D / 16; ++ks) {
-        const bf16x8 a = *reinterpret_cast<const bf16x8*>(k + fo.k + 32 * ks + mb * (32 * Img<D>::K_ROW));
+    for (int ks = 0; ks < D / 32; ++ks)
 #pragma unroll
-        for (int nb = 0; nb < 2; ++nb) s[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[nb][ks], s[nb], 0, 0, 0);
-    }
+        for (int b = 0; b < 2; ++b) {
+            const bf16x8 a = *reinterpret_cast<const bf16x8*>(k + fo.k + 4 * ks * Img<D>::K_PLANE + (2 * mb + b) * Img<D>::BLOCK);
+#pragma unroll
+            for (int nb = 0; nb < NC; ++nb) s[b][nb] = mfma(a, qf[nb][ks], s[b][nb]);
+        }
 }
 
-template <bool MASK>
-__device__ __forceinline__ void mask_half(f32x16 (&s)[2], const int (&col_pos)[2], int key_base, int h) {
-    if (!MASK) return;
+__device__ __forceinline__ void mask_half(f32x4 (&s)[2][NC], const int (&col_pos)[NC], int key_base, int kg) {
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb)
+    for (int nb = 0; nb < NC; ++nb) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int key = key_base + 8 * (v >> 2) + 4 * h + (v & 3);
-            if (key > col_pos[nb]) s[nb][v] = -INFINITY;
-        }
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                if (key_base + 16 * b + 4 * kg + v > col_pos[nb]) s[b][nb][v] = -INFINITY;
+        __builtin_amdgcn_sched_barrier(0);   // (block by block: the results of all comparisons at once take scalar registers that the loop needs)
+    }
 }
 
 // The two bf16 numbers of a word, 0 in the place of one that is not finite.
@@ -466,25 +517,23 @@ __device__ __forceinline__ uint32_t finite_or_zero(uint32_t w) {
     return w;
 }
 
-// O^T += V^T P^T for the 32 keys of half mb.  FINITE_ONLY: without the values that are not finite.
+// O^T += V^T P^T for the 32 keys of half mb: o[md][nb][v] is dim 16 md + 4 kg + v.  FINITE_ONLY: without the values that are not finite.
 template <int D, bool SPLIT, bool FINITE_ONLY = false>
 __device__ __forceinline__ void pv_half(const unsigned char* vt, int mb, const Weights<SPLIT>& pf, const FragOffsets<D>& fo,
-                                        f32x16 (&o)[D / 32][2]) {
+                                        f32x4 (&o)[D / 16][NC]) {
 #pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
-        const int kb = 2 * mb + kk;
+    for (int md = 0; md < D / 16; ++md) {
+        bf16x8 a = *reinterpret_cast<const bf16x8*>(vt + fo.v + 4 * mb * Img<D>::V_PLANE + md * Img<D>::BLOCK);
+        if constexpr (FINITE_ONLY) {
+            u32x4 bits = __builtin_bit_cast(u32x4, a);
 #pragma unroll
-        for (int md = 0; md < D / 32; ++md) {
-            bf16x8 a = *reinterpret_cast<const bf16x8*>(vt + fo.v + 32 * kb + md * (32 * V_ROW));
-            if constexpr (FINITE_ONLY) {
-                u32x4 bits = __builtin_bit_cast(u32x4, a);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) bits[e] = finite_or_zero(bits[e]);
-                a = __builtin_bit_cast(bf16x8, bits);
-            }
-#pragma unroll
-            for (int nb = 0; nb < 2; ++nb) pf.multiply(a, nb, kk, o[md][nb]);
+            for (int e = 0; e < 4; ++e) bits[e] = finite_or_zero(bits[e]);
+            a = __builtin_bit_cast(bf16x8, bits);
         }
+#pragma unroll
+        for (int i = 0; i < Weights<SPLIT>::PARTS; ++i)
+#pragma unroll
+            for (int nb = 0; nb < NC; ++nb) o[md][nb] = mfma(a, pf.operand(i, nb), o[md][nb]);
     }
 }
 
@@ -501,133 +550,54 @@ __device__ __forceinline__ bool holds_not_finite(const unsigned char* vt) {
 }
 // O^T += those values, for the columns that see them.  Their weights are positive: an infinity stays what it is, a NaN too.
 template <int D>
-__device__ __forceinline__ void add_not_finite(const unsigned char* vt, int key_base, const int (&col_pos)[2], int h,
-                                               f32x16 (&o)[D / 32][2]) {
+__device__ __forceinline__ void add_not_finite(const unsigned char* vt, int key_base, const int (&col_pos)[NC], int kg,
+                                               f32x4 (&o)[D / 16][NC]) {
     for (int t = 0; t < KT; ++t) {
-        const unsigned char* key = vt + 2 * key_slot(t) + 4 * h * V_ROW;
+        const int slot = key_slot(t);
+        const unsigned char* key = vt + (slot >> 3) * Img<D>::V_PLANE + 2 * (slot & 7);
 #pragma unroll
-        for (int md = 0; md < D / 32; ++md)
+        for (int md = 0; md < D / 16; ++md)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const uint32_t w = *reinterpret_cast<const uint16_t*>(key + (32 * md + 8 * (v >> 2) + (v & 3)) * V_ROW);
+            for (int v = 0; v < 4; ++v) {
+                const uint32_t w = *reinterpret_cast<const uint16_t*>(key + 16 * (16 * md + 4 * kg + v));
                 if ((w & 0x7F80u) != 0x7F80u) continue;
 #pragma unroll
-                for (int nb = 0; nb < 2; ++nb)
+                for (int nb = 0; nb < NC; ++nb)
                     if (key_base + t <= col_pos[nb]) o[md][nb][v] += __uint_as_float(w << 16);
             }
     }
 }
 
-// One step of the fast kernel's software pipeline, at the granularity of 32 keys ("a half").  It turns the
-// logits of half j (s_cur) into bf16 weights (pf_cur), while the matrix cores form the logits of half j+1
-// (s_nxt = K Q^T, 16 instructions at head_dim 128) and add half j-1 to the output (O^T += V^T P^T with pf_prev, 16
-// instructions, 48 with split weights).  The three strands are independent, so the vector ALU's exp work runs in the shadow of the
-// matrix instructions.  The exponent reference is fixed per column: no maximum, no rescale, no branch.
-template <int D, bool SPLIT, bool MASK, bool DO_QK>
-__device__ __forceinline__ void pipeline_step(const unsigned char* k_next, int mb_next, const unsigned char* vt_prev,
-                                              int mb_prev, const FragOffsets<D>& fo, const bf16x8 (&qf)[2][D / 16],
-                                              f32x16 (&s_cur)[2], f32x16 (&s_nxt)[2], const Weights<SPLIT>& pf_prev,
-                                              Weights<SPLIT>& pf_cur, f32x16 (&o)[D / 32][2],
-                                              float (&lsum)[2], const float (&mref)[2], const int (&col_pos)[2],
-                                              int key_base, int h, float scale_log2e) {
-    mask_half<MASK>(s_cur, col_pos, key_base, h);
-    if (DO_QK) {
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) s_nxt[nb][v] = 0.f;
-    }
-    // Operand fragments are requested from LDS PF matrix steps before their use (rotating register buffer), so the
-    // LDS latency overlaps the matrix and vector work already in flight.
-    constexpr int PF = 4;
-    constexpr int NK = Img<D>::NK, MD = Img<D>::MD;   // steps 0 .. NK - 1: logits, NK .. 2 NK - 1: output
-    bf16x8 fr[PF + 1];
-    auto frag = [&](int i) -> bf16x8 {   // i < NK: K fragment ks = i of the next half;  else: V fragment (kk, md)
-        if (i < NK) return *reinterpret_cast<const bf16x8*>(k_next + fo.k + 32 * i + mb_next * (32 * Img<D>::K_ROW));
-        const int j = i - NK, kk = j / MD, md = j % MD;
-        return *reinterpret_cast<const bf16x8*>(vt_prev + fo.v + 32 * (2 * mb_prev + kk) + md * (32 * V_ROW));
-    };
-    constexpr int first = DO_QK ? 0 : NK;
-#pragma unroll
-    for (int i = 0; i < PF; ++i) fr[i] = frag(first + i);
-    float psum0 = 0.f, psum1 = 0.f;
-    constexpr int EW = 16 / NK;   // weights per matrix step: column block 0 during the logits, block 1 during the output
-#pragma unroll
-    for (int i = first; i < 2 * NK; ++i) {
-        if (i + PF < 2 * NK) fr[(i - first + PF) % (PF + 1)] = frag(i + PF);
-        const bf16x8 a = fr[(i - first) % (PF + 1)];
-        if (i < NK) {
-#pragma unroll
-            for (int nb = 0; nb < 2; ++nb) s_nxt[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[nb][i], s_nxt[nb], 0, 0, 0);
-        } else {
-            const int j = i - NK, kk = j / MD, md = j % MD;
-#pragma unroll
-            for (int nb = 0; nb < 2; ++nb) pf_prev.multiply(a, nb, kk, o[md][nb]);
-        }
-        if (DO_QK || i >= NK) {
-            const int nb = (i < NK) ? 0 : 1;
-#pragma unroll
-            for (int e = 0; e < EW; ++e) {
-                const int v = EW * (i % NK) + e;
-                const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s_cur[nb][v], scale_log2e, -mref[nb]));
-                if (nb == 0) psum0 += p; else psum1 += p;
-                pf_cur.set(nb, v, p);
-            }
-        }
-    }
-    if (!DO_QK) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s_cur[0][v], scale_log2e, -mref[0]));
-            psum0 += p;
-            pf_cur.set(0, v, p);
-        }
-    }
-    lsum[0] += psum0;
-    lsum[1] += psum1;
-    // Ask the scheduler for: every fragment read PF matrix steps ahead of its use, and matrix and transcendental
-    // instructions (the two long-latency strands) alternating.  Measured: several per cent over its own order;
-    // patterns that also place the remaining vector work lose.
-    __builtin_amdgcn_sched_group_barrier(0x100, PF, 0);       // the first PF fragment reads
-#pragma unroll
-    for (int i = first; i < 2 * NK; ++i) {
-        if (i + PF < 2 * NK) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // fragment i + PF
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            if (SPLIT && i >= NK) __builtin_amdgcn_sched_group_barrier(0x008, Weights<SPLIT>::PARTS, 0); else __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // matrix
-            __builtin_amdgcn_sched_group_barrier(0x400, EW / 2, 0);   // transcendental
-        }
-    }
-}
-
-// Normalise, transpose through LDS and store 16 bytes per lane; lse = (m + log2 l) ln 2.
-template <int G, int D>
-__device__ __forceinline__ void store_output(const Geometry<G>& ge, f32x16 (&o)[D / 32][2], const float (&l)[2],
-                                             const float (&mref)[2], int R, int Hq, unsigned char* smem,
-                                             __bf16* __restrict__ out, float* __restrict__ lse_out) {
-    constexpr int O_PITCH = Img<D>::O_PITCH, NV = D / 8;
+// Normalise, transpose through LDS and store 16 bytes per lane; lse = (m + log2 l) ln 2.  A wave brings M of its columns' 16-dim
+// blocks, from block md0 on: all of them, or half of them beside another wave of its rows (then each stores half of the columns).
+template <int G, int D, int M>
+__device__ __forceinline__ void store_output(const Geometry<G>& ge, const f32x4 (&o)[M][NC], int md0, const float (&l)[NC],
+                                             const float (&mref)[NC], int R, int Hq, unsigned char* smem,
+                                             __bf16* __restrict__ out, float* __restrict__ lse_out, bool active = true) {
+    constexpr int O_PITCH = Img<D>::O_PITCH, NV = D / 8, MD = Img<D>::MD;
     __bf16* ob = reinterpret_cast<__bf16*>(smem) + ge.wave * 64 * O_PITCH;   // this wave's [64 columns][d]
     const int lane = threadIdx.x & 63;
+    if (active) {
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
-        const float inv_l = 1.0f / l[nb];
+        for (int nb = 0; nb < NC; ++nb) {
+            const float inv_l = 1.0f / l[nb];
 #pragma unroll
-        for (int md = 0; md < D / 32; ++md)
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
+            for (int md = 0; md < M; ++md) {
                 bf16x4 w;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) w[e] = (__bf16)(o[md][nb][4 * q4 + e] * inv_l);
-                *reinterpret_cast<bf16x4*>(&ob[(32 * nb + ge.x) * O_PITCH + 32 * md + 8 * q4 + 4 * ge.h]) = w;
+                for (int e = 0; e < 4; ++e) w[e] = (__bf16)(o[md][nb][e] * inv_l);
+                *reinterpret_cast<bf16x4*>(&ob[(16 * nb + ge.x) * O_PITCH + 16 * (md0 + md) + 4 * ge.kg]) = w;
             }
-        if (lse_out != nullptr && ge.h == 0 && ge.col_row[nb] < R && 32 * nb + ge.x < ge.trw * ge.heads)
-            lse_out[(size_t)ge.col_row[nb] * Hq + ge.col_head[nb]] =
-                (mref[nb] + __builtin_amdgcn_logf(l[nb])) * 0.6931471805599453f;
+            if (md0 == 0 && lse_out != nullptr && ge.kg == 0 && ge.col_row[nb] < R && 16 * nb + ge.x < ge.trw * ge.heads)
+                lse_out[(size_t)ge.col_row[nb] * Hq + ge.col_head[nb]] =
+                    (mref[nb] + __builtin_amdgcn_logf(l[nb])) * 0.6931471805599453f;
+        }
     }
-    __syncthreads();   // (each wave reads back only its own region; the barrier orders its LDS writes and reads)
+    __syncthreads();   // (the barrier orders the LDS writes and reads of the waves of a row group)
+    if (!active) return;
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        const int col = (64 / NV) * i + lane / NV, vec = lane % NV;
+    for (int i = 0; i < NV * M / MD; ++i) {
+        const int col = (64 / NV) * (i + (md0 > 0 ? NV * M / MD : 0)) + lane / NV, vec = lane % NV;
         const int r = ge.row0 + ge.wave * ge.trw + (col % ge.trw), head = col / ge.trw;
         if (r < R && head < ge.heads) {
             const u32x4 w = *reinterpret_cast<const u32x4*>(&ob[col * O_PITCH + 8 * vec]);
@@ -636,25 +606,25 @@ __device__ __forceinline__ void store_output(const Geometry<G>& ge, f32x16 (&o)[
     }
 }
 
-// The same for dims 32 md .. 32 md + 31 only (a workgroup of the combine pass).
+// The same for dims 32 sl .. 32 sl + 31 only (a workgroup of the combine pass).
 template <int G, int D>
-__device__ __forceinline__ void store_slice(const Geometry<G>& ge, const f32x16 (&acc)[2], int md, const float (&l)[2],
-                                            const float (&mref)[2], int R, int Hq, unsigned char* smem,
+__device__ __forceinline__ void store_slice(const Geometry<G>& ge, const f32x4 (&acc)[2][NC], int sl, const float (&l)[NC],
+                                            const float (&mref)[NC], int R, int Hq, unsigned char* smem,
                                             __bf16* __restrict__ out, float* __restrict__ lse_out) {
     constexpr int PITCH = 40;   // 32 dims + 16 bytes
     __bf16* ob = reinterpret_cast<__bf16*>(smem) + ge.wave * 64 * PITCH;
     const int lane = threadIdx.x & 63;
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
+    for (int nb = 0; nb < NC; ++nb) {
         const float inv_l = 1.0f / l[nb];
 #pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
+        for (int b = 0; b < 2; ++b) {
             bf16x4 w;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) w[e] = (__bf16)(acc[nb][4 * q4 + e] * inv_l);
-            *reinterpret_cast<bf16x4*>(&ob[(32 * nb + ge.x) * PITCH + 8 * q4 + 4 * ge.h]) = w;
+            for (int e = 0; e < 4; ++e) w[e] = (__bf16)(acc[b][nb][e] * inv_l);
+            *reinterpret_cast<bf16x4*>(&ob[(16 * nb + ge.x) * PITCH + 16 * b + 4 * ge.kg]) = w;
         }
-        if (md == 0 && lse_out != nullptr && ge.h == 0 && ge.col_row[nb] < R && 32 * nb + ge.x < ge.trw * ge.heads)
+        if (sl == 0 && lse_out != nullptr && ge.kg == 0 && ge.col_row[nb] < R && 16 * nb + ge.x < ge.trw * ge.heads)
             lse_out[(size_t)ge.col_row[nb] * Hq + ge.col_head[nb]] =
                 (mref[nb] + __builtin_amdgcn_logf(l[nb])) * 0.6931471805599453f;
     }
@@ -665,62 +635,83 @@ __device__ __forceinline__ void store_slice(const Geometry<G>& ge, const f32x16 
         const int r = ge.row0 + ge.wave * ge.trw + (col % ge.trw), head = col / ge.trw;
         if (r < R && head < ge.heads) {
             const u32x4 w = *reinterpret_cast<const u32x4*>(&ob[col * PITCH + 8 * vec]);
-            *reinterpret_cast<u32x4*>(out + ((size_t)r * Hq + ge.g * ge.heads + head) * D + 32 * md + 8 * vec) = w;
+            *reinterpret_cast<u32x4*>(out + ((size_t)r * Hq + ge.g * ge.heads + head) * D + 32 * sl + 8 * vec) = w;
         }
     }
 }
 
-// Partial result of one part of an item, per lane: its 2 x D / 2 output accumulators, the two sums, the two exponent
-// references and two scale exponents as 32-bit words.  Register-major (word r of thread t at [r * 256 + t]: every store
-// and load is one coalesced 1 KB line per wave).  Part p of item (ordinal, KV head g) lives at
+// The value of column block kg in lane (x, kg): one word per lane carries what a wave's 64 columns have once each.
+__device__ __forceinline__ float own_block(const float (&v)[NC], int kg) {
+    const float lo = (kg & 1) ? v[1] : v[0], hi = (kg & 1) ? v[3] : v[2];
+    return (kg & 2) ? hi : lo;
+}
+__device__ __forceinline__ uint32_t of_block(uint32_t word, int nb, int x) {   // and back
+    return (uint32_t)__builtin_amdgcn_ds_bpermute(4 * (16 * nb + x), (int)word);
+}
+
+// Partial result of one part of an item, per lane of a row group's wave: its D output accumulators (D / 4 of each of its four
+// columns) and one word each of its wave's column sums, exponent references and two scale exponents (own_block).  Four words of a
+// thread side by side (words 4 r .. 4 r + 3 of thread t at [4 (r * 256 + t)]: every store and load of a wave is one line of 1 KB).  Part p of item (ordinal, KV head g) lives at
 // (((query * max_row_tiles + ordinal) * n_parts + p) * Hkv + g) * WORDS.  Infinities and NaNs survive the packing (the
 // combine pass must still see an overflow).
-// F32: the accumulators as they are.  Otherwise as half-precision pairs, the 64 of a column block scaled by a power of two
-// that brings the largest of them into [0.5, 1) (11 significant bits of that column's largest value): 70 words instead of
-// 134.  Which one: half_parts.
+// F32: the accumulators as they are.  Otherwise as half-precision pairs, the D / 2 of a column in half of the dims scaled by a power of two
+// that brings the largest of them into [0.5, 1) (11 significant bits of that column's largest value): 68 words instead of
+// 132.  Which one: half_parts.
 template <int D, bool F32>
 struct Part {
-    static constexpr int O_WORDS = F32 ? D : D / 2;   // per lane, both column blocks
-    static constexpr int REGS = O_WORDS + 6;
+    static constexpr int O_WORDS = F32 ? D : D / 2;   // per lane, all column blocks
+    static constexpr int COL_WORDS = O_WORDS / NC;    // of a column block; block md of 16 dims has COL_WORDS / (D / 16) of them
+    static constexpr int SUM = O_WORDS, REFERENCE = O_WORDS + 1;
+    static constexpr int REGS = O_WORDS + 4;
     static constexpr int WORDS = REGS * 256;          // 32-bit words of a part
+    static __device__ __forceinline__ int exponent(int md) { return O_WORDS + 2 + md / (D / 32); }
+    static __device__ __forceinline__ int at(int word) { return (word >> 2) * 1024 + (word & 3); }   // place of a word, + 4 t
 };
 typedef _Float16 __attribute__((ext_vector_type(2))) f16x2;
 
+// The half of a row group's dims that a wave holds: blocks md0 .. md0 + D / 32 - 1.
 template <int D, bool F32>
-__device__ __forceinline__ void store_partial(float* __restrict__ dst_f, const f32x16 (&o)[D / 32][2], const float (&lsum)[2],
-                                              const float (&mref)[2]) {
-    constexpr int OW = Part<D, F32>::O_WORDS;
+__device__ __forceinline__ void store_partial(float* __restrict__ dst_f, const f32x4 (&o)[D / 32][NC], int md0, const float (&lsum)[NC],
+                                              const float (&mref)[NC], int kg) {
+    using P = Part<D, F32>;
     uint32_t* dst = reinterpret_cast<uint32_t*>(dst_f);
+    float sum[NC], e[NC];
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
-        int e = 0;
+    for (int nb = 0; nb < NC; ++nb) {
+        sum[nb] = column_sum(lsum[nb]);
         if constexpr (F32) {
 #pragma unroll
             for (int md = 0; md < D / 32; ++md)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) dst[(nb * (OW / 2) + md * 16 + v) * 256] = __float_as_uint(o[md][nb][v]);
+                *reinterpret_cast<f32x4*>(dst + P::at(nb * P::COL_WORDS + (md0 + md) * 4)) = o[md][nb];
         } else {
             float m = 0.f;
 #pragma unroll
             for (int md = 0; md < D / 32; ++md)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) m = fmaxf(m, fabsf(o[md][nb][v]));
+                for (int v = 0; v < 4; ++v) m = fmaxf(m, fabsf(o[md][nb][v]));
+            m = column_max(m);
             // m = f 2^e with f in [0.5, 1); an infinite m keeps e = 0: the infinity is stored as it is
-            e = (m < INFINITY) ? __builtin_amdgcn_frexp_expf(m) : 0;
+            const int ex = (m < INFINITY) ? __builtin_amdgcn_frexp_expf(m) : 0;
+            e[nb] = __uint_as_float((uint32_t)ex);
 #pragma unroll
-            for (int md = 0; md < D / 32; ++md)
+            for (int md = 0; md < D / 32; md += 2) {
+                u32x4 w;
 #pragma unroll
-                for (int v = 0; v < 16; v += 2) {
+                for (int j = 0; j < 4; ++j) {
                     f16x2 h;
-                    h[0] = (_Float16)__builtin_ldexpf(o[md][nb][v], -e);
-                    h[1] = (_Float16)__builtin_ldexpf(o[md][nb][v + 1], -e);
-                    dst[(nb * (OW / 2) + md * 8 + v / 2) * 256] = __builtin_bit_cast(uint32_t, h);
+                    h[0] = (_Float16)__builtin_ldexpf(o[md + (j >> 1)][nb][2 * (j & 1)], -ex);
+                    h[1] = (_Float16)__builtin_ldexpf(o[md + (j >> 1)][nb][2 * (j & 1) + 1], -ex);
+                    w[j] = __builtin_bit_cast(uint32_t, h);
                 }
+                *reinterpret_cast<u32x4*>(dst + P::at(nb * P::COL_WORDS + (md0 + md) * 2)) = w;
+            }
         }
-        dst[(OW + nb) * 256] = __float_as_uint(lsum[nb]);
-        dst[(OW + 2 + nb) * 256] = __float_as_uint(mref[nb]);
-        dst[(OW + 4 + nb) * 256] = (uint32_t)e;
     }
+    if (md0 == 0) {
+        dst[P::at(P::SUM)] = __float_as_uint(own_block(sum, kg));
+        dst[P::at(P::REFERENCE)] = __float_as_uint(own_block(mref, kg));
+    }
+    if constexpr (!F32) dst[P::at(P::exponent(md0))] = __float_as_uint(own_block(e, kg));
 }
 
 // One launch serves up to ATTN_MAX_BATCH queries with their own rows, index sets, tile images and outputs (Sec. 4.3:
@@ -766,61 +757,68 @@ __device__ __forceinline__ void running_max_item(const AttnQuery& aq, int g, int
     unsigned char* v_img = smem + Img<D>::K_BYTES;
     Geometry<G> ge;
     ge.init(aq.q_index, R, Hq, Hkv, aq.n_row_tiles, n_img_tiles, g, ordinal);
-    const int h = ge.h;
+    const int kg = ge.kg;
+    const bool active = threadIdx.x < 256;   // (the other waves of the fast kernel only keep the barriers)
     FragOffsets<D> fo;
-    fo.init(ge.x, h);
-    bf16x8 qf[2][D / 16];
+    fo.init(ge.x, kg);
+    bf16x8 qf[NC][D / 32];
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
-        const __bf16* qp = q_rows + ((size_t)min(ge.col_row[nb], R - 1) * Hq + ge.col_head[nb]) * D + 8 * h;
+    for (int nb = 0; nb < NC; ++nb) {
+        const __bf16* qp = q_rows + ((size_t)min(ge.col_row[nb], R - 1) * Hq + ge.col_head[nb]) * D + 8 * kg;
 #pragma unroll
-        for (int ks = 0; ks < D / 16; ++ks) qf[nb][ks] = *reinterpret_cast<const bf16x8*>(qp + 16 * ks);
+        for (int ks = 0; ks < D / 32; ++ks) qf[nb][ks] = *reinterpret_cast<const bf16x8*>(qp + 32 * ks);
     }
-    f32x16 o[D / 32][2];
+    f32x4 o[D / 16][NC];
 #pragma unroll
-    for (int md = 0; md < D / 32; ++md)
+    for (int md = 0; md < D / 16; ++md)
 #pragma unroll
-        for (int nb = 0; nb < 2; ++nb)
+        for (int nb = 0; nb < NC; ++nb) o[md][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float lsum[NC], m2[NC];
 #pragma unroll
-            for (int v = 0; v < 16; ++v) o[md][nb][v] = 0.f;
-    float lsum[2] = {0.f, 0.f};
-    float m2[2] = {NEG_BIG, NEG_BIG};
+    for (int nb = 0; nb < NC; ++nb) {
+        lsum[nb] = 0.f;
+        m2[nb] = NEG_BIG;
+    }
     ImageStager<D> sg;
     sg.init(aq.images, ge.g, n_img_tiles);
     for (int kt = 0; kt < ge.n_kt; ++kt) {
-        sg.load(kt);
+        if (active) sg.load(kt);
         __syncthreads();
-        sg.write(k_img);
+        if (active) sg.write(k_img);
         __syncthreads();
-        if (kt * KT > ge.wp_max) continue;   // wave-uniform; the barriers stay outside
+        if (!active || kt * KT > ge.wp_max) continue;   // wave-uniform; the barriers stay outside
         const bool apart = SPLIT && kt >= ge.n_plain && holds_not_finite<D>(v_img);   // some rows may not see them
 #pragma unroll
         for (int mb = 0; mb < 2; ++mb) {
-            f32x16 s[2];
+            f32x4 s[2][NC];
             qk_half<D>(k_img, mb, qf, fo, s);
-            mask_half<true>(s, ge.col_pos, kt * KT + 32 * mb, h);
+            mask_half(s, ge.col_pos, kt * KT + 32 * mb, kg);
             Weights<SPLIT> pf;
 #pragma unroll
-            for (int nb = 0; nb < 2; ++nb) {
-                float t = s[nb][0];
+            for (int nb = 0; nb < NC; ++nb) {
+                float t = fmaxf(s[0][nb][0], s[1][nb][0]);
 #pragma unroll
-                for (int v = 1; v < 16; ++v) t = fmaxf(t, s[nb][v]);
-                t = fmaxf(t, __shfl_xor(t, 32));
+                for (int v = 1; v < 4; ++v) t = fmaxf(t, fmaxf(s[0][nb][v], s[1][nb][v]));
+                t = column_max(t);
                 const float m_new = fmaxf(m2[nb], t * scale_log2e);
                 const float alpha = __builtin_amdgcn_exp2f(m2[nb] - m_new);
                 m2[nb] = m_new;
                 float psum = 0.f;
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[nb][v], scale_log2e, -m_new));
-                    psum += p;
-                    pf.set(nb, v, p);
-                }
+                for (int b = 0; b < 2; ++b)
+#pragma unroll
+                    for (int v = 0; v < 4; v += 2) {
+                        const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[b][nb][v], scale_log2e, -m_new));
+                        const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[b][nb][v + 1], scale_log2e, -m_new));
+                        psum += p0;
+                        psum += p1;
+                        pf.set_pair(nb, b, v, p0, p1);
+                    }
                 lsum[nb] = lsum[nb] * alpha + psum;
 #pragma unroll
-                for (int md = 0; md < D / 32; ++md)
+                for (int md = 0; md < D / 16; ++md)
 #pragma unroll
-                    for (int v = 0; v < 16; ++v) o[md][nb][v] *= alpha;
+                    for (int v = 0; v < 4; ++v) o[md][nb][v] *= alpha;
             }
             if constexpr (SPLIT) {
                 if (apart) pv_half<D, SPLIT, true>(v_img, mb, pf, fo, o); else pv_half<D, SPLIT>(v_img, mb, pf, fo, o);
@@ -828,42 +826,140 @@ __device__ __forceinline__ void running_max_item(const AttnQuery& aq, int g, int
                 pv_half<D, SPLIT>(v_img, mb, pf, fo, o);
             }
         }
-        if constexpr (SPLIT) { if (apart) add_not_finite<D>(v_img, kt * KT, ge.col_pos, h, o); }
+        if constexpr (SPLIT) { if (apart) add_not_finite<D>(v_img, kt * KT, ge.col_pos, kg, o); }
     }
-    float l[2];
+    float l[NC];
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb) l[nb] = lsum[nb] + __shfl_xor(lsum[nb], 32);
+    for (int nb = 0; nb < NC; ++nb) l[nb] = column_sum(lsum[nb]);
     __syncthreads();
     if (slice < 0) {
-        store_output<G, D>(ge, o, l, m2, R, Hq, smem, aq.out, aq.lse);
+        store_output<G, D>(ge, o, 0, l, m2, R, Hq, smem, aq.out, aq.lse, active);
         return;
     }
-    f32x16 acc[2] = {o[0][0], o[0][1]};
+    f32x4 acc[2][NC];
 #pragma unroll
-    for (int md = 1; md < D / 32; ++md)
-        if (md == slice) { acc[0] = o[md][0]; acc[1] = o[md][1]; }
+    for (int sl = 0; sl < D / 32; ++sl)
+        if (sl == slice)
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int nb = 0; nb < NC; ++nb) acc[b][nb] = o[2 * sl + b][nb];
     store_slice<G, D>(ge, acc, slice, l, m2, R, Hq, smem, aq.out, aq.lse);
 }
 
-// Overflow check of a finished item: with a fixed reference a runaway logit shows up as inf / nan in the sums.
-// Returns (workgroup-uniform) whether any column of the workgroup is affected; l = the columns' softmax sums.
-template <int D>
-__device__ __forceinline__ int sums_overflowed(const f32x16 (&o)[D / 32][2], const float (&lsum)[2], float (&l)[2]) {
-    bool bad = false;
+// ---- fast path: key tiles [kb, ke) of one (row tile, KV head) ---------------------------------------------
+// Eight waves, two per SIMD.  Waves w and w + 4 own the same 64 query columns; the first takes keys 0..31 of every tile, the second
+// keys 32..63, each with output accumulators of its own, which are added up at the end.
+
+// One matrix phase of a wave: O^T += V^T P^T for its half of one tile, S^T = K Q^T for its half of another one.  `vt` and `k` are the LDS
+// addresses of the halves.  Operand fragments are
+// requested from LDS PF steps of four matrix instructions ahead of their use (rotating register buffer), those of the query a
+// step of its dims ahead; the steps whose query fragments come from LDS alternate with those that have theirs in registers.
+template <int D, bool SPLIT, bool PV>
+__device__ __forceinline__ void matrix_phase(uint32_t vt, uint32_t k, const FragOffsets<D>& fo,
+                                             const bf16x8 (&qf)[NC][FastLds<D, SPLIT>::QR > 0 ? FastLds<D, SPLIT>::QR : 1], uint32_t q_lds,
+                                             const Weights<SPLIT>& p, f32x4 (&o)[D / 16][NC], f32x4 (&s)[2][NC]) {
+    using F = FastLds<D, SPLIT>;
+    constexpr int NK = F::NK, MD = Img<D>::MD, PF = 4, QR = F::QR, QL = F::QL;
+    constexpr int FIRST = PV ? 0 : MD, STEPS = MD + 2 * NK;   // steps 0 .. MD - 1: output; then logits: (dims ks, key block b)
+    // order of the dims: LDS, registers, LDS, ...; the longer kind's surplus last
+    auto dims = [&](int j) {   // j-th step of the dims -> ks; ks < QR: registers
+        constexpr int M = QR < QL ? QR : QL;
+        if (j < 2 * M) return (j & 1) ? j / 2 : QR + j / 2;
+        return QL > QR ? QR + j - M : j - M;
+    };
+    bf16x8 fr[PF + 1], qb[2][NC];
+    // (indexed from pointers: the constants then go into the instructions' offsets)
+    const lds_frag_ptr v_frag = reinterpret_cast<lds_frag_ptr>((uintptr_t)(vt + fo.v)), k_frag = reinterpret_cast<lds_frag_ptr>((uintptr_t)(k + fo.k));
+    const lds_frag_ptr q_frag = reinterpret_cast<lds_frag_ptr>((uintptr_t)q_lds);
+    auto frag = [&](int i) -> bf16x8 {
+        if (i < MD) return v_frag[i * Img<D>::BLOCK / 16];
+        return k_frag[(4 * dims((i - MD) / 2) * Img<D>::K_PLANE + (i & 1) * Img<D>::BLOCK) / 16];
+    };
+    static_assert(MD % 2 == 0, "key block of step i is i & 1");
+    auto load_q = [&](int j) {   // query fragments of the j-th step of the dims, if they are in LDS
+        const int ks = dims(j);
+        if (ks < QR) return 0;
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
-        l[nb] = lsum[nb] + __shfl_xor(lsum[nb], 32);
-        float chk = l[nb];
+        for (int nb = 0; nb < NC; ++nb) qb[j & 1][nb] = q_frag[((ks - QR) * NC + nb) * 64];
+        return NC;
+    };
+    int reads[STEPS] = {};   // LDS reads issued in front of step i's products
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int md = 0; md < D / 32; ++md)
+    for (int i = FIRST; i < FIRST + PF; ++i) fr[i % (PF + 1)] = frag(i);
+    if (!PV) reads[FIRST] += load_q(0);
 #pragma unroll
-            for (int v = 0; v < 16; ++v) chk += fabsf(o[md][nb][v]);
-        bad = bad || !(chk < INFINITY) || !(l[nb] > 0.f);
+    for (int i = FIRST; i < STEPS; ++i) {
+        if (i + PF < STEPS) {
+            fr[(i + PF) % (PF + 1)] = frag(i + PF);
+            ++reads[i];
+        }
+        if (PV && i == MD - 2) reads[i] += load_q(0);   // two steps ahead
+        if (i >= MD && (i - MD) % 2 == 0 && (i - MD) / 2 + 1 < NK) reads[i] += load_q((i - MD) / 2 + 1);
+        const bf16x8 a = fr[i % (PF + 1)];
+        if (i < MD) {
+#pragma unroll
+            for (int u = 0; u < Weights<SPLIT>::PARTS; ++u)
+#pragma unroll
+                for (int c = 0; c < NC; ++c) {   // (back and forth: neighbours in time share an operand, which saves power)
+                    const int nb = (i * Weights<SPLIT>::PARTS + u) & 1 ? NC - 1 - c : c;
+                    o[i][nb] = mfma(a, p.operand(u, nb), o[i][nb]);
+                }
+        } else {
+            const int j = (i - MD) / 2, ks = dims(j), b = i & 1;
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                const int nb = b ? NC - 1 - c : c;
+                s[b][nb] = mfma(a, ks < QR ? qf[nb][ks < QR ? ks : 0] : qb[j & 1][nb], j == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : s[b][nb]);
+            }
+        }
     }
-    return __syncthreads_or(bad ? 1 : 0);   // also: every wave is done with the rings
+    __builtin_amdgcn_sched_group_barrier(0x100, PF, 0);
+#pragma unroll
+    for (int i = FIRST; i < STEPS; ++i) {
+        if (reads[i] == 1) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        if (reads[i] == NC) __builtin_amdgcn_sched_group_barrier(0x100, NC, 0);
+        if (reads[i] > NC + 1) __builtin_amdgcn_sched_group_barrier(0x100, 2 * NC + 1, 0);
+        if (reads[i] == NC + 1) __builtin_amdgcn_sched_group_barrier(0x100, NC + 1, 0);
+        if (i < MD) __builtin_amdgcn_sched_group_barrier(0x008, NC * Weights<SPLIT>::PARTS, 0); else __builtin_amdgcn_sched_group_barrier(0x008, NC, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
 }
 
-// ---- fast path: key tiles [kb, ke) of one (row tile, KV head) ---------------------------------------------
+// Logits -> weights: exp2(s scale - reference), their sums.
+template <bool SPLIT>
+__device__ __forceinline__ void softmax_phase(const f32x4 (&s)[2][NC], Weights<SPLIT>& p, float (&lsum)[NC], const float (&mref)[NC],
+                                              float scale_log2e) {
+#pragma unroll
+    for (int nb = 0; nb < NC; ++nb) {
+        float sum[2];
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int v = 0; v < 4; v += 2) {
+                const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[b][nb][v], scale_log2e, -mref[nb]));
+                const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[b][nb][v + 1], scale_log2e, -mref[nb]));
+                if (b == 0 && v == 0) {
+                    sum[0] = p0;
+                    sum[1] = p1;
+                } else {
+                    sum[0] += p0;
+                    sum[1] += p1;
+                }
+                p.set_pair(nb, b, v, p0, p1);
+            }
+        lsum[nb] += sum[0] + sum[1];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// Halves of the accumulators that the two waves of a row group exchange at the end, and their sums.
+template <int D>
+constexpr int EXCHANGE_WAVE = Img<D>::MD / 2 * NC * 1024 + 1024;
+template <int D>
+constexpr size_t EXCHANGE_LDS = (size_t)FAST_WAVES * EXCHANGE_WAVE<D>;
+
 // part < 0: the piece is the whole item; the workgroup finishes it: overflow check, then the output, or the item again with
 // a running maximum (in this kernel: a second one that looked for flagged items cost 4 us per call and found none).
 // part >= 0: the piece is
@@ -874,7 +970,9 @@ __device__ __forceinline__ void process_piece(const AttnQuery& aq, int g, int or
                                               float* __restrict__ partials, bool half, int Hq, int Hkv, float scale_log2e,
                                               unsigned char* smem_raw) {
     using I = Img<D>;
-    Rings<D>& rg = *reinterpret_cast<Rings<D>*>(smem_raw);
+    using F = FastLds<D, SPLIT>;
+    constexpr int MD = I::MD, CH = I::K_BYTES / 1024;      // chunks of a K image, and of a V^T image
+    F& sm = *reinterpret_cast<F*>(smem_raw);
     const __bf16* __restrict__ q_rows = aq.q_rows;
     const int R = aq.R, n_img_tiles = aq.n_img_tiles;
     // ---- prologue.  Everything that does not depend on the Q index is requested first (the query fragments, and K
@@ -882,20 +980,28 @@ __device__ __forceinline__ void process_piece(const AttnQuery& aq, int g, int or
     //      prologue overlap instead of following one another. ------------------------------------------------------
     Geometry<G> ge;
     ge.init_rows(Hq, Hkv, aq.n_row_tiles, g, ordinal);
-    const int x = ge.x, h = ge.h;
     FragOffsets<D> fo;
-    fo.init(x, h);
+    fo.init(ge.x, ge.kg);
     const unsigned char* head_images = aq.images + (size_t)ge.g * n_img_tiles * I::BYTES;
-    const int wave = __builtin_amdgcn_readfirstlane(ge.wave), lane = threadIdx.x & 63;
-    dma_image<I::K_BYTES / 1024>(head_images, rg.k[2], wave, lane);   // K image 0 into ring slot 2: the exponent reference comes from it
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int second = wave >> 2;                          // which half of every tile
+    const uint32_t lane_off = (uint32_t)lane * 16u;
+    const uint32_t k_base = lds_address(sm.k[0]), v_base = lds_address(sm.vt[0]);
+    dma_image<CH>(head_images, k_base + 2 * I::K_BYTES, wave, lane_off);   // K image 0 into ring slot 2: the exponent reference comes from it
 
-    // Q fragments: B operand of S^T = K Q^T, kept in registers for the whole loop
-    bf16x8 qf[2][D / 16];
+    // Q fragments: B operand of S^T = K Q^T, for the whole loop; the two waves of a row group bring two column blocks' each to LDS
+    bf16x8 qf[NC][F::QR > 0 ? F::QR : 1], ql[2][F::QL > 0 ? F::QL : 1];
+    const uint32_t q_lds = lds_address(sm.q) + (wave & 3) * (F::QL * NC * 1024) + lane_off;
+    auto q_row = [&](int row, int head) { return q_rows + ((size_t)min(row, R - 1) * Hq + head) * D + 8 * ge.kg; };
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
-        const __bf16* qp = q_rows + ((size_t)min(ge.col_row[nb], R - 1) * Hq + ge.col_head[nb]) * D + 8 * h;
+    for (int nb = 0; nb < NC; ++nb)
 #pragma unroll
-        for (int ks = 0; ks < D / 16; ++ks) qf[nb][ks] = *reinterpret_cast<const bf16x8*>(qp + 16 * ks);
+        for (int ks = 0; ks < F::QR; ++ks) qf[nb][ks] = *reinterpret_cast<const bf16x8*>(q_row(ge.col_row[nb], ge.col_head[nb]) + 32 * ks);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const __bf16* qp = q_row(second ? ge.col_row[2 + i] : ge.col_row[i], second ? ge.col_head[2 + i] : ge.col_head[i]);
+#pragma unroll
+        for (int ks = 0; ks < F::QL; ++ks) ql[i][ks] = *reinterpret_cast<const bf16x8*>(qp + 32 * (F::QR + ks));
     }
     ge.init_positions(aq.q_index, R, n_img_tiles);
     const int n_kt = ge.n_kt;
@@ -903,102 +1009,170 @@ __device__ __forceinline__ void process_piece(const AttnQuery& aq, int g, int or
     const int per_part = part < 0 ? n_kt : (n_kt + n_parts - 1) / n_parts;
     const int kb = part < 0 ? 0 : part * per_part, ke = min(n_kt, kb + per_part);
     const int part_words = half ? Part<D, false>::WORDS : Part<D, true>::WORDS;
-    float* part_dst = part < 0 ? nullptr : partials + (((size_t)item * n_parts + part) * Hkv + g) * part_words + threadIdx.x;
+    float* part_dst = part < 0 ? nullptr : partials + (((size_t)item * n_parts + part) * Hkv + g) * part_words;
     if (kb >= ke) {   // fewer key tiles than parts: this one adds nothing
-        for (int r = 0; r < part_words; r += 256) part_dst[r] = 0.f;
+        for (int r = threadIdx.x; r < part_words; r += 64 * FAST_WAVES) part_dst[r] = 0.f;
         return;       // (the hardware waits for the outstanding copy before it retires the wave)
     }
-    f32x16 o[D / 32][2];
-#pragma unroll
-    for (int md = 0; md < D / 32; ++md)
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) o[md][nb][v] = 0.f;
-    float lsum[2] = {0.f, 0.f};
 
-    // K images kb and kb + 1 and V image kb land in LDS
-    const unsigned char* first_image = head_images + (size_t)kb * I::BYTES;
-    dma_image<I::K_BYTES / 1024>(first_image, rg.k[0], wave, lane);
-    dma_image<I::V_BYTES / 1024>(first_image + I::K_BYTES, rg.vt[0], wave, lane);
-    if (kb + 1 < n_kt) dma_image<I::K_BYTES / 1024>(first_image + I::BYTES, rg.k[1], wave, lane);
-    {   // V ring slot 2 is read (against all-zero weights) by the very first step: it must hold finite numbers
-        const u32x4 z = {0u, 0u, 0u, 0u};
-        for (int i = threadIdx.x; i < I::V_BYTES / 16; i += 256) *reinterpret_cast<u32x4*>(&rg.vt[2][16 * i]) = z;
+    // K images kb and kb + 1 and V image kb land in LDS.  (Past the piece's last tile the copies repeat that one, here and in
+    // the loop: the counts of the waits stay the same, and nobody reads them.)
+    auto tile_image = [&](int kt) { return head_images + (size_t)min(kt, ke - 1) * I::BYTES; };
+    dma_image<CH>(tile_image(kb), k_base, wave, lane_off);
+    dma_image<CH>(tile_image(kb) + I::K_BYTES, v_base, wave, lane_off);
+    dma_image<CH>(tile_image(kb + 1), k_base + I::K_BYTES, wave, lane_off);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int ks = 0; ks < F::QL; ++ks)
+            *reinterpret_cast<bf16x8 __attribute__((address_space(3)))*>((uintptr_t)(q_lds + (ks * NC + 2 * second + i) * 1024)) = ql[i][ks];
+    if (!second && ge.kg == 0) {
+#pragma unroll
+        for (int nb = 0; nb < NC; ++nb) sm.pos[wave & 3][16 * nb + ge.x] = ge.col_pos[nb];
     }
     wait_dma();
     __syncthreads();
 
+    // ---- tile loop ------------------------------------------------------------------------------------
+    // A wave alternates between a matrix phase (O += its half of tile kt - 1, logits of its half of tile kt: 64 matrix instructions at
+    // head_dim 128, 128 with split weights) and a softmax phase (exponentials of its logits).  The two waves of a SIMD do so in turn:
+    //   waves 0..3   barrier kt | matrix (kt - 1, kt) | copies kt | softmax kt
+    //   waves 4..7   barrier kt | copies kt | softmax kt - 1 | matrix (kt - 1, kt)
+    // so that the vector work of one runs beside the matrix instructions of the other.  (A barrier behind every phase, which holds the
+    // waves to it strictly, lets the matrix pipe idle whenever the one wave that feeds it waits for its operands: 17 % more cycles.)
+    // Barrier kt says that K image kt and V image kt - 1 have landed and that nobody reads K image kt - 1 and V image kt - 2 any
+    // more; the copies behind it refill those slots: K image kt + 2 and V image kt + 1.
+    // The matrix phase in front (logits of tile kb) adds V image kb with weights of 0, the one behind the last tile forms logits that
+    // nobody reads: the loop's code is the only copy of it, which the pieces of a short prompt gain from (their time is that of
+    // instructions that arrive for the first time).
+    int c0 = 0, c1 = I::K_BYTES, c2 = 2 * I::K_BYTES;   // ring slots (their bytes) of K and V images kt, kt + 1, kt + 2
+    const int n_plain = ge.n_plain;
+    f32x4 s[2][NC], o[MD][NC];
+    Weights<SPLIT> p;
+    float lsum[NC], mref[NC];
     // exponent reference of each column = the maximum of its logits over the visible ones of keys 0..31
-    f32x16 s_a[2], s_b[2];
-    qk_half<D>(rg.k[2], 0, qf, fo, s_a);
-    float mref[2];
+    matrix_phase<D, SPLIT, false>(0, k_base + 2 * I::K_BYTES, fo, qf, q_lds, p, o, s);
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
+    for (int nb = 0; nb < NC; ++nb) {
         float t = NEG_BIG;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int key = 8 * (v >> 2) + 4 * h + (v & 3);
-            t = fmaxf(t, key <= ge.col_pos[nb] ? s_a[nb][v] : NEG_BIG);
-        }
-        t = fmaxf(t, __shfl_xor(t, 32));   // key 0 (held by the h = 0 lane) is visible to every row
-        mref[nb] = t * scale_log2e;
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) t = fmaxf(t, 16 * b + 4 * ge.kg + v <= ge.col_pos[nb] ? s[b][nb][v] : NEG_BIG);
+        mref[nb] = column_max(t) * scale_log2e;   // key 0 is visible to every row
     }
-    __syncthreads();                                // ring slot 2 is free again before the loop copies into it
-    if (kb > 0) qk_half<D>(rg.k[0], 0, qf, fo, s_a);   // logits of this part's first 32 keys (else: those above)
-    Weights<SPLIT> pf_a, pf_b;
-    pf_b.clear();
+#pragma unroll
+    for (int nb = 0; nb < NC; ++nb) {
+        lsum[nb] = 0.f;
+#pragma unroll
+        for (int md = 0; md < MD; ++md) o[md][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int u = 0; u < Weights<SPLIT>::PARTS; ++u) p.part[u][nb] = u32x4{0u, 0u, 0u, 0u};
+    }
+    __syncthreads();   // K image 0 has been read: ring slot 2 is free
+    auto copies = [&](int kt) {
+        dma_image<CH>(tile_image(kt + 2), k_base + c2, wave, lane_off);
+        dma_image<CH>(tile_image(kt + 1) + I::K_BYTES, v_base + c1, wave, lane_off);
+    };
+    int vp = 0;        // ring slot of V image kt - 1
+    auto barrier = [&] {
+        __builtin_amdgcn_sched_barrier(0);
+        wait_dma_but<2 * CH / FAST_WAVES>();   // all but the newest tile's copies
+        __builtin_amdgcn_s_waitcnt(0xc07f);    // lgkmcnt(0): the wave's own fragment reads
+        plain_barrier();
+        vp = c0;
+        c0 = c1; c1 = c2; c2 = vp;
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    const uint32_t k_half = k_base + second * (2 * I::BLOCK), v_half = v_base + second * (4 * I::V_PLANE);
+    auto softmax = [&](int kt) {
+        if (__builtin_expect(kt >= n_plain, 0)) {   // weight 0 behind a column's own position
+            uint32_t ln = lane_off;
+            asm volatile("" : "+v"(ln));   // (opaque: nothing that follows from it is kept over the loop)
+            ln >>= 4;
+            int pos[NC];
+#pragma unroll
+            for (int nb = 0; nb < NC; ++nb) pos[nb] = sm.pos[wave & 3][16 * nb + (ln & 15)];
+            mask_half(s, pos, kt * KT + 32 * second, (int)(ln >> 4));
+        }
+        softmax_phase<SPLIT>(s, p, lsum, mref, scale_log2e);
+    };
+    if (!second) {
+        for (int kt = kb;; ++kt) {
+            matrix_phase<D, SPLIT, true>(v_half + vp, k_half + c0, fo, qf, q_lds, p, o, s);
+            if (kt == ke) break;
+            copies(kt);
+            softmax(kt);
+            barrier();
+        }
+    } else {
+        copies(kb);
+        for (int kt = kb;; ++kt) {
+            matrix_phase<D, SPLIT, true>(v_half + vp, k_half + c0, fo, qf, q_lds, p, o, s);
+            if (kt == ke) break;
+            barrier();
+            copies(kt + 1);
+            softmax(kt);
+        }
+    }
+    wait_dma();
 
-    // ---- tile loop ------------------------------------------------------------------------------------
-    // Iteration kt: wait for the own direct-to-LDS copies issued one iteration ago, barrier (now K image kt+1
-    // and V image kt are complete and visible, and nobody reads the slots of K image kt-1 / V image kt-2 any
-    // more), issue the copies of K image kt+2 and V image kt+1 into those slots, and run two pipeline steps:
-    //   step (kt, 0): weights of keys [64kt, 64kt+32)    | logits of (kt, 1) from K[kt]     | O += half (kt-1, 1), V[kt-1]
-    //   step (kt, 1): weights of keys [64kt+32, 64kt+64) | logits of (kt+1, 0) from K[kt+1] | O += half (kt, 0),   V[kt]
-    int k0 = 0, k1 = 1, k2 = 2;   // ring slots of K images kt, kt+1, kt+2; V images kt-1, kt, kt+1 sit in k2, k0, k1
-    int kt = kb;
-    const int plain_end = min(ge.n_plain, ke);
-    for (; kt < plain_end; ++kt) {   // plain tiles: every key visible to every row; image kt+1 always exists
-        if (kt > kb) {
-            wait_dma();
-            __syncthreads();
-        }
-        const unsigned char* nxt = head_images + (size_t)(kt + 1) * I::BYTES;
-        if (kt + 2 < n_kt) dma_image<I::K_BYTES / 1024>(nxt + I::BYTES, rg.k[k2], wave, lane);
-        dma_image<I::V_BYTES / 1024>(nxt + I::K_BYTES, rg.vt[k1], wave, lane);
-        pipeline_step<D, SPLIT, false, true>(rg.k[k0], 1, rg.vt[k2], 1, fo, qf, s_a, s_b, pf_b, pf_a, o, lsum, mref, ge.col_pos,
-                                   kt * KT, h, scale_log2e);
-        pipeline_step<D, SPLIT, false, true>(rg.k[k1], 0, rg.vt[k0], 0, fo, qf, s_b, s_a, pf_a, pf_b, o, lsum, mref, ge.col_pos,
-                                   kt * KT + 32, h, scale_log2e);
-        const int t = k0; k0 = k1; k1 = k2; k2 = t;
+    // ---- the two waves of a row group add up: each keeps half of the dims --------------------------------------
+    __syncthreads();   // (also: everyone is done with the rings)
+    ge.init_rows(Hq, Hkv, aq.n_row_tiles, g, ordinal);   // (formed anew: the loop has no registers to spare)
+    constexpr int MH = MD / 2;
+    f32x4 oh[MH][NC];
+    const int md0 = second * MH;
+    {
+        unsigned char* mine = smem_raw + (size_t)wave * EXCHANGE_WAVE<D> + lane_off;
+        const unsigned char* other = smem_raw + (size_t)(wave ^ 4) * EXCHANGE_WAVE<D> + lane_off;
+#pragma unroll
+        for (int md = 0; md < MH; ++md)
+#pragma unroll
+            for (int nb = 0; nb < NC; ++nb) {
+                f32x4 w;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {   // (element by element: a choice between the arrays' places would put them into memory)
+                    const float lo = o[md][nb][e], hi = o[MH + md][nb][e];
+                    w[e] = second ? lo : hi;
+                    oh[md][nb][e] = second ? hi : lo;
+                }
+                *reinterpret_cast<f32x4*>(mine + (md * NC + nb) * 1024) = w;
+            }
+        *reinterpret_cast<f32x4*>(mine + MH * NC * 1024) = f32x4{lsum[0], lsum[1], lsum[2], lsum[3]};
+        __syncthreads();
+#pragma unroll
+        for (int md = 0; md < MH; ++md)
+#pragma unroll
+            for (int nb = 0; nb < NC; ++nb) {
+                const f32x4 w = *reinterpret_cast<const f32x4*>(other + (md * NC + nb) * 1024);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) oh[md][nb][e] += w[e];
+            }
+        const f32x4 l2 = *reinterpret_cast<const f32x4*>(other + MH * NC * 1024);
+#pragma unroll
+        for (int nb = 0; nb < NC; ++nb) lsum[nb] += l2[nb];
     }
-    for (; kt < ke; ++kt) {           // tiles that cross some row's own position
-        if (kt > kb) {
-            wait_dma();
-            __syncthreads();
-        }
-        const unsigned char* nxt = head_images + (size_t)(kt + 1) * I::BYTES;
-        if (kt + 2 < ke) dma_image<I::K_BYTES / 1024>(nxt + I::BYTES, rg.k[k2], wave, lane);
-        if (kt + 1 < ke) dma_image<I::V_BYTES / 1024>(nxt + I::K_BYTES, rg.vt[k1], wave, lane);
-        pipeline_step<D, SPLIT, true, true>(rg.k[k0], 1, rg.vt[k2], 1, fo, qf, s_a, s_b, pf_b, pf_a, o, lsum, mref, ge.col_pos,
-                                  kt * KT, h, scale_log2e);
-        if (kt + 1 < ke)
-            pipeline_step<D, SPLIT, true, true>(rg.k[k1], 0, rg.vt[k0], 0, fo, qf, s_b, s_a, pf_a, pf_b, o, lsum, mref,
-                                      ge.col_pos, kt * KT + 32, h, scale_log2e);
-        else
-            pipeline_step<D, SPLIT, true, false>(rg.k[k1], 0, rg.vt[k0], 0, fo, qf, s_b, s_a, pf_a, pf_b, o, lsum, mref,
-                                       ge.col_pos, kt * KT + 32, h, scale_log2e);
-        const int t = k0; k0 = k1; k1 = k2; k2 = t;
-    }
-    pv_half<D, SPLIT>(rg.vt[k2], 1, pf_b, fo, o);   // the last half: V image ke-1 now sits in slot k2
-
     if (part >= 0) {   // leave the partial result; attn_combine_kernel adds the parts, checks and stores
-        if (!SPLIT && half) store_partial<D, false>(part_dst, o, lsum, mref); else store_partial<D, true>(part_dst, o, lsum, mref);
+        float* dst = part_dst + 4 * (threadIdx.x & 255);
+        if (!SPLIT && half) store_partial<D, false>(dst, oh, md0, lsum, mref, ge.kg); else store_partial<D, true>(dst, oh, md0, lsum, mref, ge.kg);
         return;
     }
-    float l[2];
-    if (!sums_overflowed<D>(o, lsum, l)) {
-        store_output<G, D>(ge, o, l, mref, R, Hq, smem_raw, aq.out, aq.lse);
+    // Overflow check: with a fixed reference a runaway logit shows up as inf / nan in the sums.
+    float l[NC];
+    bool bad = false;
+#pragma unroll
+    for (int nb = 0; nb < NC; ++nb) {
+        l[nb] = column_sum(lsum[nb]);
+        float chk = l[nb];
+#pragma unroll
+        for (int md = 0; md < MH; ++md)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) chk += fabsf(oh[md][nb][v]);
+        bad = bad || !(chk < INFINITY) || !(l[nb] > 0.f);
+    }
+    if (!__syncthreads_or(bad ? 1 : 0)) {   // (also: the exchange has been read)
+        store_output<G, D, MH>(ge, oh, md0, l, mref, R, Hq, smem_raw, aq.out, aq.lse);
         return;
     }
     // the sums overflowed the fixed exponent reference (rare): the item again, with a running maximum
@@ -1011,7 +1185,7 @@ __device__ __forceinline__ void process_piece(const AttnQuery& aq, int g, int or
 // dealt to n_parts workgroups in equal consecutive shares; items are launched longest first, so the pieces are too.
 // Dynamic LDS: the larger of the K/V rings and the epilogue's staging.
 template <int G, int D, bool SPLIT>
-__global__ __launch_bounds__(256) void attn_fixed_ref_kernel(const AttnBatch batch, float* __restrict__ partials, int n_parts,
+__global__ __launch_bounds__(64 * FAST_WAVES) void attn_fixed_ref_kernel(const AttnBatch batch, float* __restrict__ partials, int n_parts,
                                                              int half, int Hq, int Hkv, float scale_log2e) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     int t = (int)blockIdx.x;
@@ -1034,57 +1208,56 @@ __global__ __launch_bounds__(256, 2) void attn_combine_kernel(const AttnBatch ba
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     int t = (int)blockIdx.x;
     const int g = t % Hkv; t /= Hkv;
-    const int md = t % (D / 32);
+    const int sl = t % (D / 32);
     const int item = t / (D / 32);
     const int ordinal = item % batch.max_row_tiles;
     const AttnQuery& aq = batch.q[item / batch.max_row_tiles];
     if (ordinal >= aq.n_row_tiles) return;
     {
         using P = Part<D, F32>;
-        constexpr int OW = P::O_WORDS, SW = F32 ? 16 : 8;   // words of a part, of a slice of a column block
+        constexpr int SW = F32 ? 8 : 4;                     // words of a slice of a column block
         constexpr int AHEAD = 4;                            // parts whose loads are in flight together
-        const uint32_t* p0 = reinterpret_cast<const uint32_t*>(partials + ((size_t)item * n_parts * Hkv + g) * P::WORDS) + threadIdx.x;
+        const uint32_t* p0 = reinterpret_cast<const uint32_t*>(partials + ((size_t)item * n_parts * Hkv + g) * P::WORDS) + 4 * threadIdx.x;
         const size_t part_stride = (size_t)Hkv * P::WORDS;
-        f32x16 acc[2];
-        float lsum[2] = {0.f, 0.f}, mref[2];
+        f32x4 acc[2][NC];
 #pragma unroll
-        for (int nb = 0; nb < 2; ++nb) {
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[nb][v] = 0.f;
-            mref[nb] = __uint_as_float(p0[(OW + 2 + nb) * 256]);   // part 0 is never empty; every part derives the same reference
-        }
+        for (int nb = 0; nb < NC; ++nb) acc[0][nb] = acc[1][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        float sum = 0.f;
+        const uint32_t ref = p0[P::at(P::REFERENCE)];   // part 0 is never empty; every part derives the same reference
+        const int x = threadIdx.x & 15;
         auto add = [&](int first, auto count) {
             constexpr int N = decltype(count)::value;
-            uint32_t w[N][2][SW], tail[N][2][2];
+            u32x4 w[N][NC][SW / 4];
+            uint32_t tail[N][2];
 #pragma unroll
             for (int i = 0; i < N; ++i) {
                 const uint32_t* pp = p0 + (first + i) * part_stride;
 #pragma unroll
-                for (int nb = 0; nb < 2; ++nb) {
+                for (int nb = 0; nb < NC; ++nb)
 #pragma unroll
-                    for (int j = 0; j < SW; ++j) w[i][nb][j] = pp[(nb * (OW / 2) + md * SW + j) * 256];
-                    tail[i][nb][0] = pp[(OW + nb) * 256];
-                    tail[i][nb][1] = F32 ? 0u : pp[(OW + 4 + nb) * 256];
-                }
+                    for (int j = 0; j < SW; j += 4) w[i][nb][j / 4] = *reinterpret_cast<const u32x4*>(pp + P::at(nb * P::COL_WORDS + sl * SW + j));
+                tail[i][0] = pp[P::at(P::SUM)];
+                tail[i][1] = F32 ? 0u : pp[P::at(P::exponent(2 * sl))];
             }
 #pragma unroll
-            for (int i = 0; i < N; ++i)
+            for (int i = 0; i < N; ++i) {
 #pragma unroll
-                for (int nb = 0; nb < 2; ++nb) {
-                    const int e = (int)tail[i][nb][1];
+                for (int nb = 0; nb < NC; ++nb) {
+                    const int e = F32 ? 0 : (int)of_block(tail[i][1], nb, x);
 #pragma unroll
-                    for (int v = 0; v < 16; v += 2) {
+                    for (int j = 0; j < 8; j += 2) {   // accumulators j and j + 1 of the slice's eight
                         if constexpr (F32) {
-                            acc[nb][v] += __uint_as_float(w[i][nb][v]);
-                            acc[nb][v + 1] += __uint_as_float(w[i][nb][v + 1]);
+                            acc[j >> 2][nb][j & 3] += __uint_as_float(w[i][nb][j >> 2][j & 3]);
+                            acc[j >> 2][nb][(j & 3) + 1] += __uint_as_float(w[i][nb][j >> 2][(j & 3) + 1]);
                         } else {
-                            const f16x2 h = __builtin_bit_cast(f16x2, w[i][nb][v / 2]);
-                            acc[nb][v] += __builtin_ldexpf((float)h[0], e);
-                            acc[nb][v + 1] += __builtin_ldexpf((float)h[1], e);
+                            const f16x2 h = __builtin_bit_cast(f16x2, (uint32_t)w[i][nb][0][j / 2]);
+                            acc[j >> 2][nb][j & 3] += __builtin_ldexpf((float)h[0], e);
+                            acc[j >> 2][nb][(j & 3) + 1] += __builtin_ldexpf((float)h[1], e);
                         }
                     }
-                    lsum[nb] += __uint_as_float(tail[i][nb][0]);
                 }
+                sum += __uint_as_float(tail[i][0]);
+            }
         };
         int part = 0;
         for (; part + AHEAD <= n_parts; part += AHEAD) add(part, std::integral_constant<int, AHEAD>{});
@@ -1092,24 +1265,25 @@ __global__ __launch_bounds__(256, 2) void attn_combine_kernel(const AttnBatch ba
         if (part < n_parts) add(part, std::integral_constant<int, 1>{});
         Geometry<G> ge;
         ge.init(aq.q_index, aq.R, Hq, Hkv, aq.n_row_tiles, aq.n_img_tiles, g, ordinal);
-        float l[2];
+        float l[NC], mref[NC];
         bool bad = false;
 #pragma unroll
-        for (int nb = 0; nb < 2; ++nb) {
-            l[nb] = lsum[nb] + __shfl_xor(lsum[nb], 32);
+        for (int nb = 0; nb < NC; ++nb) {
+            l[nb] = __uint_as_float(of_block(__float_as_uint(sum), nb, x));
+            mref[nb] = __uint_as_float(of_block(ref, nb, x));
             float chk = l[nb];
 #pragma unroll
-            for (int v = 0; v < 16; ++v) chk += fabsf(acc[nb][v]);
+            for (int v = 0; v < 4; ++v) chk += fabsf(acc[0][nb][v]) + fabsf(acc[1][nb][v]);
             bad = bad || !(chk < INFINITY) || !(l[nb] > 0.f);
         }
         if (!__syncthreads_or(bad ? 1 : 0)) {
-            store_slice<G, D>(ge, acc, md, l, mref, aq.R, Hq, smem_raw, aq.out, aq.lse);
+            store_slice<G, D>(ge, acc, sl, l, mref, aq.R, Hq, smem_raw, aq.out, aq.lse);
             return;
         }
     }
     // the sums overflowed the fixed exponent reference (rare): the item again, with a running maximum
     __syncthreads();
-    running_max_item<G, D, SPLIT>(aq, g, ordinal, Hq, Hkv, scale_log2e, smem_raw, md);
+    running_max_item<G, D, SPLIT>(aq, g, ordinal, Hq, Hkv, scale_log2e, smem_raw, sl);
 }
 
 // ---- all items with the running maximum (FR_ATTN_SOFTMAX_RUNNING_MAX) -------------------------------------
@@ -1132,8 +1306,8 @@ struct QueryScratch {
     size_t images_bytes;
 };
 
-template <int D>
-constexpr size_t LDS_FAST = std::max(sizeof(Rings<D>), Img<D>::EPILOGUE_LDS);
+template <int D, bool SPLIT>
+constexpr size_t LDS_FAST = std::max({sizeof(FastLds<D, SPLIT>), Img<D>::EPILOGUE_LDS, EXCHANGE_LDS<D>});
 template <int D>
 constexpr size_t LDS_SAFE = std::max((size_t)Img<D>::BYTES, Img<D>::EPILOGUE_LDS);
 
@@ -1143,7 +1317,7 @@ template <int G, int D, bool SPLIT>
 hipError_t set_kernel_attributes() {
     static const hipError_t once = [] {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_fixed_ref_kernel<G, D, SPLIT>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_FAST<D>);
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_FAST<D, SPLIT>);
         if (e != hipSuccess) return e;
         e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_combine_kernel<G, D, SPLIT, true>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_SAFE<D>);
@@ -1171,11 +1345,11 @@ hipError_t pack_query(const Shape& s, const void* q_rows, const int32_t* q_index
     if ((size_t)n_img_tiles * s.Hkv * Img<D>::BYTES > sc.images_bytes) return hipErrorInvalidValue;
     if (shared == nullptr) {
         if (writeback)
-            pack_kv_images_kernel<D, true><<<dim3(n_img_tiles, s.Hkv), block, 0, st>>>(
+            pack_kv_images_kernel<D, true><<<dim3(n_img_tiles * s.Hkv), block, 0, st>>>(
                 (const __bf16*)k_cache, (const __bf16*)v_cache, (int)L, (const __bf16*)k_new, (const __bf16*)v_new, q_index, R,
                 s.Hkv, n_img_tiles, sc.images);
         else
-            pack_kv_images_kernel<D, false><<<dim3(n_img_tiles, s.Hkv), block, 0, st>>>(
+            pack_kv_images_kernel<D, false><<<dim3(n_img_tiles * s.Hkv), block, 0, st>>>(
                 (const __bf16*)k_cache, (const __bf16*)v_cache, (int)L, (const __bf16*)k_new, (const __bf16*)v_new, q_index, R,
                 s.Hkv, n_img_tiles, sc.images);
     } else if constexpr (D == 128) {   // k_cache / v_cache are the shared chunk store
@@ -1188,11 +1362,11 @@ hipError_t pack_query(const Shape& s, const void* q_rows, const int32_t* q_index
         prompt_map_kernel<<<dim3(std::max(1, (max_len + 255) / 256), shared->ct.n + 1), block, 0, st>>>(
             shared->ct, rows, (int)L, sc.store_row_map, sc.chunk_id_map);
         if (s.rope_layout == FR_ROPE_INTERLEAVED)
-            pack_kv_images_shared_kernel<FR_ROPE_INTERLEAVED><<<dim3(n_img_tiles, s.Hkv), block, 0, st>>>(
+            pack_kv_images_shared_kernel<FR_ROPE_INTERLEAVED><<<dim3(n_img_tiles * s.Hkv), block, 0, st>>>(
                 (const __bf16*)k_cache, (const __bf16*)v_cache, sc.store_row_map, sc.chunk_id_map, shared->table, (int)L,
                 (const __bf16*)k_new, (const __bf16*)v_new, q_index, R, s.Hkv, n_img_tiles, sc.images);
         else
-            pack_kv_images_shared_kernel<FR_ROPE_HALF><<<dim3(n_img_tiles, s.Hkv), block, 0, st>>>(
+            pack_kv_images_shared_kernel<FR_ROPE_HALF><<<dim3(n_img_tiles * s.Hkv), block, 0, st>>>(
                 (const __bf16*)k_cache, (const __bf16*)v_cache, sc.store_row_map, sc.chunk_id_map, shared->table, (int)L,
                 (const __bf16*)k_new, (const __bf16*)v_new, q_index, R, s.Hkv, n_img_tiles, sc.images);
     } else {
@@ -1217,11 +1391,11 @@ void launch_tile_loop(const AttnBatch& batch, dim3 grid, float* partials, int n_
                       KernelTimer* timer, bool timed, hipStream_t st) {
     if (timed) {
         const int slot = (int)(timer->n_recorded % timer->n_slots);
-        hipExtLaunchKernelGGL((attn_fixed_ref_kernel<G, D, SPLIT>), grid, dim3(256), (uint32_t)LDS_FAST<D>, st, timer->start[slot],
+        hipExtLaunchKernelGGL((attn_fixed_ref_kernel<G, D, SPLIT>), grid, dim3(64 * FAST_WAVES), (uint32_t)LDS_FAST<D, SPLIT>, st, timer->start[slot],
                               timer->stop[slot], 0u, batch, partials, n_parts, (int)half, s.Hq, s.Hkv, scale_log2e);
         ++timer->n_recorded;
     } else {
-        attn_fixed_ref_kernel<G, D, SPLIT><<<grid, dim3(256), LDS_FAST<D>, st>>>(batch, partials, n_parts, (int)half, s.Hq, s.Hkv, scale_log2e);
+        attn_fixed_ref_kernel<G, D, SPLIT><<<grid, dim3(64 * FAST_WAVES), LDS_FAST<D, SPLIT>, st>>>(batch, partials, n_parts, (int)half, s.Hq, s.Hkv, scale_log2e);
     }
 }
 
@@ -1341,8 +1515,8 @@ hipError_t launch_shared_batch(const Shape& s, int n, const SharedBatchQuery* qs
 
 // Shapes with an instance of their own; the others (any group size up to 64, head_dim 64 too) run the kernels whose group
 // size is an argument and whose weights are split (Weights).  The group size enters the prologue and the epilogue only.
-// 28 query / 4 KV heads over a 17k-token prompt, 2970 rows: 0.80 ms for the tile loop (387 GFLOP as 774 GFLOP of matrix
-// instructions: 0.97 PFLOP/s) + 0.022 + 0.018 ms; one wave per (row, head) on the vector ALU took 50.5 ms.
+// 28 query / 4 KV heads over a 17k-token prompt, 2970 rows: 0.58 ms for the tile loop (410 GFLOP as 820 GFLOP of matrix
+// instructions: 1.41 PFLOP/s) + 0.022 + 0.015 ms; one wave per (row, head) on the vector ALU took 50.5 ms.
 static bool own_instance(const Shape& s) { return s.d == 128 && (s.G == 1 || s.G == 2 || s.G == 4 || s.G == 8); }
 
 // Partial results of a launch in parts: one slot per piece.

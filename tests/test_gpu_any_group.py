@@ -120,6 +120,27 @@ def test_items_on_both_sides_of_the_split_rules(Hq, Hkv, d, lens):
     ctx.close()
 
 
+# Key tiles are 64 keys in two halves, one per wave of a row group, and the tile loop runs three tiles ahead: prompts of one half tile to
+# five tiles, whole and in parts of one tile and of none.  (bf16 weights: the tolerance of the other tests of those shapes.)
+@pytest.mark.parametrize("split", [B.FR_ATTN_SPLIT_OFF, B.FR_ATTN_SPLIT_ON, B.FR_ATTN_SPLIT_AUTO])
+@pytest.mark.parametrize("total", [2, 31, 32, 33, 63, 64, 65, 128, 129, 191, 256, 319, 320])
+@pytest.mark.parametrize("Hq,Hkv,d", [(4, 4, 128), (8, 2, 128), (7, 1, 128), (4, 2, 64)])
+def test_few_key_tiles(Hq, Hkv, d, total, split):
+    w = workload(Hq, Hkv, d, (total - 1,), 1, ratio=1.0)
+    qi = np.arange(w.L)
+    k_cache, v_cache = assembled_cache(w, w.k_cached)
+    ctx = H.make_ctx(w.shape, w.L, w.n_chunks, w.nq)
+    ctx.fr_set_option(B.FR_OPT_ATTN_SPLIT, split)
+    got, lse = run_attention(ctx, w, qi, k_cache, v_cache)
+    want, want_lse = orc.sparse_prefill_attn(w.q_full[qi], qi, k_cache, v_cache, w.k_full[qi], w.v_full[qi])
+    if (Hq, d) == (7, 128) or d == 64:
+        assert H.max_rel_err(got, want) <= OUT_TOL
+    else:
+        H.assert_close(got, want, "bf16", "few key tiles")
+    assert np.max(np.abs(lse - want_lse)) <= 1e-4
+    ctx.close()
+
+
 # Scores: products of bf16 are exact in fp32; the sums, the exponentials and the normalisers are fp32 (2^-24 relative each,
 # arguments of the exponentials up to about 30 in base 2, i.e. 2^-19 of a weight): 1e-5 of the largest score covers both
 # storage types.
