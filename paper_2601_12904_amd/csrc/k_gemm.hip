@@ -3,7 +3,7 @@
 // rotary table of the rows' positions.
 //
 // GEMM.  out[M, N] = a[M, K] . w[N, K]^T, bf16 in, fp32 accumulate.  Both operands are K-contiguous, so the
-// kernel computes the transposed tile C^T = W A^T with v_mfma_f32_32x32x16_bf16: output features run along the
+// kernel computes the transposed tile C^T = W A^T with v_mfma_f32_32x32x16_bf16 (16 x 16 x 32 in the 256 x 256 kernel): output features run along the
 // accumulator's register dimension and activation rows along lanes, which puts four consecutive features of one
 // row into one lane -- rotary pairs and (gate, up) pairs are then combined without any lane exchange.
 // Large launches run the 256 x 256 kernel further down; in the others
@@ -34,6 +34,10 @@ constexpr int BR = 128;   // activation rows per workgroup (MFMA N side)
 constexpr int BK = 64;    // K elements per tile: 128 bytes per row
 constexpr int EPI_PITCH = 64 + 4;                   // fp32 elements per row of a wave's epilogue staging
 
+// Accumulators of a wave's 64 features x 64 rows, as 32 x 32 tiles [features + 32][rows + 32] or as 16 x 16 tiles.
+typedef f32x16 Acc32[2][2];
+typedef f32x4 Acc16[4][4];
+
 enum { EPI_STORE = 0, EPI_RESIDUAL = 1, EPI_QKV_ROPE = 2, EPI_SWIGLU = 3 };
 
 struct GemmArgs {
@@ -56,6 +60,7 @@ struct GemmArgs {
 
 template <int WF>
 struct Tiling {
+    typedef Acc32 Acc;
     static constexpr int NW = 2 * WF;                    // waves per workgroup
     static constexpr int BF = 64 * WF;                   // output features per workgroup (MFMA M side)
     static constexpr int BRT = BR;                       // and rows
@@ -130,13 +135,8 @@ constexpr int MIN_K_TILES_PER_PART = 16;
 
 // Epilogue shared by the kernels: this wave's fp32 64 x 64 tile goes through LDS ([row][feature]), then every lane
 // handles 8 consecutive features of a row.  fw0 / rw0 = first feature / row of the wave's tile.
-template <int EPI>
-__device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, f32x16 (&acc)[2][2], unsigned char* smem, int wave, int lane,
-                                              int fw0, int rw0) {
+__device__ __forceinline__ void stage_tile(const Acc32& acc, float* ep, int lane) {   // -> [row][feature]
     const int x = lane & 31, h = lane >> 5;
-    // ---- epilogue: fp32 tile through LDS ([row][feature] per wave), then 8 consecutive features per lane ----
-    __syncthreads();
-    float* ep = reinterpret_cast<float*>(smem) + wave * 64 * EPI_PITCH;
 #pragma unroll
     for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
@@ -148,6 +148,22 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, f32x16 (&acc)[2
                 for (int e = 0; e < 4; ++e) t[e] = acc[mb][nb][4 * q4 + e];
                 *reinterpret_cast<f32x4*>(&ep[(32 * nb + x) * EPI_PITCH + 32 * mb + 8 * q4 + 4 * h]) = t;
             }
+}
+__device__ __forceinline__ void stage_tile(const Acc16& acc, float* ep, int lane) {
+    const int x = lane & 15, kg = lane >> 4;
+#pragma unroll
+    for (int fb = 0; fb < 4; ++fb)
+#pragma unroll
+        for (int rb = 0; rb < 4; ++rb)
+            *reinterpret_cast<f32x4*>(&ep[(16 * rb + x) * EPI_PITCH + 16 * fb + 4 * kg]) = acc[fb][rb];
+}
+template <int EPI, class Acc>
+__device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, const Acc& acc, unsigned char* smem, int wave, int lane,
+                                              int fw0, int rw0) {
+    // ---- epilogue: fp32 tile through LDS ([row][feature] per wave), then 8 consecutive features per lane ----
+    __syncthreads();
+    float* ep = reinterpret_cast<float*>(smem) + wave * 64 * EPI_PITCH;
+    stage_tile(acc, ep, lane);
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
@@ -353,7 +369,7 @@ __global__ __launch_bounds__(128 * WF) void gemm_bf16_kernel(GemmArgs g) {
 //
 // What bounds the 256 x 128 kernel is the vector-memory path that feeds the ring (48 KB per K tile and 16 matrix
 // instructions of a wave; 64 KB per 32 here), and the fragment reads, one per matrix instruction (24 per 32 here).
-// The eight waves run as two groups half a phase apart: while one wave of a SIMD multiplies (8 matrix instructions, a
+// The eight waves run as two groups half a phase apart: while one wave of a SIMD multiplies (16 matrix instructions, a
 // quarter of its tile, at raised priority), the other one reads fragments and issues copies; a barrier separates any
 // two half phases.  Per K tile and wave (w = its 4 blocks of 32 features, a = its 2 blocks of 32 rows):
 //
@@ -368,17 +384,23 @@ __global__ __launch_bounds__(128 * WF) void gemm_bf16_kernel(GemmArgs g) {
 // free one phase after it was last read, which is when its copy for tile k + 2 goes out; that copy is waited for (by
 // count, never to zero before the last two tiles) five to seven phases later, at the end of the phase in front of its
 // first read.
-// At 4096 rows of the gate / up projection (N = 28672, K = 4096): 882 -> 707 us, 1360 TFLOP/s on normally distributed
-// operands, 1830 on zeros (1054 before): with real data the chip's power limit is the bound, no longer the schedule.
+// At 4096 rows of the gate / up projection (N = 28672, K = 4096) with 32 x 32 x 16 matrix instructions: 882 -> 707 us, 1360 TFLOP/s on
+// normally distributed operands, 1830 on zeros (1054 before): with real data the chip's power limit is the bound, no longer the schedule.
+// Hence 16 x 16 x 32 instructions, which touch their accumulators half as often (1.98 instead of 1.78 PFLOP/s from registers alone), each sharing an
+// operand with its neighbours: 712 -> 656 us, 1467 TFLOP/s; 2970 rows: gate / up 550 -> 512, down 275 -> 257, O 89 -> 84, Q / K / V 142 -> 131 us.
 // Waiting only for the reads that the coming products need, with the copies one phase later: no difference.
 struct Tiling256 {
+    typedef Acc16 Acc;
     static constexpr int NW = 8;
     static constexpr int BF = 256, BRT = 256;
+    // Chunk c of row r of a piece lies at c ^ swz16(r): the 16 rows of a fragment, chunks 4 ks .. 4 ks + 3 by quarters of the wave, fall
+    // into 16 different 16-byte bank groups whether the LDS serves lanes 0 .. 15 together or 0 .. 3, 12 .. 15 and 20 .. 27.
+    static __host__ __device__ constexpr int swz16(int r) { return ((r >> 1) & 1) | ((r >> 3) & 1) << 1 | (((r >> 2) ^ (r >> 3)) & 1) << 2; }
     static constexpr int PIECE = 128 * BK * 2;             // 16 KB
     static constexpr int STAGE = 4 * PIECE;                // [w0 w1][w2 w3][a0][a1]
     static constexpr int WAVE_TILES = 16;                  // 64 x 64 pieces of the output tile, two per wave
     static constexpr int LDS_BYTES = NW * 64 * EPI_PITCH * 4;
-    static constexpr float US_PER_K_TILE = 1.6f, ROUND_BASE = 0.25f, US_LAUNCH = 9.5f, US_SPLIT = 15.0f;   // see Tiling
+    static constexpr float US_PER_K_TILE = 1.47f, ROUND_BASE = 0.27f, US_LAUNCH = 9.5f, US_SPLIT = 15.0f;   // see Tiling
     static_assert(2 * STAGE <= LDS_BYTES, "the epilogue staging is the larger one");
     static __host__ __device__ constexpr int feature0(int v) { return 128 * (v >> 3) + 64 * (v & 1); }   // v = 2 wave + half
     static __host__ __device__ constexpr int row_0(int v) { return 64 * ((v >> 1) & 3); }
@@ -397,7 +419,7 @@ template <int EPI>
 __global__ __launch_bounds__(512) void gemm_bf16_256_kernel(GemmArgs g) {
     using TL = Tiling256;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    const int tid = threadIdx.x, lane = tid & 63, x = lane & 31, h = lane >> 5;
+    const int tid = threadIdx.x, lane = tid & 63, x = lane & 15, kg = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wf = wave >> 2, wr = wave & 3;           // 2 x 4 waves; waves w and w + 4 share a SIMD
     int tile = (int)blockIdx.x, part = 0;
@@ -424,7 +446,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_256_kernel(GemmArgs g) {
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
         const int u = (j * TL::NW + wave) * 64 + lane;
-        const int r = u >> 3, c = (u & 7) ^ swz(r);
+        const int r = u >> 3, c = (u & 7) ^ TL::swz16(r);
         w_off[j] = (uint32_t)(((int64_t)(128 * (r >> 6) + (r & 63)) * g.K + 8 * c) * 2);
 #pragma unroll
         for (int hf = 0; hf < 2; ++hf)
@@ -449,37 +471,35 @@ __global__ __launch_bounds__(512) void gemm_bf16_256_kernel(GemmArgs g) {
     using CA0 = std::integral_constant<int, A0>;
     using CA1 = std::integral_constant<int, A1>;
 
-    // Fragment reads: row 64 wf + 32 b + x of a w piece (b = 0, 1), row 32 wr + x of an a piece; k step ks -> chunk
-    // (2 ks + h) ^ swz(row), and swz(32 m + x) = swz(x) ^ 4 (m & 1), so block b reads where block 0 of step ks ^ 2 b does.
+    // Fragment reads: row 64 wf + 16 b + x of a w piece (b = 0 .. 3), row 32 wr + 16 b + x of an a piece (b = 0, 1); k step ks -> chunk
+    // (4 ks + kg) ^ swz16(row).  Block i >> 1 of a 32-row group, k step i & 1: the four fragments of a group are i = 0 .. 3.
     typedef const bf16x8 __attribute__((address_space(3))) * lds_frag_ptr;
-    uint32_t rd_w[4], rd_a[4];
+    uint32_t rd_w[2], rd_a[2];
     {
         const uint32_t lds_v = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            rd_w[ks] = lds_v + (64 * wf + x) * 128 + (((2 * ks + h) ^ swz(x)) << 4);
-            rd_a[ks] = lds_v + A0 * TL::PIECE + (32 * wr + x) * 128 + (((2 * ks + h) ^ swz(x) ^ (4 * (wr & 1))) << 4);
+        for (int ks = 0; ks < 2; ++ks) {
+            rd_w[ks] = lds_v + (64 * wf + x) * 128 + (((4 * ks + kg) ^ TL::swz16(x)) << 4);
+            rd_a[ks] = lds_v + A0 * TL::PIECE + (32 * wr + x) * 128 + (((4 * ks + kg) ^ TL::swz16(x)) << 4);
         }
     }
     // (the other stage is reached by adding its offset with one vector instruction per address and tile: it lies beyond the
     // 64 KB of an instruction's offset field)
     int stage_step = TL::STAGE;
-    auto frag_w = [&](int blk, int ks) {
-        return *reinterpret_cast<lds_frag_ptr>((uintptr_t)(rd_w[ks ^ (2 * (blk & 1))] + (blk >> 1) * TL::PIECE + (blk & 1) * (32 * 128)));
+    auto frag_w = [&](int blk, int i) {   // (indexed from a pointer: the constants go into the instructions' offsets)
+        return reinterpret_cast<lds_frag_ptr>((uintptr_t)rd_w[i & 1])[((blk >> 1) * TL::PIECE + (32 * (blk & 1) + 16 * (i >> 1)) * 128) / 16];
     };
-    auto frag_a = [&](int hf, int ks) { return *reinterpret_cast<lds_frag_ptr>((uintptr_t)(rd_a[ks] + hf * TL::PIECE)); };
+    auto frag_a = [&](int hf, int i) { return reinterpret_cast<lds_frag_ptr>((uintptr_t)rd_a[i & 1])[(hf * TL::PIECE + 16 * (i >> 1) * 128) / 16]; };
 
-    f32x16 acc[2][2][2];   // [features + 64][features + 32][rows + 32]
+    Acc16 acc[2];   // [features + 64][features + 16][rows + 16]
 #pragma unroll
     for (int q = 0; q < 2; ++q)
 #pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
+        for (int fb = 0; fb < 4; ++fb)
 #pragma unroll
-            for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) acc[q][mb][nb][v] = 0.f;
+            for (int rb = 0; rb < 4; ++rb) acc[q][fb][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    bf16x8 w[4][4], a[2][4];   // [block][k step]
+    bf16x8 w[4][4], a[2][4];   // [block of 32][block of 16, k step]
     auto end_of_reads = [&] {  // own reads complete; then both groups change places
         __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
         __builtin_amdgcn_sched_barrier(0);
@@ -490,10 +510,15 @@ __global__ __launch_bounds__(512) void gemm_bf16_256_kernel(GemmArgs g) {
         constexpr int q = decltype(q_c)::value, hf = decltype(hf_c)::value;
         __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks)
+        for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-            for (int mb = 0; mb < 2; ++mb)
-                acc[q][mb][hf] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[2 * q + mb][ks], a[hf][ks], acc[q][mb][hf], 0, 0, 0);
+            for (int fb = 0; fb < 4; ++fb)
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {   // (back and forth: neighbours in time share an operand, which saves power)
+                    const int rb = (fb & 1) ? 1 - t : t;
+                    f32x4& c = acc[q][fb][2 * hf + rb];
+                    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[2 * q + (fb >> 1)][2 * (fb & 1) + ks], a[hf][2 * rb + ks], c, 0, 0, 0);
+                }
         __builtin_amdgcn_s_setprio(0);
         __builtin_amdgcn_sched_barrier(0);
         barrier_keep_loads_in_flight();
@@ -542,7 +567,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_256_kernel(GemmArgs g) {
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) w[3][ks] = frag_w(3, ks);
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {   // on to the other stage (behind the last tile: stale data, never used)
+        for (int ks = 0; ks < 2; ++ks) {   // on to the other stage (behind the last tile: stale data, never used)
             rd_w[ks] += stage_step;
             rd_a[ks] += stage_step;
         }
@@ -573,11 +598,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_256_kernel(GemmArgs g) {
         for (int q = 0; q < 2; ++q) {
             float* dst = g.partials + ((size_t)(((int)blockIdx.x - g.n_whole) * TL::WAVE_TILES + 2 * wave + q)) * PARTIAL_FLOATS_PER_WAVE + lane;
 #pragma unroll
-            for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-                for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) dst[((2 * mb + nb) * 16 + v) * 64] = acc[q][mb][nb][v];
+            for (int i = 0; i < 64; ++i) dst[i * 64] = acc[q][i >> 4][(i >> 2) & 3][i & 3];
         }
         return;
     }
@@ -597,21 +618,14 @@ __global__ __launch_bounds__(64) void gemm_fixup_kernel(GemmArgs g) {
     const int split = (int)blockIdx.x / NW, wave = (int)blockIdx.x % NW;
     int f0, r0;
     TL::origin(g, g.n_whole + split, f0, r0);
-    f32x16 acc[2][2];
+    typename TL::Acc acc;
+    constexpr int V = sizeof(acc[0][0]) / sizeof(float), B = sizeof(acc[0]) / sizeof(acc[0][0]);   // accumulators of a tile, tiles along the rows
 #pragma unroll
-    for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[mb][nb][v] = 0.f;
+    for (int i = 0; i < 64; ++i) acc[i / V / B][i / V % B][i % V] = 0.f;
     for (int p = 0; p < g.n_parts; ++p) {
         const float* src = g.partials + ((size_t)((split * g.n_parts + p) * NW + wave)) * PARTIAL_FLOATS_PER_WAVE + lane;
 #pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-            for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) acc[mb][nb][v] += src[((2 * mb + nb) * 16 + v) * 64];
+        for (int i = 0; i < 64; ++i) acc[i / V / B][i / V % B][i % V] += src[i * 64];
     }
     gemm_epilogue<EPI>(g, acc, smem, /*staging slot*/ 0, lane, f0 + TL::feature0(wave), r0 + TL::row_0(wave));
 }
@@ -709,10 +723,10 @@ hipError_t launch_gemm(const GemmArgs& g, const GemmTuning& tune, hipStream_t st
     const Plan narrow = plan_tiling<Tiling<4>>(g, n_cu, tune);
     // 256 rows per workgroup where that is the shorter launch by the estimate above: a tile of twice the area takes 1.6
     // times as long, but it comes in rounds twice as coarse and its partial sums cost more.  256 x 128 -> 256 x 256, us:
-    //   28672 x 4096 (gate / up): 1100 rows 232 stays, 2048 rows 417 -> 377, 2970 rows 652 -> 548, 16896 rows 3529 -> 2929
-    //   4096 x 14336 (down):      1100 rows 154 -> 139, 2048 rows 192 -> 196, 2970 rows 304 -> 270
-    //   4096 x 4096 (output):     1100 rows  48 stays (59), 2048 rows 62 stays (76), 2970 rows 100 -> 86
-    //   6144 x 4096 (Q / K / V):  1100 rows  54 stays (73), 2048 rows 104 -> 91, 2970 rows 146 -> 139
+    //   28672 x 4096 (gate / up): 1100 rows 235 stays, 2048 rows 425 -> 351, 2970 rows 650 -> 512, 4096 rows 895 -> 656
+    //   4096 x 14336 (down):      1100 rows 145 -> 138, 2048 rows 193 -> 181, 2970 rows 305 -> 257, 4096 rows 397 -> 314
+    //   4096 x 4096 (output):     1100 rows  46 stays, 2048 rows 63 stays, 2970 rows 103 -> 84, 4096 rows 125 -> 99
+    //   6144 x 4096 (Q / K / V):  1100 rows  58 stays, 2048 rows 105 -> 87, 2970 rows 149 -> 131, 4096 rows 183 -> 166
     //   256 x 1792:               1 row      19 stays (30)
     if (tune.tile == 0) {
         const Plan square = plan_tiling<Tiling256>(g, n_cu, tune);
