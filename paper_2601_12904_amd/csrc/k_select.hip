@@ -15,6 +15,8 @@
 // of 16384, without any search, is 8.1).
 #include "fr_internal.hpp"
 
+#include <algorithm>
+
 namespace fr {
 
 __device__ __forceinline__ uint32_t score_key(float f) {
@@ -208,11 +210,83 @@ __global__ __launch_bounds__(SEL_THREADS) void select_topk_kernel(const float* _
     for (int i = 0; i < PER; ++i) emit(i, keys[i]);
 }
 
+// The same for n <= 64 PER scores in one wave: no histogram, no barrier, no LDS.  Token 64 i + lane is key i of the lane, so
+// (i, lane) order is index order.  The threshold key is found bit by bit from the highest one in which the keys differ: a bit
+// stays set if at least k keys reach it, counted by ballots (PER compares and scalar adds); as soon as exactly k keys reach the threshold, the set
+// is known (with n distinct scores after about log2(n) + 4 bits; ties go on to the last bit and take the lowest indices).  What bounds it is the one wave's
+// issue, 12 PER cycles a bit, against ten barriers of 16 waves above.  WAVE_US
+template <int PER>
+__global__ __launch_bounds__(64) void select_topk_wave_kernel(const float* __restrict__ scores, int n, int k, int nq,
+                                                              int32_t* __restrict__ out) {
+    const int lane = threadIdx.x;
+    for (int i = lane; i < nq; i += 64) out[k + i] = n + i;   // question tokens: positions n .. n + nq - 1
+    if (k <= 0) return;                                       // (there need be no scores then)
+    uint32_t keys[PER];
+    {
+        float raw[PER];
+#pragma unroll
+        for (int i = 0; i < PER; ++i) raw[i] = scores[min(64 * i + lane, n - 1)];
+#pragma unroll
+        for (int i = 0; i < PER; ++i) keys[i] = score_key(raw[i]);
+    }
+    // keys past the end are copies of the last token's: `valid` leaves them out of every count
+    auto valid = [&](int i) { return 64 * i + lane < n; };
+    uint32_t thr = 0u, need_eq = 0u;      // taken: keys above thr, and the first need_eq that equal it
+    if (k < n) {
+        const uint32_t key0 = __builtin_amdgcn_readfirstlane(keys[0]);
+        uint32_t diff = 0u;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) diff |= keys[i] ^ key0;
+        for (int o = 32; o > 0; o >>= 1) diff |= (uint32_t)__shfl_xor((int)diff, o);
+        diff = __builtin_amdgcn_readfirstlane(diff);
+        int bit = diff ? 31 - __clz((int)diff) : -1;                       // highest bit in which two keys differ
+        thr = bit >= 31 ? 0u : bit < 0 ? key0 : key0 >> (bit + 1) << (bit + 1);
+        need_eq = (uint32_t)n;                                             // (at least k keys reach thr; all of them would be equal to it)
+        bool exact = false;
+        for (; bit >= 0 && !exact; --bit) {
+            const uint32_t cand = thr | 1u << bit;
+            int count = 0;
+#pragma unroll
+            for (int i = 0; i < PER; ++i) count += __popcll(__ballot(valid(i) && keys[i] >= cand));
+            if (count >= k) thr = cand;
+            exact = count == k;
+        }
+        int above = 0;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) above += __popcll(__ballot(valid(i) && keys[i] > thr));
+        need_eq = (uint32_t)(k - above);      // (exact: as many as there are)
+    }
+    const bool take_all = k >= n;
+    // ordered compaction
+    int pos = 0;
+    uint32_t eq_seen = 0u;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+        const bool gt = valid(i) && (take_all || keys[i] > thr), eq = valid(i) && !take_all && keys[i] == thr;
+        const uint64_t beq = __ballot(eq);
+        const bool sel = gt || (eq && eq_seen + lanes_below(beq) < need_eq);
+        const uint64_t bsel = __ballot(sel);
+        if (sel) out[pos + lanes_below(bsel)] = 64 * i + lane;
+        pos += __popcll(bsel);
+        eq_seen += (uint32_t)__popcll(beq);
+    }
+}
+
 static_assert(SELECT_ONE_WORKGROUP_MAX == (int64_t)SEL_THREADS * 32, "largest score vector of the one-workgroup kernel");
 
 hipError_t launch_select(const float* scores, int64_t n, int64_t k, int nq, int32_t* q_index, uint32_t* tmp,
                          size_t tmp_bytes, hipStream_t st) {
     if (k + nq == 0) return hipSuccess;
+    if (n > 0 && n <= 2048) {
+        const int kk = (int)std::max<int64_t>(0, std::min(k, n));
+        if (n <= 512)
+            select_topk_wave_kernel<8><<<dim3(1), dim3(64), 0, st>>>(scores, (int)n, kk, nq, q_index);
+        else if (n <= 1024)
+            select_topk_wave_kernel<16><<<dim3(1), dim3(64), 0, st>>>(scores, (int)n, kk, nq, q_index);
+        else
+            select_topk_wave_kernel<32><<<dim3(1), dim3(64), 0, st>>>(scores, (int)n, kk, nq, q_index);
+        return hipGetLastError();
+    }
     if (n <= (int64_t)SEL_THREADS * 8)
         select_topk_kernel<8><<<dim3(1), dim3(SEL_THREADS), 0, st>>>(scores, n, k, nq, q_index);
     else if (n <= (int64_t)SEL_THREADS * 16)

@@ -329,3 +329,22 @@ def test_select_rank_inside_a_histogram_bin(n, in_bin):
             torch.cuda.synchronize()
             assert np.array_equal(out.cpu().numpy(), orc.select_q_index(s, k, 1)), (ties, k)
     ctx.close()
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 511, 512, 513, 1023, 1024, 1025, 2047, 2048, 2049])
+def test_select_in_one_wave(n):
+    """Both sides of the sizes at which the selection of one wave takes another instance, or 16 waves: distinct scores, ties, one
+    value, extremes of every bit, infinities; no score at all where none is taken."""
+    ctx = H.make_ctx(synth.TINY_F32, 4096, 4, 16)
+    rng = np.random.default_rng(n)
+    inputs = {"distinct": rng.permutation(n).astype(np.float32) - n / 3, "ties": rng.integers(0, 5, size=n).astype(np.float32),
+              "constant": np.full(n, -2.5, dtype=np.float32), "extremes": rng.standard_normal(n).astype(np.float32)}
+    inputs["extremes"][rng.integers(0, n, size=4)] = [3.0e38, -3.0e38, np.inf, -np.inf]
+    for name, s in inputs.items():
+        dev = torch.from_numpy(s).cuda()
+        for k in sorted({0, 1, n // 7, n // 2, n - 1, n}):
+            out = torch.full((k + 3,), -7, dtype=torch.int32, device="cuda")
+            ctx.fr_select_topk(dev if k else None, n, k, 3, out)
+            torch.cuda.synchronize()
+            assert np.array_equal(out.cpu().numpy(), orc.select_q_index(s, k, 3)), (name, k)
+    ctx.close()
