@@ -5,15 +5,16 @@
 // the key blocks of 16 among themselves (wave w takes blocks w, w + W, ...), each with a running softmax of its own, and are
 // merged through LDS once at the end.  The shapes served here are small (verification runs of a few hundred tokens), so what
 // bounds the kernel is latency: with one wave per column tile the chip would hold a few dozen waves that walk dozens of
-// blocks each; dealt to 16 waves every wave has two or three.  S^T = K Q^T and O^T = V^T P^T with
+// blocks each; dealt to eight waves every wave has four or five.  S^T = K Q^T and O^T = V^T P^T with
 // v_mfma_f32_16x16x4_f32: keys on the register dimension of S^T, columns on lanes, and register i of the weights is
 // exactly the B operand of step i of the second product (its contraction index kg is key 4 kg + i), so the weights never
 // leave their registers.  Fresh rows are found through a position -> row map in LDS, built by the workgroup itself.
 // A weight of 0 does not take a NaN or an infinity out of a matrix product, so what a column does not see is kept out by hand:
 // keys behind the tile's last row (they may be stale or hold nothing) repeat that one, and a block that only some of the columns
 // see whole is searched for values that are not finite.
-// 4 heads, 109 rows, 544 positions, head_dim 64: 16.0 us (15.6 without the care for values that are not finite); one wave per (row, head) on the vector ALU, behind a kernel that
-// built the map: 31.5 + 2.7 us.
+// 4 heads, head_dim 64, us a call: 42 rows of 272 positions 9.3, 109 of 544 13.0, 310 of 800 16.9, 768 of 1280 24.4; with 16 waves per
+// workgroup and the values of a key as four scalar loads (11.8, 15.6, 19.1, 25.9).  Four waves are slower (11.0 .. 32.4), and so is asking for the values of the
+// next block, or of three blocks, ahead of the products (10.6 .. 28.9): more code, and the calls are short enough to be bound by fetching it.
 #include "fr_internal.hpp"
 
 #include <algorithm>
@@ -49,6 +50,9 @@ __global__ __launch_bounds__(64 * W) void attn_f32_kernel(const T* __restrict__ 
     const int g = blockIdx.x % Hkv, tile = n_tiles - 1 - blockIdx.x / Hkv;   // longest tiles first
     const int G = Hq / Hkv, cols = R * G;
     const int n = min(16 * tile + x, cols - 1), r = n / G, head = g * G + n % G;   // columns past the end: a copy of the last
+    f32x4 qv[NJ];   // dims 16 j + 4 kg + e of this lane's column
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) qv[j] = load4(q_rows + ((size_t)r * Hq + head) * D + 16 * j + 4 * kg);
     const int pos = q_index[r];
     const int p_max = q_index[min(16 * tile + 15, cols - 1) / G];   // rows ascend
     const int p_last = max(min(p_max, L - 1), 0), n_blocks = p_last / 16 + 1;   // (in bounds whatever the Q index holds)
@@ -72,14 +76,11 @@ __global__ __launch_bounds__(64 * W) void attn_f32_kernel(const T* __restrict__ 
         return f >= 0 ? fresh + ((size_t)f * Hkv + g) * D : cache + ((size_t)j * Hkv + g) * D;
     };
 
-    f32x4 qv[NJ];   // dims 16 j + 4 kg + e of this lane's column
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) qv[j] = load4(q_rows + ((size_t)r * Hq + head) * D + 16 * j + 4 * kg);
-    f32x4 o[NJ];    // O^T: dims 16 md + 4 kg + i of the column
+    f32x4 o[NJ];    // O^T: row m of product md is dim NJ m + md, so a lane's values of a key are neighbours in memory; o[md][i]: m = 4 kg + i
 #pragma unroll
     for (int md = 0; md < NJ; ++md) o[md] = f32x4{0.f, 0.f, 0.f, 0.f};
     float m = NEG_BIG, l = 0.f;
-    f32x4 kv[NJ];
+    f32x4 kv[NJ];   // key 16 b + x, dims 16 j + 4 kg + e
     auto load_k = [&](int b) {
         const T* p = row_ptr(16 * b + x, k_cache, k_new) + 4 * kg;
 #pragma unroll
@@ -87,13 +88,14 @@ __global__ __launch_bounds__(64 * W) void attn_f32_kernel(const T* __restrict__ 
     };
     if (wave < n_blocks) load_k(wave);
     for (int b = wave; b < n_blocks; b += W) {
-        float vv[4][NJ];   // values of keys 4 kg + i, dims 16 md + x
+        f32x4 vv[4][NJ / 4];   // values of keys 4 kg + i, dims NJ x ..
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const T* p = row_ptr(16 * b + 4 * kg + i, v_cache, v_new) + x;
+            const T* p = row_ptr(16 * b + 4 * kg + i, v_cache, v_new) + NJ * x;
 #pragma unroll
-            for (int md = 0; md < NJ; ++md) vv[i][md] = Elem<T>::to_f32(p[16 * md]);
+            for (int h = 0; h < NJ / 4; ++h) vv[i][h] = load4(p + 4 * h);
         }
+        auto value = [&](int i, int md) -> float { return vv[i][md >> 2][md & 3]; };
         f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {   // two chains
@@ -122,25 +124,26 @@ __global__ __launch_bounds__(64 * W) void attn_f32_kernel(const T* __restrict__ 
 #pragma unroll
         for (int md = 0; md < NJ; ++md) o[md] *= alpha;
         if (16 * b + 15 > p_first) {   // values that are not finite: out of the product, into the columns that see them
-            bool odd = false;
+            float z = 0.f;   // NaN if one of them is not finite
 #pragma unroll
             for (int i = 0; i < 4; ++i)
 #pragma unroll
-                for (int md = 0; md < NJ; ++md) odd = odd || !(fabsf(vv[i][md]) < INFINITY);
-            if (__any(odd)) {
+                for (int md = 0; md < NJ; ++md) z = __builtin_fmaf(value(i, md), 0.f, z);
+            const bool odd = !(z == 0.f);
+            if (__builtin_expect(__any(odd), 0)) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
 #pragma unroll
                     for (int md = 0; md < NJ; ++md) {
-                        const bool finite = fabsf(vv[i][md]) < INFINITY;
-                        const float apart = finite ? 0.f : vv[i][md];
-                        if (!finite) vv[i][md] = 0.f;
+                        const bool finite = fabsf(value(i, md)) < INFINITY;
+                        const float apart = finite ? 0.f : value(i, md);
+                        if (!finite) vv[i][md >> 2][md & 3] = 0.f;
                         for (int src = 0; src < 4; ++src) {   // key 4 src + i of the block
                             const bool seen = 16 * b + 4 * src + i <= pos;
                             const float weight = __shfl(p[i], 16 * src + x);
 #pragma unroll
                             for (int e = 0; e < 4; ++e) {
-                                const float v = __shfl(apart, 16 * src + 4 * kg + e);   // dim 16 md + 4 kg + e
+                                const float v = __shfl(apart, 16 * src + 4 * kg + e);   // row 4 kg + e of the product
                                 if (seen && v != 0.f) o[md][e] += weight * v;
                             }
                         }
@@ -150,7 +153,7 @@ __global__ __launch_bounds__(64 * W) void attn_f32_kernel(const T* __restrict__ 
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
-            for (int md = 0; md < NJ; ++md) o[md] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[i][md], p[i], o[md], 0, 0, 0);
+            for (int md = 0; md < NJ; ++md) o[md] = __builtin_amdgcn_mfma_f32_16x16x4f32(value(i, md), p[i], o[md], 0, 0, 0);
     }
     // ---- merge the waves ---------------------------------------------------------------------------------------------
     l = column_sum(l);
@@ -160,7 +163,10 @@ __global__ __launch_bounds__(64 * W) void attn_f32_kernel(const T* __restrict__ 
     for (int w = 0; w < W; ++w) M = fmaxf(M, m_lds[w][x]);
     const float f = __builtin_amdgcn_exp2f(m - M);   // (a wave without a visible key: m = NEG_BIG, factor 0)
 #pragma unroll
-    for (int md = 0; md < NJ; ++md) *reinterpret_cast<f32x4*>(&o_lds[wave][x][16 * md + 4 * kg]) = o[md] * f;
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int h = 0; h < NJ / 4; ++h)
+            *reinterpret_cast<f32x4*>(&o_lds[wave][x][NJ * (4 * kg + i) + 4 * h]) = f32x4{o[4 * h][i], o[4 * h + 1][i], o[4 * h + 2][i], o[4 * h + 3][i]} * f;
     __syncthreads();
     for (int i = tid; i < 16 * D; i += 64 * W) {
         const int c = i / D, e = i % D, nc = 16 * tile + c;
@@ -208,9 +214,9 @@ hipError_t launch_attn_f32(const Shape& s, const void* q_rows, const int32_t* q_
                                                             (int)L, (const T*)k_new, (const T*)v_new, inv, (T*)out, lse, s.Hq, \
                                                             s.Hkv, n_tiles, scale_log2e)
     if (s.dtype == FR_BF16) {
-        if (s.d == 64) FR_ATTN_LAUNCH(__bf16, 64, 16); else FR_ATTN_LAUNCH(__bf16, 128, 8);
+        if (s.d == 64) FR_ATTN_LAUNCH(__bf16, 64, 8); else FR_ATTN_LAUNCH(__bf16, 128, 8);
     } else {
-        if (s.d == 64) FR_ATTN_LAUNCH(float, 64, 16); else FR_ATTN_LAUNCH(float, 128, 8);
+        if (s.d == 64) FR_ATTN_LAUNCH(float, 64, 8); else FR_ATTN_LAUNCH(float, 128, 8);
     }
 #undef FR_ATTN_LAUNCH
     return hipGetLastError();
