@@ -622,8 +622,7 @@ fr_status fr_sparse_prefill_attn_shared(fr_ctx* ctx, const void* q_rows, const i
         if (e != hipSuccess) return hip_fail(ctx, "attention launch", e);
         return FR_OK;
     }
-    e = launch_rope_table(s, dl, n_chunks, ctx->ws.rope_theta, ctx->ws.rope_table, hs);
-    if (e != hipSuccess) return hip_fail(ctx, "rope table launch", e);
+    sh.deltas = &dl;
     sh.table = ctx->ws.rope_table;
     e = launch_attn_mfma(s, q_rows, q_index, R, k_store, v_store, L, k_new, v_new, out, lse_out, ctx->ws,
                          ctx->attn_softmax_mode, ctx->attn_split_mode, &sh, &ctx->attn_timer, false, hs);
@@ -728,10 +727,8 @@ fr_status fr_sparse_prefill_attn_shared_batch(fr_ctx* ctx, const fr_shared_query
             SharedBatchQuery& w = work[i];
             const BatchScratch b = batch_scratch(s, w.L, off);
             off = b.end;
-            float2* table = reinterpret_cast<float2*>(base + b.table);
-            hipError_t e = launch_rope_table(s, deltas[i], w.shared.ct.n, ctx->ws.rope_theta, table, hs);
-            if (e != hipSuccess) return hip_fail(ctx, "rope table launch", e);
-            w.shared.table = table;
+            w.shared.deltas = &deltas[i];
+            w.shared.table = reinterpret_cast<float2*>(base + b.table);
             w.store_row_map = reinterpret_cast<int32_t*>(base + b.srow);
             w.chunk_id_map = reinterpret_cast<int32_t*>(base + b.cid);
             w.images = base + b.images;

@@ -172,12 +172,14 @@ hipError_t launch_decode_attn(const Shape& s, const DecodeArgs& a, float* partia
 hipError_t launch_mark_stale(uint32_t* bits, int64_t n_words, const int32_t* rows, int n_rows, int clear, hipStream_t st);
 
 // When given to launch_attn_mfma, k_cache / v_cache are a chunk store shared between queries: prompt position
-// j in [ct.off[c], ct.off[c+1]) reads store row store_row0[c] + j - ct.off[c], its key rotated by the chunk's
-// (cos, sin) row of `table` (device, [chunks][d/2]); store_row0 is a host array.
+// j in [ct.off[c], ct.off[c+1]) reads store row store_row0[c] + j - ct.off[c], its key rotated by deltas->delta[c]
+// positions; the launch leaves the chunks' (cos, sin) rows in `table` (device scratch, [chunks][d/2]).  store_row0 and
+// deltas are on the host.
 struct SharedStoreArgs {
     ChunkTable ct;
     const int32_t* store_row0;
-    const float2* table;
+    const ChunkDeltas* deltas;
+    float2* table;
 };
 
 hipError_t launch_attn_f32(const Shape& s, const void* q_rows, const int32_t* q_index, int R, const void* k_cache,
@@ -197,7 +199,7 @@ constexpr int ATTN_MAX_BATCH = 16;
 struct SharedBatchQuery {
     const void* q_rows; const int32_t* q_index; int R; int64_t L;
     const void* k_new; const void* v_new; void* out; float* lse;
-    SharedStoreArgs shared;          // chunk table, store rows (host), rotation table (device)
+    SharedStoreArgs shared;          // chunk table, store rows and deltas (host), rotation table (device scratch)
     int32_t* store_row_map; int32_t* chunk_id_map;   // device [L] each
     unsigned char* images; size_t images_bytes;
 };

@@ -294,12 +294,17 @@ __global__ __launch_bounds__(256) void pack_kv_images_kernel(const __bf16* k_cac
 // fresh rows instead, so the store's stale entries of those tokens are never read and no per-query copy of the
 // cache exists.  Positions >= L_ctx that are not in the Q index have no data: they read as zero.
 
-// Prompt position -> (store row, chunk) for the packing kernel, so that it needs no search and no dependent loads:
-// grid (position tiles of the longest chunk, chunks + 1); the extra y index covers the positions behind the context
-// (no store row: -1).
-__global__ __launch_bounds__(256) void prompt_map_kernel(ChunkTable ct, ChunkRows rows, int L,
-                                                         int32_t* __restrict__ store_row, int32_t* __restrict__ chunk_id) {
+// Prompt position -> (store row, chunk) for the packing kernel, so that it needs no search and no dependent loads, and
+// the chunks' (cos, sin) rows, in one launch: grid (position tiles of the longest chunk, chunks + 1); the extra y index
+// covers the positions behind the context (no store row: -1).  A query's chunk tables fill most of the 4 KB of kernel
+// arguments, so a batch launches this once per query
+// (a kernel for the rotations and one for the maps: 3 + 2 us and a gap more per query; one launch 3 us).
+__global__ __launch_bounds__(256) void prompt_tables_kernel(ChunkTable ct, ChunkRows rows, ChunkDeltas deltas, int L, int half_d,
+                                                            const double* __restrict__ theta, float2* __restrict__ table,
+                                                            int32_t* __restrict__ store_row, int32_t* __restrict__ chunk_id) {
     const int c = blockIdx.y;
+    if (blockIdx.x == 0 && c < ct.n && (int)threadIdx.x < half_d)
+        table[(size_t)c * half_d + threadIdx.x] = chunk_rotation(deltas.delta[c], theta[threadIdx.x]);
     const int begin = (c < ct.n) ? ct.off[c] : ct.off[ct.n];
     const int end = (c < ct.n) ? ct.off[c + 1] : L;
     for (int j = begin + blockIdx.x * 256 + threadIdx.x; j < end; j += gridDim.x * 256) {
@@ -308,20 +313,31 @@ __global__ __launch_bounds__(256) void prompt_map_kernel(ChunkTable ct, ChunkRow
     }
 }
 
+// Every query of a batch in one launch: grid (key tiles of the longest prompt x KV heads, queries).  One
+// query's images are a few hundred workgroups, less than the chip holds: 4 queries of 1264 positions, selections and
+// attention, 178 us with a launch each, 155 with one; 8 of 4064 positions 523 -> 481; 8 of 16896 4425 -> 4350.
+struct SharedPackQuery {
+    const __bf16 *k_new, *v_new;
+    const int32_t *q_index, *store_row, *chunk_id;
+    const float2* table;
+    unsigned char* images;
+    int32_t R, L, n_img_tiles, pad;
+};
+struct SharedPackBatch { SharedPackQuery q[ATTN_MAX_BATCH]; };
 template <int LAYOUT>
-__global__ __launch_bounds__(256) void pack_kv_images_shared_kernel(const __bf16* __restrict__ k_store,
-                                                                    const __bf16* __restrict__ v_store,
-                                                                    const int32_t* __restrict__ store_row,
-                                                                    const int32_t* __restrict__ chunk_id,
-                                                                    const float2* __restrict__ table,
-                                                                    int L, const __bf16* __restrict__ k_new,
-                                                                    const __bf16* __restrict__ v_new,
-                                                                    const int32_t* __restrict__ q_index, int R, int Hkv,
-                                                                    int n_img_tiles, unsigned char* __restrict__ images) {
+__global__ __launch_bounds__(256) void pack_kv_images_shared_kernel(const SharedPackBatch batch, const __bf16* __restrict__ k_store,
+                                                                    const __bf16* __restrict__ v_store, int Hkv) {
     constexpr int D = 128;
     __shared__ __attribute__((aligned(16))) unsigned char img[Img<D>::BYTES];
     __shared__ int32_t fresh[KT];
+    const SharedPackQuery& pq = batch.q[blockIdx.y];
     const int kt = blockIdx.x / Hkv, g = blockIdx.x % Hkv;   // as in the attention kernels: the workgroups of a KV head on one XCD
+    const int L = pq.L, R = pq.R, n_img_tiles = pq.n_img_tiles;
+    if (kt >= n_img_tiles) return;   // a shorter prompt
+    const __bf16 *__restrict__ k_new = pq.k_new, *__restrict__ v_new = pq.v_new;
+    const int32_t *__restrict__ q_index = pq.q_index, *__restrict__ store_row = pq.store_row, *__restrict__ chunk_id = pq.chunk_id;
+    const float2* __restrict__ table = pq.table;
+    unsigned char* __restrict__ images = pq.images;
     const PackShare<D> ps;
     const int st_vec = ps.vec, st_key = ps.key;
     const u32x4 zero = {0u, 0u, 0u, 0u};
@@ -1333,11 +1349,13 @@ hipError_t set_kernel_attributes() {
     return once;
 }
 
-// Packing pass of one query: tile images of its effective K/V into sc.images; fills the query's line of the table.
+// Packing pass of one query: tile images of its effective K/V into sc.images; fills the query's line of the table.  With
+// `shared` it only makes the query's maps and its line of the packing launch (`pq`), which pack_shared sends for all.
 template <int D>
 hipError_t pack_query(const Shape& s, const void* q_rows, const int32_t* q_index, int R, const void* k_cache,
                       const void* v_cache, int64_t L, const void* k_new, const void* v_new, void* out, float* lse,
-                      const QueryScratch& sc, const SharedStoreArgs* shared, bool writeback, AttnQuery* aq, hipStream_t st) {
+                      const QueryScratch& sc, const SharedStoreArgs* shared, const double* theta, bool writeback, AttnQuery* aq,
+                      SharedPackQuery* pq, hipStream_t st) {
     const int TR = 4 * (64 / s.G);   // token rows per workgroup
     const int n_row_tiles = (R + TR - 1) / TR;
     const int n_img_tiles = (int)((L + KT - 1) / KT);
@@ -1359,16 +1377,10 @@ hipError_t pack_query(const Shape& s, const void* q_rows, const int32_t* q_index
             rows.row0[c] = shared->store_row0[c];
             max_len = std::max(max_len, shared->ct.off[c + 1] - shared->ct.off[c]);
         }
-        prompt_map_kernel<<<dim3(std::max(1, (max_len + 255) / 256), shared->ct.n + 1), block, 0, st>>>(
-            shared->ct, rows, (int)L, sc.store_row_map, sc.chunk_id_map);
-        if (s.rope_layout == FR_ROPE_INTERLEAVED)
-            pack_kv_images_shared_kernel<FR_ROPE_INTERLEAVED><<<dim3(n_img_tiles * s.Hkv), block, 0, st>>>(
-                (const __bf16*)k_cache, (const __bf16*)v_cache, sc.store_row_map, sc.chunk_id_map, shared->table, (int)L,
-                (const __bf16*)k_new, (const __bf16*)v_new, q_index, R, s.Hkv, n_img_tiles, sc.images);
-        else
-            pack_kv_images_shared_kernel<FR_ROPE_HALF><<<dim3(n_img_tiles * s.Hkv), block, 0, st>>>(
-                (const __bf16*)k_cache, (const __bf16*)v_cache, sc.store_row_map, sc.chunk_id_map, shared->table, (int)L,
-                (const __bf16*)k_new, (const __bf16*)v_new, q_index, R, s.Hkv, n_img_tiles, sc.images);
+        prompt_tables_kernel<<<dim3(std::max(1, (max_len + 255) / 256), shared->ct.n + 1), block, 0, st>>>(
+            shared->ct, rows, *shared->deltas, (int)L, D / 2, theta, shared->table, sc.store_row_map, sc.chunk_id_map);
+        *pq = {(const __bf16*)k_new, (const __bf16*)v_new, q_index, sc.store_row_map, sc.chunk_id_map, shared->table, sc.images,
+               R, (int)L, n_img_tiles, 0};
     } else {
         return hipErrorInvalidValue;   // (such shapes gather the query's keys and values first)
     }
@@ -1381,6 +1393,18 @@ hipError_t pack_query(const Shape& s, const void* q_rows, const int32_t* q_index
     aq->n_row_tiles = n_row_tiles;
     aq->n_img_tiles = n_img_tiles;
     aq->pad = 0;
+    return hipGetLastError();
+}
+
+// The packing launch of n queries over a shared chunk store.
+hipError_t pack_shared(const Shape& s, int n, const SharedPackBatch& pb, const void* k_store, const void* v_store, hipStream_t st) {
+    int tiles = 0;
+    for (int i = 0; i < n; ++i) tiles = std::max(tiles, pb.q[i].n_img_tiles);
+    const dim3 grid(tiles * s.Hkv, n), block(256);
+    if (s.rope_layout == FR_ROPE_INTERLEAVED)
+        pack_kv_images_shared_kernel<FR_ROPE_INTERLEAVED><<<grid, block, 0, st>>>(pb, (const __bf16*)k_store, (const __bf16*)v_store, s.Hkv);
+    else
+        pack_kv_images_shared_kernel<FR_ROPE_HALF><<<grid, block, 0, st>>>(pb, (const __bf16*)k_store, (const __bf16*)v_store, s.Hkv);
     return hipGetLastError();
 }
 
@@ -1464,7 +1488,10 @@ hipError_t launch(const Shape& s, const void* q_rows, const int32_t* q_index, in
     const QueryScratch sc{ws.store_row_map, ws.chunk_id_map, ws.kv_images, ws.kv_images_bytes};
     AttnBatch batch;
     batch.n = 1;
-    e = pack_query<D>(s, q_rows, q_index, R, k_cache, v_cache, L, k_new, v_new, out, lse, sc, shared, writeback, &batch.q[0], st);
+    SharedPackBatch pb;
+    e = pack_query<D>(s, q_rows, q_index, R, k_cache, v_cache, L, k_new, v_new, out, lse, sc, shared, ws.rope_theta, writeback,
+                      &batch.q[0], &pb.q[0], st);
+    if (e == hipSuccess && shared != nullptr) e = pack_shared(s, 1, pb, k_cache, v_cache, st);
     if (e != hipSuccess) return e;
     batch.max_row_tiles = batch.q[0].n_row_tiles;
     bool half = half_parts<SPLIT>(batch.q[0].n_img_tiles);
@@ -1491,16 +1518,19 @@ hipError_t launch_shared_batch(const Shape& s, int n, const SharedBatchQuery* qs
     batch.max_row_tiles = 0;
     const size_t slot = part_bytes<D>(false);   // partial results of a batch stay fp32
     int n_parts = 1;
+    SharedPackBatch pb;
     for (int i = 0; i < n; ++i) {
         const SharedBatchQuery& q = qs[i];
         const QueryScratch sc{q.store_row_map, q.chunk_id_map, q.images, q.images_bytes};
         e = pack_query<D>(s, q.q_rows, q.q_index, q.R, k_store, v_store, q.L, q.k_new, q.v_new, q.out, q.lse, sc, &q.shared,
-                          false, &batch.q[i], st);
+                          ws.rope_theta, false, &batch.q[i], &pb.q[i], st);
         if (e != hipSuccess) return e;
         batch.max_row_tiles = std::max(batch.max_row_tiles, batch.q[i].n_row_tiles);
         n_parts = std::max(n_parts, choose_parts(split_mode, batch.q[i].n_row_tiles * s.Hkv, batch.q[i].n_img_tiles, ws.n_cu,
                                                  slot, ws.attn_partials_bytes));
     }
+    e = pack_shared(s, n, pb, k_store, v_store, st);
+    if (e != hipSuccess) return e;
     // A batch of queries usually fills the chip by itself: every item whole, one workgroup each.  Up to a quarter of a
     // workgroup per compute unit it is cut like its queries would be alone; in between like one query of as many items.
     const int items = batch.max_row_tiles * n * s.Hkv;

@@ -2,17 +2,9 @@
 // rotated by Delta_c positions.  HBM-bound streaming: 16-byte loads and stores; a workgroup forms its chunk's (cos, sin)
 // row in fp64 itself.  880 tokens of 2 KB: 5.9 us, with a kernel that made a table of them in front 2.8 + 5.3; 16384
 // tokens: 15.2 us, before 4.7 + 14.1; 32 layers of them 0.39 ms = 5.5 TB/s either way.
-#include "fr_internal.hpp"
+#include "k_rotate.hpp"
 
 namespace fr {
-
-// (cos, sin)(Delta * theta_p), in fp64, rounded once to fp32.  Delta reaches tens of thousands of positions, so the angle
-// is formed and reduced in double precision.
-__device__ __forceinline__ float2 chunk_rotation(int32_t delta, double theta) {
-    double sn, cs;
-    sincos_reduced((double)delta * theta, &sn, &cs);
-    return make_float2((float)cs, (float)sn);
-}
 
 // table[c][p], theta: [half_d] rotary frequencies
 __global__ void rope_table_kernel(ChunkDeltas deltas, int half_d, const double* __restrict__ theta, float2* __restrict__ table) {

@@ -7,6 +7,14 @@
 
 namespace fr {
 
+// (cos, sin)(Delta * theta_p), in fp64, rounded once to fp32.  Delta reaches tens of thousands of positions, so the angle
+// is formed and reduced in double precision.
+__device__ __forceinline__ float2 chunk_rotation(int32_t delta, double theta) {
+    double sn, cs;
+    sincos_reduced((double)delta * theta, &sn, &cs);
+    return make_float2((float)cs, (float)sn);
+}
+
 typedef __attribute__((ext_vector_type(4))) uint32_t rot_u32x4;
 
 // own = elements N vec .. N vec + N - 1 of the head row (N = 16 / sizeof(T)).  Interleaved pairs: (2p, 2p + 1) inside the

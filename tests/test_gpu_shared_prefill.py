@@ -307,6 +307,43 @@ def test_shared_store_batch_in_parts(name, split):
     ctx.close()
 
 
+@pytest.mark.parametrize("layout", [B.FR_ROPE_INTERLEAVED, B.FR_ROPE_HALF])
+@pytest.mark.parametrize("n", [1, 16, 17])
+def test_shared_store_batch_of_every_size(n, layout):
+    """One packing launch for up to 16 queries of 1 to 8 key tiles, a 17th in a launch of its own: every query as alone, bit for
+    bit (the key-range split off: same kernels, same order of summation)."""
+    shape = synth.LayerShape(n_q_heads=8, n_kv_heads=2, head_dim=128, dtype="bf16", rope_base=500000.0)
+    base = synth.config_small_bf16(seed=5, chunk_lens=(200, 64, 63, 91, 1, 130), shape=shape)
+    rng = np.random.default_rng(n)
+    k_store, v_store, row0_all = scattered_store(base, rng)
+    ks_d, vs_d = H.dev(k_store, "bf16"), H.dev(v_store, "bf16")
+    chunk_len = np.diff(base.chunk_offsets)
+    ctx = H.make_ctx(shape, base.L + 64, base.n_chunks, 64, rope_layout=layout)
+    ctx.fr_set_option(B.FR_OPT_ATTN_SPLIT, B.FR_ATTN_SPLIT_OFF)
+    queries = []
+    for i in range(n):
+        chunks = rng.permutation(base.n_chunks)[:1 + i % base.n_chunks]
+        offs = np.concatenate([[0], np.cumsum([int(chunk_len[c]) for c in chunks])]).astype(np.int32)
+        nq, L_ctx = 1 + 3 * i, int(offs[-1])
+        qi = np.concatenate([np.sort(rng.choice(L_ctx, size=L_ctx // 5, replace=False)), L_ctx + np.arange(nq)]).astype(np.int32)
+        R = len(qi)
+        mk = lambda heads: torch.from_numpy(rng.standard_normal((R, heads, 128)).astype(np.float32)).to(torch.bfloat16).cuda()
+        queries.append(dict(q_rows=mk(8), q_index=torch.from_numpy(qi).cuda(), R=R, chunk_offsets=offs, chunk_store_row0=row0_all[chunks],
+                            chunk_src_pos0=rng.integers(0, 3000, size=len(chunks)).astype(np.int32), L=L_ctx + nq, k_new=mk(2), v_new=mk(2),
+                            out=torch.zeros((R, 8, 128), dtype=torch.bfloat16, device="cuda"),
+                            lse_out=torch.zeros((R, 8), dtype=torch.float32, device="cuda")))
+    ws = torch.empty(ctx.fr_shared_batch_workspace_bytes(n, max(q["L"] for q in queries)), dtype=torch.uint8, device="cuda")
+    ctx.fr_sparse_prefill_attn_shared_batch(queries, ks_d, vs_d, len(k_store), ws)
+    for q in queries:
+        single, single_lse = torch.zeros_like(q["out"]), torch.zeros_like(q["lse_out"])
+        ctx.fr_sparse_prefill_attn_shared(q["q_rows"], q["q_index"], q["R"], ks_d, vs_d, len(k_store), q["chunk_offsets"],
+                                          q["chunk_store_row0"], q["chunk_src_pos0"], q["L"], q["k_new"], q["v_new"], single, single_lse)
+        torch.cuda.synchronize()
+        assert torch.equal(single, q["out"]) and torch.equal(single_lse, q["lse_out"])
+        assert float(q["out"].abs().sum()) > 0
+    ctx.close()
+
+
 def test_shared_store_batch_full_size_sampled():
     """The launch configuration `bench.py --config 8` times (Llama-3-8B layer shape, queries of 16 chunks x 1024 tokens
     drawn from a 32-chunk store, 512 question tokens, 15 %), three queries per call: sampled output rows against the
