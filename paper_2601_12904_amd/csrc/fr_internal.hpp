@@ -208,7 +208,7 @@ hipError_t launch_attn_mfma_shared_batch(const Shape& s, int n, const SharedBatc
                                          const void* v_store, const Workspace& ws, int softmax_mode, int split_mode, struct KernelTimer* timer,
                                          hipStream_t st);
 // An attention launch with few (row tile, KV head) items deals every item's key tiles to several workgroups
-// (parts), on its own up to ATTN_SPLIT_AUTO_ITEMS items (beyond that the items alone keep the chip busy and the partial
+// (parts), on its own up to ATTN_SPLIT_AUTO_ITEMS items at most (beyond that the items alone keep the chip busy and the partial
 // results' traffic costs more than the better balance gains): two parts, more (up to ATTN_MAX_PARTS) while that still
 // leaves at most one piece per compute unit.  FR_ATTN_SPLIT_ON asks for two parts at any size the partial-result buffer
 // takes.

@@ -1425,26 +1425,33 @@ void launch_tile_loop(const AttnBatch& batch, dim3 grid, float* partials, int n_
 
 // Parts per item of a one-query launch of `items` (row tile, KV head) items over n_img_tiles key tiles.  With few items
 // the chip would idle behind the longest ones (rows ascend by position: the question rows' tiles walk the whole prompt),
-// so every item's key tiles are dealt to several workgroups.  Measured on a 17k-token prompt (256 compute units, one
-// workgroup each): two parts pay up to about 400 items (recompute ratios up to 15 %; at 30 %, 680 items, the partial
-// results' traffic and the combine pass cost more than the balance gains); below half a workgroup per compute unit more
-// parts pay until there is about one piece per compute unit (question-only prefill, 64 items: 4 parts, 0.24 -> 0.17 ms);
-// in between two parts stay best (168 items at 5 %, 128 items of the offline stage: three or four parts lose 3-15 %).
-// Short prompts (under 32 key tiles) are cut only below half a workgroup per compute unit, down to two tiles a part: a tile
-// is 1.8 us of a workgroup, the combine pass 7.5 us (920 tokens, 24 items of up to 15 tiles: 31 us whole, 14 + 7.5 in eight parts).
+// so every item's key tiles are dealt to several workgroups, at the price of the partial results' traffic and the combine pass.
+// Two parts pay up to AUTO_ITEMS items (256 compute units, one workgroup each; both sides measured per layer).  Plain weights: 17k
+// tokens, 512 of them the question's: 288 items 492 us whole, 472 in two parts, 336 512 both, 376 518 : 539; 1024 of the question:
+// 320 items 614 : 635; 8k tokens: 288 items 222 : 213, 320 229 : 228 and 277 : 282, 352 284 : 297; 33k tokens: 296 items 1231 : 1265.
+// Split weights, twice the matrix work on a tile of the same partial results: 17k tokens of seven heads per KV head 340 items
+// 777 : 742, 388 805 : 811.
+// Below half a workgroup per compute unit more parts pay until there is about one piece per compute unit (question-only prefill, 64
+// items: 446 us whole, 302, 253, 244, 277, 268 in two, three, four, six, eight parts); in between two parts stay best (168 items at
+// 5 %: 359 us, 388 and 373 in three and four).  Short prompts (under 32 key tiles) are cut only below half a workgroup per compute
+// unit, down to two tiles a part: a tile is 1.1 us of a workgroup, the combine pass 7.1 us (920 tokens, 24 items of up to 15 tiles:
+// 30.2 us whole, 18.1 + 7.1 in eight parts).
+template <bool SPLIT>
+constexpr int AUTO_ITEMS = SPLIT ? ATTN_SPLIT_AUTO_ITEMS : 320;
+template <bool SPLIT>
 int choose_parts(int split_mode, int items, int n_img_tiles, int n_cu, size_t part_bytes, size_t partials_bytes) {
     int parts = 1;
     if (split_mode == FR_ATTN_SPLIT_ON) parts = 2;
     if (split_mode == FR_ATTN_SPLIT_AUTO) {
         if (2 * items <= n_cu) parts = std::min({ATTN_MAX_PARTS, n_cu / std::max(items, 1), (n_img_tiles + 1) / 2});
-        if (n_img_tiles >= 32 && items <= ATTN_SPLIT_AUTO_ITEMS) parts = std::max(parts, 2);
+        if (n_img_tiles >= 32 && items <= AUTO_ITEMS<SPLIT>) parts = std::max(parts, 2);
     }
     while (parts > 1 && (size_t)items * parts * part_bytes > partials_bytes) --parts;
     return parts;
 }
 
 // Half-precision partial results: only for a single query of a long prompt (32 key tiles and more) whose weights are plain
-// bf16, where 400 items in two parts would otherwise move 2 x 108 MB of partial sums (combine pass 21.1 us, 15.5 us in half
+// bf16, where 376 items in two parts would otherwise move 2 x 108 MB of partial sums (combine pass 21.1 us, 15.5 us in half
 // precision).  Short prompts, batches and more than four parts, a few hundred pieces at most, keep all 32 bits
 // (6730 tokens, 32 items: 2.174e-3 off float64 in eight parts, 2.184e-3 in four of half precision; the layer takes 163 us, 159 in
 // eight of half precision, 183 in four).
@@ -1496,7 +1503,7 @@ hipError_t launch(const Shape& s, const void* q_rows, const int32_t* q_index, in
     batch.max_row_tiles = batch.q[0].n_row_tiles;
     bool half = half_parts<SPLIT>(batch.q[0].n_img_tiles);
     auto parts_of = [&](bool h) {
-        return choose_parts(split_mode, batch.q[0].n_row_tiles * s.Hkv, batch.q[0].n_img_tiles, ws.n_cu, part_bytes<D>(h),
+        return choose_parts<SPLIT>(split_mode, batch.q[0].n_row_tiles * s.Hkv, batch.q[0].n_img_tiles, ws.n_cu, part_bytes<D>(h),
                             ws.attn_partials_bytes);
     };
     int n_parts = parts_of(half);
@@ -1526,8 +1533,8 @@ hipError_t launch_shared_batch(const Shape& s, int n, const SharedBatchQuery* qs
                           ws.rope_theta, false, &batch.q[i], &pb.q[i], st);
         if (e != hipSuccess) return e;
         batch.max_row_tiles = std::max(batch.max_row_tiles, batch.q[i].n_row_tiles);
-        n_parts = std::max(n_parts, choose_parts(split_mode, batch.q[i].n_row_tiles * s.Hkv, batch.q[i].n_img_tiles, ws.n_cu,
-                                                 slot, ws.attn_partials_bytes));
+        n_parts = std::max(n_parts, choose_parts<SPLIT>(split_mode, batch.q[i].n_row_tiles * s.Hkv, batch.q[i].n_img_tiles,
+                                                        ws.n_cu, slot, ws.attn_partials_bytes));
     }
     e = pack_shared(s, n, pb, k_store, v_store, st);
     if (e != hipSuccess) return e;
@@ -1536,7 +1543,7 @@ hipError_t launch_shared_batch(const Shape& s, int n, const SharedBatchQuery* qs
     const int items = batch.max_row_tiles * n * s.Hkv;
     int tiles = 0;
     for (int i = 0; i < n; ++i) tiles = std::max(tiles, batch.q[i].n_img_tiles);
-    if (4 * items > ws.n_cu) n_parts = choose_parts(split_mode, items, tiles, ws.n_cu, slot, ws.attn_partials_bytes);
+    if (4 * items > ws.n_cu) n_parts = choose_parts<SPLIT>(split_mode, items, tiles, ws.n_cu, slot, ws.attn_partials_bytes);
     while (n_parts > 1 && (size_t)items * n_parts * slot > ws.attn_partials_bytes) --n_parts;
     return launch_packed<G, D, SPLIT>(s, batch, n_parts, false, ws, mode, timer, st);
 }

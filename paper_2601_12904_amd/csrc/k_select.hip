@@ -11,7 +11,7 @@
 // most exponent bits agree), which would pile a plain histogram onto one or two bins; the digits are therefore
 // taken from key - min(key), starting at the highest bit in which the largest and the smallest key differ.  Even so most scores lie near the smallest
 // one: with 256 bins the adds of a wave queued up behind one LDS word, and every pass costs its barriers and scans (four
-// passes of 8 bits: 9.6 / 19.5 / 33.0 us at 880 / 16384 / 32768 scores of a prompt, now 8.1 / 14.7 / 25.2; taking all
+// passes of 8 bits: 9.6 / 19.5 / 33.0 us at 880 / 16384 / 32768 scores of a prompt, now 8.1 / 14.7 / 25.2 in this kernel; up to 2048 scores take the one-wave kernel below; taking all
 // of 16384, without any search, is 8.1).
 #include "fr_internal.hpp"
 
@@ -214,7 +214,8 @@ __global__ __launch_bounds__(SEL_THREADS) void select_topk_kernel(const float* _
 // (i, lane) order is index order.  The threshold key is found bit by bit from the highest one in which the keys differ: a bit
 // stays set if at least k keys reach it, counted by ballots (PER compares and scalar adds); as soon as exactly k keys reach the threshold, the set
 // is known (with n distinct scores after about log2(n) + 4 bits; ties go on to the last bit and take the lowest indices).  What bounds it is the one wave's
-// issue, 12 PER cycles a bit, against ten barriers of 16 waves above.  WAVE_US
+// issue, 12 PER cycles a bit, against ten barriers of 16 waves above: 512 scores
+// 8.2 -> 3.1 us, 880 8.6 -> 6.6; beyond 2048 scores, 32 keys a lane, the wave would take longer than the workgroup.
 template <int PER>
 __global__ __launch_bounds__(64) void select_topk_wave_kernel(const float* __restrict__ scores, int n, int k, int nq,
                                                               int32_t* __restrict__ out) {

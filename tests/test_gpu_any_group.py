@@ -308,6 +308,25 @@ def test_parts_in_half_precision_and_in_32_bits(Hq, Hkv, rows, split, parts, key
         assert off <= 2.5e-3 and (runaway or off > 2e-4)
 
 
+@pytest.mark.parametrize("rows,parts", [(1280, 2), (1281, 1)])
+def test_where_items_stay_whole(rows, parts):
+    """40 row tiles of 32 rows and 8 KV heads, 320 items, are the last to be cut in two by themselves (half-precision sums: the bound
+    above); one row more and every item is whole, bit for bit the result with the cutting off."""
+    shape = synth.LayerShape(n_q_heads=64, n_kv_heads=8, head_dim=128, dtype="bf16", rope_base=500000.0)
+    L, nq = 64 * 33 - 5, 40
+    w = synth.config_small_bf16(seed=3, chunk_lens=(L - nq,), nq=nq, shape=shape)
+    qi = np.concatenate([np.sort(np.random.default_rng(1).choice(L - nq, size=rows - nq, replace=False)), np.arange(L - nq, L)])
+    k_cache, v_cache = assembled_cache(w, w.k_cached)
+    outs = []
+    for mode in (B.FR_ATTN_SPLIT_OFF, B.FR_ATTN_SPLIT_AUTO):
+        ctx = H.make_ctx(shape, L, 1, nq)
+        ctx.fr_set_option(B.FR_OPT_ATTN_SPLIT, mode)
+        outs.append(run_attention(ctx, w, qi, k_cache, v_cache)[0])
+        ctx.close()
+    off = np.linalg.norm(outs[1] - outs[0]) / np.linalg.norm(outs[0])
+    assert off == 0.0 if parts == 1 else 2e-4 < off <= 2.5e-3
+
+
 @pytest.mark.parametrize("in_bin", [1, 2, 255, 256, 257, 300])
 @pytest.mark.parametrize("n", [900, 8193, 32768])
 def test_select_rank_inside_a_histogram_bin(n, in_bin):
