@@ -134,7 +134,7 @@ def _ptr(t) -> Optional[int]:
 def _i32_array(values: Optional[Sequence[int]]):
     if values is None:
         return None
-    a = np.ascontiguousarray(values, dtype=np.int32)
+    a = np.ascontiguousarray(np.asarray(values), dtype=np.int32)
     # (keep `a` alive during the call; a.ctypes.data_as() is three times as slow)
     return ctypes.pointer(ctypes.c_int32.from_address(a.__array_interface__["data"][0])), a
 
