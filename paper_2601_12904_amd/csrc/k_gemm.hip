@@ -68,7 +68,9 @@ struct Tiling {
     // What a launch takes (plan_tiling): time per K tile of a full round, the share of it that a nearly empty round still
     // takes (a full round is held back by the chip's power limit), launch, pipeline fill and epilogue, a split last round.
     // Chosen so that the better of the two tilings is taken: over 742 products (N 256 .. 28672, K 128 .. 14336, 1 .. 4096
-    // rows) the choice is 0.2 % slower than the faster one on average.  Two K tiles of many features are its worst (9 %).
+    // rows) the choice was 0.2 % slower than the faster one on average, two K tiles of many features its worst (9 %).  The 256 x 256 tiling's
+    // four are fitted again to its 16 x 16 x 32 instructions, at 73 products near the line: 0.14 % on average, 2.7 % at worst
+    // (672 rows, 4096 x 8192, 61.6 us in 48 tiles of five parts, 58.2 in 96 of two; 2112 rows 145 in 144 tiles, 134.7 in 272).
     static constexpr float US_PER_K_TILE = 0.9f, ROUND_BASE = 0.33f, US_LAUNCH = 8.0f, US_SPLIT = 6.0f;
     static __host__ __device__ constexpr int feature0(int v) { return 64 * (v % WF); }
     static __host__ __device__ constexpr int row_0(int v) { return 64 * (v / WF); }
@@ -400,7 +402,7 @@ struct Tiling256 {
     static constexpr int STAGE = 4 * PIECE;                // [w0 w1][w2 w3][a0][a1]
     static constexpr int WAVE_TILES = 16;                  // 64 x 64 pieces of the output tile, two per wave
     static constexpr int LDS_BYTES = NW * 64 * EPI_PITCH * 4;
-    static constexpr float US_PER_K_TILE = 1.47f, ROUND_BASE = 0.27f, US_LAUNCH = 9.5f, US_SPLIT = 15.0f;   // see Tiling
+    static constexpr float US_PER_K_TILE = 1.47f, ROUND_BASE = 0.30f, US_LAUNCH = 9.5f, US_SPLIT = 17.0f;   // see Tiling
     static_assert(2 * STAGE <= LDS_BYTES, "the epilogue staging is the larger one");
     static __host__ __device__ constexpr int feature0(int v) { return 128 * (v >> 3) + 64 * (v & 1); }   // v = 2 wave + half
     static __host__ __device__ constexpr int row_0(int v) { return 64 * ((v >> 1) & 3); }
