@@ -260,7 +260,7 @@ fr_status fr_sparse_prefill_attn_shared(fr_ctx* ctx, const void* q_rows, const i
  *   queries    host [n_queries]: the per-query arguments of fr_sparse_prefill_attn_shared (host and device pointers
  *              as there); a query with R = 0 is skipped
  *   workspace  dev, 256-byte aligned, at least fr_shared_batch_workspace_bytes(ctx, n_queries, max over queries of L)
- *              bytes: tile images, index maps and rotation tables of the queries in flight (78 MB per 17k-token
+ *              bytes: tile images, index maps and rotation tables of the queries in flight (70 MB per 17k-token
  *              query); owned by the caller, contents undefined afterwards, must stay untouched until the call's
  *              work on the stream has finished
  * Every query is validated before the first launch.  Errors as fr_sparse_prefill_attn_shared (the message names
