@@ -11,7 +11,7 @@
 // most exponent bits agree), which would pile a plain histogram onto one or two bins; the digits are therefore
 // taken from key - min(key), starting at the highest bit in which the largest and the smallest key differ.  Even so most scores lie near the smallest
 // one: with 256 bins the adds of a wave queued up behind one LDS word, and every pass costs its barriers and scans (four
-// passes of 8 bits: 9.6 / 19.5 / 33.0 us at 880 / 16384 / 32768 scores of a prompt, now 8.1 / 14.7 / 25.2 in this kernel; up to 2048 scores take the one-wave kernel below; taking all
+// passes of 8 bits: 9.6 / 19.5 / 33.0 us at 880 / 16384 / 32768 scores of a prompt, now 8.1 / 14.7 / 25.2 in this kernel; up to 1024 scores take the one-wave kernel below; taking all
 // of 16384, without any search, is 8.1).
 #include "fr_internal.hpp"
 
@@ -215,7 +215,8 @@ __global__ __launch_bounds__(SEL_THREADS) void select_topk_kernel(const float* _
 // stays set if at least k keys reach it, counted by ballots (PER compares and scalar adds); as soon as exactly k keys reach the threshold, the set
 // is known (with n distinct scores after about log2(n) + 4 bits; ties go on to the last bit and take the lowest indices).  What bounds it is the one wave's
 // issue, 12 PER cycles a bit, against ten barriers of 16 waves above: 512 scores
-// 8.2 -> 3.1 us, 880 8.6 -> 6.6; beyond 2048 scores, 32 keys a lane, the wave would take longer than the workgroup.
+// 8.2 -> 3.1 us, 880 8.6 -> 6.6.  Beyond 1024 scores, 32 keys a lane, the wave takes longer than the workgroup: layers of 1623 and 1679
+// tokens 70.6 and 58.1 us with it, 66.7 and 54.1 without.
 template <int PER>
 __global__ __launch_bounds__(64) void select_topk_wave_kernel(const float* __restrict__ scores, int n, int k, int nq,
                                                               int32_t* __restrict__ out) {
@@ -278,14 +279,12 @@ static_assert(SELECT_ONE_WORKGROUP_MAX == (int64_t)SEL_THREADS * 32, "largest sc
 hipError_t launch_select(const float* scores, int64_t n, int64_t k, int nq, int32_t* q_index, uint32_t* tmp,
                          size_t tmp_bytes, hipStream_t st) {
     if (k + nq == 0) return hipSuccess;
-    if (n > 0 && n <= 2048) {
+    if (n > 0 && n <= 1024) {
         const int kk = (int)std::max<int64_t>(0, std::min(k, n));
         if (n <= 512)
             select_topk_wave_kernel<8><<<dim3(1), dim3(64), 0, st>>>(scores, (int)n, kk, nq, q_index);
-        else if (n <= 1024)
-            select_topk_wave_kernel<16><<<dim3(1), dim3(64), 0, st>>>(scores, (int)n, kk, nq, q_index);
         else
-            select_topk_wave_kernel<32><<<dim3(1), dim3(64), 0, st>>>(scores, (int)n, kk, nq, q_index);
+            select_topk_wave_kernel<16><<<dim3(1), dim3(64), 0, st>>>(scores, (int)n, kk, nq, q_index);
         return hipGetLastError();
     }
     if (n <= (int64_t)SEL_THREADS * 8)
