@@ -93,8 +93,8 @@ int64_t fr_workspace_bytes(const fr_ctx* ctx);
 
 /* Tuning / test switches.  FR_OPT_ATTN_SOFTMAX chooses how the tiled bf16 attention kernel keeps exp() in
  * range: AUTO (default) fixes each row's exponent reference at the maximum over its first 32 visible keys
- * and recomputes, with a running maximum, only the workgroups whose sums overflowed; RUNNING_MAX uses the
- * running maximum everywhere.  Both give the same softmax; the option exists so that tests reach both.
+ * and recomputes, against the largest logit of all keys, only the workgroups whose sums overflowed; RUNNING_MAX uses
+ * that everywhere.  Both give the same softmax; the option exists so that tests reach both.
  * FR_OPT_ATTN_SPLIT: AUTO (default) deals the key range of every (row tile, KV head) to two or more workgroups when
  * there are too few of those to fill the chip (few recomputed rows, e.g. question-only prefill or the offline stage of
  * eq. 10); OFF: never; ON: two workgroups each whenever the partial results fit the workspace.  Same results up to the

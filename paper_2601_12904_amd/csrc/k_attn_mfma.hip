@@ -31,8 +31,7 @@
 // headroom, so the fast kernel fixes each query column's reference m once (the maximum over the
 // column's first 32 visible keys) and never rescales: the tile loop holds no maximum, no
 // comparison and no branch on values.  If a later logit exceeds the reference by more than that headroom
-// the sums overflow to inf; the workgroup then recomputes its item with the classic online softmax
-// (running maximum).
+// the sums overflow to inf; the workgroup then finds the largest logit of its keys in a pass of its own and does the piece again.
 //
 // K/V tile images.  Every row tile of a KV head walks the same K/V stream (47 row tiles per head at 17k
 // tokens / 15 %), so the work that does not depend on the rows is done once, by a packing pre-pass: for each
@@ -44,7 +43,7 @@
 //
 // What a row does not see.  A weight of 0 does not take a NaN or an infinity out of a matrix product.  Positions behind the last
 // row of the Q index may hold anything: they are not read.  A value that is not finite and that only some rows of a tile see makes the
-// sums of the others NaN, which the overflow check finds; in the instances with split weights running_max_item then keeps such values apart.  (In
+// sums of the others NaN, which the overflow check finds; in the instances with split weights the second go then keeps such values apart.  (In
 // the others the code for it would cost the tile loop 0.6 % through its registers; there a row is NaN too if one of the at most 63
 // positions behind it in its last key tile is.)
 #include "fr_internal.hpp"
@@ -68,6 +67,7 @@ typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 
 constexpr int KT = 64;           // keys per tile
 constexpr float NEG_BIG = -1.0e30f;
+constexpr float ITEM_DONE = INFINITY;   // in the place of a half-precision part's reference: its item has been stored
 
 // Tile image = [K image][V^T image], 16 KB each at head_dim 128, 8 KB at 64.  Both are stored as the matrix operands read them: in
 // planes of 16 bytes per row,
@@ -92,6 +92,7 @@ struct Img {
 // layout of S^T hands the keys to the second product.  Slot of key t (0..63) of a tile:
 __device__ __forceinline__ int key_slot(int t) { return (t & 32) + 8 * ((t >> 2) & 3) + 4 * ((t >> 4) & 1) + (t & 3); }
 constexpr int NC = 4;            // blocks of 16 query columns per wave
+constexpr int FAST_WAVES = 8;    // of the fast kernel
 
 // LDS of the fast kernel: rings of K and V^T images (see its tile loop) and the part of the query fragments that does not stay in
 // registers, as [row group][column block][matrix step][lane]: both waves of a row group read the same 16 bytes per lane.
@@ -104,6 +105,7 @@ struct __attribute__((aligned(16))) FastLds {
     unsigned char vt[3][Img<D>::V_BYTES];
     unsigned char q[QL > 0 ? 4 * QL * NC * 1024 : 16];
     int pos[4][64];                                           // positions of the row groups' columns (masked tiles)
+    float ref[FAST_WAVES][64];                                // the waves' largest logits (EXACT)
 };
 
 __device__ __forceinline__ uint32_t perm_lo(uint32_t a, uint32_t b) {  // (a.lo16, b.lo16) -> a in low half
@@ -393,7 +395,6 @@ __device__ __forceinline__ void dma_chunk(const unsigned char* src, uint32_t lds
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(lane_off), "s"(src), "s"(lds_dst) : "memory");
 }
 typedef const bf16x8 __attribute__((address_space(3)))* lds_frag_ptr;
-constexpr int FAST_WAVES = 8;
 // A wave's share of an image: chunks w, w + 8, ... of its N.  `wave` must be wave-uniform in the compiler's eyes (readfirstlane).
 template <int N>
 __device__ __forceinline__ void dma_image(const unsigned char* src, uint32_t lds_dst, int wave, uint32_t lane_off) {
@@ -413,31 +414,6 @@ __device__ __forceinline__ void plain_barrier() {   // without the fences of __s
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
 }
-
-// ---- staging in the safe kernel: image -> registers -> LDS, 16 bytes per lane and copy -------------------
-template <int D>
-struct ImageStager {
-    static constexpr int BYTES = Img<D>::BYTES;
-    static constexpr int N = (BYTES + 4095) / 4096;   // the last copy may be a part of the workgroup's
-    const unsigned char* head_images;   // images of this KV head
-    int lane_off;                       // threadIdx.x * 16
-    u32x4 reg[N];
-    __device__ __forceinline__ void init(const unsigned char* images, int g, int n_img_tiles) {
-        head_images = images + (size_t)g * n_img_tiles * BYTES;
-        lane_off = threadIdx.x * 16;
-    }
-    __device__ __forceinline__ void load(int kt) {
-        const unsigned char* p = head_images + (size_t)kt * BYTES;
-#pragma unroll
-        for (int i = 0; i < N; ++i)
-            reg[i] = *reinterpret_cast<const u32x4*>(p + min(i * 4096 + lane_off, BYTES - 16));
-    }
-    __device__ __forceinline__ void write(unsigned char* img) const {
-#pragma unroll
-        for (int i = 0; i < N; ++i)
-            if (i * 4096 + lane_off < BYTES) *reinterpret_cast<u32x4*>(img + i * 4096 + lane_off) = reg[i];
-    }
-};
 
 // Per-lane byte offsets of the operand fragments inside an image: row x, 16-byte quarter kg.
 template <int D>
@@ -496,24 +472,6 @@ struct Weights {
     __device__ __forceinline__ bf16x8 operand(int i, int nb) const { return __builtin_bit_cast(bf16x8, part[i][nb]); }
 };
 
-// S^T for 32 keys (half mb of a staged tile) against this wave's 64 query columns: s[b][nb][v] is key 16 b + 4 kg + v.
-template <int D>
-__device__ __forceinline__ void qk_half(const unsigned char* k, int mb, const bf16x8 (&qf)[NC][D / 32], const FragOffsets<D>& fo,
-                                        f32x4 (&s)[2][NC]) {
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-        for (int nb = 0; nb < NC; ++nb) s[b][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int ks = 0; ks < D / 32; ++ks)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            const bf16x8 a = *reinterpret_cast<const bf16x8*>(k + fo.k + 4 * ks * Img<D>::K_PLANE + (2 * mb + b) * Img<D>::BLOCK);
-#pragma unroll
-            for (int nb = 0; nb < NC; ++nb) s[b][nb] = mfma(a, qf[nb][ks], s[b][nb]);
-        }
-}
-
 __device__ __forceinline__ void mask_half(f32x4 (&s)[2][NC], const int (&col_pos)[NC], int key_base, int kg) {
 #pragma unroll
     for (int nb = 0; nb < NC; ++nb) {
@@ -533,53 +491,42 @@ __device__ __forceinline__ uint32_t finite_or_zero(uint32_t w) {
     return w;
 }
 
-// O^T += V^T P^T for the 32 keys of half mb: o[md][nb][v] is dim 16 md + 4 kg + v.  FINITE_ONLY: without the values that are not finite.
-template <int D, bool SPLIT, bool FINITE_ONLY = false>
-__device__ __forceinline__ void pv_half(const unsigned char* vt, int mb, const Weights<SPLIT>& pf, const FragOffsets<D>& fo,
-                                        f32x4 (&o)[D / 16][NC]) {
-#pragma unroll
-    for (int md = 0; md < D / 16; ++md) {
-        bf16x8 a = *reinterpret_cast<const bf16x8*>(vt + fo.v + 4 * mb * Img<D>::V_PLANE + md * Img<D>::BLOCK);
-        if constexpr (FINITE_ONLY) {
-            u32x4 bits = __builtin_bit_cast(u32x4, a);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) bits[e] = finite_or_zero(bits[e]);
-            a = __builtin_bit_cast(bf16x8, bits);
-        }
-#pragma unroll
-        for (int i = 0; i < Weights<SPLIT>::PARTS; ++i)
-#pragma unroll
-            for (int nb = 0; nb < NC; ++nb) o[md][nb] = mfma(a, pf.operand(i, nb), o[md][nb]);
-    }
-}
+// Behind a barrier; uniform in the compiler's eyes too (what lies behind a divergent branch keeps its registers through the other side).
+__device__ __forceinline__ bool any_of_workgroup(bool v) { return __builtin_amdgcn_readfirstlane(__syncthreads_or(v ? 1 : 0)) != 0; }
 
-// Does the V^T image of a tile hold a value that is not finite?  The same answer in every lane of the wave.
+// Takes the values that are not finite out of half of a V^T image, for this wave a quarter of it.  Were there any?
 template <int D>
-__device__ __forceinline__ bool holds_not_finite(const unsigned char* vt) {
+__device__ __forceinline__ bool drop_not_finite(unsigned char* half, int quarter) {
+    constexpr int QUARTER = Img<D>::V_BYTES / 8;
     bool found = false;
-    for (int i = (threadIdx.x & 63) * 16; i < Img<D>::V_BYTES; i += 1024) {
-        const u32x4 w = *reinterpret_cast<const u32x4*>(vt + i);
+    for (int i = quarter * QUARTER + (threadIdx.x & 63) * 16; i < (quarter + 1) * QUARTER; i += 1024) {
+        u32x4 w = *reinterpret_cast<const u32x4*>(half + i);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) found = found || finite_or_zero(w[e]) != w[e];
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t kept = finite_or_zero(w[e]);
+            found = found || kept != w[e];
+            w[e] = kept;
+        }
+        *reinterpret_cast<u32x4*>(half + i) = w;
     }
-    return __any(found);
+    return found;
 }
-// O^T += those values, for the columns that see them.  Their weights are positive: an infinity stays what it is, a NaN too.
-template <int D>
-__device__ __forceinline__ void add_not_finite(const unsigned char* vt, int key_base, const int (&col_pos)[NC], int kg,
-                                               f32x4 (&o)[D / 16][NC]) {
+// O^T += those values of an image in memory, for the columns that see them: their weights are positive, so an infinity stays what it is, a
+// NaN too.  M of the columns' 16-dim blocks, from block md0 on.
+template <int D, int M>
+__device__ __forceinline__ void add_not_finite(const unsigned char* vt, int key_base, const int (&col_pos)[NC], int kg, int md0, f32x4 (&o)[M][NC]) {
+#pragma unroll 1
     for (int t = 0; t < KT; ++t) {
         const int slot = key_slot(t);
-        const unsigned char* key = vt + (slot >> 3) * Img<D>::V_PLANE + 2 * (slot & 7);
+        const unsigned char* key = vt + (slot >> 3) * Img<D>::V_PLANE + 2 * (slot & 7) + 16 * (16 * md0 + 4 * kg);
 #pragma unroll
-        for (int md = 0; md < D / 16; ++md)
+        for (int md = 0; md < M; ++md)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const uint32_t w = *reinterpret_cast<const uint16_t*>(key + 16 * (16 * md + 4 * kg + v));
-                if ((w & 0x7F80u) != 0x7F80u) continue;
+                const uint32_t w = *reinterpret_cast<const uint16_t*>(key + 16 * (16 * md + v));
+                const float add = (w & 0x7F80u) == 0x7F80u ? __uint_as_float(w << 16) : 0.f;
 #pragma unroll
-                for (int nb = 0; nb < NC; ++nb)
-                    if (key_base + t <= col_pos[nb]) o[md][nb][v] += __uint_as_float(w << 16);
+                for (int nb = 0; nb < NC; ++nb) o[md][nb][v] += key_base + t <= col_pos[nb] ? add : 0.f;
             }
     }
 }
@@ -589,28 +536,25 @@ __device__ __forceinline__ void add_not_finite(const unsigned char* vt, int key_
 template <int G, int D, int M>
 __device__ __forceinline__ void store_output(const Geometry<G>& ge, const f32x4 (&o)[M][NC], int md0, const float (&l)[NC],
                                              const float (&mref)[NC], int R, int Hq, unsigned char* smem,
-                                             __bf16* __restrict__ out, float* __restrict__ lse_out, bool active = true) {
+                                             __bf16* __restrict__ out, float* __restrict__ lse_out) {
     constexpr int O_PITCH = Img<D>::O_PITCH, NV = D / 8, MD = Img<D>::MD;
     __bf16* ob = reinterpret_cast<__bf16*>(smem) + ge.wave * 64 * O_PITCH;   // this wave's [64 columns][d]
     const int lane = threadIdx.x & 63;
-    if (active) {
 #pragma unroll
-        for (int nb = 0; nb < NC; ++nb) {
-            const float inv_l = 1.0f / l[nb];
+    for (int nb = 0; nb < NC; ++nb) {
+        const float inv_l = 1.0f / l[nb];
 #pragma unroll
-            for (int md = 0; md < M; ++md) {
-                bf16x4 w;
+        for (int md = 0; md < M; ++md) {
+            bf16x4 w;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) w[e] = (__bf16)(o[md][nb][e] * inv_l);
-                *reinterpret_cast<bf16x4*>(&ob[(16 * nb + ge.x) * O_PITCH + 16 * (md0 + md) + 4 * ge.kg]) = w;
-            }
-            if (md0 == 0 && lse_out != nullptr && ge.kg == 0 && ge.col_row[nb] < R && 16 * nb + ge.x < ge.trw * ge.heads)
-                lse_out[(size_t)ge.col_row[nb] * Hq + ge.col_head[nb]] =
-                    (mref[nb] + __builtin_amdgcn_logf(l[nb])) * 0.6931471805599453f;
+            for (int e = 0; e < 4; ++e) w[e] = (__bf16)(o[md][nb][e] * inv_l);
+            *reinterpret_cast<bf16x4*>(&ob[(16 * nb + ge.x) * O_PITCH + 16 * (md0 + md) + 4 * ge.kg]) = w;
         }
+        if (md0 == 0 && lse_out != nullptr && ge.kg == 0 && ge.col_row[nb] < R && 16 * nb + ge.x < ge.trw * ge.heads)
+            lse_out[(size_t)ge.col_row[nb] * Hq + ge.col_head[nb]] =
+                (mref[nb] + __builtin_amdgcn_logf(l[nb])) * 0.6931471805599453f;
     }
     __syncthreads();   // (the barrier orders the LDS writes and reads of the waves of a row group)
-    if (!active) return;
 #pragma unroll
     for (int i = 0; i < NV * M / MD; ++i) {
         const int col = (64 / NV) * (i + (md0 > 0 ? NV * M / MD : 0)) + lane / NV, vec = lane % NV;
@@ -623,11 +567,13 @@ __device__ __forceinline__ void store_output(const Geometry<G>& ge, const f32x4 
 }
 
 // The same for dims 32 sl .. 32 sl + 31 only (a workgroup of the combine pass).
+constexpr int SLICE_PITCH = 40;   // 32 dims + 16 bytes
+constexpr int SLICE_LDS = 4 * 64 * SLICE_PITCH * (int)sizeof(__bf16);
 template <int G, int D>
 __device__ __forceinline__ void store_slice(const Geometry<G>& ge, const f32x4 (&acc)[2][NC], int sl, const float (&l)[NC],
                                             const float (&mref)[NC], int R, int Hq, unsigned char* smem,
                                             __bf16* __restrict__ out, float* __restrict__ lse_out) {
-    constexpr int PITCH = 40;   // 32 dims + 16 bytes
+    constexpr int PITCH = SLICE_PITCH;
     __bf16* ob = reinterpret_cast<__bf16*>(smem) + ge.wave * 64 * PITCH;
     const int lane = threadIdx.x & 63;
 #pragma unroll
@@ -658,7 +604,8 @@ __device__ __forceinline__ void store_slice(const Geometry<G>& ge, const f32x4 (
 
 // The value of column block kg in lane (x, kg): one word per lane carries what a wave's 64 columns have once each.
 __device__ __forceinline__ float own_block(const float (&v)[NC], int kg) {
-    const float lo = (kg & 1) ? v[1] : v[0], hi = (kg & 1) ? v[3] : v[2];
+    const float v0 = v[0], v1 = v[1], v2 = v[2], v3 = v[3];   // (a choice between places of the array would put it into memory)
+    const float lo = (kg & 1) ? v1 : v0, hi = (kg & 1) ? v3 : v2;
     return (kg & 2) ? hi : lo;
 }
 __device__ __forceinline__ uint32_t of_block(uint32_t word, int nb, int x) {   // and back
@@ -669,7 +616,7 @@ __device__ __forceinline__ uint32_t of_block(uint32_t word, int nb, int x) {   /
 // columns) and one word each of its wave's column sums, exponent references and two scale exponents (own_block).  Four words of a
 // thread side by side (words 4 r .. 4 r + 3 of thread t at [4 (r * 256 + t)]: every store and load of a wave is one line of 1 KB).  Part p of item (ordinal, KV head g) lives at
 // (((query * max_row_tiles + ordinal) * n_parts + p) * Hkv + g) * WORDS.  Infinities and NaNs survive the packing (the
-// combine pass must still see an overflow).
+// output shows what the values held).
 // F32: the accumulators as they are.  Otherwise as half-precision pairs, the D / 2 of a column in half of the dims scaled by a power of two
 // that brings the largest of them into [0.5, 1) (11 significant bits of that column's largest value): 68 words instead of
 // 132.  Which one: half_parts.
@@ -677,7 +624,7 @@ template <int D, bool F32>
 struct Part {
     static constexpr int O_WORDS = F32 ? D : D / 2;   // per lane, all column blocks
     static constexpr int COL_WORDS = O_WORDS / NC;    // of a column block; block md of 16 dims has COL_WORDS / (D / 16) of them
-    static constexpr int SUM = O_WORDS, REFERENCE = O_WORDS + 1;
+    static constexpr int SUM = O_WORDS, REFERENCE = O_WORDS + 1;   // and the exponents: four words side by side
     static constexpr int REGS = O_WORDS + 4;
     static constexpr int WORDS = REGS * 256;          // 32-bit words of a part
     static __device__ __forceinline__ int exponent(int md) { return O_WORDS + 2 + md / (D / 32); }
@@ -687,14 +634,13 @@ typedef _Float16 __attribute__((ext_vector_type(2))) f16x2;
 
 // The half of a row group's dims that a wave holds: blocks md0 .. md0 + D / 32 - 1.
 template <int D, bool F32>
-__device__ __forceinline__ void store_partial(float* __restrict__ dst_f, const f32x4 (&o)[D / 32][NC], int md0, const float (&lsum)[NC],
+__device__ __forceinline__ void store_partial(float* __restrict__ dst_f, const f32x4 (&o)[D / 32][NC], int md0, const float (&l)[NC],
                                               const float (&mref)[NC], int kg) {
     using P = Part<D, F32>;
     uint32_t* dst = reinterpret_cast<uint32_t*>(dst_f);
-    float sum[NC], e[NC];
+    float e[NC];
 #pragma unroll
     for (int nb = 0; nb < NC; ++nb) {
-        sum[nb] = column_sum(lsum[nb]);
         if constexpr (F32) {
 #pragma unroll
             for (int md = 0; md < D / 32; ++md)
@@ -724,7 +670,7 @@ __device__ __forceinline__ void store_partial(float* __restrict__ dst_f, const f
         }
     }
     if (md0 == 0) {
-        dst[P::at(P::SUM)] = __float_as_uint(own_block(sum, kg));
+        dst[P::at(P::SUM)] = __float_as_uint(own_block(l, kg));
         dst[P::at(P::REFERENCE)] = __float_as_uint(own_block(mref, kg));
     }
     if constexpr (!F32) dst[P::at(P::exponent(md0))] = __float_as_uint(own_block(e, kg));
@@ -750,119 +696,6 @@ struct AttnBatch {
     AttnQuery q[ATTN_MAX_BATCH];
     int n, max_row_tiles;
 };
-struct BlockWork {
-    int g, ordinal, query;
-    __device__ __forceinline__ void init(int max_row_tiles, int Hkv) {
-        int t = (int)blockIdx.x;
-        g = t % Hkv; t /= Hkv;
-        ordinal = t % max_row_tiles;
-        query = t / max_row_tiles;
-    }
-};
-
-// ---- classic online softmax (running maximum) for one (row tile, KV head): the whole key range, one workgroup.
-//      Runs where the fixed exponent reference overflowed, and everywhere under FR_ATTN_SOFTMAX_RUNNING_MAX.
-//      `smem` holds one image or the epilogue's staging; every thread of the workgroup calls it.  slice >= 0: only the
-//      dims of that block of 32 are stored (a workgroup of the combine pass).  -------------------------------------------
-template <int G, int D, bool SPLIT>
-__device__ __forceinline__ void running_max_item(const AttnQuery& aq, int g, int ordinal, int Hq, int Hkv,
-                                                 float scale_log2e, unsigned char* smem, int slice = -1) {
-    const __bf16* __restrict__ q_rows = aq.q_rows;
-    const int R = aq.R, n_img_tiles = aq.n_img_tiles;
-    unsigned char* k_img = smem;
-    unsigned char* v_img = smem + Img<D>::K_BYTES;
-    Geometry<G> ge;
-    ge.init(aq.q_index, R, Hq, Hkv, aq.n_row_tiles, n_img_tiles, g, ordinal);
-    const int kg = ge.kg;
-    const bool active = threadIdx.x < 256;   // (the other waves of the fast kernel only keep the barriers)
-    FragOffsets<D> fo;
-    fo.init(ge.x, kg);
-    bf16x8 qf[NC][D / 32];
-#pragma unroll
-    for (int nb = 0; nb < NC; ++nb) {
-        const __bf16* qp = q_rows + ((size_t)min(ge.col_row[nb], R - 1) * Hq + ge.col_head[nb]) * D + 8 * kg;
-#pragma unroll
-        for (int ks = 0; ks < D / 32; ++ks) qf[nb][ks] = *reinterpret_cast<const bf16x8*>(qp + 32 * ks);
-    }
-    f32x4 o[D / 16][NC];
-#pragma unroll
-    for (int md = 0; md < D / 16; ++md)
-#pragma unroll
-        for (int nb = 0; nb < NC; ++nb) o[md][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float lsum[NC], m2[NC];
-#pragma unroll
-    for (int nb = 0; nb < NC; ++nb) {
-        lsum[nb] = 0.f;
-        m2[nb] = NEG_BIG;
-    }
-    ImageStager<D> sg;
-    sg.init(aq.images, ge.g, n_img_tiles);
-    for (int kt = 0; kt < ge.n_kt; ++kt) {
-        if (active) sg.load(kt);
-        __syncthreads();
-        if (active) sg.write(k_img);
-        __syncthreads();
-        if (!active || kt * KT > ge.wp_max) continue;   // wave-uniform; the barriers stay outside
-        const bool apart = SPLIT && kt >= ge.n_plain && holds_not_finite<D>(v_img);   // some rows may not see them
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb) {
-            f32x4 s[2][NC];
-            qk_half<D>(k_img, mb, qf, fo, s);
-            mask_half(s, ge.col_pos, kt * KT + 32 * mb, kg);
-            Weights<SPLIT> pf;
-#pragma unroll
-            for (int nb = 0; nb < NC; ++nb) {
-                float t = fmaxf(s[0][nb][0], s[1][nb][0]);
-#pragma unroll
-                for (int v = 1; v < 4; ++v) t = fmaxf(t, fmaxf(s[0][nb][v], s[1][nb][v]));
-                t = column_max(t);
-                const float m_new = fmaxf(m2[nb], t * scale_log2e);
-                const float alpha = __builtin_amdgcn_exp2f(m2[nb] - m_new);
-                m2[nb] = m_new;
-                float psum = 0.f;
-#pragma unroll
-                for (int b = 0; b < 2; ++b)
-#pragma unroll
-                    for (int v = 0; v < 4; v += 2) {
-                        const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[b][nb][v], scale_log2e, -m_new));
-                        const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[b][nb][v + 1], scale_log2e, -m_new));
-                        psum += p0;
-                        psum += p1;
-                        pf.set_pair(nb, b, v, p0, p1);
-                    }
-                lsum[nb] = lsum[nb] * alpha + psum;
-#pragma unroll
-                for (int md = 0; md < D / 16; ++md)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) o[md][nb][v] *= alpha;
-            }
-            if constexpr (SPLIT) {
-                if (apart) pv_half<D, SPLIT, true>(v_img, mb, pf, fo, o); else pv_half<D, SPLIT>(v_img, mb, pf, fo, o);
-            } else {
-                pv_half<D, SPLIT>(v_img, mb, pf, fo, o);
-            }
-        }
-        if constexpr (SPLIT) { if (apart) add_not_finite<D>(v_img, kt * KT, ge.col_pos, kg, o); }
-    }
-    float l[NC];
-#pragma unroll
-    for (int nb = 0; nb < NC; ++nb) l[nb] = column_sum(lsum[nb]);
-    __syncthreads();
-    if (slice < 0) {
-        store_output<G, D>(ge, o, 0, l, m2, R, Hq, smem, aq.out, aq.lse, active);
-        return;
-    }
-    f32x4 acc[2][NC];
-#pragma unroll
-    for (int sl = 0; sl < D / 32; ++sl)
-        if (sl == slice)
-#pragma unroll
-            for (int b = 0; b < 2; ++b)
-#pragma unroll
-                for (int nb = 0; nb < NC; ++nb) acc[b][nb] = o[2 * sl + b][nb];
-    store_slice<G, D>(ge, acc, slice, l, m2, R, Hq, smem, aq.out, aq.lse);
-}
-
 // ---- fast path: key tiles [kb, ke) of one (row tile, KV head) ---------------------------------------------
 // Eight waves, two per SIMD.  Waves w and w + 4 own the same 64 query columns; the first takes keys 0..31 of every tile, the second
 // keys 32..63, each with output accumulators of its own, which are added up at the end.
@@ -976,13 +809,17 @@ constexpr int EXCHANGE_WAVE = Img<D>::MD / 2 * NC * 1024 + 1024;
 template <int D>
 constexpr size_t EXCHANGE_LDS = (size_t)FAST_WAVES * EXCHANGE_WAVE<D>;
 
-// part < 0: the piece is the whole item; the workgroup finishes it: overflow check, then the output, or the item again with
-// a running maximum (in this kernel: a second one that looked for flagged items cost 4 us per call and found none).
-// part >= 0: the piece is
-// share `part` of `n_parts` of the item's key tiles; it leaves its partial sums, and attn_combine_kernel finishes
-// the item.  Every part uses the same exponent reference (each derives it from keys 0..31), so the parts simply add up.
-template <int G, int D, bool SPLIT>
-__device__ __forceinline__ void process_piece(const AttnQuery& aq, int g, int ordinal, int part, int n_parts, int item,
+// part < 0: the piece is the whole item; the workgroup finishes it.  part >= 0: the piece is share `part` of `n_parts` of the
+// item's key tiles; it leaves its partial sums and their exponent reference, and attn_combine_kernel finishes the item.  Every part derives
+// the same reference from keys 0..31, so as a rule the parts simply add up.
+// EXACT = false: returns false where the sums overflowed that reference, and what it stored is worth nothing; the caller then does the piece
+// again with EXACT = true, whose reference is the largest logit of the piece's own keys, found in a pass over them that forms nothing but
+// logits (a part then leaves it as its reference).  So both run the same loop in the same kernel.  A second kernel that looked for flagged items
+// cost 4 us per call and found none; a loop that rescales its accumulators to a running maximum spills registers, and one of four waves beside
+// this one took, with every item of 2970 of 16896 rows overflowing, 2190 us a call whole and 6180 in two parts, now 888 and 1125 (402 and 407
+// without overflow); without a fixed reference to begin with 1310 us, now 575.
+template <int G, int D, bool SPLIT, bool EXACT>
+__device__ __forceinline__ bool process_piece(const AttnQuery& aq, int g, int ordinal, int part, int n_parts, int item,
                                               float* __restrict__ partials, bool half, int Hq, int Hkv, float scale_log2e,
                                               unsigned char* smem_raw) {
     using I = Img<D>;
@@ -1003,7 +840,7 @@ __device__ __forceinline__ void process_piece(const AttnQuery& aq, int g, int or
     const int second = wave >> 2;                          // which half of every tile
     const uint32_t lane_off = (uint32_t)lane * 16u;
     const uint32_t k_base = lds_address(sm.k[0]), v_base = lds_address(sm.vt[0]);
-    dma_image<CH>(head_images, k_base + 2 * I::K_BYTES, wave, lane_off);   // K image 0 into ring slot 2: the exponent reference comes from it
+    if constexpr (!EXACT) dma_image<CH>(head_images, k_base + 2 * I::K_BYTES, wave, lane_off);   // K image 0 into ring slot 2: the exponent reference comes from it
 
     // Q fragments: B operand of S^T = K Q^T, for the whole loop; the two waves of a row group bring two column blocks' each to LDS
     bf16x8 qf[NC][F::QR > 0 ? F::QR : 1], ql[2][F::QL > 0 ? F::QL : 1];
@@ -1027,8 +864,9 @@ __device__ __forceinline__ void process_piece(const AttnQuery& aq, int g, int or
     const int part_words = half ? Part<D, false>::WORDS : Part<D, true>::WORDS;
     float* part_dst = part < 0 ? nullptr : partials + (((size_t)item * n_parts + part) * Hkv + g) * part_words;
     if (kb >= ke) {   // fewer key tiles than parts: this one adds nothing
-        for (int r = threadIdx.x; r < part_words; r += 64 * FAST_WAVES) part_dst[r] = 0.f;
-        return;       // (the hardware waits for the outstanding copy before it retires the wave)
+        const int ref_word = half ? Part<D, false>::at(Part<D, false>::REFERENCE) : Part<D, true>::at(Part<D, true>::REFERENCE);
+        for (int r = threadIdx.x; r < part_words; r += 64 * FAST_WAVES) part_dst[r] = r >= ref_word && (r - ref_word) % 4 == 0 ? NEG_BIG : 0.f;
+        return true;  // (the hardware waits for the outstanding copy before it retires the wave)
     }
 
     // K images kb and kb + 1 and V image kb land in LDS.  (Past the piece's last tile the copies repeat that one, here and in
@@ -1046,6 +884,11 @@ __device__ __forceinline__ void process_piece(const AttnQuery& aq, int g, int or
 #pragma unroll
         for (int nb = 0; nb < NC; ++nb) sm.pos[wave & 3][16 * nb + ge.x] = ge.col_pos[nb];
     }
+    if constexpr (EXACT) {   // V ring slot 2 holds zeros for the matrix phase in front
+#pragma unroll
+        for (int i = 0; i < I::V_BYTES / (64 * FAST_WAVES * 16); ++i)
+            *reinterpret_cast<u32x4*>(sm.vt[2] + (i * 64 * FAST_WAVES + threadIdx.x) * 16) = u32x4{0u, 0u, 0u, 0u};
+    }
     wait_dma();
     __syncthreads();
 
@@ -1058,7 +901,7 @@ __device__ __forceinline__ void process_piece(const AttnQuery& aq, int g, int or
     // waves to it strictly, lets the matrix pipe idle whenever the one wave that feeds it waits for its operands: 17 % more cycles.)
     // Barrier kt says that K image kt and V image kt - 1 have landed and that nobody reads K image kt - 1 and V image kt - 2 any
     // more; the copies behind it refill those slots: K image kt + 2 and V image kt + 1.
-    // The matrix phase in front (logits of tile kb) adds V image kb with weights of 0, the one behind the last tile forms logits that
+    // The matrix phase in front (logits of tile kb) adds V image kb with weights of 0 (zeros, if its values may not be finite), the one behind the last tile forms logits that
     // nobody reads: the loop's code is the only copy of it, which the pieces of a short prompt gain from (their time is that of
     // instructions that arrive for the first time).
     int c0 = 0, c1 = I::K_BYTES, c2 = 2 * I::K_BYTES;   // ring slots (their bytes) of K and V images kt, kt + 1, kt + 2
@@ -1066,16 +909,48 @@ __device__ __forceinline__ void process_piece(const AttnQuery& aq, int g, int or
     f32x4 s[2][NC], o[MD][NC];
     Weights<SPLIT> p;
     float lsum[NC], mref[NC];
+    if constexpr (EXACT) {   // the maximum of its logits over the piece's visible keys
+        float t[NC] = {NEG_BIG, NEG_BIG, NEG_BIG, NEG_BIG};
+        for (int kt = kb; kt < ke; ++kt) {   // K images kt and kt + 1 are in ring slots, kt + 2 follows
+            dma_image<CH>(tile_image(kt + 2), k_base + c2, wave, lane_off);
+            matrix_phase<D, SPLIT, false>(0, k_base + second * (2 * I::BLOCK) + c0, fo, qf, q_lds, p, o, s);
+            if (kt >= ge.n_plain) mask_half(s, ge.col_pos, kt * KT + 32 * second, ge.kg);
+#pragma unroll
+            for (int nb = 0; nb < NC; ++nb)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) t[nb] = fmaxf(t[nb], fmaxf(s[0][nb][v], s[1][nb][v]));
+            wait_dma_but<CH / FAST_WAVES>();       // all but the newest image
+            __builtin_amdgcn_s_waitcnt(0xc07f);    // lgkmcnt(0): the wave's own fragment reads
+            plain_barrier();
+            const int c = c0;
+            c0 = c1; c1 = c2; c2 = c;
+        }
+#pragma unroll
+        for (int nb = 0; nb < NC; ++nb) {
+            t[nb] = column_max(t[nb]);
+            if (ge.kg == 0) sm.ref[wave][16 * nb + ge.x] = t[nb];
+        }
+        wait_dma();
+        __syncthreads();
+#pragma unroll
+        for (int nb = 0; nb < NC; ++nb) mref[nb] = fmaxf(t[nb], sm.ref[wave ^ 4][16 * nb + ge.x]) * scale_log2e;
+        c0 = 0; c1 = I::K_BYTES; c2 = 2 * I::K_BYTES;
+        dma_image<CH>(tile_image(kb), k_base, wave, lane_off);   // and once more from the start
+        dma_image<CH>(tile_image(kb + 1), k_base + I::K_BYTES, wave, lane_off);
+        wait_dma();
+        __syncthreads();
+    } else {
     // exponent reference of each column = the maximum of its logits over the visible ones of keys 0..31
-    matrix_phase<D, SPLIT, false>(0, k_base + 2 * I::K_BYTES, fo, qf, q_lds, p, o, s);
+        matrix_phase<D, SPLIT, false>(0, k_base + 2 * I::K_BYTES, fo, qf, q_lds, p, o, s);
 #pragma unroll
-    for (int nb = 0; nb < NC; ++nb) {
-        float t = NEG_BIG;
+        for (int nb = 0; nb < NC; ++nb) {
+            float t = NEG_BIG;
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+            for (int b = 0; b < 2; ++b)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) t = fmaxf(t, 16 * b + 4 * ge.kg + v <= ge.col_pos[nb] ? s[b][nb][v] : NEG_BIG);
-        mref[nb] = column_max(t) * scale_log2e;   // key 0 is visible to every row
+                for (int v = 0; v < 4; ++v) t = fmaxf(t, 16 * b + 4 * ge.kg + v <= ge.col_pos[nb] ? s[b][nb][v] : NEG_BIG);
+            mref[nb] = column_max(t) * scale_log2e;   // key 0 is visible to every row
+        }
     }
 #pragma unroll
     for (int nb = 0; nb < NC; ++nb) {
@@ -1085,12 +960,12 @@ __device__ __forceinline__ void process_piece(const AttnQuery& aq, int g, int or
 #pragma unroll
         for (int u = 0; u < Weights<SPLIT>::PARTS; ++u) p.part[u][nb] = u32x4{0u, 0u, 0u, 0u};
     }
-    __syncthreads();   // K image 0 has been read: ring slot 2 is free
+    if constexpr (!EXACT) __syncthreads();   // K image 0 has been read: ring slot 2 is free
     auto copies = [&](int kt) {
         dma_image<CH>(tile_image(kt + 2), k_base + c2, wave, lane_off);
         dma_image<CH>(tile_image(kt + 1) + I::K_BYTES, v_base + c1, wave, lane_off);
     };
-    int vp = 0;        // ring slot of V image kt - 1
+    int vp = EXACT ? 2 * I::V_BYTES : 0;   // ring slot of V image kt - 1
     auto barrier = [&] {
         __builtin_amdgcn_sched_barrier(0);
         wait_dma_but<2 * CH / FAST_WAVES>();   // all but the newest tile's copies
@@ -1101,17 +976,31 @@ __device__ __forceinline__ void process_piece(const AttnQuery& aq, int g, int or
         __builtin_amdgcn_sched_barrier(0);
     };
     const uint32_t k_half = k_base + second * (2 * I::BLOCK), v_half = v_base + second * (4 * I::V_PLANE);
+    auto positions = [&](int (&pos)[NC]) {   // of the lane's columns; returns kg
+        uint32_t ln = lane_off;
+        asm volatile("" : "+v"(ln));   // (opaque: nothing that follows from it is kept over the loop)
+        ln >>= 4;
+#pragma unroll
+        for (int nb = 0; nb < NC; ++nb) pos[nb] = sm.pos[wave & 3][16 * nb + (ln & 15)];
+        return (int)(ln >> 4);
+    };
     auto softmax = [&](int kt) {
         if (__builtin_expect(kt >= n_plain, 0)) {   // weight 0 behind a column's own position
-            uint32_t ln = lane_off;
-            asm volatile("" : "+v"(ln));   // (opaque: nothing that follows from it is kept over the loop)
-            ln >>= 4;
             int pos[NC];
-#pragma unroll
-            for (int nb = 0; nb < NC; ++nb) pos[nb] = sm.pos[wave & 3][16 * nb + (ln & 15)];
-            mask_half(s, pos, kt * KT + 32 * second, (int)(ln >> 4));
+            const int kg = positions(pos);
+            mask_half(s, pos, kt * KT + 32 * second, kg);
         }
         softmax_phase<SPLIT>(s, p, lsum, mref, scale_log2e);
+    };
+    // Values of tile kt that are not finite leave the image; the columns that see them get them at the end.  Called between barrier kt + 1
+    // and the matrix phase behind it, by all waves for the same tiles.
+    bool apart = false;
+    auto keep_apart = [&](int kt) {
+        if constexpr (EXACT && SPLIT) {
+            if (kt < n_plain) return;
+            const bool found = drop_not_finite<D>(sm.vt[0] + vp + second * (4 * I::V_PLANE), wave & 3);
+            apart = any_of_workgroup(found) || apart;
+        }
     };
     if (!second) {
         for (int kt = kb;; ++kt) {
@@ -1120,6 +1009,7 @@ __device__ __forceinline__ void process_piece(const AttnQuery& aq, int g, int or
             copies(kt);
             softmax(kt);
             barrier();
+            keep_apart(kt);
         }
     } else {
         copies(kb);
@@ -1129,6 +1019,7 @@ __device__ __forceinline__ void process_piece(const AttnQuery& aq, int g, int or
             barrier();
             copies(kt + 1);
             softmax(kt);
+            keep_apart(kt);
         }
     }
     wait_dma();
@@ -1169,40 +1060,48 @@ __device__ __forceinline__ void process_piece(const AttnQuery& aq, int g, int or
 #pragma unroll
         for (int nb = 0; nb < NC; ++nb) lsum[nb] += l2[nb];
     }
-    if (part >= 0) {   // leave the partial result; attn_combine_kernel adds the parts, checks and stores
-        float* dst = part_dst + 4 * (threadIdx.x & 255);
-        if (!SPLIT && half) store_partial<D, false>(dst, oh, md0, lsum, mref, ge.kg); else store_partial<D, true>(dst, oh, md0, lsum, mref, ge.kg);
-        return;
+    if constexpr (EXACT) {
+        if (apart) {
+            ge.init_positions(aq.q_index, R, n_img_tiles);
+            for (int kt = max(kb, n_plain); kt < ke; ++kt)
+                add_not_finite<D, MH>(head_images + (size_t)kt * I::BYTES + I::K_BYTES, kt * KT, ge.col_pos, ge.kg, md0, oh);
+        }
     }
-    // Overflow check: with a fixed reference a runaway logit shows up as inf / nan in the sums.
+    // Overflow check: with a fixed reference a runaway logit shows up as inf / nan in the sums.  The sums of a part stay so far below
+    // that up to eight of them add up.
     float l[NC];
     bool bad = false;
+    const float limit = part < 0 ? INFINITY : 0x1p123f;
 #pragma unroll
     for (int nb = 0; nb < NC; ++nb) {
         l[nb] = column_sum(lsum[nb]);
-        float chk = l[nb];
+        if constexpr (!EXACT) {
+            float chk = l[nb];
 #pragma unroll
-        for (int md = 0; md < MH; ++md)
+            for (int md = 0; md < MH; ++md)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) chk += fabsf(oh[md][nb][v]);
-        bad = bad || !(chk < INFINITY) || !(l[nb] > 0.f);
+                for (int v = 0; v < 4; ++v) chk += fabsf(oh[md][nb][v]);
+            bad = bad || !(chk < limit);
+        }
     }
-    if (!__syncthreads_or(bad ? 1 : 0)) {   // (also: the exchange has been read)
+    bad = any_of_workgroup(bad);   // (also: the exchange has been read)
+    if (part >= 0) {   // leave the partial result; attn_combine_kernel adds the parts and stores
+        float* dst = part_dst + 4 * (threadIdx.x & 255);
+        if (!SPLIT && half) store_partial<D, false>(dst, oh, md0, l, mref, ge.kg); else store_partial<D, true>(dst, oh, md0, l, mref, ge.kg);
+    } else {
         store_output<G, D, MH>(ge, oh, md0, l, mref, R, Hq, smem_raw, aq.out, aq.lse);
-        return;
     }
-    // the sums overflowed the fixed exponent reference (rare): the item again, with a running maximum
-    __syncthreads();
-    running_max_item<G, D, SPLIT>(aq, g, ordinal, Hq, Hkv, scale_log2e, smem_raw);
+    return !bad;   // (stored all the same: the second go writes the same places, each from the same thread)
 }
 
 // blockIdx.x = ((query * max_row_tiles + ordinal) * n_parts + part) * Hkv + KV head.  n_parts = 1: every item whole.
 // n_parts > 1 (few items: the chip would idle behind the longest ones): the key tiles of every item are
 // dealt to n_parts workgroups in equal consecutive shares; items are launched longest first, so the pieces are too.
+// exact: no fixed reference to begin with (FR_ATTN_SOFTMAX_RUNNING_MAX).
 // Dynamic LDS: the larger of the K/V rings and the epilogue's staging.
 template <int G, int D, bool SPLIT>
 __global__ __launch_bounds__(64 * FAST_WAVES) void attn_fixed_ref_kernel(const AttnBatch batch, float* __restrict__ partials, int n_parts,
-                                                             int half, int Hq, int Hkv, float scale_log2e) {
+                                                             int half, int exact, int Hq, int Hkv, float scale_log2e) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     int t = (int)blockIdx.x;
     const int g = t % Hkv; t /= Hkv;
@@ -1210,18 +1109,30 @@ __global__ __launch_bounds__(64 * FAST_WAVES) void attn_fixed_ref_kernel(const A
     const int ordinal = t % batch.max_row_tiles, query = t / batch.max_row_tiles;
     const AttnQuery& aq = batch.q[query];
     if (ordinal >= aq.n_row_tiles) return;
-    process_piece<G, D, SPLIT>(aq, g, ordinal, n_parts > 1 ? part : -1, n_parts, t, partials, half != 0, Hq, Hkv, scale_log2e, smem_raw);
+    const int share = n_parts > 1 ? part : -1;
+    bool redo = exact != 0;
+    if (!redo) {
+        redo = !process_piece<G, D, SPLIT, false>(aq, g, ordinal, share, n_parts, t, partials, half != 0, Hq, Hkv, scale_log2e, smem_raw);
+        if (redo) __syncthreads();   // (the epilogue's staging has been read)
+    }
+    if (!redo) return;
+    // Parts in half precision: the whole item, whose sums then stay in 32 bits; every part that overflowed does so and stores the same.
+    const bool whole = !SPLIT && half && share >= 0;
+    process_piece<G, D, SPLIT, true>(aq, g, ordinal, whole ? -1 : share, n_parts, t, partials, half != 0, Hq, Hkv, scale_log2e, smem_raw);
+    if (whole && threadIdx.x < 256) {
+        using P = Part<D, false>;
+        partials[(((size_t)t * n_parts + part) * Hkv + g) * P::WORDS + 4 * threadIdx.x + P::at(P::REFERENCE)] = ITEM_DONE;
+    }
 }
 
-// ---- combine: adds the parts of every item, then checks and stores like the fast path's own epilogue; on overflow
-//      the item is recomputed with a running maximum.  One workgroup per (item, 32 dims of the output): the pass is bound by
-//      the latency of its loads, and a workgroup per item left a short prompt's 24 items in eight parts to 24 compute units
-//      (24 us; now 7.5; the offline stage's 128 items in two parts 13.6 -> 7.6).  A column's sum is added up by every slice; a slice that sees an overflow computes and stores its own dims.
-//      grid.x = ((query * max_row_tiles + ordinal) * D / 32 + slice) * Hkv + KV head, LDS = max(epilogue staging, one image).
+// ---- combine: adds the parts of every item and stores like the fast path's own epilogue.  One workgroup per (item, 32 dims of the output):
+//      the pass is bound by the latency of its loads, and a workgroup per item left a short prompt's 24 items in eight parts to 24 compute units
+//      (24 us; now 7.5; the offline stage's 128 items in two parts 13.6 -> 7.6).  A column's sum is added up by every slice.
+//      grid.x = ((query * max_row_tiles + ordinal) * D / 32 + slice) * Hkv + KV head.
 template <int G, int D, bool SPLIT, bool F32>
 __global__ __launch_bounds__(256, 2) void attn_combine_kernel(const AttnBatch batch, const float* __restrict__ partials,
-                                                              int n_parts, int Hq, int Hkv, float scale_log2e) {
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+                                                              int n_parts, int Hq, int Hkv) {
+    __shared__ __attribute__((aligned(16))) unsigned char staging[SLICE_LDS];
     int t = (int)blockIdx.x;
     const int g = t % Hkv; t /= Hkv;
     const int sl = t % (D / 32);
@@ -1229,89 +1140,103 @@ __global__ __launch_bounds__(256, 2) void attn_combine_kernel(const AttnBatch ba
     const int ordinal = item % batch.max_row_tiles;
     const AttnQuery& aq = batch.q[item / batch.max_row_tiles];
     if (ordinal >= aq.n_row_tiles) return;
-    {
-        using P = Part<D, F32>;
-        constexpr int SW = F32 ? 8 : 4;                     // words of a slice of a column block
-        constexpr int AHEAD = 4;                            // parts whose loads are in flight together
-        const uint32_t* p0 = reinterpret_cast<const uint32_t*>(partials + ((size_t)item * n_parts * Hkv + g) * P::WORDS) + 4 * threadIdx.x;
-        const size_t part_stride = (size_t)Hkv * P::WORDS;
-        f32x4 acc[2][NC];
+    using P = Part<D, F32>;
+    constexpr int SW = F32 ? 8 : 4;                     // words of a slice of a column block
+    constexpr int AHEAD = 4;                            // parts whose loads are in flight together
+    typedef std::conditional_t<F32, u32x2, u32x4> Tail; // sum, reference (and exponents; words that nobody reads would be waited for)
+    const uint32_t* p0 = reinterpret_cast<const uint32_t*>(partials + ((size_t)item * n_parts * Hkv + g) * P::WORDS) + 4 * threadIdx.x;
+    const size_t part_stride = (size_t)Hkv * P::WORDS;
+    f32x4 acc[2][NC];
 #pragma unroll
-        for (int nb = 0; nb < NC; ++nb) acc[0][nb] = acc[1][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-        float sum = 0.f;
-        const uint32_t ref = p0[P::at(P::REFERENCE)];   // part 0 is never empty; every part derives the same reference
-        const int x = threadIdx.x & 15;
-        auto add = [&](int first, auto count) {
-            constexpr int N = decltype(count)::value;
-            u32x4 w[N][NC][SW / 4];
-            uint32_t tail[N][2];
+    for (int nb = 0; nb < NC; ++nb) acc[0][nb] = acc[1][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float sum = 0.f, ref = NEG_BIG;
+    bool done = false;
+    const int x = threadIdx.x & 15;
+    auto add = [&](int first, auto count) {
+        constexpr int N = decltype(count)::value;
+        u32x4 w[N][NC][SW / 4];
+        Tail tail[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const uint32_t* pp = p0 + (first + i) * part_stride;
+#pragma unroll
+            for (int nb = 0; nb < NC; ++nb)
+#pragma unroll
+                for (int j = 0; j < SW; j += 4) w[i][nb][j / 4] = *reinterpret_cast<const u32x4*>(pp + P::at(nb * P::COL_WORDS + sl * SW + j));
+            tail[i] = *reinterpret_cast<const Tail*>(pp + P::at(P::SUM));
+        }
+        __builtin_amdgcn_sched_barrier(0);   // (all loads before the first wait)
+        auto reference = [&](int i) { return __uint_as_float(tail[i][1]); };
+        if (first == 0) ref = reference(0);   // part 0 is never empty; an empty part brings NEG_BIG and zeros
+        if constexpr (F32) {   // equal references as a rule; another one where a part overflowed it
+            bool other = false;
+            float m = ref;
 #pragma unroll
             for (int i = 0; i < N; ++i) {
-                const uint32_t* pp = p0 + (first + i) * part_stride;
-#pragma unroll
-                for (int nb = 0; nb < NC; ++nb)
-#pragma unroll
-                    for (int j = 0; j < SW; j += 4) w[i][nb][j / 4] = *reinterpret_cast<const u32x4*>(pp + P::at(nb * P::COL_WORDS + sl * SW + j));
-                tail[i][0] = pp[P::at(P::SUM)];
-                tail[i][1] = F32 ? 0u : pp[P::at(P::exponent(2 * sl))];
+                other |= (reference(i) != ref) & (reference(i) != NEG_BIG);
+                m = fmaxf(m, reference(i));
             }
-#pragma unroll
-            for (int i = 0; i < N; ++i) {
+            if (__builtin_expect(__any(other), 0)) {
+                const float f = __builtin_amdgcn_exp2f(ref - m);
+                ref = m;
+                sum *= f;
 #pragma unroll
                 for (int nb = 0; nb < NC; ++nb) {
-                    const int e = F32 ? 0 : (int)of_block(tail[i][1], nb, x);
+                    const float fb = __uint_as_float(of_block(__float_as_uint(f), nb, x));
+                    acc[0][nb] *= fb;
+                    acc[1][nb] *= fb;
+                }
 #pragma unroll
-                    for (int j = 0; j < 8; j += 2) {   // accumulators j and j + 1 of the slice's eight
-                        if constexpr (F32) {
-                            acc[j >> 2][nb][j & 3] += __uint_as_float(w[i][nb][j >> 2][j & 3]);
-                            acc[j >> 2][nb][(j & 3) + 1] += __uint_as_float(w[i][nb][j >> 2][(j & 3) + 1]);
-                        } else {
-                            const f16x2 h = __builtin_bit_cast(f16x2, (uint32_t)w[i][nb][0][j / 2]);
-                            acc[j >> 2][nb][j & 3] += __builtin_ldexpf((float)h[0], e);
-                            acc[j >> 2][nb][(j & 3) + 1] += __builtin_ldexpf((float)h[1], e);
-                        }
+                for (int i = 0; i < N; ++i) {
+                    const float fi = __builtin_amdgcn_exp2f(reference(i) - m);
+                    tail[i][0] = __float_as_uint(__uint_as_float(tail[i][0]) * fi);
+#pragma unroll
+                    for (int nb = 0; nb < NC; ++nb) {
+                        const float fb = __uint_as_float(of_block(__float_as_uint(fi), nb, x));
+#pragma unroll
+                        for (int j = 0; j < SW; ++j) w[i][nb][j / 4][j & 3] = __float_as_uint(__uint_as_float(w[i][nb][j / 4][j & 3]) * fb);
                     }
                 }
-                sum += __uint_as_float(tail[i][0]);
             }
-        };
-        int part = 0;
-        for (; part + AHEAD <= n_parts; part += AHEAD) add(part, std::integral_constant<int, AHEAD>{});
-        if (part + 2 <= n_parts) { add(part, std::integral_constant<int, 2>{}); part += 2; }
-        if (part < n_parts) add(part, std::integral_constant<int, 1>{});
-        Geometry<G> ge;
-        ge.init(aq.q_index, aq.R, Hq, Hkv, aq.n_row_tiles, aq.n_img_tiles, g, ordinal);
-        float l[NC], mref[NC];
-        bool bad = false;
+        } else {
 #pragma unroll
-        for (int nb = 0; nb < NC; ++nb) {
-            l[nb] = __uint_as_float(of_block(__float_as_uint(sum), nb, x));
-            mref[nb] = __uint_as_float(of_block(ref, nb, x));
-            float chk = l[nb];
+            for (int i = 0; i < N; ++i) done |= reference(i) == ITEM_DONE;
+        }
 #pragma unroll
-            for (int v = 0; v < 4; ++v) chk += fabsf(acc[0][nb][v]) + fabsf(acc[1][nb][v]);
-            bad = bad || !(chk < INFINITY) || !(l[nb] > 0.f);
+        for (int i = 0; i < N; ++i) {
+#pragma unroll
+            for (int nb = 0; nb < NC; ++nb) {
+                int e = 0;
+                if constexpr (!F32) e = (int)of_block(tail[i][P::exponent(2 * sl) - P::SUM], nb, x);
+#pragma unroll
+                for (int j = 0; j < 8; j += 2) {   // accumulators j and j + 1 of the slice's eight
+                    if constexpr (F32) {
+                        acc[j >> 2][nb][j & 3] += __uint_as_float(w[i][nb][j >> 2][j & 3]);
+                        acc[j >> 2][nb][(j & 3) + 1] += __uint_as_float(w[i][nb][j >> 2][(j & 3) + 1]);
+                    } else {
+                        const f16x2 h = __builtin_bit_cast(f16x2, (uint32_t)w[i][nb][0][j / 2]);
+                        acc[j >> 2][nb][j & 3] += __builtin_ldexpf((float)h[0], e);
+                        acc[j >> 2][nb][(j & 3) + 1] += __builtin_ldexpf((float)h[1], e);
+                    }
+                }
+            }
+            sum += __uint_as_float(tail[i][0]);
         }
-        if (!__syncthreads_or(bad ? 1 : 0)) {
-            store_slice<G, D>(ge, acc, sl, l, mref, aq.R, Hq, smem_raw, aq.out, aq.lse);
-            return;
-        }
+    };
+    int part = 0;
+    for (; part + AHEAD <= n_parts; part += AHEAD) add(part, std::integral_constant<int, AHEAD>{});
+    if (part + 2 <= n_parts) { add(part, std::integral_constant<int, 2>{}); part += 2; }
+    if (part < n_parts) add(part, std::integral_constant<int, 1>{});
+    if (__any(done)) return;   // the same in every wave
+    Geometry<G> ge;
+    ge.init_rows(Hq, Hkv, aq.n_row_tiles, g, ordinal);
+    float l[NC], mref[NC];
+#pragma unroll
+    for (int nb = 0; nb < NC; ++nb) {
+        l[nb] = __uint_as_float(of_block(__float_as_uint(sum), nb, x));
+        mref[nb] = __uint_as_float(of_block(__float_as_uint(ref), nb, x));
     }
-    // the sums overflowed the fixed exponent reference (rare): the item again, with a running maximum
-    __syncthreads();
-    running_max_item<G, D, SPLIT>(aq, g, ordinal, Hq, Hkv, scale_log2e, smem_raw, sl);
-}
-
-// ---- all items with the running maximum (FR_ATTN_SOFTMAX_RUNNING_MAX) -------------------------------------
-template <int G, int D, bool SPLIT>
-__global__ __launch_bounds__(256) void attn_running_max_kernel(const AttnBatch batch, int Hq, int Hkv,
-                                                               float scale_log2e) {
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-    BlockWork bw;
-    bw.init(batch.max_row_tiles, Hkv);
-    const AttnQuery& aq = batch.q[bw.query];
-    if (bw.ordinal >= aq.n_row_tiles) return;
-    running_max_item<G, D, SPLIT>(aq, bw.g, bw.ordinal, Hq, Hkv, scale_log2e, smem_raw);
+    store_slice<G, D>(ge, acc, sl, l, mref, aq.R, Hq, staging, aq.out, aq.lse);
 }
 
 // Where one query's packing pass leaves its results.
@@ -1324,27 +1249,14 @@ struct QueryScratch {
 
 template <int D, bool SPLIT>
 constexpr size_t LDS_FAST = std::max({sizeof(FastLds<D, SPLIT>), Img<D>::EPILOGUE_LDS, EXCHANGE_LDS<D>});
-template <int D>
-constexpr size_t LDS_SAFE = std::max((size_t)Img<D>::BYTES, Img<D>::EPILOGUE_LDS);
 
-// Raises the kernels' dynamic LDS limit, once per process (C++ initialises a function-local static exactly once,
+// Raises the kernel's dynamic LDS limit, once per process (C++ initialises a function-local static exactly once,
 // also when several host threads arrive together).
 template <int G, int D, bool SPLIT>
 hipError_t set_kernel_attributes() {
     static const hipError_t once = [] {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_fixed_ref_kernel<G, D, SPLIT>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_FAST<D, SPLIT>);
-        if (e != hipSuccess) return e;
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_combine_kernel<G, D, SPLIT, true>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_SAFE<D>);
-        if (e != hipSuccess) return e;
-        if constexpr (!SPLIT) {
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_combine_kernel<G, D, SPLIT, false>),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_SAFE<D>);
-            if (e != hipSuccess) return e;
-        }
-        return hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_running_max_kernel<G, D, SPLIT>),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_SAFE<D>);
+        return hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_fixed_ref_kernel<G, D, SPLIT>),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_FAST<D, SPLIT>);
     }();
     return once;
 }
@@ -1411,15 +1323,15 @@ hipError_t pack_shared(const Shape& s, int n, const SharedPackBatch& pb, const v
 // Launches the key-tile loop; with a live timer its event pair rides on the kernel's own dispatch (start and end of its
 // execution), so the stream carries no extra marker packets and the kernels before and after it are not held up.
 template <int G, int D, bool SPLIT>
-void launch_tile_loop(const AttnBatch& batch, dim3 grid, float* partials, int n_parts, bool half, const Shape& s, float scale_log2e,
-                      KernelTimer* timer, bool timed, hipStream_t st) {
+void launch_tile_loop(const AttnBatch& batch, dim3 grid, float* partials, int n_parts, bool half, bool exact, const Shape& s,
+                      float scale_log2e, KernelTimer* timer, bool timed, hipStream_t st) {
     if (timed) {
         const int slot = (int)(timer->n_recorded % timer->n_slots);
         hipExtLaunchKernelGGL((attn_fixed_ref_kernel<G, D, SPLIT>), grid, dim3(64 * FAST_WAVES), (uint32_t)LDS_FAST<D, SPLIT>, st, timer->start[slot],
-                              timer->stop[slot], 0u, batch, partials, n_parts, (int)half, s.Hq, s.Hkv, scale_log2e);
+                              timer->stop[slot], 0u, batch, partials, n_parts, (int)half, (int)exact, s.Hq, s.Hkv, scale_log2e);
         ++timer->n_recorded;
     } else {
-        attn_fixed_ref_kernel<G, D, SPLIT><<<grid, dim3(64 * FAST_WAVES), LDS_FAST<D, SPLIT>, st>>>(batch, partials, n_parts, (int)half, s.Hq, s.Hkv, scale_log2e);
+        attn_fixed_ref_kernel<G, D, SPLIT><<<grid, dim3(64 * FAST_WAVES), LDS_FAST<D, SPLIT>, st>>>(batch, partials, n_parts, (int)half, (int)exact, s.Hq, s.Hkv, scale_log2e);
     }
 }
 
@@ -1461,26 +1373,26 @@ bool half_parts(int n_img_tiles) { return !SPLIT && n_img_tiles >= 32; }
 template <int D>
 size_t part_bytes(bool half) { return (half ? Part<D, false>::WORDS : Part<D, true>::WORDS) * sizeof(float); }
 
-// Packed queries -> attention launches: tile loop (+ combine pass), or the running-maximum kernel.
+// Packed queries -> attention launches: tile loop (+ combine pass).
 template <int G, int D, bool SPLIT>
 hipError_t launch_packed(const Shape& s, const AttnBatch& batch, int n_parts, bool half, const Workspace& ws, int mode,
                          KernelTimer* timer, hipStream_t st) {
     const float scale_log2e = (1.0f / sqrtf((float)s.d)) * 1.4426950408889634f;
     const dim3 grid(batch.max_row_tiles * batch.n * s.Hkv);
-    if (mode == FR_ATTN_SOFTMAX_RUNNING_MAX) {   // every item with the running maximum
-        attn_running_max_kernel<G, D, SPLIT><<<grid, dim3(256), LDS_SAFE<D>, st>>>(batch, s.Hq, s.Hkv, scale_log2e);
+    if (mode == FR_ATTN_SOFTMAX_RUNNING_MAX) {   // every item whole
+        launch_tile_loop<G, D, SPLIT>(batch, grid, nullptr, 1, false, true, s, scale_log2e, nullptr, false, st);
         return hipGetLastError();
     }
     const bool timed = timer != nullptr && timer->n_slots > 0;
-    launch_tile_loop<G, D, SPLIT>(batch, dim3(grid.x * n_parts), ws.attn_partials, n_parts, half, s, scale_log2e, timer, timed, st);
-    if (n_parts > 1) {   // adds the parts, stores, and recomputes the items whose sums overflowed
+    launch_tile_loop<G, D, SPLIT>(batch, dim3(grid.x * n_parts), ws.attn_partials, n_parts, half, false, s, scale_log2e, timer, timed, st);
+    if (n_parts > 1) {
         if constexpr (!SPLIT) {
             if (half) {
-                attn_combine_kernel<G, D, SPLIT, false><<<dim3(grid.x * (D / 32)), dim3(256), LDS_SAFE<D>, st>>>(batch, ws.attn_partials, n_parts, s.Hq, s.Hkv, scale_log2e);
+                attn_combine_kernel<G, D, SPLIT, false><<<dim3(grid.x * (D / 32)), dim3(256), 0, st>>>(batch, ws.attn_partials, n_parts, s.Hq, s.Hkv);
                 return hipGetLastError();
             }
         }
-        attn_combine_kernel<G, D, SPLIT, true><<<dim3(grid.x * (D / 32)), dim3(256), LDS_SAFE<D>, st>>>(batch, ws.attn_partials, n_parts, s.Hq, s.Hkv, scale_log2e);
+        attn_combine_kernel<G, D, SPLIT, true><<<dim3(grid.x * (D / 32)), dim3(256), 0, st>>>(batch, ws.attn_partials, n_parts, s.Hq, s.Hkv);
     }
     return hipGetLastError();
 }

@@ -101,6 +101,36 @@ def test_attention_logits_beyond_the_fixed_reference(Hq, Hkv, d, split):
     ctx.close()
 
 
+# Parts of an item in 32 bits (short prompts; more than four; split weights) and in half precision (two, four parts of 33 key tiles), parts
+# without a key among them, and whole items
+@pytest.mark.parametrize("Hq,Hkv,d,total,split", [(8, 2, 128, 1300, B.FR_ATTN_SPLIT_AUTO), (2, 2, 128, 700, B.FR_ATTN_SPLIT_ON), (7, 1, 128, 1300, B.FR_ATTN_SPLIT_AUTO),
+                                                  (4, 2, 64, 1300, B.FR_ATTN_SPLIT_AUTO), (8, 2, 128, 2100, B.FR_ATTN_SPLIT_ON), (64, 8, 128, 2100, B.FR_ATTN_SPLIT_AUTO),
+                                                  (8, 2, 128, 2100, B.FR_ATTN_SPLIT_AUTO), (8, 2, 128, 700, B.FR_ATTN_SPLIT_OFF), (7, 1, 128, 2100, B.FR_ATTN_SPLIT_ON)])
+@pytest.mark.parametrize("size", [16.25, 40.0])
+def test_two_parts_beyond_the_reference(Hq, Hkv, d, total, split, size):
+    """Two keys far apart whose logits, for one head of each group, lie 2^124 or 2^300 above the first ones (half of the latter at
+    head_dim 64 and more): what overflows is done again with a reference of its own, the rest is not, and both come together.  Weights and
+    sums stay as precise as without."""
+    w = workload(Hq, Hkv, d, (total - 20,), 20, ratio=0.05)
+    w.q_full[:, ::Hq // Hkv, 0] = 60.0
+    w.k_full[:, :, 0] *= 0.01
+    for j, x in ((total // 4, size), (3 * total // 4, size + 0.125)):
+        w.k_full[j] *= 0.01
+        w.k_full[j, :, 0] = x
+    w.k_full = synth.round_to_storage(w.k_full, "bf16")
+    qi = np.concatenate([np.sort(np.random.default_rng(total).choice(total - 20, size=150, replace=False)), np.arange(total - 20, total)])
+    ctx = H.make_ctx(w.shape, total, w.n_chunks, w.nq)
+    ctx.fr_set_option(B.FR_OPT_ATTN_SPLIT, split)
+    got, lse = run_attention(ctx, w, qi, w.k_full, w.v_full)
+    want, want_lse = orc.sparse_prefill_attn(w.q_full[qi], qi, w.k_full, w.v_full, w.k_full[qi], w.v_full[qi])
+    ctx.close()
+    if Hq // Hkv == 7 or d == 64:
+        assert H.max_rel_err(got, want) <= OUT_TOL
+    else:
+        H.assert_close(got, want, "bf16", "attention")
+    assert np.max(np.abs(lse - want_lse) / np.maximum(1.0, np.abs(want_lse))) <= 1e-4
+
+
 # Row tiles hold 4 floor(64 / G) rows.  Short prompts are cut up to 128 items (row tiles x KV heads; half of 256 compute units),
 # prompts of 32 key tiles and more up to 400: one case on either side of both lines, and the smallest.
 @pytest.mark.parametrize("Hq,Hkv,d,lens", [(7, 1, 128, (500, 413)), (4, 2, 64, (500, 413)),                      # 28 and 16 items: eight parts
