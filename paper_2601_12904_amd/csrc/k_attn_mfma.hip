@@ -42,10 +42,8 @@
 // copies: no lookups, no pointer selects, no permutes, no address arithmetic, no staging registers.
 //
 // What a row does not see.  A weight of 0 does not take a NaN or an infinity out of a matrix product.  Positions behind the last
-// row of the Q index may hold anything: they are not read.  A value that is not finite and that only some rows of a tile see makes the
-// sums of the others NaN, which the overflow check finds; in the instances with split weights the second go then keeps such values apart.  (In
-// the others the code for it would cost the tile loop 0.6 % through its registers; there a row is NaN too if one of the at most 63
-// positions behind it in its last key tile is.)
+// row of the Q index may hold anything: they are not read.  A value that is not finite and that only some rows of an item see makes the
+// sums of the others NaN, which the overflow check finds; the second go then keeps such values apart.
 #include "fr_internal.hpp"
 #include "k_rotate.hpp"
 
@@ -816,8 +814,8 @@ constexpr size_t EXCHANGE_LDS = (size_t)FAST_WAVES * EXCHANGE_WAVE<D>;
 // again with EXACT = true, whose reference is the largest logit of the piece's own keys, found in a pass over them that forms nothing but
 // logits (a part then leaves it as its reference).  So both run the same loop in the same kernel.  A second kernel that looked for flagged items
 // cost 4 us per call and found none; a loop that rescales its accumulators to a running maximum spills registers, and one of four waves beside
-// this one took, with every item of 2970 of 16896 rows overflowing, 2190 us a call whole and 6180 in two parts, now 888 and 1125 (402 and 407
-// without overflow); without a fixed reference to begin with 1310 us, now 575.
+// this one took, with every item of 2970 of 16896 rows overflowing, 2190 us a call whole and 6180 in two parts, now 913 and 1190 (397 and 407
+// without overflow); without a fixed reference to begin with 1310 us, now 590.
 template <int G, int D, bool SPLIT, bool EXACT>
 __device__ __forceinline__ bool process_piece(const AttnQuery& aq, int g, int ordinal, int part, int n_parts, int item,
                                               float* __restrict__ partials, bool half, int Hq, int Hkv, float scale_log2e,
@@ -996,7 +994,7 @@ __device__ __forceinline__ bool process_piece(const AttnQuery& aq, int g, int or
     // and the matrix phase behind it, by all waves for the same tiles.
     bool apart = false;
     auto keep_apart = [&](int kt) {
-        if constexpr (EXACT && SPLIT) {
+        if constexpr (EXACT) {
             if (kt < n_plain) return;
             const bool found = drop_not_finite<D>(sm.vt[0] + vp + second * (4 * I::V_PLANE), wave & 3);
             apart = any_of_workgroup(found) || apart;

@@ -1,6 +1,6 @@
 """Attention must not depend on values that no row sees: stale cache rows of listed positions, rows behind the last listed
-one (a cache with room to spare, rows that the write-back has not reached yet), and, except in the tiled kernels of group sizes
-1, 2, 4 and 8 at head_dim 128, for a row whatever lies behind its own position.  All of them hold NaN or infinity here, which a weight of zero does not take away: `pytest -m gpu`."""
+one (a cache with room to spare, rows that the write-back has not reached yet), and for a row whatever lies behind its own
+position.  All of them hold NaN or infinity here, which a weight of zero does not take away: `pytest -m gpu`."""
 import numpy as np
 import pytest
 import torch
@@ -83,7 +83,11 @@ def test_rows_that_hold_nothing(case_args, option, with_new):
     ctx.close()
 
 
-@pytest.mark.parametrize("case_args,option", [(c, option) for c, option in CASES if c in FP32_PRODUCTS or c[:3] in ((7, 1, 128), (14, 2, 64))])
+# few rows of a long prompt: the 64 / G rows of a wave lie a dozen key tiles apart, as do the value and the rows in front of it
+SPARSE = [(Hq, Hkv, 128, "bf16", (700, 611, 800), 20, 0.03) for Hq, Hkv in ((2, 2), (4, 2), (8, 2), (16, 2), (7, 1))]
+
+
+@pytest.mark.parametrize("case_args,option", CASES + [(c, option) for c in SPARSE for option in (WHOLE, PARTS, RUNNING)])
 def test_values_that_are_not_finite_reach_later_rows_only(case_args, option):
     """A fresh value row with a NaN and an infinity, and a cached one that no listed row has replaced: rows in front of them
     are as without them, rows behind them have the NaN and the infinity in those elements and are otherwise as without them."""
