@@ -208,11 +208,10 @@ hipError_t launch_attn_mfma_shared_batch(const Shape& s, int n, const SharedBatc
                                          const void* v_store, const Workspace& ws, int softmax_mode, int split_mode, struct KernelTimer* timer,
                                          hipStream_t st);
 // An attention launch with few (row tile, KV head) items deals every item's key tiles to several workgroups
-// (parts), on its own up to ATTN_SPLIT_AUTO_ITEMS items at most (beyond that the items alone keep the chip busy and the partial
-// results' traffic costs more than the better balance gains): two parts, more (up to ATTN_MAX_PARTS) while that still
-// leaves at most one piece per compute unit.  FR_ATTN_SPLIT_ON asks for two parts at any size the partial-result buffer
-// takes.
-constexpr int ATTN_SPLIT_AUTO_ITEMS = 400;
+// (parts): two up to 1.5 items per compute unit at most (choose_parts has the line and its figures), more (up to ATTN_MAX_PARTS) while that
+// still leaves at most one piece per compute unit.  FR_ATTN_SPLIT_ON asks for two parts at any size the partial-result buffer
+// takes: ATTN_SPLIT_ITEMS items, a little more than 1.5 for each of 256 compute units.
+constexpr int ATTN_SPLIT_ITEMS = 400;
 constexpr int ATTN_MAX_PARTS = 8;
 size_t attn_mfma_partials_bytes(const Shape& s, int64_t max_tokens);
 

@@ -50,6 +50,7 @@
 #include <hip/hip_ext.h>
 
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 namespace fr {
@@ -1082,11 +1083,12 @@ __device__ __forceinline__ bool process_piece(const AttnQuery& aq, int g, int or
             bad = bad || !(chk < limit);
         }
     }
-    bad = any_of_workgroup(bad);   // (also: the exchange has been read)
     if (part >= 0) {   // leave the partial result; attn_combine_kernel adds the parts and stores
         float* dst = part_dst + 4 * (threadIdx.x & 255);
         if (!SPLIT && half) store_partial<D, false>(dst, oh, md0, l, mref, ge.kg); else store_partial<D, true>(dst, oh, md0, l, mref, ge.kg);
+        if constexpr (!EXACT) bad = any_of_workgroup(bad);
     } else {
+        if constexpr (EXACT) __syncthreads(); else bad = any_of_workgroup(bad);   // (also: the exchange has been read)
         store_output<G, D, MH>(ge, oh, md0, l, mref, R, Hq, smem_raw, aq.out, aq.lse);
     }
     return !bad;   // (stored all the same: the second go writes the same places, each from the same thread)
@@ -1335,34 +1337,51 @@ void launch_tile_loop(const AttnBatch& batch, dim3 grid, float* partials, int n_
 
 // Parts per item of a one-query launch of `items` (row tile, KV head) items over n_img_tiles key tiles.  With few items
 // the chip would idle behind the longest ones (rows ascend by position: the question rows' tiles walk the whole prompt),
-// so every item's key tiles are dealt to several workgroups, at the price of the partial results' traffic and the combine pass.
-// Two parts pay up to AUTO_ITEMS items (256 compute units, one workgroup each; both sides measured per layer).  Plain weights: 17k
-// tokens, 512 of them the question's: 288 items 492 us whole, 472 in two parts, 336 512 both, 376 518 : 539; 1024 of the question:
-// 320 items 614 : 635; 8k tokens: 288 items 222 : 213, 320 229 : 228 and 277 : 282, 352 284 : 297; 33k tokens: 296 items 1231 : 1265.
-// Split weights, twice the matrix work on a tile of the same partial results: 17k tokens of seven heads per KV head 340 items
-// 777 : 742, 388 805 : 811.
+// so every item's key tiles are dealt to several workgroups, at the price of the partial results' traffic, the combine pass, and a
+// prologue, an exchange between the waves and one matrix phase more per piece.  738 calls measured with one to eight parts, 100 to 17k tokens,
+// row sets spread over the prompt and at its end (their items are all long); the host cannot tell the two apart, so a line lies where what one
+// of them loses the other gains.  us a call, whole : two parts, 32 / 8 heads, spread : at the end:
+//   2600 tokens, 264 items   69 :  80 and  70 :  89      6000, 304 items  142 : 143 and 200 : 199     11600, 352 items  270 : 268 and 435 : 389
+//   4000 tokens, 264 items   97 :  98 and 117 : 134      8192, 328 items  190 : 191 and 293 : 272     16896, 352 items  384 : 381
+// 376 items of 16896 tokens, the ordinary request, are 391 : 403 spread and 657 : 589 at the end; above 1.5 items per compute unit the parts make a
+// fourth half round anyway (400 items at the end of 11600 tokens 434 : 484).  So: two parts from 32 key tiles on, up to a quarter of the compute
+// units in items for each doubling of the prompt beyond four key tiles, at most 11 / 8 of their number; split weights, twice the matrix work
+// on a tile of the same partial results, an eighth more, at most 1.5 times, and at head_dim 64, half the partial results, 1.5 times in any case.
 // Below half a workgroup per compute unit more parts pay until there is about one piece per compute unit (question-only prefill, 64
-// items: 446 us whole, 302, 253, 244, 277, 268 in two, three, four, six, eight parts); in between two parts stay best (168 items at
-// 5 %: 359 us, 388 and 373 in three and four).  Short prompts (under 32 key tiles) are cut only below half a workgroup per compute
-// unit, down to two tiles a part: a tile is 1.1 us of a workgroup, the combine pass 7.1 us (920 tokens, 24 items of up to 15 tiles:
-// 30.2 us whole, 18.1 + 7.1 in eight parts).
-template <bool SPLIT>
-constexpr int AUTO_ITEMS = SPLIT ? ATTN_SPLIT_AUTO_ITEMS : 320;
-template <bool SPLIT>
+// items: 446 us whole, 302, 253, 244, 277, 268 in two, three, four, six, eight parts, with the loop of four waves); in between two parts stay best.
+// The smallest piece: four tiles (32 / 8 heads, 24 items of 8 tiles 24.4 us whole, 23.6, 22.8, 23.2, 24.1 in two to five parts; 40 of 5 tiles 20.4 whole,
+// 23.0 in two), two where there are next to no items or the weights are split (28 / 4 heads, 20 items of 8 tiles 33.7 whole, 29.6, 29.0, 27.7, 28.7 in two to
+// five parts); more than a quarter of a workgroup per compute unit and fewer than 16 tiles stay whole (64 items of 8 tiles 23.7 whole, 25.3 and 27.1 in
+// two and four parts).
+template <int D, bool SPLIT>
 int choose_parts(int split_mode, int items, int n_img_tiles, int n_cu, size_t part_bytes, size_t partials_bytes) {
     int parts = 1;
     if (split_mode == FR_ATTN_SPLIT_ON) parts = 2;
     if (split_mode == FR_ATTN_SPLIT_AUTO) {
-        if (2 * items <= n_cu) parts = std::min({ATTN_MAX_PARTS, n_cu / std::max(items, 1), (n_img_tiles + 1) / 2});
-        if (n_img_tiles >= 32 && items <= AUTO_ITEMS<SPLIT>) parts = std::max(parts, 2);
+        const int tiles = n_img_tiles;
+        if (2 * items <= n_cu) {
+            int pieces;
+            if (SPLIT)
+                pieces = tiles == 4 || tiles == 5 ? tiles : (tiles + 1) / 2;   // (a tile each, in one round trip: 28 / 4 heads, 8 items of 5 tiles 24.9 us in three parts, 24.5 in five)
+            else if (32 * items <= n_cu)
+                pieces = tiles < 5 ? 1 : (tiles + 1) / 2;
+            else if (tiles < 6 || (tiles < 16 && 4 * items > n_cu))
+                pieces = 1;
+            else
+                pieces = tiles < 10 ? (tiles + 2) / 3 : (tiles + 2) / 4;
+            parts = std::max(1, std::min({ATTN_MAX_PARTS, n_cu / std::max(items, 1), pieces}));
+        }
+        const int most = n_cu + (SPLIT ? n_cu / 2 : 3 * n_cu / 8);
+        const float line = n_cu / 4 * std::log2(tiles / 4.f) + (SPLIT ? n_cu / 8 : 0);
+        if (tiles >= 32 && items <= most && (D == 64 || items <= line)) parts = std::max(parts, 2);
     }
     while (parts > 1 && (size_t)items * parts * part_bytes > partials_bytes) --parts;
     return parts;
 }
 
 // Half-precision partial results: only for a single query of a long prompt (32 key tiles and more) whose weights are plain
-// bf16, where 376 items in two parts would otherwise move 2 x 108 MB of partial sums (combine pass 21.1 us, 15.5 us in half
-// precision).  Short prompts, batches and more than four parts, a few hundred pieces at most, keep all 32 bits
+// bf16, where 376 items in two parts would otherwise move 2 x 101.6 MB of partial sums (2 x 52.3 in half precision; combine pass XX us).
+// Short prompts, batches and more than four parts, a few hundred pieces at most, keep all 32 bits
 // (6730 tokens, 32 items: 2.174e-3 off float64 in eight parts, 2.184e-3 in four of half precision; the layer takes 163 us, 159 in
 // eight of half precision, 183 in four).
 constexpr int HALF_MAX_PARTS = 4;
@@ -1413,7 +1432,7 @@ hipError_t launch(const Shape& s, const void* q_rows, const int32_t* q_index, in
     batch.max_row_tiles = batch.q[0].n_row_tiles;
     bool half = half_parts<SPLIT>(batch.q[0].n_img_tiles);
     auto parts_of = [&](bool h) {
-        return choose_parts<SPLIT>(split_mode, batch.q[0].n_row_tiles * s.Hkv, batch.q[0].n_img_tiles, ws.n_cu, part_bytes<D>(h),
+        return choose_parts<D, SPLIT>(split_mode, batch.q[0].n_row_tiles * s.Hkv, batch.q[0].n_img_tiles, ws.n_cu, part_bytes<D>(h),
                             ws.attn_partials_bytes);
     };
     int n_parts = parts_of(half);
@@ -1443,7 +1462,7 @@ hipError_t launch_shared_batch(const Shape& s, int n, const SharedBatchQuery* qs
                           ws.rope_theta, false, &batch.q[i], &pb.q[i], st);
         if (e != hipSuccess) return e;
         batch.max_row_tiles = std::max(batch.max_row_tiles, batch.q[i].n_row_tiles);
-        n_parts = std::max(n_parts, choose_parts<SPLIT>(split_mode, batch.q[i].n_row_tiles * s.Hkv, batch.q[i].n_img_tiles,
+        n_parts = std::max(n_parts, choose_parts<D, SPLIT>(split_mode, batch.q[i].n_row_tiles * s.Hkv, batch.q[i].n_img_tiles,
                                                         ws.n_cu, slot, ws.attn_partials_bytes));
     }
     e = pack_shared(s, n, pb, k_store, v_store, st);
@@ -1453,7 +1472,7 @@ hipError_t launch_shared_batch(const Shape& s, int n, const SharedBatchQuery* qs
     const int items = batch.max_row_tiles * n * s.Hkv;
     int tiles = 0;
     for (int i = 0; i < n; ++i) tiles = std::max(tiles, batch.q[i].n_img_tiles);
-    if (4 * items > ws.n_cu) n_parts = choose_parts<SPLIT>(split_mode, items, tiles, ws.n_cu, slot, ws.attn_partials_bytes);
+    if (4 * items > ws.n_cu) n_parts = choose_parts<D, SPLIT>(split_mode, items, tiles, ws.n_cu, slot, ws.attn_partials_bytes);
     while (n_parts > 1 && (size_t)items * n_parts * slot > ws.attn_partials_bytes) --n_parts;
     return launch_packed<G, D, SPLIT>(s, batch, n_parts, false, ws, mode, timer, st);
 }
@@ -1469,8 +1488,8 @@ static bool own_instance(const Shape& s) { return s.d == 128 && (s.G == 1 || s.G
 // Partial results of a launch in parts: one slot per piece.
 size_t attn_mfma_partials_bytes(const Shape& s, int64_t max_tokens) {
     const int64_t tr = 4 * (64 / s.G);   // token rows per workgroup
-    const int64_t items = std::min<int64_t>(((max_tokens + tr - 1) / tr) * s.Hkv, ATTN_SPLIT_AUTO_ITEMS);
-    // two parts of the most items that are split without being asked (32-bit words unless they may be half_parts), and up
+    const int64_t items = std::min<int64_t>(((max_tokens + tr - 1) / tr) * s.Hkv, ATTN_SPLIT_ITEMS);
+    // two parts of ATTN_SPLIT_ITEMS items (32-bit words unless they may be half_parts), and up
     // to eight parts of few items (about one piece per compute unit), always in 32 bits
     const size_t full = (s.d == 128 ? Part<128, true>::WORDS : Part<64, true>::WORDS) * sizeof(float);
     const size_t half = own_instance(s) ? Part<128, false>::WORDS * sizeof(float) : full;

@@ -104,7 +104,7 @@ def test_attention_logits_beyond_the_fixed_reference(Hq, Hkv, d, split):
 # Parts of an item in 32 bits (short prompts; more than four; split weights) and in half precision (two, four parts of 33 key tiles), parts
 # without a key among them, and whole items
 @pytest.mark.parametrize("Hq,Hkv,d,total,split", [(8, 2, 128, 1300, B.FR_ATTN_SPLIT_AUTO), (2, 2, 128, 700, B.FR_ATTN_SPLIT_ON), (7, 1, 128, 1300, B.FR_ATTN_SPLIT_AUTO),
-                                                  (4, 2, 64, 1300, B.FR_ATTN_SPLIT_AUTO), (8, 2, 128, 2100, B.FR_ATTN_SPLIT_ON), (64, 8, 128, 2100, B.FR_ATTN_SPLIT_AUTO),
+                                                  (4, 2, 64, 1300, B.FR_ATTN_SPLIT_AUTO), (8, 2, 128, 2100, B.FR_ATTN_SPLIT_ON), (80, 10, 128, 2100, B.FR_ATTN_SPLIT_AUTO),
                                                   (8, 2, 128, 2100, B.FR_ATTN_SPLIT_AUTO), (8, 2, 128, 700, B.FR_ATTN_SPLIT_OFF), (7, 1, 128, 2100, B.FR_ATTN_SPLIT_ON)])
 @pytest.mark.parametrize("size", [16.25, 40.0])
 def test_two_parts_beyond_the_reference(Hq, Hkv, d, total, split, size):
@@ -132,11 +132,11 @@ def test_two_parts_beyond_the_reference(Hq, Hkv, d, total, split, size):
 
 
 # Row tiles hold 4 floor(64 / G) rows.  Short prompts are cut up to 128 items (row tiles x KV heads; half of 256 compute units),
-# prompts of 32 key tiles and more up to 400: one case on either side of both lines, and the smallest.
+# prompts of 33 key tiles up to 64 log2(33 / 4) + 32 = 226: one case on either side of both lines, and the smallest.
 @pytest.mark.parametrize("Hq,Hkv,d,lens", [(7, 1, 128, (500, 413)), (4, 2, 64, (500, 413)),                      # 28 and 16 items: eight parts
                                            (28, 4, 128, (500, 413)), (56, 8, 128, (500, 413)),                  # 112 in two parts, 224 whole
                                            (32, 16, 64, (500, 413)), (34, 17, 64, (500, 413)),                  # 128 in two parts, 136 whole
-                                           (42, 6, 128, (1000, 990)), (56, 8, 128, (1000, 990))])               # 348 in two parts, 464 whole
+                                           (21, 3, 128, (1000, 990)), (42, 6, 128, (1000, 990)), (56, 8, 128, (1000, 990))])   # 174 in two parts, 348 and 464 whole
 def test_items_on_both_sides_of_the_split_rules(Hq, Hkv, d, lens):
     """Every row of a prompt of several key tiles (100 % recompute equals dense causal attention)."""
     w = workload(Hq, Hkv, d, lens, 65, ratio=1.0)
@@ -338,12 +338,13 @@ def test_parts_in_half_precision_and_in_32_bits(Hq, Hkv, rows, split, parts, key
         assert off <= 2.5e-3 and (runaway or off > 2e-4)
 
 
-@pytest.mark.parametrize("rows,parts", [(1280, 2), (1281, 1)])
-def test_where_items_stay_whole(rows, parts):
-    """40 row tiles of 32 rows and 8 KV heads, 320 items, are the last to be cut in two by themselves (half-precision sums: the bound
-    above); one row more and every item is whole, bit for bit the result with the cutting off."""
+@pytest.mark.parametrize("rows,key_tiles,parts", [(768, 33, 2), (769, 33, 1), (1024, 64, 2), (1025, 64, 1), (1408, 257, 2), (1409, 257, 1)])
+def test_where_items_stay_whole(rows, key_tiles, parts):
+    """Row tiles of 32 rows and 8 KV heads.  64 log2(33 / 4) = 194.7: of 33 key tiles, 192 items are the last to be cut in two by
+    themselves (half-precision sums: the bound above); one row more and every item is whole, bit for bit the result with the cutting off.
+    64 key tiles: 256 items; 182 and more: 352, 11 / 8 of 256 compute units."""
     shape = synth.LayerShape(n_q_heads=64, n_kv_heads=8, head_dim=128, dtype="bf16", rope_base=500000.0)
-    L, nq = 64 * 33 - 5, 40
+    L, nq = 64 * key_tiles - 5, 40
     w = synth.config_small_bf16(seed=3, chunk_lens=(L - nq,), nq=nq, shape=shape)
     qi = np.concatenate([np.sort(np.random.default_rng(1).choice(L - nq, size=rows - nq, replace=False)), np.arange(L - nq, L)])
     k_cache, v_cache = assembled_cache(w, w.k_cached)
