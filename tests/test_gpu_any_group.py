@@ -301,6 +301,34 @@ def test_parts_of_short_prompts_keep_32_bits(Hq, Hkv, d):
     assert np.linalg.norm(outs[1] - outs[0]) <= 1.2e-4 * np.linalg.norm(outs[0])
 
 
+@pytest.mark.parametrize("d", [64, 128])
+def test_fp32_sums_round_once_per_key_block(d):
+    """Keys of zeros: every weight is 1 and the sums of the values, from [1, 2), show nothing but their own rounding.  The oracle's
+    counterpart adds 16 keys at a time with one rounding, in eight chains (the waves; blocks dealt in turn), and the chains one after
+    the other.  A matrix product onto the running sum rounds that several times a block: 2.4 times the error measured; with two
+    roundings a block it would be the root of 2 in the chains, 1.25 in all, so 1.2."""
+    L, R, rng = 8000, 16, np.random.default_rng(d)
+    shape = synth.LayerShape(n_q_heads=4, n_kv_heads=4, head_dim=d, dtype="f32", rope_base=10000.0)
+    v = (1.0 + rng.random((L, 4, d))).astype(np.float32)
+    ctx = H.make_ctx(shape, L, 1, R)
+    out = torch.zeros((R, 4, d), dtype=torch.float32, device="cuda")
+    ctx.fr_sparse_prefill_attn(H.dev(rng.standard_normal((R, 4, d)).astype(np.float32), "f32"), torch.arange(L - R, L, dtype=torch.int32, device="cuda"), R,
+                               torch.zeros((L, 4, d), device="cuda"), H.dev(v, "f32"), L, None, None, out)
+    torch.cuda.synchronize()
+    ctx.close()
+    got = out.cpu().numpy().astype(np.float64)[-1]
+    want = v.astype(np.float64).mean(axis=0)
+    blocks = v.astype(np.float64).reshape(L // 16, 16, 4, d).sum(axis=1)
+    total = np.zeros((4, d), dtype=np.float32)
+    for wave in range(8):
+        chain = np.zeros((4, d), dtype=np.float32)
+        for b in blocks[wave::8]:
+            chain = (chain + b).astype(np.float32)
+        total = total + chain
+    once = (total / np.float32(L)).astype(np.float64)
+    assert np.linalg.norm(got - want) <= 1.2 * np.linalg.norm(once - want)
+
+
 # (query heads, recomputed context rows, split): two parts are asked for; eight parts of the few items of a small call; four
 # parts (64 items of 32 rows)
 @pytest.mark.parametrize("Hq,Hkv,rows,split,parts", [(Hq, 2, 30, B.FR_ATTN_SPLIT_ON, 2) for Hq in (2, 4, 8, 16)] +
