@@ -66,12 +66,13 @@ struct Tiling {
     static constexpr int BRT = BR;                       // and rows
     static constexpr int WAVE_TILES = NW;                // 64 x 64 pieces of the output tile
     // What a launch takes (plan_tiling): time per K tile of a full round, the share of it that a nearly empty round still
-    // takes (a full round is held back by the chip's power limit), launch, pipeline fill and epilogue, a split last round.
-    // Chosen so that the better of the two tilings is taken: over 742 products (N 256 .. 28672, K 128 .. 14336, 1 .. 4096
-    // rows) the choice was 0.2 % slower than the faster one on average, two K tiles of many features its worst (9 %).  The 256 x 256 tiling's
-    // four are fitted again to its 16 x 16 x 32 instructions, at 73 products near the line: 0.14 % on average, 2.7 % at worst
-    // (672 rows, 4096 x 8192, 61.6 us in 48 tiles of five parts, 58.2 in 96 of two; 2112 rows 145 in 144 tiles, 134.7 in 272).
-    static constexpr float US_PER_K_TILE = 0.9f, ROUND_BASE = 0.33f, US_LAUNCH = 8.0f, US_SPLIT = 6.0f;
+    // takes (a full round is held back by the chip's power limit), the same where that round is the launch's only one, its tiles whole or split,
+    // launch, pipeline fill and epilogue, a split last round.
+    // Chosen so that the better of the two tilings is taken, at first over 742 products (N 256 .. 28672, K 128 .. 14336, 1 .. 4096 rows).  With the 256 x 256
+    // tiling's 16 x 16 x 32 instructions, over 482 products at and near the line: the choice is 0.4 % off the faster one on average (the shares of a last round for every
+    // launch: 2.6 %); single products up to 15 % (328 rows, 28672 x 11008, 289 us in 256 x 128, 252 in 256 x 256).  1100 rows of 4096 x 8192, 144 whole tiles of
+    // 256 x 128 or 80 of 256 x 256 in three parts: 82 and 88 us.
+    static constexpr float US_PER_K_TILE = 0.9f, ROUND_BASE = 0.33f, ONLY_BASE = 0.24f, ONLY_BASE_SPLIT = 0.33f, US_LAUNCH = 8.0f, US_SPLIT = 6.0f;
     static __host__ __device__ constexpr int feature0(int v) { return 64 * (v % WF); }
     static __host__ __device__ constexpr int row_0(int v) { return 64 * (v / WF); }
     // feature tiles fastest, so that workgroups that share an activation tile are neighbours
@@ -402,7 +403,7 @@ struct Tiling256 {
     static constexpr int STAGE = 4 * PIECE;                // [w0 w1][w2 w3][a0][a1]
     static constexpr int WAVE_TILES = 16;                  // 64 x 64 pieces of the output tile, two per wave
     static constexpr int LDS_BYTES = NW * 64 * EPI_PITCH * 4;
-    static constexpr float US_PER_K_TILE = 1.47f, ROUND_BASE = 0.30f, US_LAUNCH = 9.5f, US_SPLIT = 17.0f;   // see Tiling
+    static constexpr float US_PER_K_TILE = 1.47f, ROUND_BASE = 0.30f, ONLY_BASE = 0.20f, ONLY_BASE_SPLIT = 0.15f, US_LAUNCH = 9.5f, US_SPLIT = 17.0f;   // see Tiling
     static_assert(2 * STAGE <= LDS_BYTES, "the epilogue staging is the larger one");
     static __host__ __device__ constexpr int feature0(int v) { return 128 * (v >> 3) + 64 * (v & 1); }   // v = 2 wave + half
     static __host__ __device__ constexpr int row_0(int v) { return 64 * ((v >> 1) & 3); }
@@ -693,7 +694,8 @@ Plan plan_tiling(const GemmArgs& g, int n_cu, const GemmTuning& tune) {
     p.n_parts = std::max(n_parts, 1);
     p.n_whole = p.n_parts > 1 ? p.n_tiles - rest : p.n_tiles;
     const float last = (float)(rest * p.n_parts) / (float)n_cu;   // share of the CUs that the last round keeps busy
-    const float last_round = rest ? TL::ROUND_BASE + (1.0f - TL::ROUND_BASE) * last : 0.0f;
+    const float base = p.n_tiles > n_cu ? TL::ROUND_BASE : p.n_parts > 1 ? TL::ONLY_BASE_SPLIT : TL::ONLY_BASE;
+    const float last_round = rest ? base + (1.0f - base) * last : 0.0f;
     p.us = TL::US_PER_K_TILE * n_kt * ((float)(p.n_tiles / n_cu) + last_round / (float)p.n_parts) + TL::US_LAUNCH +
            (p.n_parts > 1 ? TL::US_SPLIT : 0.0f);
     return p;
