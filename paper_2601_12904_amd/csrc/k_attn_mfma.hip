@@ -1127,7 +1127,7 @@ __global__ __launch_bounds__(64 * FAST_WAVES) void attn_fixed_ref_kernel(const A
 
 // ---- combine: adds the parts of every item and stores like the fast path's own epilogue.  One workgroup per (item, 32 dims of the output):
 //      the pass is bound by the latency of its loads, and a workgroup per item left a short prompt's 24 items in eight parts to 24 compute units
-//      (24 us; now 7.5; the offline stage's 128 items in two parts 13.6 -> 7.6).  A column's sum is added up by every slice.
+//      (24 us; now 4 to 6; the offline stage's 128 items in two parts 13.6 -> 6.6).  A column's sum is added up by every slice.
 //      grid.x = ((query * max_row_tiles + ordinal) * D / 32 + slice) * Hkv + KV head.
 template <int G, int D, bool SPLIT, bool F32>
 __global__ __launch_bounds__(256, 2) void attn_combine_kernel(const AttnBatch batch, const float* __restrict__ partials,
@@ -1380,7 +1380,8 @@ int choose_parts(int split_mode, int items, int n_img_tiles, int n_cu, size_t pa
 }
 
 // Half-precision partial results: only for a single query of a long prompt (32 key tiles and more) whose weights are plain
-// bf16, where 376 items in two parts would otherwise move 2 x 101.6 MB of partial sums (2 x 52.3 in half precision; combine pass XX us).
+// bf16, where the most items that are cut on their own, 352 in two parts, would otherwise move 2 x 95.2 MB of partial sums, as they are 2 x 49.0
+// (combine pass 12.8 us; 332 items in 32 bits, split weights, 18.8).
 // Short prompts, batches and more than four parts, a few hundred pieces at most, keep all 32 bits
 // (6730 tokens, 32 items: 2.174e-3 off float64 in eight parts, 2.184e-3 in four of half precision; the layer takes 163 us, 159 in
 // eight of half precision, 183 in four).

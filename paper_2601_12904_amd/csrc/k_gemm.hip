@@ -69,9 +69,9 @@ struct Tiling {
     // takes (a full round is held back by the chip's power limit), the same where that round is the launch's only one, its tiles whole or split,
     // launch, pipeline fill and epilogue, a split last round.
     // Chosen so that the better of the two tilings is taken, at first over 742 products (N 256 .. 28672, K 128 .. 14336, 1 .. 4096 rows).  With the 256 x 256
-    // tiling's 16 x 16 x 32 instructions, over 482 products at and near the line: the choice is 0.4 % off the faster one on average (the shares of a last round for every
-    // launch: 2.6 %); single products up to 15 % (328 rows, 28672 x 11008, 289 us in 256 x 128, 252 in 256 x 256).  1100 rows of 4096 x 8192, 144 whole tiles of
-    // 256 x 128 or 80 of 256 x 256 in three parts: 82 and 88 us.
+    // tiling's 16 x 16 x 32 instructions: over 352 products (32 row counts of 11 shapes) the choice is 0.3 % off the faster one on average, 18 % at worst (384 rows,
+    // 28672 x 4096, 101 us in 256 x 128, 86 in 256 x 256); over 130 more, picked because estimates disagree there, 4.5 %, 37 % at worst (877 rows, 18944 x 4096,
+    // 175 us, 128 in 256 x 256).  1100 rows of 4096 x 8192, 144 whole tiles of 256 x 128 or 80 of 256 x 256 in three parts: 82 and 88 us.
     static constexpr float US_PER_K_TILE = 0.9f, ROUND_BASE = 0.33f, ONLY_BASE = 0.24f, ONLY_BASE_SPLIT = 0.33f, US_LAUNCH = 8.0f, US_SPLIT = 6.0f;
     static __host__ __device__ constexpr int feature0(int v) { return 64 * (v % WF); }
     static __host__ __device__ constexpr int row_0(int v) { return 64 * (v / WF); }
