@@ -1127,7 +1127,7 @@ __global__ __launch_bounds__(64 * FAST_WAVES) void attn_fixed_ref_kernel(const A
 
 // ---- combine: adds the parts of every item and stores like the fast path's own epilogue.  One workgroup per (item, 32 dims of the output):
 //      the pass is bound by the latency of its loads, and a workgroup per item left a short prompt's 24 items in eight parts to 24 compute units
-//      (24 us; now 4 to 6; the offline stage's 128 items in two parts 13.6 -> 6.6).  A column's sum is added up by every slice.
+//      (24 us; with one per 32 dims 7.5, in four parts 4.2).  A column's sum is added up by every slice.
 //      grid.x = ((query * max_row_tiles + ordinal) * D / 32 + slice) * Hkv + KV head.
 template <int G, int D, bool SPLIT, bool F32>
 __global__ __launch_bounds__(256, 2) void attn_combine_kernel(const AttnBatch batch, const float* __restrict__ partials,

@@ -242,8 +242,7 @@ __global__ __launch_bounds__(64) void select_topk_wave_kernel(const float* __res
         for (int o = 32; o > 0; o >>= 1) diff |= (uint32_t)__shfl_xor((int)diff, o);
         diff = __builtin_amdgcn_readfirstlane(diff);
         int bit = diff ? 31 - __clz((int)diff) : -1;                       // highest bit in which two keys differ
-        thr = bit >= 31 ? 0u : bit < 0 ? key0 : key0 >> (bit + 1) << (bit + 1);
-        need_eq = (uint32_t)n;                                             // (at least k keys reach thr; all of them would be equal to it)
+        thr = bit >= 31 ? 0u : bit < 0 ? key0 : key0 >> (bit + 1) << (bit + 1);   // (at least k keys reach it)
         bool exact = false;
         for (; bit >= 0 && !exact; --bit) {
             const uint32_t cand = thr | 1u << bit;

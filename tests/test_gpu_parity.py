@@ -534,7 +534,7 @@ def test_layer_under_hip_graph():
 
 
 def test_attention_softmax_modes_agree():
-    """The running-maximum kernel alone (forced through fr_set_option) gives the oracle's result too."""
+    """Every item against the largest logit of its keys (forced through fr_set_option) gives the oracle's result too."""
     w = workloads()["small_bf16"](5)
     k_ctx, _, k, qi = staged(w)
     k_cache, v_cache = assembled_cache(w, k_ctx)
@@ -542,7 +542,7 @@ def test_attention_softmax_modes_agree():
     want, want_lse = orc.sparse_prefill_attn(w.q_full[qi], qi, k_cache, v_cache, w.k_full[qi], w.v_full[qi])
     ctx.fr_set_option(B.FR_OPT_ATTN_SOFTMAX, B.FR_ATTN_SOFTMAX_RUNNING_MAX)
     got, lse = run_attention(ctx, w, qi, k_cache, v_cache)
-    H.assert_close(got, want, "bf16", "running-max attention")
+    H.assert_close(got, want, "bf16", "attention against the largest logit")
     assert np.max(np.abs(lse - want_lse)) <= 2e-3
     ctx.fr_set_option(B.FR_OPT_ATTN_SOFTMAX, B.FR_ATTN_SOFTMAX_AUTO)
     got2, _ = run_attention(ctx, w, qi, k_cache, v_cache)
@@ -555,7 +555,7 @@ def test_attention_softmax_modes_agree():
 def test_attention_logits_far_above_the_first_keys():
     """Degenerate case of the fixed exponent reference: logits that grow along the sequence until exp2 would
     overflow against the maximum of the first 32 keys.  The default path must still match the oracle (the
-    overflowing workgroups are recomputed with a running maximum)."""
+    overflowing workgroups do their items again against the largest logit)."""
     shape = synth.LLAMA3_8B_BF16
     rng = np.random.default_rng(11)
     L_ctx, nq, d = 600, 24, shape.head_dim
@@ -656,8 +656,8 @@ def test_attention_kernel_timer():
 
 
 def test_attention_split_with_runaway_logits():
-    """Split launch + overflow of the fixed exponent reference: the combine step must flag the workgroups and the
-    running-maximum kernel recompute them."""
+    """Split launch + overflow of the fixed exponent reference: the parts that overflow are done again, and the combine step must
+    allow for their references."""
     shape = synth.LLAMA3_8B_BF16
     rng = np.random.default_rng(12)
     L_ctx, nq, d = 500, 40, shape.head_dim

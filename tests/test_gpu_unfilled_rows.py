@@ -48,8 +48,8 @@ def attend(ctx, w, qi, q, k_cache, v_cache, k_new=None, v_new=None, writeback=Fa
 # head_dim 64 and 128, bf16 with more than 64 heads per KV head
 FP32_PRODUCTS = [(4, 4, 64, "f32", (128, 77), 32, 0.15), (4, 1, 64, "f32", (130, 60), 9, 0.15), (5, 1, 128, "f32", (260, 40), 9, 0.2),
                  (2, 2, 64, "f32", (8100, 200), 21, 0.01), (80, 1, 64, "bf16", (90, 60), 5, 0.2)]
-# the tiled kernels: group sizes with and without an instance of their own, head_dim 64; items whole, in parts, and with a
-# running maximum throughout
+# the tiled kernels: group sizes with and without an instance of their own, head_dim 64; items whole, in parts, and against the
+# largest logit throughout
 TILED = [(Hq, Hkv, d, "bf16", (130, 0, 333, 61), 37, 0.2) for Hq, Hkv, d in ((4, 4, 128), (4, 2, 128), (8, 2, 128), (16, 2, 128), (7, 1, 128), (14, 2, 64))]
 WHOLE, PARTS, RUNNING = (B.FR_OPT_ATTN_SPLIT, B.FR_ATTN_SPLIT_OFF), (B.FR_OPT_ATTN_SPLIT, B.FR_ATTN_SPLIT_ON), (B.FR_OPT_ATTN_SOFTMAX, B.FR_ATTN_SOFTMAX_RUNNING_MAX)
 CASES = [(c, WHOLE) for c in FP32_PRODUCTS] + [(c, option) for c in TILED for option in (WHOLE, PARTS, RUNNING)]
