@@ -14,8 +14,8 @@
 // see whole is searched for values that are not finite.
 // A block's product is formed from zero and added to the running sum with one rounding: onto the running sum the product rounds that several
 // times a block, which the longer chains of eight waves had made 1 to 3 % worse against float64 than 16 (head_dim 64: 1.652e-7 with 16
-// waves, 1.670e-7 with eight, now 1.610e-7 at 109 of 544 positions; 1.5 to 2 % of the call).
-// 4 heads, head_dim 64, us a call: 42 rows of 272 positions 9.0, 109 of 544 13.0, 310 of 800 17.0, 768 of 1280 24.8; with 16 waves per
+// waves, 1.670e-7 with eight, now 1.610e-7 at 109 of 544 positions; 1 % of the call).
+// 4 heads, head_dim 64, us a call: 42 rows of 272 positions 9.0, 109 of 544 12.9, 310 of 800 16.9, 768 of 1280 24.7; with 16 waves per
 // workgroup and the values of a key as four scalar loads 11.1, 15.2, 18.9, 26.0.  Four waves are slower, and so is asking for the values of the
 // next block, or of three blocks, ahead of the products: more code, and the calls are short enough to be bound by fetching it.
 #include "fr_internal.hpp"
@@ -124,9 +124,7 @@ __global__ __launch_bounds__(64 * W) void attn_f32_kernel(const T* __restrict__ 
             psum += p[i];
         }
         l = l * alpha + psum;
-        f32x4 pv[NJ];   // of this block alone: added to o with one rounding, so the number of blocks a wave walks counts for little
-#pragma unroll
-        for (int md = 0; md < NJ; ++md) pv[md] = f32x4{0.f, 0.f, 0.f, 0.f};
+        float scale_o = alpha;
         if (16 * b + 15 > p_first) {   // values that are not finite: out of the product, into the columns that see them
             float z = 0.f;   // NaN if one of them is not finite
 #pragma unroll
@@ -135,6 +133,9 @@ __global__ __launch_bounds__(64 * W) void attn_f32_kernel(const T* __restrict__ 
                 for (int md = 0; md < NJ; ++md) z = __builtin_fmaf(value(i, md), 0.f, z);
             const bool odd = !(z == 0.f);
             if (__builtin_expect(__any(odd), 0)) {
+#pragma unroll
+                for (int md = 0; md < NJ; ++md) o[md] *= alpha;
+                scale_o = 1.f;
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -148,20 +149,22 @@ __global__ __launch_bounds__(64 * W) void attn_f32_kernel(const T* __restrict__ 
 #pragma unroll
                             for (int e = 0; e < 4; ++e) {
                                 const float v = __shfl(apart, 16 * src + 4 * kg + e);   // row 4 kg + e of the product
-                                if (seen && v != 0.f) pv[md][e] += weight * v;
+                                if (seen && v != 0.f) o[md][e] += weight * v;
                             }
                         }
                     }
             }
         }
+        f32x4 pv[NJ];   // of this block alone: added to o with one rounding, so the number of blocks a wave walks counts for little
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
-            for (int md = 0; md < NJ; ++md) pv[md] = __builtin_amdgcn_mfma_f32_16x16x4f32(value(i, md), p[i], pv[md], 0, 0, 0);
+            for (int md = 0; md < NJ; ++md)
+                pv[md] = __builtin_amdgcn_mfma_f32_16x16x4f32(value(i, md), p[i], i == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : pv[md], 0, 0, 0);
 #pragma unroll
         for (int md = 0; md < NJ; ++md)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) o[md][e] = __builtin_fmaf(o[md][e], alpha, pv[md][e]);
+            for (int e = 0; e < 4; ++e) o[md][e] = __builtin_fmaf(o[md][e], scale_o, pv[md][e]);
     }
     // ---- merge the waves ---------------------------------------------------------------------------------------------
     l = column_sum(l);
