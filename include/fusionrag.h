@@ -97,7 +97,8 @@ int64_t fr_workspace_bytes(const fr_ctx* ctx);
  * that everywhere.  Both give the same softmax; the option exists so that tests reach both.
  * FR_OPT_ATTN_SPLIT: AUTO (default) deals the key range of every (row tile, KV head) to two or more workgroups when
  * there are too few of those to fill the chip (few recomputed rows, e.g. question-only prefill or the offline stage of
- * eq. 10); OFF: never; ON: two workgroups each whenever the partial results fit the workspace.  Same results up to the
+ * eq. 10); OFF: never; ON: two workgroups each whenever the partial results fit the workspace.  (Under AUTO of both
+ * options short bf16 prompts run in one launch of another kernel, with a running maximum.)  Same results up to the
  * summation order and, for up to four parts of a prompt of 32 key tiles of 64 and more at group sizes 1, 2, 4, 8 and
  * head_dim 128, the partial sums' storage format (half precision after a per-column power-of-two scale: 11
  * significant bits of a column's largest partial value, finer than the bf16 output); all other parts keep 32 bits.
@@ -110,8 +111,8 @@ int64_t fr_workspace_bytes(const fr_ctx* ctx);
  * workgroups (one per CU), the tiles of that round are split along K over several workgroups each and a second small
  * kernel adds the parts; 0: never.  Same results up to fp32 summation order; for tests and tuning.  (Like every
  * option these two belong to the context they are set on.)
- * FR_OPT_ATTN_KERNEL_TIMER: value n in [0, 256]: the tiled attention launch attaches an event pair to the dispatch of
- * its dominant kernel (the key-tile loop) on the call's stream, start and end of that kernel's execution, and keeps
+ * FR_OPT_ATTN_KERNEL_TIMER: value n in [0, 256]: the bf16 attention launch attaches an event pair to the dispatch of
+ * its dominant kernel (the key-tile loop; a short prompt's only one) on the call's stream, start and end of that kernel's execution, and keeps
  * the last n pairs; 0 (default) switches the timer off.  Read with fr_attn_kernel_times.  For benchmarks: the events
  * see one kernel, not the whole call. */
 typedef enum { FR_OPT_ATTN_SOFTMAX = 1, FR_OPT_ATTN_SPLIT = 2, FR_OPT_DECODE_KERNEL = 3, FR_OPT_GEMM_TILE = 4,

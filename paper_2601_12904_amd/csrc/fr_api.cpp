@@ -511,11 +511,14 @@ static fr_status check_rows(fr_ctx* ctx, int32_t R, int64_t L) {
     return FR_OK;
 }
 
-// Attention over a cache of the query's own (or a gathered copy): tiled kernels, or the one with fp32 products.
+// Attention over a cache of the query's own (or a gathered copy): one launch for short prompts, tiled kernels, or the one with fp32 products.
+// (The options that ask for a treatment of the tiled items ask for those kernels.)
 static hipError_t attn_over_cache(fr_ctx* ctx, const void* q_rows, const int32_t* q_index, int32_t R, const void* k_cache,
                                   const void* v_cache, int64_t L, const void* k_new, const void* v_new, void* out,
                                   float* lse_out, bool writeback, hipStream_t hs) {
     const Shape& s = ctx->shape;
+    if (ctx->attn_softmax_mode == FR_ATTN_SOFTMAX_AUTO && ctx->attn_split_mode == FR_ATTN_SPLIT_AUTO && attn_direct_pays(s, R, L, ctx->ws.n_cu))
+        return launch_attn_direct(s, q_rows, q_index, R, k_cache, v_cache, L, k_new, v_new, out, lse_out, ctx->ws.n_cu, &ctx->attn_timer, writeback, hs);
     if (attn_mfma_supported(s))   // (the tiled path finds the fresh rows of a key tile while it packs the tile)
         return launch_attn_mfma(s, q_rows, q_index, R, k_cache, v_cache, L, k_new, v_new, out, lse_out, ctx->ws,
                                 ctx->attn_softmax_mode, ctx->attn_split_mode, nullptr, &ctx->attn_timer, writeback, hs);

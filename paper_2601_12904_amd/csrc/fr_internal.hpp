@@ -185,6 +185,11 @@ struct SharedStoreArgs {
 hipError_t launch_attn_f32(const Shape& s, const void* q_rows, const int32_t* q_index, int R, const void* k_cache,
                            const void* v_cache, int64_t L, const void* k_new, const void* v_new, int32_t* inv, void* out,
                            float* lse, hipStream_t st);
+// bf16 prompts short enough for one launch without packed images and parts (attn_direct_pays).  No workspace.
+bool attn_direct_pays(const Shape& s, int R, int64_t L, int n_cu);
+hipError_t launch_attn_direct(const Shape& s, const void* q_rows, const int32_t* q_index, int R, const void* k_cache,
+                              const void* v_cache, int64_t L, const void* k_new, const void* v_new, void* out, float* lse,
+                              int n_cu, KernelTimer* timer, bool writeback, hipStream_t st);
 bool attn_mfma_supported(const Shape& s);
 bool attn_mfma_store_supported(const Shape& s);   // also over a chunk store (launch_attn_mfma with `shared`, and the batch)
 hipError_t launch_attn_mfma(const Shape& s, const void* q_rows, const int32_t* q_index, int R,

@@ -1,0 +1,98 @@
+"""Attention of short bf16 prompts in one launch, at the edges of its key blocks, column tiles and dispatch rule, against the
+oracle and against the tiled kernels (FR_ATTN_SPLIT_OFF asks for those): `pytest -m gpu`."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import fusionrag_oracle as orc
+from paper_2601_12904_amd import binding as B
+from paper_2601_12904_amd import synth
+from tests import harness as H
+from tests import test_gpu_unfilled_rows as unfilled
+
+pytestmark = pytest.mark.gpu
+
+# Output elements are rounded to bf16 once (half a unit: 2^-8 of the tensor's largest value at most).  Weights of shapes with an instance
+# of their own are rounded to bf16 too: 2^-9 of each weight, as often up as down, at most 2^-8 of the largest value with signs against us.
+TOL = {True: 2.0 ** -8 + 2.0 ** -14, False: 2.0 ** -7 + 2.0 ** -14}
+
+
+def inputs(Hq, Hkv, d, L, R, seed, at_end=False):
+    rng = np.random.default_rng(seed)
+    qi = np.arange(L - R, L) if at_end else np.sort(np.concatenate([rng.choice(L - 1, R - 1, replace=False), [L - 1]]))
+    bf = lambda *s, scale=1.0: synth.round_to_storage((rng.standard_normal(s) * scale).astype(np.float32), "bf16")  # noqa: E731
+    return (qi, bf(R, Hq, d, scale=d ** 0.5), *(bf(L, Hkv, d, scale=d ** -0.5) for _ in range(2)), *(bf(R, Hkv, d, scale=d ** -0.5) for _ in range(2)))
+
+
+def attend(Hq, Hkv, d, qi, q, kc, vc, kn, vn, split, writeback=False):
+    L, R = len(kc), len(qi)
+    c = B.Context(Hq, Hkv, d, B.FR_BF16, 500000.0, max_tokens=L, max_chunks=1, max_question_tokens=1)
+    c.fr_set_option(B.FR_OPT_ATTN_SPLIT, split)
+    out = torch.zeros((R, Hq, d), dtype=torch.bfloat16, device="cuda")
+    lse = torch.zeros((R, Hq), dtype=torch.float32, device="cuda")
+    k, v = H.dev(kc, "bf16"), H.dev(vc, "bf16")
+    call = c.fr_sparse_prefill_attn_writeback if writeback else c.fr_sparse_prefill_attn
+    call(H.dev(q, "bf16"), torch.from_numpy(qi.astype(np.int32)).cuda(), R, k, v, L, *(None if x is None else H.dev(x, "bf16") for x in (kn, vn)), out, lse)
+    torch.cuda.synchronize()
+    c.close()
+    return H.host(out), lse.cpu().numpy(), H.host(k), H.host(v)
+
+
+# (query heads, KV heads, head_dim): 32-column tiles of 32, 8, 4, 4 4/7 and half a row; head_dim 64; one KV head and a number that is no power of two
+SHAPES = [(1, 1, 128), (12, 3, 128), (16, 2, 128), (7, 1, 128), (64, 1, 128), (3, 3, 64), (14, 2, 64)]
+# positions: one, the last of a key block, one behind, one behind a round of eight blocks; rows: one, tiles with and without a rest
+SIZES = [(1, 1), (31, 5), (32, 32), (33, 8), (64, 9), (257, 40), (530, 100)]
+
+
+@pytest.mark.parametrize("L,R", SIZES)
+@pytest.mark.parametrize("Hq,Hkv,d", SHAPES)
+def test_against_the_oracle(Hq, Hkv, d, L, R):
+    qi, q, kc, vc, kn, vn = inputs(Hq, Hkv, d, L, R, seed=L + Hq)
+    want, want_lse = orc.sparse_prefill_attn(q, qi, kc, vc, kn, vn)
+    k_eff, v_eff = orc.kv_scatter(qi, kn, vn, kc, vc)
+    tol = TOL[d == 64 or Hq // Hkv not in (1, 2, 4, 8)]
+    for new, kv, writeback in (((kn, vn), (kc, vc), False), ((kn, vn), (kc, vc), True), ((None, None), (k_eff, v_eff), False)):
+        got, lse, k, v = attend(Hq, Hkv, d, qi, q, *kv, *new, B.FR_ATTN_SPLIT_AUTO, writeback)
+        assert H.max_rel_err(got, want) <= tol
+        assert np.max(np.abs(lse - want_lse)) <= 1e-4
+        assert np.array_equal(k, k_eff if writeback else kv[0]) and np.array_equal(v, v_eff if writeback else kv[1])
+
+
+# Either side of the rule's lines for 256 compute units: 32-column tiles (R x 32 heads / 32, or 16 heads at head_dim 64) and positions; and of the
+# line between 16 and 32 columns per workgroup.
+@pytest.mark.parametrize("at_end", [False, True])
+@pytest.mark.parametrize("Hq,Hkv,d,L,R", [(32, 8, 128, 700, 128), (32, 8, 128, 700, 129), (32, 8, 128, 1024, 512), (32, 8, 128, 1024, 513), (32, 8, 128, 1025, 384),
+                                          (32, 8, 128, 1792, 384), (32, 8, 128, 1793, 256), (32, 8, 128, 1793, 257), (28, 4, 128, 6144, 288), (32, 8, 128, 6145, 20),
+                                          (16, 8, 64, 4096, 768), (16, 8, 64, 4097, 512)])
+def test_both_sides_of_the_rule(Hq, Hkv, d, L, R, at_end):
+    args = inputs(Hq, Hkv, d, L, R, seed=L + R, at_end=at_end)
+    got, lse, _, _ = attend(Hq, Hkv, d, *args, B.FR_ATTN_SPLIT_AUTO)
+    tiled, tiled_lse, _, _ = attend(Hq, Hkv, d, *args, B.FR_ATTN_SPLIT_OFF)
+    assert H.max_rel_err(got, tiled) <= 2 * TOL[d == 64 or Hq // Hkv == 7]      # both are off float64
+    assert np.max(np.abs(lse - tiled_lse)) <= 2e-4
+
+
+AUTO = (B.FR_OPT_ATTN_SPLIT, B.FR_ATTN_SPLIT_AUTO)
+
+
+@pytest.mark.parametrize("with_new", [True, False])
+@pytest.mark.parametrize("case_args", unfilled.TILED)
+def test_rows_that_hold_nothing(case_args, with_new):
+    unfilled.test_rows_that_hold_nothing(case_args, AUTO, with_new)
+
+
+@pytest.mark.parametrize("case_args", unfilled.TILED + unfilled.SPARSE)
+def test_values_that_are_not_finite_reach_later_rows_only(case_args):
+    unfilled.test_values_that_are_not_finite_reach_later_rows_only(case_args, AUTO)
+
+
+def test_running_maximum():
+    """Logits that rise by 2^20 along the prompt: every block raises the maximum of all columns."""
+    qi, q, kc, vc, kn, vn = inputs(8, 2, 128, 600, 90, seed=5)
+    ramp = np.linspace(0.0, 16.0, 600, dtype=np.float32)
+    q[:, :, 0], kc[:, :, 0], kn[:, :, 0] = 10.0, ramp[:, None], ramp[qi][:, None]
+    q, kc, kn = (synth.round_to_storage(x, "bf16") for x in (q, kc, kn))
+    got, lse, _, _ = attend(8, 2, 128, qi, q, kc, vc, kn, vn, B.FR_ATTN_SPLIT_AUTO)
+    want, want_lse = orc.sparse_prefill_attn(q, qi, kc, vc, kn, vn)
+    assert H.max_rel_err(got, want) <= TOL[False]
+    assert np.max(np.abs(lse - want_lse)) <= 1e-4
