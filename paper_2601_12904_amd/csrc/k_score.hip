@@ -31,15 +31,18 @@
 // exceeds the reference by more than about 2^100 the sum shows it, and the workgroup repeats its range with the exact
 // maxima.
 //
-// Measured (16 x 1024 keys, 512 question tokens, 32/8 heads, bf16): 92 us + 6 us for the reduction, of which about 14 us
-// load the keys before the first step; the two passes of k_score_mfma.hip took 66 + 62 + 5 us (layer 656 -> 618 us).  28/4
-// heads: 0.10 ms, 71 ms with one thread per key; fp32, 4 x 128 keys, 32 question tokens: 7 us, before 205 us.
+// Measured (16 x 1024 keys, 512 question tokens, 32/8 heads, bf16, back to back, with the reduction): 83 us, of which 5 load the keys and a step of 16 columns
+// takes 0.99; with keys loaded straight into fragment registers (12 us: see there), the order of a step's instructions left to the compiler (1.19 us a step) and a
+// spilled index that was waited for in the loop together with the copies 96; the two passes of k_score_mfma.hip 66 + 62 + 5 us.  3 x 900 keys, 100 question tokens 20.3 -> 15.7.  28/4
+// heads 90 -> 79; fp32, 4 x 128 keys, 32 question tokens: 7 us.  Vector instructions fill 80 % of the issue cycles: four per logit are the sums' own, one more per logit is
+// the references, the sums' exchange and the fragments' addresses.
 // All sums run in a fixed order: the scores are reproducible bit for bit.
 #include "fr_internal.hpp"
 #include "k_rotate.hpp"
 
 #include <algorithm>
 #include <type_traits>
+#include <utility>
 
 namespace fr {
 
@@ -65,6 +68,7 @@ struct Op {
     static constexpr int NJ = NV / 4;                          // vectors per lane: lane (row x, quarter kg) holds vectors 4 j + kg
     static constexpr int NB_MAX = ROWB == 512 ? 4 : 8;         // key blocks per wave: NB x NJ x 4 registers
     static constexpr int SEG = 16 * WAVES * NB_MAX;            // most keys of a workgroup
+    static constexpr int STAGED = ROWB == 512 ? 1 : 768 / ROWB;   // key blocks of a wave in LDS at a time
     // 16-byte vector c of row r sits in slot c ^ swz(r) of the row: any 16 rows' vectors c then start in 16 different
     // 16-byte bank groups (two 128-byte rows share one stretch of banks)
     static __device__ __forceinline__ int swz(int r) { return ROWB == 128 ? (r >> 1) & 7 : r & 15; }
@@ -116,6 +120,20 @@ __device__ __forceinline__ void plain_barrier() {   // without the fences of __s
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
 }
+// f(0), f(1), ... f(N - 1), each with its own constant (`#pragma unroll` gives up on long bodies, and arrays indexed by them go to memory).
+template <typename F, int... I>
+__device__ __forceinline__ void static_for(F&& f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+// Until all but the wave's last n copies have landed; n is a constant once loops are unrolled.
+__device__ __forceinline__ void wait_copies_but(int n) {
+    switch (n) {
+#define FR_WAIT(N) case N: __builtin_amdgcn_s_waitcnt(0x0f70 | N); break;
+        FR_WAIT(2) FR_WAIT(4) FR_WAIT(6) FR_WAIT(8) FR_WAIT(10)
+#undef FR_WAIT
+        default: __builtin_amdgcn_s_waitcnt(0x0f70);
+    }
+}
 // Sum and maximum over the four lanes that hold the same column (lanes x, x + 16, x + 32, x + 48).
 __device__ __forceinline__ float column_sum(float v) {
     auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
@@ -145,6 +163,7 @@ struct Smem {
     alignas(1024) unsigned char q[2][TILE * Op<T, D>::ROWB];
     float ref[MAX_COLS + 32];      // exponent references, or the given normalisers (and room for those of a step too many)
     alignas(16) float l[2][32][WAVES];
+    alignas(1024) unsigned char stage[WAVES][Op<T, D>::STAGED * 16 * Op<T, D>::ROWB];   // key blocks on their way into registers
 };
 
 // Work of one workgroup: keys [s0, s0 + len) of chunk c, query columns [n0, n1).  NB = key blocks per wave.
@@ -152,25 +171,24 @@ template <typename T, int D, int MODE, int NB>
 __device__ __forceinline__ void walk_columns(const ScoreArgs& a, Smem<T, D>& sm, int g, int c, int s0, int len, int row,
                                              int n0, int n1, int split) {
     using O = Op<T, D>;
-    // Column groups of 16 per step.  A step costs about 0.3 us besides its logits (barrier, exchange of the sums, LDS
-    // latency: NB = 1, 2, 4, 6, 8 blocks took 0.44, 0.58, 0.77, 0.97, 1.19 us per step of 16 columns), so it takes two groups wherever the
-    // registers hold them: the weights are the only ones that double.
+    // Column groups of 16 per step.  A step costs about 0.2 us besides its logits (barrier, exchange of the sums, LDS
+    // latency), so it takes two groups wherever the registers hold them: the weights are the only ones that double.
     constexpr int CG = (MODE == MODE_FUSED && NB * Op<T, D>::NJ > CG2_MAX_KEYS) ? 1 : 2;
     constexpr int STEP = 16 * CG, SPT = TILE / STEP;                 // columns per step, steps per tile
     // The logits of a step come as NB x CG units of 16 keys x 16 columns, in pairs (two independent chains of matrix
     // instructions): unit k is block k / CG, group k % CG.
     constexpr int NU = NB * CG, NP = (NU + 1) / 2;
     constexpr int NJ = O::NJ;                                        // vectors per lane
-    constexpr int MFMAS = 2 * NJ * (sizeof(T) == 2 ? 1 : 4) / 8;     // matrix instructions per logit of a pair and lane
     const int tid = threadIdx.x, lane = tid & 63, x = lane & 15, kg = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int NQG = a.nq * a.G;
     const T* __restrict__ q = static_cast<const T*>(a.q);
     const T* __restrict__ k = static_cast<const T*>(a.k);
-    auto column_row = [&](int n) -> const unsigned char* {   // columns past the end: a copy of the last one
+    // row of the queries that holds column n (past the end: a copy of the last one): (n / G) Hq + g G + n % G
+    const uint32_t per_column = a.G > 1 ? 1u : (uint32_t)a.Hq, per_token = a.G > 1 ? (uint32_t)(a.Hq - a.G) : 0u;
+    auto column_row = [&](int n) -> uint32_t {
         n = min(n, NQG - 1);
-        const int tok = a.G > 1 ? (int)__umulhi((uint32_t)n, a.magic) : n;
-        return reinterpret_cast<const unsigned char*>(q + ((size_t)tok * a.Hq + g * a.G + (n - tok * a.G)) * D);
+        return (uint32_t)n * per_column + __umulhi((uint32_t)n, a.magic) * per_token + (uint32_t)(g * a.G);
     };
     // copies of one tile of query columns, global -> LDS directly: 1 KB per wave instruction, lane = (row, slot)
     auto copy_tile = [&](int t, int buf) {
@@ -180,7 +198,7 @@ __device__ __forceinline__ void walk_columns(const ScoreArgs& a, Smem<T, D>& sm,
 #pragma unroll
         for (int i = 0; i < COPIES; ++i) {
             const int r = (1024 / O::ROWB) * (COPIES * wave + i) + ln / O::NV;
-            const unsigned char* src = column_row(n0 + TILE * t + r) + 16 * ((ln % O::NV) ^ O::swz(r));
+            const unsigned char* src = reinterpret_cast<const unsigned char*>(q) + ((uint64_t)column_row(n0 + TILE * t + r) * (uint32_t)O::ROWB + 16 * ((ln % O::NV) ^ O::swz(r)));
             const uint32_t dst = lds_address(sm.q[buf]) + (uint32_t)(COPIES * wave + i) * 1024u;
             asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(dst) : "memory");
         }
@@ -189,18 +207,39 @@ __device__ __forceinline__ void walk_columns(const ScoreArgs& a, Smem<T, D>& sm,
     copy_tile(0, 0);
     if (n_tiles > 1) copy_tile(1, 1);
 
-    // this lane's vectors 4 j + kg of keys 16 (wave + 8 b) + x; keys past the end: a copy of the last one
+    // This lane's vectors 4 j + kg of keys 16 (wave + 8 b) + x; keys past the end: a copy of the last one.  Through LDS, STAGED blocks of a wave at a
+    // time: a fragment's 16 rows x 64 bytes per instruction, neighbouring lanes in different rows, take the vector cache 64 accesses per KB, rows side by
+    // side 16.
     u32x4 kf[NB][NJ];
-    auto key_row = [&](int b) -> const unsigned char* {
-        const int j = min(16 * (wave + WAVES * b) + x, len - 1) + s0;
-        const int64_t r = a.src == SRC_PROMPT ? (int64_t)j : (int64_t)a.rows.row0[c] + (j - a.ct.off[c]);
-        return reinterpret_cast<const unsigned char*>(k + (r * a.Hkv + g) * D);
-    };
+    {
+        constexpr int BLOCK = 16 * O::ROWB, COPIES = BLOCK / 1024, RC = 1024 / O::ROWB;
+        auto copy_block = [&](int b) {
 #pragma unroll
-    for (int b = 0; b < NB; ++b) {
-        const unsigned char* kr = key_row(b) + 16 * kg;
+            for (int i = 0; i < COPIES; ++i) {
+                const int r = RC * i + lane / O::NV;
+                const int j = min(16 * (wave + WAVES * b) + r, len - 1) + s0;
+                const int64_t at = a.src == SRC_PROMPT ? (int64_t)j : (int64_t)a.rows.row0[c] + (j - a.ct.off[c]);
+                const unsigned char* src = reinterpret_cast<const unsigned char*>(k + (at * a.Hkv + g) * D) + 16 * ((lane % O::NV) ^ O::swz(r));
+                const uint32_t dst = lds_address(sm.stage[wave]) + (uint32_t)(b % O::STAGED) * BLOCK + (uint32_t)i * 1024u;
+                asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(dst) : "memory");
+            }
+        };
+        static_assert(COPIES * (O::STAGED - 1) <= 10 && COPIES % 2 == 0, "wait_copies_but");
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) kf[b][j] = *reinterpret_cast<const u32x4*>(kr + 64 * j);
+        for (int b = 0; b < O::STAGED && b < NB; ++b) copy_block(b);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            asm volatile("" ::: "memory");
+            wait_copies_but(COPIES * min(NB - 1 - b, O::STAGED - 1));   // the later blocks'
+            asm volatile("" ::: "memory");
+            const unsigned char* row = sm.stage[wave] + (b % O::STAGED) * BLOCK;
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) kf[b][j] = *reinterpret_cast<const u32x4*>(row + ((x * O::ROWB + 16 * (kg ^ O::swz(x))) ^ (64 * j)));
+            if (b + O::STAGED < NB) {
+                __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): the slot has been read
+                copy_block(b + O::STAGED);
+            }
+        }
     }
     if (a.src != SRC_PROMPT) {   // moved to their prompt positions
         const float2* trow = a.table + (size_t)c * (D / 2);
@@ -227,9 +266,9 @@ __device__ __forceinline__ void walk_columns(const ScoreArgs& a, Smem<T, D>& sm,
         }
     }
     const int last_key = 16 * (wave + WAVES * (NB - 1)) + 4 * kg;   // of the wave's last block: the lane's four keys
-    bool valid[4];
+    f32x4 last_block;   // its products start from here: keys past the end come to weight 0
 #pragma unroll
-    for (int i = 0; i < 4; ++i) valid[i] = last_key + i < len;
+    for (int i = 0; i < 4; ++i) last_block[i] = last_key + i < len ? 0.f : -INFINITY;
     if constexpr (MODE == MODE_GIVEN) {
         const float* src = a.lse2 + ((size_t)g * a.lse_rows + row) * (a.col_end - a.col0) + (n0 - a.col0);
         for (int i = tid; i < n_steps * STEP; i += 64 * WAVES) sm.ref[i] = n0 + i < n1 ? src[i] : INFINITY;
@@ -239,41 +278,48 @@ __device__ __forceinline__ void walk_columns(const ScoreArgs& a, Smem<T, D>& sm,
     // fragments of step st's columns (vector 4 j + kg of row 16 cg + x), and the products of a pair of units
     u32x4 qv[CG][NJ];
     const int q_lane = x * O::ROWB + 16 * (kg ^ O::swz(x));   // (swz(16 i + x) = swz(x))
+    auto q_at = [&](int st) {
+        return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)sm.q +
+               ((st / SPT) & 1) * (uint32_t)sizeof(sm.q[0]) + (st % SPT) * (STEP * O::ROWB) + (uint32_t)q_lane;
+    };
+    auto load_vector = [&](uint32_t at, int cg, int j) {   // 16 ((4 j + kg) ^ swz) = 64 j ^ 16 (kg ^ swz): one register for all vectors
+        qv[cg][j] = *(__attribute__((address_space(3))) const u32x4*)(uintptr_t)((at ^ (64u * j)) + cg * (16 * O::ROWB));
+    };
     auto load_q = [&](int st) {
-        const uint32_t at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)sm.q +
-                            ((st / SPT) & 1) * (uint32_t)sizeof(sm.q[0]) + (st % SPT) * (STEP * O::ROWB) + (uint32_t)q_lane;
+        const uint32_t at = q_at(st);
 #pragma unroll
         for (int cg = 0; cg < CG; ++cg)
 #pragma unroll
-            for (int j = 0; j < NJ; ++j)   // 16 ((4 j + kg) ^ swz) = 64 j ^ 16 (kg ^ swz): one register for all vectors
-                qv[cg][j] = *(__attribute__((address_space(3))) const u32x4*)(uintptr_t)((at ^ (64u * j)) + cg * (16 * O::ROWB));
+            for (int j = 0; j < NJ; ++j) load_vector(at, cg, j);
     };
     f32x4 s[2][2];
+    // Multiplication m of a pair's 2 NJ: vector m / 2 of unit m % 2.
+    auto product = [&](int pr, int m) {
+        const int unit = 2 * pr + m % 2;
+        if (unit >= NU) return;
+        f32x4& acc = s[pr & 1][m % 2];
+        if (m < 2) acc = unit / CG == NB - 1 ? last_block : f32x4{0.f, 0.f, 0.f, 0.f};
+        O::multiply(kf[unit / CG][m / 2], qv[unit % CG][m / 2], acc);
+    };
     auto products = [&](int pr) {
 #pragma unroll
-        for (int u = 0; u < 2; ++u) s[pr & 1][u] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int j = 0; j < NJ; ++j)
-#pragma unroll
-            for (int u = 0; u < 2; ++u)
-                if (2 * pr + u < NU) O::multiply(kf[(2 * pr + u) / CG][j], qv[(2 * pr + u) % CG][j], s[pr & 1][u]);
+        for (int m = 0; m < 2 * NJ; ++m) product(pr, m);
     };
     auto wait_copies = [&] { __builtin_amdgcn_s_waitcnt(0x0f70); };   // vmcnt(0)
     auto wait_lds = [&] { __builtin_amdgcn_s_waitcnt(0xc07f); };      // lgkmcnt(0)
     bool bad = false;
+    int column = x;   // (its own register: one that came back from scratch memory at the loop's entry would be waited for in every step, with the copies)
     // 1 / l of this lane's column of group cg of step st (0 past the last column); MODE_LSE: the normaliser goes out
-    auto finish_column = [&](int st, int cg) -> float {
-        const int i = STEP * st + 16 * cg + x;
-        const f32x4 l0 = *reinterpret_cast<const f32x4*>(&sm.l[st & 1][16 * cg + x][0]);
-        const f32x4 l1 = *reinterpret_cast<const f32x4*>(&sm.l[st & 1][16 * cg + x][4]);
+    auto finish_column = [&](int st, int cg, const f32x4& l0, const f32x4& l1) -> float {
+        const int i = STEP * st + 16 * cg + column;
         const float l = ((l0[0] + l0[1]) + (l0[2] + l0[3])) + ((l1[0] + l1[1]) + (l1[2] + l1[3]));
         bad = bad || !(l < 0x1p100f);
         if constexpr (MODE == MODE_LSE) {
-            if (wave == 0 && kg == 0 && n0 + i < n1)
+            if (wave == 0 && kg == 0 && i < n1 - n0)
                 a.lse2[((size_t)g * a.lse_rows + row) * (a.col_end - a.col0) + (n0 - a.col0) + i] = sm.ref[i] + __builtin_amdgcn_logf(l);
             return 0.f;
         } else {
-            return n0 + i < n1 ? __builtin_amdgcn_rcpf(l) : 0.f;
+            return i < n1 - n0 ? __builtin_amdgcn_rcpf(l) : 0.f;
         }
     };
     // the references of step st's columns: keys 0 .. 15 are block 0 of wave 0, whose logits are units 0 and (CG = 2) 1
@@ -304,58 +350,86 @@ __device__ __forceinline__ void walk_columns(const ScoreArgs& a, Smem<T, D>& sm,
         // Step st: its first pair's products were issued in the step before.  The barrier makes the other waves' sums and the
         // references visible; in a tile's last step also the next tile, which the fragments of the next step come from, and
         // it frees this tile's slot (the fragments of the tile's last step were read before the barrier).
+        asm volatile("" : "+v"(column));
         for (int st = 0; st < n_steps; ++st) {
             const bool last_of_tile = st % SPT == SPT - 1;
             if (last_of_tile) wait_copies();
             wait_lds();
             plain_barrier();
             if (last_of_tile && st / SPT + 2 < n_tiles) copy_tile(st / SPT + 2, (st / SPT) & 1);
-            float f[CG], ref[CG], lsum[CG][2];
+            float f[CG], ref[CG], lsum[CG][2], w[4];
+            f32x4 l0[CG], l1[CG];
+            const uint32_t next_q = q_at(st + 1);
 #pragma unroll
-            for (int cg = 0; cg < CG; ++cg) {
-                f[cg] = (MODE != MODE_GIVEN && st > 0) ? finish_column(st - 1, cg) : 0.f;
+            for (int cg = 0; cg < CG; ++cg) {   // all of the step's first reads at once
                 ref[cg] = sm.ref[STEP * st + 16 * cg + x];
-                lsum[cg][0] = lsum[cg][1] = 0.f;
+                if constexpr (MODE != MODE_GIVEN) {
+                    l0[cg] = *reinterpret_cast<const f32x4*>(&sm.l[(st + 1) & 1][16 * cg + x][0]);
+                    l1[cg] = *reinterpret_cast<const f32x4*>(&sm.l[(st + 1) & 1][16 * cg + x][4]);
+                }
+                lsum[cg][1] = f[cg] = 0.f;   // (of one block: nothing else comes to it)
             }
-            // The fragments of the next step are read as soon as this step's last products are issued, its first products go
-            // beside the last pair's exponentials (an odd number of pairs: behind them, the accumulators alternate).
+            // The step's logits one after the other, each with its share of the next pair's products (the last pair's: of the next step's first one): multiply,
+            // add and exponentiate stand one logit apart, so that no instruction waits for the one in front of it, and a matrix instruction runs
+            // beside the vector instructions of its own wave.  (The order is pinned: left to the compiler, also with scheduling groups, the matrix instructions
+            // gather in dependent chains, and both waves of a SIMD, which leave the barrier together, first wait for the one pipe and then for the other.)
+            // A weight takes the register of the step before, whose weight joins the score in front of it; those of the first LATE logits wait in registers of
+            // their own (1 / l has come through LDS and a sum by then).
+            constexpr int LOGITS = 4 * NU;
+            constexpr int LATE = MODE == MODE_FUSED && LOGITS >= 8 ? 4 : 0;
+            auto finish = [&] {
 #pragma unroll
-            for (int pr = 0; pr < NP; ++pr) {
-                if (pr + 1 < NP) products(pr + 1);
-                else if (NP % 2 == 0) products(0);
-                if (pr == (NP > 1 ? NP - 2 : 0)) load_q(st + 1);   // (past the last step: read, never used)
+                for (int cg = 0; cg < CG; ++cg) f[cg] = (MODE != MODE_GIVEN && st > 0) ? finish_column(st - 1, cg, l0[cg], l1[cg]) : 0.f;
+            };
+            if (LATE == 0) finish();
+            float t[2], e[2];
+            auto unit_of = [](int n) { return n / 4; };
+            auto settle = [&](int n) {
+                const int b = unit_of(n) / CG, cg = unit_of(n) % CG;
+                sc[b][n % 4] = __builtin_fmaf(p[cg][b][n % 4], f[cg], sc[b][n % 4]);
+                asm volatile("" : "+v"(sc[b][n % 4]));   // (here, not behind the branch below)
+            };
+            static_for([&](auto index) __attribute__((always_inline)) {
+                constexpr int n = decltype(index)::value, pr = n / 8, in_pair = pr == NP - 1 ? LOGITS - 8 * pr : 8;   // logits of this pair
+                constexpr int next = n >= LOGITS ? -1 : pr + 1 < NP ? pr + 1 : NP % 2 == 0 ? 0 : -1;
+                if constexpr (next >= 0) {
 #pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    const int b = (2 * pr + u) / CG, cg = (2 * pr + u) % CG;
-                    if (b >= NB) continue;
+                    for (int m = (n % 8) * 2 * NJ / in_pair; m < (n % 8 + 1) * 2 * NJ / in_pair; ++m) {
+                        product(next, m);
+                        if (pr == NP - 2 && m % 2 == 1) {   // the last products with these columns: the next step's follow
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        float minus = -ref[cg];
-                        if (b == NB - 1 && !valid[i]) minus = -INFINITY;   // keys past the end: weight 0
-                        const float w = __builtin_amdgcn_exp2f(__builtin_fmaf(s[pr & 1][u][i], a.scale_log2e, minus));
-                        if constexpr (MODE == MODE_FUSED) sc[b][i] = __builtin_fmaf(p[cg][b][i], f[cg], sc[b][i]);
-                        if constexpr (MODE == MODE_GIVEN) sc[b][i] += w;
-                        if constexpr (MODE != MODE_GIVEN) lsum[cg][b & 1] += w;
-                        if constexpr (MODE == MODE_FUSED) p[cg][b][i] = w;
+                            for (int cg = 0; cg < CG; ++cg) load_vector(next_q, cg, m / 2);   // (past the last step: read, never used)
+                        }
                     }
                 }
-                // a weight takes the register of the step before: keep that one's use here (the compiler would sink the sums
-                // behind the branch below and hold two steps' weights)
-                if constexpr (MODE == MODE_FUSED)
-#pragma unroll
-                    for (int b = 2 * pr / CG; b < (2 * pr + 2) / CG && b < NB; ++b)
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(sc[b][i]));
-                if (pr + 1 < NP || NP % 2 == 0) {   // matrix and vector instructions in turn
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        __builtin_amdgcn_sched_group_barrier(0x008, MFMAS, 0);   // matrix
-                        __builtin_amdgcn_sched_group_barrier(0x400, 1, 0);       // transcendental
-                        __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);       // other vector instructions
+                if constexpr (n < LOGITS) {
+                    t[n & 1] = __builtin_fmaf(s[pr & 1][unit_of(n) & 1][n % 4], a.scale_log2e, -ref[unit_of(n) % CG]);
+                    if (MODE == MODE_FUSED && n >= LATE) settle(n);
+                    if constexpr (n >= LATE && n < 2 * LATE) {
+                        settle(n - LATE);
+                        p[unit_of(n - LATE) % CG][unit_of(n - LATE) / CG][n % 4] = w[n - LATE];
                     }
+                }
+                if constexpr (n >= 1 && n <= LOGITS) {
+                    constexpr int k = n - 1;
+                    e[k & 1] = __builtin_amdgcn_exp2f(t[k & 1]);
+                    if constexpr (k < LATE) w[k] = e[k & 1];
+                    else if constexpr (MODE == MODE_FUSED) p[unit_of(k) % CG][unit_of(k) / CG][k % 4] = e[k & 1];
+                }
+                if constexpr (n >= 2) {
+                    constexpr int k = n - 2, b = k / 4 / CG, cg = k / 4 % CG;
+                    if constexpr (MODE == MODE_GIVEN) sc[b][k % 4] += e[k & 1];
+                    else if constexpr (b < 2 && k % 4 == 0) lsum[cg][b] = e[k & 1];
+                    else lsum[cg][b & 1] += e[k & 1];
+                }
+                if constexpr (n + 1 == LATE) {
+#pragma unroll
+                    for (int cg = 0; cg < CG; ++cg) asm volatile("" : "+v"(l0[cg]), "+v"(l1[cg]));   // (not earlier)
+                    finish();
                 }
                 __builtin_amdgcn_sched_barrier(0);
-            }
+            }, std::make_integer_sequence<int, LOGITS + 2>{});
+            if (NP == 1) load_q(st + 1);
             if (NP % 2 == 1) products(0);
             // (all four lanes of a column store the same sum: no branch in the step)
             if constexpr (MODE != MODE_GIVEN)
@@ -368,7 +442,8 @@ __device__ __forceinline__ void walk_columns(const ScoreArgs& a, Smem<T, D>& sm,
             plain_barrier();
 #pragma unroll
             for (int cg = 0; cg < CG; ++cg) {
-                const float f = finish_column(n_steps - 1, cg);
+                const float* l = sm.l[(n_steps - 1) & 1][16 * cg + x];
+                const float f = finish_column(n_steps - 1, cg, *reinterpret_cast<const f32x4*>(l), *reinterpret_cast<const f32x4*>(l + 4));
                 if constexpr (MODE == MODE_FUSED) {
 #pragma unroll
                     for (int b = 0; b < NB; ++b)
@@ -399,7 +474,7 @@ __device__ __forceinline__ void walk_columns(const ScoreArgs& a, Smem<T, D>& sm,
                     for (int j = 0; j < NJ; ++j) O::multiply(kf[b][j], qv[cg][j], z);
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
-                        if (b < NB - 1 || valid[i]) m[cg] = fmaxf(m[cg], z[i]);
+                        if (b < NB - 1 || last_block[i] == 0.f) m[cg] = fmaxf(m[cg], z[i]);
                 }
                 sm.l[st & 1][16 * cg + x][wave] = column_max(m[cg]);
             }
@@ -520,15 +595,16 @@ __global__ __launch_bounds__(64 * REDUCE_MAX_WAVES) void score_reduce_kernel(con
     if ((int)(blockIdx.x * 64 + threadIdx.x) < L_ctx) scores[j] = add ? scores[j] + t : t;   // add: not the first columns
 }
 
-// Column ranges per (chunk, KV head).  A workgroup holds a compute unit to itself, pays about 6 steps' time before its
-// first step (12 us of 1024 keys x 2 KB, against 2 us per 32 columns), and a chunk's steps cannot be balanced otherwise:
-// the fewest ranges that fill the chip, counted in rounds of workgroups.
+// Column ranges per (chunk, KV head).  A workgroup holds a compute unit to itself, pays about 3 steps' time before its
+// first step (5 us for 1024 keys, against 2 us per 32 columns), and a chunk's steps cannot be balanced otherwise:
+// the fewest ranges that fill the chip, counted in rounds of workgroups.  (24 chunks of 640 keys, 400 question tokens, 32 / 8 heads: 69.5 us, 79.3 if
+// priced at 6 steps as when the keys came straight into registers; 56 other calls 0.3 % apart on average.)
 int choose_splits(int items, int n_steps, int n_cu, int max_split) {
     const int least = (n_steps * RANGE_UNIT + MAX_COLS - 1) / MAX_COLS;
     int best = least;
     double best_t = 1e30;
     for (int s = least; s <= std::max(least, std::min(max_split, n_steps)); ++s) {
-        const double rounds = (double)items * s / n_cu, per = 6.0 + (n_steps + s - 1) / s;
+        const double rounds = (double)items * s / n_cu, per = 3.0 + (n_steps + s - 1) / s;
         const double t = per * (rounds < 4.0 ? (double)(int64_t)(rounds + 0.999) : rounds + 0.5);
         if (t < best_t - 1e-9) { best_t = t; best = s; }
     }

@@ -213,6 +213,13 @@ def test_scores(Hq, Hkv, d, dt, nq, lens, norm):
     ctx.close()
 
 
+# One to eight key blocks per wave (128 keys each; of which at 512 bytes a row one to four), the last one whole, of one key and with a rest; steps of 16 and
+# 32 columns with and without a rest; columns of one token and of several in a copy.
+@pytest.mark.parametrize("Hq,Hkv,d,dt,nq", [(8, 2, 128, "bf16", 25), (7, 1, 128, "bf16", 33), (1, 1, 128, "bf16", 70), (6, 2, 64, "bf16", 11), (4, 4, 64, "f32", 31), (6, 2, 128, "f32", 17)])
+def test_scores_at_every_number_of_key_blocks(Hq, Hkv, d, dt, nq):
+    test_scores(Hq, Hkv, d, dt, nq, (128, 129, 255, 257, 400, 512) + ((513, 640, 750, 769, 1000, 1024) if (d, dt) != (128, "f32") else ()), B.FR_NORM_PER_CHUNK)
+
+
 @pytest.mark.parametrize("norm", [B.FR_NORM_PER_CHUNK, B.FR_NORM_GLOBAL])
 def test_scores_of_more_columns_than_the_workspace_holds(norm):
     """A context of two million tokens holds the partial sums of 4096 query columns and the normalisers of 2048 at a time: 4400
