@@ -4,7 +4,7 @@
 // The score of context token j is the column sum, over all question rows and query heads, of the softmax-normalised
 // attention weights.  A weight needs its row's normaliser, i.e. the logits of every key in the softmax's scope, before it
 // can be added up.  Where the scope is a chunk of at most SEG keys (the usual case: chunks of 1024 tokens, softmax per
-// chunk) one workgroup holds the whole chunk: its keys sit in the registers of the eight waves and the query columns
+// chunk) one workgroup holds the whole chunk: its keys sit in the registers of its eight (four) waves and the query columns
 // stream past them, so every logit and every exponential is formed once.  Otherwise the chunk (or, for one softmax over
 // the whole context, the prompt) is cut into segments of at most SEG keys and walked twice.
 //
@@ -55,20 +55,20 @@ typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 enum { MODE_FUSED = 0, MODE_LSE = 1, MODE_GIVEN = 2 };
 enum { SRC_PROMPT = 0, SRC_STORE_INTERLEAVED = 1, SRC_STORE_HALF = 2 };
 
-constexpr int WAVES = 8;
+constexpr int MOST_WAVES = 8;     // of a workgroup; chunks of up to half as many keys have four
 constexpr int TILE = 64;          // query columns per LDS tile
 constexpr int RANGE_UNIT = 32;    // column ranges are multiples of the longest step
 constexpr int MAX_COLS = 2048;    // query columns per workgroup (their references sit in LDS)
 constexpr int CG2_MAX_KEYS = 20;  // most 4-register key vectors per lane with two column groups per step in MODE_FUSED
 
-template <typename T, int D>
+template <typename T, int D, int WAVES = MOST_WAVES>
 struct Op {
     static constexpr int ROWB = D * (int)sizeof(T);            // bytes of a head row: 128, 256 or 512
     static constexpr int NV = ROWB / 16;                       // its 16-byte vectors
     static constexpr int NJ = NV / 4;                          // vectors per lane: lane (row x, quarter kg) holds vectors 4 j + kg
     static constexpr int NB_MAX = ROWB == 512 ? 4 : 8;         // key blocks per wave: NB x NJ x 4 registers
     static constexpr int SEG = 16 * WAVES * NB_MAX;            // most keys of a workgroup
-    static constexpr int STAGED = ROWB == 512 ? 1 : 768 / ROWB;   // key blocks of a wave in LDS at a time
+    static constexpr int STAGED = ROWB == 512 ? 1 : 512 / ROWB;   // key blocks of a wave in LDS at a time (two workgroups of four waves share the LDS)
     // 16-byte vector c of row r sits in slot c ^ swz(r) of the row: any 16 rows' vectors c then start in 16 different
     // 16-byte bank groups (two 128-byte rows share one stretch of banks)
     static __device__ __forceinline__ int swz(int r) { return ROWB == 128 ? (r >> 1) & 7 : r & 15; }
@@ -158,7 +158,7 @@ __device__ __forceinline__ float row_sum(float v) {   // over the 16 lanes of a 
     return add_rotated<0x121>(v);
 }
 
-template <typename T, int D>
+template <typename T, int D, int WAVES>
 struct Smem {
     alignas(1024) unsigned char q[2][TILE * Op<T, D>::ROWB];
     float ref[MAX_COLS + 32];      // exponent references, or the given normalisers (and room for those of a step too many)
@@ -167,10 +167,10 @@ struct Smem {
 };
 
 // Work of one workgroup: keys [s0, s0 + len) of chunk c, query columns [n0, n1).  NB = key blocks per wave.
-template <typename T, int D, int MODE, int NB>
-__device__ __forceinline__ void walk_columns(const ScoreArgs& a, Smem<T, D>& sm, int g, int c, int s0, int len, int row,
+template <typename T, int D, int WAVES, int MODE, int NB>
+__device__ __forceinline__ void walk_columns(const ScoreArgs& a, Smem<T, D, WAVES>& sm, int g, int c, int s0, int len, int row,
                                              int n0, int n1, int split) {
-    using O = Op<T, D>;
+    using O = Op<T, D, WAVES>;
     // Column groups of 16 per step.  A step costs about 0.2 us besides its logits (barrier, exchange of the sums, LDS
     // latency), so it takes two groups wherever the registers hold them: the weights are the only ones that double.
     constexpr int CG = (MODE == MODE_FUSED && NB * Op<T, D>::NJ > CG2_MAX_KEYS) ? 1 : 2;
@@ -310,9 +310,10 @@ __device__ __forceinline__ void walk_columns(const ScoreArgs& a, Smem<T, D>& sm,
     bool bad = false;
     int column = x;   // (its own register: one that came back from scratch memory at the loop's entry would be waited for in every step, with the copies)
     // 1 / l of this lane's column of group cg of step st (0 past the last column); MODE_LSE: the normaliser goes out
-    auto finish_column = [&](int st, int cg, const f32x4& l0, const f32x4& l1) -> float {
+    auto finish_column = [&](int st, int cg, const f32x4 (&sums)[WAVES / 4]) -> float {
         const int i = STEP * st + 16 * cg + column;
-        const float l = ((l0[0] + l0[1]) + (l0[2] + l0[3])) + ((l1[0] + l1[1]) + (l1[2] + l1[3]));
+        float l = (sums[0][0] + sums[0][1]) + (sums[0][2] + sums[0][3]);
+        if constexpr (WAVES == 8) l += (sums[1][0] + sums[1][1]) + (sums[1][2] + sums[1][3]);
         bad = bad || !(l < 0x1p100f);
         if constexpr (MODE == MODE_LSE) {
             if (wave == 0 && kg == 0 && i < n1 - n0)
@@ -358,14 +359,14 @@ __device__ __forceinline__ void walk_columns(const ScoreArgs& a, Smem<T, D>& sm,
             plain_barrier();
             if (last_of_tile && st / SPT + 2 < n_tiles) copy_tile(st / SPT + 2, (st / SPT) & 1);
             float f[CG], ref[CG], lsum[CG][2], w[4];
-            f32x4 l0[CG], l1[CG];
+            f32x4 l[CG][WAVES / 4];   // the waves' sums
             const uint32_t next_q = q_at(st + 1);
 #pragma unroll
             for (int cg = 0; cg < CG; ++cg) {   // all of the step's first reads at once
                 ref[cg] = sm.ref[STEP * st + 16 * cg + x];
                 if constexpr (MODE != MODE_GIVEN) {
-                    l0[cg] = *reinterpret_cast<const f32x4*>(&sm.l[(st + 1) & 1][16 * cg + x][0]);
-                    l1[cg] = *reinterpret_cast<const f32x4*>(&sm.l[(st + 1) & 1][16 * cg + x][4]);
+#pragma unroll
+                    for (int h = 0; h < WAVES / 4; ++h) l[cg][h] = *reinterpret_cast<const f32x4*>(&sm.l[(st + 1) & 1][16 * cg + x][4 * h]);
                 }
                 lsum[cg][1] = f[cg] = 0.f;   // (of one block: nothing else comes to it)
             }
@@ -379,7 +380,7 @@ __device__ __forceinline__ void walk_columns(const ScoreArgs& a, Smem<T, D>& sm,
             constexpr int LATE = MODE == MODE_FUSED && LOGITS >= 8 ? 4 : 0;
             auto finish = [&] {
 #pragma unroll
-                for (int cg = 0; cg < CG; ++cg) f[cg] = (MODE != MODE_GIVEN && st > 0) ? finish_column(st - 1, cg, l0[cg], l1[cg]) : 0.f;
+                for (int cg = 0; cg < CG; ++cg) f[cg] = (MODE != MODE_GIVEN && st > 0) ? finish_column(st - 1, cg, l[cg]) : 0.f;
             };
             if (LATE == 0) finish();
             float t[2], e[2];
@@ -424,7 +425,9 @@ __device__ __forceinline__ void walk_columns(const ScoreArgs& a, Smem<T, D>& sm,
                 }
                 if constexpr (n + 1 == LATE) {
 #pragma unroll
-                    for (int cg = 0; cg < CG; ++cg) asm volatile("" : "+v"(l0[cg]), "+v"(l1[cg]));   // (not earlier)
+                    for (int cg = 0; cg < CG; ++cg)
+#pragma unroll
+                        for (int h = 0; h < WAVES / 4; ++h) asm volatile("" : "+v"(l[cg][h]));   // (not earlier)
                     finish();
                 }
                 __builtin_amdgcn_sched_barrier(0);
@@ -442,8 +445,10 @@ __device__ __forceinline__ void walk_columns(const ScoreArgs& a, Smem<T, D>& sm,
             plain_barrier();
 #pragma unroll
             for (int cg = 0; cg < CG; ++cg) {
-                const float* l = sm.l[(n_steps - 1) & 1][16 * cg + x];
-                const float f = finish_column(n_steps - 1, cg, *reinterpret_cast<const f32x4*>(l), *reinterpret_cast<const f32x4*>(l + 4));
+                f32x4 l[WAVES / 4];
+#pragma unroll
+                for (int h = 0; h < WAVES / 4; ++h) l[h] = *reinterpret_cast<const f32x4*>(&sm.l[(n_steps - 1) & 1][16 * cg + x][4 * h]);
+                const float f = finish_column(n_steps - 1, cg, l);
                 if constexpr (MODE == MODE_FUSED) {
 #pragma unroll
                     for (int b = 0; b < NB; ++b)
@@ -511,10 +516,10 @@ __device__ __forceinline__ void walk_columns(const ScoreArgs& a, Smem<T, D>& sm,
 
 // One workgroup = (KV head, chunk, segment of the chunk, column range).  1-D grid, KV head fastest: with 8 KV heads an
 // XCD's L2 serves the queries of one head and the keys that its column ranges share.
-template <typename T, int D, int MODE>
+template <typename T, int D, int WAVES, int MODE>
 __global__ __launch_bounds__(64 * WAVES, 2) void score_kernel(const ScoreArgs a) {
-    using O = Op<T, D>;
-    __shared__ Smem<T, D> sm;
+    using O = Op<T, D, WAVES>;
+    __shared__ Smem<T, D, WAVES> sm;
     int t = blockIdx.x;
     const int g = t % a.Hkv; t /= a.Hkv;
     const int split = t % a.n_split; t /= a.n_split;
@@ -532,17 +537,17 @@ __global__ __launch_bounds__(64 * WAVES, 2) void score_kernel(const ScoreArgs a)
     int row = lse_row<O::SEG>(c, c0) + part;             // MODE_LSE: this segment's normalisers go there
     if (MODE == MODE_GIVEN) row = a.global_scope ? a.lse_rows - 1 : row - part;   // combined: the chunk's first row, or the last of all
     switch ((len + 16 * WAVES - 1) / (16 * WAVES)) {
-        case 1: walk_columns<T, D, MODE, 1>(a, sm, g, c, s0, len, row, n0, n1, split); break;
-        case 2: walk_columns<T, D, MODE, 2>(a, sm, g, c, s0, len, row, n0, n1, split); break;
-        case 3: walk_columns<T, D, MODE, 3>(a, sm, g, c, s0, len, row, n0, n1, split); break;
-        case 4: walk_columns<T, D, MODE, 4>(a, sm, g, c, s0, len, row, n0, n1, split); break;
+        case 1: walk_columns<T, D, WAVES, MODE, 1>(a, sm, g, c, s0, len, row, n0, n1, split); break;
+        case 2: walk_columns<T, D, WAVES, MODE, 2>(a, sm, g, c, s0, len, row, n0, n1, split); break;
+        case 3: walk_columns<T, D, WAVES, MODE, 3>(a, sm, g, c, s0, len, row, n0, n1, split); break;
+        case 4: walk_columns<T, D, WAVES, MODE, 4>(a, sm, g, c, s0, len, row, n0, n1, split); break;
         default:
             if constexpr (O::NB_MAX > 4) {
                 switch ((len + 16 * WAVES - 1) / (16 * WAVES)) {
-                    case 5: walk_columns<T, D, MODE, 5>(a, sm, g, c, s0, len, row, n0, n1, split); break;
-                    case 6: walk_columns<T, D, MODE, 6>(a, sm, g, c, s0, len, row, n0, n1, split); break;
-                    case 7: walk_columns<T, D, MODE, 7>(a, sm, g, c, s0, len, row, n0, n1, split); break;
-                    default: walk_columns<T, D, MODE, 8>(a, sm, g, c, s0, len, row, n0, n1, split); break;
+                    case 5: walk_columns<T, D, WAVES, MODE, 5>(a, sm, g, c, s0, len, row, n0, n1, split); break;
+                    case 6: walk_columns<T, D, WAVES, MODE, 6>(a, sm, g, c, s0, len, row, n0, n1, split); break;
+                    case 7: walk_columns<T, D, WAVES, MODE, 7>(a, sm, g, c, s0, len, row, n0, n1, split); break;
+                    default: walk_columns<T, D, WAVES, MODE, 8>(a, sm, g, c, s0, len, row, n0, n1, split); break;
                 }
             }
     }
@@ -612,6 +617,9 @@ int choose_splits(int items, int n_steps, int n_cu, int max_split) {
 }
 
 template <typename T, int D>
+constexpr bool FEW_WAVES = D * sizeof(T) <= 256;   // two workgroups' LDS fits a compute unit
+
+template <typename T, int D>
 hipError_t run(const Shape& s, const void* q, int nq, const void* k, const ChunkTable& ct, int norm, const Workspace& ws,
                float* scores, int src, const int32_t* store_row0, const float2* table, hipStream_t st) {
     using O = Op<T, D>;
@@ -637,6 +645,13 @@ hipError_t run(const Shape& s, const void* q, int nq, const void* k, const Chunk
     a.max_parts = (max_len + O::SEG - 1) / O::SEG;   // (at least segments(len) for every chunk)
     a.lse_rows = ct.n + L_ctx / O::SEG + 1;
     const bool two_walks = a.global_scope || a.max_parts > 1;
+    // Four waves where every chunk fits them: two workgroups then share a compute unit, each with barriers of its own, and a wave has twice the key blocks per
+    // exchange of the sums.  64 x 300 keys, 512 question tokens, 64 / 8 heads 290 -> 193 us; 64 x 220, 100 tokens, 32 / 8 heads 38 -> 30; 24 x 300, 200 tokens 33.9 -> 29.7.  Not for a
+    // few steps, whose time is that of the loads in front (24 x 500 keys, 16 tokens, 64 / 8 heads 13.8 : 14.7, 16 x 220, 40 tokens, 32 / 8 heads 10.9 : 11.4), nor with one launch for
+    // the short chunks and one for the others: each leaves the chip idle at its end (12 calls 1 to 59 % longer).
+    bool few_waves = false;
+    if constexpr (FEW_WAVES<T, D>)
+        few_waves = !two_walks && max_len <= Op<T, D, MOST_WAVES / 2>::SEG && (int64_t)n * s.Hkv * ((NQG + RANGE_UNIT - 1) / RANGE_UNIT) >= 4 * ws.n_cu;
     // All columns at once where the workspace holds their partial sums and normalisers (score_lse_floats, score_column_ranges), else in turns.
     int64_t cols = std::min<int64_t>(NQG, (int64_t)ws.col_splits * MAX_COLS);
     if (two_walks) cols = std::min<int64_t>(cols, (int64_t)(ws.lse_floats / ((size_t)s.Hkv * a.lse_rows)));
@@ -646,22 +661,25 @@ hipError_t run(const Shape& s, const void* q, int nq, const void* k, const Chunk
     for (a.col0 = 0; a.col0 < NQG; a.col0 = a.col_end) {
         a.col_end = (int)std::min<int64_t>(NQG, a.col0 + cols);
         const int n_cols = a.col_end - a.col0, n_steps = (n_cols + RANGE_UNIT - 1) / RANGE_UNIT;
-        a.n_split = choose_splits(n * all_parts * s.Hkv, n_steps, ws.n_cu, ws.col_splits);
+        a.n_split = choose_splits(n * all_parts * s.Hkv, n_steps, few_waves ? 2 * ws.n_cu : ws.n_cu, ws.col_splits);
         a.split_cols = (n_steps + a.n_split - 1) / a.n_split * RANGE_UNIT;
         a.n_split = (n_cols + a.split_cols - 1) / a.split_cols;
         if (a.n_split > ws.col_splits) return hipErrorInvalidValue;
-        const dim3 block(64 * WAVES);
+        const dim3 block(64 * MOST_WAVES);
         if (!a.global_scope && min_parts == 1) {   // (the chunks of several segments return at once)
             a.max_parts = 1;
-            score_kernel<T, D, MODE_FUSED><<<dim3(n * a.n_split * s.Hkv), block, 0, st>>>(a);
+            const dim3 grid(n * a.n_split * s.Hkv);
+            if constexpr (FEW_WAVES<T, D>)
+                if (few_waves) score_kernel<T, D, MOST_WAVES / 2, MODE_FUSED><<<grid, dim3(32 * MOST_WAVES), 0, st>>>(a);
+            if (!few_waves) score_kernel<T, D, MOST_WAVES, MODE_FUSED><<<grid, block, 0, st>>>(a);
             a.max_parts = all_parts;
         }
         if (two_walks) {
             const dim3 grid(n * a.max_parts * a.n_split * s.Hkv);
-            score_kernel<T, D, MODE_LSE><<<grid, block, 0, st>>>(a);
+            score_kernel<T, D, MOST_WAVES, MODE_LSE><<<grid, block, 0, st>>>(a);
             score_lse_combine_kernel<O::SEG><<<dim3((n_cols + 255) / 256, s.Hkv, a.global_scope ? 1 : ct.n), dim3(256), 0, st>>>(
                 ct, n_cols, a.lse_rows, a.global_scope, a.lse2);
-            score_kernel<T, D, MODE_GIVEN><<<grid, block, 0, st>>>(a);
+            score_kernel<T, D, MOST_WAVES, MODE_GIVEN><<<grid, block, 0, st>>>(a);
         }
         const int n_sums = a.n_split * s.Hkv;
         score_reduce_kernel<<<dim3((L_ctx + 63) / 64), dim3(64, std::min(REDUCE_MAX_WAVES, (n_sums + REDUCE_AHEAD - 1) / REDUCE_AHEAD)), 0, st>>>(

@@ -220,6 +220,13 @@ def test_scores_at_every_number_of_key_blocks(Hq, Hkv, d, dt, nq):
     test_scores(Hq, Hkv, d, dt, nq, (128, 129, 255, 257, 400, 512) + ((513, 640, 750, 769, 1000, 1024) if (d, dt) != (128, "f32") else ()), B.FR_NORM_PER_CHUNK)
 
 
+# Workgroups of four waves: chunks of one to eight blocks of 64 keys, from 1024 (chunk, KV head, 32 columns) on; one chunk of 513 keys: eight waves for all.
+@pytest.mark.parametrize("longest", [512, 513])
+@pytest.mark.parametrize("Hq,Hkv,d,dt,nq", [(32, 8, 128, "bf16", 121), (28, 4, 128, "bf16", 170), (16, 8, 64, "bf16", 230), (8, 8, 64, "f32", 500)])
+def test_scores_of_chunks_for_four_waves(Hq, Hkv, d, dt, nq, longest):
+    test_scores(Hq, Hkv, d, dt, nq, (1, 64, 65, 130, 255, 300, 449, longest), B.FR_NORM_PER_CHUNK)
+
+
 @pytest.mark.parametrize("norm", [B.FR_NORM_PER_CHUNK, B.FR_NORM_GLOBAL])
 def test_scores_of_more_columns_than_the_workspace_holds(norm):
     """A context of two million tokens holds the partial sums of 4096 query columns and the normalisers of 2048 at a time: 4400
