@@ -15,12 +15,13 @@
 // A block's product is formed from zero and added to the running sum with one rounding: onto the running sum the product rounds that several
 // times a block, which the longer chains of eight waves had made 1 to 3 % worse against float64 than 16 (head_dim 64: 1.652e-7 with 16
 // waves, 1.670e-7 with eight, now 1.610e-7 at 109 of 544 positions; 1 % of the call).
-// 4 heads, head_dim 64, us a call: 42 rows of 272 positions 9.0, 109 of 544 12.9, 310 of 800 16.9, 768 of 1280 24.7; with 16 waves per
-// workgroup and the values of a key as four scalar loads 11.1, 15.2, 18.9, 26.0.  Four waves are slower, and so is asking for the values of the
-// next block, or of three blocks, ahead of the products: more code, and the calls are short enough to be bound by fetching it.
+// 4 heads, head_dim 64, us a call, keys and values straight into fragment registers : through LDS: 42 rows of 272 positions 9.5 : 8.5, 109 of 544 13.3 : 11.6, 310 of 800
+// 17.3 : 15.1, 768 of 1280 25.2 : 21.6; bf16, 80 heads over one KV head, 172 of 920 49 : 32.  A round of eight blocks takes about a microsecond of the matrix pipes, on as
+// many compute units as there are column tiles.  Four waves are slower, 16 waves too (11.1 and 15.2 where eight took 9.0 and 12.9).
 #include "fr_internal.hpp"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace fr {
 
@@ -46,10 +47,15 @@ __global__ __launch_bounds__(64 * W) void attn_f32_kernel(const T* __restrict__ 
                                                           const int32_t* __restrict__ inv, T* __restrict__ out,
                                                           float* __restrict__ lse, int Hq, int Hkv, int n_tiles, float scale_log2e) {
     constexpr int NJ = D / 16, PITCH = D + 4;
-    __shared__ float o_lds[W][16][PITCH];
+    constexpr int RB = D * (int)sizeof(T), RV = RB / 16, COPIES = 16 * RB / 1024, RC = 1024 / RB;   // bytes of a head row, its 16-byte vectors; copies of a block of 16, rows of a copy
+    struct Blocks { unsigned char k[W][16 * RB], v[W][16 * RB]; };
+    struct Merge { float o[W][16][PITCH]; };
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[sizeof(Blocks) > sizeof(Merge) ? sizeof(Blocks) : sizeof(Merge)];
+    Blocks& blocks = *reinterpret_cast<Blocks*>(smem);
+    auto& o_lds = reinterpret_cast<Merge*>(smem)->o;
     __shared__ float m_lds[W][16], l_lds[W][16];
     __shared__ uint16_t row_of[MAP_MAX_L];   // fresh row + 1 of a position, 0 = none (only where `inv` is not given)
-    const int tid = threadIdx.x, lane = tid & 63, x = lane & 15, kg = lane >> 4, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, x = lane & 15, kg = lane >> 4, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = blockIdx.x % Hkv, tile = n_tiles - 1 - blockIdx.x / Hkv;   // longest tiles first
     const int G = Hq / Hkv, cols = R * G;
     const int n = min(16 * tile + x, cols - 1), r = n / G, head = g * G + n % G;   // columns past the end: a copy of the last
@@ -72,31 +78,59 @@ __global__ __launch_bounds__(64 * W) void attn_f32_kernel(const T* __restrict__ 
         }
         __syncthreads();
     }
-    auto fresh_row = [&](int j) -> int { return own_map ? (int)row_of[j] - 1 : have_new ? inv[j] : -1; };
-    auto row_ptr = [&](int j, const T* cache, const T* fresh) -> const T* {
-        j = min(j, p_last);
-        const int f = fresh_row(j);
-        return f >= 0 ? fresh + ((size_t)f * Hkv + g) * D : cache + ((size_t)j * Hkv + g) * D;
+    // A wave's block of 16 keys, and of their values, in LDS: copied global -> LDS (no registers, no wait) while the wave works on the one before, rows side by side: a
+    // fragment's 16 rows x 64 bytes per instruction, neighbouring lanes in different rows, take the vector cache four times the accesses.
+    // Vector c of key row r sits in place c ^ swz(r): the 16 rows of a fragment read meet in no bank.
+    const int q = lane / RV, vec = lane % RV;
+    auto swz = [](int r) { return RB == 128 ? (r >> 1) & 7 : r & 15; };
+    auto lds_address = [](const void* p) { return __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) const unsigned char*)p); };
+    auto dma = [](const unsigned char* src, uint32_t dst) { asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(dst) : "memory"); };
+    auto wait_but = [](auto n) {   // until all but the wave's last n copies have landed
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0x0f70 | decltype(n)::value);
+        asm volatile("" ::: "memory");
+    };
+    const uint32_t k_lds = lds_address(blocks.k[wave]), v_lds = lds_address(blocks.v[wave]);
+    size_t source[COPIES];   // byte offset of the lane's rows of the block on its way
+    bool fresh[COPIES];
+    auto copy_k = [&](int b) {
+        int f[COPIES];   // fresh rows
+        auto key = [&](int i) { return min(16 * b + RC * i + q, p_last); };   // keys behind the tile's last row repeat that one
+        if (own_map) {
+#pragma unroll
+            for (int i = 0; i < COPIES; ++i) f[i] = (int)row_of[key(i)] - 1;
+        } else {
+#pragma unroll
+            for (int i = 0; i < COPIES; ++i) f[i] = have_new ? inv[key(i)] : -1;
+        }
+#pragma unroll
+        for (int i = 0; i < COPIES; ++i) {
+            fresh[i] = f[i] >= 0;
+            source[i] = ((size_t)(fresh[i] ? f[i] : key(i)) * Hkv + g) * RB;
+        }
+#pragma unroll
+        for (int i = 0; i < COPIES; ++i)
+            dma(reinterpret_cast<const unsigned char*>(fresh[i] ? k_new : k_cache) + source[i] + 16 * (vec ^ swz(RC * i + q)), k_lds + 1024 * i);
+    };
+    auto copy_v = [&] {   // of the same block
+#pragma unroll
+        for (int i = 0; i < COPIES; ++i) dma(reinterpret_cast<const unsigned char*>(fresh[i] ? v_new : v_cache) + source[i] + 16 * vec, v_lds + 1024 * i);
     };
 
     f32x4 o[NJ];    // O^T: row m of product md is dim NJ m + md, so a lane's values of a key are neighbours in memory; o[md][i]: m = 4 kg + i
 #pragma unroll
     for (int md = 0; md < NJ; ++md) o[md] = f32x4{0.f, 0.f, 0.f, 0.f};
     float m = NEG_BIG, l = 0.f;
-    f32x4 kv[NJ];   // key 16 b + x, dims 16 j + 4 kg + e
-    auto load_k = [&](int b) {
-        const T* p = row_ptr(16 * b + x, k_cache, k_new) + 4 * kg;
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) kv[j] = load4(p + 16 * j);
-    };
-    if (wave < n_blocks) load_k(wave);
+    wait_but(std::integral_constant<int, 0>{});   // (nothing that the compiler counts is in flight from here on)
+    copy_k(min(wave, n_blocks - 1));   // (past the last block: that one again, nobody uses it; the counts of the waits stay the same)
+    copy_v();
     for (int b = wave; b < n_blocks; b += W) {
-        f32x4 vv[4][NJ / 4];   // values of keys 4 kg + i, dims NJ x ..
+        wait_but(std::integral_constant<int, COPIES>{});
+        f32x4 kv[NJ], vv[4][NJ / 4];   // key 16 b + x, dims 16 j + 4 kg + e; values of keys 4 kg + i, dims NJ x ..
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const T* p = row_ptr(16 * b + 4 * kg + i, v_cache, v_new) + NJ * x;
-#pragma unroll
-            for (int h = 0; h < NJ / 4; ++h) vv[i][h] = load4(p + 4 * h);
+        for (int j = 0; j < NJ; ++j) {
+            const int at = (16 * j + 4 * kg) * (int)sizeof(T);
+            kv[j] = load4(reinterpret_cast<const T*>(blocks.k[wave] + x * RB + ((at / 16) ^ swz(x)) * 16 + at % 16));
         }
         auto value = [&](int i, int md) -> float { return vv[i][md >> 2][md & 3]; };
         f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
@@ -107,7 +141,8 @@ __global__ __launch_bounds__(64 * W) void attn_f32_kernel(const T* __restrict__ 
             s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[j][2], qv[j][2], s0, 0, 0, 0);
             s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[j][3], qv[j][3], s1, 0, 0, 0);
         }
-        if (b + W < n_blocks) load_k(b + W);
+        __builtin_amdgcn_sched_barrier(0);
+        copy_k(min(b + W, n_blocks - 1));
         f32x4 s = s0 + s1;
         float mx = NEG_BIG;
 #pragma unroll
@@ -125,6 +160,11 @@ __global__ __launch_bounds__(64 * W) void attn_f32_kernel(const T* __restrict__ 
         }
         l = l * alpha + psum;
         float scale_o = alpha;
+        wait_but(std::integral_constant<int, COPIES>{});
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int h = 0; h < NJ / 4; ++h) vv[i][h] = load4(reinterpret_cast<const T*>(blocks.v[wave] + (4 * kg + i) * RB) + NJ * x + 4 * h);
         if (16 * b + 15 > p_first) {   // values that are not finite: out of the product, into the columns that see them
             float z = 0.f;   // NaN if one of them is not finite
 #pragma unroll
@@ -165,7 +205,11 @@ __global__ __launch_bounds__(64 * W) void attn_f32_kernel(const T* __restrict__ 
         for (int md = 0; md < NJ; ++md)
 #pragma unroll
             for (int e = 0; e < 4; ++e) o[md][e] = __builtin_fmaf(o[md][e], scale_o, pv[md][e]);
+        __builtin_amdgcn_sched_barrier(0);
+        copy_v();
     }
+    wait_but(std::integral_constant<int, 0>{});
+    __syncthreads();   // everyone is done with the copies
     // ---- merge the waves ---------------------------------------------------------------------------------------------
     l = column_sum(l);
     if (kg == 0) { m_lds[wave][x] = m; l_lds[wave][x] = l; }
