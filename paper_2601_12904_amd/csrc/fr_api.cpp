@@ -323,7 +323,7 @@ fr_status fr_rope_shift(fr_ctx* ctx, const void* k_src, void* k_dst, const int32
     if ((st = need_device(ctx)) != FR_OK) return st;
     hipStream_t hs = (hipStream_t)stream;
     const hipError_t e = launch_rope_shift(s, k_src, k_dst, ct, dl, max_len, ctx->ws.rope_theta, n_batch, src_batch_stride,
-                                           dst_batch_stride, nullptr, hs);
+                                           dst_batch_stride, nullptr, ctx->ws.n_cu, hs);
     if (e != hipSuccess) return hip_fail(ctx, "rope shift launch", e);
     return FR_OK;
 }
@@ -426,11 +426,11 @@ static fr_status gather_from_store(fr_ctx* ctx, const void* k_store, const void*
     hipError_t e = hipSuccess;
     if (L_ctx > 0) {
         const ChunkDeltas zero{};
-        e = launch_rope_shift(s, v_store, ctx->ws.store_v, ct, zero, max_len, ctx->ws.rope_theta, 1, 0, 0, &rows, hs);
+        e = launch_rope_shift(s, v_store, ctx->ws.store_v, ct, zero, max_len, ctx->ws.rope_theta, 1, 0, 0, &rows, ctx->ws.n_cu, hs);
         if (e != hipSuccess) return hip_fail(ctx, "value gather launch", e);
     }
     if (L_ctx > 0) {
-        e = launch_rope_shift(s, k_store, ctx->ws.store_k, ct, dl, max_len, ctx->ws.rope_theta, 1, 0, 0, &rows, hs);
+        e = launch_rope_shift(s, k_store, ctx->ws.store_k, ct, dl, max_len, ctx->ws.rope_theta, 1, 0, 0, &rows, ctx->ws.n_cu, hs);
         if (e != hipSuccess) return hip_fail(ctx, "key gather launch", e);
     }
     const int64_t row_words = (int64_t)s.Hkv * s.d * s.esize / 4;

@@ -109,7 +109,7 @@ hipError_t launch_rope_table(const Shape& s, const ChunkDeltas& deltas, int n_ch
 // prompt offset.
 hipError_t launch_rope_shift(const Shape& s, const void* src, void* dst, const ChunkTable& ct, const ChunkDeltas& deltas,
                              int max_chunk_len, const double* theta, int n_batch, int64_t src_stride,
-                             int64_t dst_stride, const ChunkRows* src_rows, hipStream_t st);
+                             int64_t dst_stride, const ChunkRows* src_rows, int n_cu, hipStream_t st);
 hipError_t launch_clear_words(uint32_t* words, int64_t n_words, hipStream_t st);
 hipError_t launch_kv_scatter(const Shape& s, const void* k_new, const void* v_new, const int32_t* q_index,
                              int R, void* k_cache, void* v_cache, int64_t L, hipStream_t st);

@@ -517,17 +517,18 @@ __global__ __launch_bounds__(256, 2) void decode_partial_mfma_kernel(
     }
 }
 
-// One workgroup per (query, query head): merges the pieces of the query's segments, then of its page.  Every wave takes
-// pieces w, w + 4, ... (their loads do not depend on one another: the weights come from the maximum over all pieces, found
-// first), the four waves are added in wave order.
+// One workgroup per (query, query head): merges the pieces of the query's segments, then of its page.  The pass is one trip to memory: wave w takes pieces
+// w, w + W, ... (W = the workgroup's waves), up to COMBINE_AHEAD of them with all loads in flight together and references of its own, and the waves are merged through LDS in
+// wave order.  (Four waves with four pieces in flight behind a search for the largest reference: 5.3 us for the 76 pieces of each of two queries; sixteen waves 3.3.)
+constexpr int COMBINE_AHEAD = 6, COMBINE_MAX_WAVES = 16;
 template <typename T, int D>
-__global__ __launch_bounds__(256) void decode_combine_kernel(const float* __restrict__ partials, const int32_t* __restrict__ seg_offsets,
+__global__ __launch_bounds__(64 * COMBINE_MAX_WAVES) void decode_combine_kernel(const float* __restrict__ partials, const int32_t* __restrict__ seg_offsets,
                                                              int n_seg, int Hq, Pieces pc, T* __restrict__ out,
                                                              float* __restrict__ lse_out) {
     constexpr int PF = part_floats<D>();
     constexpr int EPT = D / 64;   // elements per lane
-    __shared__ float o_lds[4][D], l_lds[4], m_lds[4];
-    const int b = blockIdx.x, h = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    __shared__ float o_lds[COMBINE_MAX_WAVES][D], l_lds[COMBINE_MAX_WAVES], m_lds[COMBINE_MAX_WAVES];
+    const int b = blockIdx.x, h = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
     int s0 = seg_offsets[b], s1 = seg_offsets[b + 1];
     s0 = max(0, min(s0, n_seg));
     s1 = max(s0, min(s1, n_seg));
@@ -536,32 +537,50 @@ __global__ __launch_bounds__(256) void decode_combine_kernel(const float* __rest
         const int piece = i < from_seg ? s0 * pc.seg + i : n_seg * pc.seg + b * pc.page + (i - from_seg);
         return partials + ((size_t)piece * Hq + h) * PF;
     };
-    float mt = NEG_BIG;
-    for (int i = threadIdx.x; i < n; i += 256) mt = fmaxf(mt, part(i)[0]);
-    for (int sft = 32; sft > 0; sft >>= 1) mt = fmaxf(mt, __shfl_xor(mt, sft));
-    if (lane == 0) m_lds[wave] = mt;
-    __syncthreads();
-    mt = fmaxf(fmaxf(m_lds[0], m_lds[1]), fmaxf(m_lds[2], m_lds[3]));
-    float lt = 0.f, ot[EPT];
+    float mt = NEG_BIG, lt = 0.f, ot[EPT];
 #pragma unroll
     for (int e = 0; e < EPT; ++e) ot[e] = 0.f;
-#pragma unroll 4
-    for (int i = wave; i < n; i += 4) {
-        const float* p = part(i);
-        const float a = __builtin_amdgcn_exp2f(p[0] - mt);
-        lt += p[1] * a;
+    for (int i0 = wave; i0 < n; i0 += COMBINE_AHEAD * waves) {
+        float pm[COMBINE_AHEAD], pl[COMBINE_AHEAD], po[COMBINE_AHEAD][EPT];
 #pragma unroll
-        for (int e = 0; e < EPT; ++e) ot[e] += p[2 + lane * EPT + e] * a;
+        for (int u = 0; u < COMBINE_AHEAD; ++u) {   // (past the end: the last piece, which does not count; behind a branch each load would be waited for)
+            const float* p = part(min(i0 + u * waves, n - 1));
+            pm[u] = p[0];
+            pl[u] = p[1];
+#pragma unroll
+            for (int e = 0; e < EPT; ++e) po[u][e] = p[2 + lane * EPT + e];
+        }
+        float m_new = mt;
+#pragma unroll
+        for (int u = 0; u < COMBINE_AHEAD; ++u) m_new = i0 + u * waves < n ? fmaxf(m_new, pm[u]) : m_new;
+        const float alpha = __builtin_amdgcn_exp2f(mt - m_new);
+        mt = m_new;
+        lt *= alpha;
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) ot[e] *= alpha;
+#pragma unroll
+        for (int u = 0; u < COMBINE_AHEAD; ++u) {
+            if (i0 + u * waves >= n) continue;   // (not a factor of 0: the piece may hold anything)
+            const float a = __builtin_amdgcn_exp2f(pm[u] - mt);
+            lt += pl[u] * a;
+#pragma unroll
+            for (int e = 0; e < EPT; ++e) ot[e] += po[u][e] * a;
+        }
     }
 #pragma unroll
     for (int e = 0; e < EPT; ++e) o_lds[wave][lane * EPT + e] = ot[e];
-    if (lane == 0) l_lds[wave] = lt;
+    if (lane == 0) { l_lds[wave] = lt; m_lds[wave] = mt; }
     __syncthreads();
-    lt = (l_lds[0] + l_lds[1]) + (l_lds[2] + l_lds[3]);
-    const float inv = 1.0f / lt;
-    for (int e = threadIdx.x; e < D; e += 256)
-        out[((size_t)b * Hq + h) * D + e] = Elem<T>::from_f32(((o_lds[0][e] + o_lds[1][e]) + (o_lds[2][e] + o_lds[3][e])) * inv);
-    if (lse_out != nullptr && threadIdx.x == 0) lse_out[(size_t)b * Hq + h] = (mt + __builtin_amdgcn_logf(lt)) * 0.6931471805599453f;
+    if (threadIdx.x >= D) return;
+    for (int w = 0; w < waves; ++w) mt = fmaxf(mt, m_lds[w]);
+    float l = 0.f, o = 0.f;
+    for (int w = 0; w < waves; ++w) {
+        const float a = __builtin_amdgcn_exp2f(m_lds[w] - mt);   // (a wave without a piece: NEG_BIG, factor 0)
+        l += l_lds[w] * a;
+        o += o_lds[w][threadIdx.x] * a;
+    }
+    out[((size_t)b * Hq + h) * D + threadIdx.x] = Elem<T>::from_f32(o * (1.0f / l));
+    if (lse_out != nullptr && threadIdx.x == 0) lse_out[(size_t)b * Hq + h] = (mt + __builtin_amdgcn_logf(l)) * 0.6931471805599453f;
 }
 
 // Sets the bits of the listed store rows in one query's mask (optionally clearing the mask first).
@@ -628,8 +647,11 @@ hipError_t run(const Shape& s, const DecodeArgs& a, float* partials, const doubl
             (const T*)a.q, a.B, (const T*)a.k_shared, (const T*)a.v_shared, a.n_shared, a.seg_offsets, a.seg_row0, a.seg_len,
             a.seg_delta, a.n_seg, a.stale_bits, a.stale_words, (const T*)a.k_pages, (const T*)a.v_pages, a.page_stride,
             a.page_len, s.Hq, s.Hkv, theta, s.rope_layout, scale_log2e, partials, pc);
-    decode_combine_kernel<T, D><<<dim3(a.B, s.Hq), dim3(256), 0, st>>>(partials, a.seg_offsets, a.n_seg, s.Hq, pc, (T*)a.out,
-                                                                       a.lse_out);
+    // as many waves as the pieces of an average query need for one turn, at least those that hold the output's dims
+    const int64_t pieces = (int64_t)a.n_seg * pc.seg / a.B + pc.page;
+    const int waves = (int)std::max<int64_t>(D / 64, std::min<int64_t>(COMBINE_MAX_WAVES, (pieces + COMBINE_AHEAD - 1) / COMBINE_AHEAD));
+    decode_combine_kernel<T, D><<<dim3(a.B, s.Hq), dim3(64 * waves), 0, st>>>(partials, a.seg_offsets, a.n_seg, s.Hq, pc, (T*)a.out,
+                                                                              a.lse_out);
     return hipGetLastError();
 }
 

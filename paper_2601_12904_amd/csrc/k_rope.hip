@@ -1,7 +1,7 @@
 // Position recovery of cached chunk keys (Sec. 2.2.1 footnote, Appendix A): every key of chunk c is
 // rotated by Delta_c positions.  HBM-bound streaming: 16-byte loads and stores; a workgroup forms its chunk's (cos, sin)
-// row in fp64 itself.  880 tokens of 2 KB: 5.9 us, with a kernel that made a table of them in front 2.8 + 5.3; 16384
-// tokens: 15.2 us, before 4.7 + 14.1; 32 layers of them 0.39 ms = 5.5 TB/s either way.
+// row in fp64 itself.  880 tokens of 2 KB: 2.8 us back to back (4.2 with 32 tokens per workgroup, which leaves two thirds of the chip without one; 4800 tokens 4.6 : 5.2,
+// of 1 KB 3.6 either way); 16384 tokens: 12.5 us; 32 layers of them 0.39 ms = 5.5 TB/s.
 #include "k_rotate.hpp"
 
 namespace fr {
@@ -127,16 +127,19 @@ hipError_t launch_rope_table(const Shape& s, const ChunkDeltas& deltas, int n_ch
 
 hipError_t launch_rope_shift(const Shape& s, const void* src, void* dst, const ChunkTable& ct, const ChunkDeltas& deltas,
                              int max_chunk_len, const double* theta, int n_batch, int64_t src_stride,
-                             int64_t dst_stride, const ChunkRows* src_rows, hipStream_t st) {
+                             int64_t dst_stride, const ChunkRows* src_rows, int n_cu, hipStream_t st) {
     if (ct.n == 0 || max_chunk_len == 0 || n_batch == 0) return hipSuccess;
     const ChunkRows none{};
     const ChunkRows& rows = src_rows ? *src_rows : none;
     const int from_store = src_rows ? 1 : 0;
-    constexpr int TOK = 32;
-    dim3 grid((max_chunk_len + TOK - 1) / TOK, ct.n, n_batch);
-#define FR_ROPE_LAUNCH(T, LAY)                                                                      \
+    // Tokens per workgroup: 32, eight vectors of a thread in flight twice over; while that would leave compute units without a workgroup, 8 (see the head).
+    const bool few = (int64_t)((max_chunk_len + 31) / 32) * ct.n * n_batch < n_cu;
+    const int tok = few ? 8 : 32;
+    dim3 grid((max_chunk_len + tok - 1) / tok, ct.n, n_batch);
+#define FR_ROPE_LAUNCH_TOK(T, LAY, TOK)                                                             \
     rope_shift_kernel<T, LAY, TOK><<<grid, dim3(256), 0, st>>>((const T*)src, (T*)dst, ct, deltas, theta, \
                                                                s.Hkv, s.d, src_stride, dst_stride, rows, from_store)
+#define FR_ROPE_LAUNCH(T, LAY) do { if (few) FR_ROPE_LAUNCH_TOK(T, LAY, 8); else FR_ROPE_LAUNCH_TOK(T, LAY, 32); } while (0)
     if (s.dtype == FR_BF16) {
         if (s.rope_layout == FR_ROPE_INTERLEAVED)
             FR_ROPE_LAUNCH(__bf16, FR_ROPE_INTERLEAVED);
@@ -148,6 +151,7 @@ hipError_t launch_rope_shift(const Shape& s, const void* src, void* dst, const C
         else
             FR_ROPE_LAUNCH(float, FR_ROPE_HALF);
     }
+#undef FR_ROPE_LAUNCH_TOK
 #undef FR_ROPE_LAUNCH
     return hipGetLastError();
 }
