@@ -394,16 +394,18 @@ fr_status fr_score_select(fr_ctx* ctx, const void* q_question, int32_t nq, const
     hipStream_t hs = (hipStream_t)stream;
     float* scores = scores_out ? scores_out : ctx->ws.scores;
     const bool need_scores = (scores_out != nullptr) || (k > 0 && k < L_ctx);
+    SelectAfter select{k, nq, q_index_out, false};
     if (L_ctx > 0 && need_scores) {
         hipError_t e;
         if (nq > 0 && norm != FR_NORM_RAW)
-            e = launch_score(s, q_question, nq, k_ctx, ct, norm, ctx->ws, scores, nullptr, nullptr, hs);
+            e = launch_score(s, q_question, nq, k_ctx, ct, norm, ctx->ws, scores, nullptr, nullptr, &select, hs);
         else if (nq > 0 && score_raw_supported(s))
             e = launch_score_raw(s, q_question, nq, k_ctx, L_ctx, ctx->ws.qsum, scores, hs);
         else
             e = launch_score_simt(s, q_question, nq, k_ctx, L_ctx, scores, hs);
         if (e != hipSuccess) return hip_fail(ctx, "score launch", e);
     }
+    if (select.done) return FR_OK;
     hipError_t e = launch_select(scores, L_ctx, k, nq, q_index_out, ctx->ws.select_tmp, select_workspace_bytes(), hs);
     if (e != hipSuccess) return hip_fail(ctx, "select launch", e);
     return FR_OK;
@@ -485,6 +487,7 @@ fr_status fr_score_select_shared(fr_ctx* ctx, const void* q_question, int32_t nq
     hipStream_t hs = (hipStream_t)stream;
     float* scores = scores_out ? scores_out : ctx->ws.scores;
     const bool need_scores = (scores_out != nullptr) || (k > 0 && k < L_ctx);
+    SelectAfter select{k, nq, q_index_out, false};
     if (L_ctx > 0 && need_scores) {
         hipError_t e;
         if (nq == 0) {   // no question rows: every score is an empty sum (the generic kernel writes the zeros; no key is read)
@@ -492,10 +495,11 @@ fr_status fr_score_select_shared(fr_ctx* ctx, const void* q_question, int32_t nq
         } else {
             e = launch_rope_table(s, dl, n_chunks, ctx->ws.rope_theta, ctx->ws.rope_table, hs);
             if (e != hipSuccess) return hip_fail(ctx, "rope table launch", e);
-            e = launch_score(s, q_question, nq, k_store, ct, norm, ctx->ws, scores, chunk_store_row0, ctx->ws.rope_table, hs);
+            e = launch_score(s, q_question, nq, k_store, ct, norm, ctx->ws, scores, chunk_store_row0, ctx->ws.rope_table, &select, hs);
         }
         if (e != hipSuccess) return hip_fail(ctx, "score launch", e);
     }
+    if (select.done) return FR_OK;
     hipError_t e = launch_select(scores, L_ctx, k, nq, q_index_out, ctx->ws.select_tmp, select_workspace_bytes(), hs);
     if (e != hipSuccess) return hip_fail(ctx, "select launch", e);
     return FR_OK;

@@ -128,8 +128,18 @@ hipError_t launch_score_two_pass(const Shape& s, const void* q, int nq, const vo
                                  hipStream_t st);
 size_t score_lse_floats(const Shape& s, int64_t max_tokens, int max_chunks, int max_q);
 int score_column_ranges(const Shape& s, int64_t max_tokens, int max_q);
+// `select`: what the caller selects from the scores; done = the launches have done that too.
+struct SelectAfter {
+    int64_t k;
+    int nq;
+    int32_t* q_index;
+    bool done;
+};
 hipError_t launch_score(const Shape& s, const void* q, int nq, const void* k, const ChunkTable& ct, int norm,
-                        const Workspace& ws, float* scores, const int32_t* store_row0, const float2* table, hipStream_t st);
+                        const Workspace& ws, float* scores, const int32_t* store_row0, const float2* table, SelectAfter* select, hipStream_t st);
+// scores[j] = sum of n_parts partial sums [n_parts][n], and the selection from them, in one launch (short prompts).  0 <= k <= n.
+bool sum_and_select_pays(int64_t n, int n_parts);
+hipError_t launch_sum_and_select(const float* partial, int n_parts, int n, float* scores, int k, int nq, int32_t* q_index, hipStream_t st);
 
 // `tmp` (tmp_bytes bytes of device scratch) is used beyond SELECT_ONE_WORKGROUP_MAX scores only; a scratch too small
 // for n gives hipErrorInvalidValue before anything is launched.

@@ -621,7 +621,7 @@ constexpr bool FEW_WAVES = D * sizeof(T) <= 256;   // two workgroups' LDS fits a
 
 template <typename T, int D>
 hipError_t run(const Shape& s, const void* q, int nq, const void* k, const ChunkTable& ct, int norm, const Workspace& ws,
-               float* scores, int src, const int32_t* store_row0, const float2* table, hipStream_t st) {
+               float* scores, int src, const int32_t* store_row0, const float2* table, SelectAfter* select, hipStream_t st) {
     using O = Op<T, D>;
     const int L_ctx = ct.off[ct.n], NQG = nq * s.G;
     ScoreArgs a;
@@ -682,6 +682,10 @@ hipError_t run(const Shape& s, const void* q, int nq, const void* k, const Chunk
             score_kernel<T, D, MOST_WAVES, MODE_GIVEN><<<grid, block, 0, st>>>(a);
         }
         const int n_sums = a.n_split * s.Hkv;
+        if (a.col0 == 0 && a.col_end == NQG && sum_and_select_pays(L_ctx, n_sums)) {
+            select->done = true;
+            return launch_sum_and_select(ws.col_partial, n_sums, L_ctx, scores, (int)select->k, select->nq, select->q_index, st);
+        }
         score_reduce_kernel<<<dim3((L_ctx + 63) / 64), dim3(64, std::min(REDUCE_MAX_WAVES, (n_sums + REDUCE_AHEAD - 1) / REDUCE_AHEAD)), 0, st>>>(
             ws.col_partial, n_sums, L_ctx, a.col0 > 0, scores);
     }
@@ -718,7 +722,8 @@ int score_column_ranges(const Shape& s, int64_t max_tokens, int max_q) {
 // written; chunk c occupies its rows store_row0[c] .., and its keys are moved to their prompt positions while they are
 // loaded (`table`: device, [chunks][d / 2]).
 hipError_t launch_score(const Shape& s, const void* q, int nq, const void* k, const ChunkTable& ct, int norm,
-                        const Workspace& ws, float* scores, const int32_t* store_row0, const float2* table, hipStream_t st) {
+                        const Workspace& ws, float* scores, const int32_t* store_row0, const float2* table, SelectAfter* select, hipStream_t st) {
+    select->done = false;
     if (ct.off[ct.n] == 0 || nq == 0) return hipSuccess;
     if (score_two_pass_supported(s)) {
         int max_len = 0;
@@ -728,10 +733,10 @@ hipError_t launch_score(const Shape& s, const void* q, int nq, const void* k, co
     }
     const int src = !store_row0 ? SRC_PROMPT : s.rope_layout == FR_ROPE_INTERLEAVED ? SRC_STORE_INTERLEAVED : SRC_STORE_HALF;
     if (s.dtype == FR_BF16)
-        return s.d == 64 ? run<__bf16, 64>(s, q, nq, k, ct, norm, ws, scores, src, store_row0, table, st)
-                         : run<__bf16, 128>(s, q, nq, k, ct, norm, ws, scores, src, store_row0, table, st);
-    return s.d == 64 ? run<float, 64>(s, q, nq, k, ct, norm, ws, scores, src, store_row0, table, st)
-                     : run<float, 128>(s, q, nq, k, ct, norm, ws, scores, src, store_row0, table, st);
+        return s.d == 64 ? run<__bf16, 64>(s, q, nq, k, ct, norm, ws, scores, src, store_row0, table, select, st)
+                         : run<__bf16, 128>(s, q, nq, k, ct, norm, ws, scores, src, store_row0, table, select, st);
+    return s.d == 64 ? run<float, 64>(s, q, nq, k, ct, norm, ws, scores, src, store_row0, table, select, st)
+                     : run<float, 128>(s, q, nq, k, ct, norm, ws, scores, src, store_row0, table, select, st);
 }
 
 }  // namespace fr

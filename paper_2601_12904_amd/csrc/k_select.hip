@@ -218,19 +218,11 @@ __global__ __launch_bounds__(SEL_THREADS) void select_topk_kernel(const float* _
 // 8.2 -> 3.1 us, 880 8.6 -> 6.6.  Beyond 1024 scores, 32 keys a lane, the wave takes longer than the workgroup: layers of 1623 and 1679
 // tokens 70.6 and 58.1 us with it, 66.7 and 54.1 without.
 template <int PER>
-__global__ __launch_bounds__(64) void select_topk_wave_kernel(const float* __restrict__ scores, int n, int k, int nq,
-                                                              int32_t* __restrict__ out) {
-    const int lane = threadIdx.x;
-    for (int i = lane; i < nq; i += 64) out[k + i] = n + i;   // question tokens: positions n .. n + nq - 1
-    if (k <= 0) return;                                       // (there need be no scores then)
+__device__ __forceinline__ void select_in_wave(const float (&raw)[PER], int n, int k, int32_t* __restrict__ out) {
+    const int lane = threadIdx.x & 63;
     uint32_t keys[PER];
-    {
-        float raw[PER];
 #pragma unroll
-        for (int i = 0; i < PER; ++i) raw[i] = scores[min(64 * i + lane, n - 1)];
-#pragma unroll
-        for (int i = 0; i < PER; ++i) keys[i] = score_key(raw[i]);
-    }
+    for (int i = 0; i < PER; ++i) keys[i] = score_key(raw[i]);
     // keys past the end are copies of the last token's: `valid` leaves them out of every count
     auto valid = [&](int i) { return 64 * i + lane < n; };
     uint32_t thr = 0u, need_eq = 0u;      // taken: keys above thr, and the first need_eq that equal it
@@ -271,6 +263,72 @@ __global__ __launch_bounds__(64) void select_topk_wave_kernel(const float* __res
         pos += __popcll(bsel);
         eq_seen += (uint32_t)__popcll(beq);
     }
+}
+
+template <int PER>
+__global__ __launch_bounds__(64) void select_topk_wave_kernel(const float* __restrict__ scores, int n, int k, int nq,
+                                                              int32_t* __restrict__ out) {
+    const int lane = threadIdx.x;
+    for (int i = lane; i < nq; i += 64) out[k + i] = n + i;   // question tokens: positions n .. n + nq - 1
+    if (k <= 0) return;                                       // (there need be no scores then)
+    float raw[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) raw[i] = scores[min(64 * i + lane, n - 1)];
+    select_in_wave<PER>(raw, n, k, out);
+}
+
+// The scores' partial sums added up and selected from in one launch (score_reduce_kernel's sums in its order): a launch less for short prompts, whose calls are bound
+// by them on the device and on the host (4 x 128 tokens, 4 partial sums: the host's part of a selection call 13.0 -> 8.3 us).  Thread (quad of tokens, a): group w = a, a + 4, ..
+// of eight partial sums, 16 bytes a load (one token a thread is a quarter of a compute unit's load rate: 880 tokens, 40 partial sums 2 us more); then a token a thread;
+// then wave 0 selects.
+constexpr int SUM_GROUPS = 8;   // of eight partial sums at most
+template <int PER>
+__global__ __launch_bounds__(1024) void sum_and_select_kernel(const float* __restrict__ partial, int n_parts, int n, float* __restrict__ scores, int k,
+                                                              int nq, int32_t* __restrict__ out) {
+    typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    __shared__ __attribute__((aligned(16))) float sums[SUM_GROUPS][1024];
+    const int tid = threadIdx.x, groups = (n_parts + 7) / 8;
+    const int j = min(4 * (tid & 255), max(n - 4, 0));   // (the last quad of a number that is none of fours overlaps the one in front: the same sums twice)
+    for (int w = tid >> 8; w < groups; w += 4) {         // group w: parts w, w + groups, ...
+        f32x4u v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const float* p = partial + (size_t)min(w + u * groups, n_parts - 1) * n + j;
+            if (n >= 4) v[u] = *reinterpret_cast<const f32x4u*>(p);
+            else v[u] = f32x4u{p[0], p[min(1, n - 1)], p[min(2, n - 1)], 0.f};
+        }
+        f32x4 g = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (w + u * groups < n_parts) g += f32x4(v[u]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sums[w][j + e] = g[e];
+    }
+    for (int i = tid; i < nq; i += 1024) out[k + i] = n + i;   // question tokens: positions n .. n + nq - 1
+    __syncthreads();
+    if (tid < n) {
+        float t = 0.f;
+        for (int w = 0; w < groups; ++w) t += sums[w][tid];
+        scores[tid] = t;
+        sums[0][tid] = t;   // (this token's words are this thread's)
+    }
+    __syncthreads();
+    if (tid >= 64 || k <= 0) return;
+    float raw[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) raw[i] = sums[0][min(64 * i + tid, n - 1)];
+    select_in_wave<PER>(raw, n, k, out);
+}
+
+bool sum_and_select_pays(int64_t n, int n_parts) { return n > 0 && n <= 1024 && n_parts <= 8 * SUM_GROUPS; }
+
+hipError_t launch_sum_and_select(const float* partial, int n_parts, int n, float* scores, int k, int nq, int32_t* q_index, hipStream_t st) {
+    if (n <= 512)
+        sum_and_select_kernel<8><<<dim3(1), dim3(1024), 0, st>>>(partial, n_parts, n, scores, k, nq, q_index);
+    else
+        sum_and_select_kernel<16><<<dim3(1), dim3(1024), 0, st>>>(partial, n_parts, n, scores, k, nq, q_index);
+    return hipGetLastError();
 }
 
 static_assert(SELECT_ONE_WORKGROUP_MAX == (int64_t)SEL_THREADS * 32, "largest score vector of the one-workgroup kernel");

@@ -96,3 +96,27 @@ def test_running_maximum():
     want, want_lse = orc.sparse_prefill_attn(q, qi, kc, vc, kn, vn)
     assert H.max_rel_err(got, want) <= TOL[False]
     assert np.max(np.abs(lse - want_lse)) <= 1e-4
+
+
+# Sums and selection in one launch: up to 1024 tokens and 64 partial sums (KV heads x column ranges); quads of tokens with a rest, fewer than four tokens
+@pytest.mark.parametrize("Hq,Hkv,d,dt,nq", [(4, 4, 64, "f32", 9), (32, 8, 128, "bf16", 40), (64, 32, 128, "bf16", 70)])
+@pytest.mark.parametrize("L", [1, 2, 3, 4, 5, 63, 511, 512, 513, 1021, 1024, 1025])
+def test_selection_beside_the_sums(Hq, Hkv, d, dt, nq, L):
+    shape = synth.LayerShape(n_q_heads=Hq, n_kv_heads=Hkv, head_dim=d, dtype=dt, rope_base=10000.0)
+    w = synth.config_small_bf16(seed=L, chunk_lens=tuple(len(x) for x in np.array_split(np.arange(L), min(4, L))), nq=nq, shape=shape)
+    k = synth.round_to_storage(w.k_cached, dt)
+    k[L // 2:] = k[:L - L // 2] if L % 2 == 0 else k[L // 2:]     # even: equal scores in pairs of chunks
+    want = orc.critical_scores(w.q_question, k, w.chunk_offsets)
+    ctx = H.make_ctx(shape, w.L, w.n_chunks, nq)
+    q, kd = H.dev(w.q_question, dt), H.dev(k, dt)
+    for take in {0, 1, (L + 6) // 7, L - 1, L}:
+        scores = torch.full((L,), -7.0, dtype=torch.float32, device="cuda")
+        qi, again = (torch.full((take + nq,), -1, dtype=torch.int32, device="cuda") for _ in range(2))
+        ctx.fr_score_select(q, nq, kd, w.chunk_offsets, take, B.FR_NORM_PER_CHUNK, scores, qi)
+        ctx.fr_select_topk(scores, L, take, nq, again)
+        torch.cuda.synchronize()
+        assert H.max_rel_err(scores.cpu().numpy().astype(np.float64), want) <= 1e-4
+        assert np.array_equal(qi.cpu().numpy(), again.cpu().numpy())
+        ctx.fr_score_select(q, nq, kd, w.chunk_offsets, take, B.FR_NORM_PER_CHUNK, None, again)
+        assert np.array_equal(qi.cpu().numpy(), again.cpu().numpy())
+    ctx.close()
