@@ -493,9 +493,7 @@ fr_status fr_score_select_shared(fr_ctx* ctx, const void* q_question, int32_t nq
         if (nq == 0) {   // no question rows: every score is an empty sum (the generic kernel writes the zeros; no key is read)
             e = launch_score_simt(s, q_question, 0, k_store, L_ctx, scores, hs);
         } else {
-            e = launch_rope_table(s, dl, n_chunks, ctx->ws.rope_theta, ctx->ws.rope_table, hs);
-            if (e != hipSuccess) return hip_fail(ctx, "rope table launch", e);
-            e = launch_score(s, q_question, nq, k_store, ct, norm, ctx->ws, scores, chunk_store_row0, ctx->ws.rope_table, &select, hs);
+            e = launch_score(s, q_question, nq, k_store, ct, norm, ctx->ws, scores, chunk_store_row0, &dl, &select, hs);
         }
         if (e != hipSuccess) return hip_fail(ctx, "score launch", e);
     }

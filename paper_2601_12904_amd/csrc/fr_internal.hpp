@@ -136,7 +136,7 @@ struct SelectAfter {
     bool done;
 };
 hipError_t launch_score(const Shape& s, const void* q, int nq, const void* k, const ChunkTable& ct, int norm,
-                        const Workspace& ws, float* scores, const int32_t* store_row0, const float2* table, SelectAfter* select, hipStream_t st);
+                        const Workspace& ws, float* scores, const int32_t* store_row0, const ChunkDeltas* deltas, SelectAfter* select, hipStream_t st);
 // scores[j] = sum of n_parts partial sums [n_parts][n], and the selection from them, in one launch (short prompts).  0 <= k <= n.
 bool sum_and_select_pays(int64_t n, int n_parts);
 hipError_t launch_sum_and_select(const float* partial, int n_parts, int n, float* scores, int k, int nq, int32_t* q_index, hipStream_t st);

@@ -17,10 +17,10 @@ __device__ __forceinline__ float2 chunk_rotation(int32_t delta, double theta) {
 
 typedef __attribute__((ext_vector_type(4))) uint32_t rot_u32x4;
 
-// own = elements N vec .. N vec + N - 1 of the head row (N = 16 / sizeof(T)).  Interleaved pairs: (2p, 2p + 1) inside the
-// vector.  Half-split pairs: (p, p + D/2): `partner` is the vector D/2 elements away.
-template <typename T, int D, int LAYOUT>
-__device__ __forceinline__ rot_u32x4 rotate_key_vector(rot_u32x4 own, rot_u32x4 partner, const float2* __restrict__ trow, int vec) {
+// own = elements N vec .. N vec + N - 1 of the head row (N = 16 / sizeof(T)), `t` their rotations: interleaved pairs (2p, 2p + 1) inside the
+// vector have N / 2, half-split pairs (p, p + D/2), whose `partner` is the vector D/2 elements away, N; low: own holds the first elements of its pairs.
+template <typename T, int LAYOUT>
+__device__ __forceinline__ rot_u32x4 rotate_vector(rot_u32x4 own, rot_u32x4 partner, const float2* t, bool low) {
     constexpr int N = 16 / sizeof(T);
     struct alignas(16) V { T v[N]; };
     const V mine = __builtin_bit_cast(V, own), other = __builtin_bit_cast(V, partner);
@@ -28,22 +28,28 @@ __device__ __forceinline__ rot_u32x4 rotate_key_vector(rot_u32x4 own, rot_u32x4 
     if (LAYOUT == FR_ROPE_INTERLEAVED) {
 #pragma unroll
         for (int e = 0; e < N / 2; ++e) {
-            const float2 t = trow[(N / 2) * vec + e];
             const float a = Elem<T>::to_f32(mine.v[2 * e]), b = Elem<T>::to_f32(mine.v[2 * e + 1]);
-            y.v[2 * e] = Elem<T>::from_f32(a * t.x - b * t.y);
-            y.v[2 * e + 1] = Elem<T>::from_f32(b * t.x + a * t.y);
+            y.v[2 * e] = Elem<T>::from_f32(a * t[e].x - b * t[e].y);
+            y.v[2 * e + 1] = Elem<T>::from_f32(b * t[e].x + a * t[e].y);
         }
     } else {
-        const bool low = vec < D / (2 * N);   // this vector holds the first elements of its pairs
 #pragma unroll
         for (int e = 0; e < N; ++e) {
-            const float2 t = trow[(N * vec + e) & (D / 2 - 1)];
             const float m = Elem<T>::to_f32(mine.v[e]), o = Elem<T>::to_f32(other.v[e]);
             const float a = low ? m : o, b = low ? o : m;
-            y.v[e] = low ? Elem<T>::from_f32(a * t.x - b * t.y) : Elem<T>::from_f32(b * t.x + a * t.y);
+            y.v[e] = low ? Elem<T>::from_f32(a * t[e].x - b * t[e].y) : Elem<T>::from_f32(b * t[e].x + a * t[e].y);
         }
     }
     return __builtin_bit_cast(rot_u32x4, y);
+}
+// The same with the rotations of the head row in memory.
+template <typename T, int D, int LAYOUT>
+__device__ __forceinline__ rot_u32x4 rotate_key_vector(rot_u32x4 own, rot_u32x4 partner, const float2* __restrict__ trow, int vec) {
+    constexpr int N = 16 / sizeof(T), M = LAYOUT == FR_ROPE_INTERLEAVED ? N / 2 : N;
+    float2 t[M];
+#pragma unroll
+    for (int e = 0; e < M; ++e) t[e] = trow[(M * vec + e) & (D / 2 - 1)];
+    return rotate_vector<T, LAYOUT>(own, partner, t, vec < D / (2 * N));
 }
 
 }  // namespace fr

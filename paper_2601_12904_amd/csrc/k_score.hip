@@ -86,7 +86,7 @@ struct Op {
 struct ScoreArgs {
     const void* q;
     const void* k;
-    const float2* table;      // (cos, sin) rows of the chunks, stores only
+    const double* theta;      // [D / 2] rotary frequencies, stores only
     float* lse2;              // [Hkv][lse_rows][col_end - col0] base-2 normalisers of the two-pass modes
     float* partial;           // [n_split][Hkv][L_ctx]
     int col0, col_end;        // the launch's query columns
@@ -95,6 +95,7 @@ struct ScoreArgs {
     float scale_log2e;
     ChunkTable ct;
     ChunkRows rows;
+    ChunkDeltas deltas;       // stores only
     uint8_t order[FR_MAX_CHUNKS];   // chunks, longest first
 };
 
@@ -163,6 +164,7 @@ struct Smem {
     alignas(1024) unsigned char q[2][TILE * Op<T, D>::ROWB];
     float ref[MAX_COLS + 32];      // exponent references, or the given normalisers (and room for those of a step too many)
     alignas(16) float l[2][32][WAVES];
+    float2 rotation[D / 2];        // of the chunk's keys, stores only
     alignas(1024) unsigned char stage[WAVES][Op<T, D>::STAGED * 16 * Op<T, D>::ROWB];   // key blocks on their way into registers
 };
 
@@ -227,41 +229,60 @@ __device__ __forceinline__ void walk_columns(const ScoreArgs& a, Smem<T, D, WAVE
         static_assert(COPIES * (O::STAGED - 1) <= 10 && COPIES % 2 == 0, "wait_copies_but");
 #pragma unroll
         for (int b = 0; b < O::STAGED && b < NB; ++b) copy_block(b);
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            asm volatile("" ::: "memory");
-            wait_copies_but(COPIES * min(NB - 1 - b, O::STAGED - 1));   // the later blocks'
-            asm volatile("" ::: "memory");
-            const unsigned char* row = sm.stage[wave] + (b % O::STAGED) * BLOCK;
-#pragma unroll
-            for (int j = 0; j < NJ; ++j) kf[b][j] = *reinterpret_cast<const u32x4*>(row + ((x * O::ROWB + 16 * (kg ^ O::swz(x))) ^ (64 * j)));
-            if (b + O::STAGED < NB) {
-                __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): the slot has been read
-                copy_block(b + O::STAGED);
-            }
-        }
-    }
-    if (a.src != SRC_PROMPT) {   // moved to their prompt positions
-        const float2* trow = a.table + (size_t)c * (D / 2);
-        if (a.src == SRC_STORE_INTERLEAVED) {
+        auto load_blocks = [&](auto rotate) __attribute__((always_inline)) {
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
+                asm volatile("" ::: "memory");
+                wait_copies_but(COPIES * min(NB - 1 - b, O::STAGED - 1));   // the later blocks'
+                asm volatile("" ::: "memory");
+                const unsigned char* row = sm.stage[wave] + (b % O::STAGED) * BLOCK;
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) kf[b][j] = *reinterpret_cast<const u32x4*>(row + ((x * O::ROWB + 16 * (kg ^ O::swz(x))) ^ (64 * j)));
+                if (b + O::STAGED < NB) {
+                    __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): the slot has been read
+                    copy_block(b + O::STAGED);
+                }
+                rotate(b);
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) asm volatile("" : "+v"(kf[b][j]));   // rounded here: the compiler moves what the layouts' paths end
+                __builtin_amdgcn_sched_barrier(0);                                // with behind them, with twice the registers
+            }
+        };
+        // From a store: moved to their prompt positions on the way.  A lane meets the same NJ vectors of every key row, so their rotations, which the
+        // workgroup forms itself, stay in its registers meanwhile.  Selection call, 28 query heads on 4 KV heads of 128 in bf16: 16 chunks of 1024 keys and
+        // 512 question tokens 95.1 -> 80.4 us (from a prompt 80.3), 3 of 900 and 100 28.7 -> 19.3 (14.9), against a table in memory, which took a launch of
+        // its own, and the rotations loaded from it block by block after all keys.
+        if (a.src == SRC_PROMPT) {
+            load_blocks([](int) __attribute__((always_inline)) {});
+        } else {
+            constexpr int N = 16 / (int)sizeof(T);
+            if (tid < D / 2) sm.rotation[tid] = chunk_rotation(a.deltas.delta[c], a.theta[tid]);
+            __syncthreads();
+            if (a.src == SRC_STORE_INTERLEAVED) {
+                float2 t[NJ][N / 2];
 #pragma unroll
                 for (int j = 0; j < NJ; ++j)
-                    kf[b][j] = rotate_key_vector<T, D, FR_ROPE_INTERLEAVED>(kf[b][j], kf[b][j], trow, 4 * j + kg);
-                __builtin_amdgcn_sched_barrier(0);   // block by block: the registers are taken
-            }
-        } else {   // (p, p + D/2): the partner of vector 4 j + kg is vector 4 (j ^ NJ / 2) + kg of the same lane
-            static_assert(NJ % 2 == 0, "pairs inside a lane");
 #pragma unroll
-            for (int b = 0; b < NB; ++b) {
+                    for (int e = 0; e < N / 2; ++e) t[j][e] = sm.rotation[N / 2 * (4 * j + kg) + e];
+                load_blocks([&](int b) __attribute__((always_inline)) {
 #pragma unroll
-                for (int j = 0; j < NJ / 2; ++j) {
-                    const u32x4 lo = kf[b][j], hi = kf[b][j + NJ / 2];
-                    kf[b][j] = rotate_key_vector<T, D, FR_ROPE_HALF>(lo, hi, trow, 4 * j + kg);
-                    kf[b][j + NJ / 2] = rotate_key_vector<T, D, FR_ROPE_HALF>(hi, lo, trow, 4 * (j + NJ / 2) + kg);
-                }
-                __builtin_amdgcn_sched_barrier(0);
+                    for (int j = 0; j < NJ; ++j) kf[b][j] = rotate_vector<T, FR_ROPE_INTERLEAVED>(kf[b][j], kf[b][j], t[j], false);
+                });
+            } else {   // (p, p + D/2): the partner of vector 4 j + kg is vector 4 (j + NJ / 2) + kg of the same lane
+                static_assert(NJ % 2 == 0, "pairs inside a lane");
+                float2 t[NJ / 2][N];
+#pragma unroll
+                for (int j = 0; j < NJ / 2; ++j)
+#pragma unroll
+                    for (int e = 0; e < N; ++e) t[j][e] = sm.rotation[N * (4 * j + kg) + e];
+                load_blocks([&](int b) __attribute__((always_inline)) {
+#pragma unroll
+                    for (int j = 0; j < NJ / 2; ++j) {
+                        const u32x4 lo = kf[b][j], hi = kf[b][j + NJ / 2];
+                        kf[b][j] = rotate_vector<T, FR_ROPE_HALF>(lo, hi, t[j], true);
+                        kf[b][j + NJ / 2] = rotate_vector<T, FR_ROPE_HALF>(hi, lo, t[j], false);
+                    }
+                });
             }
         }
     }
@@ -621,17 +642,18 @@ constexpr bool FEW_WAVES = D * sizeof(T) <= 256;   // two workgroups' LDS fits a
 
 template <typename T, int D>
 hipError_t run(const Shape& s, const void* q, int nq, const void* k, const ChunkTable& ct, int norm, const Workspace& ws,
-               float* scores, int src, const int32_t* store_row0, const float2* table, SelectAfter* select, hipStream_t st) {
+               float* scores, int src, const int32_t* store_row0, const ChunkDeltas* deltas, SelectAfter* select, hipStream_t st) {
     using O = Op<T, D>;
     const int L_ctx = ct.off[ct.n], NQG = nq * s.G;
     ScoreArgs a;
-    a.q = q; a.k = k; a.table = table; a.lse2 = ws.lse; a.partial = ws.col_partial;
+    a.q = q; a.k = k; a.theta = ws.rope_theta; a.lse2 = ws.lse; a.partial = ws.col_partial;
     a.nq = nq; a.Hq = s.Hq; a.Hkv = s.Hkv; a.G = s.G;
     a.src = src;
     a.global_scope = norm == FR_NORM_GLOBAL;
     a.magic = (uint32_t)((((uint64_t)1 << 32) + s.G - 1) / s.G);
     a.scale_log2e = (1.0f / sqrtf((float)s.d)) * 1.4426950408889634f;
     a.ct = ct;
+    if (deltas) a.deltas = *deltas;
     int n = 0, max_len = 0, min_parts = INT32_MAX;   // non-empty chunks, longest first
     for (int c = 0; c < ct.n; ++c) {
         a.rows.row0[c] = store_row0 ? store_row0[c] : 0;
@@ -720,23 +742,28 @@ int score_column_ranges(const Shape& s, int64_t max_tokens, int max_q) {
 //
 // Softmax scopes only; FR_NORM_RAW has kernels of its own.  store_row0 != NULL (host): k is a chunk store that is never
 // written; chunk c occupies its rows store_row0[c] .., and its keys are moved to their prompt positions while they are
-// loaded (`table`: device, [chunks][d / 2]).
+// loaded (`deltas`: host, positions per chunk).
 hipError_t launch_score(const Shape& s, const void* q, int nq, const void* k, const ChunkTable& ct, int norm,
-                        const Workspace& ws, float* scores, const int32_t* store_row0, const float2* table, SelectAfter* select, hipStream_t st) {
+                        const Workspace& ws, float* scores, const int32_t* store_row0, const ChunkDeltas* deltas, SelectAfter* select, hipStream_t st) {
     select->done = false;
     if (ct.off[ct.n] == 0 || nq == 0) return hipSuccess;
     if (score_two_pass_supported(s)) {
         int max_len = 0;
         for (int c = 0; c < ct.n; ++c) max_len = std::max(max_len, ct.off[c + 1] - ct.off[c]);
-        if (norm == FR_NORM_GLOBAL || max_len > Op<__bf16, 128>::SEG)
-            return launch_score_two_pass(s, q, nq, k, ct, norm, ws, scores, store_row0, table, st);
+        if (norm == FR_NORM_GLOBAL || max_len > Op<__bf16, 128>::SEG) {
+            if (store_row0) {
+                const hipError_t e = launch_rope_table(s, *deltas, ct.n, ws.rope_theta, ws.rope_table, st);
+                if (e != hipSuccess) return e;
+            }
+            return launch_score_two_pass(s, q, nq, k, ct, norm, ws, scores, store_row0, ws.rope_table, st);
+        }
     }
     const int src = !store_row0 ? SRC_PROMPT : s.rope_layout == FR_ROPE_INTERLEAVED ? SRC_STORE_INTERLEAVED : SRC_STORE_HALF;
     if (s.dtype == FR_BF16)
-        return s.d == 64 ? run<__bf16, 64>(s, q, nq, k, ct, norm, ws, scores, src, store_row0, table, select, st)
-                         : run<__bf16, 128>(s, q, nq, k, ct, norm, ws, scores, src, store_row0, table, select, st);
-    return s.d == 64 ? run<float, 64>(s, q, nq, k, ct, norm, ws, scores, src, store_row0, table, select, st)
-                     : run<float, 128>(s, q, nq, k, ct, norm, ws, scores, src, store_row0, table, select, st);
+        return s.d == 64 ? run<__bf16, 64>(s, q, nq, k, ct, norm, ws, scores, src, store_row0, deltas, select, st)
+                         : run<__bf16, 128>(s, q, nq, k, ct, norm, ws, scores, src, store_row0, deltas, select, st);
+    return s.d == 64 ? run<float, 64>(s, q, nq, k, ct, norm, ws, scores, src, store_row0, deltas, select, st)
+                     : run<float, 128>(s, q, nq, k, ct, norm, ws, scores, src, store_row0, deltas, select, st);
 }
 
 }  // namespace fr

@@ -227,6 +227,34 @@ def test_scores_of_chunks_for_four_waves(Hq, Hkv, d, dt, nq, longest):
     test_scores(Hq, Hkv, d, dt, nq, (1, 64, 65, 130, 255, 300, 449, longest), B.FR_NORM_PER_CHUNK)
 
 
+# The keys of a store are rotated to their prompt positions on the way into the registers: the scores are those of the shifted prompt, within what test_scores
+# derives for bf16 and twice the tolerance of one side in f32.  Both layouts, one to eight key blocks per wave, rows of the store in any order, distances of both signs.
+@pytest.mark.parametrize("layout", [B.FR_ROPE_HALF, B.FR_ROPE_INTERLEAVED])
+@pytest.mark.parametrize("Hq,Hkv,d,dt,nq", [(7, 1, 128, "bf16", 33), (6, 2, 64, "bf16", 11), (4, 4, 64, "f32", 31), (6, 2, 128, "f32", 17), (28, 4, 128, "bf16", 170)])
+def test_scores_of_a_store_are_those_of_the_shifted_prompt(Hq, Hkv, d, dt, nq, layout):
+    lens = (1, 64, 130, 255, 300, 449, 512) if nq == 170 else (128, 129, 400, 512) + ((640, 769, 1024) if (d, dt) != (128, "f32") else ())
+    shape = synth.LayerShape(n_q_heads=Hq, n_kv_heads=Hkv, head_dim=d, dtype=dt, rope_base=10000.0)
+    w = synth.config_small_bf16(seed=4, chunk_lens=lens, nq=nq, shape=shape)
+    ctx = H.make_ctx(shape, w.L, w.n_chunks, w.nq, rope_layout=layout)
+    offs = np.asarray(w.chunk_offsets)
+    src_pos = np.asarray([(0, 3, 5000, 70000)[c % 4] for c in range(len(lens))], np.int32)
+    row0, at = np.zeros(len(lens), np.int32), 5
+    for c in reversed(range(len(lens))):   # the store holds them last chunk first, with gaps of 5 rows
+        row0[c], at = at, at + lens[c] + 5
+    store = np.zeros((at, Hkv, d), np.float32)
+    for c in range(len(lens)):
+        store[row0[c]:row0[c] + lens[c]] = w.k_cached[offs[c]:offs[c + 1]]
+    q, prompt = H.dev(w.q_question, dt), H.dev(w.k_cached, dt)
+    ctx.fr_rope_shift(prompt, prompt, w.chunk_offsets, src_pos)
+    got = [torch.full((w.L_ctx,), -7.0, dtype=torch.float32, device="cuda") for _ in range(2)]
+    qi = torch.zeros(w.nq, dtype=torch.int32, device="cuda")
+    ctx.fr_score_select(q, w.nq, prompt, w.chunk_offsets, 0, B.FR_NORM_PER_CHUNK, got[0], qi)
+    ctx.fr_score_select_shared(q, w.nq, H.dev(store, dt), at, w.chunk_offsets, row0, src_pos, 0, B.FR_NORM_PER_CHUNK, got[1], qi)
+    torch.cuda.synchronize()
+    assert H.max_rel_err(got[1].cpu().numpy(), got[0].cpu().numpy()) <= (5e-3 if dt == "bf16" else 2 * SCORE_TOL)
+    ctx.close()
+
+
 @pytest.mark.parametrize("norm", [B.FR_NORM_PER_CHUNK, B.FR_NORM_GLOBAL])
 def test_scores_of_more_columns_than_the_workspace_holds(norm):
     """A context of two million tokens holds the partial sums of 4096 query columns and the normalisers of 2048 at a time: 4400
