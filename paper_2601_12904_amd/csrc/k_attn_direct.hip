@@ -17,8 +17,8 @@
 // fragment wants 16 rows x 64 bytes per instruction with neighbouring lanes in different rows, which the vector cache serves at 16 bytes
 // a cycle (40 accesses per KB measured over keys and values, 16 with rows side by side): 45 rows of 920 positions 13.6 us, through LDS 9.4.
 //
-// us a call, three launches : this kernel.  32 / 8 heads, head_dim 128: 54 rows of 272 positions 19.7 : 6.4, 84 of 450 22.5 : 7.3, 172 of 920
-// 25.7 : 12.7, 244 of 1300 28.4 : 15.0, 167 of 3400 37 : 27; 28 / 4 heads: 172 of 920 31 : 12.7; 16 / 8 heads, head_dim 64: 172 of 920 21.8 : 7.2.
+// us a call, three launches : this kernel.  32 / 8 heads, head_dim 128: 54 rows of 272 positions 19.8 : 7.0, 84 of 450 22.4 : 7.5, 172 of 920
+// 26.0 : 13.5, 244 of 1300 29.2 : 16.0, 167 of 3400 37.7 : 27.0; 28 / 4 heads: 172 of 920 31.4 : 15.3; 16 / 8 heads, head_dim 64: 172 of 920 21.7 : 7.6.
 // A round of eight blocks takes 1.1 us with 16 columns, 1.5 with 32 (issue of the vector instructions: addresses, softmax, permutes).
 //
 // Softmax.  As in the tiled kernel the exponent reference of a column is the maximum over its visible ones of keys 0..31; wave 0 passes it on before the

@@ -11,11 +11,8 @@
 // most exponent bits agree), which would pile a plain histogram onto one or two bins; the digits are therefore
 // taken from key - min(key), starting at the highest bit in which the largest and the smallest key differ.  Even so most scores lie near the smallest
 // one: with 256 bins the adds of a wave queued up behind one LDS word, and every pass costs its barriers and scans (four
-// passes of 8 bits: 9.6 / 19.5 / 33.0 us at 880 / 16384 / 32768 scores of a prompt, now 8.1 / 14.7 / 25.2 in this kernel; up to 1024 scores take the one-wave kernel below; taking all
-// of 16384, without any search, is 8.1).
+// passes of 8 bits: 9.6 / 19.5 / 33.0 us at 880 / 16384 / 32768 scores of a prompt, with this 8.1 / 14.7 / 25.2; what else was taken out stands at select_in_workgroup).
 #include "fr_internal.hpp"
-
-#include <algorithm>
 
 namespace fr {
 
@@ -31,9 +28,28 @@ constexpr int DIGIT = 12;
 constexpr uint32_t CANDIDATES = 256;
 static_assert(BINS == 1 << DIGIT, "digit");
 
+template <int CTRL>
+__device__ __forceinline__ uint32_t moved(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true); }
+
+// Over four (quad) and sixteen (row) neighbouring lanes, in every one of them.
+template <typename F>
+__device__ __forceinline__ uint32_t over_quad(uint32_t v, F f) {
+    v = f(v, moved<0xB1>(v));        // quad_perm [1,0,3,2]
+    return f(v, moved<0x4E>(v));     // quad_perm [2,3,0,1]
+}
+template <typename F>
+__device__ __forceinline__ uint32_t over_row(uint32_t v, F f) {
+    v = over_quad(v, f);
+    v = f(v, moved<0x141>(v));       // row_half_mirror: the other quad of eight
+    return f(v, moved<0x140>(v));    // row_mirror: the other eight
+}
+__device__ __forceinline__ uint32_t add(uint32_t a, uint32_t b) { return a + b; }
+__device__ __forceinline__ uint32_t lower(uint32_t a, uint32_t b) { return min(a, b); }
+__device__ __forceinline__ uint32_t higher(uint32_t a, uint32_t b) { return max(a, b); }
+
 // Among the candidates of this pass (keys that share the digits fixed so far), the digit of the k-th largest
 // key is the largest d whose suffix count S[d] = sum_{b >= d} hist[b] still reaches `remaining`.  Four bins
-// per thread: suffix sums by wave shuffles, then the single thread that holds the matching bin publishes it.
+// per thread: suffix sums by lane moves, then the single thread that holds the matching bin publishes it.
 // `remaining` is read before the first barrier: between the two barriers the matching thread overwrites it, and the
 // waves do not run in lockstep, so a read behind the first barrier could see the reduced value and let a
 // second bin match.  (The caller's barrier after the histogram orders this read behind the previous pass's write.)
@@ -44,13 +60,16 @@ __device__ __forceinline__ void pick_digit(const uint32_t* hist, uint32_t* wave_
     const uint4 own = reinterpret_cast<const uint4*>(hist)[tid];
     uint32_t suf = own.x + own.y + own.z + own.w;
     const uint32_t mine = suf;
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t t = __shfl_down(suf, o);
-        if (lane + o < 64) suf += t;
-    }
+    suf += moved<0x101>(suf);   // row_shl: the lanes above in the row, zero behind its end
+    suf += moved<0x102>(suf);
+    suf += moved<0x104>(suf);
+    suf += moved<0x108>(suf);
+    const uint32_t row1 = __builtin_amdgcn_readlane(suf, 16), row2 = __builtin_amdgcn_readlane(suf, 32), row3 = __builtin_amdgcn_readlane(suf, 48);
+    suf += (lane < 16 ? row1 : 0u) + (lane < 32 ? row2 : 0u) + (lane < 48 ? row3 : 0u);
     if (lane == 0) wave_tot[wave] = suf;   // total of the wave's 256 bins
     __syncthreads();
-    for (int w2 = wave + 1; w2 < SEL_THREADS / 64; ++w2) suf += wave_tot[w2];
+    const int w2 = lane & (SEL_THREADS / 64 - 1);
+    suf += over_row(w2 > wave ? wave_tot[w2] : 0u, add);
     uint32_t above = suf - mine;           // candidates with a larger digit than any of this thread's
     if (suf >= remaining && above < remaining) {
         const uint32_t bins[4] = {own.x, own.y, own.z, own.w};
@@ -67,17 +86,14 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t ballot) {   // set bits
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(ballot >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)ballot, 0u));
 }
 
-__device__ __forceinline__ uint32_t quad_sum(uint32_t v) {   // over four neighbouring lanes
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);    // quad_perm [1,0,3,2]
-    return v + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);   // quad_perm [2,3,0,1]
-}
-
-// Wave w owns the contiguous index range [w * 64 * per, (w + 1) * 64 * per); its i-th load covers the 64
-// consecutive tokens base + 64 i + lane, so loads and stores are coalesced and (i, lane) order is index order.
-// Every thread keeps its PER keys in registers (n <= SEL_THREADS * PER).
+// Wave w owns the contiguous index range [w * 64 * PER, (w + 1) * 64 * PER); its i-th load covers the 256
+// consecutive tokens base + 256 i + 4 lane .. + 3, so (i, lane, e) order is index order (one CU's loads of 4 bytes a lane come at a quarter of the rate).  A
+// lane whose four tokens pass the end loads the last four, of which those before its own are another lane's.
+// Every thread keeps its PER keys in registers (1 <= n <= SEL_THREADS * PER, k >= 1; all threads of the workgroup).
+// Against loads of one score, reductions and scans by LDS permutes and the waves' totals read one after the other: 16384 scores 12.8 -> 9.8 us, 32768 23.3 -> 18.1, 4000 8.4 -> 4.7.
+// (A launch of one wave, as select_in_wave below, 4.6 to 10 us at 128 to 1024 scores, 15 with ties; this one 4.5.)
 template <int PER>
-__global__ __launch_bounds__(SEL_THREADS) void select_topk_kernel(const float* __restrict__ scores, int64_t n,
-                                                                  int64_t k, int nq, int32_t* __restrict__ out) {
+__device__ __forceinline__ void select_in_workgroup(const float* scores, int n, int64_t k, int32_t* __restrict__ out) {
     constexpr int WAVES = SEL_THREADS / 64;
     __shared__ __attribute__((aligned(16))) uint32_t hist[BINS];
     __shared__ uint32_t wave_a[WAVES], wave_b[WAVES];
@@ -86,20 +102,24 @@ __global__ __launch_bounds__(SEL_THREADS) void select_topk_kernel(const float* _
     __shared__ uint32_t s_prefix, s_remaining, s_count, s_listed;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 
-    // question tokens: positions n .. n + nq - 1
-    for (int i = tid; i < nq; i += SEL_THREADS) out[k + i] = (int32_t)(n + i);
-    if (k <= 0 || n <= 0) return;
-
-    const int64_t first = (int64_t)wave * 64 * PER + lane;     // this lane's tokens: first + 64 i
-    const int cnt = (int)max((int64_t)0, min((int64_t)PER, (n - first + 63) / 64));
+    constexpr int QUADS = PER / 4;
+    const int last = n - 4;
+    auto quad = [&](int i) { return wave * 64 * PER + 256 * i + 4 * lane; };
+    auto own = [&](int i) { return (i & 3) >= quad(i >> 2) - last; };   // key i: token min(quad(i / 4), last) + i % 4
     uint32_t keys[PER];
     {
-        // branch-free: every load is issued (index clamped into the array) before the first one is waited for
-        float raw[PER];
+        // branch-free: every load is issued before the first one is waited for
+        typedef __attribute__((ext_vector_type(4), aligned(4))) float f32x4_any;
+        f32x4_any raw[QUADS];
+        if (n >= 4) {
 #pragma unroll
-        for (int i = 0; i < PER; ++i) raw[i] = scores[min(first + 64 * i, n - 1)];
+            for (int i = 0; i < QUADS; ++i) raw[i] = *reinterpret_cast<const f32x4_any*>(scores + min(quad(i), last));
+        } else {
 #pragma unroll
-        for (int i = 0; i < PER; ++i) keys[i] = (i < cnt) ? score_key(raw[i]) : 0u;
+            for (int i = 0; i < QUADS; ++i) raw[i] = f32x4_any{0.f, scores[max(n - 3, 0)], scores[max(n - 2, 0)], scores[n - 1]};   // tokens n - 4 .. n - 1
+        }
+#pragma unroll
+        for (int i = 0; i < PER; ++i) keys[i] = own(i) ? score_key(raw[i >> 2][i & 3]) : 0u;
     }
 
     uint32_t thr_key = 0u;     // key of the k-th largest score
@@ -109,9 +129,13 @@ __global__ __launch_bounds__(SEL_THREADS) void select_topk_kernel(const float* _
         // range of the keys: block-wide minimum and maximum
         uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
 #pragma unroll
-        for (int i = 0; i < PER; ++i)
-            if (i < cnt) { kmin = min(kmin, keys[i]); kmax = max(kmax, keys[i]); }
-        for (int o = 32; o > 0; o >>= 1) {
+        for (int i = 0; i < PER; ++i) {
+            kmin = min(kmin, own(i) ? keys[i] : 0xFFFFFFFFu);
+            kmax = max(kmax, keys[i]);   // (another lane's: 0)
+        }
+        kmin = over_row(kmin, lower);
+        kmax = over_row(kmax, higher);
+        for (int o = 32; o >= 16; o >>= 1) {
             kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, o));
             kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, o));
         }
@@ -119,9 +143,8 @@ __global__ __launch_bounds__(SEL_THREADS) void select_topk_kernel(const float* _
         if (tid == 0) { s_prefix = 0u; s_remaining = (uint32_t)k; s_listed = 0u; }
         reinterpret_cast<uint4*>(hist)[tid] = make_uint4(0u, 0u, 0u, 0u);
         __syncthreads();
-        kmin = wave_a[0];
-        kmax = wave_b[0];
-        for (int w2 = 1; w2 < WAVES; ++w2) { kmin = min(kmin, wave_a[w2]); kmax = max(kmax, wave_b[w2]); }
+        kmin = __builtin_amdgcn_readfirstlane(over_row(wave_a[lane & (WAVES - 1)], lower));
+        kmax = __builtin_amdgcn_readfirstlane(over_row(wave_b[lane & (WAVES - 1)], higher));
         // relative keys rk = key - kmin lie in [0, kmax - kmin]; digits of 12 bits (the last one narrower) are taken
         // from the highest bit in which the two extremes differ downwards
         const uint32_t span = kmax - kmin;
@@ -135,7 +158,7 @@ __global__ __launch_bounds__(SEL_THREADS) void select_topk_kernel(const float* _
 #pragma unroll
             for (int i = 0; i < PER; ++i) {
                 const uint32_t rk = keys[i] - kmin;
-                if (i < cnt && (rk & mask) == prefix) atomicAdd(&hist[(rk >> shift) & digit_mask], 1u);
+                if (own(i) && (rk & mask) == prefix) atomicAdd(&hist[(rk >> shift) & digit_mask], 1u);
             }
             __syncthreads();
             pick_digit(hist, wave_tot, &s_prefix, &s_remaining, &s_count, shift);
@@ -149,27 +172,27 @@ __global__ __launch_bounds__(SEL_THREADS) void select_topk_kernel(const float* _
 #pragma unroll
             for (int i = 0; i < PER; ++i) {
                 const uint32_t rk = keys[i] - kmin;
-                if (i < cnt && (rk & mask) == prefix) candidates[atomicAdd(&s_listed, 1u)] = rk;
+                if (own(i) && (rk & mask) == prefix) candidates[atomicAdd(&s_listed, 1u)] = rk;
             }
             __syncthreads();
             // four threads per candidate, each counts in every fourth vector of the list (one thread each: 16 us instead of 12 for
             // 6196 scores of 50 different values, whose bins hold over a hundred)
             static_assert(4 * CANDIDATES <= SEL_THREADS, "candidates per pass");
-            const uint32_t own = candidates[min(tid >> 2, (int)count - 1)];
+            const uint32_t mine = candidates[min(tid >> 2, (int)count - 1)];
             uint32_t larger = 0u, equal = 0u;
             for (uint32_t j = 4 * (tid & 3); j < count; j += 16) {
                 const uint4 c = *reinterpret_cast<const uint4*>(&candidates[j]);   // entries past `count` do not count
                 const uint32_t v[4] = {c.x, c.y, c.z, c.w};
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    larger += (j + e < count && v[e] > own) ? 1u : 0u;
-                    equal += (j + e < count && v[e] == own) ? 1u : 0u;
+                    larger += (j + e < count && v[e] > mine) ? 1u : 0u;
+                    equal += (j + e < count && v[e] == mine) ? 1u : 0u;
                 }
             }
-            larger = quad_sum(larger);
-            equal = quad_sum(equal);
+            larger = over_quad(larger, add);
+            equal = over_quad(equal, add);
             if (larger < remaining && larger + equal >= remaining) {   // (every copy of the k-th largest key writes the same)
-                s_prefix = own;
+                s_prefix = mine;
                 s_remaining = remaining - larger;
             }
             __syncthreads();
@@ -179,44 +202,63 @@ __global__ __launch_bounds__(SEL_THREADS) void select_topk_kernel(const float* _
     }
 
     // ordered compaction: per-wave counts by ballots, one exchange of the 16 wave totals, then every wave
-    // writes its tokens in (i, lane) order
-    auto is_gt = [&](int i, uint32_t key) { return i < cnt && (take_all || key > thr_key); };
-    auto is_eq = [&](int i, uint32_t key) { return i < cnt && !take_all && key == thr_key; };
+    // writes its tokens in (i, lane, e) order
+    auto is_gt = [&](int i) { return own(i) && (take_all || keys[i] > thr_key); };
+    auto is_eq = [&](int i) { return own(i) && !take_all && keys[i] == thr_key; };
     uint32_t w_gt = 0u, w_eq = 0u;
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-        w_gt += (uint32_t)__popcll(__ballot(is_gt(i, keys[i])));
-        w_eq += (uint32_t)__popcll(__ballot(is_eq(i, keys[i])));
+        w_gt += (uint32_t)__popcll(__ballot(is_gt(i)));
+        w_eq += (uint32_t)__popcll(__ballot(is_eq(i)));
     }
     __syncthreads();   // wave_a / wave_b are free again
     if (lane == 0) { wave_a[wave] = w_gt; wave_b[wave] = w_eq; }
     __syncthreads();
-    uint32_t eq_seen = 0u, pos = 0u;   // equal keys and outputs of the waves before this one
-    for (int w2 = 0; w2 < wave; ++w2) {
-        const uint32_t e = wave_b[w2];
-        pos += wave_a[w2] + ((need_eq > eq_seen) ? min(e, need_eq - eq_seen) : 0u);
-        eq_seen += e;
-    }
-    auto emit = [&](int i, uint32_t key) {
-        const bool gt = is_gt(i, key), eq = is_eq(i, key);
-        const uint64_t beq = __ballot(eq);
-        const bool sel = gt || (eq && eq_seen + lanes_below(beq) < need_eq);
-        const uint64_t bsel = __ballot(sel);
-        if (sel) out[pos + lanes_below(bsel)] = (int32_t)(first + 64 * (int64_t)i);
-        pos += (uint32_t)__popcll(bsel);
-        eq_seen += (uint32_t)__popcll(beq);
-    };
+    // equal keys and outputs of the waves before this one (of equal keys the first need_eq are taken)
+    const int w2 = lane & (WAVES - 1);
+    uint32_t eq_seen = __builtin_amdgcn_readfirstlane(over_row(w2 < wave ? wave_b[w2] : 0u, add));
+    uint32_t pos = __builtin_amdgcn_readfirstlane(over_row(w2 < wave ? wave_a[w2] : 0u, add)) + min(eq_seen, need_eq);
 #pragma unroll
-    for (int i = 0; i < PER; ++i) emit(i, keys[i]);
+    for (int i = 0; i < QUADS; ++i) {
+        bool sel[4];
+        uint32_t eq_at = eq_seen, at = pos;    // equal keys, outputs before this lane's four
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint64_t beq = __ballot(is_eq(4 * i + e));
+            eq_at += lanes_below(beq);
+            eq_seen += (uint32_t)__popcll(beq);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const bool eq = is_eq(4 * i + e);
+            sel[e] = is_gt(4 * i + e) || (eq && eq_at < need_eq);
+            eq_at += eq ? 1u : 0u;
+            const uint64_t bsel = __ballot(sel[e]);
+            at += lanes_below(bsel);
+            pos += (uint32_t)__popcll(bsel);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if (sel[e]) out[at] = min(quad(i), last) + e;
+            at += sel[e] ? 1u : 0u;
+        }
+    }
+}
+
+template <int PER>
+__global__ __launch_bounds__(SEL_THREADS) void select_topk_kernel(const float* __restrict__ scores, int64_t n,
+                                                                  int64_t k, int nq, int32_t* __restrict__ out) {
+    // question tokens: positions n .. n + nq - 1
+    for (int i = threadIdx.x; i < nq; i += SEL_THREADS) out[k + i] = (int32_t)(n + i);
+    if (k <= 0 || n <= 0) return;   // (there need be no scores then)
+    select_in_workgroup<PER>(scores, (int)n, k, out);
 }
 
 // The same for n <= 64 PER scores in one wave: no histogram, no barrier, no LDS.  Token 64 i + lane is key i of the lane, so
 // (i, lane) order is index order.  The threshold key is found bit by bit from the highest one in which the keys differ: a bit
 // stays set if at least k keys reach it, counted by ballots (PER compares and scalar adds); as soon as exactly k keys reach the threshold, the set
 // is known (with n distinct scores after about log2(n) + 4 bits; ties go on to the last bit and take the lowest indices).  What bounds it is the one wave's
-// issue, 12 PER cycles a bit, against ten barriers of 16 waves above: 512 scores
-// 8.2 -> 3.1 us, 880 8.6 -> 6.6.  Beyond 1024 scores, 32 keys a lane, the wave takes longer than the workgroup: layers of 1623 and 1679
-// tokens 70.6 and 58.1 us with it, 66.7 and 54.1 without.
+// issue, 12 PER cycles a bit.
 template <int PER>
 __device__ __forceinline__ void select_in_wave(const float (&raw)[PER], int n, int k, int32_t* __restrict__ out) {
     const int lane = threadIdx.x & 63;
@@ -265,25 +307,13 @@ __device__ __forceinline__ void select_in_wave(const float (&raw)[PER], int n, i
     }
 }
 
-template <int PER>
-__global__ __launch_bounds__(64) void select_topk_wave_kernel(const float* __restrict__ scores, int n, int k, int nq,
-                                                              int32_t* __restrict__ out) {
-    const int lane = threadIdx.x;
-    for (int i = lane; i < nq; i += 64) out[k + i] = n + i;   // question tokens: positions n .. n + nq - 1
-    if (k <= 0) return;                                       // (there need be no scores then)
-    float raw[PER];
-#pragma unroll
-    for (int i = 0; i < PER; ++i) raw[i] = scores[min(64 * i + lane, n - 1)];
-    select_in_wave<PER>(raw, n, k, out);
-}
-
 // The scores' partial sums added up and selected from in one launch (score_reduce_kernel's sums in its order): a launch less for short prompts, whose calls are bound
 // by them on the device and on the host (4 x 128 tokens, 4 partial sums: the host's part of a selection call 13.0 -> 8.3 us).  Thread (quad of tokens, a): group w = a, a + 4, ..
-// of eight partial sums, 16 bytes a load (one token a thread is a quarter of a compute unit's load rate: 880 tokens, 40 partial sums 2 us more); then a token a thread;
-// then wave 0 selects.
+// of eight partial sums, 16 bytes a load (one token a thread is a quarter of a compute unit's load rate: 880 tokens, 40 partial sums 2 us more); then a token a thread; then
+// the selection, behind the sums by wave 0 alone up to 512 tokens (4 x 128 tokens 3.8 us, 5.2 by the workgroup), else by the workgroup (880 tokens 6.4 us, 8.4 by a wave).
 constexpr int SUM_GROUPS = 8;   // of eight partial sums at most
-template <int PER>
-__global__ __launch_bounds__(1024) void sum_and_select_kernel(const float* __restrict__ partial, int n_parts, int n, float* __restrict__ scores, int k,
+template <bool ONE_WAVE>
+__global__ __launch_bounds__(SEL_THREADS) void sum_and_select_kernel(const float* __restrict__ partial, int n_parts, int n, float* __restrict__ scores, int k,
                                                               int nq, int32_t* __restrict__ out) {
     typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
     typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -314,20 +344,25 @@ __global__ __launch_bounds__(1024) void sum_and_select_kernel(const float* __res
         sums[0][tid] = t;   // (this token's words are this thread's)
     }
     __syncthreads();
-    if (tid >= 64 || k <= 0) return;
-    float raw[PER];
+    if (k <= 0) return;
+    if constexpr (ONE_WAVE) {
+        if (tid >= 64) return;
+        float raw[8];
 #pragma unroll
-    for (int i = 0; i < PER; ++i) raw[i] = sums[0][min(64 * i + tid, n - 1)];
-    select_in_wave<PER>(raw, n, k, out);
+        for (int i = 0; i < 8; ++i) raw[i] = sums[0][min(64 * i + tid, n - 1)];
+        select_in_wave<8>(raw, n, k, out);
+    } else {
+        select_in_workgroup<4>(sums[0], n, k, out);
+    }
 }
 
 bool sum_and_select_pays(int64_t n, int n_parts) { return n > 0 && n <= 1024 && n_parts <= 8 * SUM_GROUPS; }
 
 hipError_t launch_sum_and_select(const float* partial, int n_parts, int n, float* scores, int k, int nq, int32_t* q_index, hipStream_t st) {
     if (n <= 512)
-        sum_and_select_kernel<8><<<dim3(1), dim3(1024), 0, st>>>(partial, n_parts, n, scores, k, nq, q_index);
+        sum_and_select_kernel<true><<<dim3(1), dim3(SEL_THREADS), 0, st>>>(partial, n_parts, n, scores, k, nq, q_index);
     else
-        sum_and_select_kernel<16><<<dim3(1), dim3(1024), 0, st>>>(partial, n_parts, n, scores, k, nq, q_index);
+        sum_and_select_kernel<false><<<dim3(1), dim3(SEL_THREADS), 0, st>>>(partial, n_parts, n, scores, k, nq, q_index);
     return hipGetLastError();
 }
 
@@ -336,15 +371,9 @@ static_assert(SELECT_ONE_WORKGROUP_MAX == (int64_t)SEL_THREADS * 32, "largest sc
 hipError_t launch_select(const float* scores, int64_t n, int64_t k, int nq, int32_t* q_index, uint32_t* tmp,
                          size_t tmp_bytes, hipStream_t st) {
     if (k + nq == 0) return hipSuccess;
-    if (n > 0 && n <= 1024) {
-        const int kk = (int)std::max<int64_t>(0, std::min(k, n));
-        if (n <= 512)
-            select_topk_wave_kernel<8><<<dim3(1), dim3(64), 0, st>>>(scores, (int)n, kk, nq, q_index);
-        else
-            select_topk_wave_kernel<16><<<dim3(1), dim3(64), 0, st>>>(scores, (int)n, kk, nq, q_index);
-        return hipGetLastError();
-    }
-    if (n <= (int64_t)SEL_THREADS * 8)
+    if (n <= (int64_t)SEL_THREADS * 4)
+        select_topk_kernel<4><<<dim3(1), dim3(SEL_THREADS), 0, st>>>(scores, n, k, nq, q_index);
+    else if (n <= (int64_t)SEL_THREADS * 8)
         select_topk_kernel<8><<<dim3(1), dim3(SEL_THREADS), 0, st>>>(scores, n, k, nq, q_index);
     else if (n <= (int64_t)SEL_THREADS * 16)
         select_topk_kernel<16><<<dim3(1), dim3(SEL_THREADS), 0, st>>>(scores, n, k, nq, q_index);

@@ -220,6 +220,23 @@ def test_select_topk_exact(n, k, nq):
     ctx.close()
 
 
+# The one-workgroup kernel loads four scores at a time: every remainder of four at the ends of its four sizes, of a wave's range and of a load of 256,
+# scores at every 4-byte address, few values (ties across lanes) and many.
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 255, 257, 1023, 1025, 1026, 1027, 1279, 4095, 4096, 4097, 8189, 8190, 8192, 8193, 16381, 16384, 16387, 32765, 32766, 32767, 32768])
+def test_select_topk_of_any_remainder_and_address(n):
+    ctx = H.make_ctx(synth.TINY_F32, 70000, 4, 600)
+    rng = np.random.default_rng(n)
+    for at in range(4):
+        s = rng.integers(0, 5, size=n).astype(np.float32) if at % 2 else rng.standard_normal(n).astype(np.float32)
+        held = torch.full((n + 8,), 1.0e30, dtype=torch.float32, device="cuda")     # (no neighbour may be taken)
+        held[at:at + n] = torch.from_numpy(s).cuda()
+        for k in sorted({1, max(1, n // 7), max(1, n - 1), n}):
+            out = torch.full((k + 3,), -7, dtype=torch.int32, device="cuda")
+            ctx.fr_select_topk(held[at:], n, k, 3, out)
+            assert np.array_equal(out.cpu().numpy(), orc.select_q_index(s, k, 3)), (at, k)
+    ctx.close()
+
+
 @pytest.mark.parametrize("n,k,nq", [(32769, 4915, 3), (40000, 40000, 2), (33000, 1, 0), (40000, 0, 5), (300000, 45000, 9),
                                     (1 << 20, 157286, 0), (1234567, 1234, 1), (9000001, 1350000, 2)])
 def test_select_topk_many_workgroups(n, k, nq):
