@@ -40,12 +40,19 @@ class fr_layer_desc(ctypes.Structure):
                 ("rope_index_base", ctypes.c_int32)]
 
 
+def _shared_query_fields(arr):
+    """`arr`: type of the host int32 arrays."""
+    return [("q_rows", ctypes.c_void_p), ("q_index", ctypes.c_void_p), ("R", ctypes.c_int32), ("chunk_offsets", arr), ("chunk_store_row0", arr),
+            ("chunk_src_pos0", arr), ("n_chunks", ctypes.c_int32), ("L", ctypes.c_int64), ("k_new", ctypes.c_void_p), ("v_new", ctypes.c_void_p),
+            ("out", ctypes.c_void_p), ("lse_out", ctypes.c_void_p)]
+
+
 class fr_shared_query(ctypes.Structure):
-    _fields_ = [("q_rows", ctypes.c_void_p), ("q_index", ctypes.c_void_p), ("R", ctypes.c_int32),
-                ("chunk_offsets", ctypes.c_void_p), ("chunk_store_row0", ctypes.c_void_p),   # host int32 arrays
-                ("chunk_src_pos0", ctypes.c_void_p), ("n_chunks", ctypes.c_int32), ("L", ctypes.c_int64),
-                ("k_new", ctypes.c_void_p), ("v_new", ctypes.c_void_p), ("out", ctypes.c_void_p),
-                ("lse_out", ctypes.c_void_p)]
+    _fields_ = _shared_query_fields(ctypes.POINTER(ctypes.c_int32))
+
+
+class _shared_query_by_address(ctypes.Structure):
+    _fields_ = _shared_query_fields(ctypes.c_void_p)
 
 
 class FusionRAGError(RuntimeError):
@@ -54,21 +61,32 @@ class FusionRAGError(RuntimeError):
         self.status = status
 
 
-_lib = None
+_lib = _lib_by_address = None
 
 
 def load() -> ctypes.CDLL:
-    """Load libfusionrag.so (built in-tree by `python -m paper_2601_12904_amd.build`)."""
+    """Load libfusionrag.so (built in-tree by `python -m paper_2601_12904_amd.build`).  Host int32 arrays are pointers or arrays of c_int32."""
     global _lib
-    if _lib is not None:
-        return _lib
+    if _lib is None:
+        _lib = _open(ctypes.POINTER(ctypes.c_int32), fr_shared_query)
+    return _lib
+
+
+def _load_by_address() -> ctypes.CDLL:
+    """The same library for Context, which hands host int32 arrays over by address (_i32_array): a pointer object takes 0.5 us each."""
+    global _lib_by_address
+    if _lib_by_address is None:
+        _lib_by_address = _open(ctypes.c_void_p, _shared_query_by_address)
+    return _lib_by_address
+
+
+def _open(arr, shared_query) -> ctypes.CDLL:
+    """A handle of the library, its entry points declared with these types of host int32 arrays and shared-store queries."""
     if not os.path.exists(_LIB_PATH):
         raise ImportError(f"{_LIB_PATH} is missing: build it with `python -m paper_2601_12904_amd.build` "
                           "(there is no fallback path)")
     lib = ctypes.CDLL(_LIB_PATH)
     vp, i32, i64, f64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64, ctypes.c_double
-    pi32 = ctypes.POINTER(ctypes.c_int32)
-    arr = vp   # host int32 array, by address (_i32_array)
     lib.fr_create.argtypes = [ctypes.POINTER(fr_layer_desc), i64, i32, i32, ctypes.POINTER(vp)]
     lib.fr_create.restype = i32
     lib.fr_destroy.argtypes = [vp]
@@ -103,7 +121,7 @@ def load() -> ctypes.CDLL:
     lib.fr_sparse_prefill_attn_shared.restype = i32
     lib.fr_shared_batch_workspace_bytes.argtypes = [vp, i32, i64]
     lib.fr_shared_batch_workspace_bytes.restype = i64
-    lib.fr_sparse_prefill_attn_shared_batch.argtypes = [vp, ctypes.POINTER(fr_shared_query), i32, vp, vp, i64, vp, i64, vp]
+    lib.fr_sparse_prefill_attn_shared_batch.argtypes = [vp, ctypes.POINTER(shared_query), i32, vp, vp, i64, vp, i64, vp]
     lib.fr_sparse_prefill_attn_shared_batch.restype = i32
     lib.fr_decode_attn.argtypes = [vp, vp, i32, vp, vp, i64, vp, vp, vp, vp, i32, vp, i64, vp, vp, i64, vp, vp, vp, vp]
     lib.fr_decode_attn.restype = i32
@@ -119,7 +137,6 @@ def load() -> ctypes.CDLL:
     lib.fr_linear_swiglu.restype = i32
     lib.fr_qkv_rope.argtypes = [vp, vp, vp, i32, i32, vp, vp, vp, vp, vp]
     lib.fr_qkv_rope.restype = i32
-    _lib = lib
     return lib
 
 
@@ -179,7 +196,7 @@ class Context:
     def __init__(self, n_q_heads: int, n_kv_heads: int, head_dim: int, dtype: int, rope_base: float,
                  max_tokens: int, max_chunks: int, max_question_tokens: int,
                  rope_layout: int = FR_ROPE_INTERLEAVED, rope_index_base: int = 0):
-        self._lib = load()
+        self._lib = _load_by_address()
         self.desc = fr_layer_desc(n_q_heads, n_kv_heads, head_dim, dtype, rope_base, rope_layout, rope_index_base)
         h = ctypes.c_void_p()
         st = self._lib.fr_create(ctypes.byref(self.desc), int(max_tokens), int(max_chunks), int(max_question_tokens),
@@ -279,16 +296,16 @@ class Context:
                                             workspace_bytes: Optional[int] = None, stream=None):
         """queries: sequence of dicts with the keys q_rows, q_index, R, chunk_offsets, chunk_store_row0, chunk_src_pos0,
         L, k_new, v_new, out and optionally lse_out (the per-query arguments of fr_sparse_prefill_attn_shared)."""
-        arr = (fr_shared_query * max(1, len(queries)))()
+        arr = (_shared_query_by_address * max(1, len(queries)))()
         keep = []
         for i, q in enumerate(queries):
             offs, a = _i32_array(q["chunk_offsets"])
             row0, b = _i32_array(q["chunk_store_row0"])
             src, c = _i32_array(q["chunk_src_pos0"])
             keep += [a, b, c]
-            arr[i] = fr_shared_query(_ptr(q["q_rows"]), _ptr(q["q_index"]), int(q["R"]), offs, row0, src, len(a) - 1,
-                                     int(q["L"]), _ptr(q["k_new"]), _ptr(q["v_new"]), _ptr(q["out"]),
-                                     _ptr(q.get("lse_out")))
+            arr[i] = _shared_query_by_address(_ptr(q["q_rows"]), _ptr(q["q_index"]), int(q["R"]), offs, row0, src, len(a) - 1,
+                                              int(q["L"]), _ptr(q["k_new"]), _ptr(q["v_new"]), _ptr(q["out"]),
+                                              _ptr(q.get("lse_out")))
         if workspace_bytes is None:
             workspace_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
         self._check(self._lib.fr_sparse_prefill_attn_shared_batch(self._h, arr, len(queries), _ptr(k_store), _ptr(v_store),

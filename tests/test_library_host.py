@@ -180,6 +180,33 @@ def test_shared_batch_argument_errors():
     c.close()
 
 
+def test_host_arrays_of_the_c_interface():
+    """Who calls the library's functions directly hands host arrays over as arrays of, or pointers to, c_int32: other element types and plain
+    addresses are refused, in arguments and in the fields of a shared-store query."""
+    lib = B.load()
+    c = B.Context(32, 8, 128, B.FR_BF16, 5e5, max_tokens=600, max_chunks=4, max_question_tokens=32)
+    P, zero = 4096, (ctypes.c_int32 * 2)(0, 0)
+    offs = (ctypes.c_int32 * 3)(0, 8, 16)
+    pointer = ctypes.cast(offs, ctypes.POINTER(ctypes.c_int32))
+    for o in (offs, pointer, ctypes.byref(ctypes.c_int32.from_buffer(offs))):      # (keys at NULL: refused behind the arrays' own checks)
+        assert lib.fr_rope_shift(c._h, None, None, o, zero, None, 0, 2, 1, 0, 0, None) == B.FR_ERR_INVALID_ARG
+    assert lib.fr_rope_shift(c._h, None, None, zero, zero, None, 0, 1, 1, 0, 0, None) == B.FR_OK               # nothing to do
+    wrong = (ctypes.c_int64 * 3)(0, 8, 16)
+    for o in (wrong, ctypes.cast(offs, ctypes.POINTER(ctypes.c_int64)), ctypes.cast(offs, ctypes.c_void_p), ctypes.addressof(offs)):
+        with pytest.raises(ctypes.ArgumentError):
+            lib.fr_rope_shift(c._h, P, P, o, zero, None, 0, 2, 1, 0, 0, None)
+        with pytest.raises(TypeError):
+            B.fr_shared_query(P, P, 0, o, zero, zero, 2, 20, P, P, P, None)
+    queries = (B.fr_shared_query * 2)(B.fr_shared_query(P, P, 0, offs, zero, zero, 2, 20, P, P, P, None),
+                                      B.fr_shared_query(P, P, 0, pointer, pointer, zero, 2, 20, P, P, P, None))
+    assert lib.fr_sparse_prefill_attn_shared_batch(c._h, queries, 2, P, P, 100, None, 0, None) == B.FR_OK      # no rows: nothing to do
+    queries[1].chunk_store_row0 = (ctypes.c_int32 * 2)(0, 96)                                                  # past the store
+    assert lib.fr_sparse_prefill_attn_shared_batch(c._h, queries, 2, P, P, 100, None, 0, None) == B.FR_ERR_INVALID_ARG
+    queries[1].chunk_store_row0 = None
+    assert lib.fr_sparse_prefill_attn_shared_batch(c._h, queries, 2, P, P, 100, None, 0, None) == B.FR_ERR_INVALID_ARG
+    c.close()
+
+
 def test_shared_score_select_argument_errors():
     import torch
     c = B.Context(32, 8, 128, B.FR_BF16, 5e5, max_tokens=600, max_chunks=4, max_question_tokens=32)
