@@ -15,8 +15,9 @@
 // A block's product is formed from zero and added to the running sum with one rounding: onto the running sum the product rounds that several
 // times a block, which the longer chains of eight waves had made 1 to 3 % worse against float64 than 16 (head_dim 64: 1.652e-7 with 16
 // waves, 1.670e-7 with eight, now 1.610e-7 at 109 of 544 positions; 1 % of the call).
-// 4 heads, head_dim 64, us a call, keys and values straight into fragment registers : through LDS: 42 rows of 272 positions 9.5 : 8.5, 109 of 544 13.3 : 11.6, 310 of 800
-// 17.3 : 15.1, 768 of 1280 25.2 : 21.6; bf16, 80 heads over one KV head, 172 of 920 49 : 32.  A round of eight blocks takes about a microsecond of the matrix pipes, on as
+// 4 heads, head_dim 64, us a call, keys and values straight into fragment registers : through LDS: 42 rows of 272 positions 9.3 : 7.9, 109 of 544 13.2 : 11.3, 310 of 800
+// 17.3 : 14.9, 768 of 1280 25.4 : 21.2; bf16, 80 heads over one KV head, 172 of 920 46 : 31; with copies of a block past the end, which the waves then wait for, 8.3, 11.6, 15.1,
+// 21.5, 32, and few keys slower than from registers: 1 row of 36 positions 4.5 : 4.3 (4.8), 12 of 40, 8 / 2 heads of 128, 8.4 : 8.1 (8.9).  A round of eight blocks takes about a microsecond of the matrix pipes, on as
 // many compute units as there are column tiles.  Four waves are slower, 16 waves too (11.1 and 15.2 where eight took 9.0 and 12.9).
 #include "fr_internal.hpp"
 
@@ -93,21 +94,28 @@ __global__ __launch_bounds__(64 * W) void attn_f32_kernel(const T* __restrict__ 
     const uint32_t k_lds = lds_address(blocks.k[wave]), v_lds = lds_address(blocks.v[wave]);
     size_t source[COPIES];   // byte offset of the lane's rows of the block on its way
     bool fresh[COPIES];
-    auto copy_k = [&](int b) {
+    auto locate = [&](int b) {
         int f[COPIES];   // fresh rows
         auto key = [&](int i) { return min(16 * b + RC * i + q, p_last); };   // keys behind the tile's last row repeat that one
         if (own_map) {
 #pragma unroll
             for (int i = 0; i < COPIES; ++i) f[i] = (int)row_of[key(i)] - 1;
+        } else if (have_new) {
+#pragma unroll
+            for (int i = 0; i < COPIES; ++i) f[i] = inv[key(i)];
+#pragma unroll
+            for (int i = 0; i < COPIES; ++i) asm volatile("" : "+v"(f[i]));   // (waited for here: behind the branch the other calls would wait for their values' copies)
         } else {
 #pragma unroll
-            for (int i = 0; i < COPIES; ++i) f[i] = have_new ? inv[key(i)] : -1;
+            for (int i = 0; i < COPIES; ++i) f[i] = -1;
         }
 #pragma unroll
         for (int i = 0; i < COPIES; ++i) {
             fresh[i] = f[i] >= 0;
             source[i] = ((size_t)(fresh[i] ? f[i] : key(i)) * Hkv + g) * RB;
         }
+    };
+    auto copy_k = [&] {   // of the block that has been located
 #pragma unroll
         for (int i = 0; i < COPIES; ++i)
             dma(reinterpret_cast<const unsigned char*>(fresh[i] ? k_new : k_cache) + source[i] + 16 * (vec ^ swz(RC * i + q)), k_lds + 1024 * i);
@@ -122,9 +130,14 @@ __global__ __launch_bounds__(64 * W) void attn_f32_kernel(const T* __restrict__ 
     for (int md = 0; md < NJ; ++md) o[md] = f32x4{0.f, 0.f, 0.f, 0.f};
     float m = NEG_BIG, l = 0.f;
     wait_but(std::integral_constant<int, 0>{});   // (nothing that the compiler counts is in flight from here on)
-    copy_k(min(wave, n_blocks - 1));   // (past the last block: that one again, nobody uses it; the counts of the waits stay the same)
-    copy_v();
+    if (wave < n_blocks) {
+        locate(wave);
+        copy_k();
+        copy_v();
+    }
     for (int b = wave; b < n_blocks; b += W) {
+        // (nothing is copied past the end: of few keys a wave has a block or two, and would wait for one more)
+        const bool more = b + W < n_blocks;
         wait_but(std::integral_constant<int, COPIES>{});
         f32x4 kv[NJ], vv[4][NJ / 4];   // key 16 b + x, dims 16 j + 4 kg + e; values of keys 4 kg + i, dims NJ x ..
 #pragma unroll
@@ -142,7 +155,7 @@ __global__ __launch_bounds__(64 * W) void attn_f32_kernel(const T* __restrict__ 
             s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[j][3], qv[j][3], s1, 0, 0, 0);
         }
         __builtin_amdgcn_sched_barrier(0);
-        copy_k(min(b + W, n_blocks - 1));
+        locate(min(b + W, n_blocks - 1));
         f32x4 s = s0 + s1;
         float mx = NEG_BIG;
 #pragma unroll
@@ -160,7 +173,12 @@ __global__ __launch_bounds__(64 * W) void attn_f32_kernel(const T* __restrict__ 
         }
         l = l * alpha + psum;
         float scale_o = alpha;
-        wait_but(std::integral_constant<int, COPIES>{});
+        if (more) {
+            copy_k();
+            wait_but(std::integral_constant<int, COPIES>{});
+        } else {
+            wait_but(std::integral_constant<int, 0>{});
+        }
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -206,9 +224,8 @@ __global__ __launch_bounds__(64 * W) void attn_f32_kernel(const T* __restrict__ 
 #pragma unroll
             for (int e = 0; e < 4; ++e) o[md][e] = __builtin_fmaf(o[md][e], scale_o, pv[md][e]);
         __builtin_amdgcn_sched_barrier(0);
-        copy_v();
+        if (more) copy_v();
     }
-    wait_but(std::integral_constant<int, 0>{});
     __syncthreads();   // everyone is done with the copies
     // ---- merge the waves ---------------------------------------------------------------------------------------------
     l = column_sum(l);

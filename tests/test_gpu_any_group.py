@@ -306,10 +306,12 @@ def test_scores_beyond_the_first_reference(norm):
 
 # fp32 products (fp32 storage; bf16 with more than 64 heads per KV head): sums of a few hundred fp32 terms, 1e-5 of the
 # largest output as everywhere for fp32; prompts below and above the size whose position map fits LDS (8192), column tiles
-# with rows of several and of less than one tile, fewer key blocks than waves.
+# with rows of several and of less than one tile, fewer key blocks than waves, one block a wave, one wave with two, all with two, one with three.
 @pytest.mark.parametrize("Hq,Hkv,d,dt,lens,nq,ratio", [(4, 4, 64, "f32", (5,), 3, 0.5), (4, 4, 64, "f32", (128, 77), 32, 0.15),
                                                        (6, 2, 64, "f32", (300, 0, 129), 17, 1.0), (5, 1, 128, "f32", (260, 40), 9, 0.2),
-                                                       (2, 1, 64, "f32", (8100, 200), 21, 0.01), (80, 1, 64, "bf16", (90, 60), 5, 0.2)])
+                                                       (2, 1, 64, "f32", (8100, 200), 21, 0.01), (80, 1, 64, "bf16", (90, 60), 5, 0.2),
+                                                       (4, 4, 64, "f32", (120,), 8, 0.1), (4, 4, 64, "f32", (121,), 8, 0.1), (8, 2, 128, "f32", (121,), 8, 0.1),
+                                                       (8, 2, 128, "f32", (248,), 8, 0.1), (8, 2, 128, "f32", (249,), 8, 0.1)])
 def test_attention_with_fp32_products(Hq, Hkv, d, dt, lens, nq, ratio):
     shape = synth.LayerShape(n_q_heads=Hq, n_kv_heads=Hkv, head_dim=d, dtype=dt, rope_base=500000.0)
     w = synth.config_small_bf16(seed=Hq + nq, ratio=ratio, chunk_lens=lens, nq=nq, shape=shape)
