@@ -132,8 +132,12 @@ hipError_t launch_rope_shift(const Shape& s, const void* src, void* dst, const C
     const ChunkRows none{};
     const ChunkRows& rows = src_rows ? *src_rows : none;
     const int from_store = src_rows ? 1 : 0;
-    // Tokens per workgroup: 32, eight vectors of a thread in flight twice over; while that would leave compute units without a workgroup, 8 (see the head).
-    const bool few = (int64_t)((max_chunk_len + 31) / 32) * ct.n * n_batch < n_cu;
+    // Tokens per workgroup: 32, eight vectors of a thread in flight twice over; while that would leave compute units without a workgroup, 8 (see the head).  Four times the
+    // workgroups cost more than they bring where a row is short: from half the units on below 1536 bytes (32 : 8 tokens, us, 128 and 250 tiles: rows of 1024 bytes 3.5 : 3.3 and 4.2 : 4.5, of
+    // 1536 4.0 : 3.4 and 5.3 : 5.0, of 2048 5.4 : 4.3 and 6.5 : 6.0), and where 32 tokens are but a vector (two in the half-split layout) of a thread (128 tiles 2.8 : 2.9).
+    const int64_t tiles = (int64_t)((max_chunk_len + 31) / 32) * ct.n * n_batch;
+    const int row = s.Hkv * s.d * s.esize, short_row = s.rope_layout == FR_ROPE_HALF ? 512 : 256;
+    const bool few = row >= 1536 ? tiles < n_cu : row >= short_row && 2 * tiles <= n_cu;
     const int tok = few ? 8 : 32;
     dim3 grid((max_chunk_len + tok - 1) / tok, ct.n, n_batch);
 #define FR_ROPE_LAUNCH_TOK(T, LAY, TOK)                                                             \

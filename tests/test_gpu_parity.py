@@ -109,6 +109,39 @@ def test_rope_shift_batched_layers_and_empty_chunk():
     ctx.close()
 
 
+# Tokens per workgroup: 8 while tiles of 32 tokens (of the longest chunk, for each chunk and layer) are fewer than the compute units, or no more than half of them for rows
+# below 1536 bytes, else 32, as for rows below 256 bytes (512 in the half-split layout).  Both sides of the lines (chunks of up to 100 tokens, four tiles each, for 256 units),
+# ragged last tiles, an empty chunk and one of a token; 32 tokens of 8 heads of 128 are more vectors than a thread has in flight (a second turn, and a fourth in fp32), as 8
+# tokens of 32 heads are.
+@pytest.mark.parametrize("chunks", [32, 33, 63, 64])
+@pytest.mark.parametrize("layout", [B.FR_ROPE_INTERLEAVED, B.FR_ROPE_HALF])
+@pytest.mark.parametrize("Hkv,d,dt", [(8, 128, "bf16"), (3, 64, "bf16"), (8, 128, "f32"), (1, 64, "f32"), (1, 64, "bf16"), (3, 128, "f32"), (32, 128, "f32")])
+def test_rope_shift_tokens_per_workgroup(Hkv, d, dt, layout, chunks):
+    assert torch.cuda.get_device_properties(0).multi_processor_count == 256
+    shape = synth.LayerShape(n_q_heads=Hkv, n_kv_heads=Hkv, head_dim=d, dtype=dt, rope_base=10000.0)
+    rng = np.random.default_rng(chunks + d)
+    lens = np.concatenate([[0, 1, 8, 31, 32, 33, 100, 97], rng.integers(1, 100 if Hkv < 32 else 40, size=chunks - 8)])
+    offs = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    n = int(offs[-1])
+    x = synth.round_to_storage(rng.standard_normal((n, Hkv, d)).astype(np.float32), dt)
+    src_pos, dst_pos = rng.integers(0, 4000, size=chunks).astype(np.int32), rng.integers(0, 60000, size=chunks).astype(np.int32)
+    ctx = H.make_ctx(shape, n + 1, chunks, 1, rope_layout=layout)
+    src = H.dev(x, dt)
+    dst = torch.full((n + 1, Hkv, d), 7.0, dtype=src.dtype, device="cuda")
+    ctx.fr_rope_shift(src, dst, offs, src_pos, dst_pos)
+    torch.cuda.synchronize()
+    assert torch.all(dst[n] == 7.0)                                              # nothing behind the last token
+    want = orc.rope_shift(x, offs, src_pos, dst_pos, shape.rope_base, "half" if layout == B.FR_ROPE_HALF else "interleaved")
+    got = H.host(dst[:n])
+    # the bound of test_rope_shift: rounded once to storage, one unit
+    ulp = 2.0 ** -7 if dt == "bf16" else 2.0 ** -21
+    assert np.all(np.abs(got - want) <= ulp * np.abs(want) + (1e-6 if dt == "f32" else 1e-4) * np.abs(want).max())
+    ctx.fr_rope_shift(src, src, offs, src_pos, dst_pos)
+    torch.cuda.synchronize()
+    assert torch.equal(src, dst[:n])                                             # in place gives the same bits
+    ctx.close()
+
+
 @pytest.mark.parametrize("norm", [B.FR_NORM_PER_CHUNK, B.FR_NORM_GLOBAL, B.FR_NORM_RAW])
 @pytest.mark.parametrize("name,seed", CASES)
 def test_score_select(name, seed, norm):
