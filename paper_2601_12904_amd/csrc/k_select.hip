@@ -14,6 +14,8 @@
 // passes of 8 bits: 9.6 / 19.5 / 33.0 us at 880 / 16384 / 32768 scores of a prompt, with this 8.1 / 14.7 / 25.2; what else was taken out stands at select_in_workgroup).
 #include "fr_internal.hpp"
 
+#include <algorithm>
+
 namespace fr {
 
 __device__ __forceinline__ uint32_t score_key(float f) {
@@ -254,6 +256,63 @@ __global__ __launch_bounds__(SEL_THREADS) void select_topk_kernel(const float* _
     select_in_workgroup<PER>(scores, (int)n, k, out);
 }
 
+// At most 128 scores: a lane has a token and counts the keys above its own, one broadcast after the other; a wave for each 64 tokens, each of which holds all keys.  Fewer than k
+// of them: chosen, or tied at the k-th largest key, of whose tokens the first are taken.  No histogram, a barrier at most, nearly the same time whatever the scores are; what bounds
+// it are the launch and three instructions a key.  Other waves are there for the question tokens only.
+constexpr int FEW_WAVES = 2;
+__global__ __launch_bounds__(SEL_THREADS) void select_few_kernel(const float* __restrict__ scores, int n, int k, int nq, int32_t* __restrict__ out) {
+    __shared__ int s_chosen[FEW_WAVES], s_most[FEW_WAVES], s_tied[FEW_WAVES];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), token = threadIdx.x;
+    for (int i = threadIdx.x; i < nq; i += blockDim.x) out[k + i] = n + i;   // question tokens: positions n .. n + nq - 1
+    if (k <= 0) return;                                                      // (there need be no scores then)
+    uint32_t keys[FEW_WAVES], key = 0u;   // (0, past the end: above no key)
+#pragma unroll
+    for (int i = 0; i < FEW_WAVES; ++i) keys[i] = 64 * i + lane < n ? score_key(scores[min(64 * i + lane, n - 1)]) : 0u;
+#pragma unroll
+    for (int i = 0; i < FEW_WAVES; ++i) key = wave == i ? keys[i] : key;
+    int above = token < n ? 0 : k;
+    if (64 * wave < n) {
+#pragma unroll
+        for (int i = 0; i < FEW_WAVES; ++i)
+            for (int j = 0; j < min(64, n - 64 * i); j += 16)
+#pragma unroll
+                for (int u = 0; u < 16; ++u) above += __builtin_amdgcn_readlane(keys[i], j + u) > key ? 1 : 0;
+    }
+    // the tied key, if it has more tokens than are taken, is the chosen one with the most keys above it
+    auto largest = [&] {
+        const uint32_t v = over_row(above < k ? (uint32_t)above : 0u, higher);
+        return (int)max(max(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)), max(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
+    };
+    uint64_t chosen = __ballot(above < k);
+    int total = __popcll(chosen), at = 0, most = 0, tied_before = 0;
+    if (n > 64) {
+        const int own = largest();
+        if (wave < FEW_WAVES && lane == 0) { s_chosen[wave] = total; s_most[wave] = own; }
+        const int own_tied = __popcll(__ballot(above < k && above == own));
+        if (wave < FEW_WAVES && lane == 0) s_tied[wave] = own_tied;
+        __syncthreads();
+        if (64 * wave >= n) return;
+        const int waves = (n + 63) / 64;
+        total = 0;
+        for (int w = 0; w < waves; ++w) { total += s_chosen[w]; most = max(most, s_most[w]); }
+        int above_before = 0;
+        for (int w = 0; w < wave; ++w) {
+            const int tied = s_most[w] == most ? s_tied[w] : 0;
+            tied_before += tied;
+            above_before += s_chosen[w] - tied;
+        }
+        at = above_before + min(tied_before, k - most);
+    } else {
+        if (wave > 0) return;
+        if (total > k) most = largest();
+    }
+    if (total > k) {
+        const uint64_t tied = __ballot(above == most);
+        chosen = __ballot(above < most || (above == most && tied_before + (int)lanes_below(tied) < k - most));
+    }
+    if (chosen >> lane & 1) out[at + lanes_below(chosen)] = token;
+}
+
 // The same for n <= 64 PER scores in one wave: no histogram, no barrier, no LDS.  Token 64 i + lane is key i of the lane, so
 // (i, lane) order is index order.  The threshold key is found bit by bit from the highest one in which the keys differ: a bit
 // stays set if at least k keys reach it, counted by ballots (PER compares and scalar adds); as soon as exactly k keys reach the threshold, the set
@@ -371,7 +430,11 @@ static_assert(SELECT_ONE_WORKGROUP_MAX == (int64_t)SEL_THREADS * 32, "largest sc
 hipError_t launch_select(const float* scores, int64_t n, int64_t k, int nq, int32_t* q_index, uint32_t* tmp,
                          size_t tmp_bytes, hipStream_t st) {
     if (k + nq == 0) return hipSuccess;
-    if (n <= (int64_t)SEL_THREADS * 4)
+    // Up to 128 scores by counting, a wave for each 64 of them and of the question tokens (us, counted : workgroup, 3, 64, 100, 128 scores 2.2, 2.7, 3.9, 4.1 : 4.6, 160 and 256
+    // 4.8 and 6.4 : 4.6; a bit-by-bit search in one wave took 3.1 to 5.3, 8.6 with ties).
+    if (n <= 64 * FEW_WAVES)
+        select_few_kernel<<<dim3(1), dim3(64 * std::max((int)(n + 63) / 64, std::min(SEL_THREADS / 64, std::max(1, (nq + 63) / 64)))), 0, st>>>(scores, (int)n, (int)k, nq, q_index);
+    else if (n <= (int64_t)SEL_THREADS * 4)
         select_topk_kernel<4><<<dim3(1), dim3(SEL_THREADS), 0, st>>>(scores, n, k, nq, q_index);
     else if (n <= (int64_t)SEL_THREADS * 8)
         select_topk_kernel<8><<<dim3(1), dim3(SEL_THREADS), 0, st>>>(scores, n, k, nq, q_index);

@@ -453,20 +453,34 @@ def test_select_rank_inside_a_histogram_bin(n, in_bin):
     ctx.close()
 
 
-@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 511, 512, 513, 1023, 1024, 1025, 2047, 2048, 2049])
+def ranked(s, k, nq):
+    """The selection's own order, NaN included: scores by their bits, larger first, then lower index (orc.select_q_index where all are numbers and zeros have one sign)."""
+    u = s.view(np.uint32)
+    key = np.where(u >> 31, ~u, u | np.uint32(1 << 31)).astype(np.int64)
+    return np.concatenate([np.sort(np.lexsort((np.arange(len(s)), -key))[:k]), len(s) + np.arange(nq)])
+
+
+@pytest.mark.parametrize("n", [1, 2, 15, 16, 17, 63, 64, 65, 80, 127, 128, 129, 191, 192, 193, 255, 256, 257, 511, 512, 513, 1023, 1024, 1025, 2047, 2048, 2049])
 def test_select_in_one_wave(n):
-    """Both sides of the sizes at which the selection of one wave takes another instance, or 16 waves: distinct scores, ties, one
-    value, extremes of every bit, infinities; no score at all where none is taken."""
-    ctx = H.make_ctx(synth.TINY_F32, 4096, 4, 16)
+    """Small numbers of scores: up to 128 counted, a wave for each 64, from there on by the workgroup's histogram (one wave selects behind sums of up to 512 scores only:
+    test_selection_beside_the_sums).  Distinct scores, ties, one value, extremes of every bit, infinities, NaN of both signs; no score at all where none is taken; fewer and
+    more question tokens than the scores' waves hold."""
+    ctx = H.make_ctx(synth.TINY_F32, 4096, 4, 600)
     rng = np.random.default_rng(n)
     inputs = {"distinct": rng.permutation(n).astype(np.float32) - n / 3, "ties": rng.integers(0, 5, size=n).astype(np.float32),
               "constant": np.full(n, -2.5, dtype=np.float32), "extremes": rng.standard_normal(n).astype(np.float32)}
     inputs["extremes"][rng.integers(0, n, size=4)] = [3.0e38, -3.0e38, np.inf, -np.inf]
     for name, s in inputs.items():
         dev = torch.from_numpy(s).cuda()
-        for k in sorted({0, 1, n // 7, n // 2, n - 1, n}):
-            out = torch.full((k + 3,), -7, dtype=torch.int32, device="cuda")
-            ctx.fr_select_topk(dev if k else None, n, k, 3, out)
-            torch.cuda.synchronize()
-            assert np.array_equal(out.cpu().numpy(), orc.select_q_index(s, k, 3)), (name, k)
+        for k in sorted({0, 1, n // 7, n // 3, n // 2, n - 1, n}):
+            for nq in (3, 600) if k == n // 3 else (3,):
+                out = torch.full((k + nq + 1,), -7, dtype=torch.int32, device="cuda")
+                ctx.fr_select_topk(dev if k else None, n, k, nq, out)
+                torch.cuda.synchronize()
+                got = out.cpu().numpy()
+                assert got[-1] == -7 and np.array_equal(got[:-1], ranked(s, k, nq)), (name, k, nq)
+                assert name == "not numbers" or np.array_equal(got[:-1], orc.select_q_index(s, k, nq)), (name, k, nq)
     ctx.close()
+    inputs["runs"] = np.repeat(rng.permutation(n // 30 + 1), 30)[:n].astype(np.float32)      # ties in a wave and across two
+    inputs["not numbers"] = inputs["extremes"].copy()
+    inputs["not numbers"].view(np.uint32)[rng.integers(0, n, size=n // 8 + 2)] = rng.choice(np.array([0x7FC00000, 0xFFC00000, 0xFFFFFFFF, 0x7F800001], dtype=np.uint32), size=n // 8 + 2)
