@@ -470,6 +470,9 @@ def test_select_in_one_wave(n):
     inputs = {"distinct": rng.permutation(n).astype(np.float32) - n / 3, "ties": rng.integers(0, 5, size=n).astype(np.float32),
               "constant": np.full(n, -2.5, dtype=np.float32), "extremes": rng.standard_normal(n).astype(np.float32)}
     inputs["extremes"][rng.integers(0, n, size=4)] = [3.0e38, -3.0e38, np.inf, -np.inf]
+    inputs["runs"] = np.repeat(rng.permutation(n // 30 + 1), 30)[:n].astype(np.float32)      # ties in a wave and across two
+    inputs["not numbers"] = inputs["extremes"].copy()
+    inputs["not numbers"].view(np.uint32)[rng.integers(0, n, size=n // 8 + 2)] = rng.choice(np.array([0x7FC00000, 0xFFC00000, 0xFFFFFFFF, 0x7F800001], dtype=np.uint32), size=n // 8 + 2)
     for name, s in inputs.items():
         dev = torch.from_numpy(s).cuda()
         for k in sorted({0, 1, n // 7, n // 3, n // 2, n - 1, n}):
@@ -481,6 +484,3 @@ def test_select_in_one_wave(n):
                 assert got[-1] == -7 and np.array_equal(got[:-1], ranked(s, k, nq)), (name, k, nq)
                 assert name == "not numbers" or np.array_equal(got[:-1], orc.select_q_index(s, k, nq)), (name, k, nq)
     ctx.close()
-    inputs["runs"] = np.repeat(rng.permutation(n // 30 + 1), 30)[:n].astype(np.float32)      # ties in a wave and across two
-    inputs["not numbers"] = inputs["extremes"].copy()
-    inputs["not numbers"].view(np.uint32)[rng.integers(0, n, size=n // 8 + 2)] = rng.choice(np.array([0x7FC00000, 0xFFC00000, 0xFFFFFFFF, 0x7F800001], dtype=np.uint32), size=n // 8 + 2)
