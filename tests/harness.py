@@ -4,6 +4,8 @@ from ties within 1e-3 relative score; floating point within max relative error (
 over the tensor divided by max |oracle|) of 2e-2 for bf16 storage and 1e-5 for fp32."""
 from __future__ import annotations
 
+import ctypes
+
 import numpy as np
 from paper_2601_12904_amd import binding as B  # noqa: F401
 from paper_2601_12904_amd import synth  # noqa: F401
@@ -74,3 +76,20 @@ def assert_index_set(q_index_gpu: np.ndarray, oracle_scores: np.ndarray, k: int,
     assert np.all(in_window[diff]), (f"{len(diff)} selected tokens differ from the oracle's set and "
                                      f"{int((~in_window[diff]).sum())} of them are outside the tie window")
     return int(in_window.sum())
+
+
+class _Shape(ctypes.Structure):
+    """The library's own description of a layer (fr::Shape)."""
+    _fields_ = [(n, ctypes.c_int) for n in ("Hq", "Hkv", "d", "G", "dtype", "esize")] + \
+               [("rope_base", ctypes.c_double), ("rope_layout", ctypes.c_int), ("rope_index_base", ctypes.c_int)]
+
+
+def in_one_launch(Hq: int, Hkv: int, d: int, R: int, L: int, n_cu: int = None, dtype: int = B.FR_BF16) -> bool:
+    """Whether R rows of a prompt of L positions over a cache of their own take the one-launch attention kernel when no option asks for another:
+    the library's own rule, so that a test that means the tiled kernels notices when it no longer reaches them."""
+    if n_cu is None:
+        import torch
+        n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    rule = B.load()._ZN2fr16attn_direct_paysERKNS_5ShapeEili          # fr::attn_direct_pays(const Shape&, int, long, int)
+    rule.argtypes, rule.restype = [ctypes.POINTER(_Shape), ctypes.c_int, ctypes.c_int64, ctypes.c_int], ctypes.c_bool
+    return rule(ctypes.byref(_Shape(Hq, Hkv, d, Hq // Hkv, dtype, 4 if dtype == B.FR_F32 else 2, 1e4, 0, 0)), R, L, n_cu)

@@ -198,3 +198,15 @@ def test_decode_attn_pieces(chunk_lens, prompts, n_gen, page_stride, generic):
     # variance is off by a standard deviation of at most 2^-9 / sqrt 3, and so is the sum's logarithm where one key
     # dominates.  Five of them for up to 1200 results over a few keys each (in fp64 with such queries: 3.18e-3 at worst).
     assert np.max(np.abs(lse - want_lse)) <= 5 * 2.0 ** -9 / np.sqrt(3)
+
+
+@pytest.mark.parametrize("name", ["llama_bf16", "bf16_d64_g2", "f32_d128_g4", "tiny_f32"])
+def test_decode_merge_of_unequal_queries(name):
+    """The merge has as many waves as the pieces of an average query need for one turn: a query with several times as many (three turns and more), one with a
+    single piece (waves without one) and one with a few, in a batch."""
+    shape = SHAPES[name]
+    bt = make_batch(shape, 12, chunk_lens=(40, 9), prompts=((0, 1) * 200, (), (1, 0), (0,)), nq=(3, 1, 2, 1), n_gen=(1, 1, 1, 1))
+    want, want_lse = orc.decode_attn(bt["q"], bt["k_store"], bt["v_store"], bt["segments"], bt["stale"], bt["k_pages"], bt["v_pages"], shape.rope_base)
+    got, lse, _ = run_gpu(bt)
+    H.assert_close(got, want, shape.dtype, "merge of unequal queries")
+    assert np.max(np.abs(lse - want_lse)) <= (1e-4 if shape.dtype == "f32" else 5 * 2.0 ** -9 / np.sqrt(3))

@@ -378,6 +378,24 @@ def run_attention(ctx, w, qi, k_cache, v_cache, with_new=True, want_lse=True):
     return H.host(out), (lse.cpu().numpy().astype(np.float64) if want_lse else None)
 
 
+def run_attention_over_store(ctx, w, qi, k_cache, v_cache):
+    """The same through the shared-store call: the context rows are a chunk at its own positions (a rotation by zero leaves keys as stored).  Shapes with an
+    instance of their own run the tiled kernels there, however short the prompt."""
+    R, n = len(qi), w.L_ctx
+    q_rows, k_new, v_new = (H.dev(x[qi], "bf16") for x in (w.q_full, w.k_full, w.v_full))
+    out = torch.zeros((R, w.shape.n_q_heads, w.shape.head_dim), dtype=torch.bfloat16, device="cuda")
+    lse = torch.zeros((R, w.shape.n_q_heads), dtype=torch.float32, device="cuda")
+    ctx.fr_sparse_prefill_attn_shared(q_rows, torch.from_numpy(qi.astype(np.int32)).cuda(), R, H.dev(k_cache[:n], "bf16"), H.dev(v_cache[:n], "bf16"), n,
+                                      [0, n], [0], [0], w.L, k_new, v_new, out, lse)
+    torch.cuda.synchronize()
+    return H.host(out), lse.cpu().numpy().astype(np.float64)
+
+
+def one_launch(w, qi):
+    """Whether the workload's rows run the one-launch attention by default."""
+    return H.in_one_launch(w.shape.n_q_heads, w.shape.n_kv_heads, w.shape.head_dim, len(qi), w.L, dtype=H.FR_DTYPE[w.shape.dtype])
+
+
 @pytest.mark.parametrize("name,seed", CASES)
 def test_sparse_prefill_attn(name, seed):
     w = workloads()[name](seed)
@@ -465,6 +483,25 @@ def test_kv_scatter_bit_exact(name, seed):
     ctx.close()
 
 
+# Rows of 48, 24, 96, 48 and 224 vectors of 16 bytes, which are no power of two, and of 8 and 512; one row, a workgroup's 1024 vectors with and without a rest, several workgroups
+@pytest.mark.parametrize("R", [1, 5, 21, 43, 64, 300])
+@pytest.mark.parametrize("Hkv,d,dt", [(3, 128, "bf16"), (3, 64, "bf16"), (6, 64, "f32"), (6, 64, "bf16"), (7, 128, "f32"), (1, 64, "bf16"), (16, 128, "f32")])
+def test_kv_scatter_rows_of_any_number_of_vectors(Hkv, d, dt, R):
+    rng = np.random.default_rng(R + Hkv)
+    L = 2 * R + 3
+    shape = synth.LayerShape(n_q_heads=Hkv, n_kv_heads=Hkv, head_dim=d, dtype=dt, rope_base=10000.0)
+    ctx = H.make_ctx(shape, L, 1, 1)
+    rows = lambda n: synth.round_to_storage(rng.standard_normal((n, Hkv, d)).astype(np.float32), dt)  # noqa: E731
+    k_new, v_new, k_cache, v_cache = rows(R), rows(R), rows(L), rows(L)
+    qi = np.sort(rng.choice(L, size=R, replace=False))
+    kc, vc = H.dev(k_cache, dt), H.dev(v_cache, dt)
+    ctx.fr_kv_scatter(H.dev(k_new, dt), H.dev(v_new, dt), torch.from_numpy(qi.astype(np.int32)).cuda(), R, kc, vc, L)
+    torch.cuda.synchronize()
+    want_k, want_v = orc.kv_scatter(qi, k_new, v_new, k_cache, v_cache)
+    assert np.array_equal(H.host(kc), want_k.astype(np.float64)) and np.array_equal(H.host(vc), want_v.astype(np.float64))
+    ctx.close()
+
+
 def test_kv_scatter_ignores_positions_outside_the_cache():
     """A Q index entry outside [0, L) breaks the caller's contract; the kernel's own bounds check drops that row
     instead of writing outside the cache, and every other row is written as usual."""
@@ -521,8 +558,9 @@ def test_chained_layer(name, seed):
     ctx.close()
 
 
-def test_layer_under_hip_graph():
-    """The four calls captured once into a HIP graph and replayed with different cache contents, the program's own eager
+@pytest.mark.parametrize("split", [B.FR_ATTN_SPLIT_AUTO, B.FR_ATTN_SPLIT_OFF, B.FR_ATTN_SPLIT_ON])
+def test_layer_under_hip_graph(split):
+    """The four calls (attention in one launch, tiled with whole items, and in parts) captured once into a HIP graph and replayed with different cache contents, the program's own eager
     work and synchronisations between the replays: every replay equals the eager calls on the same inputs bit for bit
     (the calls allocate nothing, synchronise nothing and clear their scratch with kernels, so they can be captured)."""
     w = workloads()["small_bf16"](2)
@@ -530,7 +568,9 @@ def test_layer_under_hip_graph():
     Hq, Hkv, d = w.shape.n_q_heads, w.shape.n_kv_heads, w.shape.head_dim
     _, _, k, _ = staged(w)
     R = k + w.nq
+    assert H.in_one_launch(Hq, Hkv, d, R, w.L)      # (AUTO)
     ctx = H.make_ctx(w.shape, w.L, w.n_chunks, w.nq)
+    ctx.fr_set_option(B.FR_OPT_ATTN_SPLIT, split)
     rng = np.random.default_rng(4)
     variants = [(H.dev(w.k_cached, dt), H.dev(w.v_cached, dt))]
     for _ in range(2):   # two more stale caches of the same prompt
@@ -602,10 +642,11 @@ def test_attention_softmax_modes_agree():
     ctx.close()
 
 
-def test_attention_logits_far_above_the_first_keys():
+@pytest.mark.parametrize("split", [B.FR_ATTN_SPLIT_AUTO, B.FR_ATTN_SPLIT_OFF])
+def test_attention_logits_far_above_the_first_keys(split):
     """Degenerate case of the fixed exponent reference: logits that grow along the sequence until exp2 would
-    overflow against the maximum of the first 32 keys.  The default path must still match the oracle (the
-    overflowing workgroups do their items again against the largest logit)."""
+    overflow against the maximum of the first 32 keys.  The result must still match the oracle, from the one-launch kernel (AUTO), whose references go
+    up, and from whole tiled items (OFF), which the overflowing workgroups do again against the largest logit."""
     shape = synth.LLAMA3_8B_BF16
     rng = np.random.default_rng(11)
     L_ctx, nq, d = 600, 24, shape.head_dim
@@ -622,7 +663,9 @@ def test_attention_logits_far_above_the_first_keys():
     qi = np.concatenate([sel, L_ctx + np.arange(nq)])
     w = synth.Workload("ramp", shape, 0, np.array([0, L_ctx], np.int32), np.zeros(1, np.int32), nq, 0.15,
                        k_all[:L_ctx], v_all[:L_ctx], q_all, k_all, v_all, np.zeros(0, np.int64))
+    assert one_launch(w, qi)      # (AUTO)
     ctx = H.make_ctx(shape, L, 1, nq)
+    ctx.fr_set_option(B.FR_OPT_ATTN_SPLIT, split)
     got, lse = run_attention(ctx, w, qi, k_all, v_all)
     want, want_lse = orc.sparse_prefill_attn(q_all[qi], qi, k_all, v_all, k_all[qi], v_all[qi])
     H.assert_close(got, want, "bf16", "attention with runaway logits")
@@ -657,16 +700,18 @@ def test_attention_split_key_range(seed, ratio):
     ctx.close()
 
 
-@pytest.mark.parametrize("name", ["tiny_f32", "small_bf16"])
-def test_attention_with_fused_writeback(name):
+@pytest.mark.parametrize("name,split", [("tiny_f32", B.FR_ATTN_SPLIT_AUTO), *(("small_bf16", x) for x in (B.FR_ATTN_SPLIT_AUTO, B.FR_ATTN_SPLIT_OFF, B.FR_ATTN_SPLIT_ON))])
+def test_attention_with_fused_writeback(name, split):
     """fr_sparse_prefill_attn_writeback = attention + write-back in one call: output and caches equal the two-call path
-    bit for bit (the tiled path fuses the copy into its packing pass, the generic path runs the scatter kernel)."""
+    bit for bit (the one-launch kernel copies at its end, the tiled path in its packing pass, the generic path runs the scatter kernel)."""
     w = workloads()[name](6)
     dt, tdt = w.shape.dtype, H.TORCH_DTYPE[w.shape.dtype]
     k_ctx, _, _, qi = staged(w)
     k_cache, v_cache = assembled_cache(w, k_ctx)
     R = len(qi)
+    assert one_launch(w, qi) == (dt == "bf16")      # (AUTO)
     ctx = H.make_ctx(w.shape, w.L, w.n_chunks, w.nq)
+    ctx.fr_set_option(B.FR_OPT_ATTN_SPLIT, split)
     q_rows, k_new, v_new = H.dev(w.q_full[qi], dt), H.dev(w.k_full[qi], dt), H.dev(w.v_full[qi], dt)
     qi_d = torch.from_numpy(qi.astype(np.int32)).cuda()
     kc1, vc1 = H.dev(k_cache, dt), H.dev(v_cache, dt)
@@ -685,12 +730,16 @@ def test_attention_with_fused_writeback(name):
     ctx.close()
 
 
-def test_attention_kernel_timer():
-    """The optional event pairs around the dominant attention kernel: one duration per launch, the most recent kept."""
+@pytest.mark.parametrize("split", [B.FR_ATTN_SPLIT_AUTO, B.FR_ATTN_SPLIT_OFF, B.FR_ATTN_SPLIT_ON])
+def test_attention_kernel_timer(split):
+    """The optional event pairs around the dominant attention kernel (the one launch; the tile loop of whole items and of parts): one duration per launch,
+    the most recent kept."""
     w = synth.config_small_bf16(seed=2)
     k_ctx, _, _, qi = staged(w)
     k_cache, v_cache = assembled_cache(w, k_ctx)
     ctx = H.make_ctx(w.shape, w.L, w.n_chunks, w.nq)
+    assert one_launch(w, qi)      # (AUTO)
+    ctx.fr_set_option(B.FR_OPT_ATTN_SPLIT, split)
     assert ctx.fr_attn_kernel_times() == []
     ctx.fr_set_option(B.FR_OPT_ATTN_KERNEL_TIMER, 3)
     for _ in range(5):

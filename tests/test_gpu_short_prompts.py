@@ -47,6 +47,7 @@ SIZES = [(1, 1), (31, 5), (32, 32), (33, 8), (64, 9), (257, 40), (530, 100)]
 @pytest.mark.parametrize("L,R", SIZES)
 @pytest.mark.parametrize("Hq,Hkv,d", SHAPES)
 def test_against_the_oracle(Hq, Hkv, d, L, R):
+    assert H.in_one_launch(Hq, Hkv, d, R, L)
     qi, q, kc, vc, kn, vn = inputs(Hq, Hkv, d, L, R, seed=L + Hq)
     want, want_lse = orc.sparse_prefill_attn(q, qi, kc, vc, kn, vn)
     k_eff, v_eff = orc.kv_scatter(qi, kn, vn, kc, vc)
@@ -58,13 +59,16 @@ def test_against_the_oracle(Hq, Hkv, d, L, R):
         assert np.array_equal(k, k_eff if writeback else kv[0]) and np.array_equal(v, v_eff if writeback else kv[1])
 
 
-# Either side of the rule's lines for 256 compute units: 32-column tiles (R x 32 heads / 32, or 16 heads at head_dim 64) and positions; and of the
-# line between 16 and 32 columns per workgroup.
+# Either side of the rule's lines for 256 compute units: 32-column tiles (R x 32 heads / 32, R x 16 heads / 32 at head_dim 64, R x 7 / 32 for each of 4 KV heads) and
+# positions; and of the line between 16 and 32 columns per workgroup.
 @pytest.mark.parametrize("at_end", [False, True])
-@pytest.mark.parametrize("Hq,Hkv,d,L,R", [(32, 8, 128, 700, 128), (32, 8, 128, 700, 129), (32, 8, 128, 1024, 512), (32, 8, 128, 1024, 513), (32, 8, 128, 1025, 384),
-                                          (32, 8, 128, 1792, 384), (32, 8, 128, 1793, 256), (32, 8, 128, 1793, 257), (28, 4, 128, 6144, 288), (32, 8, 128, 6145, 20),
-                                          (16, 8, 64, 4096, 768), (16, 8, 64, 4097, 512)])
-def test_both_sides_of_the_rule(Hq, Hkv, d, L, R, at_end):
+@pytest.mark.parametrize("Hq,Hkv,d,L,R,one", [(32, 8, 128, 700, 128, True), (32, 8, 128, 700, 129, True), (32, 8, 128, 1024, 512, True), (32, 8, 128, 1024, 513, False),
+                                              (32, 8, 128, 1025, 384, True), (32, 8, 128, 1025, 385, False), (32, 8, 128, 1792, 384, True), (32, 8, 128, 1792, 385, False),
+                                              (32, 8, 128, 1793, 256, True), (32, 8, 128, 1793, 257, False), (28, 4, 128, 6144, 288, True), (28, 4, 128, 6144, 293, False),
+                                              (32, 8, 128, 6144, 20, True), (32, 8, 128, 6145, 20, False), (16, 8, 64, 4096, 768, True), (16, 8, 64, 4096, 769, False),
+                                              (16, 8, 64, 4097, 512, True), (16, 8, 64, 4097, 513, False)])
+def test_both_sides_of_the_rule(Hq, Hkv, d, L, R, one, at_end):
+    assert H.in_one_launch(Hq, Hkv, d, R, L) == one
     args = inputs(Hq, Hkv, d, L, R, seed=L + R, at_end=at_end)
     got, lse, _, _ = attend(Hq, Hkv, d, *args, B.FR_ATTN_SPLIT_AUTO)
     tiled, tiled_lse, _, _ = attend(Hq, Hkv, d, *args, B.FR_ATTN_SPLIT_OFF)
@@ -86,16 +90,28 @@ def test_values_that_are_not_finite_reach_later_rows_only(case_args):
     unfilled.test_values_that_are_not_finite_reach_later_rows_only(case_args, AUTO)
 
 
-def test_running_maximum():
-    """Logits that rise by 2^20 along the prompt: every block raises the maximum of all columns."""
-    qi, q, kc, vc, kn, vn = inputs(8, 2, 128, 600, 90, seed=5)
-    ramp = np.linspace(0.0, 16.0, 600, dtype=np.float32)
+@pytest.mark.parametrize("rise", [16.0, 320.0])
+@pytest.mark.parametrize("Hq,Hkv,d", [(8, 2, 128), (7, 1, 128), (4, 2, 64)])
+def test_rising_references(Hq, Hkv, d, rise):
+    """Logits that rise along the prompt.  A reference goes up where a lane's eight weights of a block, against the columns' maximum over keys 0..31 or what they have been
+    raised to, sum to more than 2^10: with a rise of 320 every block of every wave does that for all of its columns (its largest logit is more than 2^11 above that
+    of any block in front), with 16, 2^20 to 2^28 over the prompt, only some of the later ones do."""
+    L = 600
+    qi, q, kc, vc, kn, vn = inputs(Hq, Hkv, d, L, 90, seed=5)
+    assert H.in_one_launch(Hq, Hkv, d, len(qi), L)
+    ramp = np.linspace(0.0, rise, L, dtype=np.float32)
     q[:, :, 0], kc[:, :, 0], kn[:, :, 0] = 10.0, ramp[:, None], ramp[qi][:, None]
     q, kc, kn = (synth.round_to_storage(x, "bf16") for x in (q, kc, kn))
-    got, lse, _, _ = attend(8, 2, 128, qi, q, kc, vc, kn, vn, B.FR_ATTN_SPLIT_AUTO)
+    if rise == 320.0:
+        k_eff, _ = orc.kv_scatter(qi, kn, vn, kc, vc)
+        s = np.einsum("rgqd,jgd->rgqj", q.reshape(len(qi), Hkv, Hq // Hkv, d), k_eff) / np.sqrt(d) * np.log2(np.e)
+        blocks = s[..., :L // 32 * 32].reshape(*s.shape[:3], -1, 32).max(axis=-1)
+        assert np.min(np.diff(blocks)) > 11
+    got, lse, _, _ = attend(Hq, Hkv, d, qi, q, kc, vc, kn, vn, B.FR_ATTN_SPLIT_AUTO)
     want, want_lse = orc.sparse_prefill_attn(q, qi, kc, vc, kn, vn)
-    assert H.max_rel_err(got, want) <= TOL[False]
-    assert np.max(np.abs(lse - want_lse)) <= 1e-4
+    # a logit of up to 577 in base 2 is rounded to 2^-24 of that, 3.4e-5, and its weight is off by as much; the sum's logarithm by three of them
+    assert H.max_rel_err(got, want) <= TOL[d == 64 or Hq // Hkv == 7] + 2.0 ** -14
+    assert np.max(np.abs(lse - want_lse)) <= (1e-4 if rise == 16.0 else 2e-4)
 
 
 # Sums and selection in one launch: up to 1024 tokens and 64 partial sums (KV heads x column ranges); quads of tokens with a rest, fewer than four tokens
@@ -105,7 +121,8 @@ def test_selection_beside_the_sums(Hq, Hkv, d, dt, nq, L):
     shape = synth.LayerShape(n_q_heads=Hq, n_kv_heads=Hkv, head_dim=d, dtype=dt, rope_base=10000.0)
     w = synth.config_small_bf16(seed=L, chunk_lens=tuple(len(x) for x in np.array_split(np.arange(L), min(4, L))), nq=nq, shape=shape)
     k = synth.round_to_storage(w.k_cached, dt)
-    k[L // 2:] = k[:L - L // 2] if L % 2 == 0 else k[L // 2:]     # even: equal scores in pairs of chunks
+    if L % 2 == 0:
+        k[L // 2:] = k[:L // 2]     # equal scores in pairs of chunks
     want = orc.critical_scores(w.q_question, k, w.chunk_offsets)
     ctx = H.make_ctx(shape, w.L, w.n_chunks, nq)
     q, kd = H.dev(w.q_question, dt), H.dev(k, dt)
@@ -119,4 +136,37 @@ def test_selection_beside_the_sums(Hq, Hkv, d, dt, nq, L):
         assert np.array_equal(qi.cpu().numpy(), again.cpu().numpy())
         ctx.fr_score_select(q, nq, kd, w.chunk_offsets, take, B.FR_NORM_PER_CHUNK, None, again)
         assert np.array_equal(qi.cpu().numpy(), again.cpu().numpy())
+    ctx.close()
+
+
+# Scores of few values: keys of zeros (every score of chunks of equal length the same, the selection's first bit is none) and two or seven different keys in turn; chunks
+# of garbage (NaN: all scores of the chunk).  Up to 512 tokens one wave selects by ballots, up to 1024 the workgroup by a histogram; fr_select_topk the workgroup.
+@pytest.mark.parametrize("kind", ["one", "two", "seven", "garbage"])
+@pytest.mark.parametrize("L", [64, 65, 300, 511, 512, 513, 700, 1021, 1024])
+def test_tied_scores_beside_the_sums(L, kind):
+    Hq, Hkv, d, nq, chunks = 8, 2, 128, 9, 4
+    shape = synth.LayerShape(n_q_heads=Hq, n_kv_heads=Hkv, head_dim=d, dtype="bf16", rope_base=10000.0)
+    rng = np.random.default_rng(L)
+    bf = lambda *s: synth.round_to_storage(rng.standard_normal(s).astype(np.float32), "bf16")  # noqa: E731
+    some = bf({"one": 1, "two": 2, "seven": 7, "garbage": 7}[kind], Hkv, d) * (0.0 if kind == "one" else 1.0)
+    k = some[rng.integers(0, len(some), size=L)]
+    cut = np.array([len(x) for x in np.array_split(np.arange(L), chunks)])
+    offs = np.concatenate([[0], np.cumsum(cut)]).astype(np.int32)
+    if kind == "garbage":
+        k[int(offs[1]) + 3, 1, 5], k[int(offs[3]) + 1, 0, 0] = np.nan, np.inf
+    ctx = H.make_ctx(shape, L + nq, chunks, nq)
+    q, kd = H.dev(bf(nq, Hq, d), "bf16"), H.dev(k, "bf16")
+    scores = torch.full((L,), -7.0, dtype=torch.float32, device="cuda")
+    for take in sorted({1, 2, L // 7, L // 2, L - 1, L}):
+        got, again = (torch.full((take + nq,), -1, dtype=torch.int32, device="cuda") for _ in range(2))
+        ctx.fr_score_select(q, nq, kd, offs, take, B.FR_NORM_PER_CHUNK, scores, got)
+        ctx.fr_select_topk(scores, L, take, nq, again)
+        torch.cuda.synchronize()
+        s = scores.cpu().numpy()
+        if kind == "garbage":
+            assert np.isnan(s).sum() == cut[1] + cut[3]
+            assert torch.equal(got, again)
+        else:
+            assert len(np.unique(s)) <= chunks * len(some)            # (every chunk has a normaliser of its own)
+            assert np.array_equal(got.cpu().numpy(), orc.select_q_index(s, take, nq))
     ctx.close()

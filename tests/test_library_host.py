@@ -9,6 +9,7 @@ import pytest
 
 from oracle import fusionrag_oracle as orc
 from paper_2601_12904_amd import binding as B
+from tests import harness as H
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -234,6 +235,18 @@ def test_shared_score_select_argument_errors():
     if not torch.cuda.is_available():
         expect(B.FR_ERR_DEVICE, call32)
     c32.close()
+
+
+def test_rule_of_short_prompts():
+    """Both sides of every line of the rule that takes a call to the one-launch attention, for 256 compute units: 32-column tiles of all KV heads up to two
+    per unit (1024 positions), one and a half (1792; 4096 at head_dim 64), one (6144); up to 64 heads per KV head; bf16."""
+    for Hq, Hkv, d, R, L in ((32, 8, 128, 512, 1024), (32, 8, 128, 384, 1025), (32, 8, 128, 384, 1792), (32, 8, 128, 256, 1793), (32, 8, 128, 256, 6144),
+                             (16, 8, 64, 768, 4096), (16, 8, 64, 512, 4097), (28, 4, 128, 292, 6144), (64, 1, 128, 100, 530)):
+        assert H.in_one_launch(Hq, Hkv, d, R, L, 256) and not H.in_one_launch(Hq, Hkv, d, R + 1 if Hq != 64 else R, L if Hq != 64 else 6145, 256)
+    for L, longer in ((1024, 1025), (1792, 1793), (6144, 6145)):
+        R = {1024: 512, 1792: 384, 6144: 256}[L]
+        assert H.in_one_launch(32, 8, 128, R, L, 256) and not H.in_one_launch(32, 8, 128, R, longer, 256)
+    assert not H.in_one_launch(65, 1, 128, 1, 10, 256) and not H.in_one_launch(4, 4, 64, 1, 10, 256, B.FR_F32)
 
 
 def test_bench_work_counts():
