@@ -1350,9 +1350,11 @@ void launch_tile_loop(const AttnBatch& batch, dim3 grid, float* partials, int n_
 // Below half a workgroup per compute unit more parts pay until there is about one piece per compute unit (question-only prefill, 64
 // items: 446 us whole, 302, 253, 244, 277, 268 in two, three, four, six, eight parts, with the loop of four waves); in between two parts stay best.
 // The smallest piece: four tiles (32 / 8 heads, 24 items of 8 tiles 24.4 us whole, 23.6, 22.8, 23.2, 24.1 in two to five parts; 40 of 5 tiles 20.4 whole,
-// 23.0 in two), two where there are next to no items or the weights are split (28 / 4 heads, 20 items of 8 tiles 33.7 whole, 29.6, 29.0, 27.7, 28.7 in two to
-// five parts); more than a quarter of a workgroup per compute unit and fewer than 16 tiles stay whole (64 items of 8 tiles 23.7 whole, 25.3 and 27.1 in
-// two and four parts).
+// 23.0 in two), two where there are next to no items or the weights are split; more than a quarter of a workgroup per compute unit and fewer than 16 tiles stay whole (64
+// items of 8 tiles 23.7 whole, 25.3 and 27.1 in two and four parts).  Of short prompts those over a chunk store come here, and over caches of their own those with too many
+// columns for one launch (attn_direct_pays).  Split weights, which read no store, have 65 items and more then, and stay whole up to seven tiles (whole : as many parts as
+// there are units for, 55 calls: 100 items of 4 tiles 25.6 : 33.0, 67 of 6 29.4 : 33.8, 80 of 6 tiles of head_dim 64 23.7 : 25.8, 85 of 7 31.6 : 35.0, 96 of 8 33.9 : 34.0,
+// 80 of 9 36.4 : 34.1, 76 of 12 42.4 : 36.6).
 template <int D, bool SPLIT>
 int choose_parts(int split_mode, int items, int n_img_tiles, int n_cu, size_t part_bytes, size_t partials_bytes) {
     int parts = 1;
@@ -1362,7 +1364,7 @@ int choose_parts(int split_mode, int items, int n_img_tiles, int n_cu, size_t pa
         if (2 * items <= n_cu) {
             int pieces;
             if (SPLIT)
-                pieces = tiles == 4 || tiles == 5 ? tiles : (tiles + 1) / 2;   // (a tile each, in one round trip: 28 / 4 heads, 8 items of 5 tiles 24.9 us in three parts, 24.5 in five)
+                pieces = tiles < 8 ? 1 : (tiles + 1) / 2;
             else if (32 * items <= n_cu)
                 pieces = tiles < 5 ? 1 : (tiles + 1) / 2;
             else if (tiles < 6 || (tiles < 16 && 4 * items > n_cu))

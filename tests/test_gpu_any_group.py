@@ -160,6 +160,55 @@ def test_items_on_both_sides_of_the_split_rules(Hq, Hkv, d, lens):
     ctx.close()
 
 
+# Items of split weights in more than two parts: few rows of a prompt beyond the positions of the one-launch kernel.  Items (row tiles x KV heads) of 256 compute
+# units: 5 and 4 in eight parts, 32 in eight, 48 in five, 68 in three, 112 in two (two and more by counts), 16 of head_dim 64 in eight.
+@pytest.mark.parametrize("Hq,Hkv,d,rows,parts", [(7, 1, 128, 150, 8), (16, 1, 128, 90, 8), (28, 4, 128, 280, 8), (28, 4, 128, 400, 5), (28, 4, 128, 600, 3), (28, 4, 128, 1000, 2),
+                                                 (4, 2, 64, 1000, 8), (3, 1, 128, 84, 8)])
+def test_items_of_split_weights_in_several_parts(Hq, Hkv, d, rows, parts):
+    """Against the oracle, and against whole items: the parts keep 32 bits.  fp32 sums of n = 6200 weights differ by some 2^-24 sqrt(n) = 4.7e-6 of an
+    element, which moves 2^-8 relative (one bf16 unit) in a share of 4.7e-6 / 2^-8 = 1.2e-3 of the elements: sqrt(1.2e-3) 2^-8 = 1.4e-4 of the norm."""
+    w = workload(Hq, Hkv, d, (3000, 3140), 60)
+    qi = np.concatenate([np.sort(np.random.default_rng(rows).choice(w.L_ctx, size=rows - w.nq, replace=False)), np.arange(w.L_ctx, w.L)])
+    items = -(-rows // (4 * (64 // (Hq // Hkv)))) * Hkv
+    assert not one_launch(w, qi) and min(8, torch.cuda.get_device_properties(0).multi_processor_count // items) == parts
+    k_cache, v_cache = assembled_cache(w, w.k_cached)
+    outs = []
+    for split in (B.FR_ATTN_SPLIT_OFF, B.FR_ATTN_SPLIT_AUTO):
+        ctx = H.make_ctx(w.shape, w.L, w.n_chunks, w.nq)
+        ctx.fr_set_option(B.FR_OPT_ATTN_SPLIT, split)
+        outs.append(run_attention(ctx, w, qi, k_cache, v_cache))
+        ctx.close()
+    some = np.unique(np.concatenate([np.arange(0, rows, 5), [rows - 1]]))
+    want, want_lse = orc.sparse_prefill_attn(w.q_full[qi], qi, k_cache, v_cache, w.k_full[qi], w.v_full[qi], rows=some)
+    for got, lse in outs:
+        assert H.max_rel_err(got[some], want) <= OUT_TOL
+        assert np.max(np.abs(lse[some] - want_lse)) <= 1e-4
+    off = np.linalg.norm(outs[1][0] - outs[0][0]) / np.linalg.norm(outs[0][0])
+    assert 0.0 < off <= 2e-4 or np.any(outs[1][1] != outs[0][1])      # (the order of the sums shows that there are parts)
+    assert off <= 2e-4
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,total,parts", [(64, 1, 128, 448, 1), (64, 1, 128, 449, 2), (60, 20, 64, 448, 1), (60, 20, 64, 460, 2)])
+def test_where_items_of_split_weights_stay_whole(Hq, Hkv, d, total, parts):
+    """More columns than one launch takes, up to 128 items (row tiles of 4 and of 84 rows x KV heads): seven key tiles stay whole, bit for bit the result with the cutting off, eight are
+    cut in two."""
+    w = workload(Hq, Hkv, d, (total - 10,), 10)
+    qi = np.arange(total) if Hkv == 1 else np.sort(np.random.default_rng(total).choice(total, 400, replace=False))
+    items = -(-len(qi) // (4 * (64 // (Hq // Hkv)))) * Hkv
+    assert not one_launch(w, qi) and 64 < items <= 128 and -(-total // 64) == 6 + parts
+    outs = []
+    for split in (B.FR_ATTN_SPLIT_OFF, B.FR_ATTN_SPLIT_AUTO):
+        ctx = H.make_ctx(w.shape, w.L, w.n_chunks, w.nq)
+        ctx.fr_set_option(B.FR_OPT_ATTN_SPLIT, split)
+        outs.append(run_attention(ctx, w, qi, w.k_full, w.v_full))
+        ctx.close()
+    assert np.any(outs[1][1] != outs[0][1]) == (parts == 2)
+    assert np.linalg.norm(outs[1][0] - outs[0][0]) <= (0.0 if parts == 1 else 1.2e-4) * np.linalg.norm(outs[0][0])
+    some = np.arange(0, len(qi), 7)
+    want, _ = orc.sparse_prefill_attn(w.q_full[qi], qi, w.k_full, w.v_full, w.k_full[qi], w.v_full[qi], rows=some)
+    assert H.max_rel_err(outs[1][0][some], want) <= OUT_TOL
+
+
 # Key tiles are 64 keys in two halves, one per wave of a row group, and the tile loop runs three tiles ahead: prompts of one half tile to
 # five tiles, whole and in parts of one tile and of none (by the rule: over a store), and the one-launch kernel (AUTO).  (bf16 weights: the tolerance of the other
 # tests of those shapes.)
