@@ -98,7 +98,8 @@ int64_t fr_workspace_bytes(const fr_ctx* ctx);
  * FR_OPT_ATTN_SPLIT: AUTO (default) deals the key range of every (row tile, KV head) to two or more workgroups when
  * there are too few of those to fill the chip (few recomputed rows, e.g. question-only prefill or the offline stage of
  * eq. 10); OFF: never; ON: two workgroups each whenever the partial results fit the workspace.  (Under AUTO of both
- * options short bf16 prompts run in one launch of another kernel, with a running maximum.)  Same results up to the
+ * options short bf16 prompts run in one launch of another kernel, whose exponent references are the same maxima over keys 0..31, raised by whole
+ * powers of two where a block's weights leave them far behind.)  Same results up to the
  * summation order and, for up to four parts of a prompt of 32 key tiles of 64 and more at group sizes 1, 2, 4, 8 and
  * head_dim 128, the partial sums' storage format (half precision after a per-column power-of-two scale: 11
  * significant bits of a column's largest partial value, finer than the bf16 output); all other parts keep 32 bits.

@@ -34,8 +34,8 @@
 // Measured (16 x 1024 keys, 512 question tokens, 32/8 heads, bf16, back to back, with the reduction): 83 us, of which 5 load the keys and a step of 16 columns
 // takes 0.99; with keys loaded straight into fragment registers (12 us: see there), the order of a step's instructions left to the compiler (1.19 us a step) and a
 // spilled index that was waited for in the loop together with the copies 96; the two passes of k_score_mfma.hip 66 + 62 + 5 us.  3 x 900 keys, 100 question tokens 20.3 -> 15.7.  28/4
-// heads 90 -> 79; fp32, 4 x 128 keys, 32 question tokens: 7 us.  Vector instructions fill 80 % of the issue cycles: four per logit are the sums' own, one more per logit is
-// the references, the sums' exchange and the fragments' addresses.
+// heads 90 -> 79; fp32, 4 x 128 keys, 32 question tokens: 7 us.  Vector instructions are issued in 70 % of the kernel's cycles (the matrix pipes work in 37 %): four per logit are the sums' own, one more
+// per logit is the references, the sums' exchange and the fragments' addresses.
 // All sums run in a fixed order: the scores are reproducible bit for bit.
 #include "fr_internal.hpp"
 #include "k_rotate.hpp"

@@ -11,7 +11,7 @@
 // most exponent bits agree), which would pile a plain histogram onto one or two bins; the digits are therefore
 // taken from key - min(key), starting at the highest bit in which the largest and the smallest key differ.  Even so most scores lie near the smallest
 // one: with 256 bins the adds of a wave queued up behind one LDS word, and every pass costs its barriers and scans (four
-// passes of 8 bits: 9.6 / 19.5 / 33.0 us at 880 / 16384 / 32768 scores of a prompt, with this 8.1 / 14.7 / 25.2; what else was taken out stands at select_in_workgroup).
+// passes of 8 bits 9.6 / 19.5 / 33.0 us at 880 / 16384 / 32768 scores of a prompt, one of 12 bits 8.1 / 14.7 / 25.2, and with what stands at select_in_workgroup 4.7 / 9.7 / 18.0).
 #include "fr_internal.hpp"
 
 #include <algorithm>
@@ -92,7 +92,7 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t ballot) {   // set bits
 // consecutive tokens base + 256 i + 4 lane .. + 3, so (i, lane, e) order is index order (one CU's loads of 4 bytes a lane come at a quarter of the rate).  A
 // lane whose four tokens pass the end loads the last four, of which those before its own are another lane's.
 // Every thread keeps its PER keys in registers (1 <= n <= SEL_THREADS * PER, k >= 1; all threads of the workgroup).
-// Against loads of one score, reductions and scans by LDS permutes and the waves' totals read one after the other: 16384 scores 12.8 -> 9.8 us, 32768 23.3 -> 18.1, 4000 8.4 -> 4.7.
+// Against loads of one score, reductions and scans by LDS permutes and the waves' totals read one after the other: 16384 scores 13.0 -> 9.7 us, 32768 23.5 -> 18.0, 4000 8.7 -> 5.0.
 // (A launch of one wave, as select_in_wave below, 4.6 to 10 us at 128 to 1024 scores, 15 with ties; this one 4.5.)
 template <int PER>
 __device__ __forceinline__ void select_in_workgroup(const float* scores, int n, int64_t k, int32_t* __restrict__ out) {
